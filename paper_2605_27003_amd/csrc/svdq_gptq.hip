@@ -57,204 +57,368 @@ void hessian_kernel(const uint16_t* __restrict__ x, int64_t ldx, const float* __
 }
 
 // ---- preparation: binary64 copies, dead channels, damping with the diagonal summed in index order
-__global__ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, double damp, int N, int K,
-                               double* __restrict__ A, double* __restrict__ W) {
-    const size_t stride = (size_t)gridDim.x * blockDim.x, t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    __shared__ double add;
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int k = 0; k < K; ++k) {
-            const double d = H[(size_t)k * K + k];
-            s = __dadd_rn(s, d == 0.0 ? 1.0 : d);
+constexpr int DIAG_CHUNK = 4096;
+__global__ __launch_bounds__(256)
+void diag_sum_kernel(const double* __restrict__ H, double damp, int K, double* __restrict__ add) {
+    __shared__ double dg[DIAG_CHUNK];
+    double s = 0.0;
+    for (int k0 = 0; k0 < K; k0 += DIAG_CHUNK) {
+        const int n = min(DIAG_CHUNK, K - k0);
+        for (int k = threadIdx.x; k < n; k += 256) {
+            const double d = H[(size_t)(k0 + k) * K + k0 + k];
+            dg[k] = d == 0.0 ? 1.0 : d;
         }
-        add = __dmul_rn(damp, __ddiv_rn(s, (double)K));
+        __syncthreads();
+        if (threadIdx.x == 0)
+#pragma unroll 16
+            for (int k = 0; k < n; ++k) s = __dadd_rn(s, dg[k]);       // one chain of additions: the definition's order
+        __syncthreads();
     }
-    __syncthreads();
-    for (size_t e = t0; e < (size_t)K * K; e += stride) {
-        const int a = (int)(e / K), b = (int)(e - (size_t)a * K);
-        double v = H[e];
-        if (a == b) v = __dadd_rn(v == 0.0 ? 1.0 : v, add);
-        A[e] = v;
-    }
-    for (size_t e = t0; e < (size_t)K * N; e += stride) {
-        const int k = (int)(e / N);
-        W[e] = (H[(size_t)k * K + k] == 0.0) ? 0.0 : (double)R[e];
-    }
+    if (threadIdx.x == 0) *add = __dmul_rn(damp, __ddiv_rn(s, (double)K));
+}
+__global__ __launch_bounds__(256)
+void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, const double* __restrict__ add, int N, int K,
+                    double* __restrict__ A, double* __restrict__ W) {
+    const int k = blockIdx.x;                                          // one row of H and of R
+    const double d = H[(size_t)k * K + k], dd = __dadd_rn(d == 0.0 ? 1.0 : d, *add);
+    for (int j = threadIdx.x; j < K; j += 256) A[(size_t)k * K + j] = (j == k) ? dd : H[(size_t)k * K + j];
+    for (int n = threadIdx.x; n < N; n += 256) W[(size_t)k * N + n] = (d == 0.0) ? 0.0 : (double)R[(size_t)k * N + n];
 }
 
 // ---- Panel-blocked form of both eliminations.  Every element of H^-1 (and of W) must receive, in the order of the
 // pivots, one rounded product and one rounded subtraction per pivot: that sequence per element is the definition, and
-// it does not say WHEN an element is touched.  Pivots are taken in panels of PB = 64.  Inside a panel only the panel's
-// own rows and columns (2 x 64 x K elements) are brought up to date after every pivot, by small kernels, and each
-// pivot's column (as it stood when the pivot was taken) and scaled row are saved; everything else receives its 64
-// updates in one pass at the end of the panel from the saved columns and rows, in pivot order, with the same two
-// rounded operations per update.  Bit-identical to the pivot-by-pivot form; the K x K matrix crosses HBM once per
-// panel instead of once per pivot.
+// it does not say WHEN an element is touched.  Pivots are taken in panels of PB = 64, two launches per panel:
+//   panel kernel   brings the panel's own rows and columns (2 x 64 x K elements, for the weights 64 x N) through all 64
+//                  pivots.  A row outside the panel only needs the panel's diagonal block as it stood at each pivot,
+//                  and a column likewise, so rows and columns are independent of each other: a block takes 64 of them
+//                  and first runs the 64 x 64 diagonal block itself (every block repeats that; it is a chain of 64
+//                  dependent steps, and a launch of its own would cost as much again).  The pivot's column and scaled
+//                  row, as they stood when the pivot was taken, are saved.
+//   rank update    everything else receives its 64 updates in one pass from the saved columns and rows, in pivot
+//                  order, with the same two rounded operations per update.
+// Bit-identical to the pivot-by-pivot form.  K = N = 5120: one launch per pivot and step (25 600 launches) took 112 ms,
+// of which the rank updates were 31.
 constexpr int PB = 64;
+constexpr int PTHREADS = 1024;           // 64 vectors x 16 lanes
 
-// X[a][b] <- (..((X[a][b] - L[a][0] R[0][b]) - L[a][1] R[1][b]).. - L[a][PB-1] R[PB-1][b]) for a in [a0, a1),
-// b in [b0, b1), skipping the 64-aligned index block [skip, skip + PB) in both directions (skip < 0: none).
-// L is [rows][PB], R is [PB][ldr].  a0, a1, b0 multiples of 64.  One 64 x 64 tile per block, 4 x 4 elements per thread.
-__global__ __launch_bounds__(256)
-void seq_rank_update_kernel(double* __restrict__ X, size_t ldx, int a0, int a1, int b0, int b1, int skip,
-                            const double* __restrict__ L, const double* __restrict__ R, size_t ldr) {
-    __shared__ double Lt[PB][64];       // Lt[q][row]
-    __shared__ double Rs[PB][64];       // Rs[q][col]
-    const int ta = a0 + blockIdx.y * 64, tb = b0 + blockIdx.x * 64;
-    if (ta == skip || tb == skip) return;
-    for (int e = threadIdx.x; e < 64 * PB; e += 256) {
-        const int rr = e / PB, q = e - rr * PB;
-        Lt[q][rr] = (ta + rr < a1) ? L[(size_t)(ta + rr) * PB + q] : 0.0;
-        const int qq = e / 64, c = e - qq * 64;
-        Rs[qq][c] = (tb + c < b1) ? R[(size_t)qq * ldr + tb + c] : 0.0;
+// ---- A vector of 64 elements (one row or column of the panel) lives in 16 lanes (a DPP row), four elements each.
+// Pivot 4 it + k is always element k of the row's lane 0: after every four pivots the vectors turn by one lane, so the
+// loop body needs no lane index of its own.  sl = (lane + it) % 16 is the place of a lane's four elements.
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+__device__ __forceinline__ double row_first(double v) { return dpp64<0x150>(v); }             // row_newbcast:0
+__device__ __forceinline__ double row_turn(double v) { return dpp64<0x120 + 15>(v); }         // row_ror:15: from lane + 1
+
+struct PanelTables {
+    double (*R)[PB];       // [q][t]: row q of the diagonal block divided by its pivot, when pivot q was taken
+    double (*C)[PB];       // [q][t]: column q
+    double* d;             // [q]: pivot
+};
+
+// The diagonal block through its 64 pivots (all 1024 threads: row t = tid / 16).  INV: in-place Gauss-Jordan inverse
+// (see below); otherwise elimination of the rows and columns behind the pivot only.  Leaves the tables; the block's
+// final values are in x.
+template <bool INV>
+__device__ __forceinline__ void panel_diagonal(double (&x)[4], const PanelTables& tb) {
+    const int t = threadIdx.x >> 4, pos = threadIdx.x & 15;
+    for (int it = 0; it < 16; ++it) {
+        const int sl = (pos + it) & 15;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int q = 4 * it + k;
+            const double c = row_first(x[k]);
+            double r[4];
+            if (t == q) {                                 // c is the pivot
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    r[j] = __ddiv_rn(x[j], c);
+                    tb.R[q][4 * sl + j] = r[j];
+                }
+                if (pos == 0) tb.d[q] = c;
+            }
+            if (pos == 0) tb.C[q][t] = c;
+            __syncthreads();
+            const double d = tb.d[q];
+            const bool own = pos == 0;                    // element k of this lane is column q
+            if (INV) {
+                const double e = __ddiv_rn(t == q ? 1.0 : -c, d);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double rj = tb.R[q][4 * sl + j];
+                    const double v = (t == q) ? rj : __dsub_rn(x[j], __dmul_rn(c, rj));
+                    x[j] = (own && j == k) ? e : v;
+                }
+            } else if (t > q) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double v = __dsub_rn(x[j], __dmul_rn(c, tb.R[q][4 * sl + j]));
+                    x[j] = (4 * sl + j > q) ? v : x[j];
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
     }
     __syncthreads();
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    double v[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int a = ta + ty * 4 + i, c = tb + tx * 4 + j;
-            v[i][j] = (a < a1 && c < b1) ? X[(size_t)a * ldx + c] : 0.0;
-        }
-    for (int q = 0; q < PB; ++q) {
-        double l[4], r[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) l[i] = Lt[q][ty * 4 + i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r[j] = Rs[q][tx * 4 + j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[i][j] = __dsub_rn(v[i][j], __dmul_rn(l[i], r[j]));
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int a = ta + ty * 4 + i, c = tb + tx * 4 + j;
-            if (a < a1 && c < b1) X[(size_t)a * ldx + c] = v[i][j];
-        }
 }
+
+// Where panel index b (64-blocks outside the panel's own) lies.
+__device__ __forceinline__ int outside_block(int b, int pb) { return b < pb ? b : b + 1; }
 
 // ---- in-place Gauss-Jordan inverse without pivoting.  Step p: d = A[p][p], col = A[:, p], row = A[p, :] / d;
 // A[a][j] -= col[a] row[j] elsewhere, A[p][j] = row[j], A[a][p] = -col[a] / d, A[p][p] = 1 / d.
-// gj_pivot: save col and row of pivot p (panel starting at p0) as they stand.
-__global__ void gj_pivot_kernel(const double* __restrict__ A, int K, int p, int p0, double* __restrict__ C, double* __restrict__ Rw) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= K) return;
-    const double d = A[(size_t)p * K + p];
-    C[(size_t)i * PB + (p - p0)] = A[(size_t)i * K + p];
-    Rw[(size_t)(p - p0) * K + i] = __ddiv_rn(A[(size_t)p * K + i], d);
-}
-// gj_panel: apply step p to the panel's columns (all rows) and the panel's rows (all other columns)
-__global__ void gj_panel_kernel(double* __restrict__ A, int K, int p, int p0, const double* __restrict__ C, const double* __restrict__ Rw) {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    const int q = p - p0;
-    const double d = C[(size_t)p * PB + q];
-    const size_t n1 = (size_t)K * PB, total = n1 + (size_t)PB * (K - PB);
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-        int a, j;
-        if (e < n1) {                                   // the panel's columns
-            a = (int)(e / PB);
-            j = p0 + (int)(e - (size_t)a * PB);
-        } else {                                        // the panel's rows, columns outside the panel
-            const size_t f = e - n1;
-            a = p0 + (int)(f / (K - PB));
-            j = (int)(f - (size_t)(a - p0) * (K - PB));
-            if (j >= p0) j += PB;
+// Blocks 0 .. nb - 1: 64 rows outside the panel; nb .. 2 nb - 1: 64 columns outside it; the last block only runs the
+// diagonal block and writes it to Dnew (the other blocks read it from A meanwhile; the rank update puts it in place).
+// Saves LT[q][a] = column of pivot p0 + q, Rr[q][j] = its scaled row.
+__global__ __launch_bounds__(PTHREADS)
+void gj_panel_kernel(double* __restrict__ A, int K, int p0, double* __restrict__ LT, double* __restrict__ Rr,
+                     double* __restrict__ Dnew) {
+    __shared__ __attribute__((aligned(16))) double Rt[PB][PB], Ct[PB][PB], dt[PB];
+    const PanelTables tb{Rt, Ct, dt};
+    const int nb = K / PB - 1, pb = p0 / PB;
+    const int v = threadIdx.x >> 4, pos = threadIdx.x & 15;
+    const int role = ((int)blockIdx.x < nb) ? 0 : ((int)blockIdx.x < 2 * nb) ? 1 : 2;
+    const int idx = outside_block((int)blockIdx.x - role * nb, pb) * PB + v;     // this vector's row or column
+    double x[4], dg[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        dg[j] = A[(size_t)(p0 + v) * K + p0 + 4 * pos + j];
+        x[j] = 0.0;
+        if (role == 0) x[j] = A[(size_t)idx * K + p0 + 4 * pos + j];
+        if (role == 1) x[j] = A[(size_t)(p0 + 4 * pos + j) * K + idx];
+    }
+    panel_diagonal<true>(dg, tb);
+    if (role == 2) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Dnew[v * PB + 4 * pos + j] = dg[j];
+        return;
+    }
+    for (int it = 0; it < 16; ++it) {
+        const int sl = (pos + it) & 15;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int q = 4 * it + k;
+            const double c = row_first(x[k]), d = dt[q];
+            const double e = __ddiv_rn(role == 0 ? -c : c, d);
+            if (role == 0) {
+                if (pos == 0) LT[(size_t)q * K + idx] = c;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[j] = __dsub_rn(x[j], __dmul_rn(c, Rt[q][4 * sl + j]));
+            } else {
+                if (pos == 0) Rr[(size_t)q * K + idx] = e;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[j] = __dsub_rn(x[j], __dmul_rn(Ct[q][4 * sl + j], e));
+            }
+            x[k] = (pos == 0) ? e : x[k];
         }
-        const size_t at = (size_t)a * K + j;
-        double v;
-        if (a == p) v = (j == p) ? __ddiv_rn(1.0, d) : Rw[(size_t)q * K + j];
-        else if (j == p) v = __ddiv_rn(-C[(size_t)a * PB + q], d);
-        else v = __dsub_rn(A[at], __dmul_rn(C[(size_t)a * PB + q], Rw[(size_t)q * K + j]));
-        A[at] = v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (role == 0) A[(size_t)idx * K + p0 + 4 * pos + j] = x[j];
+        else A[(size_t)(p0 + 4 * pos + j) * K + idx] = x[j];
     }
 }
 
-// ---- column i: scale at a group start, code, error (kept in Err[i - i0][:] for the deferred spreading)
-__global__ void column_kernel(const double* __restrict__ W, const double* __restrict__ Hinv, int N, int K, int i, int i0,
-                              float* __restrict__ scur, float* __restrict__ sw, int8_t* __restrict__ codes,
-                              double* __restrict__ Err) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    float s;
-    if ((i & 63) == 0) {
-        double a = 0.0;
-        for (int t = 0; t < 64; ++t) a = fmax(a, fabs(W[(size_t)(i + t) * N + n]));
-        s = __fdiv_rn((float)a, 7.0f);
-        scur[n] = s;
-        sw[(size_t)(i >> 6) * N + n] = s;
-    } else {
-        s = scur[n];
+// ---- one panel of the visit: indices i0 .. i0 + 63 = one 64-group.  For each index i: code and error of every
+// channel, the error spread over the panel's later weights, index i eliminated from H^-1 (A[a][b] -= A[a][i] (A[i][b] / d)
+// for a, b > i).  Blocks 0 .. nr - 1: 64 rows of A behind the panel; nr .. 2 nr - 1: 64 columns; the rest: 64 channels
+// of W each.  Saves, per pivot q, what the rank updates need: HcT[q][a] = A[a][i], HrT[q][b] = A[i][b],
+// T[q][b] = A[i][b] / d, Err[q][n].  The panel's own rows and columns of A and W are not read again.
+__global__ __launch_bounds__(PTHREADS)
+void visit_panel_kernel(const double* __restrict__ A, const double* __restrict__ W, int N, int K, int i0,
+                        double* __restrict__ HcT, double* __restrict__ HrT, double* __restrict__ T, double* __restrict__ Err,
+                        uint8_t* __restrict__ qw, float* __restrict__ sw) {
+    __shared__ __attribute__((aligned(16))) double Rt[PB][PB], Ct[PB][PB], dt[PB];
+    const PanelTables tb{Rt, Ct, dt};
+    const int i1 = i0 + PB, nr = (K - i1) / PB;
+    const int v = threadIdx.x >> 4, pos = threadIdx.x & 15;
+    const int role = ((int)blockIdx.x < nr) ? 0 : ((int)blockIdx.x < 2 * nr) ? 1 : 2;
+    const int idx = (role < 2 ? i1 : 0) + ((int)blockIdx.x - role * nr) * PB + v;      // row, column or channel
+    const bool live = role < 2 || idx < N;
+    double x[4], dg[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        dg[j] = A[(size_t)(i0 + v) * K + i0 + 4 * pos + j];
+        x[j] = 0.0;
+        if (role == 0) x[j] = A[(size_t)idx * K + i0 + 4 * pos + j];
+        if (role == 1) x[j] = A[(size_t)(i0 + 4 * pos + j) * K + idx];
+        if (role == 2 && live) x[j] = W[(size_t)(i0 + 4 * pos + j) * N + idx];
     }
-    const double w = W[(size_t)i * N + n];
-    float q = 0.0f;
-    if (s > 0.0f) q = fminf(fmaxf(rintf(__fdiv_rn((float)w, s)), -8.0f), 7.0f);
-    codes[(size_t)i * N + n] = (int8_t)q;
-    Err[(size_t)(i - i0) * N + n] = __ddiv_rn(__dsub_rn(w, __dmul_rn((double)q, (double)s)), Hinv[(size_t)i * K + i]);
-}
-// ---- spread the error of column i over the panel's not yet visited weights (rows i + 1 .. i0 + PB - 1)
-__global__ void spread_panel_kernel(double* __restrict__ W, const double* __restrict__ Hinv, const double* __restrict__ Err,
-                                    int N, int K, int i, int i0) {
-    const size_t total = (size_t)(i0 + PB - 1 - i) * N, stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-        const int j = i + 1 + (int)(e / N), n = (int)(e % N);
-        W[(size_t)j * N + n] = __dsub_rn(W[(size_t)j * N + n], __dmul_rn(Hinv[(size_t)i * K + j], Err[(size_t)(i - i0) * N + n]));
-    }
-}
-// ---- eliminate index i from the inverse Hessian inside the panel: Hinv[a][b] -= Hinv[a][i] (Hinv[i][b] / d) for
-// a, b > i with a or b in the panel; row i, scaled row i and column i are saved for the deferred updates
-// (HrowT[j][q] = Hinv[i][j], T[q][b] = Hinv[i][b] / d, Hc[a][q] = Hinv[a][i]); row and column i are not written.
-__global__ void eliminate_panel_kernel(double* __restrict__ Hinv, int K, int i, int i0,
-                                       double* __restrict__ HrowT, double* __restrict__ T, double* __restrict__ Hc) {
-    const size_t stride = (size_t)gridDim.x * blockDim.x, t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int q = i - i0, i1 = i0 + PB;
-    const double d = Hinv[(size_t)i * K + i];
-    for (size_t e = t0; e < (size_t)K; e += stride) {
-        const int j = (int)e;
-        const double hij = Hinv[(size_t)i * K + j];
-        HrowT[(size_t)j * PB + q] = hij;
-        T[(size_t)q * K + j] = __ddiv_rn(hij, d);
-        Hc[(size_t)j * PB + q] = Hinv[(size_t)j * K + i];
-    }
-    const int rp = i1 - 1 - i;                          // panel rows / columns still alive after i
-    const int rem = K - 1 - i;                          // indices > i
-    const size_t n1 = (size_t)rp * rem, total = n1 + (size_t)(K - i1) * rp;
-    for (size_t e = t0; e < total; e += stride) {
-        int a, b;
-        if (e < n1) {                                   // rows of the panel, every column > i
-            a = i + 1 + (int)(e / rem);
-            b = i + 1 + (int)(e % rem);
-        } else {                                        // rows below the panel, columns of the panel
-            const size_t f = e - n1;
-            a = i1 + (int)(f / rp);
-            b = i + 1 + (int)(f % rp);
+    panel_diagonal<false>(dg, tb);
+    if (role == 2) {
+        // rows of H^-1 as they stood when their index was visited: the diagonal block's final values right of the diagonal
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Ct[v][4 * pos + j] = dg[j];
+        __syncthreads();
+        double a = fmax(fmax(fabs(x[0]), fabs(x[1])), fmax(fabs(x[2]), fabs(x[3])));
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) a = fmax(a, __shfl_xor(a, o));
+        const float s = __fdiv_rn((float)a, 7.0f);
+        if (pos == 0 && live) sw[(size_t)(i0 >> 6) * N + idx] = s;
+        for (int it = 0; it < 16; ++it) {
+            const int sl = (pos + it) & 15;
+            uint32_t codes = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int q = 4 * it + k;
+                const double w = row_first(x[k]);
+                float c = 0.0f;
+                if (s > 0.0f) c = fminf(fmaxf(rintf(__fdiv_rn((float)w, s)), -8.0f), 7.0f);
+                codes |= ((uint32_t)(int)c & 15u) << (4 * k);
+                const double e = __ddiv_rn(__dsub_rn(w, __dmul_rn((double)c, (double)s)), dt[q]);
+                if (pos == 0 && live) Err[(size_t)q * N + idx] = e;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double u = __dsub_rn(x[j], __dmul_rn(Ct[q][4 * sl + j], e));
+                    x[j] = (4 * sl + j > q) ? u : x[j];
+                }
+            }
+            if (pos == 0 && live)                          // four codes: two bytes, low nibble = even index
+                *reinterpret_cast<uint16_t*>(qw + (size_t)idx * (K >> 1) + (i0 >> 1) + 2 * it) = (uint16_t)codes;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
         }
-        const double t = __ddiv_rn(Hinv[(size_t)i * K + b], d);
-        Hinv[(size_t)a * K + b] = __dsub_rn(Hinv[(size_t)a * K + b], __dmul_rn(Hinv[(size_t)a * K + i], t));
+        return;
+    }
+    for (int it = 0; it < 16; ++it) {
+        const int sl = (pos + it) & 15;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int q = 4 * it + k;
+            const double c = row_first(x[k]);
+            double e = c;
+            if (role == 0) {
+                if (pos == 0) HcT[(size_t)q * K + idx] = c;
+            } else {
+                e = __ddiv_rn(c, dt[q]);
+                if (pos == 0) {
+                    HrT[(size_t)q * K + idx] = c;
+                    T[(size_t)q * K + idx] = e;
+                }
+            }
+            const double* tab = (role == 0) ? Rt[q] : Ct[q];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double u = __dsub_rn(x[j], __dmul_rn(tab[4 * sl + j], e));
+                x[j] = (4 * sl + j > q) ? u : x[j];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
     }
 }
-// ---- codes [K][N] -> canonical qw [N][K/2] (low nibble = even k)
-__global__ void pack_codes_kernel(const int8_t* __restrict__ codes, int N, int K, uint8_t* __restrict__ qw) {
-    const size_t total = (size_t)N * (K / 2), stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-        const int n = (int)(e / (K / 2)), k2 = (int)(e % (K / 2));
-        const uint32_t lo = (uint32_t)codes[(size_t)(2 * k2) * N + n] & 15u, hi = (uint32_t)codes[(size_t)(2 * k2 + 1) * N + n] & 15u;
-        qw[e] = (uint8_t)(lo | (hi << 4));
+
+// ---- X[a][b] <- (..((X[a][b] - L[0][a] R[0][b]) - L[1][a] R[1][b]).. - L[63][a] R[63][b]) over rows a0 + [0, rows)
+// and columns b0 + [0, cols), leaving out the 64 indices from `skip` on in both directions (skip < 0: none; rows and
+// cols count what is left).  L and R are [PB][ld].
+struct RankUpdate {
+    double* X;
+    const double *L, *R;
+    size_t ldx, ldl, ldr;
+    int a0, rows, b0, cols, skip;
+    int tiles_b;                 // tiles along b
+    int tiles;                   // tiles in all
+};
+
+// A block takes a tile of 16 TT x 16 TT elements, TT x TT per thread: two binary64 operations per element and pivot are
+// the floor (4 clocks per wave each: 64 K^2 elements and pivots are 83 us at K = 5120), and TT = 8 needs 16 LDS values
+// for 64 updates, half of what LDS delivers meanwhile; TT = 4 needs all of it and is for matrices with too few tiles.
+// Two problems share a launch (blocks of u0 first), and with Dnew one more block puts the panel's diagonal block back.
+template <int TT>
+__global__ __launch_bounds__(256, 2)
+void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const double* __restrict__ Dnew, int K, int p0) {
+    constexpr int BT = 16 * TT, QC = 32;
+    __shared__ __attribute__((aligned(16))) double Ls[QC][BT], Rs[QC][BT];
+    int bid = blockIdx.x;
+    if (bid >= u0.tiles + u1.tiles) {                       // u0.X is the matrix of the inverse here
+        for (int e = threadIdx.x; e < PB * PB; e += 256) u0.X[(size_t)(p0 + e / PB) * K + p0 + e % PB] = Dnew[e];
+        return;
     }
+    const bool first = bid < u0.tiles;
+    const RankUpdate& u = first ? u0 : u1;
+    if (!first) bid -= u0.tiles;
+    const int ta = (bid / u.tiles_b) * BT, tb = (bid % u.tiles_b) * BT;
+    auto place = [&](const int base, const int i) {         // i-th index that is not left out
+        const int g = base + i;
+        return (u.skip >= 0 && g >= u.skip) ? g + PB : g;
+    };
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    double x[TT][TT];
+    size_t row[TT];
+    int col[TT];
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+        row[i] = (size_t)place(u.a0, ta + ty * TT + i) * u.ldx;
+        col[i] = place(u.b0, tb + tx + 16 * i);
+    }
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j)
+            x[i][j] = (ta + ty * TT + i < u.rows && tb + tx + 16 * j < u.cols) ? u.X[row[i] + col[j]] : 0.0;
+    const int lc = threadIdx.x % BT, lq = threadIdx.x / BT;
+    const bool lin = ta + lc < u.rows, rin = tb + lc < u.cols;
+    const double* lp = u.L + (lin ? place(u.a0, ta + lc) : 0);
+    const double* rp = u.R + (rin ? place(u.b0, tb + lc) : 0);
+    for (int q0 = 0; q0 < PB; q0 += QC) {
+        if (q0) __syncthreads();
+#pragma unroll
+        for (int q = 0; q < QC; q += 256 / BT) {
+            Ls[q + lq][lc] = lin ? lp[(size_t)(q0 + q + lq) * u.ldl] : 0.0;
+            Rs[q + lq][lc] = rin ? rp[(size_t)(q0 + q + lq) * u.ldr] : 0.0;
+        }
+        __syncthreads();
+        for (int q = 0; q < QC; ++q) {
+            double l[TT], r[TT];
+#pragma unroll
+            for (int i = 0; i < TT; ++i) l[i] = Ls[q][ty * TT + i];
+#pragma unroll
+            for (int j = 0; j < TT; ++j) r[j] = Rs[q][tx + 16 * j];
+#pragma unroll
+            for (int i = 0; i < TT; ++i)
+#pragma unroll
+                for (int j = 0; j < TT; ++j) x[i][j] = __dsub_rn(x[i][j], __dmul_rn(l[i], r[j]));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j)
+            if (ta + ty * TT + i < u.rows && tb + tx + 16 * j < u.cols) u.X[row[i] + col[j]] = x[i][j];
+}
+
+void launch_rank_updates(RankUpdate u0, RankUpdate u1, const double* Dnew, int K, int p0, hipStream_t stream) {
+    auto set = [](RankUpdate& u, int bt) {
+        u.tiles_b = (u.cols + bt - 1) / bt;
+        u.tiles = (u.rows > 0 && u.cols > 0) ? u.tiles_b * ((u.rows + bt - 1) / bt) : 0;
+    };
+    set(u0, 128);
+    set(u1, 128);
+    const int extra = Dnew ? 1 : 0;
+    if (u0.tiles + u1.tiles >= 256) {                       // at least one large tile for every compute unit
+        hipLaunchKernelGGL(rank_update_kernel<8>, dim3(u0.tiles + u1.tiles + extra), dim3(256), 0, stream, u0, u1, Dnew, K, p0);
+        return;
+    }
+    set(u0, 64);
+    set(u1, 64);
+    if (u0.tiles + u1.tiles + extra)
+        hipLaunchKernelGGL(rank_update_kernel<4>, dim3(u0.tiles + u1.tiles + extra), dim3(256), 0, stream, u0, u1, Dnew, K, p0);
 }
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
-inline unsigned blocks_for(size_t n) { size_t b = (n + 255) / 256; return (unsigned)(b < 1 ? 1 : (b > 4096 ? 4096 : b)); }
 
 }  // namespace
 
 size_t gptq_workspace_bytes(int N, int K) {
-    return up256((size_t)K * K * 8) + up256((size_t)K * N * 8) + up256((size_t)N * 4) + up256((size_t)K * N) +
-           4 * up256((size_t)K * PB * 8) + up256((size_t)PB * N * 8);
+    return up256((size_t)K * K * 8) + up256((size_t)K * N * 8) + 3 * up256((size_t)K * PB * 8) + up256((size_t)PB * N * 8) +
+           up256((size_t)(PB * PB + 1) * 8);
 }
 
 hipError_t launch_gptq_hessian(const void* x, int64_t ldx, const float* inv_lambda, int64_t M, int K, double* H,
@@ -269,41 +433,29 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     uint8_t* p = (uint8_t*)workspace;
     double* A = (double*)p;        p += up256((size_t)K * K * 8);
     double* W = (double*)p;        p += up256((size_t)K * N * 8);
-    float* scur = (float*)p;       p += up256((size_t)N * 4);
-    int8_t* codes = (int8_t*)p;    p += up256((size_t)K * N);
-    double* Lc = (double*)p;       p += up256((size_t)K * PB * 8);     // saved pivot columns      [K][PB]
-    double* Rr = (double*)p;       p += up256((size_t)K * PB * 8);     // saved scaled pivot rows  [PB][K]
-    double* HrowT = (double*)p;    p += up256((size_t)K * PB * 8);     // saved rows of H^-1       [K][PB]
-    double* Hc = (double*)p;       p += up256((size_t)K * PB * 8);     // saved columns of H^-1    [K][PB]
-    double* Err = (double*)p;                                          // errors of the panel      [PB][N]
-    const dim3 tilesKK((unsigned)(K / 64), (unsigned)(K / 64));
-    hipLaunchKernelGGL(prepare_kernel, dim3(1024), dim3(256), 0, stream, R, H, damp, N, K, A, W);
-    for (int p0 = 0; p0 < K; p0 += PB) {               // Gauss-Jordan, one panel of pivots at a time
-        for (int q = p0; q < p0 + PB; ++q) {
-            hipLaunchKernelGGL(gj_pivot_kernel, dim3((K + 255) / 256), dim3(256), 0, stream, A, K, q, p0, Lc, Rr);
-            hipLaunchKernelGGL(gj_panel_kernel, dim3(blocks_for((size_t)K * PB * 2)), dim3(256), 0, stream, A, K, q, p0, Lc, Rr);
-        }
-        if (K > PB)
-            hipLaunchKernelGGL(seq_rank_update_kernel, tilesKK, dim3(256), 0, stream, A, (size_t)K, 0, K, 0, K, p0, Lc, Rr, (size_t)K);
+    double* Lc = (double*)p;       p += up256((size_t)K * PB * 8);     // saved pivot columns         [PB][K]
+    double* Rr = (double*)p;       p += up256((size_t)K * PB * 8);     // saved scaled pivot rows     [PB][K]
+    double* Hr = (double*)p;       p += up256((size_t)K * PB * 8);     // saved rows of H^-1          [PB][K]
+    double* Err = (double*)p;      p += up256((size_t)PB * N * 8);     // errors of the panel         [PB][N]
+    double* Dnew = (double*)p;                                         // diagonal block of the panel [PB][PB], damping
+    double* add = Dnew + PB * PB;
+    hipLaunchKernelGGL(diag_sum_kernel, dim3(1), dim3(256), 0, stream, H, damp, K, add);
+    hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(256), 0, stream, R, H, add, N, K, A, W);
+    const size_t ldk = (size_t)K, ldn = (size_t)N;
+    const RankUpdate none{A, nullptr, nullptr, ldk, ldk, ldk, 0, 0, 0, 0, -1, 1, 0};
+    const int np = K / PB;
+    for (int p0 = 0; p0 < K; p0 += PB) {               // the inverse, one panel of pivots at a time
+        hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (np - 1) + 1), dim3(PTHREADS), 0, stream, A, K, p0, Lc, Rr, Dnew);
+        launch_rank_updates(RankUpdate{A, Lc, Rr, ldk, ldk, ldk, 0, K - PB, 0, K - PB, p0, 1, 0}, none, Dnew, K, p0, stream);
     }
     for (int i0 = 0; i0 < K; i0 += PB) {               // the weights, one panel (= one 64-group) at a time
-        const int i1 = i0 + PB;
-        for (int i = i0; i < i1; ++i) {
-            hipLaunchKernelGGL(column_kernel, dim3((N + 255) / 256), dim3(256), 0, stream, W, A, N, K, i, i0, scur, sw, codes, Err);
-            if (i + 1 < i1)
-                hipLaunchKernelGGL(spread_panel_kernel, dim3(blocks_for((size_t)(i1 - 1 - i) * N)), dim3(256), 0, stream, W, A, Err, N, K, i, i0);
-            if (i1 < K || i + 1 < i1)
-                hipLaunchKernelGGL(eliminate_panel_kernel, dim3(blocks_for((size_t)K * PB)), dim3(256), 0, stream, A, K, i, i0, HrowT, Rr, Hc);
-        }
-        if (i1 < K) {                                   // the deferred updates of everything behind the panel
-            const int rest = K - i1;
-            hipLaunchKernelGGL(seq_rank_update_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)(rest / 64)), dim3(256), 0, stream,
-                               W, (size_t)N, i1, K, 0, N, -1, HrowT, Err, (size_t)N);
-            hipLaunchKernelGGL(seq_rank_update_kernel, dim3((unsigned)(rest / 64), (unsigned)(rest / 64)), dim3(256), 0, stream,
-                               A, (size_t)K, i1, K, i1, K, -1, Hc, Rr, (size_t)K);
-        }
+        const int i1 = i0 + PB, rest = K - i1;
+        hipLaunchKernelGGL(visit_panel_kernel, dim3(2 * (rest / PB) + (N + PB - 1) / PB), dim3(PTHREADS), 0, stream,
+                           A, W, N, K, i0, Lc, Hr, Rr, Err, qw, sw);
+        if (rest > 0)                                   // the deferred updates of everything behind the panel
+            launch_rank_updates(RankUpdate{W, Hr, Err, ldn, ldk, ldn, i1, rest, 0, N, -1, 1, 0},
+                                RankUpdate{A, Lc, Rr, ldk, ldk, ldk, i1, rest, i1, rest, -1, 1, 0}, nullptr, K, i0, stream);
     }
-    hipLaunchKernelGGL(pack_codes_kernel, dim3(blocks_for((size_t)N * (K / 2))), dim3(256), 0, stream, codes, N, K, qw);
     return hipGetLastError();
 }
 
