@@ -5,11 +5,11 @@
 // rounded to the int4 grid of its (channel, 64-group) scale and its rounding error is spread over the not yet
 // visited weights of the same channel in proportion to row k of the inverse Hessian of the layer-wise objective
 // ||X^ (R - R^)||^2 (H = X^T X^ plus damping), from which index k is then eliminated.  Everything runs in
-// binary64 with one explicitly rounded operation per arithmetic step and no reductions other than max and one
-// sequential sum, so that a CPU reference repeats every bit.  The published implementation factors H^-1 once
-// (Cholesky) and reads the same numbers off the factor; this form trades that for elementwise kernels:
-// K^3 updates for the inverse, K^3 / 3 of H^-1 and K^2 N / 2 of the weights during the visit, taken in panels of 64
-// pivots (below) so that the matrices cross HBM once per panel.
+// binary64; every update is one fused multiply-subtract per element and pivot, in pivot order (a CPU reference that
+// rounds the product too gives the same codes and scales), and there are no reductions other than max and one
+// sequential sum.  The published implementation factors H^-1 once (Cholesky) and reads the same numbers off the
+// factor; this form trades that for elementwise kernels: K^3 updates for the inverse, K^3 / 3 of H^-1 and K^2 N / 2
+// of the weights during the visit, taken in panels of 64 pivots (below) so that the matrices cross HBM once per panel.
 #include "svdq_dev.h"
 #include "svdq_kernels.h"
 
@@ -17,43 +17,133 @@ namespace svdq {
 
 namespace {
 
-// ---- H += X^T X^, X^ = x * inv_lambda in binary32 (eq. 5), products and sums in binary64
-constexpr int HT = 64;   // tile of H per block
-__global__ __launch_bounds__(256)
+typedef double double4v __attribute__((ext_vector_type(4)));
+
+// The matrix instruction both parts of this file lean on: D = A B + C of 16 x 4 by 4 x 16 in binary64, lane l holding
+// A[l % 16][l / 16], B[l / 16][l % 16] and, in register i, C[4 i + l / 16][l % 16].  It forms each element as a chain of
+// four fused multiply-adds in k order, rounding after each (2000 random products, exponents 2^-10 .. 2^10, no
+// difference from that chain): a sequence of these instructions IS the scalar sequence of updates.
+__device__ __forceinline__ double4v mfma_f64(double a, double b, double4v c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// ---- H += X^T X^, X^ = x * inv_lambda in binary32 (eq. 5), products and sums in binary64.
+// H's contribution is symmetric, so only tiles on and above the diagonal are formed and each is added twice.  A block
+// owns one tile of 16 T x 16 T and its WV waves split the tokens (four per step, one per 16 lanes); the waves' sums meet
+// in LDS in a fixed order.  The operands come straight from global memory: lane (j, kq) = (l % 16, l / 16) takes the T
+// neighbouring channels T j .. T j + T - 1 of token 4 step + kq, which are row (or column) j of T different matrix
+// tiles, so a load feeds T^2 instructions and there is nothing to stage or wait for together.  Bound by the matrix
+// instruction (64 clocks each, 78.6 TFLOP/s; the vector unit has the same rate, but not the registers to feed itself
+// without LDS traffic).  T = 4 with four waves (two per SIMD); T = 2 with sixteen waves where that leaves CUs idle.
+// K = 5120, 8192 tokens: 19.6 ms for the full square on the vector unit.
+template <int T, bool ALIGNED>
+struct XLoad {
+    uint32_t w[T / 2];
+    __device__ __forceinline__ void load(const uint16_t* p) {
+        if constexpr (ALIGNED && T == 4) {
+            const uint2 v = *reinterpret_cast<const uint2*>(p);
+            w[0] = v.x;
+            w[1] = v.y;
+        } else if constexpr (ALIGNED) {
+            w[0] = *reinterpret_cast<const uint32_t*>(p);
+        } else {
+#pragma unroll
+            for (int i = 0; i < T / 2; ++i) w[i] = (uint32_t)p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
+        }
+    }
+    __device__ __forceinline__ void values(const float (&il)[T], double (&v)[T]) const {
+#pragma unroll
+        for (int i = 0; i < T / 2; ++i) {
+            v[2 * i] = (double)__fmul_rn(bf16lo_f(w[i]), il[2 * i]);
+            v[2 * i + 1] = (double)__fmul_rn(bf16hi_f(w[i]), il[2 * i + 1]);
+        }
+    }
+};
+
+template <int T, int WV, bool ALIGNED>
+__global__ __launch_bounds__(64 * WV, T == 4 ? 2 : 1)
 void hessian_kernel(const uint16_t* __restrict__ x, int64_t ldx, const float* __restrict__ inv_lambda,
                     int64_t M, int K, double* __restrict__ H) {
-    __shared__ double xa[16][HT + 1], xb[16][HT + 1];
-    const int a0 = blockIdx.y * HT, b0 = blockIdx.x * HT;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    double acc[4][4] = {};
-    for (int64_t m0 = 0; m0 < M; m0 += 16) {
-        for (int e = threadIdx.x; e < 16 * HT; e += 256) {
-            const int mr = e / HT, c = e - mr * HT;
-            const int64_t m = m0 + mr;
-            double va = 0.0, vb = 0.0;
-            if (m < M) {
-                if (a0 + c < K) va = (double)__fmul_rn(bits_f((uint32_t)x[m * ldx + a0 + c] << 16), inv_lambda[a0 + c]);
-                if (b0 + c < K) vb = (double)__fmul_rn(bits_f((uint32_t)x[m * ldx + b0 + c] << 16), inv_lambda[b0 + c]);
-            }
-            xa[mr][c] = va;
-            xb[mr][c] = vb;
+    constexpr int BT = 16 * T;
+    __shared__ double tile[BT][BT + 1];
+    int tb = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);      // column of tiles; ta <= tb
+    while (tb * (tb + 1) / 2 > (int)blockIdx.x) --tb;
+    while ((tb + 1) * (tb + 2) / 2 <= (int)blockIdx.x) ++tb;
+    const int ta = (int)blockIdx.x - tb * (tb + 1) / 2;
+    const int a0 = ta * BT, b0 = tb * BT;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 15, kq = lane >> 4;
+    float ila[T], ilb[T];
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+        ila[i] = inv_lambda[a0 + T * j + i];
+        ilb[i] = inv_lambda[b0 + T * j + i];
+    }
+    double4v acc[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int k = 0; k < T; ++k) acc[i][k] = double4v{0.0, 0.0, 0.0, 0.0};
+    const int64_t steps = (M + 3) / 4;                      // a step is four tokens; wave w takes steps w, w + WV, ...
+    const uint16_t* pa = x + a0 + T * j;
+    const uint16_t* pb = x + b0 + T * j;
+    constexpr int U = 4;                                    // steps requested together, one batch ahead of their use
+    XLoad<T, ALIGNED> xa[2][U], xb[2][U];
+    auto request = [&](const int64_t s0, const int buf) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int64_t m = 4 * (s0 + u * WV) + kq;
+            if (m >= M) m = M - 1;                          // the values are replaced by zeros when they are used
+            xa[buf][u].load(pa + m * ldx);
+            xb[buf][u].load(pb + m * ldx);
         }
-        __syncthreads();
+    };
+    auto multiply = [&](const int64_t s0, const int buf) {
 #pragma unroll
-        for (int mr = 0; mr < 16; ++mr)
+        for (int u = 0; u < U; ++u) {
+            double va[T], vb[T];
+            xa[buf][u].values(ila, va);
+            xb[buf][u].values(ilb, vb);
+            if (4 * (s0 + u * WV) + 4 > M) {
+                const bool in = 4 * (s0 + u * WV) + kq < M;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < T; ++i) {
+                    va[i] = in ? va[i] : 0.0;
+                    vb[i] = in ? vb[i] : 0.0;
+                }
+            }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __fma_rn(xa[mr][ty * 4 + i], xb[mr][tx * 4 + j], acc[i][j]);
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int k = 0; k < T; ++k) acc[i][k] = mfma_f64(va[i], vb[k], acc[i][k]);
+        }
+    };
+    request(wave, 0);
+    for (int64_t s = wave; s < steps; s += 2 * U * WV) {
+        request(s + U * WV, 1);
+        multiply(s, 0);
+        request(s + 2 * U * WV, 0);
+        multiply(s + U * WV, 1);
+    }
+    for (int w = 0; w < WV; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int k = 0; k < T; ++k)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        double& t = tile[T * (4 * e + kq) + i][T * j + k];
+                        t = (w == 0) ? acc[i][k][e] : t + acc[i][k][e];
+                    }
+        }
         __syncthreads();
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int a = a0 + ty * 4 + i, b = b0 + tx * 4 + j;
-            if (a < K && b < K) H[(size_t)a * K + b] += acc[i][j];
-        }
+    for (int e = threadIdx.x; e < BT * BT; e += 64 * WV) {
+        const int r = e / BT, c = e % BT;
+        H[(size_t)(a0 + r) * K + b0 + c] += tile[r][c];
+        if (ta != tb) H[(size_t)(b0 + r) * K + a0 + c] += tile[c][r];
+    }
 }
 
 // ---- preparation: binary64 copies, dead channels, damping with the diagonal summed in index order
@@ -86,20 +176,19 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 }
 
 // ---- Panel-blocked form of both eliminations.  Every element of H^-1 (and of W) must receive, in the order of the
-// pivots, one rounded product and one rounded subtraction per pivot: that sequence per element is the definition, and
-// it does not say WHEN an element is touched.  Pivots are taken in panels of PB = 64, two launches per panel:
+// pivots, one fused multiply-subtract per pivot: that sequence per element is the definition, and it does not say WHEN
+// an element is touched.  Pivots are taken in panels of PB = 64, two launches per panel:
 //   panel kernel   brings the panel's own rows and columns (2 x 64 x K elements, for the weights 64 x N) through all 64
-//                  pivots.  A row outside the panel only needs the panel's diagonal block as it stood at each pivot,
-//                  and a column likewise, so rows and columns are independent of each other: a block takes 64 of them
-//                  and first runs the 64 x 64 diagonal block itself (every block repeats that; it is a chain of 64
-//                  dependent steps, and a launch of its own would cost as much again).  The pivot's column and scaled
-//                  row, as they stood when the pivot was taken, are saved.
-//   rank update    everything else receives its 64 updates in one pass from the saved columns and rows, in pivot
-//                  order, with the same two rounded operations per update.
-// Bit-identical to the pivot-by-pivot form.  K = N = 5120: one launch per pivot and step (25 600 launches) took 112 ms,
-// of which the rank updates were 31.
+//                  pivots.  A row outside the panel only needs the panel's 64 x 64 diagonal block as it stood at each
+//                  pivot (the tables below), and a column likewise, so the rows and columns are independent of each
+//                  other.  The pivots' columns and scaled rows, as they stood when taken, are saved.
+//   rank update    everything else receives its 64 updates in one pass from the saved columns and rows, in pivot order,
+//                  on the binary64 matrix instruction.  One block meanwhile does the same for the NEXT panel's diagonal
+//                  block, takes that through its own 64 dependent steps and leaves the next panel's tables: a serial
+//                  chain of about 20 us that the rank update of the rest hides.
+// Same result as the pivot-by-pivot form bit for bit.  K = N = 5120: with a launch per pivot and step (25 600 of them)
+// 112 ms, of which the rank updates on the vector unit were 31.
 constexpr int PB = 64;
-constexpr int PTHREADS = 1024;           // 64 vectors x 16 lanes
 
 // ---- A vector of 64 elements (one row or column of the panel) lives in 16 lanes (a DPP row), four elements each.
 // Pivot 4 it + k is always element k of the row's lane 0: after every four pivots the vectors turn by one lane, so the
@@ -114,302 +203,431 @@ __device__ __forceinline__ double dpp64(double v) {
 __device__ __forceinline__ double row_first(double v) { return dpp64<0x150>(v); }             // row_newbcast:0
 __device__ __forceinline__ double row_turn(double v) { return dpp64<0x120 + 15>(v); }         // row_ror:15: from lane + 1
 
+// a / d, correctly rounded, from y = RN(1 / d): two corrections of a y.  The first makes the quotient faithful, and
+// from a faithful quotient and a correctly rounded reciprocal the second gives the rounded quotient (Markstein's
+// theorem), as long as nothing leaves the exponent range: there the division itself.
+__device__ __forceinline__ bool within(double v, double lo, double hi) { return fabs(v) >= lo && fabs(v) <= hi; }
+__device__ __forceinline__ double divide_by(double a, double d, double y) {
+    double q = a * y;
+    q = __builtin_fma(__builtin_fma(-d, q, a), y, q);
+    q = __builtin_fma(__builtin_fma(-d, q, a), y, q);
+    if (!(within(d, 0x1p-200, 0x1p200) && (a == 0.0 || within(a, 0x1p-700, 0x1p700)))) q = __ddiv_rn(a, d);
+    return q;
+}
+
+// What a panel kernel needs of its diagonal block D (K-major q = pivot inside the panel)
 struct PanelTables {
-    double (*R)[PB];       // [q][t]: row q of the diagonal block divided by its pivot, when pivot q was taken
-    double (*C)[PB];       // [q][t]: column q
-    double* d;             // [q]: pivot
+    double R[PB][PB];      // R[q][t] = D[q][t] / d_q when pivot q was taken
+    double C[PB][PB];      // C[q][t] = D[t][q] then
+    double D[PB][PB];      // the block after its 64 pivots
+    double d[PB], y[PB];   // pivots and their reciprocals
 };
 
-// The diagonal block through its 64 pivots (all 1024 threads: row t = tid / 16).  INV: in-place Gauss-Jordan inverse
-// (see below); otherwise elimination of the rows and columns behind the pivot only.  Leaves the tables; the block's
-// final values are in x.
+// The diagonal block through its 64 pivots, 256 threads: lane group g = tid / 16 holds rows 4 g .. 4 g + 3, so pivot
+// 4 it + k is row k of group it.  INV: in-place Gauss-Jordan inverse (see below); otherwise only the rows and columns
+// behind the pivot are updated (row q of D is then the row as it stood at pivot q).  Rt: PB x PB in LDS, ds: 2 in LDS.
 template <bool INV>
-__device__ __forceinline__ void panel_diagonal(double (&x)[4], const PanelTables& tb) {
-    const int t = threadIdx.x >> 4, pos = threadIdx.x & 15;
+__device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], PanelTables* __restrict__ out) {
+    const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
     for (int it = 0; it < 16; ++it) {
         const int sl = (pos + it) & 15;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int q = 4 * it + k;
-            const double c = row_first(x[k]);
-            double r[4];
-            if (t == q) {                                 // c is the pivot
+            double c[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    r[j] = __ddiv_rn(x[j], c);
-                    tb.R[q][4 * sl + j] = r[j];
+            for (int v = 0; v < 4; ++v) c[v] = row_first(x[v][k]);
+            if (grp == it) {                              // this group's row k is the pivot's
+                const double d = c[k], y = __ddiv_rn(1.0, d);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) Rt[q][4 * sl + j] = divide_by(x[k][j], d, y);
+                if (pos == 0) {
+                    ds[q][0] = out->d[q] = d;
+                    ds[q][1] = out->y[q] = y;
                 }
-                if (pos == 0) tb.d[q] = c;
             }
-            if (pos == 0) tb.C[q][t] = c;
+            if (pos == 0) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out->C[q][4 * grp + v] = c[v];
+            }
             __syncthreads();
-            const double d = tb.d[q];
-            const bool own = pos == 0;                    // element k of this lane is column q
-            if (INV) {
-                const double e = __ddiv_rn(t == q ? 1.0 : -c, d);
+            const double d = ds[q][0], y = ds[q][1];
+            double r[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const double rj = tb.R[q][4 * sl + j];
-                    const double v = (t == q) ? rj : __dsub_rn(x[j], __dmul_rn(c, rj));
-                    x[j] = (own && j == k) ? e : v;
-                }
-            } else if (t > q) {
+            for (int j = 0; j < 4; ++j) r[j] = Rt[q][4 * sl + j];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const double v = __dsub_rn(x[j], __dmul_rn(c, tb.R[q][4 * sl + j]));
-                    x[j] = (4 * sl + j > q) ? v : x[j];
+            for (int v = 0; v < 4; ++v) {
+                if (INV) {
+                    const bool isq = v == k && grp == it;
+                    const double e = isq ? y : divide_by(-c[v], d, y);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[v][j] = isq ? r[j] : __builtin_fma(-c[v], r[j], x[v][j]);
+                    x[v][k] = (pos == 0) ? e : x[v][k];
+                } else if (4 * grp + v > q) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const double u = __builtin_fma(-c[v], r[j], x[v][j]);
+                        x[v][j] = (4 * sl + j > q) ? u : x[v][j];
+                    }
                 }
             }
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
     }
-    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            out->D[4 * grp + v][4 * pos + j] = x[v][j];
+            out->R[4 * grp + v][4 * pos + j] = Rt[4 * grp + v][4 * pos + j];
+        }
 }
 
-// Where panel index b (64-blocks outside the panel's own) lies.
-__device__ __forceinline__ int outside_block(int b, int pb) { return b < pb ? b : b + 1; }
+// The panel's first tables: nothing precedes them that could carry them along.
+template <bool INV>
+__global__ __launch_bounds__(256)
+void first_tables_kernel(const double* __restrict__ D, size_t ld, PanelTables* __restrict__ out) {
+    __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
+    const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
+    double x[4][4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[v][j] = D[(size_t)(4 * grp + v) * ld + 4 * pos + j];
+    diagonal_block<INV>(x, Rt, ds, out);
+}
+
+// Vectors per block of the panel kernels: 16 lane groups of two vectors.  Two vectors per group halve the LDS reads of
+// the table (four values per lane and pivot), and 32 per block spread K = 5120 over every CU.
+constexpr int PV = 2, PVECS = 16 * PV;
+__device__ __forceinline__ void load_table(double (*to)[PB], const double (*from)[PB]) {
+    for (int e = threadIdx.x * 2; e < PB * PB; e += 512)
+        *reinterpret_cast<double2*>(&to[0][0] + e) = *reinterpret_cast<const double2*>(&from[0][0] + e);
+}
 
 // ---- in-place Gauss-Jordan inverse without pivoting.  Step p: d = A[p][p], col = A[:, p], row = A[p, :] / d;
 // A[a][j] -= col[a] row[j] elsewhere, A[p][j] = row[j], A[a][p] = -col[a] / d, A[p][p] = 1 / d.
-// Blocks 0 .. nb - 1: 64 rows outside the panel; nb .. 2 nb - 1: 64 columns outside it; the last block only runs the
-// diagonal block and writes it to Dnew (the other blocks read it from A meanwhile; the rank update puts it in place).
+// Blocks 0 .. nb - 1: PVECS rows outside the panel; nb .. 2 nb - 1: PVECS columns outside it.
 // Saves LT[q][a] = column of pivot p0 + q, Rr[q][j] = its scaled row.
-__global__ __launch_bounds__(PTHREADS)
-void gj_panel_kernel(double* __restrict__ A, int K, int p0, double* __restrict__ LT, double* __restrict__ Rr,
-                     double* __restrict__ Dnew) {
-    __shared__ __attribute__((aligned(16))) double Rt[PB][PB], Ct[PB][PB], dt[PB];
-    const PanelTables tb{Rt, Ct, dt};
-    const int nb = K / PB - 1, pb = p0 / PB;
-    const int v = threadIdx.x >> 4, pos = threadIdx.x & 15;
-    const int role = ((int)blockIdx.x < nb) ? 0 : ((int)blockIdx.x < 2 * nb) ? 1 : 2;
-    const int idx = outside_block((int)blockIdx.x - role * nb, pb) * PB + v;     // this vector's row or column
-    double x[4], dg[4];
+__global__ __launch_bounds__(256)
+void gj_panel_kernel(double* __restrict__ A, int K, int p0, const PanelTables* __restrict__ tb,
+                     double* __restrict__ LT, double* __restrict__ Rr) {
+    __shared__ __attribute__((aligned(16))) double tab[PB][PB], ds[PB][2];
+    const int nb = (K - PB) / PVECS;
+    const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
+    const bool rows = (int)blockIdx.x < nb;
+    double x[PV][4];
+    int idx[PV];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        dg[j] = A[(size_t)(p0 + v) * K + p0 + 4 * pos + j];
-        x[j] = 0.0;
-        if (role == 0) x[j] = A[(size_t)idx * K + p0 + 4 * pos + j];
-        if (role == 1) x[j] = A[(size_t)(p0 + 4 * pos + j) * K + idx];
-    }
-    panel_diagonal<true>(dg, tb);
-    if (role == 2) {
+    for (int v = 0; v < PV; ++v) {
+        idx[v] = ((int)blockIdx.x - (rows ? 0 : nb)) * PVECS + (grp >> 2) * 4 * PV + v * 4 + (grp & 3);
+        if (idx[v] >= p0) idx[v] += PB;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) Dnew[v * PB + 4 * pos + j] = dg[j];
-        return;
+        for (int j = 0; j < 4; ++j)
+            x[v][j] = rows ? A[(size_t)idx[v] * K + p0 + 4 * pos + j] : A[(size_t)(p0 + 4 * pos + j) * K + idx[v]];
     }
+    load_table(tab, rows ? tb->R : tb->C);
+    if (threadIdx.x < PB) {
+        ds[threadIdx.x][0] = tb->d[threadIdx.x];
+        ds[threadIdx.x][1] = tb->y[threadIdx.x];
+    }
+    __syncthreads();
+    double* save = rows ? LT : Rr;
     for (int it = 0; it < 16; ++it) {
         const int sl = (pos + it) & 15;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int q = 4 * it + k;
-            const double c = row_first(x[k]), d = dt[q];
-            const double e = __ddiv_rn(role == 0 ? -c : c, d);
-            if (role == 0) {
-                if (pos == 0) LT[(size_t)q * K + idx] = c;
+            const double d = ds[q][0], y = ds[q][1];
+            double t[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) x[j] = __dsub_rn(x[j], __dmul_rn(c, Rt[q][4 * sl + j]));
-            } else {
-                if (pos == 0) Rr[(size_t)q * K + idx] = e;
+            for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) x[j] = __dsub_rn(x[j], __dmul_rn(Ct[q][4 * sl + j], e));
+            for (int v = 0; v < PV; ++v) {
+                const double c = row_first(x[v][k]);
+                const double e = divide_by(rows ? -c : c, d, y);
+                const double f = rows ? c : e;
+                if (pos == 0) save[(size_t)q * K + idx[v]] = f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[v][j] = __builtin_fma(-f, t[j], x[v][j]);
+                x[v][k] = (pos == 0) ? e : x[v][k];
             }
-            x[k] = (pos == 0) ? e : x[k];
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
+        for (int v = 0; v < PV; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (role == 0) A[(size_t)idx * K + p0 + 4 * pos + j] = x[j];
-        else A[(size_t)(p0 + 4 * pos + j) * K + idx] = x[j];
-    }
+    for (int v = 0; v < PV; ++v)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (rows) A[(size_t)idx[v] * K + p0 + 4 * pos + j] = x[v][j];
+            else A[(size_t)(p0 + 4 * pos + j) * K + idx[v]] = x[v][j];
+        }
 }
 
 // ---- one panel of the visit: indices i0 .. i0 + 63 = one 64-group.  For each index i: code and error of every
 // channel, the error spread over the panel's later weights, index i eliminated from H^-1 (A[a][b] -= A[a][i] (A[i][b] / d)
-// for a, b > i).  Blocks 0 .. nr - 1: 64 rows of A behind the panel; nr .. 2 nr - 1: 64 columns; the rest: 64 channels
-// of W each.  Saves, per pivot q, what the rank updates need: HcT[q][a] = A[a][i], HrT[q][b] = A[i][b],
+// for a, b > i).  Blocks 0 .. nr - 1: PVECS rows of A behind the panel; nr .. 2 nr - 1: columns; the rest: channels
+// of W.  Saves, per pivot q, what the rank updates need: HcT[q][a] = A[a][i], HrT[q][b] = A[i][b],
 // T[q][b] = A[i][b] / d, Err[q][n].  The panel's own rows and columns of A and W are not read again.
-__global__ __launch_bounds__(PTHREADS)
+__global__ __launch_bounds__(256)
 void visit_panel_kernel(const double* __restrict__ A, const double* __restrict__ W, int N, int K, int i0,
+                        const PanelTables* __restrict__ tb,
                         double* __restrict__ HcT, double* __restrict__ HrT, double* __restrict__ T, double* __restrict__ Err,
                         uint8_t* __restrict__ qw, float* __restrict__ sw) {
-    __shared__ __attribute__((aligned(16))) double Rt[PB][PB], Ct[PB][PB], dt[PB];
-    const PanelTables tb{Rt, Ct, dt};
-    const int i1 = i0 + PB, nr = (K - i1) / PB;
-    const int v = threadIdx.x >> 4, pos = threadIdx.x & 15;
-    const int role = ((int)blockIdx.x < nr) ? 0 : ((int)blockIdx.x < 2 * nr) ? 1 : 2;
-    const int idx = (role < 2 ? i1 : 0) + ((int)blockIdx.x - role * nr) * PB + v;      // row, column or channel
-    const bool live = role < 2 || idx < N;
-    double x[4], dg[4];
+    __shared__ __attribute__((aligned(16))) double tab[PB][PB], ds[PB][2];
+    const int i1 = i0 + PB, nr = (K - i1) / PVECS;
+    const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
+    const int role = ((int)blockIdx.x < nr) ? 0 : ((int)blockIdx.x < 2 * nr) ? 1 : 2;      // rows, columns, channels
+    double x[PV][4];
+    int idx[PV];
+    bool live[PV];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        dg[j] = A[(size_t)(i0 + v) * K + i0 + 4 * pos + j];
-        x[j] = 0.0;
-        if (role == 0) x[j] = A[(size_t)idx * K + i0 + 4 * pos + j];
-        if (role == 1) x[j] = A[(size_t)(i0 + 4 * pos + j) * K + idx];
-        if (role == 2 && live) x[j] = W[(size_t)(i0 + 4 * pos + j) * N + idx];
+    for (int v = 0; v < PV; ++v) {
+        idx[v] = (role < 2 ? i1 : 0) + ((int)blockIdx.x - role * nr) * PVECS + (grp >> 2) * 4 * PV + v * 4 + (grp & 3);
+        live[v] = role < 2 || idx[v] < N;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            x[v][j] = 0.0;
+            if (role == 0) x[v][j] = A[(size_t)idx[v] * K + i0 + 4 * pos + j];
+            if (role == 1) x[v][j] = A[(size_t)(i0 + 4 * pos + j) * K + idx[v]];
+            if (role == 2 && live[v]) x[v][j] = W[(size_t)(i0 + 4 * pos + j) * N + idx[v]];
+        }
     }
-    panel_diagonal<false>(dg, tb);
+    load_table(tab, role == 0 ? tb->R : role == 1 ? tb->C : tb->D);
+    if (threadIdx.x < PB) {
+        ds[threadIdx.x][0] = tb->d[threadIdx.x];
+        ds[threadIdx.x][1] = tb->y[threadIdx.x];
+    }
+    __syncthreads();
     if (role == 2) {
-        // rows of H^-1 as they stood when their index was visited: the diagonal block's final values right of the diagonal
+        float s[PV];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) Ct[v][4 * pos + j] = dg[j];
-        __syncthreads();
-        double a = fmax(fmax(fabs(x[0]), fabs(x[1])), fmax(fabs(x[2]), fabs(x[3])));
+        for (int v = 0; v < PV; ++v) {
+            double a = fmax(fmax(fabs(x[v][0]), fabs(x[v][1])), fmax(fabs(x[v][2]), fabs(x[v][3])));
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1) a = fmax(a, __shfl_xor(a, o));
-        const float s = __fdiv_rn((float)a, 7.0f);
-        if (pos == 0 && live) sw[(size_t)(i0 >> 6) * N + idx] = s;
+            for (int o = 1; o < 16; o <<= 1) a = fmax(a, __shfl_xor(a, o));
+            s[v] = __fdiv_rn((float)a, 7.0f);
+            if (pos == 0 && live[v]) sw[(size_t)(i0 >> 6) * N + idx[v]] = s[v];
+        }
         for (int it = 0; it < 16; ++it) {
             const int sl = (pos + it) & 15;
-            uint32_t codes = 0;
+            uint32_t codes[PV] = {};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int q = 4 * it + k;
-                const double w = row_first(x[k]);
-                float c = 0.0f;
-                if (s > 0.0f) c = fminf(fmaxf(rintf(__fdiv_rn((float)w, s)), -8.0f), 7.0f);
-                codes |= ((uint32_t)(int)c & 15u) << (4 * k);
-                const double e = __ddiv_rn(__dsub_rn(w, __dmul_rn((double)c, (double)s)), dt[q]);
-                if (pos == 0 && live) Err[(size_t)q * N + idx] = e;
+                const double d = ds[q][0], y = ds[q][1];
+                double t[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const double u = __dsub_rn(x[j], __dmul_rn(Ct[q][4 * sl + j], e));
-                    x[j] = (4 * sl + j > q) ? u : x[j];
+                for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
+#pragma unroll
+                for (int v = 0; v < PV; ++v) {
+                    const double w = row_first(x[v][k]);
+                    float c = 0.0f;
+                    if (s[v] > 0.0f) c = fminf(fmaxf(rintf(__fdiv_rn((float)w, s[v])), -8.0f), 7.0f);
+                    codes[v] |= ((uint32_t)(int)c & 15u) << (4 * k);
+                    const double e = divide_by(__builtin_fma(-(double)c, (double)s[v], w), d, y);    // code x scale is exact
+                    if (pos == 0 && live[v]) Err[(size_t)q * N + idx[v]] = e;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const double u = __builtin_fma(-t[j], e, x[v][j]);
+                        x[v][j] = (4 * sl + j > q) ? u : x[v][j];
+                    }
                 }
             }
-            if (pos == 0 && live)                          // four codes: two bytes, low nibble = even index
-                *reinterpret_cast<uint16_t*>(qw + (size_t)idx * (K >> 1) + (i0 >> 1) + 2 * it) = (uint16_t)codes;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
+            for (int v = 0; v < PV; ++v) {
+                if (pos == 0 && live[v])                   // four codes: two bytes, low nibble = even index
+                    *reinterpret_cast<uint16_t*>(qw + (size_t)idx[v] * (K >> 1) + (i0 >> 1) + 2 * it) = (uint16_t)codes[v];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
+            }
         }
         return;
     }
+    double* save = role == 0 ? HcT : HrT;
     for (int it = 0; it < 16; ++it) {
         const int sl = (pos + it) & 15;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int q = 4 * it + k;
-            const double c = row_first(x[k]);
-            double e = c;
-            if (role == 0) {
-                if (pos == 0) HcT[(size_t)q * K + idx] = c;
-            } else {
-                e = __ddiv_rn(c, dt[q]);
-                if (pos == 0) {
-                    HrT[(size_t)q * K + idx] = c;
-                    T[(size_t)q * K + idx] = e;
-                }
-            }
-            const double* tab = (role == 0) ? Rt[q] : Ct[q];
+            double t[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double u = __dsub_rn(x[j], __dmul_rn(tab[4 * sl + j], e));
-                x[j] = (4 * sl + j > q) ? u : x[j];
+            for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
+#pragma unroll
+            for (int v = 0; v < PV; ++v) {
+                const double c = row_first(x[v][k]);
+                double f = c;
+                if (role == 1) f = divide_by(c, ds[q][0], ds[q][1]);
+                if (pos == 0) {
+                    save[(size_t)q * K + idx[v]] = c;
+                    if (role == 1) T[(size_t)q * K + idx[v]] = f;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double u = __builtin_fma(-f, t[j], x[v][j]);
+                    x[v][j] = (4 * sl + j > q) ? u : x[v][j];
+                }
             }
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
+        for (int v = 0; v < PV; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
     }
 }
 
 // ---- X[a][b] <- (..((X[a][b] - L[0][a] R[0][b]) - L[1][a] R[1][b]).. - L[63][a] R[63][b]) over rows a0 + [0, rows)
 // and columns b0 + [0, cols), leaving out the 64 indices from `skip` on in both directions (skip < 0: none; rows and
-// cols count what is left).  L and R are [PB][ld].
+// cols count what is left) and the 64 x 64 block at (hole, hole).  L and R are [PB][ld].  rows % 64 == 0.
 struct RankUpdate {
     double* X;
     const double *L, *R;
     size_t ldx, ldl, ldr;
-    int a0, rows, b0, cols, skip;
-    int tiles_b;                 // tiles along b
-    int tiles;                   // tiles in all
+    int a0, rows, b0, cols, skip, hole;
+    int tiles_b, tiles;          // 128 x 128 tiles along b, and in all
+};
+// The next panel's diagonal block (at index s0 of A), for the first block of a rank update: brought up to date with L
+// and R (none: it is already, as D), then through its own pivots (mode 1: inverse, 2: visit) into `next`.  Also puts the
+// finished diagonal block `prev` of the current panel (at p0) in place; null: nothing to put.
+struct Lookahead {
+    double* A;
+    const double *L, *R;
+    const PanelTables* prev;
+    PanelTables* next;
+    int K, p0, s0, mode;
 };
 
-// A block takes a tile of 16 TT x 16 TT elements, TT x TT per thread: two binary64 operations per element and pivot are
-// the floor (4 clocks per wave each: 64 K^2 elements and pivots are 83 us at K = 5120), and TT = 8 needs 16 LDS values
-// for 64 updates, half of what LDS delivers meanwhile; TT = 4 needs all of it and is for matrices with too few tiles.
-// Two problems share a launch (blocks of u0 first), and with Dnew one more block puts the panel's diagonal block back.
-template <int TT>
-__global__ __launch_bounds__(256, 2)
-void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const double* __restrict__ Dnew, int K, int p0) {
-    constexpr int BT = 16 * TT, QC = 32;
-    __shared__ __attribute__((aligned(16))) double Ls[QC][BT], Rs[QC][BT];
-    int bid = blockIdx.x;
-    if (bid >= u0.tiles + u1.tiles) {                       // u0.X is the matrix of the inverse here
-        for (int e = threadIdx.x; e < PB * PB; e += 256) u0.X[(size_t)(p0 + e / PB) * K + p0 + e % PB] = Dnew[e];
-        return;
-    }
-    const bool first = bid < u0.tiles;
-    const RankUpdate& u = first ? u0 : u1;
-    if (!first) bid -= u0.tiles;
-    const int ta = (bid / u.tiles_b) * BT, tb = (bid % u.tiles_b) * BT;
-    auto place = [&](const int base, const int i) {         // i-th index that is not left out
-        const int g = base + i;
-        return (u.skip >= 0 && g >= u.skip) ? g + PB : g;
+// acc[i][k] = 16 x 16 tiles of the 16 NI x 64 elements at X; through all 64 pivots.  Operands straight from global
+// memory (L2): 64 x 64 elements per wave and 4 pivots are 16 matrix instructions (1024 clocks) on 8 loads, the next
+// four requested while they run.
+template <int NI>
+__device__ __forceinline__ void update_chain(double4v (&acc)[NI][4], const double* __restrict__ L, size_t ldl,
+                                             const double* __restrict__ R, size_t ldr, int lane, const int (&rcol)[4]) {
+    const int j = lane & 15, kq = lane >> 4;
+    double a[2][NI], b[2][4];
+    auto request = [&](const int s, const int buf) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) a[buf][i] = -L[(size_t)(4 * s + kq) * ldl + 16 * i + j];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[buf][i] = R[(size_t)(4 * s + kq) * ldr + rcol[i]];
     };
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    double x[TT][TT];
-    size_t row[TT];
-    int col[TT];
+    auto multiply = [&](const int buf) {
 #pragma unroll
-    for (int i = 0; i < TT; ++i) {
-        row[i] = (size_t)place(u.a0, ta + ty * TT + i) * u.ldx;
-        col[i] = place(u.b0, tb + tx + 16 * i);
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[i][k] = mfma_f64(a[buf][i], b[buf][k], acc[i][k]);
+    };
+    request(0, 0);
+    for (int s = 0; s < PB / 4; s += 2) {
+        request(s + 1, 1);
+        multiply(0);
+        if (s + 2 < PB / 4) request(s + 2, 0);
+        multiply(1);
     }
-#pragma unroll
-    for (int i = 0; i < TT; ++i)
-#pragma unroll
-        for (int j = 0; j < TT; ++j)
-            x[i][j] = (ta + ty * TT + i < u.rows && tb + tx + 16 * j < u.cols) ? u.X[row[i] + col[j]] : 0.0;
-    const int lc = threadIdx.x % BT, lq = threadIdx.x / BT;
-    const bool lin = ta + lc < u.rows, rin = tb + lc < u.cols;
-    const double* lp = u.L + (lin ? place(u.a0, ta + lc) : 0);
-    const double* rp = u.R + (rin ? place(u.b0, tb + lc) : 0);
-    for (int q0 = 0; q0 < PB; q0 += QC) {
-        if (q0) __syncthreads();
-#pragma unroll
-        for (int q = 0; q < QC; q += 256 / BT) {
-            Ls[q + lq][lc] = lin ? lp[(size_t)(q0 + q + lq) * u.ldl] : 0.0;
-            Rs[q + lq][lc] = rin ? rp[(size_t)(q0 + q + lq) * u.ldr] : 0.0;
-        }
-        __syncthreads();
-        for (int q = 0; q < QC; ++q) {
-            double l[TT], r[TT];
-#pragma unroll
-            for (int i = 0; i < TT; ++i) l[i] = Ls[q][ty * TT + i];
-#pragma unroll
-            for (int j = 0; j < TT; ++j) r[j] = Rs[q][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < TT; ++i)
-#pragma unroll
-                for (int j = 0; j < TT; ++j) x[i][j] = __dsub_rn(x[i][j], __dmul_rn(l[i], r[j]));
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < TT; ++i)
-#pragma unroll
-        for (int j = 0; j < TT; ++j)
-            if (ta + ty * TT + i < u.rows && tb + tx + 16 * j < u.cols) u.X[row[i] + col[j]] = x[i][j];
 }
 
-void launch_rank_updates(RankUpdate u0, RankUpdate u1, const double* Dnew, int K, int p0, hipStream_t stream) {
-    auto set = [](RankUpdate& u, int bt) {
-        u.tiles_b = (u.cols + bt - 1) / bt;
-        u.tiles = (u.rows > 0 && u.cols > 0) ? u.tiles_b * ((u.rows + bt - 1) / bt) : 0;
-    };
-    set(u0, 128);
-    set(u1, 128);
-    const int extra = Dnew ? 1 : 0;
-    if (u0.tiles + u1.tiles >= 256) {                       // at least one large tile for every compute unit
-        hipLaunchKernelGGL(rank_update_kernel<8>, dim3(u0.tiles + u1.tiles + extra), dim3(256), 0, stream, u0, u1, Dnew, K, p0);
+__device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB], double (*ds)[2]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, kq = lane >> 4;
+    if (la.prev)
+        for (int e = tid; e < PB * PB; e += 256) la.A[(size_t)(la.p0 + e / PB) * la.K + la.p0 + e % PB] = la.prev->D[e / PB][e % PB];
+    if (la.mode == 0) return;
+    const int grp = tid >> 4, pos = tid & 15;
+    double x[4][4];
+    if (la.L) {
+        double4v acc[1][4];
+        const double* X = la.A + (size_t)(la.s0 + 16 * wave) * la.K + la.s0;
+        int rcol[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            rcol[k] = 16 * k + j;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[0][k][e] = X[(size_t)(4 * e + kq) * la.K + 16 * k + j];
+        }
+        update_chain<1>(acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, rcol);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Rt[16 * wave + 4 * e + kq][16 * k + j] = acc[0][k][e];
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[v][i] = Rt[4 * grp + v][4 * pos + i];
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[v][i] = la.prev->D[4 * grp + v][4 * pos + i];
+    }
+    if (la.mode == 1) diagonal_block<true>(x, Rt, ds, la.next);
+    else diagonal_block<false>(x, Rt, ds, la.next);
+}
+
+// Block 0 looks ahead; the others take 128 x 128 elements of u0's or u1's matrix, 64 x 64 per wave.  Every element is
+// read and written once per 64 updates: 16 bytes for 64 fused multiply-adds of 0.025 ns-chip each, so HBM bounds the
+// large matrices (K = 5120: 420 MB, 85 us at the rate of a copy) and the matrix unit needs half of that.
+__global__ __launch_bounds__(256, 2)
+void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const Lookahead la) {
+    __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
+    if (blockIdx.x == 0) {
+        look_ahead(la, Rt, ds);
         return;
     }
-    set(u0, 64);
-    set(u1, 64);
-    if (u0.tiles + u1.tiles + extra)
-        hipLaunchKernelGGL(rank_update_kernel<4>, dim3(u0.tiles + u1.tiles + extra), dim3(256), 0, stream, u0, u1, Dnew, K, p0);
+    const int bid = (int)blockIdx.x - 1;
+    const RankUpdate u = (bid < u0.tiles) ? u0 : u1;
+    const int t = (bid < u0.tiles) ? bid : bid - u0.tiles;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 15, kq = lane >> 4;
+    const int ia = (t / u.tiles_b) * 128 + (wave >> 1) * 64, ib = (t % u.tiles_b) * 128 + (wave & 1) * 64;
+    if (ia >= u.rows || ib >= u.cols) return;
+    int ga = u.a0 + ia, gb = u.b0 + ib;                     // 64-blocks do not straddle what is left out
+    if (u.skip >= 0) {
+        if (ga >= u.skip) ga += PB;
+        if (gb >= u.skip) gb += PB;
+    }
+    if (ga == u.hole && gb == u.hole) return;
+    double* X = u.X + (size_t)ga * u.ldx;
+    double4v acc[4][4];
+    int col[4];
+    bool in[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        in[k] = ib + 16 * k + j < u.cols;
+        col[k] = in[k] ? gb + 16 * k + j : gb;              // a column beyond the matrix re-reads one that exists
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][k][e] = X[(size_t)(16 * i + 4 * e + kq) * u.ldx + col[k]];
+    update_chain<4>(acc, u.L + ga, u.ldl, u.R, u.ldr, lane, col);
+    // the stores' 64 addresses are formed again here; kept from the loads they would spill
+#pragma unroll
+    for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(col[k]));
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (in[k]) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) X[(size_t)(16 * i + 4 * e + kq) * u.ldx + col[k]] = acc[i][k][e];
+        }
+}
+
+void launch_rank_updates(RankUpdate u0, RankUpdate u1, const Lookahead& la, hipStream_t stream) {
+    for (RankUpdate* u : {&u0, &u1}) {
+        u->tiles_b = (u->cols + 127) / 128;
+        u->tiles = (u->rows > 0 && u->cols > 0) ? u->tiles_b * ((u->rows + 127) / 128) : 0;
+    }
+    hipLaunchKernelGGL(rank_update_kernel, dim3(1 + u0.tiles + u1.tiles), dim3(256), 0, stream, u0, u1, la);
 }
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -418,13 +636,22 @@ inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 size_t gptq_workspace_bytes(int N, int K) {
     return up256((size_t)K * K * 8) + up256((size_t)K * N * 8) + 3 * up256((size_t)K * PB * 8) + up256((size_t)PB * N * 8) +
-           up256((size_t)(PB * PB + 1) * 8);
+           2 * up256(sizeof(PanelTables)) + 256;
 }
 
 hipError_t launch_gptq_hessian(const void* x, int64_t ldx, const float* inv_lambda, int64_t M, int K, double* H,
                                hipStream_t stream) {
-    const unsigned t = (unsigned)((K + HT - 1) / HT);
-    hipLaunchKernelGGL(hessian_kernel, dim3(t, t), dim3(256), 0, stream, (const uint16_t*)x, ldx, inv_lambda, M, K, H);
+    const bool aligned = (reinterpret_cast<uintptr_t>(x) & 7) == 0 && ldx % 4 == 0;
+    const int n64 = K / 64, n32 = K / 32;
+    const unsigned tiles64 = (unsigned)(n64 * (n64 + 1) / 2), tiles32 = (unsigned)(n32 * (n32 + 1) / 2);
+    const bool large = tiles64 >= 512;                      // two 64 x 64 tiles for every compute unit
+    auto go = [&](auto kern, unsigned blocks, unsigned threads) {
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(threads), 0, stream, (const uint16_t*)x, ldx, inv_lambda, M, K, H);
+    };
+    if (large && aligned) go(hessian_kernel<4, 4, true>, tiles64, 256);
+    else if (large) go(hessian_kernel<4, 4, false>, tiles64, 256);
+    else if (aligned) go(hessian_kernel<2, 16, true>, tiles32, 1024);
+    else go(hessian_kernel<2, 16, false>, tiles32, 1024);
     return hipGetLastError();
 }
 
@@ -437,24 +664,40 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     double* Rr = (double*)p;       p += up256((size_t)K * PB * 8);     // saved scaled pivot rows     [PB][K]
     double* Hr = (double*)p;       p += up256((size_t)K * PB * 8);     // saved rows of H^-1          [PB][K]
     double* Err = (double*)p;      p += up256((size_t)PB * N * 8);     // errors of the panel         [PB][N]
-    double* Dnew = (double*)p;                                         // diagonal block of the panel [PB][PB], damping
-    double* add = Dnew + PB * PB;
+    PanelTables* tabs[2];                                              // this panel's and the next one's
+    for (auto& t : tabs) {
+        t = (PanelTables*)p;
+        p += up256(sizeof(PanelTables));
+    }
+    double* add = (double*)p;                                          // the damping term
     hipLaunchKernelGGL(diag_sum_kernel, dim3(1), dim3(256), 0, stream, H, damp, K, add);
     hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(256), 0, stream, R, H, add, N, K, A, W);
     const size_t ldk = (size_t)K, ldn = (size_t)N;
-    const RankUpdate none{A, nullptr, nullptr, ldk, ldk, ldk, 0, 0, 0, 0, -1, 1, 0};
+    const RankUpdate none{A, nullptr, nullptr, ldk, ldk, ldk, 0, 0, 0, 0, -1, -1, 1, 0};
     const int np = K / PB;
-    for (int p0 = 0; p0 < K; p0 += PB) {               // the inverse, one panel of pivots at a time
-        hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (np - 1) + 1), dim3(PTHREADS), 0, stream, A, K, p0, Lc, Rr, Dnew);
-        launch_rank_updates(RankUpdate{A, Lc, Rr, ldk, ldk, ldk, 0, K - PB, 0, K - PB, p0, 1, 0}, none, Dnew, K, p0, stream);
+    int cur = 0;                                       // tabs[cur]: the current panel's
+    hipLaunchKernelGGL(first_tables_kernel<true>, dim3(1), dim3(256), 0, stream, A, ldk, tabs[cur]);
+    for (int b = 0; b < np; ++b) {                     // the inverse, one panel of pivots at a time
+        const int p0 = b * PB;
+        if (np > 1)
+            hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (K - PB) / PVECS), dim3(256), 0, stream, A, K, p0, tabs[cur], Lc, Rr);
+        // next: the following panel, and after the last one the first panel of the visit
+        const int s0 = (b + 1 < np) ? p0 + PB : 0;
+        const bool same = s0 == p0;                    // a single panel: its own finished block is what is visited
+        const Lookahead la{A, same ? nullptr : Lc, Rr, tabs[cur], tabs[cur ^ 1], K, p0, s0, (b + 1 < np) ? 1 : 2};
+        launch_rank_updates(RankUpdate{A, Lc, Rr, ldk, ldk, ldk, 0, K - PB, 0, K - PB, p0, same ? -1 : s0, 1, 0}, none, la, stream);
+        cur ^= 1;
     }
-    for (int i0 = 0; i0 < K; i0 += PB) {               // the weights, one panel (= one 64-group) at a time
-        const int i1 = i0 + PB, rest = K - i1;
-        hipLaunchKernelGGL(visit_panel_kernel, dim3(2 * (rest / PB) + (N + PB - 1) / PB), dim3(PTHREADS), 0, stream,
-                           A, W, N, K, i0, Lc, Hr, Rr, Err, qw, sw);
-        if (rest > 0)                                   // the deferred updates of everything behind the panel
-            launch_rank_updates(RankUpdate{W, Hr, Err, ldn, ldk, ldn, i1, rest, 0, N, -1, 1, 0},
-                                RankUpdate{A, Lc, Rr, ldk, ldk, ldk, i1, rest, i1, rest, -1, 1, 0}, nullptr, K, i0, stream);
+    for (int b = 0; b < np; ++b) {                     // the weights, one panel (= one 64-group) at a time
+        const int i0 = b * PB, i1 = i0 + PB, rest = K - i1;
+        hipLaunchKernelGGL(visit_panel_kernel, dim3(2 * (rest / PVECS) + (N + PVECS - 1) / PVECS), dim3(256), 0, stream,
+                           A, W, N, K, i0, tabs[cur], Lc, Hr, Rr, Err, qw, sw);
+        if (rest > 0) {                                // the deferred updates of everything behind the panel
+            const Lookahead la{A, Lc, Rr, nullptr, tabs[cur ^ 1], K, 0, i1, 2};
+            launch_rank_updates(RankUpdate{W, Hr, Err, ldn, ldk, ldn, i1, rest, 0, N, -1, -1, 1, 0},
+                                RankUpdate{A, Lc, Rr, ldk, ldk, ldk, i1, rest, i1, rest, -1, i1, 1, 0}, la, stream);
+        }
+        cur ^= 1;
     }
     return hipGetLastError();
 }
