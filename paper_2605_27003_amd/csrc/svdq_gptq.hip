@@ -10,6 +10,8 @@
 // sequential sum.  The published implementation factors H^-1 once (Cholesky) and reads the same numbers off the
 // factor; this form trades that for elementwise kernels: K^3 updates for the inverse, K^3 / 3 of H^-1 and K^2 N / 2
 // of the weights during the visit, taken in panels of 64 pivots (below) so that the matrices cross HBM once per panel.
+#include <type_traits>
+
 #include "svdq_dev.h"
 #include "svdq_kernels.h"
 
@@ -205,15 +207,26 @@ __device__ __forceinline__ double row_turn(double v) { return dpp64<0x120 + 15>(
 
 // a / d, correctly rounded, from y = RN(1 / d): two corrections of a y.  The first makes the quotient faithful, and
 // from a faithful quotient and a correctly rounded reciprocal the second gives the rounded quotient (Markstein's
-// theorem), as long as nothing leaves the exponent range: there the division itself.
-__device__ __forceinline__ bool within(double v, double lo, double hi) { return fabs(v) >= lo && fabs(v) <= hi; }
-__device__ __forceinline__ double divide_by(double a, double d, double y) {
+// theorem), as long as nothing leaves the exponent range; `bad` collects whether anything may have, and the callers
+// then repeat the whole panel with SLOW, the division itself.  (A branch at every division would cost more than the
+// division: it ends the overlap of one vector's chain with the next one's.)  d and y: reciprocal_of below.
+template <bool SLOW>
+__device__ __forceinline__ double divide_by(double a, double d, double y, bool& bad) {
+    if (SLOW) return __ddiv_rn(a, d);
     double q = a * y;
     q = __builtin_fma(__builtin_fma(-d, q, a), y, q);
     q = __builtin_fma(__builtin_fma(-d, q, a), y, q);
-    if (!(within(d, 0x1p-200, 0x1p200) && (a == 0.0 || within(a, 0x1p-700, 0x1p700)))) q = __ddiv_rn(a, d);
+    const uint32_t ex = (uint32_t)(__builtin_bit_cast(uint64_t, q) >> 52) & 0x7ffu;     // 2^-600 .. 2^600, or 0 / d
+    bad |= (ex - 423u > 1200u) && !(q == 0.0 && a == 0.0);
     return q;
 }
+// RN(1 / d), or NaN (which every quotient then is: bad) where d is too large or small for divide_by
+__device__ __forceinline__ double reciprocal_of(double d) {
+    const double y = __ddiv_rn(1.0, d);
+    return (fabs(d) >= 0x1p-200 && fabs(d) <= 0x1p200) ? y : __builtin_nan("");
+}
+// wait for this wave's LDS traffic, then for the other waves: stores to global memory stay in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // What a panel kernel needs of its diagonal block D (K-major q = pivot inside the panel)
 struct PanelTables {
@@ -226,9 +239,10 @@ struct PanelTables {
 // The diagonal block through its 64 pivots, 256 threads: lane group g = tid / 16 holds rows 4 g .. 4 g + 3, so pivot
 // 4 it + k is row k of group it.  INV: in-place Gauss-Jordan inverse (see below); otherwise only the rows and columns
 // behind the pivot are updated (row q of D is then the row as it stood at pivot q).  Rt: PB x PB in LDS, ds: 2 in LDS.
-template <bool INV>
-__device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], PanelTables* __restrict__ out) {
+template <bool INV, bool SLOW>
+__device__ __forceinline__ bool diagonal_pass(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], PanelTables* __restrict__ out) {
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
+    bool bad = false;
     for (int it = 0; it < 16; ++it) {
         const int sl = (pos + it) & 15;
 #pragma unroll
@@ -238,19 +252,19 @@ __device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[P
 #pragma unroll
             for (int v = 0; v < 4; ++v) c[v] = row_first(x[v][k]);
             if (grp == it) {                              // this group's row k is the pivot's
-                const double d = c[k], y = __ddiv_rn(1.0, d);
+                const double d = c[k], y = reciprocal_of(d);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) Rt[q][4 * sl + j] = divide_by(x[k][j], d, y);
+                for (int j = 0; j < 4; ++j) Rt[q][4 * sl + j] = divide_by<SLOW>(x[k][j], d, y, bad);
                 if (pos == 0) {
-                    ds[q][0] = out->d[q] = d;
-                    ds[q][1] = out->y[q] = y;
+                    ds[q][0] = d;
+                    ds[q][1] = y;
                 }
             }
             if (pos == 0) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) out->C[q][4 * grp + v] = c[v];
             }
-            __syncthreads();
+            lds_barrier();
             const double d = ds[q][0], y = ds[q][1];
             double r[4];
 #pragma unroll
@@ -259,15 +273,15 @@ __device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[P
             for (int v = 0; v < 4; ++v) {
                 if (INV) {
                     const bool isq = v == k && grp == it;
-                    const double e = isq ? y : divide_by(-c[v], d, y);
+                    const double e = divide_by<SLOW>(isq ? 1.0 : -c[v], d, y, bad);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) x[v][j] = isq ? r[j] : __builtin_fma(-c[v], r[j], x[v][j]);
                     x[v][k] = (pos == 0) ? e : x[v][k];
-                } else if (4 * grp + v > q) {
+                } else {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const double u = __builtin_fma(-c[v], r[j], x[v][j]);
-                        x[v][j] = (4 * sl + j > q) ? u : x[v][j];
+                        x[v][j] = (4 * grp + v > q && 4 * sl + j > q) ? u : x[v][j];
                     }
                 }
             }
@@ -277,6 +291,24 @@ __device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[P
 #pragma unroll
             for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
     }
+    return bad;
+}
+template <bool INV>
+__device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], PanelTables* __restrict__ out) {
+    const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out->D[4 * grp + v][4 * pos + j] = x[v][j];       // kept for a second pass
+    if (__syncthreads_or(diagonal_pass<INV, false>(x, Rt, ds, out))) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[v][j] = out->D[4 * grp + v][4 * pos + j];
+        __syncthreads();
+        diagonal_pass<INV, true>(x, Rt, ds, out);
+        __syncthreads();
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -284,6 +316,10 @@ __device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[P
             out->D[4 * grp + v][4 * pos + j] = x[v][j];
             out->R[4 * grp + v][4 * pos + j] = Rt[4 * grp + v][4 * pos + j];
         }
+    if (threadIdx.x < PB) {
+        out->d[threadIdx.x] = ds[threadIdx.x][0];
+        out->y[threadIdx.x] = ds[threadIdx.x][1];
+    }
 }
 
 // The panel's first tables: nothing precedes them that could carry them along.
@@ -325,42 +361,66 @@ void gj_panel_kernel(double* __restrict__ A, int K, int p0, const PanelTables* _
     for (int v = 0; v < PV; ++v) {
         idx[v] = ((int)blockIdx.x - (rows ? 0 : nb)) * PVECS + (grp >> 2) * 4 * PV + v * 4 + (grp & 3);
         if (idx[v] >= p0) idx[v] += PB;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            x[v][j] = rows ? A[(size_t)idx[v] * K + p0 + 4 * pos + j] : A[(size_t)(p0 + 4 * pos + j) * K + idx[v]];
     }
+    auto load = [&]() {
+#pragma unroll
+        for (int v = 0; v < PV; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                x[v][j] = rows ? A[(size_t)idx[v] * K + p0 + 4 * pos + j] : A[(size_t)(p0 + 4 * pos + j) * K + idx[v]];
+    };
+    load();
     load_table(tab, rows ? tb->R : tb->C);
     if (threadIdx.x < PB) {
         ds[threadIdx.x][0] = tb->d[threadIdx.x];
         ds[threadIdx.x][1] = tb->y[threadIdx.x];
     }
     __syncthreads();
-    double* save = rows ? LT : Rr;
-    for (int it = 0; it < 16; ++it) {
-        const int sl = (pos + it) & 15;
+    double* const save = rows ? LT : Rr;
+    auto pass = [&](auto ROWS, auto SLOWC) {
+        constexpr bool R = decltype(ROWS)::value;
+        bool bad = false;
+        for (int it = 0; it < 16; ++it) {
+            const int sl = (pos + it) & 15;
+            double f[4][PV];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int q = 4 * it + k;
-            const double d = ds[q][0], y = ds[q][1];
-            double t[4];
+            for (int k = 0; k < 4; ++k) {
+                const int q = 4 * it + k;
+                const double d = ds[q][0], y = ds[q][1];
+                double t[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
+                for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
 #pragma unroll
-            for (int v = 0; v < PV; ++v) {
-                const double c = row_first(x[v][k]);
-                const double e = divide_by(rows ? -c : c, d, y);
-                const double f = rows ? c : e;
-                if (pos == 0) save[(size_t)q * K + idx[v]] = f;
+                for (int v = 0; v < PV; ++v) {
+                    const double c = row_first(x[v][k]);
+                    const double e = divide_by<decltype(SLOWC)::value>(R ? -c : c, d, y, bad);
+                    f[k][v] = R ? c : e;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) x[v][j] = __builtin_fma(-f, t[j], x[v][j]);
-                x[v][k] = (pos == 0) ? e : x[v][k];
+                    for (int j = 0; j < 4; ++j) x[v][j] = __builtin_fma(-f[k][v], t[j], x[v][j]);
+                    x[v][k] = (pos == 0) ? e : x[v][k];
+                }
             }
+            if (pos == 0) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int v = 0; v < PV; ++v) save[(size_t)(4 * it + k) * K + idx[v]] = f[k][v];
+            }
+#pragma unroll
+            for (int v = 0; v < PV; ++v)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
         }
-#pragma unroll
-        for (int v = 0; v < PV; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
-    }
+        return bad;
+    };
+    auto run = [&](auto ROWS) {
+        if (__any(pass(ROWS, std::false_type{}))) {
+            load();
+            pass(ROWS, std::true_type{});
+        }
+    };
+    if (rows) run(std::true_type{});
+    else run(std::false_type{});
 #pragma unroll
     for (int v = 0; v < PV; ++v)
 #pragma unroll
@@ -391,14 +451,19 @@ void visit_panel_kernel(const double* __restrict__ A, const double* __restrict__
     for (int v = 0; v < PV; ++v) {
         idx[v] = (role < 2 ? i1 : 0) + ((int)blockIdx.x - role * nr) * PVECS + (grp >> 2) * 4 * PV + v * 4 + (grp & 3);
         live[v] = role < 2 || idx[v] < N;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            x[v][j] = 0.0;
-            if (role == 0) x[v][j] = A[(size_t)idx[v] * K + i0 + 4 * pos + j];
-            if (role == 1) x[v][j] = A[(size_t)(i0 + 4 * pos + j) * K + idx[v]];
-            if (role == 2 && live[v]) x[v][j] = W[(size_t)(i0 + 4 * pos + j) * N + idx[v]];
-        }
     }
+    auto load = [&]() {
+#pragma unroll
+        for (int v = 0; v < PV; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                x[v][j] = 0.0;
+                if (role == 0) x[v][j] = A[(size_t)idx[v] * K + i0 + 4 * pos + j];
+                if (role == 1) x[v][j] = A[(size_t)(i0 + 4 * pos + j) * K + idx[v]];
+                if (role == 2 && live[v]) x[v][j] = W[(size_t)(i0 + 4 * pos + j) * N + idx[v]];
+            }
+    };
+    load();
     load_table(tab, role == 0 ? tb->R : role == 1 ? tb->C : tb->D);
     if (threadIdx.x < PB) {
         ds[threadIdx.x][0] = tb->d[threadIdx.x];
@@ -415,70 +480,98 @@ void visit_panel_kernel(const double* __restrict__ A, const double* __restrict__
             s[v] = __fdiv_rn((float)a, 7.0f);
             if (pos == 0 && live[v]) sw[(size_t)(i0 >> 6) * N + idx[v]] = s[v];
         }
+        auto pass = [&](auto SLOWC) {
+            bool bad = false;
+            for (int it = 0; it < 16; ++it) {
+                const int sl = (pos + it) & 15;
+                uint32_t codes[PV] = {};
+                double e[4][PV];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int q = 4 * it + k;
+                    const double d = ds[q][0], y = ds[q][1];
+                    double t[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
+#pragma unroll
+                    for (int v = 0; v < PV; ++v) {
+                        const double w = row_first(x[v][k]);
+                        float c = fminf(fmaxf(rintf(__fdiv_rn((float)w, s[v])), -8.0f), 7.0f);
+                        c = (s[v] > 0.0f) ? c : 0.0f;
+                        codes[v] |= ((uint32_t)(int)c & 15u) << (4 * k);
+                        e[k][v] = divide_by<decltype(SLOWC)::value>(__builtin_fma(-(double)c, (double)s[v], w), d, y, bad);   // code x scale is exact
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const double u = __builtin_fma(-t[j], e[k][v], x[v][j]);
+                            x[v][j] = (4 * sl + j > q) ? u : x[v][j];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < PV; ++v) {
+                    if (pos == 0 && live[v]) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) Err[(size_t)(4 * it + k) * N + idx[v]] = e[k][v];
+                        // four codes: two bytes, low nibble = even index
+                        *reinterpret_cast<uint16_t*>(qw + (size_t)idx[v] * (K >> 1) + (i0 >> 1) + 2 * it) = (uint16_t)codes[v];
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
+                }
+            }
+            return bad;
+        };
+        if (__any(pass(std::false_type{}))) {
+            load();
+            pass(std::true_type{});
+        }
+        return;
+    }
+    double* const save = role == 0 ? HcT : HrT;
+    auto pass = [&](auto COLS, auto SLOWC) {
+        constexpr bool C = decltype(COLS)::value;
+        bool bad = false;
         for (int it = 0; it < 16; ++it) {
             const int sl = (pos + it) & 15;
-            uint32_t codes[PV] = {};
+            double c[4][PV], f[4][PV];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int q = 4 * it + k;
-                const double d = ds[q][0], y = ds[q][1];
                 double t[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
 #pragma unroll
                 for (int v = 0; v < PV; ++v) {
-                    const double w = row_first(x[v][k]);
-                    float c = 0.0f;
-                    if (s[v] > 0.0f) c = fminf(fmaxf(rintf(__fdiv_rn((float)w, s[v])), -8.0f), 7.0f);
-                    codes[v] |= ((uint32_t)(int)c & 15u) << (4 * k);
-                    const double e = divide_by(__builtin_fma(-(double)c, (double)s[v], w), d, y);    // code x scale is exact
-                    if (pos == 0 && live[v]) Err[(size_t)q * N + idx[v]] = e;
+                    c[k][v] = row_first(x[v][k]);
+                    f[k][v] = C ? divide_by<decltype(SLOWC)::value>(c[k][v], ds[q][0], ds[q][1], bad) : c[k][v];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const double u = __builtin_fma(-t[j], e, x[v][j]);
+                        const double u = __builtin_fma(-f[k][v], t[j], x[v][j]);
                         x[v][j] = (4 * sl + j > q) ? u : x[v][j];
                     }
                 }
             }
+            if (pos == 0) {
 #pragma unroll
-            for (int v = 0; v < PV; ++v) {
-                if (pos == 0 && live[v])                   // four codes: two bytes, low nibble = even index
-                    *reinterpret_cast<uint16_t*>(qw + (size_t)idx[v] * (K >> 1) + (i0 >> 1) + 2 * it) = (uint16_t)codes[v];
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int v = 0; v < PV; ++v) {
+                        save[(size_t)(4 * it + k) * K + idx[v]] = c[k][v];
+                        if (C) T[(size_t)(4 * it + k) * K + idx[v]] = f[k][v];
+                    }
+            }
+#pragma unroll
+            for (int v = 0; v < PV; ++v)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
-            }
         }
-        return;
-    }
-    double* save = role == 0 ? HcT : HrT;
-    for (int it = 0; it < 16; ++it) {
-        const int sl = (pos + it) & 15;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int q = 4 * it + k;
-            double t[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
-#pragma unroll
-            for (int v = 0; v < PV; ++v) {
-                const double c = row_first(x[v][k]);
-                double f = c;
-                if (role == 1) f = divide_by(c, ds[q][0], ds[q][1]);
-                if (pos == 0) {
-                    save[(size_t)q * K + idx[v]] = c;
-                    if (role == 1) T[(size_t)q * K + idx[v]] = f;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const double u = __builtin_fma(-f, t[j], x[v][j]);
-                    x[v][j] = (4 * sl + j > q) ? u : x[v][j];
-                }
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < PV; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
+        return bad;
+    };
+    if (role == 0) {
+        pass(std::false_type{}, std::false_type{});
+    } else if (__any(pass(std::true_type{}, std::false_type{}))) {
+        load();
+        pass(std::true_type{}, std::true_type{});
     }
 }
 
@@ -491,6 +584,7 @@ struct RankUpdate {
     size_t ldx, ldl, ldr;
     int a0, rows, b0, cols, skip, hole;
     int tiles_b, tiles;          // 128 x 128 tiles along b, and in all
+    bool backwards;              // every other update walks its tiles backwards, first through what is still in the caches
 };
 // The next panel's diagonal block (at index s0 of A), for the first block of a rank update: brought up to date with L
 // and R (none: it is already, as D), then through its own pivots (mode 1: inverse, 2: visit) into `next`.  Also puts the
@@ -503,25 +597,34 @@ struct Lookahead {
     int K, p0, s0, mode;
 };
 
-// acc[i][k] = 16 x 16 tiles of the 16 NI x 64 elements at X; through all 64 pivots.  Operands straight from global
-// memory (L2): 64 x 64 elements per wave and 4 pivots are 16 matrix instructions (1024 clocks) on 8 loads, the next
-// four requested while they run.
-template <int NI>
+// acc[i][k]: a wave's 16 NI x 64 elements through all 64 pivots; lane (j, kq) = (l % 16, l / 16) holds in acc[i][k][e]
+// row 16 i + 4 e + kq, column wave_col(j, k): two neighbouring columns per lane, so that a row's accesses are 256
+// contiguous bytes of 16 bytes a lane.  Operands straight from global memory (L2): 64 x 64 elements per wave and 4
+// pivots are 16 matrix instructions (1024 clocks) on 6 loads, the next four pivots' requested while they run.
+__device__ __forceinline__ int wave_col(int j, int k) { return 32 * (k >> 1) + 2 * j + (k & 1); }
+// the two values at p[0], p[1] (second: p + d1, for a matrix whose rows are not 16-byte aligned)
+template <bool PAIR>
+__device__ __forceinline__ double2 load2(const double* p, int d1) {
+    if constexpr (PAIR) return *reinterpret_cast<const double2*>(p);
+    return double2{p[0], p[d1]};
+}
+template <int NI, bool PAIR>
 __device__ __forceinline__ void update_chain(double4v (&acc)[NI][4], const double* __restrict__ L, size_t ldl,
-                                             const double* __restrict__ R, size_t ldr, int lane, const int (&rcol)[4]) {
+                                             const double* __restrict__ R, size_t ldr, int lane, const int (&col)[2], const int (&d1)[2]) {
     const int j = lane & 15, kq = lane >> 4;
-    double a[2][NI], b[2][4];
+    double a[2][NI];
+    double2 b[2][2];
     auto request = [&](const int s, const int buf) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) a[buf][i] = -L[(size_t)(4 * s + kq) * ldl + 16 * i + j];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b[buf][i] = R[(size_t)(4 * s + kq) * ldr + rcol[i]];
+        for (int i = 0; i < 2; ++i) b[buf][i] = load2<PAIR>(R + (size_t)(4 * s + kq) * ldr + col[i], d1[i]);
     };
     auto multiply = [&](const int buf) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc[i][k] = mfma_f64(a[buf][i], b[buf][k], acc[i][k]);
+            for (int k = 0; k < 4; ++k) acc[i][k] = mfma_f64(a[buf][i], (k & 1) ? b[buf][k >> 1].y : b[buf][k >> 1].x, acc[i][k]);
     };
     request(0, 0);
     for (int s = 0; s < PB / 4; s += 2) {
@@ -542,18 +645,16 @@ __device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB]
     if (la.L) {
         double4v acc[1][4];
         const double* X = la.A + (size_t)(la.s0 + 16 * wave) * la.K + la.s0;
-        int rcol[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            rcol[k] = 16 * k + j;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[0][k][e] = X[(size_t)(4 * e + kq) * la.K + 16 * k + j];
-        }
-        update_chain<1>(acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, rcol);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) Rt[16 * wave + 4 * e + kq][16 * k + j] = acc[0][k][e];
+            for (int e = 0; e < 4; ++e) acc[0][k][e] = X[(size_t)(4 * e + kq) * la.K + wave_col(j, k)];
+        const int col[2] = {2 * j, 32 + 2 * j}, d1[2] = {1, 1};
+        update_chain<1, true>(acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, col, d1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Rt[16 * wave + 4 * e + kq][wave_col(j, k)] = acc[0][k][e];
         __syncthreads();
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -573,6 +674,7 @@ __device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB]
 // Block 0 looks ahead; the others take 128 x 128 elements of u0's or u1's matrix, 64 x 64 per wave.  Every element is
 // read and written once per 64 updates: 16 bytes for 64 fused multiply-adds of 0.025 ns-chip each, so HBM bounds the
 // large matrices (K = 5120: 420 MB, 85 us at the rate of a copy) and the matrix unit needs half of that.
+template <bool PAIR>
 __global__ __launch_bounds__(256, 2)
 void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const Lookahead la) {
     __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
@@ -582,7 +684,8 @@ void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const Lookahea
     }
     const int bid = (int)blockIdx.x - 1;
     const RankUpdate u = (bid < u0.tiles) ? u0 : u1;
-    const int t = (bid < u0.tiles) ? bid : bid - u0.tiles;
+    int t = (bid < u0.tiles) ? bid : bid - u0.tiles;
+    if (u.backwards) t = u.tiles - 1 - t;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 15, kq = lane >> 4;
     const int ia = (t / u.tiles_b) * 128 + (wave >> 1) * 64, ib = (t % u.tiles_b) * 128 + (wave & 1) * 64;
@@ -595,39 +698,58 @@ void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const Lookahea
     if (ga == u.hole && gb == u.hole) return;
     double* X = u.X + (size_t)ga * u.ldx;
     double4v acc[4][4];
-    int col[4];
-    bool in[4];
+    int col[2], d1[2];                                      // a column beyond the matrix re-reads one that exists
+    bool in[2][2];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        in[k] = ib + 16 * k + j < u.cols;
-        col[k] = in[k] ? gb + 16 * k + j : gb;              // a column beyond the matrix re-reads one that exists
+    for (int k = 0; k < 2; ++k) {
+        const int c = ib + 32 * k + 2 * j;
+        in[k][0] = c < u.cols;
+        in[k][1] = c + 1 < u.cols;
+        col[k] = in[k][0] ? gb + 32 * k + 2 * j : gb;
+        d1[k] = in[k][1] ? 1 : 0;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][k][e] = X[(size_t)(16 * i + 4 * e + kq) * u.ldx + col[k]];
-    update_chain<4>(acc, u.L + ga, u.ldl, u.R, u.ldr, lane, col);
-    // the stores' 64 addresses are formed again here; kept from the loads they would spill
+            for (int k = 0; k < 2; ++k) {
+                const double2 v = load2<PAIR>(X + (size_t)(16 * i + 4 * e + kq) * u.ldx + col[k], d1[k]);
+                acc[i][2 * k][e] = v.x;
+                acc[i][2 * k + 1][e] = v.y;
+            }
+    update_chain<4, PAIR>(acc, u.L + ga, u.ldl, u.R, u.ldr, lane, col, d1);
+    // the stores' addresses are formed again here; kept from the loads they would spill
 #pragma unroll
-    for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(col[k]));
+    for (int k = 0; k < 2; ++k) asm volatile("" : "+v"(col[k]));
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (in[k]) {
+    for (int k = 0; k < 2; ++k)
+        if (in[k][0]) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) X[(size_t)(16 * i + 4 * e + kq) * u.ldx + col[k]] = acc[i][k][e];
+                for (int e = 0; e < 4; ++e) {
+                    double* to = X + (size_t)(16 * i + 4 * e + kq) * u.ldx + col[k];
+                    if constexpr (PAIR) {
+                        *reinterpret_cast<double2*>(to) = double2{acc[i][2 * k][e], acc[i][2 * k + 1][e]};
+                    } else {
+                        to[0] = acc[i][2 * k][e];
+                        if (in[k][1]) to[1] = acc[i][2 * k + 1][e];
+                    }
+                }
         }
 }
 
-void launch_rank_updates(RankUpdate u0, RankUpdate u1, const Lookahead& la, hipStream_t stream) {
+void launch_rank_updates(RankUpdate u0, RankUpdate u1, const Lookahead& la, bool backwards, hipStream_t stream) {
+    bool pair = true;
     for (RankUpdate* u : {&u0, &u1}) {
         u->tiles_b = (u->cols + 127) / 128;
         u->tiles = (u->rows > 0 && u->cols > 0) ? u->tiles_b * ((u->rows + 127) / 128) : 0;
+        u->backwards = backwards;
+        pair = pair && u->ldx % 2 == 0 && u->ldr % 2 == 0;
     }
-    hipLaunchKernelGGL(rank_update_kernel, dim3(1 + u0.tiles + u1.tiles), dim3(256), 0, stream, u0, u1, la);
+    auto kern = pair ? rank_update_kernel<true> : rank_update_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(1 + u0.tiles + u1.tiles), dim3(256), 0, stream, u0, u1, la);
 }
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -673,7 +795,7 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     hipLaunchKernelGGL(diag_sum_kernel, dim3(1), dim3(256), 0, stream, H, damp, K, add);
     hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(256), 0, stream, R, H, add, N, K, A, W);
     const size_t ldk = (size_t)K, ldn = (size_t)N;
-    const RankUpdate none{A, nullptr, nullptr, ldk, ldk, ldk, 0, 0, 0, 0, -1, -1, 1, 0};
+    const RankUpdate none{A, nullptr, nullptr, ldk, ldk, ldk, 0, 0, 0, 0, -1, -1, 1, 0, false};
     const int np = K / PB;
     int cur = 0;                                       // tabs[cur]: the current panel's
     hipLaunchKernelGGL(first_tables_kernel<true>, dim3(1), dim3(256), 0, stream, A, ldk, tabs[cur]);
@@ -685,7 +807,7 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
         const int s0 = (b + 1 < np) ? p0 + PB : 0;
         const bool same = s0 == p0;                    // a single panel: its own finished block is what is visited
         const Lookahead la{A, same ? nullptr : Lc, Rr, tabs[cur], tabs[cur ^ 1], K, p0, s0, (b + 1 < np) ? 1 : 2};
-        launch_rank_updates(RankUpdate{A, Lc, Rr, ldk, ldk, ldk, 0, K - PB, 0, K - PB, p0, same ? -1 : s0, 1, 0}, none, la, stream);
+        launch_rank_updates(RankUpdate{A, Lc, Rr, ldk, ldk, ldk, 0, K - PB, 0, K - PB, p0, same ? -1 : s0, 1, 0, false}, none, la, b & 1, stream);
         cur ^= 1;
     }
     for (int b = 0; b < np; ++b) {                     // the weights, one panel (= one 64-group) at a time
@@ -694,8 +816,8 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
                            A, W, N, K, i0, tabs[cur], Lc, Hr, Rr, Err, qw, sw);
         if (rest > 0) {                                // the deferred updates of everything behind the panel
             const Lookahead la{A, Lc, Rr, nullptr, tabs[cur ^ 1], K, 0, i1, 2};
-            launch_rank_updates(RankUpdate{W, Hr, Err, ldn, ldk, ldn, i1, rest, 0, N, -1, -1, 1, 0},
-                                RankUpdate{A, Lc, Rr, ldk, ldk, ldk, i1, rest, i1, rest, -1, i1, 1, 0}, la, stream);
+            launch_rank_updates(RankUpdate{W, Hr, Err, ldn, ldk, ldn, i1, rest, 0, N, -1, -1, 1, 0, false},
+                                RankUpdate{A, Lc, Rr, ldk, ldk, ldk, i1, rest, i1, rest, -1, i1, 1, 0, false}, la, b & 1, stream);
         }
         cur ^= 1;
     }
