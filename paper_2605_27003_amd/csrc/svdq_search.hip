@@ -4,7 +4,7 @@
 // compares these sums; this file is the one extra kernel it needs.
 //
 // Deterministic: NPART blocks each own a fixed, strided set of 8-element chunks and sum them in a fixed
-// order in binary64; a second one-block kernel adds the NPART partial sums in index order.
+// order in binary64; a second one-block kernel adds the NPART partial sums, in a fixed order too.
 //
 // Also here: the expectation over a bin's calibration steps (the same reduction ADDED to a device accumulator) and
 // the arg-min over the candidates, so that a C caller can run the whole search without host arithmetic.
@@ -53,14 +53,22 @@ void sq_error_partial_kernel(const uint16_t* __restrict__ yref, int64_t ldr, con
     if (threadIdx.x == 0) partials[blockIdx.x] = red[0];
 }
 
-// ADD = true: out[0] += the sum (one thread, so the accumulation over calls on a stream is deterministic)
+// The NPART partial sums in a fixed order (a thread's four, then a tree): one block.  One thread adding them one after
+// the other waited for 1024 loads and additions in turn (57 us).  ADD = true: out[0] += the sum, so the accumulation
+// over calls on a stream is deterministic.
 template <bool ADD>
-__global__ void sq_error_final_kernel(const double* __restrict__ partials, int n, double* __restrict__ out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < n; ++i) s += partials[i];
-        out[0] = ADD ? out[0] + s : s;
+__global__ __launch_bounds__(256)
+void sq_error_final_kernel(const double* __restrict__ partials, double* __restrict__ out) {
+    static_assert(SQ_ERROR_PARTIALS == 1024, "four per thread");
+    __shared__ double red[256];
+    const int t = threadIdx.x;
+    red[t] = (partials[t] + partials[t + 256]) + (partials[t + 512] + partials[t + 768]);
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (t < w) red[t] += red[t + w];
+        __syncthreads();
     }
+    if (t == 0) out[0] = ADD ? out[0] + red[0] : red[0];
 }
 
 // idx[row] = first index of the smallest entry of table[row][0..ncols): one thread per row
@@ -101,9 +109,9 @@ hipError_t launch_sq_error(const void* yref, int64_t ldr, const void* y, int64_t
     hipLaunchKernelGGL(sq_error_partial_kernel, dim3(SQ_ERROR_PARTIALS), dim3(256), 0, stream,
                        (const uint16_t*)yref, ldr, (const uint16_t*)y, ldy, M, N, workspace);
     if (add)
-        hipLaunchKernelGGL(sq_error_final_kernel<true>, dim3(1), dim3(64), 0, stream, workspace, SQ_ERROR_PARTIALS, out);
+        hipLaunchKernelGGL(sq_error_final_kernel<true>, dim3(1), dim3(256), 0, stream, workspace, out);
     else
-        hipLaunchKernelGGL(sq_error_final_kernel<false>, dim3(1), dim3(64), 0, stream, workspace, SQ_ERROR_PARTIALS, out);
+        hipLaunchKernelGGL(sq_error_final_kernel<false>, dim3(1), dim3(256), 0, stream, workspace, out);
     return hipGetLastError();
 }
 
