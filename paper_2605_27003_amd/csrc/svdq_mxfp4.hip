@@ -24,6 +24,7 @@
 #include "svdq_epilogue.h"
 #include "svdq_kernels.h"
 #include "svdq_lds.h"
+#include "svdq_quant_dev.h"
 #include "svdq_tiles.h"
 
 namespace svdq {
@@ -35,10 +36,6 @@ typedef int int8v __attribute__((ext_vector_type(8)));
 // ------------------------------------------------------------------------------------------------
 // kernel (a'): smooth, per-token per-32-block shared exponent, E2M1 codes, h = x^ L1
 // ------------------------------------------------------------------------------------------------
-constexpr int QROWS = 64;     // token rows per block
-constexpr int QWAVES = 4;     // K is split between the waves by stage (two 64-groups = 128 k)
-constexpr int QHPART_BYTES = QWAVES * QROWS * 33 * 4;
-
 // One 32-row block of one group: this lane's 32 values -> 16 bytes of codes and the block's E8M0 byte.
 __device__ __forceinline__ void quantize_block_mx(const uint4 (&xv)[4], const float* __restrict__ il_lds, float rho,
                                                   uint4& codes, uint32_t& e8) {
@@ -82,8 +79,9 @@ __device__ __forceinline__ void quantize_block_mx(const uint4 (&xv)[4], const fl
 // Outputs: qx [K/64][M][32 B] (as the int4 path) and sxe [ceil(K/128)][M][2][2] bytes: for token m and stage s
 // (groups 2s, 2s+1) the two bytes [half h][group j] are the E8M0 scales of MX block 2 (2s + j) + h.
 // GELU = true: every x is replaced by bf16(gelu(x)) as it arrives (svdq_act.h).
-template <bool LOWRANK, bool GELU>
-__global__ __launch_bounds__(256, 2)
+// A block takes 32 RB rows with WV waves (quant_geom); K is split between the waves by stage (two 64-groups = 128 k).
+template <bool LOWRANK, bool GELU, int RB, int WV>
+__global__ __launch_bounds__(64 * WV, WV == 4 ? 2 : 1)
 void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                         const float* __restrict__ inv_lambda, float rho,
                         const uint4* __restrict__ l1p, int64_t M, int K, int r,
@@ -98,44 +96,45 @@ void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
     const int hf = lane >> 5;
     const int ng = K >> 6;
     const int nstages = (ng + 1) >> 1;
-    const int64_t row0 = (int64_t)blockIdx.x * QROWS;
+    constexpr int ROWS = 32 * RB;
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
 
-    for (int i = tid * 4; i < K; i += 1024)
+    for (int i = tid * 4; i < K; i += 256 * WV)
         *reinterpret_cast<float4*>(il_s + i) = *reinterpret_cast<const float4*>(inv_lambda + i);
 
-    float16v acc[2];
+    float16v acc[RB];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < RB; ++b)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[b][i] = 0.0f;
 
-    const uint16_t* xrow[2];
-    int64_t rows[2];
+    const uint16_t* xrow[RB];
+    int64_t rows[RB];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < RB; ++b) {
         rows[b] = row0 + 32 * b + rr;
         const int64_t rowc = rows[b] < M ? rows[b] : M - 1;
         xrow[b] = x + rowc * ldx + hf * 32;
     }
 
-    // round rd of this wave = group 2 (wave + 4 (rd / 2)) + rd % 2: the two groups of a stage follow each other
+    // round rd of this wave = group 2 (wave + WV (rd / 2)) + rd % 2: the two groups of a stage follow each other
     // so that their two scale bytes leave as one 16-bit store.  Software pipeline as in the int4 kernel: the
     // next round's x is in flight while the current one is processed; two register buffers alternate.
-    auto group_of = [&](const int rd) { return 2 * (wave + QWAVES * (rd >> 1)) + (rd & 1); };
-    const int my_stages = (nstages > wave) ? (nstages - wave + QWAVES - 1) / QWAVES : 0;
+    auto group_of = [&](const int rd) { return 2 * (wave + WV * (rd >> 1)) + (rd & 1); };
+    const int my_stages = (nstages > wave) ? (nstages - wave + WV - 1) / WV : 0;
     const int rounds = 2 * my_stages;
-    uint4 xa[2][4], xb[2][4];
+    uint4 xa[RB][4], xb[RB][4];
     if (rounds > 0) {
         const int g0 = group_of(0);                      // exists: stage `wave` exists, so group 2 wave < ng
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < RB; ++b)
 #pragma unroll
             for (int s = 0; s < 4; ++s) xa[b][s] = reinterpret_cast<const uint4*>(xrow[b] + g0 * 64)[s];
     }
     __syncthreads();
 
-    uint32_t e_first[2] = {0u, 0u};
-    auto round_body = [&](const int rd, uint4 (&xc)[2][4], uint4 (&xn)[2][4], auto PAR) {
+    uint32_t e_first[RB] = {};
+    auto round_body = [&](const int rd, uint4 (&xc)[RB][4], uint4 (&xn)[RB][4], auto PAR) {
         constexpr int parity = decltype(PAR)::value;
         const int g = group_of(rd);
         const bool exists = g < ng;                      // only the second group of the last stage can be missing
@@ -153,7 +152,7 @@ void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
         int gn = (rd + 1 < rounds) ? group_of(rd + 1) : gl;
         if (gn >= ng) gn = ng - 1;
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < RB; ++b)
 #pragma unroll
             for (int s = 0; s < 4; ++s) xn[b][s] = reinterpret_cast<const uint4*>(xrow[b] + gn * 64)[s];
         __builtin_amdgcn_sched_barrier(0);
@@ -161,10 +160,23 @@ void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
         const float* il_lds = il_s + gl * 64 + hf * 32;
         if (GELU) {
 #pragma unroll
-            for (int b = 0; b < 2; ++b) gelu_tanh_rows(xc[b]);
+            for (int b = 0; b < RB; ++b) gelu_tanh_rows(xc[b]);
         }
+        auto project = [&]() {
+            if (!(LOWRANK && exists)) return;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int sidx = 0; sidx < 4; ++sidx) {
+                    bf16x8 av = __builtin_bit_cast(bf16x8, xc[b][sidx]);
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, bfrag[sidx][0]), acc[b], 0, 0, 0);
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, bfrag[sidx][1]), acc[b], 0, 0, 0);
+                }
+        };
+        // one row block per wave: ahead of the quantiser chain, so that the fragments' registers are free in it
+        if (RB == 1) project();
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
             uint4 codes;
             uint32_t e8;
             quantize_block_mx(xc[b], il_lds, rho, codes, e8);
@@ -178,16 +190,7 @@ void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                 sxe[((size_t)st * M + rows[b]) * 2 + hf] = (uint16_t)(e_first[b] | (e8 << 8));
             }
         }
-        if (LOWRANK && exists) {
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int sidx = 0; sidx < 4; ++sidx) {
-                    bf16x8 av = __builtin_bit_cast(bf16x8, xc[b][sidx]);
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, bfrag[sidx][0]), acc[b], 0, 0, 0);
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, bfrag[sidx][1]), acc[b], 0, 0, 0);
-                }
-        }
+        if (RB > 1) project();
     };
     for (int rd = 0; rd < rounds; rd += 2) {
         round_body(rd, xa, xb, IC<0>{});
@@ -196,21 +199,25 @@ void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
 
     if (LOWRANK) {
         __syncthreads();                                     // every wave is done with inv_lambda in LDS
-        float* hpart = reinterpret_cast<float*>(smem_raw);   // [4][64][33]
+        float* hpart = reinterpret_cast<float*>(smem_raw);   // [WV][ROWS][32]
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < RB; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 int rloc = 32 * b + 8 * (i >> 2) + 4 * hf + (i & 3);
-                hpart[(wave * QROWS + rloc) * 33 + rr] = acc[b][i];
+                hpart[(wave * ROWS + rloc) * 32 + rr] = acc[b][i];
             }
         __syncthreads();
-        for (int idx = tid; idx < QROWS * r; idx += 256) {
+        for (int idx = tid; idx < ROWS * r; idx += 64 * WV) {
             int rloc = idx / r, j = idx - rloc * r;
             int64_t row = row0 + rloc;
-            if (row < M)
-                h[row * r + j] = (hpart[(0 * QROWS + rloc) * 33 + j] + hpart[(1 * QROWS + rloc) * 33 + j]) +
-                                 (hpart[(2 * QROWS + rloc) * 33 + j] + hpart[(3 * QROWS + rloc) * 33 + j]);
+            if (row < M) {
+                auto part = [&](int w) { return hpart[(w * ROWS + rloc) * 32 + j]; };
+                float t = (part(0) + part(1)) + (part(2) + part(3));
+#pragma unroll
+                for (int w = 4; w < WV; w += 4) t += (part(w) + part(w + 1)) + (part(w + 2) + part(w + 3));
+                h[row * r + j] = t;
+            }
         }
     }
 }
@@ -981,20 +988,28 @@ hipError_t launch_pack_weight_mx(const uint8_t* qw, const uint8_t* sw, int N, in
     return hipGetLastError();
 }
 
+template <bool GELU, int RB, int WV>
+static hipError_t launch_quantize_mx_geom(const void* x, int64_t ldx, const float* inv_lambda, float rho,
+                                          const void* l1p, int64_t M, int K, int r,
+                                          uint8_t* qx, uint8_t* sxe, float* h, hipStream_t stream) {
+    const unsigned blocks = (unsigned)((M + 32 * RB - 1) / (32 * RB));
+    const size_t hpart = l1p ? (size_t)WV * 32 * RB * 32 * sizeof(float) : 0;
+    const size_t lds = ((size_t)K * sizeof(float) > hpart) ? (size_t)K * sizeof(float) : hpart;
+    if (l1p)
+        hipLaunchKernelGGL((quantize_mx_kernel<true, GELU, RB, WV>), dim3(blocks), dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, qx, (uint16_t*)sxe, h);
+    else
+        hipLaunchKernelGGL((quantize_mx_kernel<false, GELU, RB, WV>), dim3(blocks), dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, qx, (uint16_t*)sxe, h);
+    return hipGetLastError();
+}
+
 template <bool GELU>
 static hipError_t launch_quantize_mx_any(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                          const void* l1p, int64_t M, int K, int r,
                                          uint8_t* qx, uint8_t* sxe, float* h, hipStream_t stream) {
-    const unsigned blocks = (unsigned)((M + QROWS - 1) / QROWS);
-    size_t lds = (size_t)K * sizeof(float);
-    if (lds < (size_t)QHPART_BYTES) lds = QHPART_BYTES;
-    if (l1p)
-        hipLaunchKernelGGL((quantize_mx_kernel<true, GELU>), dim3(blocks), dim3(256), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, qx, (uint16_t*)sxe, h);
-    else
-        hipLaunchKernelGGL((quantize_mx_kernel<false, GELU>), dim3(blocks), dim3(256), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, qx, (uint16_t*)sxe, h);
-    return hipGetLastError();
+    auto go = quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_mx_geom<GELU, 2, 4> : launch_quantize_mx_geom<GELU, 1, 8>;
+    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sxe, h, stream);
 }
 
 hipError_t launch_quantize_mx(const void* x, int64_t ldx, const float* inv_lambda, float rho,

@@ -5,6 +5,13 @@
 
 namespace svdq {
 
+// Rows x waves of a block of the quantise kernels.  All of K is one block's work (h is a sum over it), so few rows
+// leave few blocks.  Below QUANT_SMALL_ROWS rows a block takes 32 rows with eight waves (K = 5120: 35 -> 19 us at
+// M = 512, 37 -> 26 us at M = 8192; the two geometries meet between 8192 and 16384 rows, where 64 rows fill the CUs).
+enum class QuantGeom { R64W4, R32W8 };
+constexpr int64_t QUANT_SMALL_ROWS = 12288;
+inline QuantGeom quant_geom(int64_t M) { return M >= QUANT_SMALL_ROWS ? QuantGeom::R64W4 : QuantGeom::R32W8; }
+
 // max over the two lanes (l, l^32) that share a token row.  The compiler builtin
 // (not inline asm) so that the wait states v_permlane32_swap needs after a VALU
 // write of its operands are inserted.

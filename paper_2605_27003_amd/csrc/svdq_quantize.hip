@@ -3,8 +3,8 @@
 // int4 codes (eq. 3) and feeds the raw bf16 x to the bf16 matrix cores for the
 // low-rank down-projection h = x^ L1 (eq. 7).
 //
-// Layout.  A block of 256 threads (4 waves) owns 64 token rows; wave w owns the
-// 64-groups g = w, w+4, ...  Lane l of a wave holds row (l % 32) of a 32-row
+// Layout.  A block of WV waves owns 32 RB token rows; wave w owns the
+// 64-groups g = w, w+WV, ...  Lane l of a wave holds row (l % 32) of a 32-row
 // block and the 32 consecutive k values [64 g + 32 (l/32), +32) of that row:
 // 64 contiguous bytes, read as four 16-byte loads.  That is at the same time
 //   - the A-operand layout of v_mfma_f32_32x32x16_bf16 (row = lane % 32, eight
@@ -27,11 +27,6 @@ namespace svdq {
 
 namespace {
 
-constexpr int ROWS_PER_BLOCK = 64;
-constexpr int WAVES = 4;
-
-constexpr int HPART_BYTES = WAVES * ROWS_PER_BLOCK * 33 * 4;
-
 // E3M2 = false: qx [K/64][M][32 B] nibbles.  E3M2 = true: qx is the activation operand buffer of the FP6 GEMM,
 // per group a block of Mp rows (Mp = M rounded up to a multiple of 4; rows M..Mp-1 are never written):
 //   [Mp][2 halves][16 B]   bytes 0..15 of each lane's 24 code bytes
@@ -41,13 +36,17 @@ constexpr int HPART_BYTES = WAVES * ROWS_PER_BLOCK * 33 * 4;
 // sx [K/64][M] binary32 is written in both cases (skipped if null with E3M2).
 // GELU = true: x is the feed-forward block's pre-activation; every value is replaced by bf16(gelu(x)) as it
 // arrives (svdq_act.h), and the pass continues as if a separate element-wise kernel had written that tensor.
-template <bool LOWRANK, bool E3M2, bool GELU>
-__global__ __launch_bounds__(256, 2)
+// RB x WV = 2 x 4 is the geometry for many tokens: a fragment of L1 is loaded once for 64 rows.  A block's waves walk
+// K / 64 groups in turn, about 1.7 us each (the latency of the x loads), so with few row blocks the walk is what is waited
+// for (M = 512, K = 5120: 8 blocks, 34 us): 1 x 8 then spreads rows and groups over more CUs and
+// waves (sixteen waves gain nothing: what a CU can deliver bounds it then).
+template <bool LOWRANK, bool E3M2, bool GELU, int RB, int WV>
+__global__ __launch_bounds__(64 * WV, WV == 4 ? 2 : 1)
 void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                      const float* __restrict__ inv_lambda, float rho,
                      const uint4* __restrict__ l1p, int64_t M, int K, int r,
                      uint8_t* __restrict__ qx, float* __restrict__ sx, float* __restrict__ h) {
-    // LDS: inv_lambda[K] during the main loop, then the 4 x 64 x 33 partial sums of h
+    // LDS: inv_lambda[K] during the main loop, then the WV x 32 RB x 32 partial sums of h
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
     float* il_s = reinterpret_cast<float*>(smem_raw);
 
@@ -57,21 +56,22 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
     const int rr = lane & 31;          // row inside a 32-row block
     const int hf = lane >> 5;          // which 32-k half of the group
     const int ng = K >> 6;
-    const int64_t row0 = (int64_t)blockIdx.x * ROWS_PER_BLOCK;
+    constexpr int ROWS = 32 * RB;
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
 
-    for (int i = tid * 4; i < K; i += 1024)
+    for (int i = tid * 4; i < K; i += 256 * WV)
         *reinterpret_cast<float4*>(il_s + i) = *reinterpret_cast<const float4*>(inv_lambda + i);
 
-    float16v acc[2];
+    float16v acc[RB];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < RB; ++b)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[b][i] = 0.0f;
 
-    const uint16_t* xrow[2];
-    int64_t rows[2];
+    const uint16_t* xrow[RB];
+    int64_t rows[RB];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < RB; ++b) {
         rows[b] = row0 + 32 * b + rr;
         const int64_t rowc = rows[b] < M ? rows[b] : M - 1;             // clamp loads of the ragged tail
         xrow[b] = x + rowc * ldx + hf * 32;
@@ -80,18 +80,18 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
     // software pipeline: x of this wave's NEXT group is in flight while the current one is processed.
     // Two register buffers alternate roles (the round body is instantiated twice), so there is no copy
     // and the wait for a prefetched group sits right before its first use, one full round later.
-    uint4 xa[2][4], xb[2][4];
+    uint4 xa[RB][4], xb[RB][4];
     if (wave < ng) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < RB; ++b)
 #pragma unroll
             for (int s = 0; s < 4; ++s) xa[b][s] = reinterpret_cast<const uint4*>(xrow[b] + wave * 64)[s];
     }
     __syncthreads();
 
-    const int rounds = (ng + WAVES - 1) / WAVES;
-    auto round_body = [&](const int rd, uint4 (&xc)[2][4], uint4 (&xn)[2][4]) {
-        const int g = rd * WAVES + wave;
+    const int rounds = (ng + WV - 1) / WV;
+    auto round_body = [&](const int rd, uint4 (&xc)[RB][4], uint4 (&xn)[RB][4]) {
+        const int g = rd * WV + wave;
         if (g < ng) {
             // B operands (hi and lo piece of inv_lambda*L1) of the four k-steps: issued first, used last
             uint4 bfrag[4][2];
@@ -108,9 +108,9 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
             __builtin_amdgcn_sched_barrier(0);
             // unconditional (the last round re-reads its own group): a load under a branch would make
             // the compiler assume the smaller outstanding count and wait for the prefetch early
-            const int gn = (g + WAVES < ng) ? g + WAVES : g;
+            const int gn = (g + WV < ng) ? g + WV : g;
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < RB; ++b)
 #pragma unroll
                 for (int s = 0; s < 4; ++s) xn[b][s] = reinterpret_cast<const uint4*>(xrow[b] + gn * 64)[s];
             __builtin_amdgcn_sched_barrier(0);
@@ -118,10 +118,23 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
             const float* il_lds = il_s + g * 64 + hf * 32;
             if (GELU) {
 #pragma unroll
-                for (int b = 0; b < 2; ++b) gelu_tanh_rows(xc[b]);
+                for (int b = 0; b < RB; ++b) gelu_tanh_rows(xc[b]);
             }
+            auto project = [&]() {
+                if (!(LOWRANK)) return;
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
+                for (int b = 0; b < RB; ++b)
+#pragma unroll
+                    for (int sidx = 0; sidx < 4; ++sidx) {
+                        bf16x8 av = __builtin_bit_cast(bf16x8, xc[b][sidx]);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, bfrag[sidx][0]), acc[b], 0, 0, 0);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, bfrag[sidx][1]), acc[b], 0, 0, 0);
+                    }
+            };
+            // one row block per wave: ahead of the quantiser chain, so that the fragments' registers are free in it
+            if (RB == 1) project();
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
                 LaneCodes<E3M2> codes;
                 float s;
                 quantize_rows<E3M2>(xc[b], il_lds, rho, codes, s);
@@ -143,16 +156,7 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                     }
                 }
             }
-            if (LOWRANK) {
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int sidx = 0; sidx < 4; ++sidx) {
-                        bf16x8 av = __builtin_bit_cast(bf16x8, xc[b][sidx]);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, bfrag[sidx][0]), acc[b], 0, 0, 0);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, bfrag[sidx][1]), acc[b], 0, 0, 0);
-                    }
-            }
+            if (RB > 1) project();
         }
     };
     for (int rd = 0; rd < rounds; rd += 2) {
@@ -164,21 +168,25 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
         // D layout of the 32x32 MFMA: lane holds column (lane % 32); register i holds
         // row 8*(i/4) + 4*(lane/32) + (i%4).
         __syncthreads();                                     // every wave is done with inv_lambda in LDS
-        float* hpart = reinterpret_cast<float*>(smem_raw);   // [WAVES][64][33]
+        float* hpart = reinterpret_cast<float*>(smem_raw);   // [WV][ROWS][32]
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < RB; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 int rloc = 32 * b + 8 * (i >> 2) + 4 * hf + (i & 3);
-                hpart[(wave * ROWS_PER_BLOCK + rloc) * 33 + rr] = acc[b][i];
+                hpart[(wave * ROWS + rloc) * 32 + rr] = acc[b][i];
             }
         __syncthreads();
-        for (int idx = tid; idx < ROWS_PER_BLOCK * r; idx += 256) {
+        for (int idx = tid; idx < ROWS * r; idx += 64 * WV) {
             int rloc = idx / r, j = idx - rloc * r;
             int64_t row = row0 + rloc;
-            if (row < M)
-                h[row * r + j] = (hpart[(0 * ROWS_PER_BLOCK + rloc) * 33 + j] + hpart[(1 * ROWS_PER_BLOCK + rloc) * 33 + j]) +
-                                 (hpart[(2 * ROWS_PER_BLOCK + rloc) * 33 + j] + hpart[(3 * ROWS_PER_BLOCK + rloc) * 33 + j]);
+            if (row < M) {
+                auto part = [&](int w) { return hpart[(w * ROWS + rloc) * 32 + j]; };
+                float t = (part(0) + part(1)) + (part(2) + part(3));
+#pragma unroll
+                for (int w = 4; w < WV; w += 4) t += (part(w) + part(w + 1)) + (part(w + 2) + part(w + 3));
+                h[row * r + j] = t;
+            }
         }
     }
 }
@@ -229,20 +237,28 @@ hipError_t launch_scale_chain(const float* a, float rho, int64_t n, float* s, fl
     return hipGetLastError();
 }
 
+template <bool E3M2, bool GELU, int RB, int WV>
+static hipError_t launch_quantize_geom(const void* x, int64_t ldx, const float* inv_lambda, float rho,
+                                       const void* l1p, int64_t M, int K, int r,
+                                       uint8_t* qx, float* sx, float* h, hipStream_t stream) {
+    const unsigned blocks = (unsigned)((M + 32 * RB - 1) / (32 * RB));
+    const size_t hpart = l1p ? (size_t)WV * 32 * RB * 32 * sizeof(float) : 0;
+    const size_t lds = ((size_t)K * sizeof(float) > hpart) ? (size_t)K * sizeof(float) : hpart;
+    if (l1p)
+        hipLaunchKernelGGL((quantize_kernel<true, E3M2, GELU, RB, WV>), dim3(blocks), dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, qx, sx, h);
+    else
+        hipLaunchKernelGGL((quantize_kernel<false, E3M2, GELU, RB, WV>), dim3(blocks), dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, qx, sx, h);
+    return hipGetLastError();
+}
+
 template <bool E3M2, bool GELU>
 static hipError_t launch_quantize_any(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                       const void* l1p, int64_t M, int K, int r,
                                       uint8_t* qx, float* sx, float* h, hipStream_t stream) {
-    const unsigned blocks = (unsigned)((M + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK);
-    size_t lds = (size_t)K * sizeof(float);
-    if (lds < (size_t)HPART_BYTES) lds = HPART_BYTES;
-    if (l1p)
-        hipLaunchKernelGGL((quantize_kernel<true, E3M2, GELU>), dim3(blocks), dim3(256), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, qx, sx, h);
-    else
-        hipLaunchKernelGGL((quantize_kernel<false, E3M2, GELU>), dim3(blocks), dim3(256), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, qx, sx, h);
-    return hipGetLastError();
+    auto go = quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_geom<E3M2, GELU, 2, 4> : launch_quantize_geom<E3M2, GELU, 1, 8>;
+    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, stream);
 }
 
 hipError_t launch_quantize(const void* x, int64_t ldx, const float* inv_lambda, float rho,
