@@ -26,9 +26,13 @@ inline TileGrid make_tile_grid(int mtiles, int ntiles) {
 
 // number of block ids (some of them name no tile: tile_of returns false)
 __host__ __device__ inline int tile_ids(const TileGrid& g) {
-    return g.nmajor ? ((g.ntiles + 7) / 8) * 8 * g.mtiles : ((g.mtiles + 63) / 64) * 64 * g.ntiles;
+    return g.nmajor ? ((g.ntiles + 7) / 8) * 8 * g.mtiles : ((g.mtiles + 7) / 8) * 8 * g.ntiles;
 }
 
+// An XCD's ids number its own tiles without gaps; only an XCD that owns fewer token (or channel) tiles than the others
+// has ids left over, at its end.  (With the last group of token tiles numbered as if it were full, 7 of 8 ids named no
+// tile at mtiles = 8, and the blocks that did all fell on the same few CUs of the XCD's round-robin: M = 1024,
+// K = N = 5120 took 103 us where M = 1536 took 57.)
 __device__ __forceinline__ bool tile_of(const TileGrid& g, int id, int& mt, int& nt) {
     const int xcd = id & 7, idx = id >> 3;
     if (g.nmajor) {
@@ -37,10 +41,13 @@ __device__ __forceinline__ bool tile_of(const TileGrid& g, int id, int& mt, int&
         mt = idx - q * g.mtiles;
         return nt < g.ntiles;
     }
+    const int own = (g.mtiles - xcd + 7) >> 3;                           // token tiles of this XCD
     const int sm = idx / (8 * g.ntiles), rem = idx - sm * (8 * g.ntiles);
-    nt = rem >> 3;
-    mt = (sm * 8 + (rem & 7)) * 8 + xcd;
-    return mt < g.mtiles;
+    const int width = (own - 8 * sm < 8) ? own - 8 * sm : 8;             // token tiles of this group of eight
+    if (width <= 0 || rem >= width * g.ntiles) return false;
+    nt = rem / width;
+    mt = (sm * 8 + rem - nt * width) * 8 + xcd;
+    return true;
 }
 
 }  // namespace svdq
