@@ -253,6 +253,40 @@ int svdq_quantize_act_gelu(int format, const void* x_bf16, int64_t ldx, const fl
 int svdq_debug_gelu(const void* x_bf16, int64_t n, void* out_bf16, void* stream);
 
 /*
+ * ---- The whole layer in one call: quantise pass and GEMM of any format on a layer's resident tensors.  What the two
+ * calls of the format compute, chosen by size: with few tokens K is split between blocks in the quantise pass and
+ * between waves in the GEMM, so y and h are summed in another order than there (same codes and scales).
+ *   format        SVDQ_FMT_*; w_packed from that format's packer.  SVDQ_FMT_INT4_E3M2 may instead keep the canonical
+ *                 qw [N, K/2] and sw [K/64, N] resident (w_packed NULL); they are expanded when needed.
+ *   inv_lambda, l1_packed, L2_bf16, bias, r   as for the separate calls (r = 0: l1_packed and L2_bf16 NULL)
+ * svdq_layer_forward: x, ldx, rho, M as svdq_quantize_act, gelu != 0 as svdq_quantize_act_gelu;
+ *   codes, scales   the format's activation buffers (scales unused and may be NULL for SVDQ_FMT_INT4_E3M2)
+ *   h               [M, r] binary32; holds intermediate values, not necessarily h, afterwards
+ *   scratch         svdq_layer_scratch_bytes(layer, M) bytes, 16-byte aligned, or NULL (slower with few tokens)
+ *   staging         svdq_layer_staging_bytes(layer, M) bytes, 16-byte aligned: room for the expanded weights of one
+ *                   GEMM (0 bytes if they are resident or M is small: NULL then)
+ *   y               out [M, ldy] bf16
+ * svdq_layer_gemm: the second half, from activations quantised by the format's own call.
+ */
+typedef struct {
+    int format, N, K, r;
+    const float* inv_lambda;
+    const void* l1_packed;
+    const void* L2_bf16;
+    const float* bias;
+    const void* w_packed;
+    const uint8_t* qw;
+    const void* sw;
+} svdq_layer;
+size_t svdq_layer_scratch_bytes(const svdq_layer* layer, int64_t M);
+size_t svdq_layer_staging_bytes(const svdq_layer* layer, int64_t M);
+int svdq_layer_forward(const svdq_layer* layer, const void* x_bf16, int64_t ldx, float rho, int gelu, int64_t M,
+                       void* codes, void* scales, float* h, void* scratch, void* staging,
+                       void* y, int64_t ldy, void* stream);
+int svdq_layer_gemm(const svdq_layer* layer, const void* codes, const void* scales, const float* h, int64_t M,
+                    void* staging, void* y, int64_t ldy, void* stream);
+
+/*
  * ---- GPTQ on the residual (Sec. III-B: the residual branch is quantised with GPTQ instead of round-to-nearest).
  * Offline calibration.  Column-sequential form of the algorithm in binary64: weights are visited in the order
  * k = 0..K-1; a visited weight is rounded to the int4 grid of its (channel, 64-group) scale (absmax of the group's

@@ -40,6 +40,10 @@ EXPORTS = {
     "svdq_linear_mxfp4": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _i32, _vp, _i64, _i32, _vp]),
     "svdq_linear_mxfp4_next": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _i32, _i32,
                                       _vp, _f32, _vp, _i32, _vp, _vp, _vp, _vp]),
+    "svdq_layer_scratch_bytes": (ctypes.c_size_t, [_vp, _i64]),
+    "svdq_layer_staging_bytes": (ctypes.c_size_t, [_vp, _i64]),
+    "svdq_layer_forward": (_i32, [_vp, _vp, _i64, _f32, _i32, _i64, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _vp]),
+    "svdq_layer_gemm": (_i32, [_vp, _vp, _vp, _vp, _i64, _vp, _vp, _i64, _vp]),
     "svdq_gptq_workspace_bytes": (ctypes.c_size_t, [_i32, _i32]),
     "svdq_gptq_hessian": (_i32, [_vp, _i64, _vp, _i64, _i32, _vp, _vp]),
     "svdq_gptq_quantize": (_i32, [_vp, _vp, ctypes.c_double, _i32, _i32, _vp, _vp, _vp, _vp]),
@@ -499,6 +503,16 @@ def _staging_buffer(nbytes, device):
     return buf
 
 
+class _Layer(ctypes.Structure):
+    """svdq_layer of include/svdq.h."""
+    _fields_ = ([(n, _i32) for n in ("format", "N", "K", "r")] +
+                [(n, _vp) for n in ("inv_lambda", "l1_packed", "L2_bf16", "bias", "w_packed", "qw", "sw")])
+
+
+def _addr(t):
+    return None if t is None else t.data_ptr()
+
+
 class W4A4Linear:
     """One quantised linear resident in HBM: weights and low-rank factors, reusable output buffers.
 
@@ -511,17 +525,22 @@ class W4A4Linear:
     def __init__(self, inv_lambda, L1_bf16, L2_bf16, qw, sw, bias, container="e3m2", resident="w4"):
         assert container in ("e3m2", "nibble", "mxfp4") and resident in ("w4", "packed")
         self.container = container
+        self.format = {"e3m2": FMT_INT4_E3M2, "nibble": FMT_INT4, "mxfp4": FMT_MXFP4}[container]
         self.N, self.K = qw.shape[0], qw.shape[1] * 2
         self.r = 0 if L1_bf16 is None else L1_bf16.shape[1]
         self.inv_lambda = inv_lambda
         self.l1_packed = pack_lowrank_down(L1_bf16, inv_lambda) if self.r else None
         self.L2 = L2_bf16 if self.r else None
+        self.qw = self.sw = None
         if container == "e3m2" and resident == "w4":
             self.qw, self.sw, self.w_packed = qw, sw, None
         else:
             self.w_packed = {"e3m2": pack_weight_e3m2, "nibble": pack_weight, "mxfp4": pack_weight_mxfp4}[container](qw, sw)
         self.bias = bias
         self._bufs = None
+        self._layer = _Layer(self.format, self.N, self.K, self.r, *map(_addr, (
+            self.inv_lambda, self.l1_packed, self.L2, self.bias, self.w_packed, self.qw, self.sw)))
+        self._ref = ctypes.addressof(self._layer)
 
     def weights(self):
         """The packed weights the GEMM takes: resident, or expanded now from the resident 4-bit form."""
@@ -531,6 +550,7 @@ class W4A4Linear:
 
     def buffers(self, M, device):
         if self._bufs is None or self._bufs[3].shape[0] != M:
+            lib = load_library()
             if self.container == "e3m2":
                 qx = ActE3M2(torch.empty(act_e3m2_bytes(M, self.K), dtype=torch.uint8, device=device), M, self.K)
                 sx = None
@@ -540,28 +560,40 @@ class W4A4Linear:
                       else torch.empty(((self.K // 64 + 1) // 2, M, 2, 2), dtype=torch.uint8, device=device))
             h = torch.empty((M, self.r), dtype=torch.float32, device=device) if self.r else None
             y = torch.empty((M, self.N), dtype=torch.bfloat16, device=device)
+            n = lib.svdq_layer_scratch_bytes(self._ref, M)
+            self._scratch = torch.empty(n, dtype=torch.uint8, device=device) if n else None
+            self._staging_bytes = lib.svdq_layer_staging_bytes(self._ref, M)
+            if self.w_packed is None:                    # reserved with the first buffers, though small M expands nothing
+                _staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), device)
+            self._ptrs = tuple(map(_addr, (qx.buf if self.container == "e3m2" else qx, sx, h, self._scratch)))
             self._bufs = (qx, sx, h, y)
         return self._bufs
+
+    def _staging(self, device):
+        return _staging_buffer(self._staging_bytes, device).data_ptr() if self._staging_bytes else None
 
     def quantize(self, x_bf16, rho, gelu=False):
         """Kernel (a) into the layer's buffers; gelu=True applies the feed-forward block's activation on the fly."""
         out = self.buffers(x_bf16.shape[0], x_bf16.device)[:3]
         if gelu:
-            fmt = {"e3m2": FMT_INT4_E3M2, "nibble": FMT_INT4, "mxfp4": FMT_MXFP4}[self.container]
-            return quantize_act_gelu(fmt, x_bf16, self.inv_lambda, rho, self.l1_packed, self.r, out=out)
+            return quantize_act_gelu(self.format, x_bf16, self.inv_lambda, rho, self.l1_packed, self.r, out=out)
         fn = {"e3m2": quantize_act_e3m2, "nibble": quantize_act, "mxfp4": quantize_act_mxfp4}[self.container]
         return fn(x_bf16, self.inv_lambda, rho, self.l1_packed, self.r, out=out)
 
     def gemm(self, qx, sx, h):
-        if self.container == "e3m2":
-            y = self.buffers(qx.M, qx.buf.device)[3]
-            return linear_w4a4_e3m2(qx, self.weights(), self.N, h, self.L2, self.bias, out=y)
-        y = self.buffers(qx.shape[1], qx.device)[3]
-        fn = linear_w4a4 if self.container == "nibble" else linear_mxfp4
-        return fn(qx, sx, self.w_packed, self.N, h, self.L2, self.bias, out=y)
+        codes = qx.buf if self.container == "e3m2" else qx
+        M, device = (qx.M if self.container == "e3m2" else qx.shape[1]), codes.device
+        y = self.buffers(M, device)[3]
+        _check(load_library().svdq_layer_gemm(self._ref, codes.data_ptr(), _addr(sx), _addr(h), M, self._staging(device),
+                                              y.data_ptr(), self.N, _stream()), "svdq_layer_gemm")
+        return y
 
     def forward(self, x_bf16, rho, gelu=False):
-        qx, sx, h = self.quantize(x_bf16, rho, gelu)
-        return self.gemm(qx, sx, h)
-
-
+        M, K = x_bf16.shape
+        assert x_bf16.dtype == torch.bfloat16 and x_bf16.stride(1) == 1 and K == self.K
+        device = x_bf16.device
+        y = self.buffers(M, device)[3]
+        _check((_lib or load_library()).svdq_layer_forward(
+            self._ref, x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, rho, gelu, M, *self._ptrs, self._staging(device),
+            y.data_ptr(), self.N, torch.cuda.current_stream().cuda_stream), "svdq_layer_forward")
+        return y

@@ -370,6 +370,130 @@ int svdq_linear_mxfp4_next(const uint8_t* qx, const uint8_t* sx_e8m0, const void
                                                   next_qx, next_sx_e8m0, next_h, (hipStream_t)stream));
 }
 
+// ---- the whole layer in one call
+static int layer_check(const svdq_layer* L, int64_t M) {
+    if (!L || !L->inv_lambda || M < 0) return SVDQ_ERR_INVALID_ARG;
+    if (L->format < SVDQ_FMT_INT4 || L->format > SVDQ_FMT_MXFP4) return SVDQ_ERR_INVALID_ARG;
+    const bool canonical = !L->w_packed;
+    if (canonical && (L->format != SVDQ_FMT_INT4_E3M2 || !L->qw || !L->sw)) return SVDQ_ERR_INVALID_ARG;
+    if (L->r == 0 ? (L->l1_packed || L->L2_bf16) : (!L->l1_packed || !L->L2_bf16)) return SVDQ_ERR_INVALID_ARG;
+    if (L->N <= 0 || L->K <= 0 || L->K % SVDQ_GROUP || L->N % SVDQ_N_TILE || L->K > SVDQ_MAX_K) return SVDQ_ERR_UNSUPPORTED_SHAPE;
+    if (L->r != 0 && !rank_ok(L->r)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
+    if (!aligned16(L->inv_lambda) || !aligned16(L->l1_packed) || !aligned16(L->L2_bf16) || !aligned16(L->bias) ||
+        !aligned16(L->w_packed) || !aligned16(L->qw) || !aligned16(L->sw))
+        return SVDQ_ERR_UNSUPPORTED_SHAPE;
+    return M > SVDQ_MAX_M ? SVDQ_ERR_UNSUPPORTED_SHAPE : SVDQ_OK;
+}
+
+static bool small_path(const svdq_layer* L, int64_t M) { return svdq::small_shape(M, L->N, L->format == SVDQ_FMT_MXFP4) != 0; }
+
+// K slices of the quantise pass: blocks for every CU where the row blocks (32 rows) are few, at least a group for each of a
+// block's eight waves, and no more slices than the few-token GEMM takes partial h's.
+static int layer_slices(const svdq_layer* L, int64_t M) {
+    const int64_t row_blocks = (M + 31) / 32;
+    const int groups = L->K / 64, units = L->format == SVDQ_FMT_MXFP4 ? (groups + 1) / 2 : groups;   // MXFP4 splits by pairs
+    int s = svdq::SMALL_SLICES;
+    while (s > 1 && (s * row_blocks > 256 || groups / s < 8)) s >>= 1;
+    const int slice = (units + s - 1) / s;
+    return (units + slice - 1) / slice;
+}
+
+size_t svdq_layer_scratch_bytes(const svdq_layer* L, int64_t M) {
+    if (layer_check(L, M) != SVDQ_OK || L->r == 0) return 0;
+    const int s = layer_slices(L, M);
+    return s > 1 ? (size_t)s * (size_t)M * L->r * sizeof(float) : 0;
+}
+
+size_t svdq_layer_staging_bytes(const svdq_layer* L, int64_t M) {
+    if (layer_check(L, M) != SVDQ_OK || L->w_packed || small_path(L, M)) return 0;
+    return svdq::packed_weight_e3m2_bytes(L->N, L->K);
+}
+
+// the GEMM on checked arguments; h: `slices` partial h's for the few-token kernel, one otherwise
+static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, const float* h, int slices, int64_t M,
+                      void* staging, void* y, int64_t ldy, hipStream_t stream) {
+    const int N = L->N, K = L->K, r = L->r;
+    const uint8_t* wp = (const uint8_t*)L->w_packed;
+    if (small_path(L, M)) {
+        const void *w0 = wp, *w1 = nullptr, *w2 = nullptr;
+        int source = svdq::SMALL_E3M2_PACKED;
+        if (L->format == SVDQ_FMT_INT4) {
+            source = svdq::SMALL_NIBBLE;
+            w1 = wp + svdq::packed_weight_codes_bytes(N, K);
+        } else if (L->format == SVDQ_FMT_MXFP4) {
+            source = svdq::SMALL_MXFP4;
+            w1 = wp + svdq::packed_mx_codes_bytes(N, K);
+        } else if (!wp) {
+            source = svdq::SMALL_E3M2_CANONICAL;
+            w0 = L->qw;
+            w1 = L->sw;
+        } else {
+            w1 = wp + svdq::packed_e3m2_w0_bytes(N, K);
+            w2 = (const uint8_t*)w1 + svdq::packed_e3m2_w1_bytes(N, K);
+        }
+        return hip_status(svdq::launch_small_gemm(source, codes, scales, w0, w1, w2, h, slices, L->L2_bf16, L->bias, M, N, K, r, y, ldy, stream));
+    }
+    if (L->format == SVDQ_FMT_INT4)
+        return hip_status(svdq::launch_linear(codes, (const float*)scales, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, 0, stream));
+    if (L->format == SVDQ_FMT_MXFP4)
+        return hip_status(svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, 0, stream));
+    if (!wp) {
+        if (!staging || !aligned16(staging)) return SVDQ_ERR_INVALID_ARG;
+        const hipError_t e = svdq::launch_pack_weight_e3m2(L->qw, (const float*)L->sw, N, K, staging, stream);
+        if (e != hipSuccess) return hip_status(e);
+        wp = (const uint8_t*)staging;
+    }
+    return hip_status(svdq::launch_linear_e3m2(codes, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, 0, stream));
+}
+
+static int layer_out_check(const svdq_layer* L, const void* codes, const void* scales, const void* h, const void* y, int64_t ldy) {
+    if (!codes || !y || (L->format != SVDQ_FMT_INT4_E3M2 && !scales) || (L->r != 0 && !h)) return SVDQ_ERR_INVALID_ARG;
+    if (ldy < L->N || ldy % 8 || !aligned16(codes) || !aligned16(scales) || !aligned16(h) || !aligned16(y)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
+    return SVDQ_OK;
+}
+
+int svdq_layer_gemm(const svdq_layer* L, const void* codes, const void* scales, const float* h, int64_t M,
+                    void* staging, void* y, int64_t ldy, void* stream) {
+    if (int e = layer_check(L, M)) return e;
+    if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
+    if (M == 0) return SVDQ_OK;
+    if (int a = check_arch()) return a;
+    return layer_gemm(L, (const uint8_t*)codes, scales, h, 1, M, staging, y, ldy, (hipStream_t)stream);
+}
+
+int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, float rho, int gelu, int64_t M,
+                       void* codes, void* scales, float* h, void* scratch, void* staging,
+                       void* y, int64_t ldy, void* stream_) {
+    if (int e = layer_check(L, M)) return e;
+    if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
+    if (!x_bf16 || !(rho > 0.0f) || !(rho <= 1.0f)) return SVDQ_ERR_INVALID_ARG;
+    if (ldx < L->K || ldx % 8 || !aligned16(x_bf16) || !aligned16(scratch)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
+    if (!L->w_packed && !small_path(L, M) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
+    if (M == 0) return SVDQ_OK;
+    if (int a = check_arch()) return a;
+    hipStream_t stream = (hipStream_t)stream_;
+    const int K = L->K, r = L->r;
+    // without h there is nothing to add up over the slices
+    int slices = (r == 0 || scratch) ? layer_slices(L, M) : 1;
+    float* const ho = (r != 0 && slices > 1) ? (float*)scratch : h;
+    hipError_t e;
+    if (L->format == SVDQ_FMT_INT4)
+        e = svdq::launch_quantize(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, (float*)scales, ho, gelu != 0, stream, slices);
+    else if (L->format == SVDQ_FMT_MXFP4)
+        e = svdq::launch_quantize_mx(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, (uint8_t*)scales, ho, gelu != 0, stream, slices);
+    else
+        e = svdq::launch_quantize_e3m2(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, nullptr, ho, gelu != 0, stream, slices);
+    if (e != hipSuccess) return hip_status(e);
+    const float* hin = ho;
+    if (r != 0 && slices > 1 && !small_path(L, M)) {
+        e = svdq::launch_sum_slices(ho, slices, M, r, h, stream);
+        if (e != hipSuccess) return hip_status(e);
+        hin = h;
+        slices = 1;
+    }
+    return layer_gemm(L, (const uint8_t*)codes, scales, r ? hin : nullptr, r ? slices : 1, M, staging, y, ldy, stream);
+}
+
 size_t svdq_gptq_workspace_bytes(int N, int K) {
     if (N <= 0 || K <= 0 || K % SVDQ_GROUP) return 0;
     return svdq::gptq_workspace_bytes(N, K);

@@ -486,6 +486,7 @@ __global__ void pack_weight_kernel(const uint8_t* __restrict__ qw, const float* 
 
 }  // namespace
 
+size_t packed_weight_codes_bytes(int N, int K) { return wfrag_bytes(N, K); }
 size_t packed_weight_bytes(int N, int K) { return wfrag_bytes(N, K) + sfrag_bytes(N, K) + cfrag_bytes(N, K); }
 
 hipError_t launch_pack_weight(const uint8_t* qw, const float* sw, int N, int K, void* out, hipStream_t stream) {

@@ -513,9 +513,8 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
 // [N/32][K/64][32 channels][8 B]: bf16 {w1, w1, w2, w2} with w1 + w2 ~ sw[g][n] (the lanes of k half 0 read the
 // entry; those of k half 1 read zeros).
 // Runs before every GEMM whose weights stay resident in the canonical form, so it has to keep up with HBM: a lane turns
-// 32 nibbles into 32 fields with a sign-extending bit-field extract and an int -> float conversion each and ONE
-// hardware conversion of the 32 floats (exact on integers; bit arithmetic per field was 480 vector instructions and
-// bound the kernel: 18.7 us for 5120 x 5120, 36 MB).  A wave takes four neighbouring groups of 32 channels: 128 bytes
+// 32 nibbles into 32 fields with the hardware conversions (e3m2_of_nibbles; bit arithmetic per field was 480 vector
+// instructions and bound the kernel: 18.7 us for 5120 x 5120, 36 MB).  A wave takes four neighbouring groups of 32 channels: 128 bytes
 // of every channel's row, all requested before the first conversion.
 constexpr int PACK_GROUPS = 4;
 __global__ __launch_bounds__(256)
@@ -544,18 +543,10 @@ void pack_weight_e3m2_kernel(const uint8_t* __restrict__ qw, const float* __rest
 #pragma unroll
     for (int i = 0; i < PACK_GROUPS; ++i) {
         if (g0 + i >= ng) break;
-        const int nw[4] = {(int)nib[i].x, (int)nib[i].y, (int)nib[i].z, (int)nib[i].w};
-        f32x16 ev, od;                                // field 2 j comes from the first vector, 2 j + 1 from the second
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int w = nw[j >> 2], b = 8 * (j & 3);
-            ev[j] = (float)((w << (28 - b)) >> 28);
-            od[j] = (float)((w << (24 - b)) >> 28);
-        }
-        const u32x6 c = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(ev, od, 1.0f);
+        const LaneCodes<true> c = e3m2_of_nibbles(nib[i]);
         const size_t v = ((size_t)nb * ng + g0 + i) * 64 + lane;
-        o1[v] = uint4{c[0], c[1], c[2], c[3]};
-        o2[v] = uint2{c[4], c[5]};
+        o1[v] = c.lo;
+        o2[v] = c.hi;
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {

@@ -84,7 +84,7 @@ template <bool LOWRANK, bool GELU, int RB, int WV>
 __global__ __launch_bounds__(64 * WV, WV == 4 ? 2 : 1)
 void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                         const float* __restrict__ inv_lambda, float rho,
-                        const uint4* __restrict__ l1p, int64_t M, int K, int r,
+                        const uint4* __restrict__ l1p, int64_t M, int K, int r, int slice,
                         uint8_t* __restrict__ qx, uint16_t* __restrict__ sxe, float* __restrict__ h) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
     float* il_s = reinterpret_cast<float*>(smem_raw);
@@ -95,12 +95,16 @@ void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
     const int rr = lane & 31;
     const int hf = lane >> 5;
     const int ng = K >> 6;
-    const int nstages = (ng + 1) >> 1;
+    // this block's stages [st0, nstages): all of K, or slice blockIdx.y of it (then h is that slice's partial sum)
+    const int st0 = (int)blockIdx.y * slice, all = (ng + 1) >> 1;
+    const int nstages = (st0 + slice < all) ? st0 + slice : all;
+    const int k0 = st0 * 128, k1 = (nstages * 128 < K) ? nstages * 128 : K;
+    h += (size_t)blockIdx.y * M * r;
     constexpr int ROWS = 32 * RB;
     const int64_t row0 = (int64_t)blockIdx.x * ROWS;
 
-    for (int i = tid * 4; i < K; i += 256 * WV)
-        *reinterpret_cast<float4*>(il_s + i) = *reinterpret_cast<const float4*>(inv_lambda + i);
+    for (int i = tid * 4; i < k1 - k0; i += 256 * WV)
+        *reinterpret_cast<float4*>(il_s + i) = *reinterpret_cast<const float4*>(inv_lambda + k0 + i);
 
     float16v acc[RB];
 #pragma unroll
@@ -120,8 +124,8 @@ void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
     // round rd of this wave = group 2 (wave + WV (rd / 2)) + rd % 2: the two groups of a stage follow each other
     // so that their two scale bytes leave as one 16-bit store.  Software pipeline as in the int4 kernel: the
     // next round's x is in flight while the current one is processed; two register buffers alternate.
-    auto group_of = [&](const int rd) { return 2 * (wave + WV * (rd >> 1)) + (rd & 1); };
-    const int my_stages = (nstages > wave) ? (nstages - wave + WV - 1) / WV : 0;
+    auto group_of = [&](const int rd) { return 2 * (st0 + wave + WV * (rd >> 1)) + (rd & 1); };
+    const int mine = nstages - st0 - wave, my_stages = (mine > 0) ? (mine + WV - 1) / WV : 0;
     const int rounds = 2 * my_stages;
     uint4 xa[RB][4], xb[RB][4];
     if (rounds > 0) {
@@ -157,7 +161,7 @@ void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t ldx,
             for (int s = 0; s < 4; ++s) xn[b][s] = reinterpret_cast<const uint4*>(xrow[b] + gn * 64)[s];
         __builtin_amdgcn_sched_barrier(0);
 
-        const float* il_lds = il_s + gl * 64 + hf * 32;
+        const float* il_lds = il_s + gl * 64 - k0 + hf * 32;
         if (GELU) {
 #pragma unroll
             for (int b = 0; b < RB; ++b) gelu_tanh_rows(xc[b]);
@@ -991,32 +995,33 @@ hipError_t launch_pack_weight_mx(const uint8_t* qw, const uint8_t* sw, int N, in
 template <bool GELU, int RB, int WV>
 static hipError_t launch_quantize_mx_geom(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                           const void* l1p, int64_t M, int K, int r,
-                                          uint8_t* qx, uint8_t* sxe, float* h, hipStream_t stream) {
-    const unsigned blocks = (unsigned)((M + 32 * RB - 1) / (32 * RB));
+                                          uint8_t* qx, uint8_t* sxe, float* h, int slices, hipStream_t stream) {
+    const int all = (K / 64 + 1) / 2, slice = (all + slices - 1) / slices;     // stages, and stages per slice
+    const dim3 blocks((unsigned)((M + 32 * RB - 1) / (32 * RB)), (unsigned)((all + slice - 1) / slice));
     const size_t hpart = l1p ? (size_t)WV * 32 * RB * 32 * sizeof(float) : 0;
-    const size_t lds = ((size_t)K * sizeof(float) > hpart) ? (size_t)K * sizeof(float) : hpart;
+    const size_t il = (size_t)slice * 128 * sizeof(float), lds = (il > hpart) ? il : hpart;
     if (l1p)
-        hipLaunchKernelGGL((quantize_mx_kernel<true, GELU, RB, WV>), dim3(blocks), dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, qx, (uint16_t*)sxe, h);
+        hipLaunchKernelGGL((quantize_mx_kernel<true, GELU, RB, WV>), blocks, dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, slice, qx, (uint16_t*)sxe, h);
     else
-        hipLaunchKernelGGL((quantize_mx_kernel<false, GELU, RB, WV>), dim3(blocks), dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, qx, (uint16_t*)sxe, h);
+        hipLaunchKernelGGL((quantize_mx_kernel<false, GELU, RB, WV>), blocks, dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, slice, qx, (uint16_t*)sxe, h);
     return hipGetLastError();
 }
 
 template <bool GELU>
 static hipError_t launch_quantize_mx_any(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                          const void* l1p, int64_t M, int K, int r,
-                                         uint8_t* qx, uint8_t* sxe, float* h, hipStream_t stream) {
-    auto go = quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_mx_geom<GELU, 2, 4> : launch_quantize_mx_geom<GELU, 1, 8>;
-    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sxe, h, stream);
+                                         uint8_t* qx, uint8_t* sxe, float* h, int slices, hipStream_t stream) {
+    auto go = slices == 1 && quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_mx_geom<GELU, 2, 4> : launch_quantize_mx_geom<GELU, 1, 8>;
+    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sxe, h, slices, stream);
 }
 
 hipError_t launch_quantize_mx(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                               const void* l1p, int64_t M, int K, int r,
-                              uint8_t* qx, uint8_t* sxe, float* h, bool gelu, hipStream_t stream) {
-    return gelu ? launch_quantize_mx_any<true>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sxe, h, stream)
-                : launch_quantize_mx_any<false>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sxe, h, stream);
+                              uint8_t* qx, uint8_t* sxe, float* h, bool gelu, hipStream_t stream, int slices) {
+    return gelu ? launch_quantize_mx_any<true>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sxe, h, slices, stream)
+                : launch_quantize_mx_any<false>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sxe, h, slices, stream);
 }
 
 // compute units of the current device (256 on MI355X; fewer in a partitioned mode), cached per device

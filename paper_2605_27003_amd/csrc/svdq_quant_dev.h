@@ -6,11 +6,12 @@
 namespace svdq {
 
 // Rows x waves of a block of the quantise kernels.  All of K is one block's work (h is a sum over it), so few rows
-// leave few blocks.  Below QUANT_SMALL_ROWS rows a block takes 32 rows with eight waves (K = 5120: 35 -> 19 us at
-// M = 512, 37 -> 26 us at M = 8192; the two geometries meet between 8192 and 16384 rows, where 64 rows fill the CUs).
+// leave few blocks.  Up to QUANT_SMALL_ROWS rows a block takes 32 rows with eight waves: one block for every CU at most
+// (K = 5120: 35 -> 19 us at M = 512, 37 -> 26 us at M = 8192; beyond, a second round of blocks costs more than the
+// 64-row geometry does: M = 11000, 42 against 33 us).
 enum class QuantGeom { R64W4, R32W8 };
-constexpr int64_t QUANT_SMALL_ROWS = 12288;
-inline QuantGeom quant_geom(int64_t M) { return M >= QUANT_SMALL_ROWS ? QuantGeom::R64W4 : QuantGeom::R32W8; }
+constexpr int64_t QUANT_SMALL_ROWS = 8192;
+inline QuantGeom quant_geom(int64_t M) { return M > QUANT_SMALL_ROWS ? QuantGeom::R64W4 : QuantGeom::R32W8; }
 
 // max over the two lanes (l, l^32) that share a token row.  The compiler builtin
 // (not inline asm) so that the wait states v_permlane32_swap needs after a VALU
@@ -54,6 +55,38 @@ constexpr uint32_t PACK_JUNK = (uint32_t)(0x4B400000ull * 0x11111111ull);
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 template <bool E3M2> struct LaneCodes { uint4 lo; uint2 hi; };
+
+// 32 floats / scale -> E3M2 fields: field 2 j from ev, 2 j + 1 from od.  Inline asm for the early-clobber mark: the
+// instruction writes its six result registers while it still reads its sources, and the compiler, which does not know,
+// may let them overlap (seen with a result two registers into the first source: byte 19 of the 24 was wrong).
+__device__ __forceinline__ u32x6 e3m2_of_floats(const f32x16& ev, const f32x16& od, const float scale) {
+    u32x6 c;
+    asm("v_cvt_scalef32_2xpk16_bf6_f32 %0, %1, %2, %3\n\ts_nop 1" : "=&v"(c) : "v"(ev), "v"(od), "s"(scale));
+    return c;
+}
+
+// 32 two's-complement nibbles, ascending, -> the E3M2 fields of the same integers.  v_cvt_off_f32_i4 turns the low four
+// bits of a byte (chosen by the instruction) into their signed value / 16: one instruction per code and a shift per
+// eight; the block conversion takes the 1 / 16 back.  Its two inputs interleave: field 2 j from the first vector.
+__device__ __forceinline__ LaneCodes<true> e3m2_of_nibbles(const uint4& nib) {
+    const uint32_t nw[4] = {nib.x, nib.y, nib.z, nib.w};
+    f32x16 ev, od;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        uint32_t hi = nw[d] >> 4;
+        asm("" : "+v"(hi));                    // or the compiler extracts every byte of it with an instruction of its own
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            ev[4 * d + b] = __builtin_amdgcn_cvt_off_f32_i4((int)((nw[d] >> (8 * b)) & 0xffu));
+            od[4 * d + b] = __builtin_amdgcn_cvt_off_f32_i4((int)((hi >> (8 * b)) & 0xffu));
+        }
+    }
+    const u32x6 c = e3m2_of_floats(ev, od, 0.0625f);
+    LaneCodes<true> out;
+    out.lo = uint4{c[0], c[1], c[2], c[3]};
+    out.hi = uint2{c[4], c[5]};
+    return out;
+}
 
 // One 32-row block of one group: quantiser chain on this lane's 32 values.
 template <bool E3M2>
@@ -101,7 +134,7 @@ __device__ __forceinline__ void quantize_rows(const uint4 (&xv)[4], const float*
             ev[j] = __builtin_rintf(u0);
             od[j] = __builtin_rintf(u1);
         }
-        const u32x6 c = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(ev, od, 1.0f);
+        const u32x6 c = e3m2_of_floats(ev, od, 1.0f);
         codes.lo = uint4{c[0], c[1], c[2], c[3]};
         codes.hi = uint2{c[4], c[5]};
         return;

@@ -44,7 +44,7 @@ template <bool LOWRANK, bool E3M2, bool GELU, int RB, int WV>
 __global__ __launch_bounds__(64 * WV, WV == 4 ? 2 : 1)
 void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                      const float* __restrict__ inv_lambda, float rho,
-                     const uint4* __restrict__ l1p, int64_t M, int K, int r,
+                     const uint4* __restrict__ l1p, int64_t M, int K, int r, int slice,
                      uint8_t* __restrict__ qx, float* __restrict__ sx, float* __restrict__ h) {
     // LDS: inv_lambda[K] during the main loop, then the WV x 32 RB x 32 partial sums of h
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
@@ -55,12 +55,15 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
     const int wave = tid >> 6;
     const int rr = lane & 31;          // row inside a 32-row block
     const int hf = lane >> 5;          // which 32-k half of the group
-    const int ng = K >> 6;
+    // this block's groups [g0, ng): all of K, or slice blockIdx.y of it (then h is that slice's partial sum)
+    const int g0 = (int)blockIdx.y * slice;
+    const int ng = (g0 + slice < (K >> 6)) ? g0 + slice : (K >> 6);
+    h += (size_t)blockIdx.y * M * r;
     constexpr int ROWS = 32 * RB;
     const int64_t row0 = (int64_t)blockIdx.x * ROWS;
 
-    for (int i = tid * 4; i < K; i += 256 * WV)
-        *reinterpret_cast<float4*>(il_s + i) = *reinterpret_cast<const float4*>(inv_lambda + i);
+    for (int i = tid * 4; i < (ng - g0) * 64; i += 256 * WV)
+        *reinterpret_cast<float4*>(il_s + i) = *reinterpret_cast<const float4*>(inv_lambda + g0 * 64 + i);
 
     float16v acc[RB];
 #pragma unroll
@@ -81,17 +84,17 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
     // Two register buffers alternate roles (the round body is instantiated twice), so there is no copy
     // and the wait for a prefetched group sits right before its first use, one full round later.
     uint4 xa[RB][4], xb[RB][4];
-    if (wave < ng) {
+    if (g0 + wave < ng) {
 #pragma unroll
         for (int b = 0; b < RB; ++b)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) xa[b][s] = reinterpret_cast<const uint4*>(xrow[b] + wave * 64)[s];
+            for (int s = 0; s < 4; ++s) xa[b][s] = reinterpret_cast<const uint4*>(xrow[b] + (g0 + wave) * 64)[s];
     }
     __syncthreads();
 
-    const int rounds = (ng + WV - 1) / WV;
+    const int rounds = (ng - g0 + WV - 1) / WV;
     auto round_body = [&](const int rd, uint4 (&xc)[RB][4], uint4 (&xn)[RB][4]) {
-        const int g = rd * WV + wave;
+        const int g = g0 + rd * WV + wave;
         if (g < ng) {
             // B operands (hi and lo piece of inv_lambda*L1) of the four k-steps: issued first, used last
             uint4 bfrag[4][2];
@@ -115,7 +118,7 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                 for (int s = 0; s < 4; ++s) xn[b][s] = reinterpret_cast<const uint4*>(xrow[b] + gn * 64)[s];
             __builtin_amdgcn_sched_barrier(0);
 
-            const float* il_lds = il_s + g * 64 + hf * 32;
+            const float* il_lds = il_s + (g - g0) * 64 + hf * 32;
             if (GELU) {
 #pragma unroll
                 for (int b = 0; b < RB; ++b) gelu_tanh_rows(xc[b]);
@@ -240,39 +243,40 @@ hipError_t launch_scale_chain(const float* a, float rho, int64_t n, float* s, fl
 template <bool E3M2, bool GELU, int RB, int WV>
 static hipError_t launch_quantize_geom(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                        const void* l1p, int64_t M, int K, int r,
-                                       uint8_t* qx, float* sx, float* h, hipStream_t stream) {
-    const unsigned blocks = (unsigned)((M + 32 * RB - 1) / (32 * RB));
+                                       uint8_t* qx, float* sx, float* h, int slices, hipStream_t stream) {
+    const int slice = (K / 64 + slices - 1) / slices;                      // groups per slice
+    const dim3 blocks((unsigned)((M + 32 * RB - 1) / (32 * RB)), (unsigned)((K / 64 + slice - 1) / slice));
     const size_t hpart = l1p ? (size_t)WV * 32 * RB * 32 * sizeof(float) : 0;
-    const size_t lds = ((size_t)K * sizeof(float) > hpart) ? (size_t)K * sizeof(float) : hpart;
+    const size_t il = (size_t)slice * 64 * sizeof(float), lds = (il > hpart) ? il : hpart;
     if (l1p)
-        hipLaunchKernelGGL((quantize_kernel<true, E3M2, GELU, RB, WV>), dim3(blocks), dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, qx, sx, h);
+        hipLaunchKernelGGL((quantize_kernel<true, E3M2, GELU, RB, WV>), blocks, dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, slice, qx, sx, h);
     else
-        hipLaunchKernelGGL((quantize_kernel<false, E3M2, GELU, RB, WV>), dim3(blocks), dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, qx, sx, h);
+        hipLaunchKernelGGL((quantize_kernel<false, E3M2, GELU, RB, WV>), blocks, dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, slice, qx, sx, h);
     return hipGetLastError();
 }
 
 template <bool E3M2, bool GELU>
 static hipError_t launch_quantize_any(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                       const void* l1p, int64_t M, int K, int r,
-                                      uint8_t* qx, float* sx, float* h, hipStream_t stream) {
-    auto go = quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_geom<E3M2, GELU, 2, 4> : launch_quantize_geom<E3M2, GELU, 1, 8>;
-    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, stream);
+                                      uint8_t* qx, float* sx, float* h, int slices, hipStream_t stream) {
+    auto go = slices == 1 && quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_geom<E3M2, GELU, 2, 4> : launch_quantize_geom<E3M2, GELU, 1, 8>;
+    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, stream);
 }
 
 hipError_t launch_quantize(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                            const void* l1p, int64_t M, int K, int r,
-                           uint8_t* qx, float* sx, float* h, bool gelu, hipStream_t stream) {
-    return gelu ? launch_quantize_any<false, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, stream)
-                : launch_quantize_any<false, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, stream);
+                           uint8_t* qx, float* sx, float* h, bool gelu, hipStream_t stream, int slices) {
+    return gelu ? launch_quantize_any<false, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, stream)
+                : launch_quantize_any<false, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, stream);
 }
 
 hipError_t launch_quantize_e3m2(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                 const void* l1p, int64_t M, int K, int r,
-                                uint8_t* act, float* sx, float* h, bool gelu, hipStream_t stream) {
-    return gelu ? launch_quantize_any<true, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, stream)
-                : launch_quantize_any<true, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, stream);
+                                uint8_t* act, float* sx, float* h, bool gelu, hipStream_t stream, int slices) {
+    return gelu ? launch_quantize_any<true, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, slices, stream)
+                : launch_quantize_any<true, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, slices, stream);
 }
 
 // Test hook: the activation alone, through the device function the quantise kernels use.

@@ -1,0 +1,354 @@
+// The layer's GEMM (b)+(c) for few tokens.
+//
+// The tile kernels stage 128 or 256 tokens by 128 or 256 channels through LDS and walk all of K in one block: with few
+// tokens that leaves most CUs without a tile and the others with one wave per SIMD waiting for every stage (M = 512,
+// N = K = 5120, E3M2: 160 blocks, 31 us; MXFP4: 40 blocks, 39 us).  Here a block of eight waves owns a small tile (32 or
+// 64 channels by 32 or 64 tokens) and its waves split K: every wave runs its share of the groups straight from global
+// memory to registers, with no LDS and no barrier in the loop, and the eight partial tiles meet in LDS at the end.
+//
+// A wave's K share also decides which part of the low-rank branch it adds: the quantise pass of this path leaves one
+// partial h per slice of K (h = sum of the slices), and h L2 is linear in h, so wave w adds (h of slice w) L2 and
+// no kernel has to add the slices up.
+//
+// Operand sources.  E3M2 activations against the canonical 4-bit weights (expanded in registers: with few tokens the
+// weights are what is read, and expanding them to 6 bits in memory first would move them three times), against the
+// expanded ones, nibble activations against the nibble kernel's packed weights (both turned into E3M2 fields in
+// registers; same integer group sums), and MXFP4.
+#include "svdq_dev.h"
+#include "svdq_epilogue.h"
+#include "svdq_kernels.h"
+#include "svdq_lds.h"
+#include "svdq_quant_dev.h"
+
+namespace svdq {
+
+namespace {
+
+typedef int int8v __attribute__((ext_vector_type(8)));
+
+constexpr int WV = SMALL_SLICES;
+
+struct SmallArgs {
+    const uint8_t* codes;
+    const void* scales;
+    const uint8_t *w0, *w1, *w2;
+    const float* h;              // hs partial h's, [M, r] each
+    int hs;
+    const uint16_t* L2;
+    const float* bias;
+    int64_t M;
+    int N, K, r;
+    uint16_t* y;
+    int64_t ldy;
+};
+
+// Loads are buffer loads: a descriptor and a wave-uniform offset in scalar registers plus a per-lane 32-bit offset that is
+// fixed for the kernel.  (With 64-bit addresses per lane, two registers for every load in flight, the compiler spills.)
+// All tensors of this path are far below 4 GB.
+struct Buffers {
+    __amdgpu_buffer_rsrc_t codes, scales, w0, w1, w2;
+};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* p) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0xffffffffu, 0x00027000);
+}
+template <class T>
+__device__ __forceinline__ T at(__amdgpu_buffer_rsrc_t b, const uint32_t uniform, const uint32_t lane_off) {
+    if constexpr (sizeof(T) == 16) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(b, lane_off, uniform, 0));
+    else if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b, lane_off, uniform, 0));
+    else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, lane_off, uniform, 0));
+    else return __builtin_amdgcn_raw_buffer_load_b16(b, lane_off, uniform, 0);
+}
+template <int MT>
+struct LaneOffsets {
+    uint32_t row[MT];            // token (clamped to M - 1)
+    uint32_t kh, l32, lane, n;   // k half, lane % 32, lane, first channel + lane % 32
+};
+
+// What a lane loads for one step (a 64-group; MXFP4: two) of its tokens and of its channels, and how the two become
+// matrix instructions on y.
+template <int SRC, int MT>
+struct Tokens {
+    uint4 x[MT];
+    uint2 xh[MT];
+    uint32_t sx[MT];
+    __device__ __forceinline__ void load(const SmallArgs& a, const Buffers& B, const int g, const LaneOffsets<MT>& o) {
+        const uint32_t M = (uint32_t)a.M;
+        if constexpr (SRC == SMALL_NIBBLE) {
+#pragma unroll
+            for (int mi = 0; mi < MT; ++mi) {
+                x[mi] = at<uint4>(B.codes, (uint32_t)g * M * 32, o.row[mi] * 32 + o.kh * 16);
+                sx[mi] = at<uint32_t>(B.scales, (uint32_t)g * M * 4, o.row[mi] * 4);
+            }
+        } else {
+            const uint32_t Mp = (M + 3) & ~3u;
+            const uint32_t blk = (uint32_t)g * Mp * E3M2_ROW_BYTES;
+#pragma unroll
+            for (int mi = 0; mi < MT; ++mi) {
+                x[mi] = at<uint4>(B.codes, blk, o.row[mi] * 32 + o.kh * 16);
+                xh[mi] = at<uint2>(B.codes, blk + Mp * 32, (o.kh * Mp + o.row[mi]) * 8);
+                sx[mi] = at<uint32_t>(B.codes, blk + Mp * 48, o.row[mi] * 8);
+            }
+        }
+    }
+};
+template <int SRC, int NI>
+struct Channels {
+    uint4 w[NI];
+    uint2 wh[NI], sf[NI];
+    uint32_t sw[NI];
+    template <int MT>
+    __device__ __forceinline__ void load(const SmallArgs& a, const Buffers& B, const int g, const int nb, const LaneOffsets<MT>& o) {
+        const int ng = a.K >> 6;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            const uint32_t fr = (uint32_t)(nb + ni) * ng + g;
+            if constexpr (SRC == SMALL_E3M2_CANONICAL) {
+                w[ni] = at<uint4>(B.w0, (uint32_t)g * 32 + (uint32_t)ni * 16 * a.K, o.n * (uint32_t)(a.K >> 1) + o.kh * 16);
+                sw[ni] = at<uint32_t>(B.w1, ((uint32_t)g * a.N + ni * 32) * 4, o.n * 4);
+            } else if constexpr (SRC == SMALL_E3M2_PACKED) {
+                w[ni] = at<uint4>(B.w0, fr * 1024, o.lane * 16);
+                wh[ni] = at<uint2>(B.w1, fr * 512, o.lane * 8);
+                sf[ni] = at<uint2>(B.w2, fr * 256, o.l32 * 8);
+            } else {
+                w[ni] = at<uint4>(B.w0, fr * 1024, o.lane * 16);
+                sf[ni] = at<uint2>(B.w1, fr * 512, o.l32 * 8);
+            }
+        }
+    }
+};
+template <int SRC, int NI, int MT>
+__device__ __forceinline__ void multiply(const Tokens<SRC, MT>& t, const Channels<SRC, NI>& c, float16v (&y)[NI][MT], const int kh) {
+    float16v zero;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+    LaneCodes<true> xf[MT];
+    uint2 sp[MT];
+#pragma unroll
+    for (int mi = 0; mi < MT; ++mi) {
+        if constexpr (SRC == SMALL_NIBBLE) xf[mi] = e3m2_of_nibbles(t.x[mi]);
+        else xf[mi] = LaneCodes<true>{t.x[mi], t.xh[mi]};
+        uint32_t p = (SRC == SMALL_NIBBLE) ? split_bf16(bits_f(t.sx[mi])) : t.sx[mi];
+        p = kh ? 0u : p;                              // the scale product uses the lanes of k half 0 only
+        sp[mi] = uint2{p, p};
+    }
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        LaneCodes<true> wf;
+        uint2 s;
+        if constexpr (SRC == SMALL_E3M2_PACKED) wf = LaneCodes<true>{c.w[ni], c.wh[ni]};
+        else wf = e3m2_of_nibbles(c.w[ni]);
+        if constexpr (SRC == SMALL_E3M2_CANONICAL) {
+            const uint32_t p = split_bf16(bits_f(c.sw[ni])), w1 = p & 0xffffu, w2 = p >> 16;
+            s = uint2{w1 | (w1 << 16), w2 | (w2 << 16)};
+        } else {
+            s = c.sf[ni];
+        }
+        s.x = kh ? 0u : s.x;
+        s.y = kh ? 0u : s.y;
+        const int8v av = {(int)wf.lo.x, (int)wf.lo.y, (int)wf.lo.z, (int)wf.lo.w, (int)wf.hi.x, (int)wf.hi.y, 0, 0};
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi) {
+            const int8v bv = {(int)xf[mi].lo.x, (int)xf[mi].lo.y, (int)xf[mi].lo.z, (int)xf[mi].lo.w,
+                              (int)xf[mi].hi.x, (int)xf[mi].hi.y, 0, 0};
+            const float16v P = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, zero, 3, 3, 0, 0x7f, 0, 0x7f);
+            const float16v S = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(short4v, s),
+                                                                        __builtin_bit_cast(short4v, sp[mi]), zero, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) y[ni][mi][i] = __builtin_fmaf(P[i], S[i], y[ni][mi][i]);
+        }
+    }
+}
+
+template <int MT>
+struct Tokens<SMALL_MXFP4, MT> {
+    uint4 x[2][MT];
+    uint32_t sx[MT];
+    __device__ __forceinline__ void load(const SmallArgs& a, const Buffers& B, const int st, const LaneOffsets<MT>& o) {
+        const int ng = a.K >> 6;
+        const uint32_t M = (uint32_t)a.M;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int g = (2 * st + j < ng) ? 2 * st + j : ng - 1;      // a group past K: its scale bytes are zero
+#pragma unroll
+            for (int mi = 0; mi < MT; ++mi) x[j][mi] = at<uint4>(B.codes, (uint32_t)g * M * 32, o.row[mi] * 32 + o.kh * 16);
+        }
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi) sx[mi] = at<uint16_t>(B.scales, (uint32_t)st * M * 4, o.row[mi] * 4 + o.kh * 2);
+    }
+};
+template <int NI>
+struct Channels<SMALL_MXFP4, NI> {
+    uint4 w[2][NI];
+    uint32_t sw[NI];
+    template <int MT>
+    __device__ __forceinline__ void load(const SmallArgs& a, const Buffers& B, const int st, const int nb, const LaneOffsets<MT>& o) {
+        const int ng = a.K >> 6, nst = (ng + 1) >> 1;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                w[j][ni] = at<uint4>(B.w0, ((uint32_t)(nb + ni) * ng + ((2 * st + j < ng) ? 2 * st + j : ng - 1)) * 1024, o.lane * 16);
+            sw[ni] = at<uint16_t>(B.w1, ((uint32_t)(nb + ni) * nst + st) * 128, o.lane * 2);
+        }
+    }
+};
+template <int NI, int MT, int J>
+__device__ __forceinline__ void multiply_group(const Tokens<SMALL_MXFP4, MT>& t, const Channels<SMALL_MXFP4, NI>& c, float16v (&y)[NI][MT]) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        const int8v av = {(int)c.w[J][ni].x, (int)c.w[J][ni].y, (int)c.w[J][ni].z, (int)c.w[J][ni].w, 0, 0, 0, 0};
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi) {
+            const int8v bv = {(int)t.x[J][mi].x, (int)t.x[J][mi].y, (int)t.x[J][mi].z, (int)t.x[J][mi].w, 0, 0, 0, 0};
+            y[ni][mi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, y[ni][mi], 4, 4, J, (int)c.sw[ni], J, (int)t.sx[mi]);
+        }
+    }
+}
+template <int NI, int MT>
+__device__ __forceinline__ void multiply(const Tokens<SMALL_MXFP4, MT>& t, const Channels<SMALL_MXFP4, NI>& c, float16v (&y)[NI][MT], const int) {
+    multiply_group<NI, MT, 0>(t, c, y);
+    multiply_group<NI, MT, 1>(t, c, y);
+}
+
+template <int SRC, int NI, int MT>
+__global__ __launch_bounds__(64 * WV, NI * MT >= 4 ? 2 : 4)
+void small_gemm_kernel(const SmallArgs a) {
+    constexpr int Q = NI * MT * 4;                        // quads of accumulator registers (four neighbouring channels)
+    __shared__ float4 part[WV / 2][Q][64];
+    const int lane = threadIdx.x & 63, l32 = lane & 31, kh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = (int)blockIdx.x * 32 * NI;
+    const int64_t m0 = (int64_t)blockIdx.y * 32 * MT;
+    const Buffers B{buffer(a.codes), buffer(a.scales), buffer(a.w0), buffer(a.w1), buffer(a.w2)};
+    LaneOffsets<MT> off{{}, (uint32_t)kh, (uint32_t)l32, (uint32_t)lane, (uint32_t)(n0 + l32)};
+#pragma unroll
+    for (int mi = 0; mi < MT; ++mi) {
+        const int64_t m = m0 + 32 * mi + l32;
+        off.row[mi] = (uint32_t)(m < a.M ? m : a.M - 1);  // rows beyond M: results never stored
+    }
+    float16v y[NI][MT];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) y[ni][mi][i] = 0.0f;
+
+    // this wave's share of K: steps wave, wave + WV, ... (the lines of a canonical weight row hold four groups: taken by
+    // neighbouring waves at about the same time they are fetched once)
+    constexpr int GROUPS = (SRC == SMALL_MXFP4) ? 2 : 1;
+    const int steps = ((a.K >> 6) + GROUPS - 1) / GROUPS;
+    const int s1 = (steps - wave + WV - 1) / WV;
+    // What bounds a wave is the latency of its loads, above all of the weights, which come from HBM (one step ahead of
+    // their use, a step of 32 x 64 codes took 1.4 us at M = 1): their next DW - 1 steps are in flight, of the tokens
+    // (in L2) the next one.  Loads past the share re-read its last step: with a condition around every load and step the
+    // compiler no longer overlaps them.
+    constexpr int DW = (SRC == SMALL_MXFP4 && NI * MT > 1) ? 3 : (SRC == SMALL_E3M2_PACKED) ? 2 : 4;
+    Tokens<SRC, MT> xt[2];
+    Channels<SRC, NI> wc[DW];
+    auto clamp = [&](const int s) { return wave + WV * ((s < s1) ? s : s1 - 1); };
+    if (s1 > 0) {
+        xt[0].load(a, B, clamp(0), off);
+#pragma unroll
+        for (int d = 0; d < DW - 1; ++d) wc[d].load(a, B, clamp(d), n0 >> 5, off);
+    }
+    constexpr int U = (DW % 2) ? 2 * DW : DW;             // both rings return to their first slot
+    int s = 0;
+    for (; s + U <= s1; s += U) {
+#pragma unroll
+        for (int d = 0; d < U; ++d) {
+            wc[(d + DW - 1) % DW].load(a, B, clamp(s + d + DW - 1), n0 >> 5, off);
+            xt[(d + 1) & 1].load(a, B, clamp(s + d + 1), off);
+            multiply(xt[d & 1], wc[d % DW], y, kh);
+            __builtin_amdgcn_sched_barrier(0);            // steps interleaved would need registers for several
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < U - 1; ++d)
+        if (s + d < s1) {
+            if (d + DW - 1 < U - 1) wc[(d + DW - 1) % DW].load(a, B, clamp(s + d + DW - 1), n0 >> 5, off);
+            xt[(d + 1) & 1].load(a, B, clamp(s + d + 1), off);
+            multiply(xt[d & 1], wc[d % DW], y, kh);
+        }
+
+    if (wave == 0 || (a.r > 0 && wave < a.hs))
+        add_lowrank_bias<NI, MT>(y, a.h + (size_t)wave * a.M * a.r, a.L2, wave == 0 ? a.bias : nullptr, m0, n0, a.M, a.N, a.r, lane);
+
+    // sum of the eight partial tiles: waves 4..7 hand theirs to waves 0..3, then every wave finishes Q / 8 quads of four
+    auto quad = [&](const int q) {
+        const float16v& t = y[(q >> 2) / MT][(q >> 2) % MT];
+        return float4{t[4 * (q & 3)], t[4 * (q & 3) + 1], t[4 * (q & 3) + 2], t[4 * (q & 3) + 3]};
+    };
+    if (wave >= WV / 2) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) part[wave - WV / 2][q][lane] = quad(q);
+    }
+    __syncthreads();
+    if (wave < WV / 2) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const float4 o = part[wave][q][lane], v = quad(q);
+            part[wave][q][lane] = float4{v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w};
+        }
+    }
+    __syncthreads();
+    for (int q = wave; q < Q; q += WV) {
+        const float4 p0 = part[0][q][lane], p1 = part[1][q][lane], p2 = part[2][q][lane], p3 = part[3][q][lane];
+        const float v[4] = {(p0.x + p1.x) + (p2.x + p3.x), (p0.y + p1.y) + (p2.y + p3.y), (p0.z + p1.z) + (p2.z + p3.z),
+                            (p0.w + p1.w) + (p2.w + p3.w)};
+        const int t = q >> 2;
+        const int64_t m = m0 + 32 * (t % MT) + l32;
+        const int n = n0 + 32 * (t / MT) + 8 * (q & 3) + 4 * kh;
+        if (m < a.M) *reinterpret_cast<uint2*>(a.y + m * a.ldy + n) = uint2{f2_bf16_rne(v[0], v[1]), f2_bf16_rne(v[2], v[3])};
+    }
+}
+
+template <int SRC>
+hipError_t launch_src(const SmallArgs& a, hipStream_t stream) {
+    auto go = [&](auto kern, int ni, int mt) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(a.N / (32 * ni)), (unsigned)((a.M + 32 * mt - 1) / (32 * mt))), dim3(64 * WV), 0, stream, a);
+    };
+    if (small_shape(a.M, a.N, SRC == SMALL_MXFP4) == 1) go(small_gemm_kernel<SRC, 1, 1>, 1, 1);
+    else if constexpr (SRC == SMALL_MXFP4) go(small_gemm_kernel<SRC, 1, 2>, 1, 2);
+    else go(small_gemm_kernel<SRC, 2, 2>, 2, 2);
+    return hipGetLastError();
+}
+
+// h = sum of its slices, in slice order
+__global__ __launch_bounds__(256)
+void sum_slices_kernel(const float* __restrict__ part, int slices, int64_t n, float* __restrict__ h) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;       // n is a multiple of 16
+    if (i >= n) return;
+    float4 t = *reinterpret_cast<const float4*>(part + i);
+    for (int s = 1; s < slices; ++s) {
+        const float4 v = *reinterpret_cast<const float4*>(part + s * n + i);
+        t.x += v.x;
+        t.y += v.y;
+        t.z += v.z;
+        t.w += v.w;
+    }
+    *reinterpret_cast<float4*>(h + i) = t;
+}
+
+}  // namespace
+
+hipError_t launch_sum_slices(const float* part, int slices, int64_t M, int r, float* h, hipStream_t stream) {
+    const int64_t n = M * r;
+    hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, part, slices, n, h);
+    return hipGetLastError();
+}
+
+hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1, const void* w2,
+                             const float* h, int slices, const void* L2, const float* bias, int64_t M, int N, int K, int r,
+                             void* y, int64_t ldy, hipStream_t stream) {
+    const SmallArgs a{codes, scales, (const uint8_t*)w0, (const uint8_t*)w1, (const uint8_t*)w2, h, slices,
+                      (const uint16_t*)L2, bias, M, N, K, r, (uint16_t*)y, ldy};
+    switch (source) {
+        case SMALL_E3M2_CANONICAL: return launch_src<SMALL_E3M2_CANONICAL>(a, stream);
+        case SMALL_E3M2_PACKED: return launch_src<SMALL_E3M2_PACKED>(a, stream);
+        case SMALL_NIBBLE: return launch_src<SMALL_NIBBLE>(a, stream);
+        default: return launch_src<SMALL_MXFP4>(a, stream);
+    }
+}
+
+}  // namespace svdq

@@ -1,0 +1,72 @@
+"""The whole layer in one call (svdq_layer_forward) against the oracle, at the sizes where its kernels change or end:
+token counts around the 32- and 64-token tiles, fewer groups than a block has waves, odd group counts, K split between
+blocks in the quantise pass, and token counts on both sides of each change of kernel.
+
+Codes are compared exactly.  y: the bar of the layer (workloads/harness.py) against the oracle's binary64 value: relative
+Frobenius error <= 2e-3 (half a bf16 step at random is 1.1e-3) and per element 1e-2 rms or one bf16 step.
+"""
+import numpy as np
+import pytest
+import torch
+
+from workloads import synth
+from tests.helpers import dev, host_bits, rel_fro, unpack_act_e3m2_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def svdq():
+    import paper_2605_27003_amd as m
+    m.load_library(build_if_missing=False)
+    assert torch.cuda.is_available()
+    return m
+
+
+SHAPES = [  # M, K, N, r, gelu
+    (1, 64, 128, 16, False), (31, 192, 128, 0, False), (33, 576, 256, 32, False), (64, 1088, 128, 32, True),
+    (65, 2112, 384, 16, False),                   # K split in the quantise pass, odd group count
+    (1030, 1024, 640, 32, False),                 # 64 x 64 tiles (MXFP4: 32 x 64), ragged
+    (4096, 64, 128, 16, False), (4097, 64, 128, 16, False),     # last of the 32 x 32 tiles and the next
+    (15360, 64, 128, 0, False), (15361, 64, 128, 32, False),    # last of the 64 x 64 tiles and the next
+]
+
+
+@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble", "mxfp4"])
+@pytest.mark.parametrize("M,K,N,r,gelu", SHAPES)
+def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
+    mx = container == "mxfp4"
+    x, _ = synth.make_x(M + K, M, K, outlier_count=3, outlier_scale=30.0)
+    xa = oracle.gelu_tanh_bf16(x) if gelu else x
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(xa)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(M + K, K, N, r, cm, fmt="mxfp4" if mx else "int4")
+    lin = svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1) if r else None, dev(L.L2) if r else None, dev(L.qw), dev(L.sw),
+                          dev(L.bias), container=container.split()[0], resident="packed" if "packed" in container else "w4")
+    rho = 0.8
+    y = lin.forward(dev(x), rho, gelu=gelu)
+    torch.cuda.synchronize()
+    oq, os_ = (oracle.quantize_act_mxfp4 if mx else oracle.quantize_act)(xa, L.inv_lambda, rho)
+    qx, sx = lin.buffers(M, y.device)[:2]
+    if mx:
+        gq, gs = svdq.mx_to_token_major(qx, sx, K)
+        assert np.array_equal(gs.cpu().numpy(), os_)
+    elif container == "nibble":
+        gq, gs = svdq.to_token_major(qx, sx)
+        assert np.array_equal(gs.cpu().numpy().view(np.uint32), os_.view(np.uint32))
+    else:
+        codes, _ = unpack_act_e3m2_np(qx.buf.cpu().numpy(), M, K)
+        assert np.array_equal(codes, synth.unpack_int4(oq))
+    if mx or container == "nibble":
+        assert np.array_equal(gq.cpu().numpy(), oq)
+    oh = oracle.lowrank_down(xa, L.inv_lambda, L.L1) if r else None
+    orc = (oracle.linear_mxfp4 if mx else oracle.linear)(oq, os_, L.qw, L.sw, oh, L.L2 if r else None, L.bias)
+    got, want = synth.bf16_bits_to_f32(host_bits(y)).astype(np.float64), orc["y64"]
+    assert rel_fro(got, want) <= 2e-3
+    rms = float(np.sqrt(np.mean(want ** 2)))
+    ulp = 2.0 ** (np.floor(np.log2(np.maximum(np.abs(want), 1e-30))) - 7)
+    assert np.all(np.abs(got - want) <= np.maximum(1e-2 * rms, ulp))
+    # the GEMM alone, from the separate quantise pass: the same kernels on one h instead of its slices
+    y1 = y.clone()
+    y2 = lin.gemm(*lin.quantize(dev(x), rho, gelu))
+    torch.cuda.synchronize()
+    assert rel_fro(synth.bf16_bits_to_f32(host_bits(y2)).astype(np.float64), synth.bf16_bits_to_f32(host_bits(y1)).astype(np.float64)) <= 2e-3
