@@ -1,0 +1,46 @@
+"""GPTQ kernels at their edges: a channel count that is odd (rows of W are then not 16-byte aligned), pivots whose
+quotients leave the exponent range of the fast division, and the Hessian with unaligned rows, a token count that is no
+multiple of its four-token step, and both of its tile sizes."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import synth
+from tests.helpers import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def svdq():
+    import paper_2605_27003_amd as m
+    m.load_library(build_if_missing=False)
+    assert torch.cuda.is_available()
+    return m
+
+
+@pytest.mark.parametrize("K,N,scale", [(192, 67, 1.0), (64, 1, 1.0), (256, 96, 2.0 ** -720), (128, 64, 2.0 ** 720)])
+def test_gptq_bit_exact_at_the_edges(svdq, oracle, K, N, scale):
+    """Codes and scales are those of the definition (binary64, oracle) whatever the scale of H: scaling H scales H^-1
+    exactly, by a power of two, but takes the quotients by its diagonal out of the range of the fast division."""
+    g = np.random.default_rng(K + N)
+    z = np.round(8 * (g.standard_normal((2 * K, K)) + np.repeat(g.standard_normal((2 * K, K // 8)), 8, axis=1)))
+    H = (z.T @ z) * scale
+    R = (g.standard_normal((K, N)) * 0.02).astype(np.float32)
+    qw, sw = svdq.gptq_quantize(dev(R), torch.from_numpy(H).cuda())
+    torch.cuda.synchronize()
+    oq, os_ = oracle.gptq_quantize(R, H)
+    assert np.array_equal(sw.cpu().numpy().view(np.uint32), os_.view(np.uint32))
+    assert np.array_equal(qw.cpu().numpy(), oq)
+
+
+@pytest.mark.parametrize("M,K,ld", [(1, 64, 64), (37, 192, 192), (130, 256, 257), (41, 2048, 2048), (19, 2048, 2051)])
+def test_hessian_edges(svdq, oracle, M, K, ld):
+    """Against the oracle's binary64 product; sums of M terms in another order: M 2^-53 relative to the diagonal's size."""
+    x, _ = synth.make_x(3 + M, M, ld, outlier_count=3, outlier_scale=30.0)
+    il = (np.random.default_rng(K).random(K).astype(np.float32) + 0.5)
+    Hg = svdq.gptq_hessian(dev(x)[:, :K], dev(il))
+    torch.cuda.synchronize()
+    H = oracle.gptq_hessian(np.ascontiguousarray(x[:, :K]), il)
+    d = np.sqrt(np.diag(H))
+    assert np.all(np.abs(Hg.cpu().numpy() - H) <= (M + 2) * 2.0 ** -52 * np.outer(d, d))
