@@ -260,7 +260,9 @@ int svdq_debug_gelu(const void* x_bf16, int64_t n, void* out_bf16, void* stream)
  *                 qw [N, K/2] and sw [K/64, N] resident (w_packed NULL); they are expanded when needed.
  *   inv_lambda, l1_packed, L2_bf16, bias, r   as for the separate calls (r = 0: l1_packed and L2_bf16 NULL)
  * svdq_layer_forward: x, ldx, rho, M as svdq_quantize_act, gelu != 0 as svdq_quantize_act_gelu;
- *   codes, scales   the format's activation buffers (scales unused and may be NULL for SVDQ_FMT_INT4_E3M2)
+ *   codes           svdq_layer_codes_bytes(layer, M) bytes, 16-byte aligned, scales the format's scale buffer (unused, may
+ *                   be NULL for SVDQ_FMT_INT4_E3M2): for the quantised activations, in whichever of the library's forms
+ *                   the size calls for (SVDQ_FMT_INT4 with many tokens runs as E3M2 fields: same codes and scales)
  *   h               [M, r] binary32; holds intermediate values, not necessarily h, afterwards
  *   scratch         svdq_layer_scratch_bytes(layer, M) bytes, 16-byte aligned, or NULL (slower with few tokens)
  *   staging         svdq_layer_staging_bytes(layer, M) bytes, 16-byte aligned: room for the expanded weights of one
@@ -278,6 +280,7 @@ typedef struct {
     const uint8_t* qw;
     const void* sw;
 } svdq_layer;
+size_t svdq_layer_codes_bytes(const svdq_layer* layer, int64_t M);
 size_t svdq_layer_scratch_bytes(const svdq_layer* layer, int64_t M);
 size_t svdq_layer_staging_bytes(const svdq_layer* layer, int64_t M);
 int svdq_layer_forward(const svdq_layer* layer, const void* x_bf16, int64_t ldx, float rho, int gelu, int64_t M,

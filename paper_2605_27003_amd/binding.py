@@ -40,6 +40,7 @@ EXPORTS = {
     "svdq_linear_mxfp4": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _i32, _vp, _i64, _i32, _vp]),
     "svdq_linear_mxfp4_next": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _i32, _i32,
                                       _vp, _f32, _vp, _i32, _vp, _vp, _vp, _vp]),
+    "svdq_layer_codes_bytes": (ctypes.c_size_t, [_vp, _i64]),
     "svdq_layer_scratch_bytes": (ctypes.c_size_t, [_vp, _i64]),
     "svdq_layer_staging_bytes": (ctypes.c_size_t, [_vp, _i64]),
     "svdq_layer_forward": (_i32, [_vp, _vp, _i64, _f32, _i32, _i64, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _vp]),
@@ -516,10 +517,12 @@ def _addr(t):
 class W4A4Linear:
     """One quantised linear resident in HBM: weights and low-rank factors, reusable output buffers.
 
-    container "e3m2" (default) runs the int4 layer on the FP6 matrix cores, "nibble" the same layer on 4-bit storage
-    and the int8 matrix cores, "mxfp4" the MXFP4 format (qw then holds E2M1 codes and sw [K/32, N] E8M0 bytes).
-    resident "w4" (default, container "e3m2" only) keeps the canonical 4-bit weights (qw, sw) and expands them into a
-    staging buffer shared by all such layers of the device right before every GEMM (calls on one stream only);
+    container "e3m2" (default) runs the int4 layer on the FP6 matrix cores, "nibble" the same layer from 4-bit packed
+    weights (quantize() and gemm() on 4-bit activations and the int8 matrix cores; forward() on the FP6 ones, with the
+    same codes and scales), "mxfp4" the MXFP4 format (qw then holds E2M1 codes and sw [K/32, N] E8M0 bytes).
+    resident "w4" (default, container "e3m2" only) keeps the canonical 4-bit weights (qw, sw); these, and the nibble
+    container's, are expanded into a staging buffer shared by all such layers of the device right before a GEMM of many
+    tokens (calls on one stream only);
     "packed" keeps the container's own packed form (7 - 8 bits per weight for the int4 containers)."""
 
     def __init__(self, inv_lambda, L1_bf16, L2_bf16, qw, sw, bias, container="e3m2", resident="w4"):
@@ -551,11 +554,12 @@ class W4A4Linear:
     def buffers(self, M, device):
         if self._bufs is None or self._bufs[3].shape[0] != M:
             lib = load_library()
+            codes = torch.empty(lib.svdq_layer_codes_bytes(self._ref, M), dtype=torch.uint8, device=device)
+            self._codes = codes
             if self.container == "e3m2":
-                qx = ActE3M2(torch.empty(act_e3m2_bytes(M, self.K), dtype=torch.uint8, device=device), M, self.K)
-                sx = None
+                qx, sx = ActE3M2(codes, M, self.K), None
             else:
-                qx = torch.empty((self.K // 64, M, 32), dtype=torch.uint8, device=device)
+                qx = codes[: M * self.K // 2].view(self.K // 64, M, 32)
                 sx = (torch.empty((self.K // 64, M), dtype=torch.float32, device=device) if self.container == "nibble"
                       else torch.empty(((self.K // 64 + 1) // 2, M, 2, 2), dtype=torch.uint8, device=device))
             h = torch.empty((M, self.r), dtype=torch.float32, device=device) if self.r else None
@@ -563,9 +567,9 @@ class W4A4Linear:
             n = lib.svdq_layer_scratch_bytes(self._ref, M)
             self._scratch = torch.empty(n, dtype=torch.uint8, device=device) if n else None
             self._staging_bytes = lib.svdq_layer_staging_bytes(self._ref, M)
-            if self.w_packed is None:                    # reserved with the first buffers, though small M expands nothing
+            if self.container == "e3m2" and self.w_packed is None:      # reserved with the first buffers, though small M expands nothing
                 _staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), device)
-            self._ptrs = tuple(map(_addr, (qx.buf if self.container == "e3m2" else qx, sx, h, self._scratch)))
+            self._ptrs = tuple(map(_addr, (codes, sx, h, self._scratch)))
             self._bufs = (qx, sx, h, y)
         return self._bufs
 

@@ -342,7 +342,7 @@ int svdq_linear_mxfp4(const uint8_t* qx, const uint8_t* sx_e8m0, const void* w_p
     if (M > SVDQ_MAX_M) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
-    return hip_status(svdq::launch_linear_mx(qx, sx_e8m0, w_packed, h, L2_bf16, bias, M, N, K, r, y, ldy,
+    return hip_status(svdq::launch_linear_mx(qx, sx_e8m0, w_packed, h, L2_bf16, bias, M, 0, M, N, K, r, y, ldy,
                                              out_dtype == SVDQ_OUT_F32, (hipStream_t)stream));
 }
 
@@ -404,13 +404,25 @@ size_t svdq_layer_scratch_bytes(const svdq_layer* L, int64_t M) {
     return s > 1 ? (size_t)s * (size_t)M * L->r * sizeof(float) : 0;
 }
 
+// Nibble storage with more tokens than the few-token path takes runs as E3M2 fields as well: the FP6 instruction takes a
+// whole group at twice the int8 rate, and writing the activations as fields (56 instead of 36 bytes per token and group)
+// and expanding the weights cost less than that saves (M = 32760, K = N = 5120: 1.05 against 1.39 ms; M = 512: 39
+// against 44 us).  Same codes, same integer group sums, same scale pieces.
+static bool as_fields(const svdq_layer* L, int64_t M) { return L->format == SVDQ_FMT_INT4 && !small_path(L, M); }
+
+size_t svdq_layer_codes_bytes(const svdq_layer* L, int64_t M) {
+    if (layer_check(L, M) != SVDQ_OK) return 0;
+    return (L->format == SVDQ_FMT_INT4_E3M2 || as_fields(L, M)) ? svdq::act_e3m2_bytes(M, L->K) : (size_t)M * L->K / 2;
+}
+
 size_t svdq_layer_staging_bytes(const svdq_layer* L, int64_t M) {
-    if (layer_check(L, M) != SVDQ_OK || L->w_packed || small_path(L, M)) return 0;
+    if (layer_check(L, M) != SVDQ_OK || small_path(L, M) || (L->w_packed && !as_fields(L, M))) return 0;
     return svdq::packed_weight_e3m2_bytes(L->N, L->K);
 }
 
-// the GEMM on checked arguments; h: `slices` partial h's for the few-token kernel, one otherwise
-static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, const float* h, int slices, int64_t M,
+// The GEMM on checked arguments.  h: `slices` partial h's for the few-token kernel, one otherwise.  fields: codes are
+// E3M2 fields whatever the format.
+static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool fields, const float* h, int slices, int64_t M,
                       void* staging, void* y, int64_t ldy, hipStream_t stream) {
     const int N = L->N, K = L->K, r = L->r;
     const uint8_t* wp = (const uint8_t*)L->w_packed;
@@ -431,15 +443,22 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
             w1 = wp + svdq::packed_e3m2_w0_bytes(N, K);
             w2 = (const uint8_t*)w1 + svdq::packed_e3m2_w1_bytes(N, K);
         }
-        return hip_status(svdq::launch_small_gemm(source, codes, scales, w0, w1, w2, h, slices, L->L2_bf16, L->bias, M, N, K, r, y, ldy, stream));
+        return hip_status(svdq::launch_small_gemm(source, codes, scales, w0, w1, w2, h, slices, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
     }
-    if (L->format == SVDQ_FMT_INT4)
+    if (L->format == SVDQ_FMT_MXFP4) {
+        const int64_t main = svdq::mx_main_rows(M, N, K);
+        const hipError_t e = svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, 0, main, N, K, r, y, ldy, 0, stream);
+        if (e != hipSuccess || main == M) return hip_status(e);
+        if (!svdq::small_shape(M - main, N))
+            return hip_status(svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, main, M, N, K, r, y, ldy, 0, stream));
+        return hip_status(svdq::launch_small_gemm(svdq::SMALL_MXFP4, codes, scales, wp, wp + svdq::packed_mx_codes_bytes(N, K), nullptr, h, 1,
+                                                  L->L2_bf16, L->bias, M, main, N, K, r, y, ldy, stream));
+    }
+    if (L->format == SVDQ_FMT_INT4 && !fields)
         return hip_status(svdq::launch_linear(codes, (const float*)scales, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, 0, stream));
-    if (L->format == SVDQ_FMT_MXFP4)
-        return hip_status(svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, 0, stream));
-    if (!wp) {
-        if (!staging || !aligned16(staging)) return SVDQ_ERR_INVALID_ARG;
-        const hipError_t e = svdq::launch_pack_weight_e3m2(L->qw, (const float*)L->sw, N, K, staging, stream);
+    if (!wp || L->format == SVDQ_FMT_INT4) {
+        const hipError_t e = wp ? svdq::launch_repack_weight_e3m2(wp, N, K, staging, stream)
+                                : svdq::launch_pack_weight_e3m2(L->qw, (const float*)L->sw, N, K, staging, stream);
         if (e != hipSuccess) return hip_status(e);
         wp = (const uint8_t*)staging;
     }
@@ -456,9 +475,10 @@ int svdq_layer_gemm(const svdq_layer* L, const void* codes, const void* scales, 
                     void* staging, void* y, int64_t ldy, void* stream) {
     if (int e = layer_check(L, M)) return e;
     if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
+    if (!L->w_packed && !small_path(L, M) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
-    return layer_gemm(L, (const uint8_t*)codes, scales, h, 1, M, staging, y, ldy, (hipStream_t)stream);
+    return layer_gemm(L, (const uint8_t*)codes, scales, false, h, 1, M, staging, y, ldy, (hipStream_t)stream);
 }
 
 int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, float rho, int gelu, int64_t M,
@@ -468,7 +488,8 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
     if (!x_bf16 || !(rho > 0.0f) || !(rho <= 1.0f)) return SVDQ_ERR_INVALID_ARG;
     if (ldx < L->K || ldx % 8 || !aligned16(x_bf16) || !aligned16(scratch)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
-    if (!L->w_packed && !small_path(L, M) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
+    const bool fields = as_fields(L, M);
+    if ((fields || (!L->w_packed && !small_path(L, M))) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
     hipStream_t stream = (hipStream_t)stream_;
@@ -477,7 +498,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     int slices = (r == 0 || scratch) ? layer_slices(L, M) : 1;
     float* const ho = (r != 0 && slices > 1) ? (float*)scratch : h;
     hipError_t e;
-    if (L->format == SVDQ_FMT_INT4)
+    if (L->format == SVDQ_FMT_INT4 && !fields)
         e = svdq::launch_quantize(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, (float*)scales, ho, gelu != 0, stream, slices);
     else if (L->format == SVDQ_FMT_MXFP4)
         e = svdq::launch_quantize_mx(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, (uint8_t*)scales, ho, gelu != 0, stream, slices);
@@ -491,7 +512,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
         hin = h;
         slices = 1;
     }
-    return layer_gemm(L, (const uint8_t*)codes, scales, r ? hin : nullptr, r ? slices : 1, M, staging, y, ldy, stream);
+    return layer_gemm(L, (const uint8_t*)codes, scales, fields, r ? hin : nullptr, r ? slices : 1, M, staging, y, ldy, stream);
 }
 
 size_t svdq_gptq_workspace_bytes(int N, int K) {

@@ -558,6 +558,19 @@ void pack_weight_e3m2_kernel(const uint8_t* __restrict__ qw, const float* __rest
     }
 }
 
+// The same from the nibble kernel's packed weights (svdq_gemm.hip): its code fragments hold the same bytes per lane and
+// its scale operands the same pieces, eight bytes in the lanes of k half 0.
+__global__ __launch_bounds__(256)
+void repack_weight_e3m2_kernel(const uint4* __restrict__ frag, const uint2* __restrict__ sfrag, int N, int K, uint8_t* __restrict__ out) {
+    const int ng = K >> 6;
+    const size_t v = (size_t)blockIdx.x * 256 + threadIdx.x, lane = v & 63, fr = v >> 6;
+    if (fr >= (size_t)(N >> 5) * ng) return;
+    const LaneCodes<true> c = e3m2_of_nibbles(frag[v]);
+    reinterpret_cast<uint4*>(out)[v] = c.lo;
+    reinterpret_cast<uint2*>(out + w0_bytes(N, K))[v] = c.hi;
+    if (lane < 32) reinterpret_cast<uint2*>(out + w0_bytes(N, K) + w1_bytes(N, K))[fr * 32 + lane] = sfrag[v];
+}
+
 // Activation operand buffer -> nibble codes qx [K/64][M][32 B] (the layout of the int4 path)
 __global__ void unpack_act_e3m2_kernel(const uint8_t* __restrict__ act, int64_t M, int K, uint8_t* __restrict__ qx) {
     const int ng = K >> 6;
@@ -598,6 +611,14 @@ size_t packed_weight_e3m2_bytes(int N, int K) { return w0_bytes(N, K) + w1_bytes
 hipError_t launch_pack_weight_e3m2(const uint8_t* qw, const float* sw, int N, int K, void* out, hipStream_t stream) {
     const size_t waves = (size_t)(N / 32) * ((K / 64 + PACK_GROUPS - 1) / PACK_GROUPS);
     hipLaunchKernelGGL(pack_weight_e3m2_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream, qw, sw, N, K, (uint8_t*)out);
+    return hipGetLastError();
+}
+
+hipError_t launch_repack_weight_e3m2(const void* w_packed_nibble, int N, int K, void* out, hipStream_t stream) {
+    const size_t lanes = (size_t)(N / 32) * (K / 64) * 64;
+    const uint8_t* base = (const uint8_t*)w_packed_nibble;
+    hipLaunchKernelGGL(repack_weight_e3m2_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, stream,
+                       (const uint4*)base, (const uint2*)(base + packed_weight_codes_bytes(N, K)), N, K, (uint8_t*)out);
     return hipGetLastError();
 }
 

@@ -38,6 +38,7 @@ size_t packed_weight_e3m2_bytes(int N, int K);
 inline size_t packed_e3m2_w0_bytes(int N, int K) { return (size_t)N * (K / 64) * 32; }     // planes of the packed weights
 inline size_t packed_e3m2_w1_bytes(int N, int K) { return (size_t)N * (K / 64) * 16; }
 hipError_t launch_pack_weight_e3m2(const uint8_t* qw, const float* sw, int N, int K, void* out, hipStream_t stream);
+hipError_t launch_repack_weight_e3m2(const void* w_packed_nibble, int N, int K, void* out, hipStream_t stream);
 hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
                               const float* h, const void* L2, const float* bias,
                               int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32,
@@ -55,17 +56,18 @@ hipError_t launch_unpack_act_e3m2(const uint8_t* act, int64_t M, int K, uint8_t*
 enum { SMALL_E3M2_CANONICAL = 0, SMALL_E3M2_PACKED = 1, SMALL_NIBBLE = 2, SMALL_MXFP4 = 3 };   // operand sources
 constexpr int SMALL_SLICES = 8;                  // waves of a block = most partial h's the GEMM takes
 // Which tile of the few-token GEMM a layer takes: 1: 32 channels x 32 tokens; 2: 64 x 64 (MXFP4: 32 x 64); 0: none, the
-// tile kernels.  Measured (K = 5120, us): 32 x 32 wins up to two blocks per CU (N = 5120: M <= 64, N = 512: all M up
-// to 1024; MXFP4, which waits for loads only: one); 64 x 64 then wins while its blocks are one round of two per CU (E3M2 M = 384, N = 5120: 33 against 39 of
-// the tile kernel and its weight expansion; M = 512: 46 against 39), for MXFP4, whose tile kernel has four times larger
-// tiles, twice that (M = 768, N = 5120: 30 against 34; M = 1024: even).
-inline int small_shape(int64_t M, int N, bool mxfp4) {
+// tile kernels.  Measured (K = 5120, us): 32 x 32 wins up to two blocks per CU (N = 5120: M <= 64, N = 512: all M up to
+// 1024; MXFP4, which waits for loads only: one); 64 x 64 then wins while its blocks are one round of two per CU (E3M2,
+// N = 5120: M = 384, 30 against 39 of the tile kernel and its weight expansion; M = 512, 43 against 39.  MXFP4: 256, 13
+// against 16; 384, even; N = 13824: 128, even).
+inline int small_shape(int64_t M, int N, bool mxfp4 = true) {
     const int64_t b32 = ((M + 31) / 32) * (N / 32), b64 = ((M + 63) / 64) * ((N + 63) / 64);
     if (b32 <= (mxfp4 ? 256 : 512)) return 1;
-    return b64 <= (mxfp4 ? 960 : 480) ? 2 : 0;
+    return b64 <= 480 ? 2 : 0;
 }
+// tokens [begin, M)
 hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1, const void* w2,
-                             const float* h, int slices, const void* L2, const float* bias, int64_t M, int N, int K, int r,
+                             const float* h, int slices, const void* L2, const float* bias, int64_t M, int64_t begin, int N, int K, int r,
                              void* y, int64_t ldy, hipStream_t stream);
 hipError_t launch_sum_slices(const float* part, int slices, int64_t M, int r, float* h, hipStream_t stream);
 
@@ -76,10 +78,12 @@ hipError_t launch_pack_weight_mx(const uint8_t* qw, const uint8_t* sw, int N, in
 hipError_t launch_quantize_mx(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                               const void* l1p, int64_t M, int K, int r,
                               uint8_t* qx, uint8_t* sxe, float* h, bool gelu, hipStream_t stream, int slices = 1);
+// tokens [begin, end) of M; begin a multiple of 256
 hipError_t launch_linear_mx(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
                             const float* h, const void* L2, const float* bias,
-                            int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32,
+                            int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
                             hipStream_t stream);
+int64_t mx_main_rows(int64_t M, int N, int K);       // tokens that are best left to the tile kernels (the rest: few tokens)
 hipError_t launch_linear_mx_next(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
                                  const float* h, const void* L2, const float* bias,
                                  int64_t M, int N, int K, int r, bool gelu,

@@ -287,7 +287,7 @@ struct MxGeom {
     // direct global->LDS loads per wave and stage.  4 waves: MT of A, 2 of W, 1 + 1 of scales;
     // 8 waves: 2 of A, 2 of W, 1 of scales (token scales on waves 0..3, channel scales on waves 4..7)
     static constexpr int NDMA = (WNC == 2) ? MT + 4 : 5;
-    static constexpr int NS = (WNC == 2) ? 3 : 4;                   // LDS ring slots: 78 KB (two blocks per CU) or 136 KB (one)
+    static constexpr int NS = (WNC == 2) ? 3 : 4;                   // LDS ring slots: 78 or 52 KB (two or three blocks per CU) or 136 KB (one)
     static_assert(WNC == 2 || (WNC == 4 && MT == 4), "staging is written for 4 waves, or 8 waves with 256 tokens");
 };
 
@@ -416,7 +416,7 @@ __device__ __forceinline__ void add_next_h(float16v (&hp)[MT], float* part, int 
 enum { MX_LAYER = 0, MX_NEXT = 1, MX_NEXT_GELU = 2 };
 
 template <int MT, int WNC, int MODE>
-__global__ __launch_bounds__(128 * WNC, (WNC == 2) ? 2 : 1)
+__global__ __launch_bounds__(128 * WNC, (WNC == 4) ? 1 : (MT == 4) ? 2 : 3)
 void gemm_mx_kernel(const uint8_t* __restrict__ qx, const uint16_t* __restrict__ sxe,
                     const uint4* __restrict__ wfrag, const uint16_t* __restrict__ wscale,
                     const float* __restrict__ h, const uint16_t* __restrict__ L2, const float* __restrict__ bias,
@@ -556,9 +556,10 @@ void gemm_mx_kernel(const uint8_t* __restrict__ qx, const uint16_t* __restrict__
         }
     };
 
-    // The eight matrix instructions of a group carry, between them, the LDS reads of the OTHER operand set (two per
-    // instruction) and, in a stage's second group, the slot's new transfer requests (one each).  Requested as a burst
-    // ahead of a group they are time in which the matrix pipe has nothing queued: the waves of a block run in step.
+    // The 2 MT matrix instructions of a group carry, between them, the LDS reads of the OTHER operand set (two per
+    // instruction) and, in a stage's second group, the slot's new transfer requests (one each, two with MT = 2).
+    // Requested as a burst ahead of a group they are time in which the matrix pipe has nothing queued: the waves of a
+    // block run in step.
     auto mma_with_fetch = [&](const Operands& o, auto JC, Operands& on, const uint32_t slot, const int jn, auto request) {
         constexpr int j = decltype(JC)::value;
         auto one = [&](auto TC) {
@@ -568,6 +569,7 @@ void gemm_mx_kernel(const uint8_t* __restrict__ qx, const uint16_t* __restrict__
             y[ni][mi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, y[ni][mi], 4, 4, j, (int)o.sw[ni], j, (int)o.sx[mi]);
             __builtin_amdgcn_sched_barrier(0);
             if (t < NDMA) request(t);
+            if (t + 2 * MT < NDMA) request(t + 2 * MT);
             if (t < 2) {
                 on.wf[t] = lds_read16_pinned(slot + rd_w + jn * 2048 * WNC + t * 1024);
                 on.sw[t] = lds_read2_pinned(slot + rd_sw + t * 128);
@@ -577,9 +579,11 @@ void gemm_mx_kernel(const uint8_t* __restrict__ qx, const uint16_t* __restrict__
             }
             __builtin_amdgcn_sched_barrier(0);
         };
-        static_assert(MT == 4 && NDMA <= 8, "eight instructions per group");
+        static_assert((MT == 4 || MT == 2) && NDMA <= 4 * MT, "two requests per instruction at most");
         one(IC<0>{}); one(IC<1>{}); one(IC<2>{}); one(IC<3>{});
-        one(IC<4>{}); one(IC<5>{}); one(IC<6>{}); one(IC<7>{});
+        if constexpr (MT == 4) {
+            one(IC<4>{}); one(IC<5>{}); one(IC<6>{}); one(IC<7>{});
+        }
     };
 
     // One stage.  FULL: stages s+1..s+NS exist, so the body is straight-line code (the compiler otherwise sinks
@@ -1045,32 +1049,100 @@ static inline bool walks_tiles(int mtiles, int N, int K) {
     return N % 256 == 0 && K >= 576 && (int64_t)mtiles * (N / 256) >= 2 * walking_blocks();
 }
 
-hipError_t launch_linear_mx(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
-                            const float* h, const void* L2, const float* bias,
-                            int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32,
-                            hipStream_t stream) {
-    constexpr int MT = 4;
+// ---- which tiles a launch takes.  All of them give the same bits: the order of operations per output is the same.
+enum class MxTile { T256x256, T256x128, T128x128 };
+struct MxPart {                  // token tiles of 256 [first, first + count) on tiles `tile`, estimated cost
+    MxTile tile;
+    double cost;
+};
+
+// Cheapest tile for `rows` tokens.  A launch takes what its busiest XCD takes, in whole blocks per CU c (with several
+// blocks on a CU sharing it): measured at K = 5120, 5 + 13.3 c us for 128 x 128 tiles (four waves, three blocks fit a CU),
+// 4 + 21.7 c for 256 x 128 (four waves, two blocks), 1.5 + 38 c for 256 x 256 (eight waves, one block; as one block per
+// CU that walks its tiles 37 c).  Per element the large tiles are a quarter cheaper, but M = 768, N = 5120 is 60 of them
+// on 256 CUs: 34 us against 19 with 240 tiles of 128 x 128.
+static MxPart mx_best(int64_t rows, int N, int K) {
+    auto blocks = [&](int bm, int bn) {
+        return (double)((busiest_xcd((int)((rows + bm - 1) / bm), N / bn) + CUS_PER_XCD - 1) / CUS_PER_XCD);
+    };
+    MxPart best{MxTile::T128x128, 5.0 + 13.3 * blocks(128, 128)};
+    const double c2 = 4.0 + 21.7 * blocks(256, 128);
+    if (c2 < best.cost) best = MxPart{MxTile::T256x128, c2};
+    if (N % 256 == 0) {
+        const double c1 = 1.5 + (walks_tiles((int)((rows + 255) / 256), N, K) ? 37.0 : 38.0) * blocks(256, 256);
+        if (c1 <= best.cost) best = MxPart{MxTile::T256x256, c1};
+    }
+    return best;
+}
+
+// Tokens of the first launch (a multiple of 256, or all of them): leaving the last tokens to a launch of their own on
+// smaller tiles pays where they would open another round of blocks for themselves (M = 2305, N = 13824: 70 tiles of
+// 256 x 256 on the busiest XCD's 32 CUs, 63 without the one row beyond 2304).  `tail_cost`: what a launch for the rest
+// costs, in the unit of mx_best.
+template <class TailCost>
+static int64_t mx_split(int64_t M, int N, int K, TailCost tail_cost) {
+    const int mtiles = (int)((M + 255) / 256);
+    double best = mx_best(M, N, K).cost;
+    int64_t rows = M;
+    for (int mt = mtiles - 1; mt >= 1 && mt >= mtiles - 12; --mt) {
+        const double c = mx_best((int64_t)mt * 256, N, K).cost + tail_cost(M - (int64_t)mt * 256) + 3.0;      // a launch more
+        if (c < 0.97 * best) {
+            best = c;
+            rows = (int64_t)mt * 256;
+        }
+    }
+    return rows;
+}
+
+int64_t mx_main_rows(int64_t M, int N, int K) {
+    return mx_split(M, N, K, [&](int64_t rest) {
+        const double few = 5.0 + 0.025 * (double)((rest + 63) / 64) * (double)((N + 63) / 64);                   // the few-token kernel
+        const double tiles = mx_best(rest, N, K).cost;
+        return small_shape(rest, N) && few < tiles ? few : tiles;
+    });
+}
+
+// The tiles of tokens [begin, end), begin a multiple of 256.
+static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
+                                  const float* h, const void* L2, const float* bias,
+                                  int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
+                                  hipStream_t stream) {
     const uint8_t* base = (const uint8_t*)w_packed;
     const uint16_t* wsc = (const uint16_t*)(base + mx_wfrag_bytes(N, K));
-    const int mtiles = (int)((M + 64 * MT - 1) / (64 * MT));
-    if (walks_tiles(mtiles, N, K)) {         // 256 x 256 block tiles, eight waves, one block per CU walking its tiles
-        // without a low-rank branch the kernel's h transfers still run (they have no branch): give them the codes to read
+    const int64_t rows = end - begin;
+    auto grid = [&](int bm, int bn) { return make_tile_grid((int)((rows + bm - 1) / bm), N / bn, (int)(begin / bm)); };
+    auto one_tile = [&](auto kern, int bm, int bn, int threads) {
+        const TileGrid tg = grid(bm, bn);
+        hipLaunchKernelGGL(kern, dim3((unsigned)tile_ids(tg)), dim3(threads), 0, stream,
+                           qx, (const uint16_t*)sxe, (const uint4*)base, wsc, h, (const uint16_t*)L2, bias,
+                           M, N, K, r, y, ldy, out_f32, tg, MxNext{});
+    };
+    const MxTile tile = mx_best(rows, N, K).tile;
+    if (tile == MxTile::T256x256 && walks_tiles((int)((rows + 255) / 256), N, K)) {
+        // one block per CU walking its tiles.  Without a low-rank branch the kernel's h transfers still run (they have no
+        // branch): give them the codes to read
         const float* hrows = (r > 0) ? h : (const float*)qx;
-        hipLaunchKernelGGL((gemm_mx_persistent_kernel<MT>), dim3((unsigned)walking_blocks()), dim3(512), 0, stream,
+        hipLaunchKernelGGL((gemm_mx_persistent_kernel<4>), dim3((unsigned)walking_blocks()), dim3(512), 0, stream,
                            qx, (const uint16_t*)sxe, (const uint4*)base, wsc, hrows, (const uint16_t*)L2, bias,
-                           M, N, K, r, y, ldy, out_f32, make_tile_grid(mtiles, N / 256));
-    } else if (N % 256 == 0) {               // 256 x 256 block tiles, eight waves, one block per CU and tile
-        const TileGrid tg = make_tile_grid(mtiles, N / 256);
-        hipLaunchKernelGGL((gemm_mx_kernel<MT, 4, MX_LAYER>), dim3((unsigned)tile_ids(tg)), dim3(512), 0, stream,
-                           qx, (const uint16_t*)sxe, (const uint4*)base, wsc, h, (const uint16_t*)L2, bias,
-                           M, N, K, r, y, ldy, out_f32, tg, MxNext{});
-    } else {                                 // 256 x 128 block tiles, four waves, two blocks per CU
-        const TileGrid tg = make_tile_grid(mtiles, N / 128);
-        hipLaunchKernelGGL((gemm_mx_kernel<MT, 2, MX_LAYER>), dim3((unsigned)tile_ids(tg)), dim3(256), 0, stream,
-                           qx, (const uint16_t*)sxe, (const uint4*)base, wsc, h, (const uint16_t*)L2, bias,
-                           M, N, K, r, y, ldy, out_f32, tg, MxNext{});
+                           M, N, K, r, y, ldy, out_f32, grid(256, 256));
+    } else if (tile == MxTile::T256x256) {
+        one_tile(gemm_mx_kernel<4, 4, MX_LAYER>, 256, 256, 512);
+    } else if (tile == MxTile::T256x128) {
+        one_tile(gemm_mx_kernel<4, 2, MX_LAYER>, 256, 128, 256);
+    } else {
+        one_tile(gemm_mx_kernel<2, 2, MX_LAYER>, 128, 128, 256);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_linear_mx(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
+                            const float* h, const void* L2, const float* bias,
+                            int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
+                            hipStream_t stream) {
+    const int64_t mid = begin + mx_split(end - begin, N, K, [&](int64_t rest) { return mx_best(rest, N, K).cost; });
+    hipError_t e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, begin, mid, N, K, r, y, ldy, out_f32, stream);
+    if (e == hipSuccess && mid < end) e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, mid, end, N, K, r, y, ldy, out_f32, stream);
+    return e;
 }
 
 __global__ void zero_f32_mx_kernel(float* __restrict__ p, int64_t n) {   // a kernel, not a memset (graph replays)

@@ -36,7 +36,7 @@ struct SmallArgs {
     int hs;
     const uint16_t* L2;
     const float* bias;
-    int64_t M;
+    int64_t M, begin;            // tokens [begin, M)
     int N, K, r;
     uint16_t* y;
     int64_t ldy;
@@ -218,7 +218,7 @@ void small_gemm_kernel(const SmallArgs a) {
     const int lane = threadIdx.x & 63, l32 = lane & 31, kh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = (int)blockIdx.x * 32 * NI;
-    const int64_t m0 = (int64_t)blockIdx.y * 32 * MT;
+    const int64_t m0 = a.begin + (int64_t)blockIdx.y * 32 * MT;
     const Buffers B{buffer(a.codes), buffer(a.scales), buffer(a.w0), buffer(a.w1), buffer(a.w2)};
     LaneOffsets<MT> off{{}, (uint32_t)kh, (uint32_t)l32, (uint32_t)lane, (uint32_t)(n0 + l32)};
 #pragma unroll
@@ -306,9 +306,9 @@ void small_gemm_kernel(const SmallArgs a) {
 template <int SRC>
 hipError_t launch_src(const SmallArgs& a, hipStream_t stream) {
     auto go = [&](auto kern, int ni, int mt) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)(a.N / (32 * ni)), (unsigned)((a.M + 32 * mt - 1) / (32 * mt))), dim3(64 * WV), 0, stream, a);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(a.N / (32 * ni)), (unsigned)((a.M - a.begin + 32 * mt - 1) / (32 * mt))), dim3(64 * WV), 0, stream, a);
     };
-    if (small_shape(a.M, a.N, SRC == SMALL_MXFP4) == 1) go(small_gemm_kernel<SRC, 1, 1>, 1, 1);
+    if (small_shape(a.M - a.begin, a.N, SRC == SMALL_MXFP4) == 1) go(small_gemm_kernel<SRC, 1, 1>, 1, 1);
     else if constexpr (SRC == SMALL_MXFP4) go(small_gemm_kernel<SRC, 1, 2>, 1, 2);
     else go(small_gemm_kernel<SRC, 2, 2>, 2, 2);
     return hipGetLastError();
@@ -339,10 +339,10 @@ hipError_t launch_sum_slices(const float* part, int slices, int64_t M, int r, fl
 }
 
 hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1, const void* w2,
-                             const float* h, int slices, const void* L2, const float* bias, int64_t M, int N, int K, int r,
+                             const float* h, int slices, const void* L2, const float* bias, int64_t M, int64_t begin, int N, int K, int r,
                              void* y, int64_t ldy, hipStream_t stream) {
     const SmallArgs a{codes, scales, (const uint8_t*)w0, (const uint8_t*)w1, (const uint8_t*)w2, h, slices,
-                      (const uint16_t*)L2, bias, M, N, K, r, (uint16_t*)y, ldy};
+                      (const uint16_t*)L2, bias, M, begin, N, K, r, (uint16_t*)y, ldy};
     switch (source) {
         case SMALL_E3M2_CANONICAL: return launch_src<SMALL_E3M2_CANONICAL>(a, stream);
         case SMALL_E3M2_PACKED: return launch_src<SMALL_E3M2_PACKED>(a, stream);

@@ -16,12 +16,20 @@ namespace svdq {
 
 struct TileGrid {
     int mtiles, ntiles, nmajor;
+    int mt0;                     // first token tile (a launch may cover a part of the tokens)
 };
 
-inline TileGrid make_tile_grid(int mtiles, int ntiles) {
+inline TileGrid make_tile_grid(int mtiles, int ntiles, int mt0 = 0) {
     const long long by_m = (long long)((mtiles + 7) / 8) * ntiles;       // blocks of the busiest XCD, token-major
     const long long by_n = (long long)((ntiles + 7) / 8) * mtiles;       // channel-major
-    return TileGrid{mtiles, ntiles, by_n * 10 <= by_m * 9 ? 1 : 0};
+    return TileGrid{mtiles, ntiles, by_n * 10 <= by_m * 9 ? 1 : 0, mt0};
+}
+
+// tiles of the busiest XCD: what a launch is waited for, in blocks per compute unit (CUS_PER_XCD of them)
+constexpr int CUS_PER_XCD = 32;
+inline int busiest_xcd(int mtiles, int ntiles) {
+    const TileGrid g = make_tile_grid(mtiles, ntiles);
+    return g.nmajor ? ((ntiles + 7) / 8) * mtiles : ((mtiles + 7) / 8) * ntiles;
 }
 
 // number of block ids (some of them name no tile: tile_of returns false)
@@ -38,7 +46,7 @@ __device__ __forceinline__ bool tile_of(const TileGrid& g, int id, int& mt, int&
     if (g.nmajor) {
         const int q = idx / g.mtiles;
         nt = q * 8 + xcd;
-        mt = idx - q * g.mtiles;
+        mt = g.mt0 + idx - q * g.mtiles;
         return nt < g.ntiles;
     }
     const int own = (g.mtiles - xcd + 7) >> 3;                           // token tiles of this XCD
@@ -46,7 +54,7 @@ __device__ __forceinline__ bool tile_of(const TileGrid& g, int id, int& mt, int&
     const int width = (own - 8 * sm < 8) ? own - 8 * sm : 8;             // token tiles of this group of eight
     if (width <= 0 || rem >= width * g.ntiles) return false;
     nt = rem / width;
-    mt = (sm * 8 + rem - nt * width) * 8 + xcd;
+    mt = g.mt0 + (sm * 8 + rem - nt * width) * 8 + xcd;
     return true;
 }
 

@@ -20,7 +20,9 @@ def svdq():
     import paper_2605_27003_amd as m
     m.load_library(build_if_missing=False)
     assert torch.cuda.is_available()
-    return m
+    yield m
+    from paper_2605_27003_amd import binding
+    binding._staging.clear()                      # other tests look at the size of the shared staging buffer
 
 
 SHAPES = [  # M, K, N, r, gelu
@@ -50,13 +52,15 @@ def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
     if mx:
         gq, gs = svdq.mx_to_token_major(qx, sx, K)
         assert np.array_equal(gs.cpu().numpy(), os_)
-    elif container == "nibble":
+    elif container == "nibble" and (M, N) != (15361, 128):                # that many tokens run as E3M2 fields
         gq, gs = svdq.to_token_major(qx, sx)
         assert np.array_equal(gs.cpu().numpy().view(np.uint32), os_.view(np.uint32))
     else:
-        codes, _ = unpack_act_e3m2_np(qx.buf.cpu().numpy(), M, K)
+        buf = lin._codes if container == "nibble" else qx.buf
+        codes, _ = unpack_act_e3m2_np(buf.cpu().numpy(), M, K)
         assert np.array_equal(codes, synth.unpack_int4(oq))
-    if mx or container == "nibble":
+        gq = None
+    if gq is not None:
         assert np.array_equal(gq.cpu().numpy(), oq)
     oh = oracle.lowrank_down(xa, L.inv_lambda, L.L1) if r else None
     orc = (oracle.linear_mxfp4 if mx else oracle.linear)(oq, os_, L.qw, L.sw, oh, L.L2 if r else None, L.bias)
