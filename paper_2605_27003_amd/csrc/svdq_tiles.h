@@ -53,7 +53,8 @@ __device__ __forceinline__ bool tile_of(const TileGrid& g, int id, int& mt, int&
     const int sm = idx / (8 * g.ntiles), rem = idx - sm * (8 * g.ntiles);
     const int width = (own - 8 * sm < 8) ? own - 8 * sm : 8;             // token tiles of this group of eight
     if (width <= 0 || rem >= width * g.ntiles) return false;
-    nt = rem / width;
+    if (width == 8) nt = rem >> 3;                                       // a division is 1 % of a kernel that walks tiles
+    else nt = rem / width;
     mt = g.mt0 + (sm * 8 + rem - nt * width) * 8 + xcd;
     return true;
 }
