@@ -1,4 +1,5 @@
 """ctypes binding of include/svdq.h for torch tensors (device memory and streams only)."""
+import array
 import collections
 import ctypes
 import os
@@ -85,8 +86,14 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# hipStream_t of the current stream of the current device.  torch.cuda.current_stream() builds a Stream object for it:
+# 2.8 us against 0.1 us, of the 12 us that the host needs for a layer with few tokens.
+def _raw_stream():
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream())
 
 
 def _check(rc, where):
@@ -99,8 +106,8 @@ def version():
 
 
 def alpha_lookup(table, step, step0, nsteps_expert):
-    arr = (ctypes.c_float * len(table))(*table)
-    return float(load_library().svdq_alpha_lookup(ctypes.cast(arr, _vp), len(table), step, step0, nsteps_expert))
+    arr = array.array("f", [*table])
+    return (_lib or load_library()).svdq_alpha_lookup(arr.buffer_info()[0], len(arr), step, step0, nsteps_expert)
 
 
 def packed_l1_bytes(K):
@@ -599,5 +606,5 @@ class W4A4Linear:
         y = self.buffers(M, device)[3]
         _check((_lib or load_library()).svdq_layer_forward(
             self._ref, x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, rho, gelu, M, *self._ptrs, self._staging(device),
-            y.data_ptr(), self.N, torch.cuda.current_stream().cuda_stream), "svdq_layer_forward")
+            y.data_ptr(), self.N, _raw_stream()), "svdq_layer_forward")
         return y
