@@ -462,7 +462,7 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
         if (e != hipSuccess) return hip_status(e);
         wp = (const uint8_t*)staging;
     }
-    return hip_status(svdq::launch_linear_e3m2(codes, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, 0, stream));
+    return hip_status(svdq::launch_layer_e3m2(codes, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, stream));
 }
 
 static int layer_out_check(const svdq_layer* L, const void* codes, const void* scales, const void* h, const void* y, int64_t ldy) {

@@ -88,8 +88,13 @@ struct NextLayer {
     int r;
 };
 
-template <int MODE>
-__global__ __launch_bounds__(256, 2)
+// KS = 2: the block has two teams of four waves, each with a ring of its own, that take half of K each; the second
+// team's tile is added to the first's through LDS at the end.  For launches with a block per CU at most, where one
+// team would leave every SIMD a single wave that waits for its own operands: with the expansion of the weights,
+// M = 512 .. 640, N = 5120 (160, 200 tiles) 39.6 -> 34.7 us at K = 5120, 92 -> 76 and 96 -> 82 at K = 13824.  The halves
+// overlap by a group when the group count is odd; the second team multiplies that group by zero scales.
+template <int MODE, int KS>
+__global__ __launch_bounds__(256 * KS, 2)
 void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict__ w0, const uint8_t* __restrict__ w1,
                       const uint8_t* __restrict__ sfr,
                       const float* __restrict__ h, const uint16_t* __restrict__ L2, const float* __restrict__ bias,
@@ -97,16 +102,21 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
                       int tile0, const TileGrid tg, int64_t dm0, int dmt, int32_t* __restrict__ dacc,
                       const NextLayer nx) {
     constexpr bool DUMP = MODE == MODE_DUMP, NEXT = MODE >= MODE_NEXT, GELU = MODE == MODE_NEXT_GELU;
-    __shared__ __attribute__((aligned(16))) uint8_t ring[NSLOTS * STAGE_BYTES];   // slot of group g: g % 5
+    static_assert(KS == 1 || MODE == MODE_LAYER, "two teams: the layer only");
+    __shared__ __attribute__((aligned(16))) uint8_t rings[KS * NSLOTS * STAGE_BYTES];   // slot of group g: g % 5
 
     int mt, nt;                                 // XCD-aware tile order (svdq_tiles.h)
     if (!tile_of(tg, blockIdx.x, mt, nt)) return;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int team = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int tid = threadIdx.x & 255, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
     const int l32 = lane & 31, kh = lane >> 5;
-    const int ng = K >> 6;
+    const int ngk = K >> 6;                                     // groups, and those of this team: [first, first + ng)
+    const int ng = KS == 1 ? ngk : (ngk + 1) >> 1;
+    const int first = KS == 1 ? 0 : team * (ngk - ng);
+    uint8_t* const ring = rings + (KS == 1 ? 0 : team * (NSLOTS * STAGE_BYTES));
     const int64_t Mp = (M + 3) & ~(int64_t)3;
     const int64_t m0 = (int64_t)(tile0 + mt) * BM;
     const int n0 = nt * BN;
@@ -128,20 +138,24 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
         const int64_t row = m0 + (wave & 1) * 64 + lane;
         st[0] = Stream{act, gstride, (uint32_t)(((row < M) ? row : (M - 1)) * 32 + (wave >> 1) * 16),
                        OFF_A0 + (uint32_t)((wave >> 1) * BM + (wave & 1) * 64) * 16};
-        st[1] = Stream{w0 + (size_t)nbB * ng * 1024, 1024, (uint32_t)(wave * ng * 1024 + lane * 16), OFF_W0 + (uint32_t)wave * 1024};
+        st[1] = Stream{w0 + (size_t)nbB * ngk * 1024, 1024, (uint32_t)(wave * ngk * 1024 + lane * 16), OFF_W0 + (uint32_t)wave * 1024};
         const int64_t pr = (m0 + 2 * lane < Mp - 2) ? (m0 + 2 * lane) : (Mp - 2);
         if (wave < 2) {
             st[2] = Stream{act + (size_t)Mp * 32 + (size_t)wave * Mp * 8, gstride, (uint32_t)(pr * 8), OFF_A1 + (uint32_t)wave * 1024};
         } else {
-            st[2] = Stream{w1 + (size_t)(nbB + 2 * (wave - 2)) * ng * 512, 512, (uint32_t)(kh * ng * 512 + l32 * 16),
+            st[2] = Stream{w1 + (size_t)(nbB + 2 * (wave - 2)) * ngk * 512, 512, (uint32_t)(kh * ngk * 512 + l32 * 16),
                            OFF_W1 + (uint32_t)(wave - 2) * 1024};
         }
         if (DUMP) {
             st[3] = st[2];
         } else if ((wave & 1) == 0) {
-            st[3] = Stream{sfr + (size_t)nbB * ng * 256, 256, (uint32_t)((lane >> 4) * ng * 256 + (lane & 15) * 16), OFF_SFR};
+            st[3] = Stream{sfr + (size_t)nbB * ngk * 256, 256, (uint32_t)((lane >> 4) * ngk * 256 + (lane & 15) * 16), OFF_SFR};
         } else {
             st[3] = Stream{act + (size_t)Mp * 48, gstride, (uint32_t)(pr * 8), OFF_SXP};
+        }
+        if (KS > 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st[i].base += (size_t)first * st[i].stride;
         }
     }
     auto stage_issue = [&](const int g) {
@@ -198,7 +212,7 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
     // awaited and made visible.
     const int pre = ng < NSLOTS - 1 ? ng : NSLOTS - 1;
     for (int g = 0; g < pre; ++g) stage_issue(g);
-    if (!DUMP) add_lowrank_bias<2, 2>(y, h, L2, bias, m0 + wm * 64, n0 + wn * 64, M, N, r, lane);
+    if (!DUMP && team == 0) add_lowrank_bias<2, 2>(y, h, L2, bias, m0 + wm * 64, n0 + wn * 64, M, N, r, lane);
     wait_groups(pre - 1);
     __syncthreads();
 
@@ -244,6 +258,10 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
             }
     };
     fetch(op0, ring0);
+    if (KS > 1 && team == 1 && (ngk & 1)) {              // the group both teams have: nothing from this one
+#pragma unroll
+        for (int i = 0; i < 2; ++i) op0.sf[i] = uint2{0u, 0u};
+    }
 
     // exact integer sums of one tile and group: E3M2 x E3M2, block scales 2^0 (E8M0 127), C = 0
     auto pmma = [&](const Operands& o, const int ni, const int mi) -> float16v {
@@ -398,6 +416,31 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may still be writing this block's LDS when it ends
 
     if (DUMP) return;
+    if constexpr (KS > 1) {
+        // wave w of the second team -> wave w of the first, through the second team's ring (its last operand reads have
+        // returned: they fed the last matrix instructions)
+        float4* const part = reinterpret_cast<float4*>(rings + NSLOTS * STAGE_BYTES) + wave * (16 * 64) + lane;
+        static_assert(4 * 16 * 64 * 16 <= NSLOTS * (int)STAGE_BYTES, "four waves' tiles fit the ring");
+        __syncthreads();
+        if (team == 1) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const float16v& t = y[q >> 3][(q >> 2) & 1];
+                part[q * 64] = float4{t[4 * (q & 3)], t[4 * (q & 3) + 1], t[4 * (q & 3) + 2], t[4 * (q & 3) + 3]};
+            }
+        }
+        __syncthreads();
+        if (team == 1) return;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const float4 v = part[q * 64];
+            float16v& t = y[q >> 3][(q >> 2) & 1];
+            t[4 * (q & 3)] += v.x;
+            t[4 * (q & 3) + 1] += v.y;
+            t[4 * (q & 3) + 2] += v.z;
+            t[4 * (q & 3) + 3] += v.w;
+        }
+    }
 
     const int64_t mw = m0 + wm * 64;                           // first token of this wave's tile
     if constexpr (NEXT) {
@@ -499,7 +542,7 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
     if (out_f32) {
         store_tile_f32<2, 2>(y, reinterpret_cast<float*>(yout), ldy, mw, n0 + wn * 64, M, lane);
     } else {
-        __syncthreads();                                       // every wave is done with the operand ring
+        if (KS == 1) __syncthreads();                          // every wave is done with the operand ring (KS = 2: above)
         store_tile_bf16<2>([&](int ni, int mi, int i) { return y[ni][mi][i]; },
                            ring0 + wave * 64 * YROW, lane,
                            reinterpret_cast<uint16_t*>(yout) + mw * ldy + n0 + wn * 64, ldy, M - mw);
@@ -627,18 +670,33 @@ hipError_t launch_unpack_act_e3m2(const uint8_t* act, int64_t M, int K, uint8_t*
     return hipGetLastError();
 }
 
-hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
-                              const float* h, const void* L2, const float* bias,
-                              int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32,
+// two_teams: K in halves
+static hipError_t launch_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
+                              int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32, bool two_teams,
                               hipStream_t stream) {
-    const int mtiles = (int)((M + BM - 1) / BM), ntiles = N / BN;
     const uint8_t* base = (const uint8_t*)w_packed;
-    const TileGrid tg = make_tile_grid(mtiles, ntiles);
-    hipLaunchKernelGGL(gemm_e3m2_kernel<MODE_LAYER>, dim3((unsigned)tile_ids(tg)), dim3(256), 0, stream,
+    const TileGrid tg = make_tile_grid((int)((M + BM - 1) / BM), N / BN);
+    auto kern = two_teams ? gemm_e3m2_kernel<MODE_LAYER, 2> : gemm_e3m2_kernel<MODE_LAYER, 1>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)tile_ids(tg)), dim3(two_teams ? 512 : 256), 0, stream,
                        act, base, base + w0_bytes(N, K), base + w0_bytes(N, K) + w1_bytes(N, K),
                        h, (const uint16_t*)L2, bias, M, N, K, r, y, ldy, out_f32,
                        0, tg, (int64_t)0, 0, (int32_t*)nullptr, NextLayer{});
     return hipGetLastError();
+}
+
+hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
+                              const float* h, const void* L2, const float* bias,
+                              int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32,
+                              hipStream_t stream) {
+    return launch_e3m2(act, w_packed, h, L2, bias, M, N, K, r, y, ldy, out_f32, false, stream);
+}
+
+// The layer's GEMM: with a tile per CU at most, two teams on each.  Below K = 2048 the second ring's prologue and the
+// sum of the tiles cost what the shorter loop saves (K = 1536, N = 2048, M = 640: 15.4 and 15.5 us).
+hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
+                             int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream) {
+    const bool two_teams = K >= 2048 && busiest_xcd((int)((M + BM - 1) / BM), N / BN) <= CUS_PER_XCD;
+    return launch_e3m2(act, w_packed, h, L2, bias, M, N, K, r, y, ldy, 0, two_teams, stream);
 }
 
 hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,
@@ -653,7 +711,7 @@ hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,
         const int64_t n = M * next_r;
         hipLaunchKernelGGL(zero_f32_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, next_h, n);
     }
-    auto kern = gelu ? gemm_e3m2_kernel<MODE_NEXT_GELU> : gemm_e3m2_kernel<MODE_NEXT>;
+    auto kern = gelu ? gemm_e3m2_kernel<MODE_NEXT_GELU, 1> : gemm_e3m2_kernel<MODE_NEXT, 1>;
     const TileGrid tg = make_tile_grid(mtiles, ntiles);
     hipLaunchKernelGGL(kern, dim3((unsigned)tile_ids(tg)), dim3(256), 0, stream,
                        act, base, base + w0_bytes(N, K), base + w0_bytes(N, K) + w1_bytes(N, K),
@@ -669,7 +727,7 @@ hipError_t launch_group_acc_e3m2(const uint8_t* act, const void* w_packed, int64
     const int mtiles = t1 - t0, ntiles = N / BN;
     const uint8_t* base = (const uint8_t*)w_packed;
     const TileGrid tg = make_tile_grid(mtiles, ntiles);
-    hipLaunchKernelGGL(gemm_e3m2_kernel<MODE_DUMP>, dim3((unsigned)tile_ids(tg)), dim3(256), 0, stream,
+    hipLaunchKernelGGL((gemm_e3m2_kernel<MODE_DUMP, 1>), dim3((unsigned)tile_ids(tg)), dim3(256), 0, stream,
                        act, base, base + w0_bytes(N, K), (const uint8_t*)nullptr,
                        (const float*)nullptr, (const uint16_t*)nullptr, (const float*)nullptr,
                        M, N, K, 0, (void*)nullptr, (int64_t)0, 0,

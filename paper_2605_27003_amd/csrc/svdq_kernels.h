@@ -43,6 +43,8 @@ hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
                               const float* h, const void* L2, const float* bias,
                               int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32,
                               hipStream_t stream);
+hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
+                             int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
 hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,
                                    const float* h, const void* L2, const float* bias,
                                    int64_t M, int N, int K, int r, bool gelu,
