@@ -67,6 +67,8 @@ inline int small_shape(int64_t M, int N, bool mxfp4 = true) {
     if (b32 <= (mxfp4 ? 256 : 512)) return 1;
     return b64 <= 480 ? 2 : 0;
 }
+// The few-token GEMM addresses codes and weights with 32-bit byte offsets (its tokens may be the last of many).
+inline bool small_reach(int64_t M, int64_t N, int64_t K) { return (M > N ? M : N) * K < (int64_t)1 << 32; }
 // tokens [begin, M)
 hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1, const void* w2,
                              const float* h, int slices, const void* L2, const float* bias, int64_t M, int64_t begin, int N, int K, int r,

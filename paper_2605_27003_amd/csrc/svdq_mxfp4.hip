@@ -1098,7 +1098,7 @@ int64_t mx_main_rows(int64_t M, int N, int K) {
     return mx_split(M, N, K, [&](int64_t rest) {
         const double few = 5.0 + 0.025 * (double)((rest + 63) / 64) * (double)((N + 63) / 64);                   // the few-token kernel
         const double tiles = mx_best(rest, N, K).cost;
-        return small_shape(rest, N) && few < tiles ? few : tiles;
+        return small_shape(rest, N) && small_reach(M, N, K) && few < tiles ? few : tiles;
     });
 }
 

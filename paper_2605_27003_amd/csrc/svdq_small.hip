@@ -44,7 +44,7 @@ struct SmallArgs {
 
 // Loads are buffer loads: a descriptor and a wave-uniform offset in scalar registers plus a per-lane 32-bit offset that is
 // fixed for the kernel.  (With 64-bit addresses per lane, two registers for every load in flight, the compiler spills.)
-// All tensors of this path are far below 4 GB.
+// small_reach keeps every tensor of this path below 4 GB.
 struct Buffers {
     __amdgpu_buffer_rsrc_t codes, scales, w0, w1, w2;
 };

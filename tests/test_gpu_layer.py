@@ -76,3 +76,19 @@ def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
     y2 = lin.gemm(*lin.quantize(dev(x), rho, gelu))
     torch.cuda.synchronize()
     assert rel_fro(synth.bf16_bits_to_f32(host_bits(y2)).astype(np.float64), synth.bf16_bits_to_f32(host_bits(y1)).astype(np.float64)) <= 2e-3
+
+
+def test_layer_gemm_last_tokens_beyond_4_gb(svdq):
+    """MXFP4, 4 GB of codes: the last tokens have a launch of their own on the few-token kernel where its 32-bit offsets
+    reach them, and must not have one here.  Against the tile kernels alone (sums in another order: one bf16 step)."""
+    M, K, N = 524389, 16384, 128
+    g = torch.Generator(device="cuda").manual_seed(1)
+    qw = torch.randint(0, 256, (N, K // 2), generator=g, device="cuda", dtype=torch.uint8)
+    sw = torch.randint(118, 123, (K // 32, N), generator=g, device="cuda", dtype=torch.uint8)
+    lin = svdq.W4A4Linear(torch.ones(K, device="cuda"), None, None, qw, sw, None, container="mxfp4")
+    qx, sx = lin.buffers(M, qw.device)[:2]
+    qx.random_(0, 256, generator=g)
+    sx.random_(118, 123, generator=g)
+    y = lin.gemm(qx, sx, None)[-200:].float()
+    want = svdq.linear_mxfp4(qx, sx, lin.w_packed, N)[-200:].float()
+    assert torch.all((y - want).abs() <= want.abs() * 2.0 ** -7 + 1e-3 * want.std())
