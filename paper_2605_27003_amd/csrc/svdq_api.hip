@@ -377,7 +377,7 @@ static int layer_check(const svdq_layer* L, int64_t M) {
     const bool canonical = !L->w_packed;
     if (canonical && (L->format != SVDQ_FMT_INT4_E3M2 || !L->qw || !L->sw)) return SVDQ_ERR_INVALID_ARG;
     if (L->r == 0 ? (L->l1_packed || L->L2_bf16) : (!L->l1_packed || !L->L2_bf16)) return SVDQ_ERR_INVALID_ARG;
-    if (L->N <= 0 || L->K <= 0 || L->K % SVDQ_GROUP || L->N % SVDQ_N_TILE || L->K > SVDQ_MAX_K) return SVDQ_ERR_UNSUPPORTED_SHAPE;
+    if (L->N <= 0 || L->K <= 0 || L->K % SVDQ_GROUP || L->N % SVDQ_N_TILE) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     if (L->r != 0 && !rank_ok(L->r)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     if (!aligned16(L->inv_lambda) || !aligned16(L->l1_packed) || !aligned16(L->L2_bf16) || !aligned16(L->bias) ||
         !aligned16(L->w_packed) || !aligned16(L->qw) || !aligned16(L->sw))
@@ -489,7 +489,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (int e = layer_check(L, M)) return e;
     if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
     if (!x_bf16 || !(rho > 0.0f) || !(rho <= 1.0f)) return SVDQ_ERR_INVALID_ARG;
-    if (ldx < L->K || ldx % 8 || !aligned16(x_bf16) || !aligned16(scratch)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
+    if (L->K > SVDQ_MAX_K || ldx < L->K || ldx % 8 || !aligned16(x_bf16) || !aligned16(scratch)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     const bool fields = as_fields(L, M);
     if ((fields || (!L->w_packed && !small_path(L, M))) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;

@@ -92,3 +92,26 @@ def test_layer_gemm_last_tokens_beyond_4_gb(svdq):
     y = lin.gemm(qx, sx, None)[-200:].float()
     want = svdq.linear_mxfp4(qx, sx, lin.w_packed, N)[-200:].float()
     assert torch.all((y - want).abs() <= want.abs() * 2.0 ** -7 + 1e-3 * want.std())
+
+
+@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble", "mxfp4"])
+@pytest.mark.parametrize("M", [40, 15400])
+def test_layer_gemm_beyond_quantise_limit(svdq, oracle, container, M):
+    """The quantise pass ends at K = 16384; the GEMM takes more (the layer before may emit its operands)."""
+    Kh, N = 8320, 128
+    mx = container == "mxfp4"
+    x, _ = synth.make_x(3, M, Kh, outlier_count=3, outlier_scale=30.0)
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(x)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(5, Kh, N, 0, cm, fmt="mxfp4" if mx else "int4")
+    make = lambda qw, sw: svdq.W4A4Linear(dev(L.inv_lambda), None, None, qw, sw, dev(L.bias), container=container.split()[0],
+                                          resident="packed" if "packed" in container else "w4")
+    qw, sw = dev(L.qw), dev(L.sw)
+    half, both = make(qw, sw), make(torch.cat([qw, qw], 1).contiguous(), torch.cat([sw, sw]).contiguous())
+    qx, sx, _ = half.quantize(dev(x), 0.8)
+    twice = lambda t: torch.cat([t, t]).contiguous()
+    acts = (svdq.ActE3M2(twice(qx.buf), M, 2 * Kh), None) if "e3m2" in container else (twice(qx), twice(sx))
+    y = both.gemm(*acts, None).float()
+    once = half.gemm(qx, sx, None).float()
+    want = 2.0 * once - half.bias                       # K taken twice: twice the sum, one bias
+    tol = once.abs() * 2.0 ** -7 + want.abs() * 2.0 ** -7 + 1e-3 * want.std()      # a bf16 step of each output
+    assert torch.all((y - want).abs() <= tol)
