@@ -527,9 +527,9 @@ class W4A4Linear:
     container "e3m2" (default) runs the int4 layer on the FP6 matrix cores, "nibble" the same layer from 4-bit packed
     weights (quantize() and gemm() on 4-bit activations and the int8 matrix cores; forward() on the FP6 ones, with the
     same codes and scales), "mxfp4" the MXFP4 format (qw then holds E2M1 codes and sw [K/32, N] E8M0 bytes).
-    resident "w4" (default, container "e3m2" only) keeps the canonical 4-bit weights (qw, sw); these, and the nibble
-    container's, are expanded into a staging buffer shared by all such layers of the device right before a GEMM of many
-    tokens (calls on one stream only);
+    resident "w4" (default, container "e3m2" only) keeps the canonical 4-bit weights (qw, sw) and expands them into a
+    staging buffer shared by all such layers of the device right before a GEMM of many tokens (calls on one stream only);
+    the nibble container's are expanded into a buffer of the layer's own;
     "packed" keeps the container's own packed form (7 - 8 bits per weight for the int4 containers)."""
 
     def __init__(self, inv_lambda, L1_bf16, L2_bf16, qw, sw, bias, container="e3m2", resident="w4"):
@@ -547,10 +547,19 @@ class W4A4Linear:
         else:
             self.w_packed = {"e3m2": pack_weight_e3m2, "nibble": pack_weight, "mxfp4": pack_weight_mxfp4}[container](qw, sw)
         self.bias = bias
-        self._bufs = None
-        self._layer = _Layer(self.format, self.N, self.K, self.r, *map(_addr, (
-            self.inv_lambda, self.l1_packed, self.L2, self.bias, self.w_packed, self.qw, self.sw)))
-        self._ref = ctypes.addressof(self._layer)
+        self._bufs = self._layer = self._fields = None
+
+    def _descriptor(self, r):
+        """Address of the svdq_layer of the tensors that the layer holds now (they may have been replaced), with rank r."""
+        fields = (self.format, self.N, self.K, r, _addr(self.inv_lambda), _addr(self.l1_packed), _addr(self.L2), _addr(self.bias),
+                  _addr(self.w_packed), _addr(self.qw), _addr(self.sw))
+        if fields != self._fields:
+            self._layer, self._fields = _Layer(*fields), fields
+        return ctypes.addressof(self._layer)
+
+    def __getstate__(self):
+        """Copies make buffers and a descriptor of their own."""
+        return {**self.__dict__, "_bufs": None, "_work": None, "_layer": None, "_fields": None}
 
     def weights(self):
         """The packed weights the GEMM takes: resident, or expanded now from the resident 4-bit form."""
@@ -560,28 +569,34 @@ class W4A4Linear:
 
     def buffers(self, M, device):
         if self._bufs is None or self._bufs[3].shape[0] != M:
-            lib = load_library()
-            codes = torch.empty(lib.svdq_layer_codes_bytes(self._ref, M), dtype=torch.uint8, device=device)
-            self._codes = codes
+            lib, ref, K = load_library(), self._descriptor(self.r), self.K
+            own = act_e3m2_bytes(M, K) if self.container == "e3m2" else M * K // 2
+            codes = torch.empty(max(own, lib.svdq_layer_codes_bytes(ref, M)), dtype=torch.uint8, device=device)
             if self.container == "e3m2":
-                qx, sx = ActE3M2(codes, M, self.K), None
+                qx, sx = ActE3M2(codes, M, K), None
             else:
-                qx = codes[: M * self.K // 2].view(self.K // 64, M, 32)
-                sx = (torch.empty((self.K // 64, M), dtype=torch.float32, device=device) if self.container == "nibble"
-                      else torch.empty(((self.K // 64 + 1) // 2, M, 2, 2), dtype=torch.uint8, device=device))
+                qx = codes[:own].view(K // 64, M, 32)
+                sx = (torch.empty((K // 64, M), dtype=torch.float32, device=device) if self.container == "nibble"
+                      else torch.empty(((K // 64 + 1) // 2, M, 2, 2), dtype=torch.uint8, device=device))
             h = torch.empty((M, self.r), dtype=torch.float32, device=device) if self.r else None
             y = torch.empty((M, self.N), dtype=torch.bfloat16, device=device)
-            n = lib.svdq_layer_scratch_bytes(self._ref, M)
-            self._scratch = torch.empty(n, dtype=torch.uint8, device=device) if n else None
-            self._staging_bytes = lib.svdq_layer_staging_bytes(self._ref, M)
-            if self.container == "e3m2" and self.w_packed is None:      # reserved with the first buffers, though small M expands nothing
-                _staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), device)
-            self._ptrs = tuple(map(_addr, (codes, sx, h, self._scratch)))
+            n = lib.svdq_layer_scratch_bytes(ref, M)
+            scratch = torch.empty(n, dtype=torch.uint8, device=device) if n else None
+            # Room for expanded weights: the canonical form's is shared between layers (and reserved here, though few tokens
+            # expand nothing).  The nibble container's is the layer's own: its layers may run on several streams at once.
+            n, staging, shared = lib.svdq_layer_staging_bytes(ref, M), None, False
+            if self.container == "e3m2" and self.w_packed is None:
+                _staging_buffer(packed_weight_e3m2_bytes(self.N, K), device)
+                shared = n > 0
+            elif n:
+                staging = torch.empty(n, dtype=torch.uint8, device=device)
+            self._work = (codes, sx, h, scratch, staging, shared)
             self._bufs = (qx, sx, h, y)
         return self._bufs
 
     def _staging(self, device):
-        return _staging_buffer(self._staging_bytes, device).data_ptr() if self._staging_bytes else None
+        staging, shared = self._work[4:]
+        return _staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), device).data_ptr() if shared else _addr(staging)
 
     def quantize(self, x_bf16, rho, gelu=False):
         """Kernel (a) into the layer's buffers; gelu=True applies the feed-forward block's activation on the fly."""
@@ -595,8 +610,9 @@ class W4A4Linear:
         codes = qx.buf if self.container == "e3m2" else qx
         M, device = (qx.M if self.container == "e3m2" else qx.shape[1]), codes.device
         y = self.buffers(M, device)[3]
-        _check(load_library().svdq_layer_gemm(self._ref, codes.data_ptr(), _addr(sx), _addr(h), M, self._staging(device),
-                                              y.data_ptr(), self.N, _stream()), "svdq_layer_gemm")
+        _check(load_library().svdq_layer_gemm(
+            self._descriptor(0 if h is None else h.shape[1]), codes.data_ptr(), _addr(sx), _addr(h), M, self._staging(device),
+            y.data_ptr(), self.N, _stream()), "svdq_layer_gemm")
         return y
 
     def forward(self, x_bf16, rho, gelu=False):
@@ -605,6 +621,7 @@ class W4A4Linear:
         device = x_bf16.device
         y = self.buffers(M, device)[3]
         _check((_lib or load_library()).svdq_layer_forward(
-            self._ref, x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, rho, gelu, M, *self._ptrs, self._staging(device),
+            self._descriptor(self.r), x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, float(rho), 1 if gelu else 0, M,
+            *map(_addr, self._work[:4]), self._staging(device),
             y.data_ptr(), self.N, _raw_stream()), "svdq_layer_forward")
         return y

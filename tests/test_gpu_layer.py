@@ -58,7 +58,7 @@ def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
         gq, gs = svdq.to_token_major(qx, sx)
         assert np.array_equal(gs.cpu().numpy().view(np.uint32), os_.view(np.uint32))
     else:
-        buf = lin._codes if container == "nibble" else qx.buf
+        buf = lin._work[0] if container == "nibble" else qx.buf
         codes, _ = unpack_act_e3m2_np(buf.cpu().numpy(), M, K)
         assert np.array_equal(codes, synth.unpack_int4(oq))
         gq = None
@@ -115,3 +115,19 @@ def test_layer_gemm_beyond_quantise_limit(svdq, oracle, container, M):
     want = 2.0 * once - half.bias                       # K taken twice: twice the sum, one bias
     tol = once.abs() * 2.0 ** -7 + want.abs() * 2.0 ** -7 + 1e-3 * want.std()      # a bf16 step of each output
     assert torch.all((y - want).abs() <= tol)
+
+
+def test_layer_follows_its_tensors_and_copies(svdq):
+    """Tensors replaced after construction are the ones used, and a copy has buffers of its own."""
+    import copy
+    x, _ = synth.make_x(3, 40, 512, outlier_count=3, outlier_scale=30.0)
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(x)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(5, 512, 128, 16, cm)
+    lin = svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1), dev(L.L2), dev(L.qw), dev(L.sw), dev(L.bias))
+    y = lin.forward(dev(x), np.float32(0.8)).clone()
+    other = copy.deepcopy(lin)
+    other.bias = other.bias + 64.0
+    y2 = other.forward(dev(x), 0.8)
+    assert y2.data_ptr() != lin.buffers(40, y.device)[3].data_ptr()
+    assert torch.all((y2.float() - 64.0 - y.float()).abs() <= 0.5 + y.float().abs() * 2.0 ** -7)
+    assert torch.equal(lin.forward(dev(x), 0.8), y)
