@@ -551,8 +551,10 @@ class W4A4Linear:
 
     def _descriptor(self, r):
         """Address of the svdq_layer of the tensors that the layer holds now (they may have been replaced), with rank r."""
-        fields = (self.format, self.N, self.K, r, _addr(self.inv_lambda), _addr(self.l1_packed), _addr(self.L2), _addr(self.bias),
-                  _addr(self.w_packed), _addr(self.qw), _addr(self.sw))
+        l1, L2, bias, wp, qw, sw = self.l1_packed, self.L2, self.bias, self.w_packed, self.qw, self.sw
+        fields = (self.format, self.N, self.K, r, self.inv_lambda.data_ptr(),
+                  None if l1 is None else l1.data_ptr(), None if L2 is None else L2.data_ptr(), None if bias is None else bias.data_ptr(),
+                  None if wp is None else wp.data_ptr(), None if qw is None else qw.data_ptr(), None if sw is None else sw.data_ptr())
         if fields != self._fields:
             self._layer, self._fields = _Layer(*fields), fields
         return ctypes.addressof(self._layer)
@@ -591,6 +593,7 @@ class W4A4Linear:
             elif n:
                 staging = torch.empty(n, dtype=torch.uint8, device=device)
             self._work = (codes, sx, h, scratch, staging, shared)
+            self._work_ptrs = tuple(map(_addr, self._work[:4]))          # of the buffers made here
             self._bufs = (qx, sx, h, y)
         return self._bufs
 
@@ -622,6 +625,6 @@ class W4A4Linear:
         y = self.buffers(M, device)[3]
         _check((_lib or load_library()).svdq_layer_forward(
             self._descriptor(self.r), x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, float(rho), 1 if gelu else 0, M,
-            *map(_addr, self._work[:4]), self._staging(device),
+            *self._work_ptrs, self._staging(device),
             y.data_ptr(), self.N, _raw_stream()), "svdq_layer_forward")
         return y

@@ -209,7 +209,7 @@ int svdq_pack_weight_e3m2(const uint8_t* qw, const float* sw, int N, int K, void
     if (N <= 0 || K <= 0 || K % SVDQ_GROUP || N % SVDQ_N_TILE) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     if (!aligned16(qw) || !aligned16(sw) || !aligned16(w_packed)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     if (int a = check_arch()) return a;
-    return hip_status(svdq::launch_pack_weight_e3m2(qw, sw, N, K, w_packed, (hipStream_t)stream));
+    return hip_status(svdq::launch_expand(svdq::expand_canonical_job(qw, sw, N, w_packed), K, (hipStream_t)stream));
 }
 
 int svdq_linear_w4a4_e3m2(const uint8_t* act, const void* w_packed,
@@ -422,9 +422,13 @@ size_t svdq_layer_staging_bytes(const svdq_layer* L, int64_t M) {
     return svdq::packed_weight_e3m2_bytes(L->N, L->K);
 }
 
+static svdq::ExpandJob layer_expand_job(const svdq_layer* L, void* staging) {
+    return L->w_packed ? svdq::expand_packed_job(L->w_packed, L->N, L->K, staging) : svdq::expand_canonical_job(L->qw, L->sw, L->N, staging);
+}
+
 // The GEMM on checked arguments.  h: `slices` partial h's for the few-token kernel, one otherwise.  fields: codes are
-// E3M2 fields whatever the format.
-static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool fields, const float* h, int slices, int64_t M,
+// E3M2 fields whatever the format.  expanded: staging holds the layer's weights already.
+static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool fields, bool expanded, const float* h, int slices, int64_t M,
                       void* staging, void* y, int64_t ldy, hipStream_t stream) {
     const int N = L->N, K = L->K, r = L->r;
     const uint8_t* wp = (const uint8_t*)L->w_packed;
@@ -459,9 +463,10 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
     if (L->format == SVDQ_FMT_INT4 && !fields)
         return hip_status(svdq::launch_linear(codes, (const float*)scales, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, 0, stream));
     if (!wp || L->format == SVDQ_FMT_INT4) {
-        const hipError_t e = wp ? svdq::launch_repack_weight_e3m2(wp, N, K, staging, stream)
-                                : svdq::launch_pack_weight_e3m2(L->qw, (const float*)L->sw, N, K, staging, stream);
-        if (e != hipSuccess) return hip_status(e);
+        if (!expanded) {
+            const hipError_t e = svdq::launch_expand(layer_expand_job(L, staging), K, stream);
+            if (e != hipSuccess) return hip_status(e);
+        }
         wp = (const uint8_t*)staging;
     }
     return hip_status(svdq::launch_layer_e3m2(codes, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, stream));
@@ -480,7 +485,7 @@ int svdq_layer_gemm(const svdq_layer* L, const void* codes, const void* scales, 
     if (!L->w_packed && !small_path(L, M) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
-    return layer_gemm(L, (const uint8_t*)codes, scales, false, h, 1, M, staging, y, ldy, (hipStream_t)stream);
+    return layer_gemm(L, (const uint8_t*)codes, scales, false, false, h, 1, M, staging, y, ldy, (hipStream_t)stream);
 }
 
 int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, float rho, int gelu, int64_t M,
@@ -491,7 +496,8 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (!x_bf16 || !(rho > 0.0f) || !(rho <= 1.0f)) return SVDQ_ERR_INVALID_ARG;
     if (L->K > SVDQ_MAX_K || ldx < L->K || ldx % 8 || !aligned16(x_bf16) || !aligned16(scratch)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     const bool fields = as_fields(L, M);
-    if ((fields || (!L->w_packed && !small_path(L, M))) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
+    const bool expand = fields || (!L->w_packed && !small_path(L, M));       // the GEMM needs the weights in staging
+    if (expand && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
     hipStream_t stream = (hipStream_t)stream_;
@@ -505,7 +511,8 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     else if (L->format == SVDQ_FMT_MXFP4)
         e = svdq::launch_quantize_mx(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, (uint8_t*)scales, ho, gelu != 0, stream, slices);
     else
-        e = svdq::launch_quantize_e3m2(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, nullptr, ho, gelu != 0, stream, slices);
+        e = svdq::launch_quantize_e3m2(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, nullptr, ho, gelu != 0, stream, slices,
+                                       expand ? layer_expand_job(L, staging) : svdq::ExpandJob{});
     if (e != hipSuccess) return hip_status(e);
     const float* hin = ho;
     if (r != 0 && slices > 1 && !small_path(L, M)) {
@@ -514,7 +521,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
         hin = h;
         slices = 1;
     }
-    return layer_gemm(L, (const uint8_t*)codes, scales, fields, r ? hin : nullptr, r ? slices : 1, M, staging, y, ldy, stream);
+    return layer_gemm(L, (const uint8_t*)codes, scales, fields, expand, r ? hin : nullptr, r ? slices : 1, M, staging, y, ldy, stream);
 }
 
 size_t svdq_gptq_workspace_bytes(int N, int K) {

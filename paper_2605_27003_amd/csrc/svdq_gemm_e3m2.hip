@@ -21,6 +21,7 @@
 #include "svdq_act.h"
 #include "svdq_dev.h"
 #include "svdq_epilogue.h"
+#include "svdq_expand_dev.h"
 #include "svdq_kernels.h"
 #include "svdq_lds.h"
 #include "svdq_quant_dev.h"
@@ -549,69 +550,10 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
     }
 }
 
-// Offline packing from the canonical form (qw [N][K/2] nibbles, sw [K/64][N] binary32).
-// Region 1: bytes 0..15 of the weight fragments, [N/32][K/64][64 lanes][16 B]; region 2: bytes 16..23,
-// [N/32][K/64][64 lanes][8 B]: lane (n = lane % 32, kh = lane / 32) holds the E3M2 fields of k = 64 g + 32 kh + 0..31
-// of channel n, k ascending from bit 0.  Region 3: n-side operands of the scale-product MFMA,
-// [N/32][K/64][32 channels][8 B]: bf16 {w1, w1, w2, w2} with w1 + w2 ~ sw[g][n] (the lanes of k half 0 read the
-// entry; those of k half 1 read zeros).
-// Runs before every GEMM whose weights stay resident in the canonical form, so it has to keep up with HBM: a lane turns
-// 32 nibbles into 32 fields with the hardware conversions (e3m2_of_nibbles; bit arithmetic per field was 480 vector
-// instructions and bound the kernel: 18.7 us for 5120 x 5120, 36 MB).  A wave takes four neighbouring groups of 32 channels: 128 bytes
-// of every channel's row, all requested before the first conversion.
-constexpr int PACK_GROUPS = 4;
+// 4-bit weights -> operand form (svdq_expand_dev.h): a wave per four groups of 32 channels
 __global__ __launch_bounds__(256)
-void pack_weight_e3m2_kernel(const uint8_t* __restrict__ qw, const float* __restrict__ sw,
-                             int N, int K, uint8_t* __restrict__ out) {
-    const int ng = K >> 6;
-    const int lane = threadIdx.x & 63, l32 = lane & 31, kh = lane >> 5;
-    const int gq = (ng + PACK_GROUPS - 1) / PACK_GROUPS;
-    const int id = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int nb = id / gq, g0 = (id - nb * gq) * PACK_GROUPS;
-    if (nb >= (N >> 5)) return;
-    const int n = nb * 32 + l32;
-    uint4* o1 = reinterpret_cast<uint4*>(out);
-    uint2* o2 = reinterpret_cast<uint2*>(out + w0_bytes(N, K));
-    uint2* o3 = reinterpret_cast<uint2*>(out + w0_bytes(N, K) + w1_bytes(N, K));
-    uint4 nib[PACK_GROUPS];
-    float sc[2];
-#pragma unroll
-    for (int i = 0; i < PACK_GROUPS; ++i) {
-        const int g = min(g0 + i, ng - 1);
-        nib[i] = *reinterpret_cast<const uint4*>(qw + (size_t)n * (K >> 1) + g * 32 + kh * 16);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)                       // scale pieces: half the lanes take even, half odd groups
-        sc[i] = sw[(size_t)min(g0 + 2 * i + kh, ng - 1) * N + n];
-#pragma unroll
-    for (int i = 0; i < PACK_GROUPS; ++i) {
-        if (g0 + i >= ng) break;
-        const LaneCodes<true> c = e3m2_of_nibbles(nib[i]);
-        const size_t v = ((size_t)nb * ng + g0 + i) * 64 + lane;
-        o1[v] = c.lo;
-        o2[v] = c.hi;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int g = g0 + 2 * i + kh;
-        if (g >= ng) break;
-        const uint32_t p = split_bf16(sc[i]);
-        const uint32_t w1 = p & 0xffffu, w2 = p >> 16;
-        o3[((size_t)nb * ng + g) * 32 + l32] = uint2{w1 | (w1 << 16), w2 | (w2 << 16)};
-    }
-}
-
-// The same from the nibble kernel's packed weights (svdq_gemm.hip): its code fragments hold the same bytes per lane and
-// its scale operands the same pieces, eight bytes in the lanes of k half 0.
-__global__ __launch_bounds__(256)
-void repack_weight_e3m2_kernel(const uint4* __restrict__ frag, const uint2* __restrict__ sfrag, int N, int K, uint8_t* __restrict__ out) {
-    const int ng = K >> 6;
-    const size_t v = (size_t)blockIdx.x * 256 + threadIdx.x, lane = v & 63, fr = v >> 6;
-    if (fr >= (size_t)(N >> 5) * ng) return;
-    const LaneCodes<true> c = e3m2_of_nibbles(frag[v]);
-    reinterpret_cast<uint4*>(out)[v] = c.lo;
-    reinterpret_cast<uint2*>(out + w0_bytes(N, K))[v] = c.hi;
-    if (lane < 32) reinterpret_cast<uint2*>(out + w0_bytes(N, K) + w1_bytes(N, K))[fr * 32 + lane] = sfrag[v];
+void expand_kernel(const ExpandJob e, int K) {
+    expand_weights(e, (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), threadIdx.x & 63, K);
 }
 
 // Activation operand buffer -> nibble codes qx [K/64][M][32 B] (the layout of the int4 path)
@@ -651,17 +593,14 @@ __global__ void zero_f32_kernel(float* __restrict__ p, int64_t n) {
 
 size_t packed_weight_e3m2_bytes(int N, int K) { return w0_bytes(N, K) + w1_bytes(N, K) + sf_bytes(N, K); }
 
-hipError_t launch_pack_weight_e3m2(const uint8_t* qw, const float* sw, int N, int K, void* out, hipStream_t stream) {
-    const size_t waves = (size_t)(N / 32) * ((K / 64 + PACK_GROUPS - 1) / PACK_GROUPS);
-    hipLaunchKernelGGL(pack_weight_e3m2_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream, qw, sw, N, K, (uint8_t*)out);
-    return hipGetLastError();
+ExpandJob expand_canonical_job(const void* qw, const void* sw, int N, void* out) {
+    return ExpandJob{qw, sw, (uint8_t*)out, N, true};
 }
-
-hipError_t launch_repack_weight_e3m2(const void* w_packed_nibble, int N, int K, void* out, hipStream_t stream) {
-    const size_t lanes = (size_t)(N / 32) * (K / 64) * 64;
-    const uint8_t* base = (const uint8_t*)w_packed_nibble;
-    hipLaunchKernelGGL(repack_weight_e3m2_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, stream,
-                       (const uint4*)base, (const uint2*)(base + packed_weight_codes_bytes(N, K)), N, K, (uint8_t*)out);
+ExpandJob expand_packed_job(const void* w_packed_nibble, int N, int K, void* out) {
+    return ExpandJob{w_packed_nibble, (const uint8_t*)w_packed_nibble + packed_weight_codes_bytes(N, K), (uint8_t*)out, N, false};
+}
+hipError_t launch_expand(const ExpandJob& e, int K, hipStream_t stream) {
+    hipLaunchKernelGGL(expand_kernel, dim3((unsigned)((expand_waves(e.N, K) + 3) / 4)), dim3(256), 0, stream, e, K);
     return hipGetLastError();
 }
 

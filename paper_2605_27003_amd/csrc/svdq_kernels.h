@@ -31,14 +31,24 @@ hipError_t launch_group_acc(const uint8_t* qx, const void* w_packed, int64_t M, 
 // buffer holds, per 64-group, Mp = round_up(M, 4) rows of 56 bytes in three planes (see quantize_kernel).
 constexpr int E3M2_ROW_BYTES = 56;
 inline size_t act_e3m2_bytes(int64_t M, int K) { return (size_t)(K / 64) * (size_t)((M + 3) & ~(int64_t)3) * E3M2_ROW_BYTES; }
+// 4-bit weights to be expanded into `out` (packed_weight_e3m2_bytes): canonical qw, sw or the nibble kernel's packed form
+struct ExpandJob {
+    const void *codes, *scales;
+    uint8_t* out;
+    int N;
+    bool canonical;
+};
+ExpandJob expand_canonical_job(const void* qw, const void* sw, int N, void* out);
+ExpandJob expand_packed_job(const void* w_packed_nibble, int N, int K, void* out);
+hipError_t launch_expand(const ExpandJob& e, int K, hipStream_t stream);
+// expand: weights [N, K] that blocks of the same launch expand beside the pass (out null: none)
 hipError_t launch_quantize_e3m2(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                 const void* l1p, int64_t M, int K, int r,
-                                uint8_t* act, float* sx, float* h, bool gelu, hipStream_t stream, int slices = 1);
+                                uint8_t* act, float* sx, float* h, bool gelu, hipStream_t stream, int slices = 1,
+                                const ExpandJob& expand = ExpandJob{});
 size_t packed_weight_e3m2_bytes(int N, int K);
-inline size_t packed_e3m2_w0_bytes(int N, int K) { return (size_t)N * (K / 64) * 32; }     // planes of the packed weights
-inline size_t packed_e3m2_w1_bytes(int N, int K) { return (size_t)N * (K / 64) * 16; }
-hipError_t launch_pack_weight_e3m2(const uint8_t* qw, const float* sw, int N, int K, void* out, hipStream_t stream);
-hipError_t launch_repack_weight_e3m2(const void* w_packed_nibble, int N, int K, void* out, hipStream_t stream);
+__host__ __device__ inline size_t packed_e3m2_w0_bytes(int N, int K) { return (size_t)N * (K / 64) * 32; }     // planes of the packed weights
+__host__ __device__ inline size_t packed_e3m2_w1_bytes(int N, int K) { return (size_t)N * (K / 64) * 16; }
 hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
                               const float* h, const void* L2, const float* bias,
                               int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32,

@@ -19,6 +19,7 @@
 // binary32 on the vector ALU.
 #include "svdq_act.h"
 #include "svdq_dev.h"
+#include "svdq_expand_dev.h"
 #include "svdq_kernels.h"
 #include "svdq_lds.h"
 #include "svdq_quant_dev.h"
@@ -45,7 +46,15 @@ __global__ __launch_bounds__(64 * WV, WV == 4 ? 2 : 1)
 void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                      const float* __restrict__ inv_lambda, float rho,
                      const uint4* __restrict__ l1p, int64_t M, int K, int r, int slice,
-                     uint8_t* __restrict__ qx, float* __restrict__ sx, float* __restrict__ h) {
+                     uint8_t* __restrict__ qx, float* __restrict__ sx, float* __restrict__ h,
+                     int row_blocks, const ExpandJob expand) {
+    if constexpr (E3M2) {
+        if ((int)blockIdx.x >= row_blocks) {
+            const int id = ((int)blockIdx.x - row_blocks) * (int)gridDim.y + (int)blockIdx.y;
+            expand_weights(expand, id * WV + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63, K);
+            return;
+        }
+    }
     // LDS: inv_lambda[K] during the main loop, then the WV x 32 RB x 32 partial sums of h
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
     float* il_s = reinterpret_cast<float*>(smem_raw);
@@ -243,40 +252,42 @@ hipError_t launch_scale_chain(const float* a, float rho, int64_t n, float* s, fl
 template <bool E3M2, bool GELU, int RB, int WV>
 static hipError_t launch_quantize_geom(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                        const void* l1p, int64_t M, int K, int r,
-                                       uint8_t* qx, float* sx, float* h, int slices, hipStream_t stream) {
+                                       uint8_t* qx, float* sx, float* h, int slices, const ExpandJob& expand, hipStream_t stream) {
     const int slice = (K / 64 + slices - 1) / slices;                      // groups per slice
-    const dim3 blocks((unsigned)((M + 32 * RB - 1) / (32 * RB)), (unsigned)((K / 64 + slice - 1) / slice));
+    const unsigned row_blocks = (unsigned)((M + 32 * RB - 1) / (32 * RB)), ny = (unsigned)((K / 64 + slice - 1) / slice);
+    const unsigned expand_blocks = expand.out ? (unsigned)((expand_waves(expand.N, K) + WV - 1) / WV) : 0;
+    const dim3 blocks(row_blocks + (expand_blocks + ny - 1) / ny, ny);
     const size_t hpart = l1p ? (size_t)WV * 32 * RB * 32 * sizeof(float) : 0;
     const size_t il = (size_t)slice * 64 * sizeof(float), lds = (il > hpart) ? il : hpart;
     if (l1p)
         hipLaunchKernelGGL((quantize_kernel<true, E3M2, GELU, RB, WV>), blocks, dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, slice, qx, sx, h);
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, slice, qx, sx, h, (int)row_blocks, expand);
     else
         hipLaunchKernelGGL((quantize_kernel<false, E3M2, GELU, RB, WV>), blocks, dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, slice, qx, sx, h);
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, slice, qx, sx, h, (int)row_blocks, expand);
     return hipGetLastError();
 }
 
 template <bool E3M2, bool GELU>
 static hipError_t launch_quantize_any(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                       const void* l1p, int64_t M, int K, int r,
-                                      uint8_t* qx, float* sx, float* h, int slices, hipStream_t stream) {
+                                      uint8_t* qx, float* sx, float* h, int slices, const ExpandJob& expand, hipStream_t stream) {
     auto go = slices == 1 && quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_geom<E3M2, GELU, 2, 4> : launch_quantize_geom<E3M2, GELU, 1, 8>;
-    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, stream);
+    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, expand, stream);
 }
 
 hipError_t launch_quantize(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                            const void* l1p, int64_t M, int K, int r,
                            uint8_t* qx, float* sx, float* h, bool gelu, hipStream_t stream, int slices) {
-    return gelu ? launch_quantize_any<false, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, stream)
-                : launch_quantize_any<false, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, stream);
+    return gelu ? launch_quantize_any<false, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, ExpandJob{}, stream)
+                : launch_quantize_any<false, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, ExpandJob{}, stream);
 }
 
 hipError_t launch_quantize_e3m2(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                 const void* l1p, int64_t M, int K, int r,
-                                uint8_t* act, float* sx, float* h, bool gelu, hipStream_t stream, int slices) {
-    return gelu ? launch_quantize_any<true, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, slices, stream)
-                : launch_quantize_any<true, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, slices, stream);
+                                uint8_t* act, float* sx, float* h, bool gelu, hipStream_t stream, int slices, const ExpandJob& expand) {
+    return gelu ? launch_quantize_any<true, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, slices, expand, stream)
+                : launch_quantize_any<true, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, slices, expand, stream);
 }
 
 // Test hook: the activation alone, through the device function the quantise kernels use.
