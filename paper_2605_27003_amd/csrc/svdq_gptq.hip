@@ -1,5 +1,5 @@
 // GPTQ on the residual weights (Sec. III-B: the residual branch of the SVDQuant split is quantised with GPTQ
-// instead of round-to-nearest).  Offline calibration, not part of the per-step path: clarity over speed.
+// instead of round-to-nearest).  Offline calibration, not part of the per-step path.
 //
 // The algorithm in its column-sequential form: weights are visited in the order k = 0..K-1; a visited weight is
 // rounded to the int4 grid of its (channel, 64-group) scale and its rounding error is spread over the not yet
@@ -10,6 +10,7 @@
 // sequential sum.  The published implementation factors H^-1 once (Cholesky) and reads the same numbers off the
 // factor; this form trades that for elementwise kernels: K^3 updates for the inverse, K^3 / 3 of H^-1 and K^2 N / 2
 // of the weights during the visit, taken in panels of 64 pivots (below) so that the matrices cross HBM once per panel.
+#include <climits>
 #include <type_traits>
 
 #include "svdq_dev.h"
@@ -184,12 +185,15 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 //                  pivots.  A row outside the panel only needs the panel's 64 x 64 diagonal block as it stood at each
 //                  pivot (the tables below), and a column likewise, so the rows and columns are independent of each
 //                  other.  The pivots' columns and scaled rows, as they stood when taken, are saved.
-//   rank update    everything else receives its 64 updates in one pass from the saved columns and rows, in pivot order,
-//                  on the binary64 matrix instruction.  One block meanwhile does the same for the NEXT panel's diagonal
-//                  block, takes that through its own 64 dependent steps and leaves the next panel's tables: a serial
-//                  chain of about 20 us that the rank update of the rest hides.
+//   rank update    everything else receives its updates from the saved columns and rows, in pivot order, on the
+//                  binary64 matrix instruction.  Behind the first panel of a pair only the second panel's rows and
+//                  columns do; behind the second the rest takes both panels' 128 in one pass over memory.  One
+//                  block meanwhile does the same for the NEXT panel's diagonal block, takes that through its own 64
+//                  dependent steps and leaves the next panel's tables: a serial chain of about 40 us, which is what
+//                  the launch behind a pair's first panel takes.
 // Same result as the pivot-by-pivot form bit for bit.  K = N = 5120: with a launch per pivot and step (25 600 of them)
 // 112 ms, of which the rank updates on the vector unit were 31.
+// Pairs: 19.56 -> 18.88 ms (the inverse's launches, us: 49 and 155 in turn).
 constexpr int PB = 64;
 
 // ---- A vector of 64 elements (one row or column of the panel) lives in 16 lanes (a DPP row), four elements each.
@@ -575,14 +579,14 @@ void visit_panel_kernel(const double* __restrict__ A, const double* __restrict__
     }
 }
 
-// ---- X[a][b] <- (..((X[a][b] - L[0][a] R[0][b]) - L[1][a] R[1][b]).. - L[63][a] R[63][b]) over rows a0 + [0, rows)
-// and columns b0 + [0, cols), leaving out the 64 indices from `skip` on in both directions (skip < 0: none; rows and
-// cols count what is left) and the 64 x 64 block at (hole, hole).  L and R are [PB][ld].  rows % 64 == 0.
+// ---- X[a][b] <- (..((X[a][b] - L[0][a] R[0][b]) - L[1][a] R[1][b]).. - L[depth - 1][a] R[depth - 1][b]) over rows
+// a0 + [0, rows) and columns b0 + [0, cols), leaving out the nskip indices from skip_a (rows) and skip_b (columns) on (rows
+// and cols count what is left) and the 64 x 64 block at (hole, hole).  L and R are [depth][ld].  rows % 64 == 0.
 struct RankUpdate {
     double* X;
     const double *L, *R;
     size_t ldx, ldl, ldr;
-    int a0, rows, b0, cols, skip, hole;
+    int depth, a0, rows, b0, cols, skip_a, skip_b, nskip, hole;
     int tiles_b, tiles;          // 128 x 128 tiles along b, and in all
     bool backwards;              // every other update walks its tiles backwards, first through what is still in the caches
 };
@@ -594,10 +598,10 @@ struct Lookahead {
     const double *L, *R;
     const PanelTables* prev;
     PanelTables* next;
-    int K, p0, s0, mode;
+    int depth, K, p0, s0, mode;
 };
 
-// acc[i][k]: a wave's 16 NI x 64 elements through all 64 pivots; lane (j, kq) = (l % 16, l / 16) holds in acc[i][k][e]
+// acc[i][k]: a wave's 16 NI x 64 elements through `depth` pivots (a multiple of 8); lane (j, kq) = (l % 16, l / 16) holds in acc[i][k][e]
 // row 16 i + 4 e + kq, column wave_col(j, k): two neighbouring columns per lane, so that a row's accesses are 256
 // contiguous bytes of 16 bytes a lane.  Operands straight from global memory (L2): 64 x 64 elements per wave and 4
 // pivots are 16 matrix instructions (1024 clocks) on 6 loads, the next four pivots' requested while they run.
@@ -609,7 +613,7 @@ __device__ __forceinline__ double2 load2(const double* p, int d1) {
     return double2{p[0], p[d1]};
 }
 template <int NI, bool PAIR>
-__device__ __forceinline__ void update_chain(double4v (&acc)[NI][4], const double* __restrict__ L, size_t ldl,
+__device__ __forceinline__ void update_chain(const int depth, double4v (&acc)[NI][4], const double* __restrict__ L, size_t ldl,
                                              const double* __restrict__ R, size_t ldr, int lane, const int (&col)[2], const int (&d1)[2]) {
     const int j = lane & 15, kq = lane >> 4;
     double a[2][NI];
@@ -627,10 +631,10 @@ __device__ __forceinline__ void update_chain(double4v (&acc)[NI][4], const doubl
             for (int k = 0; k < 4; ++k) acc[i][k] = mfma_f64(a[buf][i], (k & 1) ? b[buf][k >> 1].y : b[buf][k >> 1].x, acc[i][k]);
     };
     request(0, 0);
-    for (int s = 0; s < PB / 4; s += 2) {
+    for (int s = 0; s < depth / 4; s += 2) {
         request(s + 1, 1);
         multiply(0);
-        if (s + 2 < PB / 4) request(s + 2, 0);
+        if (s + 2 < depth / 4) request(s + 2, 0);
         multiply(1);
     }
 }
@@ -650,7 +654,7 @@ __device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB]
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[0][k][e] = X[(size_t)(4 * e + kq) * la.K + wave_col(j, k)];
         const int col[2] = {2 * j, 32 + 2 * j}, d1[2] = {1, 1};
-        update_chain<1, true>(acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, col, d1);
+        update_chain<1, true>(la.depth, acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, col, d1);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -671,30 +675,29 @@ __device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB]
     else diagonal_block<false>(x, Rt, ds, la.next);
 }
 
-// Block 0 looks ahead; the others take 128 x 128 elements of u0's or u1's matrix, 64 x 64 per wave.  Every element is
-// read and written once per 64 updates: 16 bytes for 64 fused multiply-adds of 0.025 ns-chip each, so HBM bounds the
-// large matrices (K = 5120: 420 MB, 85 us at the rate of a copy) and the matrix unit needs half of that.
+// Block 0 looks ahead; the others take 128 x 128 elements of the matrix of u0, u1 or u2, 64 x 64 per wave.  Every element
+// is read and written once per `depth` updates, 16 bytes: with 64 HBM bounds the large matrices (K = 5120: 420 MB, 85 us
+// at the rate of a copy, and the matrix unit needs half of that), with 128 both take about as long.
 template <bool PAIR>
 __global__ __launch_bounds__(256, 2)
-void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const Lookahead la) {
+void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const RankUpdate u2, const Lookahead la) {
     __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
     if (blockIdx.x == 0) {
         look_ahead(la, Rt, ds);
         return;
     }
-    const int bid = (int)blockIdx.x - 1;
-    const RankUpdate u = (bid < u0.tiles) ? u0 : u1;
-    int t = (bid < u0.tiles) ? bid : bid - u0.tiles;
+    int t = (int)blockIdx.x - 1;
+    const bool first = t < u0.tiles, second = !first && t < u0.tiles + u1.tiles;
+    const RankUpdate u = first ? u0 : second ? u1 : u2;
+    t -= first ? 0 : second ? u0.tiles : u0.tiles + u1.tiles;
     if (u.backwards) t = u.tiles - 1 - t;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 15, kq = lane >> 4;
     const int ia = (t / u.tiles_b) * 128 + (wave >> 1) * 64, ib = (t % u.tiles_b) * 128 + (wave & 1) * 64;
     if (ia >= u.rows || ib >= u.cols) return;
     int ga = u.a0 + ia, gb = u.b0 + ib;                     // 64-blocks do not straddle what is left out
-    if (u.skip >= 0) {
-        if (ga >= u.skip) ga += PB;
-        if (gb >= u.skip) gb += PB;
-    }
+    if (ga >= u.skip_a) ga += u.nskip;
+    if (gb >= u.skip_b) gb += u.nskip;
     if (ga == u.hole && gb == u.hole) return;
     double* X = u.X + (size_t)ga * u.ldx;
     double4v acc[4][4];
@@ -718,7 +721,7 @@ void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const Lookahea
                 acc[i][2 * k][e] = v.x;
                 acc[i][2 * k + 1][e] = v.y;
             }
-    update_chain<4, PAIR>(acc, u.L + ga, u.ldl, u.R, u.ldr, lane, col, d1);
+    update_chain<4, PAIR>(u.depth, acc, u.L + ga, u.ldl, u.R, u.ldr, lane, col, d1);
     // the stores' addresses are formed again here; kept from the loads they would spill
 #pragma unroll
     for (int k = 0; k < 2; ++k) asm volatile("" : "+v"(col[k]));
@@ -740,16 +743,16 @@ void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const Lookahea
         }
 }
 
-void launch_rank_updates(RankUpdate u0, RankUpdate u1, const Lookahead& la, bool backwards, hipStream_t stream) {
+void launch_rank_updates(RankUpdate u0, RankUpdate u1, RankUpdate u2, const Lookahead& la, bool backwards, hipStream_t stream) {
     bool pair = true;
-    for (RankUpdate* u : {&u0, &u1}) {
+    for (RankUpdate* u : {&u0, &u1, &u2}) {
         u->tiles_b = (u->cols + 127) / 128;
         u->tiles = (u->rows > 0 && u->cols > 0) ? u->tiles_b * ((u->rows + 127) / 128) : 0;
         u->backwards = backwards;
         pair = pair && u->ldx % 2 == 0 && u->ldr % 2 == 0;
     }
     auto kern = pair ? rank_update_kernel<true> : rank_update_kernel<false>;
-    hipLaunchKernelGGL(kern, dim3(1 + u0.tiles + u1.tiles), dim3(256), 0, stream, u0, u1, la);
+    hipLaunchKernelGGL(kern, dim3(1 + u0.tiles + u1.tiles + u2.tiles), dim3(256), 0, stream, u0, u1, u2, la);
 }
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -757,7 +760,7 @@ inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 }  // namespace
 
 size_t gptq_workspace_bytes(int N, int K) {
-    return up256((size_t)K * K * 8) + up256((size_t)K * N * 8) + 3 * up256((size_t)K * PB * 8) + up256((size_t)PB * N * 8) +
+    return up256((size_t)K * K * 8) + up256((size_t)K * N * 8) + 3 * up256((size_t)K * 2 * PB * 8) + up256((size_t)2 * PB * N * 8) +
            2 * up256(sizeof(PanelTables)) + 256;
 }
 
@@ -782,10 +785,11 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     uint8_t* p = (uint8_t*)workspace;
     double* A = (double*)p;        p += up256((size_t)K * K * 8);
     double* W = (double*)p;        p += up256((size_t)K * N * 8);
-    double* Lc = (double*)p;       p += up256((size_t)K * PB * 8);     // saved pivot columns         [PB][K]
-    double* Rr = (double*)p;       p += up256((size_t)K * PB * 8);     // saved scaled pivot rows     [PB][K]
-    double* Hr = (double*)p;       p += up256((size_t)K * PB * 8);     // saved rows of H^-1          [PB][K]
-    double* Err = (double*)p;      p += up256((size_t)PB * N * 8);     // errors of the panel         [PB][N]
+    // saved by the two panels of a pair, one behind the other
+    double* Lc = (double*)p;       p += up256((size_t)K * 2 * PB * 8);     // pivot columns         [2 PB][K]
+    double* Rr = (double*)p;       p += up256((size_t)K * 2 * PB * 8);     // scaled pivot rows     [2 PB][K]
+    double* Hr = (double*)p;       p += up256((size_t)K * 2 * PB * 8);     // rows of H^-1          [2 PB][K]
+    double* Err = (double*)p;      p += up256((size_t)2 * PB * N * 8);     // errors of the panel   [2 PB][N]
     PanelTables* tabs[2];                                              // this panel's and the next one's
     for (auto& t : tabs) {
         t = (PanelTables*)p;
@@ -795,29 +799,57 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     hipLaunchKernelGGL(diag_sum_kernel, dim3(1), dim3(256), 0, stream, H, damp, K, add);
     hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(256), 0, stream, R, H, add, N, K, A, W);
     const size_t ldk = (size_t)K, ldn = (size_t)N;
-    const RankUpdate none{A, nullptr, nullptr, ldk, ldk, ldk, 0, 0, 0, 0, -1, -1, 1, 0, false};
+    constexpr int ALL = INT_MAX;                       // nothing left out
+    const RankUpdate none{A, nullptr, nullptr, ldk, ldk, ldk, PB, 0, 0, 0, 0, ALL, ALL, 0, -1, 1, 0, false};
+    // `depth` updates of A or W saved from row `from` of the pair's buffers on
+    auto of_inverse = [&](int from, int depth, int a0, int rows, int b0, int cols, int skip_a, int skip_b, int nskip, int hole) {
+        return RankUpdate{A, Lc + from * ldk, Rr + from * ldk, ldk, ldk, ldk, depth, a0, rows, b0, cols, skip_a, skip_b, nskip, hole, 1, 0, false};
+    };
+    auto of_weights = [&](int depth, int a0, int rows) {
+        return RankUpdate{W, Hr, Err, ldn, ldk, ldn, depth, a0, rows, 0, N, ALL, ALL, 0, -1, 1, 0, false};
+    };
     const int np = K / PB;
     int cur = 0;                                       // tabs[cur]: the current panel's
     hipLaunchKernelGGL(first_tables_kernel<true>, dim3(1), dim3(256), 0, stream, A, ldk, tabs[cur]);
     for (int b = 0; b < np; ++b) {                     // the inverse, one panel of pivots at a time
-        const int p0 = b * PB;
+        const int p0 = b * PB, half = (b & 1) * PB;    // half: this panel's place in the pair's buffers
         if (np > 1)
-            hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (K - PB) / PVECS), dim3(256), 0, stream, A, K, p0, tabs[cur], Lc, Rr);
+            hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (K - PB) / PVECS), dim3(256), 0, stream, A, K, p0, tabs[cur],
+                               Lc + half * ldk, Rr + half * ldk);
         // next: the following panel, and after the last one the first panel of the visit
         const int s0 = (b + 1 < np) ? p0 + PB : 0;
         const bool same = s0 == p0;                    // a single panel: its own finished block is what is visited
-        const Lookahead la{A, same ? nullptr : Lc, Rr, tabs[cur], tabs[cur ^ 1], K, p0, s0, (b + 1 < np) ? 1 : 2};
-        launch_rank_updates(RankUpdate{A, Lc, Rr, ldk, ldk, ldk, 0, K - PB, 0, K - PB, p0, same ? -1 : s0, 1, 0, false}, none, la, b & 1, stream);
+        // What the next diagonal block has not had yet: both panels of a pair, but the second's only where it lies in
+        // the first (two panels: the visit starts there).
+        const int from = (half && s0 == p0 - PB) ? PB : 0, depth = half + PB - from;
+        const Lookahead la{A, same ? nullptr : Lc + from * ldk, Rr + from * ldk, tabs[cur], tabs[cur ^ 1],
+                           depth, K, p0, s0, (b + 1 < np) ? 1 : 2};
+        if (half) {
+            // everything outside both panels; then the first panel's rows and columns, which only the second's pivots are left for
+            const int q0 = p0 - PB;
+            launch_rank_updates(of_inverse(0, 2 * PB, 0, K - 2 * PB, 0, K - 2 * PB, q0, q0, 2 * PB, s0),
+                                of_inverse(PB, PB, q0, PB, 0, K - PB, ALL, p0, PB, s0),
+                                of_inverse(PB, PB, 0, K - 2 * PB, q0, PB, q0, ALL, 2 * PB, s0), la, b & 2, stream);
+        } else if (b + 1 < np) {                       // the second panel's rows, and its columns in the rows of neither
+            launch_rank_updates(of_inverse(0, PB, s0, PB, 0, K - PB, ALL, p0, PB, s0),
+                                of_inverse(0, PB, 0, K - 2 * PB, s0, PB, p0, ALL, 2 * PB, s0), none, la, false, stream);
+        } else {                                       // a last panel without a second
+            launch_rank_updates(of_inverse(0, PB, 0, K - PB, 0, K - PB, p0, p0, PB, same ? -1 : s0), none, none, la, b & 2, stream);
+        }
         cur ^= 1;
     }
     for (int b = 0; b < np; ++b) {                     // the weights, one panel (= one 64-group) at a time
-        const int i0 = b * PB, i1 = i0 + PB, rest = K - i1;
+        const int i0 = b * PB, i1 = i0 + PB, rest = K - i1, half = (b & 1) * PB;
         hipLaunchKernelGGL(visit_panel_kernel, dim3(2 * (rest / PVECS) + (N + PVECS - 1) / PVECS), dim3(256), 0, stream,
-                           A, W, N, K, i0, tabs[cur], Lc, Hr, Rr, Err, qw, sw);
-        if (rest > 0) {                                // the deferred updates of everything behind the panel
-            const Lookahead la{A, Lc, Rr, nullptr, tabs[cur ^ 1], K, 0, i1, 2};
-            launch_rank_updates(RankUpdate{W, Hr, Err, ldn, ldk, ldn, i1, rest, 0, N, -1, -1, 1, 0, false},
-                                RankUpdate{A, Lc, Rr, ldk, ldk, ldk, i1, rest, i1, rest, -1, i1, 1, 0, false}, la, b & 1, stream);
+                           A, W, N, K, i0, tabs[cur], Lc + half * ldk, Hr + half * ldk, Rr + half * ldk, Err + half * ldn, qw, sw);
+        if (rest > 0) {                                // the deferred updates of what is behind the panel
+            const Lookahead la{A, Lc, Rr, nullptr, tabs[cur ^ 1], half + PB, K, 0, i1, 2};
+            if (half)
+                launch_rank_updates(of_weights(2 * PB, i1, rest), of_inverse(0, 2 * PB, i1, rest, i1, rest, ALL, ALL, 0, i1), none,
+                                    la, b & 2, stream);
+            else                                       // of the second panel's rows and columns only
+                launch_rank_updates(of_weights(PB, i1, PB), of_inverse(0, PB, i1, PB, i1, rest, ALL, ALL, 0, i1),
+                                    of_inverse(0, PB, i1 + PB, rest - PB, i1, PB, ALL, ALL, 0, -1), la, false, stream);
         }
         cur ^= 1;
     }

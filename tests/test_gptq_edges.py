@@ -19,7 +19,8 @@ def svdq():
     return m
 
 
-@pytest.mark.parametrize("K,N,scale", [(192, 67, 1.0), (64, 1, 1.0), (256, 96, 2.0 ** -720), (128, 64, 2.0 ** 720)])
+@pytest.mark.parametrize("K,N,scale", [(192, 67, 1.0), (64, 1, 1.0), (256, 96, 2.0 ** -720), (128, 64, 2.0 ** 720),
+                                       (320, 130, 1.0), (384, 67, 2.0 ** 720)])   # panels go in pairs: 3, 1, 4, 2, 5, 6
 def test_gptq_bit_exact_at_the_edges(svdq, oracle, K, N, scale):
     """Codes and scales are those of the definition (binary64, oracle) whatever the scale of H: scaling H scales H^-1
     exactly, by a power of two, but takes the quotients by its diagonal out of the range of the fast division."""
