@@ -517,6 +517,11 @@ class _Layer(ctypes.Structure):
                 [(n, _vp) for n in ("inv_lambda", "l1_packed", "L2_bf16", "bias", "w_packed", "qw", "sw")])
 
 
+# One layer's buffers for one token count: the library's view (ptrs: codes, sx, h, scratch), the caller's (public) and what
+# they were made for (key).
+_Work = collections.namedtuple("_Work", "codes sx h scratch staging shared y public ptrs key")
+
+
 def _addr(t):
     return None if t is None else t.data_ptr()
 
@@ -547,21 +552,25 @@ class W4A4Linear:
         else:
             self.w_packed = {"e3m2": pack_weight_e3m2, "nibble": pack_weight, "mxfp4": pack_weight_mxfp4}[container](qw, sw)
         self.bias = bias
-        self._bufs = self._layer = self._fields = None
+        self._work = self._layer = None
 
     def _descriptor(self, r):
-        """Address of the svdq_layer of the tensors that the layer holds now (they may have been replaced), with rank r."""
+        """svdq_layer of the tensors that the layer holds now (they may have been replaced), with rank r.  The caller keeps
+        it through its call: another thread may take the layer's place for one of its own meanwhile."""
         l1, L2, bias, wp, qw, sw = self.l1_packed, self.L2, self.bias, self.w_packed, self.qw, self.sw
         fields = (self.format, self.N, self.K, r, self.inv_lambda.data_ptr(),
                   None if l1 is None else l1.data_ptr(), None if L2 is None else L2.data_ptr(), None if bias is None else bias.data_ptr(),
                   None if wp is None else wp.data_ptr(), None if qw is None else qw.data_ptr(), None if sw is None else sw.data_ptr())
-        if fields != self._fields:
-            self._layer, self._fields = _Layer(*fields), fields
-        return ctypes.addressof(self._layer)
+        layer = self._layer
+        if layer is None or layer.values != fields:
+            layer = _Layer(*fields)
+            layer.values = fields
+            self._layer = layer
+        return layer
 
     def __getstate__(self):
         """Copies make buffers and a descriptor of their own."""
-        return {**self.__dict__, "_bufs": None, "_work": None, "_layer": None, "_fields": None}
+        return {**self.__dict__, "_work": None, "_layer": None}
 
     def weights(self):
         """The packed weights the GEMM takes: resident, or expanded now from the resident 4-bit form."""
@@ -569,9 +578,13 @@ class W4A4Linear:
             return self.w_packed
         return pack_weight_e3m2(self.qw, self.sw, out=_staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), self.qw.device))
 
-    def buffers(self, M, device):
-        if self._bufs is None or self._bufs[3].shape[0] != M:
-            lib, ref, K = load_library(), self._descriptor(self.r), self.K
+    def _workspace(self, M, device):
+        """The layer's buffers for M tokens, made again when anything that their sizes depend on has changed.  One object:
+        a call takes all its buffers from the one that it got, whatever other threads do to the layer meanwhile."""
+        key = (M, device, self.format, self.N, self.K, self.r, self.w_packed is None)
+        work = self._work
+        if work is None or work.key != key:
+            lib, ref, K, r = load_library(), ctypes.byref(self._descriptor(self.r)), self.K, self.r
             own = act_e3m2_bytes(M, K) if self.container == "e3m2" else M * K // 2
             codes = torch.empty(max(own, lib.svdq_layer_codes_bytes(ref, M)), dtype=torch.uint8, device=device)
             if self.container == "e3m2":
@@ -580,7 +593,7 @@ class W4A4Linear:
                 qx = codes[:own].view(K // 64, M, 32)
                 sx = (torch.empty((K // 64, M), dtype=torch.float32, device=device) if self.container == "nibble"
                       else torch.empty(((K // 64 + 1) // 2, M, 2, 2), dtype=torch.uint8, device=device))
-            h = torch.empty((M, self.r), dtype=torch.float32, device=device) if self.r else None
+            h = torch.empty((M, r), dtype=torch.float32, device=device) if r else None
             y = torch.empty((M, self.N), dtype=torch.bfloat16, device=device)
             n = lib.svdq_layer_scratch_bytes(ref, M)
             scratch = torch.empty(n, dtype=torch.uint8, device=device) if n else None
@@ -592,14 +605,19 @@ class W4A4Linear:
                 shared = n > 0
             elif n:
                 staging = torch.empty(n, dtype=torch.uint8, device=device)
-            self._work = (codes, sx, h, scratch, staging, shared)
-            self._work_ptrs = tuple(map(_addr, self._work[:4]))          # of the buffers made here
-            self._bufs = (qx, sx, h, y)
-        return self._bufs
+            work = _Work(codes, sx, h, scratch, staging, shared, y, (qx, sx, h, y), tuple(map(_addr, (codes, sx, h, scratch))), key)
+            self._work = work
+        return work
 
-    def _staging(self, device):
-        staging, shared = self._work[4:]
-        return _staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), device).data_ptr() if shared else _addr(staging)
+    def buffers(self, M, device):
+        """(qx, sx, h, y) for M tokens: what quantize() fills and gemm() takes, and the output."""
+        device = torch.device(device)
+        if device.type == "cuda" and device.index is None:
+            device = torch.device("cuda", torch.cuda.current_device())
+        return self._workspace(M, device).public
+
+    def _staging(self, work, device):
+        return _staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), device).data_ptr() if work.shared else _addr(work.staging)
 
     def quantize(self, x_bf16, rho, gelu=False):
         """Kernel (a) into the layer's buffers; gelu=True applies the feed-forward block's activation on the fly."""
@@ -612,19 +630,19 @@ class W4A4Linear:
     def gemm(self, qx, sx, h):
         codes = qx.buf if self.container == "e3m2" else qx
         M, device = (qx.M if self.container == "e3m2" else qx.shape[1]), codes.device
-        y = self.buffers(M, device)[3]
+        work, layer = self._workspace(M, device), self._descriptor(0 if h is None else h.shape[1])
         _check(load_library().svdq_layer_gemm(
-            self._descriptor(0 if h is None else h.shape[1]), codes.data_ptr(), _addr(sx), _addr(h), M, self._staging(device),
-            y.data_ptr(), self.N, _stream()), "svdq_layer_gemm")
-        return y
+            ctypes.byref(layer), codes.data_ptr(), _addr(sx), _addr(h), M, self._staging(work, device),
+            work.y.data_ptr(), self.N, _stream()), "svdq_layer_gemm")
+        return work.y
 
     def forward(self, x_bf16, rho, gelu=False):
         M, K = x_bf16.shape
         assert x_bf16.dtype == torch.bfloat16 and x_bf16.stride(1) == 1 and K == self.K
         device = x_bf16.device
-        y = self.buffers(M, device)[3]
+        work, layer = self._workspace(M, device), self._descriptor(self.r)
         _check((_lib or load_library()).svdq_layer_forward(
-            self._descriptor(self.r), x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, float(rho), 1 if gelu else 0, M,
-            *self._work_ptrs, self._staging(device),
-            y.data_ptr(), self.N, _raw_stream()), "svdq_layer_forward")
-        return y
+            ctypes.byref(layer), x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, float(rho), 1 if gelu else 0, M,
+            *work.ptrs, self._staging(work, device),
+            work.y.data_ptr(), self.N, _raw_stream()), "svdq_layer_forward")
+        return work.y

@@ -5,6 +5,7 @@ import pickle
 import torch
 
 import paper_2605_27003_amd as svdq
+from paper_2605_27003_amd import binding
 
 
 def test_descriptor_follows_the_layer():
@@ -18,3 +19,67 @@ def test_descriptor_follows_the_layer():
     lin.bias = None
     lin._descriptor(16)
     assert lin._layer.bias is None and lin._layer.r == 16
+
+
+def _layer(K=1024, N=128, **kw):
+    return svdq.W4A4Linear(torch.ones(K), None, None, torch.zeros((N, K // 2), dtype=torch.uint8), torch.ones((K // 64, N)),
+                           torch.zeros(N), **kw)
+
+
+def test_buffers_follow_what_their_sizes_depend_on():
+    """A low-rank pair of another rank, or another form of the weights, between two calls with the same token count: h,
+    the partial h's and the staging buffer are written by the kernels for the layer as it is, so they have its sizes."""
+    lin, M, sizes = _layer(), 40, []
+    for r in (16, 32, 0, 32):
+        lin.r = r
+        lin.l1_packed = torch.zeros(svdq.packed_l1_bytes(lin.K), dtype=torch.uint8) if r else None
+        lin.L2 = torch.zeros((r, lin.N), dtype=torch.bfloat16) if r else None
+        h = lin.buffers(M, "cpu")[2]
+        assert h is None if r == 0 else h.shape == (M, r)
+        sizes.append((r, lin._work.scratch))
+    for r, scratch in sizes:
+        need = binding.load_library().svdq_layer_scratch_bytes(binding.ctypes.byref(lin._descriptor(r)), M)
+        assert (need > 0) == (r > 0) and (scratch is not None or not need) and (not need or scratch.numel() >= need)
+    assert lin.buffers(M, "cpu")[3] is lin.buffers(M, torch.device("cpu"))[3]
+    assert lin.buffers(M, "meta")[3].device.type == "meta" and lin.buffers(M, "cpu")[3].device.type == "cpu"
+    lin = _layer(K=4096, N=2048)
+    lin.w_packed = torch.zeros(svdq.packed_weight_e3m2_bytes(lin.N, lin.K), dtype=torch.uint8)
+    lin.buffers(4096, "cpu")
+    assert not lin._work.shared
+    lin.w_packed = None
+    lin.buffers(4096, "cpu")
+    assert lin._work.shared
+    binding._staging.clear()
+
+
+def test_a_call_keeps_its_own_buffers(monkeypatch):
+    """Another thread that runs the layer with another token count, or replaces a tensor, between this call's steps: the
+    library gets this call's buffers and descriptor all the same."""
+    lin, M, seen = _layer(), 512, []
+
+    class Lib:
+        def __getattr__(self, name):
+            return getattr(real, name)
+
+        def svdq_layer_forward(self, layer, x, ldx, rho, gelu, m, codes, *rest):
+            seen.append((m, codes))
+            return 0
+
+    real = binding.load_library()
+    monkeypatch.setattr(binding, "_lib", Lib())
+    monkeypatch.setattr(binding, "_raw_stream", lambda: 0)
+    mine = lin.buffers(M, "cpu")[0].buf
+    descriptor = type(lin)._descriptor
+
+    def other_thread(self, r):
+        monkeypatch.setattr(type(lin), "_descriptor", descriptor)
+        first = self._descriptor(r)
+        self.buffers(1, "cpu")
+        self.bias = torch.ones(self.N)
+        assert self._descriptor(r) is not first and first.bias != self.bias.data_ptr()
+        return first
+
+    monkeypatch.setattr(type(lin), "_descriptor", other_thread)
+    y = lin.forward(torch.zeros((M, lin.K), dtype=torch.bfloat16), 0.8)
+    assert seen == [(M, mine.data_ptr())] and y.shape == (M, lin.N)
+    binding._staging.clear()
