@@ -526,6 +526,9 @@ def _addr(t):
     return None if t is None else t.data_ptr()
 
 
+_FORMATS = {"e3m2": FMT_INT4_E3M2, "nibble": FMT_INT4, "mxfp4": FMT_MXFP4}
+
+
 class W4A4Linear:
     """One quantised linear resident in HBM: weights and low-rank factors, reusable output buffers.
 
@@ -540,7 +543,7 @@ class W4A4Linear:
     def __init__(self, inv_lambda, L1_bf16, L2_bf16, qw, sw, bias, container="e3m2", resident="w4"):
         assert container in ("e3m2", "nibble", "mxfp4") and resident in ("w4", "packed")
         self.container = container
-        self.format = {"e3m2": FMT_INT4_E3M2, "nibble": FMT_INT4, "mxfp4": FMT_MXFP4}[container]
+        self.format = _FORMATS[container]
         self.N, self.K = qw.shape[0], qw.shape[1] * 2
         self.r = 0 if L1_bf16 is None else L1_bf16.shape[1]
         self.inv_lambda = inv_lambda
@@ -571,6 +574,10 @@ class W4A4Linear:
     def __getstate__(self):
         """Copies make buffers and a descriptor of their own."""
         return {**self.__dict__, "_work": None, "_layer": None}
+
+    def __setstate__(self, state):
+        """Also of layers saved with their buffers, and before the format code and the canonical tensors were attributes."""
+        self.__dict__.update({"qw": None, "sw": None, **state, "format": _FORMATS[state["container"]], "_work": None, "_layer": None})
 
     def weights(self):
         """The packed weights the GEMM takes: resident, or expanded now from the resident 4-bit form."""

@@ -83,3 +83,22 @@ def test_a_call_keeps_its_own_buffers(monkeypatch):
     y = lin.forward(torch.zeros((M, lin.K), dtype=torch.bfloat16), 0.8)
     assert seen == [(M, mine.data_ptr())] and y.shape == (M, lin.N)
     binding._staging.clear()
+
+
+def test_layers_saved_by_earlier_versions():
+    """The state that pickles of layers held before the whole-layer call (no format code, qw and sw with resident 4-bit
+    weights only, buffers included): such a layer still runs."""
+    for container in ("e3m2", "nibble", "mxfp4"):
+        now = _layer()
+        state = dict(container=container, N=now.N, K=now.K, r=0, inv_lambda=now.inv_lambda, l1_packed=None, L2=None,
+                     w_packed=None, bias=now.bias, _bufs=tuple(torch.zeros((40, 1)) for _ in range(4)))
+        if container == "e3m2":
+            state.update(qw=now.qw, sw=now.sw)
+        else:
+            state["w_packed"] = torch.zeros(1 << 18, dtype=torch.uint8)
+        old = svdq.W4A4Linear.__new__(svdq.W4A4Linear)
+        copy_of = getattr(old, "__setstate__", old.__dict__.update)
+        copy_of(state)
+        assert old._descriptor(0).format == {"e3m2": 1, "nibble": 0, "mxfp4": 2}[container]
+        assert old.buffers(40, "cpu")[3].shape == (40, now.N)
+    binding._staging.clear()
