@@ -261,12 +261,13 @@ int svdq_debug_gelu(const void* x_bf16, int64_t n, void* out_bf16, void* stream)
  *   inv_lambda, l1_packed, L2_bf16, bias, r   as for the separate calls (r = 0: l1_packed and L2_bf16 NULL)
  * svdq_layer_forward: x, ldx, rho, M as svdq_quantize_act, gelu != 0 as svdq_quantize_act_gelu;
  *   codes           svdq_layer_codes_bytes(layer, M) bytes, 16-byte aligned, scales the format's scale buffer (unused, may
- *                   be NULL for SVDQ_FMT_INT4_E3M2): for the quantised activations, in whichever of the library's forms
- *                   the size calls for (SVDQ_FMT_INT4 with many tokens runs as E3M2 fields: same codes and scales)
+ *                   be NULL for SVDQ_FMT_INT4_E3M2): receive what the format's own quantise call writes there
  *   h               [M, r] binary32; holds intermediate values, not necessarily h, afterwards
  *   scratch         svdq_layer_scratch_bytes(layer, M) bytes, 16-byte aligned, or NULL (slower with few tokens)
  *   staging         svdq_layer_staging_bytes(layer, M) bytes, 16-byte aligned: room for the expanded weights of one
- *                   GEMM (0 bytes if they are resident or M is small: NULL then)
+ *                   GEMM (0 bytes if they are resident or M is small: NULL then), and for SVDQ_FMT_INT4, which runs as
+ *                   E3M2 fields with many tokens (same codes and scales), for the activations' fields.  Holds nothing
+ *                   between calls
  *   y               out [M, ldy] bf16
  * svdq_layer_gemm: the second half, from activations quantised by the format's own call.
  */

@@ -517,8 +517,8 @@ class _Layer(ctypes.Structure):
                 [(n, _vp) for n in ("inv_lambda", "l1_packed", "L2_bf16", "bias", "w_packed", "qw", "sw")])
 
 
-# One layer's buffers for one token count: the library's view (ptrs: codes, sx, h, scratch), the caller's (public) and what
-# they were made for (key).
+# One layer's buffers for one token count: the library's view (ptrs: codes, sx, h, scratch; bytes of staging, shared or
+# not), the caller's (public) and what they were made for (key).
 _Work = collections.namedtuple("_Work", "codes sx h scratch staging shared y public ptrs key")
 
 
@@ -537,8 +537,9 @@ class W4A4Linear:
     same codes and scales), "mxfp4" the MXFP4 format (qw then holds E2M1 codes and sw [K/32, N] E8M0 bytes).
     resident "w4" (default, container "e3m2" only) keeps the canonical 4-bit weights (qw, sw) and expands them into a
     staging buffer shared by all such layers of the device right before a GEMM of many tokens (calls on one stream only);
-    the nibble container's are expanded into a buffer of the layer's own;
-    "packed" keeps the container's own packed form (7 - 8 bits per weight for the int4 containers)."""
+    "packed" keeps the container's own packed form (7 - 8 bits per weight for the int4 containers), and forward() of the
+    nibble container takes the memory that it expands weights and codes into for the call alone, from torch's allocator.
+    buffers() holds, after quantize() as after forward(), what the container's quantise pass wrote."""
 
     def __init__(self, inv_lambda, L1_bf16, L2_bf16, qw, sw, bias, container="e3m2", resident="w4"):
         assert container in ("e3m2", "nibble", "mxfp4") and resident in ("w4", "packed")
@@ -592,12 +593,11 @@ class W4A4Linear:
         work = self._work
         if work is None or work.key != key:
             lib, ref, K, r = load_library(), ctypes.byref(self._descriptor(self.r)), self.K, self.r
-            own = act_e3m2_bytes(M, K) if self.container == "e3m2" else M * K // 2
-            codes = torch.empty(max(own, lib.svdq_layer_codes_bytes(ref, M)), dtype=torch.uint8, device=device)
+            codes = torch.empty(act_e3m2_bytes(M, K) if self.container == "e3m2" else M * K // 2, dtype=torch.uint8, device=device)
             if self.container == "e3m2":
                 qx, sx = ActE3M2(codes, M, K), None
             else:
-                qx = codes[:own].view(K // 64, M, 32)
+                qx = codes.view(K // 64, M, 32)
                 sx = (torch.empty((K // 64, M), dtype=torch.float32, device=device) if self.container == "nibble"
                       else torch.empty(((K // 64 + 1) // 2, M, 2, 2), dtype=torch.uint8, device=device))
             h = torch.empty((M, r), dtype=torch.float32, device=device) if r else None
@@ -605,13 +605,11 @@ class W4A4Linear:
             n = lib.svdq_layer_scratch_bytes(ref, M)
             scratch = torch.empty(n, dtype=torch.uint8, device=device) if n else None
             # Room for expanded weights: the canonical form's is shared between layers (and reserved here, though few tokens
-            # expand nothing).  The nibble container's is the layer's own: its layers may run on several streams at once.
-            n, staging, shared = lib.svdq_layer_staging_bytes(ref, M), None, False
-            if self.container == "e3m2" and self.w_packed is None:
+            # expand nothing).  The nibble container's is taken for each call: its layers may run on several streams at
+            # once, and kept it would be as much again as the packed weights, in every layer.
+            staging, shared = lib.svdq_layer_staging_bytes(ref, M), self.container == "e3m2" and self.w_packed is None
+            if shared:
                 _staging_buffer(packed_weight_e3m2_bytes(self.N, K), device)
-                shared = n > 0
-            elif n:
-                staging = torch.empty(n, dtype=torch.uint8, device=device)
             work = _Work(codes, sx, h, scratch, staging, shared, y, (qx, sx, h, y), tuple(map(_addr, (codes, sx, h, scratch))), key)
             self._work = work
         return work
@@ -624,7 +622,11 @@ class W4A4Linear:
         return self._workspace(M, device).public
 
     def _staging(self, work, device):
-        return _staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), device).data_ptr() if work.shared else _addr(work.staging)
+        """Memory for one call's expanded operands, or None; the caller holds it until its kernels are enqueued."""
+        if not work.staging:
+            return None
+        return (_staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), device) if work.shared
+                else torch.empty(work.staging, dtype=torch.uint8, device=device))
 
     def quantize(self, x_bf16, rho, gelu=False):
         """Kernel (a) into the layer's buffers; gelu=True applies the feed-forward block's activation on the fly."""
@@ -638,8 +640,9 @@ class W4A4Linear:
         codes = qx.buf if self.container == "e3m2" else qx
         M, device = (qx.M if self.container == "e3m2" else qx.shape[1]), codes.device
         work, layer = self._workspace(M, device), self._descriptor(0 if h is None else h.shape[1])
+        staging = self._staging(work, device) if work.shared else None       # nibbles are multiplied as they are
         _check(load_library().svdq_layer_gemm(
-            ctypes.byref(layer), codes.data_ptr(), _addr(sx), _addr(h), M, self._staging(work, device),
+            ctypes.byref(layer), codes.data_ptr(), _addr(sx), _addr(h), M, _addr(staging),
             work.y.data_ptr(), self.N, _stream()), "svdq_layer_gemm")
         return work.y
 
@@ -648,8 +651,9 @@ class W4A4Linear:
         assert x_bf16.dtype == torch.bfloat16 and x_bf16.stride(1) == 1 and K == self.K
         device = x_bf16.device
         work, layer = self._workspace(M, device), self._descriptor(self.r)
+        staging = self._staging(work, device)
         _check((_lib or load_library()).svdq_layer_forward(
             ctypes.byref(layer), x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, float(rho), 1 if gelu else 0, M,
-            *work.ptrs, self._staging(work, device),
+            *work.ptrs, _addr(staging),
             work.y.data_ptr(), self.N, _raw_stream()), "svdq_layer_forward")
         return work.y

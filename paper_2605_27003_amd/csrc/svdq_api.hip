@@ -179,7 +179,7 @@ static int quantize_e3m2(const void* x_bf16, int64_t ldx, const float* inv_lambd
     if (M > SVDQ_MAX_M) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
-    return hip_status(svdq::launch_quantize_e3m2(x_bf16, ldx, inv_lambda, rho, l1_packed, M, K, r, act, sx, h, gelu,
+    return hip_status(svdq::launch_quantize_e3m2(x_bf16, ldx, inv_lambda, rho, l1_packed, M, K, r, act, nullptr, sx, h, gelu,
                                                  (hipStream_t)stream));
 }
 
@@ -409,17 +409,20 @@ size_t svdq_layer_scratch_bytes(const svdq_layer* L, int64_t M) {
 // Nibble storage with more tokens than the few-token path takes runs as E3M2 fields as well: the FP6 instruction takes a
 // whole group at twice the int8 rate, and writing the activations as fields (56 instead of 36 bytes per token and group)
 // and expanding the weights cost less than that saves (M = 32760, K = N = 5120: 1.05 against 1.39 ms; M = 512: 39
-// against 44 us).  Same codes, same integer group sums, same scale pieces.
+// against 44 us).  Same codes, same integer group sums, same scale pieces.  Fields and expanded weights live in the
+// caller's staging for the call only; codes and scales receive the layer's own 4-bit form beside them.
 static bool as_fields(const svdq_layer* L, int64_t M) { return L->format == SVDQ_FMT_INT4 && !small_path(L, M); }
+static size_t staged_weight_bytes(const svdq_layer* L) { return (svdq::packed_weight_e3m2_bytes(L->N, L->K) + 255) & ~(size_t)255; }
 
 size_t svdq_layer_codes_bytes(const svdq_layer* L, int64_t M) {
     if (layer_check(L, M) != SVDQ_OK) return 0;
-    return (L->format == SVDQ_FMT_INT4_E3M2 || as_fields(L, M)) ? svdq::act_e3m2_bytes(M, L->K) : (size_t)M * L->K / 2;
+    return L->format == SVDQ_FMT_INT4_E3M2 ? svdq::act_e3m2_bytes(M, L->K) : (size_t)M * L->K / 2;
 }
 
 size_t svdq_layer_staging_bytes(const svdq_layer* L, int64_t M) {
-    if (layer_check(L, M) != SVDQ_OK || small_path(L, M) || (L->w_packed && !as_fields(L, M))) return 0;
-    return svdq::packed_weight_e3m2_bytes(L->N, L->K);
+    if (layer_check(L, M) != SVDQ_OK || small_path(L, M)) return 0;
+    if (as_fields(L, M)) return staged_weight_bytes(L) + svdq::act_e3m2_bytes(M, L->K);
+    return L->w_packed ? 0 : svdq::packed_weight_e3m2_bytes(L->N, L->K);
 }
 
 static svdq::ExpandJob layer_expand_job(const svdq_layer* L, void* staging) {
@@ -495,7 +498,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
     if (!x_bf16 || !(rho > 0.0f) || !(rho <= 1.0f)) return SVDQ_ERR_INVALID_ARG;
     if (L->K > SVDQ_MAX_K || ldx < L->K || ldx % 8 || !aligned16(x_bf16) || !aligned16(scratch)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
-    const bool fields = as_fields(L, M);
+    const bool fields = as_fields(L, M);                                     // they follow the weights in staging
     const bool expand = fields || (!L->w_packed && !small_path(L, M));       // the GEMM needs the weights in staging
     if (expand && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
@@ -505,13 +508,15 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     // without h there is nothing to add up over the slices
     int slices = (r == 0 || scratch) ? layer_slices(L, M) : 1;
     float* const ho = (r != 0 && slices > 1) ? (float*)scratch : h;
+    uint8_t* const act = fields ? (uint8_t*)staging + staged_weight_bytes(L) : (uint8_t*)codes;
     hipError_t e;
     if (L->format == SVDQ_FMT_INT4 && !fields)
         e = svdq::launch_quantize(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, (float*)scales, ho, gelu != 0, stream, slices);
     else if (L->format == SVDQ_FMT_MXFP4)
         e = svdq::launch_quantize_mx(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, (uint8_t*)scales, ho, gelu != 0, stream, slices);
     else
-        e = svdq::launch_quantize_e3m2(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, (uint8_t*)codes, nullptr, ho, gelu != 0, stream, slices,
+        e = svdq::launch_quantize_e3m2(x_bf16, ldx, L->inv_lambda, rho, L->l1_packed, M, K, r, act, fields ? (uint8_t*)codes : nullptr,
+                                       fields ? (float*)scales : nullptr, ho, gelu != 0, stream, slices,
                                        expand ? layer_expand_job(L, staging) : svdq::ExpandJob{});
     if (e != hipSuccess) return hip_status(e);
     const float* hin = ho;
@@ -521,7 +526,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
         hin = h;
         slices = 1;
     }
-    return layer_gemm(L, (const uint8_t*)codes, scales, fields, expand, r ? hin : nullptr, r ? slices : 1, M, staging, y, ldy, stream);
+    return layer_gemm(L, act, scales, fields, expand, r ? hin : nullptr, r ? slices : 1, M, staging, y, ldy, stream);
 }
 
 size_t svdq_gptq_workspace_bytes(int N, int K) {

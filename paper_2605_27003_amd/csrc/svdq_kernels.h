@@ -41,10 +41,11 @@ struct ExpandJob {
 ExpandJob expand_canonical_job(const void* qw, const void* sw, int N, void* out);
 ExpandJob expand_packed_job(const void* w_packed_nibble, int N, int K, void* out);
 hipError_t launch_expand(const ExpandJob& e, int K, hipStream_t stream);
-// expand: weights [N, K] that blocks of the same launch expand beside the pass (out null: none)
+// nib: the codes as nibbles too, [K/64][M][32 B] (null: not wanted).  expand: weights [N, K] that blocks of the same launch
+// expand beside the pass (out null: none)
 hipError_t launch_quantize_e3m2(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                 const void* l1p, int64_t M, int K, int r,
-                                uint8_t* act, float* sx, float* h, bool gelu, hipStream_t stream, int slices = 1,
+                                uint8_t* act, uint8_t* nib, float* sx, float* h, bool gelu, hipStream_t stream, int slices = 1,
                                 const ExpandJob& expand = ExpandJob{});
 size_t packed_weight_e3m2_bytes(int N, int K);
 __host__ __device__ inline size_t packed_e3m2_w0_bytes(int N, int K) { return (size_t)N * (K / 64) * 32; }     // planes of the packed weights

@@ -88,10 +88,10 @@ __device__ __forceinline__ LaneCodes<true> e3m2_of_nibbles(const uint4& nib) {
     return out;
 }
 
-// One 32-row block of one group: quantiser chain on this lane's 32 values.
-template <bool E3M2>
+// One 32-row block of one group: quantiser chain on this lane's 32 values.  BOTH: the codes of the E3M2 fields as nibbles too.
+template <bool E3M2, bool BOTH = false>
 __device__ __forceinline__ void quantize_rows(const uint4 (&xv)[4], const float* __restrict__ il_lds, float rho,
-                                              LaneCodes<E3M2>& codes, float& s_out) {
+                                              LaneCodes<E3M2>& codes, float& s_out, uint4* nibbles = nullptr) {
     float xs[32];
     float a = 0.0f;
 #pragma unroll
@@ -137,7 +137,7 @@ __device__ __forceinline__ void quantize_rows(const uint4 (&xv)[4], const float*
         const u32x6 c = e3m2_of_floats(ev, od, 1.0f);
         codes.lo = uint4{c[0], c[1], c[2], c[3]};
         codes.hi = uint2{c[4], c[5]};
-        return;
+        if constexpr (!BOTH) return;
     }
     uint32_t packed[4];
 #pragma unroll
@@ -152,7 +152,8 @@ __device__ __forceinline__ void quantize_rows(const uint4 (&xv)[4], const float*
         }
         packed[d] = (wd - PACK_JUNK) ^ 0x88888888u;
     }
-    codes.lo = uint4{packed[0], packed[1], packed[2], packed[3]};
+    if constexpr (BOTH) *nibbles = uint4{packed[0], packed[1], packed[2], packed[3]};
+    else codes.lo = uint4{packed[0], packed[1], packed[2], packed[3]};
 }
 
 }  // namespace svdq

@@ -35,19 +35,22 @@ namespace {
 //   [Mp] x 8 B             the token scale as two bf16 pieces, p = hi | lo << 16, stored twice ({p, p} is the
 //                          m-side operand of the scale-product MFMA)
 // sx [K/64][M] binary32 is written in both cases (skipped if null with E3M2).
+// BOTH (with E3M2): nib also receives the codes as nibbles, [K/64][M][32 B]: a layer whose activations are held in 4 bits
+// but multiplied as fields.  10 % more bytes than the fields alone, against a second pass over them.
 // GELU = true: x is the feed-forward block's pre-activation; every value is replaced by bf16(gelu(x)) as it
 // arrives (svdq_act.h), and the pass continues as if a separate element-wise kernel had written that tensor.
 // RB x WV = 2 x 4 is the geometry for many tokens: a fragment of L1 is loaded once for 64 rows.  A block's waves walk
 // K / 64 groups in turn, about 1.7 us each (the latency of the x loads), so with few row blocks the walk is what is waited
 // for (M = 512, K = 5120: 8 blocks, 34 us): 1 x 8 then spreads rows and groups over more CUs and
 // waves (sixteen waves gain nothing: what a CU can deliver bounds it then).
-template <bool LOWRANK, bool E3M2, bool GELU, int RB, int WV>
+template <bool LOWRANK, bool E3M2, bool GELU, int RB, int WV, bool BOTH>
 __global__ __launch_bounds__(64 * WV, WV == 4 ? 2 : 1)
 void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                      const float* __restrict__ inv_lambda, float rho,
                      const uint4* __restrict__ l1p, int64_t M, int K, int r, int slice,
-                     uint8_t* __restrict__ qx, float* __restrict__ sx, float* __restrict__ h,
+                     uint8_t* __restrict__ qx, uint8_t* __restrict__ nib, float* __restrict__ sx, float* __restrict__ h,
                      int row_blocks, const ExpandJob expand) {
+    static_assert(E3M2 || !BOTH, "nibbles are what the pass writes without E3M2");
     if constexpr (E3M2) {
         if ((int)blockIdx.x >= row_blocks) {
             const int id = ((int)blockIdx.x - row_blocks) * (int)gridDim.y + (int)blockIdx.y;
@@ -149,7 +152,8 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
             for (int b = 0; b < RB; ++b) {
                 LaneCodes<E3M2> codes;
                 float s;
-                quantize_rows<E3M2>(xc[b], il_lds, rho, codes, s);
+                uint4 nibbles;
+                quantize_rows<E3M2, BOTH>(xc[b], il_lds, rho, codes, s, &nibbles);
                 // group-major outputs: the 32 rows of this block are 1 KB of codes and 128 B of scales, contiguous
                 if (rows[b] < M) {
                     if constexpr (E3M2) {
@@ -157,6 +161,7 @@ void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
                         uint8_t* blk = qx + (size_t)g * Mp * E3M2_ROW_BYTES;
                         *reinterpret_cast<uint4*>(blk + (size_t)rows[b] * 32 + hf * 16) = codes.lo;
                         *reinterpret_cast<uint2*>(blk + Mp * 32 + ((size_t)hf * Mp + rows[b]) * 8) = codes.hi;
+                        if constexpr (BOTH) *reinterpret_cast<uint4*>(nib + ((size_t)g * M + rows[b]) * 32 + hf * 16) = nibbles;
                         if (hf == 0) {
                             const uint32_t p = split_bf16(s);
                             *reinterpret_cast<uint2*>(blk + Mp * 48 + (size_t)rows[b] * 8) = uint2{p, p};
@@ -249,10 +254,10 @@ hipError_t launch_scale_chain(const float* a, float rho, int64_t n, float* s, fl
     return hipGetLastError();
 }
 
-template <bool E3M2, bool GELU, int RB, int WV>
+template <bool E3M2, bool GELU, int RB, int WV, bool BOTH>
 static hipError_t launch_quantize_geom(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                        const void* l1p, int64_t M, int K, int r,
-                                       uint8_t* qx, float* sx, float* h, int slices, const ExpandJob& expand, hipStream_t stream) {
+                                       uint8_t* qx, uint8_t* nib, float* sx, float* h, int slices, const ExpandJob& expand, hipStream_t stream) {
     const int slice = (K / 64 + slices - 1) / slices;                      // groups per slice
     const unsigned row_blocks = (unsigned)((M + 32 * RB - 1) / (32 * RB)), ny = (unsigned)((K / 64 + slice - 1) / slice);
     const unsigned expand_blocks = expand.out ? (unsigned)((expand_waves(expand.N, K) + WV - 1) / WV) : 0;
@@ -260,34 +265,35 @@ static hipError_t launch_quantize_geom(const void* x, int64_t ldx, const float* 
     const size_t hpart = l1p ? (size_t)WV * 32 * RB * 32 * sizeof(float) : 0;
     const size_t il = (size_t)slice * 64 * sizeof(float), lds = (il > hpart) ? il : hpart;
     if (l1p)
-        hipLaunchKernelGGL((quantize_kernel<true, E3M2, GELU, RB, WV>), blocks, dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, slice, qx, sx, h, (int)row_blocks, expand);
+        hipLaunchKernelGGL((quantize_kernel<true, E3M2, GELU, RB, WV, BOTH>), blocks, dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, slice, qx, nib, sx, h, (int)row_blocks, expand);
     else
-        hipLaunchKernelGGL((quantize_kernel<false, E3M2, GELU, RB, WV>), blocks, dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, slice, qx, sx, h, (int)row_blocks, expand);
+        hipLaunchKernelGGL((quantize_kernel<false, E3M2, GELU, RB, WV, BOTH>), blocks, dim3(64 * WV), lds, stream,
+                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, slice, qx, nib, sx, h, (int)row_blocks, expand);
     return hipGetLastError();
 }
 
-template <bool E3M2, bool GELU>
+template <bool E3M2, bool GELU, bool BOTH = false>
 static hipError_t launch_quantize_any(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                       const void* l1p, int64_t M, int K, int r,
-                                      uint8_t* qx, float* sx, float* h, int slices, const ExpandJob& expand, hipStream_t stream) {
-    auto go = slices == 1 && quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_geom<E3M2, GELU, 2, 4> : launch_quantize_geom<E3M2, GELU, 1, 8>;
-    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, expand, stream);
+                                      uint8_t* qx, uint8_t* nib, float* sx, float* h, int slices, const ExpandJob& expand, hipStream_t stream) {
+    auto go = slices == 1 && quant_geom(M) == QuantGeom::R64W4 ? launch_quantize_geom<E3M2, GELU, 2, 4, BOTH> : launch_quantize_geom<E3M2, GELU, 1, 8, BOTH>;
+    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, nib, sx, h, slices, expand, stream);
 }
 
 hipError_t launch_quantize(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                            const void* l1p, int64_t M, int K, int r,
                            uint8_t* qx, float* sx, float* h, bool gelu, hipStream_t stream, int slices) {
-    return gelu ? launch_quantize_any<false, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, ExpandJob{}, stream)
-                : launch_quantize_any<false, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, sx, h, slices, ExpandJob{}, stream);
+    auto go = gelu ? launch_quantize_any<false, true> : launch_quantize_any<false, false>;
+    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, qx, nullptr, sx, h, slices, ExpandJob{}, stream);
 }
 
 hipError_t launch_quantize_e3m2(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                                 const void* l1p, int64_t M, int K, int r,
-                                uint8_t* act, float* sx, float* h, bool gelu, hipStream_t stream, int slices, const ExpandJob& expand) {
-    return gelu ? launch_quantize_any<true, true>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, slices, expand, stream)
-                : launch_quantize_any<true, false>(x, ldx, inv_lambda, rho, l1p, M, K, r, act, sx, h, slices, expand, stream);
+                                uint8_t* act, uint8_t* nib, float* sx, float* h, bool gelu, hipStream_t stream, int slices, const ExpandJob& expand) {
+    auto go = gelu ? (nib ? launch_quantize_any<true, true, true> : launch_quantize_any<true, true>)
+                   : (nib ? launch_quantize_any<true, false, true> : launch_quantize_any<true, false>);
+    return go(x, ldx, inv_lambda, rho, l1p, M, K, r, act, nib, sx, h, slices, expand, stream);
 }
 
 // Test hook: the activation alone, through the device function the quantise kernels use.

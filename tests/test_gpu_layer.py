@@ -54,12 +54,11 @@ def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
     if mx:
         gq, gs = svdq.mx_to_token_major(qx, sx, K)
         assert np.array_equal(gs.cpu().numpy(), os_)
-    elif container == "nibble" and (M, N) not in ((15361, 128), (1025, 2048), (2049, 4096)):      # those run as E3M2 fields
+    elif container == "nibble":                  # with many tokens too, where the GEMM takes E3M2 fields
         gq, gs = svdq.to_token_major(qx, sx)
         assert np.array_equal(gs.cpu().numpy().view(np.uint32), os_.view(np.uint32))
     else:
-        buf = lin._work[0] if container == "nibble" else qx.buf
-        codes, _ = unpack_act_e3m2_np(buf.cpu().numpy(), M, K)
+        codes, _ = unpack_act_e3m2_np(qx.buf.cpu().numpy(), M, K)
         assert np.array_equal(codes, synth.unpack_int4(oq))
         gq = None
     if gq is not None:
@@ -131,3 +130,23 @@ def test_layer_follows_its_tensors_and_copies(svdq):
     assert y2.data_ptr() != lin.buffers(40, y.device)[3].data_ptr()
     assert torch.all((y2.float() - 64.0 - y.float()).abs() <= 0.5 + y.float().abs() * 2.0 ** -7)
     assert torch.equal(lin.forward(dev(x), 0.8), y)
+
+
+@pytest.mark.parametrize("M", [40, 900])
+def test_nibble_layer_keeps_its_form_and_no_staging(svdq, M):
+    """The nibble container holds 4-bit activations and weights whatever its forward() multiplies: quantize()'s operands
+    outlive a forward(), and what forward() expands into is given back (few tokens expand nothing)."""
+    K, N = 1024, 2560
+    x, _ = synth.make_x(3, M, K, outlier_count=3, outlier_scale=30.0)
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(x)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(5, K, N, 16, cm)
+    lin = svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1), dev(L.L2), dev(L.qw), dev(L.sw), dev(L.bias), container="nibble")
+    q = lin.quantize(dev(x), 0.8)
+    codes, scales = q[0].clone(), q[1].clone()
+    want = lin.gemm(*q).clone()
+    before = torch.cuda.memory_allocated()
+    y = lin.forward(dev(x), 0.8)
+    assert torch.cuda.memory_allocated() - before <= 1024        # no more than the input's own rounding
+    assert torch.equal(q[0], codes) and torch.equal(q[1], scales)
+    assert rel_fro(y.double().cpu().numpy(), want.double().cpu().numpy()) <= 2e-3
+    assert rel_fro(lin.gemm(*q).double().cpu().numpy(), want.double().cpu().numpy()) <= 2e-3     # h summed in another order
