@@ -262,7 +262,7 @@ int svdq_debug_gelu(const void* x_bf16, int64_t n, void* out_bf16, void* stream)
  * svdq_layer_forward: x, ldx, rho, M as svdq_quantize_act, gelu != 0 as svdq_quantize_act_gelu;
  *   codes           svdq_layer_codes_bytes(layer, M) bytes, 16-byte aligned, scales the format's scale buffer (unused, may
  *                   be NULL for SVDQ_FMT_INT4_E3M2): receive what the format's own quantise call writes there
- *   h               [M, r] binary32; holds intermediate values, not necessarily h, afterwards
+ *   h               [M, r] binary32; receives h
  *   scratch         svdq_layer_scratch_bytes(layer, M) bytes, 16-byte aligned, or NULL (slower with few tokens)
  *   staging         svdq_layer_staging_bytes(layer, M) bytes, 16-byte aligned: room for the expanded weights of one
  *                   GEMM (0 bytes if they are resident or M is small: NULL then), and for SVDQ_FMT_INT4, which runs as

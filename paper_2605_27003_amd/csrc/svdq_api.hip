@@ -429,10 +429,10 @@ static svdq::ExpandJob layer_expand_job(const svdq_layer* L, void* staging) {
     return L->w_packed ? svdq::expand_packed_job(L->w_packed, L->N, L->K, staging) : svdq::expand_canonical_job(L->qw, L->sw, L->N, staging);
 }
 
-// The GEMM on checked arguments.  h: `slices` partial h's for the few-token kernel, one otherwise.  fields: codes are
-// E3M2 fields whatever the format.  expanded: staging holds the layer's weights already.
-static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool fields, bool expanded, const float* h, int slices, int64_t M,
-                      void* staging, void* y, int64_t ldy, hipStream_t stream) {
+// The GEMM on checked arguments.  h: `slices` partial h's for the few-token kernel, whose sum goes to hsum; one otherwise.
+// fields: codes are E3M2 fields whatever the format.  expanded: staging holds the layer's weights already.
+static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool fields, bool expanded, const float* h, int slices, float* hsum,
+                      int64_t M, void* staging, void* y, int64_t ldy, hipStream_t stream) {
     const int N = L->N, K = L->K, r = L->r;
     const uint8_t* wp = (const uint8_t*)L->w_packed;
     if (small_path(L, M)) {
@@ -452,7 +452,7 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
             w1 = wp + svdq::packed_e3m2_w0_bytes(N, K);
             w2 = (const uint8_t*)w1 + svdq::packed_e3m2_w1_bytes(N, K);
         }
-        return hip_status(svdq::launch_small_gemm(source, codes, scales, w0, w1, w2, h, slices, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
+        return hip_status(svdq::launch_small_gemm(source, codes, scales, w0, w1, w2, h, slices, slices > 1 ? hsum : nullptr, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
     }
     if (L->format == SVDQ_FMT_MXFP4) {
         const int64_t main = svdq::mx_main_rows(M, N, K);
@@ -460,7 +460,7 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
         if (e != hipSuccess || main == M) return hip_status(e);
         if (!svdq::small_shape(M - main, N) || !svdq::small_reach(M, N, K))
             return hip_status(svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, main, M, N, K, r, y, ldy, 0, stream));
-        return hip_status(svdq::launch_small_gemm(svdq::SMALL_MXFP4, codes, scales, wp, wp + svdq::packed_mx_codes_bytes(N, K), nullptr, h, 1,
+        return hip_status(svdq::launch_small_gemm(svdq::SMALL_MXFP4, codes, scales, wp, wp + svdq::packed_mx_codes_bytes(N, K), nullptr, h, 1, nullptr,
                                                   L->L2_bf16, L->bias, M, main, N, K, r, y, ldy, stream));
     }
     if (L->format == SVDQ_FMT_INT4 && !fields)
@@ -488,7 +488,7 @@ int svdq_layer_gemm(const svdq_layer* L, const void* codes, const void* scales, 
     if (!L->w_packed && !small_path(L, M) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
-    return layer_gemm(L, (const uint8_t*)codes, scales, false, false, h, 1, M, staging, y, ldy, (hipStream_t)stream);
+    return layer_gemm(L, (const uint8_t*)codes, scales, false, false, h, 1, nullptr, M, staging, y, ldy, (hipStream_t)stream);
 }
 
 int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, float rho, int gelu, int64_t M,
@@ -526,7 +526,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
         hin = h;
         slices = 1;
     }
-    return layer_gemm(L, act, scales, fields, expand, r ? hin : nullptr, r ? slices : 1, M, staging, y, ldy, stream);
+    return layer_gemm(L, act, scales, fields, expand, r ? hin : nullptr, r ? slices : 1, h, M, staging, y, ldy, stream);
 }
 
 size_t svdq_gptq_workspace_bytes(int N, int K) {

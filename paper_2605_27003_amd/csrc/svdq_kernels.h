@@ -80,9 +80,9 @@ inline int small_shape(int64_t M, int N, bool mxfp4 = true) {
 }
 // The few-token GEMM addresses codes and weights with 32-bit byte offsets (its tokens may be the last of many).
 inline bool small_reach(int64_t M, int64_t N, int64_t K) { return (M > N ? M : N) * K < (int64_t)1 << 32; }
-// tokens [begin, M)
+// tokens [begin, M).  hsum: receives the sum of the partial h's (null: not wanted)
 hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1, const void* w2,
-                             const float* h, int slices, const void* L2, const float* bias, int64_t M, int64_t begin, int N, int K, int r,
+                             const float* h, int slices, float* hsum, const void* L2, const float* bias, int64_t M, int64_t begin, int N, int K, int r,
                              void* y, int64_t ldy, hipStream_t stream);
 hipError_t launch_sum_slices(const float* part, int slices, int64_t M, int r, float* h, hipStream_t stream);
 

@@ -64,6 +64,8 @@ def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
     if gq is not None:
         assert np.array_equal(gq.cpu().numpy(), oq)
     oh = oracle.lowrank_down(xa, L.inv_lambda, L.L1) if r else None
+    if r:                                        # the operands are whole (the bar of the quantise pass alone): gemm() on them gives the layer again
+        assert rel_fro(lin.buffers(M, y.device)[2].double().cpu().numpy(), np.asarray(oh, np.float64)) <= 3e-5
     orc = (oracle.linear_mxfp4 if mx else oracle.linear)(oq, os_, L.qw, L.sw, oh, L.L2 if r else None, L.bias)
     got, want = synth.bf16_bits_to_f32(host_bits(y)).astype(np.float64), orc["y64"]
     assert rel_fro(got, want) <= 2e-3
