@@ -1,0 +1,87 @@
+// Which tiles an MXFP4 launch takes, and whether its last tokens get a launch of their own (host only).  All tiles give
+// the same bits: the order of operations per output is the same.
+#pragma once
+#include <cstdint>
+
+#include "svdq_kernels.h"
+#include "svdq_tiles.h"
+
+namespace svdq {
+
+enum class MxTile { T256x256, T256x128, T128x128 };
+struct MxPart {                  // tiles of a launch and its estimated cost, us
+    MxTile tile;
+    double cost;
+};
+
+// The tile-walking kernel needs full 256-channel tiles, a K loop of at least five stages (two more than its ring), and
+// pays once every one of its `walkers` blocks has at least two tiles.
+inline bool mx_walks(int mtiles, int N, int K, int walkers) {
+    return N % 256 == 0 && K >= 576 && (int64_t)mtiles * (N / 256) >= 2 * (int64_t)walkers;
+}
+
+// Cheapest tile for `rows` tokens.  A launch takes what its busiest XCD takes: whole blocks per CU (with several blocks on a
+// CU sharing it), or, where every CU of it is busy throughout and the clock falls, its tiles at a lower rate; with 40 % of
+// the CUs idle the clock rises.  A block takes its start and end and then its share of K.  Measured for K = 512, 1024, 2048,
+// 5120, 13824 and eighteen shapes, us a block with k = K / 5120 (and the factors on a full chip, and of k on an idle one):
+//   128 x 128   1.8 + 11.5 k (1.07, 1)     four waves, three blocks fit a CU
+//   256 x 128   4.4 + 17.3 k (1.03, 0.87)  four waves, two blocks; 15 % more for many tokens where XCDs own channels and each reads all of them
+//   256 x 256   10 + 28 k (1.15, 0.87)     eight waves, one block; 6 + 31 k as one block per CU that walks its tiles (9 + 29 k where XCDs own channels)
+// Per element the large tiles are a quarter cheaper at K = 5120, but M = 768, N = 5120 is 60 of them on 256 CUs (34 us
+// against 18 with 240 tiles of 128 x 128), and with a short K loop their starts and ends cost more than that: M = 9000,
+// N = 5120 takes 54 us on 256 x 256, 47 on 256 x 128 and 38 on 128 x 128 at K = 512, and 148, 165 and 147 at K = 5120.
+inline MxPart mx_best(int64_t rows, int N, int K, int walkers) {
+    const double k = K / 5120.0;
+    auto cost = [&](int bm, int bn, double fixed, double ends, double loop, double full, double idle) {
+        const int n = busiest_xcd((int)((rows + bm - 1) / bm), N / bn);
+        if (5 * n <= 3 * CUS_PER_XCD) return fixed + ends + idle * loop * k;
+        const double whole = (n + CUS_PER_XCD - 1) / CUS_PER_XCD, rate = full * n / CUS_PER_XCD;
+        return fixed + (ends + loop * k) * (whole > rate ? whole : rate);
+    };
+    const int m256 = (int)((rows + 255) / 256);
+    MxPart best{MxTile::T128x128, cost(128, 128, 5.0, 1.8, 11.5, 1.07, 1.0)};
+    const double wide = (rows > 6144 && make_tile_grid(m256, N / 128).nmajor) ? 1.15 : 1.0;
+    const double c2 = cost(256, 128, 4.0, wide * 4.4, wide * 17.3, 1.03, 0.87);
+    if (c2 < best.cost) best = MxPart{MxTile::T256x128, c2};
+    if (N % 256 == 0) {
+        const bool walks = mx_walks(m256, N, K, walkers), nmajor = make_tile_grid(m256, N / 256).nmajor;
+        const double c1 = !walks ? cost(256, 256, 1.5, 10.0, 28.0, 1.15, 0.87) : nmajor ? cost(256, 256, 1.5, 9.0, 29.0, 1.15, 0.87)
+                                                                                        : cost(256, 256, 1.5, 6.0, 31.0, 1.15, 0.87);
+        if (c1 <= best.cost) best = MxPart{MxTile::T256x256, c1};
+    }
+    return best;
+}
+
+// The few-token kernel (svdq_small.hip) on `rows` tokens
+inline double mx_few_cost(int64_t rows, int N, int K) {
+    return 5.0 + (0.006 + 0.019 * (K / 5120.0)) * (double)((rows + 63) / 64) * (double)((N + 63) / 64);
+}
+
+// Tokens of the first launch (a multiple of 256, or all of them): leaving the last tokens to a launch of their own on
+// smaller tiles pays where they would open another round of blocks for themselves (M = 2305, N = 13824: 70 tiles of
+// 256 x 256 on the busiest XCD's 32 CUs, 63 without the one row beyond 2304) and that round is longer than a launch, which
+// takes about 2 us at any K.  `tail_cost`: what a launch for the rest costs, in the unit of mx_best.
+template <class TailCost>
+int64_t mx_split(int64_t M, int N, int K, int walkers, TailCost tail_cost) {
+    const int mtiles = (int)((M + 255) / 256);
+    double best = mx_best(M, N, K, walkers).cost;
+    int64_t rows = M;
+    for (int mt = mtiles - 1; mt >= 1 && mt >= mtiles - 12; --mt) {
+        const double c = mx_best((int64_t)mt * 256, N, K, walkers).cost + tail_cost(M - (int64_t)mt * 256) + 2.0;
+        if (c < 0.985 * best) {
+            best = c;
+            rows = (int64_t)mt * 256;
+        }
+    }
+    return rows;
+}
+
+// Tokens of a layer that are best left to the tile kernels; the rest take the few-token kernel or smaller tiles.
+inline int64_t mx_layer_split(int64_t M, int N, int K, int walkers) {
+    return mx_split(M, N, K, walkers, [&](int64_t rest) {
+        const double few = mx_few_cost(rest, N, K), tiles = mx_best(rest, N, K, walkers).cost;
+        return small_shape(rest, N) && small_reach(M, N, K) && few < tiles ? few : tiles;
+    });
+}
+
+}  // namespace svdq

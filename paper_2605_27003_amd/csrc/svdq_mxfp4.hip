@@ -24,6 +24,7 @@
 #include "svdq_epilogue.h"
 #include "svdq_kernels.h"
 #include "svdq_lds.h"
+#include "svdq_mx_plan.h"
 #include "svdq_quant_dev.h"
 #include "svdq_tiles.h"
 
@@ -1042,65 +1043,10 @@ static int cu_count() {
 }
 
 // the tile-walking kernel runs one block per CU (a multiple of 8 blocks, so that a block stays on one XCD's share of
-// the tile order); it needs full 256-channel tiles, a K loop of at least five stages (two more than its ring), and
-// pays once every block has at least two tiles
+// the tile order)
 static inline int walking_blocks() { return cu_count() / 8 * 8; }
-static inline bool walks_tiles(int mtiles, int N, int K) {
-    return N % 256 == 0 && K >= 576 && (int64_t)mtiles * (N / 256) >= 2 * walking_blocks();
-}
 
-// ---- which tiles a launch takes.  All of them give the same bits: the order of operations per output is the same.
-enum class MxTile { T256x256, T256x128, T128x128 };
-struct MxPart {                  // token tiles of 256 [first, first + count) on tiles `tile`, estimated cost
-    MxTile tile;
-    double cost;
-};
-
-// Cheapest tile for `rows` tokens.  A launch takes what its busiest XCD takes, in whole blocks per CU c (with several
-// blocks on a CU sharing it): measured at K = 5120, 5 + 13.3 c us for 128 x 128 tiles (four waves, three blocks fit a CU),
-// 4 + 21.7 c for 256 x 128 (four waves, two blocks), 1.5 + 38 c for 256 x 256 (eight waves, one block; as one block per
-// CU that walks its tiles 37 c).  Per element the large tiles are a quarter cheaper, but M = 768, N = 5120 is 60 of them
-// on 256 CUs: 34 us against 19 with 240 tiles of 128 x 128.
-static MxPart mx_best(int64_t rows, int N, int K) {
-    auto blocks = [&](int bm, int bn) {
-        return (double)((busiest_xcd((int)((rows + bm - 1) / bm), N / bn) + CUS_PER_XCD - 1) / CUS_PER_XCD);
-    };
-    MxPart best{MxTile::T128x128, 5.0 + 13.3 * blocks(128, 128)};
-    const double c2 = 4.0 + 21.7 * blocks(256, 128);
-    if (c2 < best.cost) best = MxPart{MxTile::T256x128, c2};
-    if (N % 256 == 0) {
-        const double c1 = 1.5 + (walks_tiles((int)((rows + 255) / 256), N, K) ? 37.0 : 38.0) * blocks(256, 256);
-        if (c1 <= best.cost) best = MxPart{MxTile::T256x256, c1};
-    }
-    return best;
-}
-
-// Tokens of the first launch (a multiple of 256, or all of them): leaving the last tokens to a launch of their own on
-// smaller tiles pays where they would open another round of blocks for themselves (M = 2305, N = 13824: 70 tiles of
-// 256 x 256 on the busiest XCD's 32 CUs, 63 without the one row beyond 2304).  `tail_cost`: what a launch for the rest
-// costs, in the unit of mx_best.
-template <class TailCost>
-static int64_t mx_split(int64_t M, int N, int K, TailCost tail_cost) {
-    const int mtiles = (int)((M + 255) / 256);
-    double best = mx_best(M, N, K).cost;
-    int64_t rows = M;
-    for (int mt = mtiles - 1; mt >= 1 && mt >= mtiles - 12; --mt) {
-        const double c = mx_best((int64_t)mt * 256, N, K).cost + tail_cost(M - (int64_t)mt * 256) + 3.0;      // a launch more
-        if (c < 0.97 * best) {
-            best = c;
-            rows = (int64_t)mt * 256;
-        }
-    }
-    return rows;
-}
-
-int64_t mx_main_rows(int64_t M, int N, int K) {
-    return mx_split(M, N, K, [&](int64_t rest) {
-        const double few = 5.0 + 0.025 * (double)((rest + 63) / 64) * (double)((N + 63) / 64);                   // the few-token kernel
-        const double tiles = mx_best(rest, N, K).cost;
-        return small_shape(rest, N) && small_reach(M, N, K) && few < tiles ? few : tiles;
-    });
-}
+int64_t mx_main_rows(int64_t M, int N, int K) { return mx_layer_split(M, N, K, walking_blocks()); }
 
 // The tiles of tokens [begin, end), begin a multiple of 256.
 static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
@@ -1117,12 +1063,13 @@ static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const v
                            qx, (const uint16_t*)sxe, (const uint4*)base, wsc, h, (const uint16_t*)L2, bias,
                            M, N, K, r, y, ldy, out_f32, tg, MxNext{});
     };
-    const MxTile tile = mx_best(rows, N, K).tile;
-    if (tile == MxTile::T256x256 && walks_tiles((int)((rows + 255) / 256), N, K)) {
+    const int walkers = walking_blocks();
+    const MxTile tile = mx_best(rows, N, K, walkers).tile;
+    if (tile == MxTile::T256x256 && mx_walks((int)((rows + 255) / 256), N, K, walkers)) {
         // one block per CU walking its tiles.  Without a low-rank branch the kernel's h transfers still run (they have no
         // branch): give them the codes to read
         const float* hrows = (r > 0) ? h : (const float*)qx;
-        hipLaunchKernelGGL((gemm_mx_persistent_kernel<4>), dim3((unsigned)walking_blocks()), dim3(512), 0, stream,
+        hipLaunchKernelGGL((gemm_mx_persistent_kernel<4>), dim3((unsigned)walkers), dim3(512), 0, stream,
                            qx, (const uint16_t*)sxe, (const uint4*)base, wsc, hrows, (const uint16_t*)L2, bias,
                            M, N, K, r, y, ldy, out_f32, grid(256, 256));
     } else if (tile == MxTile::T256x256) {
@@ -1139,7 +1086,8 @@ hipError_t launch_linear_mx(const uint8_t* qx, const uint8_t* sxe, const void* w
                             const float* h, const void* L2, const float* bias,
                             int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
                             hipStream_t stream) {
-    const int64_t mid = begin + mx_split(end - begin, N, K, [&](int64_t rest) { return mx_best(rest, N, K).cost; });
+    const int walkers = walking_blocks();
+    const int64_t mid = begin + mx_split(end - begin, N, K, walkers, [&](int64_t rest) { return mx_best(rest, N, K, walkers).cost; });
     hipError_t e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, begin, mid, N, K, r, y, ldy, out_f32, stream);
     if (e == hipSuccess && mid < end) e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, mid, end, N, K, r, y, ldy, out_f32, stream);
     return e;
