@@ -386,7 +386,7 @@ static int layer_check(const svdq_layer* L, int64_t M) {
 }
 
 static bool small_path(const svdq_layer* L, int64_t M) {
-    return svdq::small_shape(M, L->N, L->format == SVDQ_FMT_MXFP4) != 0 && svdq::small_reach(M, L->N, L->K);
+    return svdq::small_shape(M, L->N, L->K, L->format == SVDQ_FMT_MXFP4) != 0 && svdq::small_reach(M, L->N, L->K);
 }
 
 // K slices of the quantise pass: blocks for every CU where the row blocks (32 rows) are few, at least a group for each of a
@@ -458,7 +458,7 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
         const int64_t main = svdq::mx_main_rows(M, N, K);
         const hipError_t e = svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, 0, main, N, K, r, y, ldy, 0, stream);
         if (e != hipSuccess || main == M) return hip_status(e);
-        if (!svdq::small_shape(M - main, N) || !svdq::small_reach(M, N, K))
+        if (!svdq::small_shape(M - main, N, K) || !svdq::small_reach(M, N, K))
             return hip_status(svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, main, M, N, K, r, y, ldy, 0, stream));
         return hip_status(svdq::launch_small_gemm(svdq::SMALL_MXFP4, codes, scales, wp, wp + svdq::packed_mx_codes_bytes(N, K), nullptr, h, 1, nullptr,
                                                   L->L2_bf16, L->bias, M, main, N, K, r, y, ldy, stream));

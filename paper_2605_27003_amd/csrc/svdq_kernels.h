@@ -69,14 +69,17 @@ hipError_t launch_unpack_act_e3m2(const uint8_t* act, int64_t M, int K, uint8_t*
 enum { SMALL_E3M2_CANONICAL = 0, SMALL_E3M2_PACKED = 1, SMALL_NIBBLE = 2, SMALL_MXFP4 = 3 };   // operand sources
 constexpr int SMALL_SLICES = 8;                  // waves of a block = most partial h's the GEMM takes
 // Which tile of the few-token GEMM a layer takes: 1: 32 channels x 32 tokens; 2: 64 x 64 (MXFP4: 32 x 64); 0: none, the
-// tile kernels.  Measured (K = 5120, us): 32 x 32 wins up to two blocks per CU (N = 5120: M <= 64, N = 512: all M up to
-// 1024; MXFP4, which waits for loads only: one); 64 x 64 then wins while its blocks are one round of two per CU (E3M2,
-// N = 5120: M = 384, 30 against 39 of the tile kernel and its weight expansion; M = 512, 43 against 39.  MXFP4: 256, 13
-// against 16; 384, even; N = 13824: 128, even).
-inline int small_shape(int64_t M, int N, bool mxfp4 = true) {
+// tile kernels.  Measured on whole layers, K = 512 .. 13824, N = 512 .. 13824, us against the tile path (whose weights are
+// expanded beside the quantise pass and whose GEMM splits K between two teams).  32 x 32 wins up to two blocks per CU
+// (MXFP4, which waits for loads only: one).  64 x 64 then wins while it is one block per CU (E3M2, K = 5120: N = 512,
+// M = 1536, 27 against 36; M = 2304, 288 blocks, 45 against 40), and up to two where few tokens meet many weights, which the
+// tile path has to expand first (N = 13824, M = 85, 432 blocks: K = 2048 23 against 26, K = 13824 73 against 114; N = 5120,
+// M = 307, even; but K = 512 16 against 15, and N = 2048, M = 960, 42 against 38).  MXFP4 expands nothing and wins up to 320
+// blocks (K = 5120: N = 512, M = 2304, 30 against 35; N = 5120, M = 230, 24 against 26; M = 307, 400 blocks, 29 against 27).
+inline int small_shape(int64_t M, int N, int K, bool mxfp4 = true) {
     const int64_t b32 = ((M + 31) / 32) * (N / 32), b64 = ((M + 63) / 64) * ((N + 63) / 64);
     if (b32 <= (mxfp4 ? 256 : 512)) return 1;
-    return b64 <= 480 ? 2 : 0;
+    return b64 <= (mxfp4 ? 320 : (N >= 4096 && K >= 2048) ? 480 : 256) ? 2 : 0;
 }
 // The few-token GEMM addresses codes and weights with 32-bit byte offsets (its tokens may be the last of many).
 inline bool small_reach(int64_t M, int64_t N, int64_t K) { return (M > N ? M : N) * K < (int64_t)1 << 32; }

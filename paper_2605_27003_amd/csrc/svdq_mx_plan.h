@@ -80,7 +80,7 @@ int64_t mx_split(int64_t M, int N, int K, int walkers, TailCost tail_cost) {
 inline int64_t mx_layer_split(int64_t M, int N, int K, int walkers) {
     return mx_split(M, N, K, walkers, [&](int64_t rest) {
         const double few = mx_few_cost(rest, N, K), tiles = mx_best(rest, N, K, walkers).cost;
-        return small_shape(rest, N) && small_reach(M, N, K) && few < tiles ? few : tiles;
+        return small_shape(rest, N, K) && small_reach(M, N, K) && few < tiles ? few : tiles;
     });
 }
 

@@ -323,7 +323,7 @@ hipError_t launch_src(const SmallArgs& a, hipStream_t stream) {
     auto go = [&](auto kern, int ni, int mt) {
         hipLaunchKernelGGL(kern, dim3((unsigned)(a.N / (32 * ni)), (unsigned)((a.M - a.begin + 32 * mt - 1) / (32 * mt)) + (a.hsum ? 1u : 0u)), dim3(64 * WV), 0, stream, a);
     };
-    if (small_shape(a.M - a.begin, a.N, SRC == SMALL_MXFP4) == 1) go(small_gemm_kernel<SRC, 1, 1>, 1, 1);
+    if (small_shape(a.M - a.begin, a.N, a.K, SRC == SMALL_MXFP4) == 1) go(small_gemm_kernel<SRC, 1, 1>, 1, 1);
     else if constexpr (SRC == SMALL_MXFP4) go(small_gemm_kernel<SRC, 1, 2>, 1, 2);
     else go(small_gemm_kernel<SRC, 2, 2>, 2, 2);
     return hipGetLastError();

@@ -30,7 +30,10 @@ SHAPES = [  # M, K, N, r, gelu
     (65, 2112, 384, 16, False),                   # K split in the quantise pass, odd group count
     (1030, 1024, 640, 32, False),                 # 64 x 64 tiles (MXFP4: 32 x 64), ragged
     (4096, 64, 128, 16, False), (4097, 64, 128, 16, False),     # last of the 32 x 32 tiles and the next
-    (15360, 64, 128, 0, False), (15361, 64, 128, 32, False),    # last of the 64 x 64 tiles and the next
+    (15360, 64, 128, 0, False), (15361, 64, 128, 32, False),
+    (8192, 64, 128, 16, False), (8193, 64, 128, 16, False),     # int4: last of the 64 x 64 tiles with few weights and the next
+    (448, 2048, 4096, 32, False), (449, 2048, 4096, 16, False),   # and with many
+    (10240, 64, 128, 32, False), (10241, 64, 128, 16, False),   # MXFP4: last of the 32 x 64 tiles and the next
     (1025, 2112, 2048, 32, False),                # E3M2: K in halves, odd group count; MXFP4: 128 x 128 tiles
     (2049, 192, 4096, 16, True),                  # MXFP4: the last token in a launch of its own
 ]
