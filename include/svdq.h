@@ -304,9 +304,10 @@ int svdq_layer_gemm(const svdq_layer* layer, const void* codes, const void* scal
  *   svdq_gptq_quantize: R [K, N] binary32 residual (row k = input channel), H as above (not modified),
  *                       workspace of svdq_gptq_workspace_bytes(N, K) bytes (16-byte aligned, device);
  *                       out qw [N, K/2] packed codes and sw [K/64, N] binary32 scales: the canonical weight form
- *                       that svdq_pack_weight and svdq_pack_weight_e3m2 take.  K % 64 == 0.  The pivots are taken
- *                       in panels of 64 (same rounded operations per element in the same order, so the result
- *                       does not depend on it); enqueues about 5 * K small kernels on `stream`.
+ *                       that svdq_pack_weight and svdq_pack_weight_e3m2 take.  K % 64 == 0.  An update of the
+ *                       elimination is one fused multiply-subtract, rounded once, per element and pivot, in pivot
+ *                       order; the pivots are taken in panels of 64, on which the result does not depend.  Enqueues
+ *                       4 * K / 64 kernels and a few more on `stream`.
  */
 size_t svdq_gptq_workspace_bytes(int N, int K);
 int svdq_gptq_hessian(const void* x_bf16, int64_t ldx, const float* inv_lambda, int64_t M, int K, double* H, void* stream);

@@ -45,12 +45,22 @@ def lib():
         L.svdq_oracle_f32_to_bf16.restype = ctypes.c_uint16
         L.svdq_oracle_f32_to_bf16.argtypes = [ctypes.c_float]
         L.svdq_oracle_hw_threads.restype = ctypes.c_int
+        L.svdq_oracle_fms_outer.restype = None
         _lib = L
     return _lib
 
 
 def hw_threads():
     return int(lib().svdq_oracle_hw_threads())
+
+
+def fms_outer(A, col, row):
+    """A -= col row^T in place, one fused multiply-subtract per element.  A [na, nb] binary64, rows contiguous."""
+    assert A.dtype == np.float64 and A.strides[1] == 8
+    col, row = np.ascontiguousarray(col, np.float64), np.ascontiguousarray(row, np.float64)
+    assert A.shape == (col.size, row.size)
+    lib().svdq_oracle_fms_outer(_p(A, ctypes.c_double), ctypes.c_int64(A.strides[0] // 8), _p(col, ctypes.c_double),
+                                _p(row, ctypes.c_double), ctypes.c_int64(col.size), ctypes.c_int64(row.size))
 
 
 def bf16_to_f32(v):

@@ -26,13 +26,25 @@ def _unpack_int4(q):
 # proportion to the inverse Hessian of the layer-wise objective ||X^ (R - R^)||^2, H = X^T X^ (+ damping), from
 # which the visited index is then eliminated.  The published implementation factors H^-1 once (Cholesky) and
 # reads the same numbers off the factor; the elimination form below is the definition it is derived from.
+#
+# The updates of the elimination are fused multiply-subtracts: one rounding per element and pivot.  fused = False rounds
+# the product first.  The two agree to rounding and usually in every code and scale, but a weight that falls on a rounding
+# boundary in one of them changes all that come after it.
+def _subtract_outer(A, col, row, fused):
+    if fused:
+        from . import fms_outer
+        fms_outer(A, col, row)
+    else:
+        A -= col[:, None] * row[None, :]
+
+
 def gptq_hessian(x_bf16, inv_lambda):
     """H = X^T X^ in binary64, X^ = x * inv_lambda in binary32 (eq. 5)."""
     xs = (_bf16_bits_to_f32(x_bf16) * np.asarray(inv_lambda, np.float32)[None, :]).astype(np.float64)
     return xs.T @ xs
 
 
-def gptq_invert(H):
+def gptq_invert(H, fused=True):
     """In-place Gauss-Jordan inverse without pivoting (H is symmetric positive definite after damping): step p
     divides row p by the pivot, subtracts multiples of it from every other row, and rewrites column p."""
     A = np.array(H, dtype=np.float64)
@@ -41,14 +53,14 @@ def gptq_invert(H):
         d = A[p, p]
         col = A[:, p].copy()
         row = A[p] / d                                   # one division per element
-        A -= col[:, None] * row[None, :]                 # one product, one subtraction per element
+        _subtract_outer(A, col, row, fused)
         A[p] = row
         A[:, p] = -col / d
         A[p, p] = 1.0 / d
     return A
 
 
-def gptq_quantize(R, H, damp=0.01):
+def gptq_quantize(R, H, damp=0.01, fused=True):
     """R [K,N] float32 residual, H [K,K] float64 -> (qw [N,K/2] packed codes, sw [K/64,N] float32 scales).
 
     Damping: H + damp * mean(diag H) * I; a channel k that no calibration token excites (H[k,k] == 0) gets
@@ -65,7 +77,7 @@ def gptq_quantize(R, H, damp=0.01):
     for v in np.diag(Hd):                               # summed in index order, so that it can be repeated exactly
         acc += float(v)
     Hd[np.arange(K), np.arange(K)] += damp * (acc / K)
-    Hinv = gptq_invert(Hd)
+    Hinv = gptq_invert(Hd, fused)
     codes = np.zeros((K, N), np.int8)
     sw = np.zeros((K // 64, N), np.float32)
     s = np.zeros(N, np.float32)
@@ -81,8 +93,8 @@ def gptq_quantize(R, H, damp=0.01):
         d = Hinv[i, i]
         err = (w - q.astype(np.float64) * s.astype(np.float64)) / d
         if i + 1 < K:
-            W[i + 1:] -= Hinv[i, i + 1:, None] * err[None, :]
-            Hinv[i + 1:, i + 1:] -= Hinv[i + 1:, i, None] * (Hinv[i, None, i + 1:] / d)
+            _subtract_outer(W[i + 1:], Hinv[i, i + 1:], err, fused)
+            _subtract_outer(Hinv[i + 1:, i + 1:], Hinv[i + 1:, i].copy(), Hinv[i, i + 1:] / d, fused)
     u = (np.ascontiguousarray(codes.T) & 0xF).astype(np.uint8)
     return (u[:, 0::2] | (u[:, 1::2] << 4)).astype(np.uint8), sw
 

@@ -72,6 +72,11 @@ int svdq_oracle_hw_threads(void) {
     return n ? (int)n : 1;
 }
 
+void svdq_oracle_fms_outer(double* A, int64_t lda, const double* col, const double* row, int64_t na, int64_t nb) {
+    for (int64_t a = 0; a < na; ++a)
+        for (int64_t b = 0; b < nb; ++b) A[a * lda + b] = std::fma(-col[a], row[b], A[a * lda + b]);
+}
+
 int svdq_oracle_quantize_act(const uint16_t* x, int64_t ldx, const float* inv_lambda,
                              float rho, int64_t M, int K,
                              uint8_t* qx, float* sx, int nthreads) {

@@ -48,6 +48,10 @@ uint16_t svdq_oracle_f32_to_bf16(float v);
 /* Number of threads the row-parallel functions use for nthreads <= 0. */
 int svdq_oracle_hw_threads(void);
 
+/* A[a][b] <- fma(-col[a], row[b], A[a][b]) for a < na, b < nb: one rounding per element (std::fma); rows of A are lda
+ * doubles apart.  For the GPTQ oracle, which is numpy otherwise. */
+void svdq_oracle_fms_outer(double* A, int64_t lda, const double* col, const double* row, int64_t na, int64_t nb);
+
 /*
  * Eq. 5 then eq. 8-9 then eq. 3: smooth, per-token per-group absmax, clipped
  * scale, round-half-to-even int4 codes, pack.

@@ -5,11 +5,13 @@
 // rounded to the int4 grid of its (channel, 64-group) scale and its rounding error is spread over the not yet
 // visited weights of the same channel in proportion to row k of the inverse Hessian of the layer-wise objective
 // ||X^ (R - R^)||^2 (H = X^T X^ plus damping), from which index k is then eliminated.  Everything runs in
-// binary64; every update is one fused multiply-subtract per element and pivot, in pivot order (a CPU reference that
-// rounds the product too gives the same codes and scales), and there are no reductions other than max and one
+// binary64; every update is one fused multiply-subtract per element and pivot, in pivot order, which is the definition
+// that a CPU reference repeats bit for bit (one that rounds the products as well agrees on ordinary Hessians, but at
+// condition numbers of 1e13 scales differ and at 1e15 codes), and there are no reductions other than max and one
 // sequential sum.  The published implementation factors H^-1 once (Cholesky) and reads the same numbers off the
 // factor; this form trades that for elementwise kernels: K^3 updates for the inverse, K^3 / 3 of H^-1 and K^2 N / 2
-// of the weights during the visit, taken in panels of 64 pivots (below) so that the matrices cross HBM once per panel.
+// of the weights during the visit, taken in panels of 64 pivots (below), two at a time, so that the matrices cross HBM
+// once per 128 pivots.
 #include <climits>
 #include <type_traits>
 

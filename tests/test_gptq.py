@@ -91,6 +91,30 @@ def test_dead_channel_and_damping():
     assert not synth.unpack_int4(qw)[:, 7].any()                     # the unexcited input channel carries no weight
 
 
+def nearly_singular_hessian(seed, K, N, noise):
+    """Eight directions and a little noise, not damped: condition number about noise^-2 K, where rounding shows."""
+    g = np.random.default_rng(seed)
+    X = g.standard_normal((4 * K, 8)) @ g.standard_normal((8, K)) + noise * g.standard_normal((4 * K, K))
+    return X.T @ X, (g.standard_normal((K, N)) * 0.02).astype(np.float32)
+
+
+def test_fused_updates_are_part_of_the_definition():
+    """An update rounds once.  With the product rounded first the result is as good, and on ordinary Hessians the same,
+    but not where H is nearly singular: scales differ (condition 1e13), then codes too (1e15)."""
+    _, _, H = correlated_hessian(3, 2000, 256)
+    H2, R = nearly_singular_hessian(0, 256, 64, 1e-5)
+    same = [oracle.gptq_quantize(R, H, 0.01, fused) for fused in (True, False)]
+    assert np.array_equal(same[0][0], same[1][0]) and np.array_equal(same[0][1], same[1][1])
+    one, two = (oracle.gptq_quantize(R, H2, 0.0, fused) for fused in (True, False))
+    assert not np.array_equal(one[1], two[1])
+    o1, o2 = oracle.gptq_objective(R, H2, *one), oracle.gptq_objective(R, H2, *two)
+    assert abs(o1 - o2) <= 1e-3 * o2
+    # one rounding per element: exact operands whose product is not representable
+    A, col, row = np.full((1, 1), 1.0), np.array([1.0 + 2.0 ** -30]), np.array([1.0 + 2.0 ** -30])
+    oracle.fms_outer(A, col, row)
+    assert A[0, 0] == -(2.0 ** -29 + 2.0 ** -60)
+
+
 # ------------------------------------------------------------------------------------------------ GPU
 @pytest.fixture(scope="module")
 def svdq():
@@ -128,6 +152,23 @@ def test_gpu_gptq_bit_exact(svdq, K, N, M):
     if N % 128 == 0:
         wp = svdq.pack_weight_e3m2(qw, sw)
         assert wp.numel() == svdq.packed_weight_e3m2_bytes(N, K)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,N,noise", [(256, 256, 1e-5), (384, 512, 1e-6)])
+def test_gpu_gptq_bit_exact_nearly_singular(svdq, K, N, noise):
+    """Where a reference that rounds the products differs in scales and codes, the GPU has the definition's."""
+    import torch
+
+    from tests.helpers import dev
+    H, R = nearly_singular_hessian(0, K, N, noise)
+    oq, os_ = oracle.gptq_quantize(R, H, 0.0)
+    uq, us = oracle.gptq_quantize(R, H, 0.0, fused=False)
+    assert not np.array_equal(os_, us)
+    qw, sw = svdq.gptq_quantize(dev(R), torch.from_numpy(H).cuda(), 0.0)
+    torch.cuda.synchronize()
+    assert np.array_equal(sw.cpu().numpy().view(np.uint32), os_.view(np.uint32))
+    assert np.array_equal(qw.cpu().numpy(), oq)
 
 
 @pytest.mark.gpu
