@@ -155,3 +155,70 @@ def test_nibble_layer_keeps_its_form_and_no_staging(svdq, M):
     assert torch.equal(q[0], codes) and torch.equal(q[1], scales)
     assert rel_fro(y.double().cpu().numpy(), want.double().cpu().numpy()) <= 2e-3
     assert rel_fro(lin.gemm(*q).double().cpu().numpy(), want.double().cpu().numpy()) <= 2e-3     # h summed in another order
+
+
+def _random_layer(svdq, container, K, N, r, seed=1):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rand = lambda *shape: torch.randn(*shape, generator=g, device="cuda")
+    qw = torch.randint(0, 256, (N, K // 2), generator=g, device="cuda", dtype=torch.uint8)
+    sw = (torch.randint(118, 123, (K // 32, N), generator=g, device="cuda", dtype=torch.uint8) if container == "mxfp4"
+          else rand(K // 64, N).abs() * 0.01 + 0.001)
+    low = ((rand(K, r) * 0.02).bfloat16(), (rand(r, N) * 0.02).bfloat16()) if r else (None, None)
+    return svdq.W4A4Linear(0.5 + rand(K).abs(), *low, qw, sw, rand(N), container=container.split()[0],
+                           resident="packed" if "packed" in container else "w4")
+
+
+# few tokens (32 x 32, 64 x 64); two teams; tile kernels; MXFP4 with a launch for the last token
+FORMS = [(40, 1088, 128, 16), (420, 2112, 4096, 0), (1025, 2112, 2048, 32), (2305, 2048, 6912, 32)]
+
+
+@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble", "mxfp4"])
+@pytest.mark.parametrize("M,K,N,r", FORMS)
+def test_layer_forward_strides_ratios_and_non_finite_rows(svdq, container, M, K, N, r):
+    """Rows of a wider tensor, clipping ratios at the ends of their range, and rows with infinities, NaN, zeros or values whose
+    scales overflow: nothing reaches another row, and those rows are finite and not exactly where they are with the separate
+    calls (the nibble container's multiplies nibbles, which overflows earlier: its finite rows only)."""
+    lin = _random_layer(svdq, container, K, N, r)
+    wide = torch.randn(M, K + 72, generator=torch.Generator(device="cuda").manual_seed(2), device="cuda").bfloat16()
+    x = wide[:, 8:K + 8]
+    for rho in (1.0, 2.0 ** -20, 0.8):
+        y = lin.forward(x.contiguous(), rho).clone()
+        assert torch.equal(lin.forward(x, rho), y)
+        if rho == 1.0:
+            assert torch.isfinite(y).all()
+    bad = x.clone()
+    rows = [1, 5, 9, 13, M - 1]
+    bad[1, 3], bad[5, K - 1], bad[9], bad[13, :64], bad[M - 1, 70] = float("inf"), float("nan"), 0, float("-inf"), 3e38
+    good = torch.ones(M, dtype=torch.bool, device="cuda")
+    good[rows] = False
+    yb = lin.forward(bad, 0.8).clone()
+    assert torch.equal(yb[good], y[good]) and torch.isfinite(yb[9]).all()
+    q = lin.quantize(bad, 0.8)
+    if container == "mxfp4":
+        apart = svdq.linear_mxfp4(q[0], q[1], lin.weights(), N, q[2], lin.L2, lin.bias)
+    elif container == "nibble":
+        apart = svdq.linear_w4a4(q[0], q[1], lin.weights(), N, q[2], lin.L2, lin.bias)
+    else:
+        apart = svdq.linear_w4a4_e3m2(q[0], lin.weights(), N, q[2], lin.L2, lin.bias)
+    if container == "nibble":
+        assert torch.isfinite(yb)[torch.isfinite(apart)].all()
+    else:
+        assert torch.equal(torch.isfinite(yb), torch.isfinite(apart))
+
+
+@pytest.mark.parametrize("M", [40, 900])
+def test_nibble_layers_on_two_streams(svdq, M):
+    """Layers of the nibble container are independent of each other: they share no buffer, whatever stream they run on."""
+    K, N = 1024, 2560
+    lins = [_random_layer(svdq, "nibble", K, N, 16, seed) for seed in (1, 2)]
+    xs = [torch.randn(M, K, generator=torch.Generator(device="cuda").manual_seed(s), device="cuda").bfloat16() for s in (3, 4)]
+    want = [lin.forward(x, 0.8).clone() for lin, x in zip(lins, xs)]
+    streams = [torch.cuda.Stream() for _ in lins]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for lin, x, s in zip(lins, xs, streams):
+            with torch.cuda.stream(s):
+                lin.forward(x, 0.8)
+    torch.cuda.synchronize()
+    for lin, w in zip(lins, want):
+        assert torch.equal(lin.buffers(M, w.device)[3], w)
