@@ -6,7 +6,8 @@ q, k, v, o 5120 x 5120, FFN up 5120 x 13824, FFN down 13824 x 5120; r = 32), i.e
 fused quantise kernel (smooth, absmax, clipped int4 quantise/pack, x^ L1) and six launches of the W4A4 GEMM with
 its fused low-rank/bias/bf16 epilogue, walking the 40-step schedule of the two experts (expert switch at step 20,
 clipping ratio looked up per timestep bin).  The three single-layer configurations at M = 32760 (attention output
-projection, FFN up, FFN down) are timed in the same run and reported as sub-records under "configs".
+projection, FFN up, FFN down) are timed in the same run: their times are in the line, their sub-records in the
+record under "configs".
 
 Every workload is timed in these executions of the layer:
   "e3m2"   int4 codes held as E3M2 fields, exact integer group sums on the FP6 matrix cores (the fast execution);
@@ -14,7 +15,8 @@ Every workload is timed in these executions of the layer:
            inside the timed step ("e3m2_prepacked" = the same with the expanded weights resident instead)
   "int4"   4-bit storage end to end, nibbles unpacked in registers, int8 matrix cores, int32 group accumulators
   "mxfp4"  the paper's own 4-bit format on the block-scaled FP4 matrix instruction
-Inputs are resident in HBM before the timed region.  Prints ONE JSON line.
+Inputs are resident in HBM before the timed region.  Prints ONE JSON line (and the whole record, with all
+sub-records, on stderr).
 """
 import argparse
 import json
@@ -103,6 +105,33 @@ def cpu_baseline(w, rows, seed=7):
             "sample": f"{n} of {w.M} token rows of {w.name}, one step, every linear ({', '.join(names)}) at full N and K "
                       f"(quantize+lowrank {tq:.2f}s, linear {tl:.2f}s)",
             "quantize_GBs": bq / tq / 1e9, "seconds": tq + tl}
+
+
+def short(v):
+    """v with its floats cut to six digits."""
+    if isinstance(v, dict):
+        return {k: short(x) for k, x in v.items()}
+    if isinstance(v, list):
+        return [short(x) for x in v]
+    return float(f"{v:.6g}") if isinstance(v, float) else v
+
+
+def result_line(full):
+    """The result line: the record without its sub-records, of which the times stay (ms per step by execution, the headline's
+    first).  Under 2000 characters, so that it survives a log of which only the end is kept; the whole record goes to stderr."""
+    roofline = lambda r: {k: r[k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic", "avg_ms") if k in r}
+    line = {k: full[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                                 "vs_baseline", "dtype", "data", "config", "weight_bytes_resident", "weight_staging_bytes",
+                                 "weight_expand_ms_per_step", "int8_mfma_kernel_pct_of_int8_peak", "pct_of_int8_peak_equivalent") if k in full}
+    line["roofline"], line["roofline_quantize"] = roofline(full["roofline"]), roofline(full["roofline_quantize"])
+    line["executions_ms"] = {ex: r["ms_per_step"] for ex, r in full.get("executions", {}).items()}
+    if "cpu_baseline" in full:
+        line["cpu_baseline"] = {k: full["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind", "seconds")}
+    if "configs" in full:
+        line["configs_ms"] = {name: {ex: r["ms_per_step"] for ex, r in c.items() if ex != "workload"} for name, c in full["configs"].items()}
+    if "ffn_chain" in full:
+        line["ffn_chain_ms"] = {f: [c["unfused_chain_ms"], c["fused_chain_ms"]] for f, c in full["ffn_chain"].items() if f != "workload"}
+    return json.dumps(short(line), separators=(",", ":"))
 
 
 def main():
@@ -424,7 +453,8 @@ def main():
                             "int4_e3m2": ffn_chain("e3m2")}
         if "mxfp4" in execs:
             out["ffn_chain"]["mxfp4"] = ffn_chain("mxfp4")
-    print(json.dumps(out))
+    print(json.dumps(out), file=sys.stderr, flush=True)
+    print(result_line(out))
 
 
 if __name__ == "__main__":
