@@ -102,3 +102,13 @@ def test_layers_saved_by_earlier_versions():
         assert old._descriptor(0).format == {"e3m2": 1, "nibble": 0, "mxfp4": 2}[container]
         assert old.buffers(40, "cpu")[3].shape == (40, now.N)
     binding._staging.clear()
+
+
+def test_stream_without_torchs_private_functions(monkeypatch):
+    """The current stream is found through torch's public interface where the private one has gone."""
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(torch, "_C", object())
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    assert binding._raw_stream() == 1234
