@@ -222,3 +222,33 @@ def test_nibble_layers_on_two_streams(svdq, M):
     torch.cuda.synchronize()
     for lin, w in zip(lins, want):
         assert torch.equal(lin.buffers(M, w.device)[3], w)
+
+
+@pytest.mark.parametrize("container", ["e3m2", "nibble", "mxfp4"])
+@pytest.mark.parametrize("M", [40, 900])
+def test_layer_forward_captured(svdq, container, M):
+    """A captured forward() keeps the memory that its operands are expanded into: every replay gives the eager result, with
+    eager calls of the layer and of others in between."""
+    K, N = 1024, 2560
+    lin, other = _random_layer(svdq, container, K, N, 16), _random_layer(svdq, container, K, N, 16, seed=2)
+    x = torch.randn(M, K, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda").bfloat16()
+    xs = [x * s for s in (1.0, -0.5, 2.0, 3.0)]
+    want = [lin.forward(v, 0.8).clone() for v in xs]
+    held = x.clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        lin.forward(held, 0.8)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y = lin.forward(held, 0.8)
+    for v, w in zip(xs, want):
+        held.copy_(v)
+        other.forward(v, 0.8)
+        lin.forward(xs[0], 0.9)
+        junk = torch.full((1 << 24,), 7, dtype=torch.uint8, device="cuda")
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, w)
+        del junk
