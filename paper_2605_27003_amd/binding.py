@@ -522,8 +522,8 @@ class _Layer(ctypes.Structure):
 
 
 # One layer's buffers for one token count: the library's view (ptrs: codes, sx, h, scratch; bytes of staging, shared or
-# not), the caller's (public) and what they were made for (key).
-_Work = collections.namedtuple("_Work", "codes sx h scratch staging shared y public ptrs key")
+# not), the caller's (public), what they were made for (key) and the descriptor that they were last used with.
+_Work = collections.namedtuple("_Work", "codes sx h scratch staging shared y public ptrs y_ptr key layer")
 
 
 def _addr(t):
@@ -572,7 +572,7 @@ class W4A4Linear:
         layer = self._layer
         if layer is None or layer.values != fields:
             layer = _Layer(*fields)
-            layer.values = fields
+            layer.values, layer.address = fields, ctypes.addressof(layer)
             self._layer = layer
         return layer
 
@@ -590,13 +590,18 @@ class W4A4Linear:
             return self.w_packed
         return pack_weight_e3m2(self.qw, self.sw, out=_staging_buffer(packed_weight_e3m2_bytes(self.N, self.K), self.qw.device))
 
-    def _workspace(self, M, device):
+    def _workspace(self, M, device, layer):
         """The layer's buffers for M tokens, made again when anything that their sizes depend on has changed.  One object:
-        a call takes all its buffers from the one that it got, whatever other threads do to the layer meanwhile."""
-        key = (M, device, self.format, self.N, self.K, self.r, self.w_packed is None)
+        a call takes all its buffers from the one that it got, whatever other threads do to the layer meanwhile.
+        layer: what _descriptor(self.r) has just returned."""
         work = self._work
-        if work is None or work.key != key:
-            lib, ref, K, r = load_library(), ctypes.byref(self._descriptor(self.r)), self.K, self.r
+        if work is not None and work.layer is layer and work.y.shape[0] == M and work.y.device == device:
+            return work
+        key = (M, device, *layer.values[:4], self.w_packed is None)
+        if work is not None and work.key == key:
+            work = self._work = work._replace(layer=layer)
+        else:
+            lib, ref, K, r = load_library(), layer.address, self.K, self.r
             codes = torch.empty(act_e3m2_bytes(M, K) if self.container == "e3m2" else M * K // 2, dtype=torch.uint8, device=device)
             if self.container == "e3m2":
                 qx, sx = ActE3M2(codes, M, K), None
@@ -614,8 +619,8 @@ class W4A4Linear:
             staging, shared = lib.svdq_layer_staging_bytes(ref, M), self.container == "e3m2" and self.w_packed is None
             if shared:
                 _staging_buffer(packed_weight_e3m2_bytes(self.N, K), device)
-            work = _Work(codes, sx, h, scratch, staging, shared, y, (qx, sx, h, y), tuple(map(_addr, (codes, sx, h, scratch))), key)
-            self._work = work
+            work = self._work = _Work(codes, sx, h, scratch, staging, shared, y, (qx, sx, h, y),
+                                      tuple(map(_addr, (codes, sx, h, scratch))), y.data_ptr(), key, layer)
         return work
 
     def buffers(self, M, device):
@@ -623,7 +628,7 @@ class W4A4Linear:
         device = torch.device(device)
         if device.type == "cuda" and device.index is None:
             device = torch.device("cuda", torch.cuda.current_device())
-        return self._workspace(M, device).public
+        return self._workspace(M, device, self._descriptor(self.r)).public
 
     def _staging(self, work, device):
         """Memory for one call's expanded operands, or None; the caller holds it until its kernels are enqueued."""
@@ -643,21 +648,22 @@ class W4A4Linear:
     def gemm(self, qx, sx, h):
         codes = qx.buf if self.container == "e3m2" else qx
         M, device = (qx.M if self.container == "e3m2" else qx.shape[1]), codes.device
-        work, layer = self._workspace(M, device), self._descriptor(0 if h is None else h.shape[1])
+        work, layer = self._workspace(M, device, self._descriptor(self.r)), self._descriptor(0 if h is None else h.shape[1])
         staging = self._staging(work, device) if work.shared else None       # nibbles are multiplied as they are
         _check(load_library().svdq_layer_gemm(
-            ctypes.byref(layer), codes.data_ptr(), _addr(sx), _addr(h), M, _addr(staging),
-            work.y.data_ptr(), self.N, _stream()), "svdq_layer_gemm")
+            layer.address, codes.data_ptr(), _addr(sx), _addr(h), M, _addr(staging),
+            work.y_ptr, self.N, _raw_stream()), "svdq_layer_gemm")
         return work.y
 
     def forward(self, x_bf16, rho, gelu=False):
         M, K = x_bf16.shape
         assert x_bf16.dtype == torch.bfloat16 and x_bf16.stride(1) == 1 and K == self.K
         device = x_bf16.device
-        work, layer = self._workspace(M, device), self._descriptor(self.r)
-        staging = self._staging(work, device)
+        layer = self._descriptor(self.r)
+        work = self._workspace(M, device, layer)
+        staging = self._staging(work, device) if work.staging else None
         _check((_lib or load_library()).svdq_layer_forward(
-            ctypes.byref(layer), x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, float(rho), 1 if gelu else 0, M,
-            *work.ptrs, _addr(staging),
-            work.y.data_ptr(), self.N, _raw_stream()), "svdq_layer_forward")
+            layer.address, x_bf16.data_ptr(), x_bf16.stride(0) if M > 1 else K, float(rho), 1 if gelu else 0, M,
+            *work.ptrs, None if staging is None else staging.data_ptr(),
+            work.y_ptr, self.N, _raw_stream()), "svdq_layer_forward")
         return work.y

@@ -62,26 +62,25 @@ def test_a_call_keeps_its_own_buffers(monkeypatch):
             return getattr(real, name)
 
         def svdq_layer_forward(self, layer, x, ldx, rho, gelu, m, codes, *rest):
-            seen.append((m, codes))
+            seen.append((m, codes, binding._Layer.from_address(layer).bias))
             return 0
 
     real = binding.load_library()
     monkeypatch.setattr(binding, "_lib", Lib())
     monkeypatch.setattr(binding, "_raw_stream", lambda: 0)
-    mine = lin.buffers(M, "cpu")[0].buf
-    descriptor = type(lin)._descriptor
+    mine, bias = lin.buffers(M, "cpu")[0].buf, lin.bias
+    other = binding.W4A4Linear(lin.inv_lambda, None, None, lin.qw, lin.sw, None)
+    other.buffers(1, "cpu")
+    workspace = binding.W4A4Linear._workspace
 
-    def other_thread(self, r):
-        monkeypatch.setattr(type(lin), "_descriptor", descriptor)
-        first = self._descriptor(r)
-        self.buffers(1, "cpu")
-        self.bias = torch.ones(self.N)
-        assert self._descriptor(r) is not first and first.bias != self.bias.data_ptr()
-        return first
+    def then_other_thread(self, *args):
+        got = workspace(self, *args)
+        self._work, self._layer = other._work, other._layer
+        return got
 
-    monkeypatch.setattr(type(lin), "_descriptor", other_thread)
+    monkeypatch.setattr(binding.W4A4Linear, "_workspace", then_other_thread)
     y = lin.forward(torch.zeros((M, lin.K), dtype=torch.bfloat16), 0.8)
-    assert seen == [(M, mine.data_ptr())] and y.shape == (M, lin.N)
+    assert seen == [(M, mine.data_ptr(), bias.data_ptr())] and y.shape == (M, lin.N)
     binding._staging.clear()
 
 
