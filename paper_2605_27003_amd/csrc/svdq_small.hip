@@ -213,6 +213,21 @@ __device__ __forceinline__ void multiply(const Tokens<SMALL_MXFP4, MT>& t, const
     multiply_group<NI, MT, 1>(t, c, y);
 }
 
+// h = sum of its slices, in slice order: four elements, number v of them (n is a multiple of 16)
+__device__ __forceinline__ void sum_slices(const float* __restrict__ part, const int slices, const int64_t n, float* __restrict__ h, const int64_t v) {
+    const int64_t i = v * 4;
+    if (i >= n) return;
+    float4 t = *reinterpret_cast<const float4*>(part + i);
+    for (int s = 1; s < slices; ++s) {
+        const float4 p = *reinterpret_cast<const float4*>(part + s * n + i);
+        t.x += p.x;
+        t.y += p.y;
+        t.z += p.z;
+        t.w += p.w;
+    }
+    *reinterpret_cast<float4*>(h + i) = t;
+}
+
 template <int SRC, int NI, int MT>
 __global__ __launch_bounds__(64 * WV, NI * MT >= 4 ? 2 : 4)
 void small_gemm_kernel(const SmallArgs a) {
@@ -222,16 +237,9 @@ void small_gemm_kernel(const SmallArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = (int)blockIdx.x * 32 * NI;
     const int64_t m0 = a.begin + (int64_t)blockIdx.y * 32 * MT;
-    if (m0 >= a.M) {                                      // the blocks behind the token tiles: h, all tokens
-        const int64_t n = a.M * a.r;                      // r is a multiple of 16
-        for (int64_t i = ((int64_t)blockIdx.x * (64 * WV) + threadIdx.x) * 4; i < n; i += (int64_t)gridDim.x * (64 * WV * 4)) {
-            float4 t = *reinterpret_cast<const float4*>(a.h + i);
-            for (int s = 1; s < a.hs; ++s) {
-                const float4 v = *reinterpret_cast<const float4*>(a.h + s * n + i);
-                t = float4{t.x + v.x, t.y + v.y, t.z + v.z, t.w + v.w};
-            }
-            *reinterpret_cast<float4*>(a.hsum + i) = t;
-        }
+    if (m0 >= a.M) {                                      // the blocks behind the token tiles
+        for (int b = (int)blockIdx.x; b < (a.M * a.r + 4 * 64 * WV - 1) / (4 * 64 * WV); b += (int)gridDim.x)
+            sum_slices(a.h, a.hs, a.M * a.r, a.hsum, (int64_t)b * (64 * WV) + threadIdx.x);
         return;
     }
     const Buffers B{buffer(a.codes), buffer(a.scales), buffer(a.w0), buffer(a.w1), buffer(a.w2)};
@@ -257,8 +265,9 @@ void small_gemm_kernel(const SmallArgs a) {
     // What bounds a wave is the latency of its loads, above all of the weights, which come from HBM (one step ahead of
     // their use, a step of 32 x 64 codes took 1.4 us at M = 1): their next DW - 1 steps are in flight, of the tokens
     // (in L2) the next one.  Loads past the share re-read its last step: with a condition around every load and step the
-    // compiler no longer overlaps them.
-    constexpr int DW = (SRC == SMALL_MXFP4 && NI * MT > 1) ? 3 : (SRC == SMALL_E3M2_PACKED) ? 2 : 4;
+    // compiler no longer overlaps them.  As many as the registers hold: nibble operands on both sides spill at 4 in a
+    // 32 x 32 tile (M = 1 .. 100, K = 576 .. 10624: 3 to 9 % slower than at 3).
+    constexpr int DW = (SRC == SMALL_E3M2_PACKED) ? 2 : ((SRC == SMALL_MXFP4 && NI * MT > 1) || (SRC == SMALL_NIBBLE && NI * MT == 1)) ? 3 : 4;
     Tokens<SRC, MT> xt[2];
     Channels<SRC, NI> wc[DW];
     auto clamp = [&](const int s) { return wave + WV * ((s < s1) ? s : s1 - 1); };
@@ -329,20 +338,9 @@ hipError_t launch_src(const SmallArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// h = sum of its slices, in slice order
 __global__ __launch_bounds__(256)
 void sum_slices_kernel(const float* __restrict__ part, int slices, int64_t n, float* __restrict__ h) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;       // n is a multiple of 16
-    if (i >= n) return;
-    float4 t = *reinterpret_cast<const float4*>(part + i);
-    for (int s = 1; s < slices; ++s) {
-        const float4 v = *reinterpret_cast<const float4*>(part + s * n + i);
-        t.x += v.x;
-        t.y += v.y;
-        t.z += v.z;
-        t.w += v.w;
-    }
-    *reinterpret_cast<float4*>(h + i) = t;
+    sum_slices(part, slices, n, h, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 }  // namespace
