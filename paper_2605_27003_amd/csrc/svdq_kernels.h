@@ -75,11 +75,13 @@ constexpr int SMALL_SLICES = 8;                  // waves of a block = most part
 // M = 1536, 27 against 36; M = 2304, 288 blocks, 45 against 40), and up to two where few tokens meet many weights, which the
 // tile path has to expand first (N = 13824, M = 85, 432 blocks: K = 2048 23 against 26, K = 13824 73 against 114; N = 5120,
 // M = 307, even; but K = 512 16 against 15, and N = 2048, M = 960, 42 against 38).  MXFP4 expands nothing and wins up to 320
-// blocks (K = 5120: N = 512, M = 2304, 30 against 35; N = 5120, M = 230, 24 against 26; M = 307, 400 blocks, 29 against 27).
+// blocks (K = 5120: N = 512, M = 2304, 30 against 35; N = 5120, M = 230, 24 against 26; M = 307, 400 blocks, 29 against 27),
+// with few channels and a long K up to 384 (K = 5120, N = 1024, M = 1536, 27 against 31; K = 512 even).
 inline int small_shape(int64_t M, int N, int K, bool mxfp4 = true) {
     const int64_t b32 = ((M + 31) / 32) * (N / 32), b64 = ((M + 63) / 64) * ((N + 63) / 64);
     if (b32 <= (mxfp4 ? 256 : 512)) return 1;
-    return b64 <= (mxfp4 ? 320 : (N >= 4096 && K >= 2048) ? 480 : 256) ? 2 : 0;
+    const int limit = mxfp4 ? (N <= 2048 && K >= 4096 ? 384 : 320) : (N >= 4096 && K >= 2048) ? 480 : 256;
+    return b64 <= limit ? 2 : 0;
 }
 // The few-token GEMM addresses codes and weights with 32-bit byte offsets (its tokens may be the last of many).
 inline bool small_reach(int64_t M, int64_t N, int64_t K) { return (M > N ? M : N) * K < (int64_t)1 << 32; }

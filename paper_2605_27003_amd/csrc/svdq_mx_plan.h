@@ -54,7 +54,7 @@ inline MxPart mx_best(int64_t rows, int N, int K, int walkers) {
 
 // The few-token kernel (svdq_small.hip) on `rows` tokens
 inline double mx_few_cost(int64_t rows, int N, int K) {
-    return 5.0 + (0.006 + 0.019 * (K / 5120.0)) * (double)((rows + 63) / 64) * (double)((N + 63) / 64);
+    return 5.0 + (0.010 + 0.028 * (K / 5120.0)) * (double)((rows + 63) / 64) * (double)((N + 63) / 64);
 }
 
 // Tokens of the first launch (a multiple of 256, or all of them): leaving the last tokens to a launch of their own on
