@@ -127,17 +127,27 @@ __device__ __forceinline__ void quantize_rows(const uint4 (&xv)[4], const float*
         // integer-valued floats to E3M2 fields, which is exact on them.  It interleaves its two inputs:
         // field 2 j comes from the first vector, field 2 j + 1 from the second.
         f32x16 ev, od;
+        uint32_t packed[4] = {};               // BOTH: the fold below in ascending order, as the values come by
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const float u0 = __builtin_amdgcn_fmed3f(__fmul_rn(xs[2 * j], inv), -8.0f, 7.0f);
             const float u1 = __builtin_amdgcn_fmed3f(__fmul_rn(xs[2 * j + 1], inv), -8.0f, 7.0f);
             ev[j] = __builtin_rintf(u0);
             od[j] = __builtin_rintf(u1);
+            if constexpr (BOTH) {
+                packed[j >> 2] += f_bits(__fadd_rn(u0, bits_f(RNE_MAGIC_BITS))) << (8 * (j & 3));
+                packed[j >> 2] += f_bits(__fadd_rn(u1, bits_f(RNE_MAGIC_BITS))) << (8 * (j & 3) + 4);
+            }
         }
         const u32x6 c = e3m2_of_floats(ev, od, 1.0f);
         codes.lo = uint4{c[0], c[1], c[2], c[3]};
         codes.hi = uint2{c[4], c[5]};
-        if constexpr (!BOTH) return;
+        if constexpr (BOTH) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) packed[d] = (packed[d] - PACK_JUNK) ^ 0x88888888u;
+            *nibbles = uint4{packed[0], packed[1], packed[2], packed[3]};
+        }
+        return;
     }
     uint32_t packed[4];
 #pragma unroll
@@ -152,8 +162,7 @@ __device__ __forceinline__ void quantize_rows(const uint4 (&xv)[4], const float*
         }
         packed[d] = (wd - PACK_JUNK) ^ 0x88888888u;
     }
-    if constexpr (BOTH) *nibbles = uint4{packed[0], packed[1], packed[2], packed[3]};
-    else codes.lo = uint4{packed[0], packed[1], packed[2], packed[3]};
+    codes.lo = uint4{packed[0], packed[1], packed[2], packed[3]};
 }
 
 }  // namespace svdq
