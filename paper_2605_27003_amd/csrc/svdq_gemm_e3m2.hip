@@ -51,7 +51,7 @@ __host__ __device__ inline size_t w0_bytes(int N, int K) { return (size_t)N * (K
 __host__ __device__ inline size_t w1_bytes(int N, int K) { return (size_t)N * (K / 64) * 16; }
 __host__ __device__ inline size_t sf_bytes(int N, int K) { return (size_t)N * (K / 64) * 8; }
 
-// int4 code of an E3M2 field (fields produced by the above only)
+// int4 code of an E3M2 field of an integer -8 .. 7: 0 -> 0; |q| = 2^e (1 + m/4) -> (e + 3) << 2 | m, sign in bit 5
 __device__ __forceinline__ int code_of_e3m2(uint32_t f) {
     const uint32_t t = f & 31u;
     const int a = (t == 0) ? 0 : (t == 12) ? 1 : (t < 20) ? (int)(t - 12) / 2 : (t < 24) ? (int)t - 16 : 8;
