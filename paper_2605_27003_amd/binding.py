@@ -657,7 +657,9 @@ class W4A4Linear:
 
     def forward(self, x_bf16, rho, gelu=False):
         M, K = x_bf16.shape
-        assert x_bf16.dtype == torch.bfloat16 and x_bf16.stride(1) == 1 and K == self.K
+        # the MXFP4 pass also takes the bits in another two-byte type, as quantize_act_mxfp4 does
+        assert x_bf16.dtype == torch.bfloat16 or (self.container == "mxfp4" and not gelu and x_bf16.element_size() == 2)
+        assert x_bf16.stride(1) == 1 and K == self.K
         device = x_bf16.device
         layer = self._descriptor(self.r)
         work = self._workspace(M, device, layer)

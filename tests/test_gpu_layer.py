@@ -252,3 +252,14 @@ def test_layer_forward_captured(svdq, container, M):
         torch.cuda.synchronize()
         assert torch.equal(y, w)
         del junk
+
+
+def test_mxfp4_forward_takes_raw_bits(svdq):
+    """bf16 bits held in 16-bit integers, as the MXFP4 quantise pass takes them; the other containers refuse them."""
+    x = torch.randn(40, 1024, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda").bfloat16()
+    lin = _random_layer(svdq, "mxfp4", 1024, 256, 16)
+    y = lin.forward(x, 0.8).clone()
+    assert torch.equal(lin.forward(x.view(torch.int16), 0.8), y)
+    for bad in (lambda: lin.forward(x.float(), 0.8), lambda: _random_layer(svdq, "e3m2", 1024, 256, 16).forward(x.view(torch.int16), 0.8)):
+        with pytest.raises(AssertionError):
+            bad()
