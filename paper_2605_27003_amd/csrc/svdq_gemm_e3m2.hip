@@ -15,11 +15,14 @@
 //
 // Orientation and staging as in the int4 kernel: the transposed tile D[n][m] (weights are the A operand);
 // block tile 128 x 128, 4 waves of 64 x 64, two blocks per CU; everything the matrix cores consume arrives by
-// direct global->LDS loads into a five-slot ring of one-group stages, requested four groups ahead.  A lane's
+// direct global->LDS loads into a five-slot ring of one-group stages, requested four groups ahead.  Many tokens
+// take the larger tiles of svdq_e3m2_walk.hip; this kernel has few and middling numbers of them, what those leave over,
+// binary32 output and the emitting epilogues.  A lane's
 // 24 code bytes live in two planes (bytes 0..15 and 16..23) so that LDS reads are one 16-byte and one 8-byte
 // access without bank conflicts and every transfer is a full 1 KB wave-wide load.
 #include "svdq_act.h"
 #include "svdq_dev.h"
+#include "svdq_e3m2_plan.h"
 #include "svdq_epilogue.h"
 #include "svdq_expand_dev.h"
 #include "svdq_kernels.h"
@@ -609,17 +612,25 @@ hipError_t launch_unpack_act_e3m2(const uint8_t* act, int64_t M, int K, uint8_t*
     return hipGetLastError();
 }
 
-// two_teams: K in halves
+// teams: two teams of waves may split K where a launch has a tile per CU at most.  Below K = 2048 the second ring's
+// prologue and the sum of the tiles cost what the shorter loop saves (K = 1536, N = 2048, M = 640: 15.4 and 15.5 us).
 static hipError_t launch_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
-                              int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32, bool two_teams,
+                              int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32, bool teams,
                               hipStream_t stream) {
+    const int64_t walked = out_f32 ? 0 : e3m2_walk_rows(M, N, K, teams, walking_blocks());
+    if (walked) {
+        const hipError_t e = launch_e3m2_walk(act, w_packed, h, L2, bias, M, walked, N, K, r, y, ldy, stream);
+        if (e != hipSuccess || walked == M) return e;
+    }
     const uint8_t* base = (const uint8_t*)w_packed;
-    const TileGrid tg = make_tile_grid((int)((M + BM - 1) / BM), N / BN);
+    const int mtiles = (int)((M - walked + BM - 1) / BM);
+    const bool two_teams = teams && K >= 2048 && busiest_xcd(mtiles, N / BN) <= CUS_PER_XCD;
+    const TileGrid tg = make_tile_grid(mtiles, N / BN);
     auto kern = two_teams ? gemm_e3m2_kernel<MODE_LAYER, 2> : gemm_e3m2_kernel<MODE_LAYER, 1>;
     hipLaunchKernelGGL(kern, dim3((unsigned)tile_ids(tg)), dim3(two_teams ? 512 : 256), 0, stream,
                        act, base, base + w0_bytes(N, K), base + w0_bytes(N, K) + w1_bytes(N, K),
                        h, (const uint16_t*)L2, bias, M, N, K, r, y, ldy, out_f32,
-                       0, tg, (int64_t)0, 0, (int32_t*)nullptr, NextLayer{});
+                       (int)(walked / BM), tg, (int64_t)0, 0, (int32_t*)nullptr, NextLayer{});
     return hipGetLastError();
 }
 
@@ -630,12 +641,9 @@ hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
     return launch_e3m2(act, w_packed, h, L2, bias, M, N, K, r, y, ldy, out_f32, false, stream);
 }
 
-// The layer's GEMM: with a tile per CU at most, two teams on each.  Below K = 2048 the second ring's prologue and the
-// sum of the tiles cost what the shorter loop saves (K = 1536, N = 2048, M = 640: 15.4 and 15.5 us).
 hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
                              int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream) {
-    const bool two_teams = K >= 2048 && busiest_xcd((int)((M + BM - 1) / BM), N / BN) <= CUS_PER_XCD;
-    return launch_e3m2(act, w_packed, h, L2, bias, M, N, K, r, y, ldy, 0, two_teams, stream);
+    return launch_e3m2(act, w_packed, h, L2, bias, M, N, K, r, y, ldy, 0, true, stream);
 }
 
 hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,

@@ -54,6 +54,9 @@ hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
                               const float* h, const void* L2, const float* bias,
                               int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32,
                               hipStream_t stream);
+// svdq_e3m2_walk.hip: tokens [0, rows) of M, rows a multiple of 256 or M; N a multiple of 256, K >= 320, bf16 y
+hipError_t launch_e3m2_walk(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
+                            int64_t M, int64_t rows, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
 hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
                              int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
 hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,
@@ -92,6 +95,7 @@ hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scale
 hipError_t launch_sum_slices(const float* part, int slices, int64_t M, int r, float* h, hipStream_t stream);
 
 // svdq_mxfp4.hip
+int walking_blocks();                            // blocks of a kernel that walks its tiles: one per CU, a multiple of 8
 size_t packed_weight_mx_bytes(int N, int K);
 inline size_t packed_mx_codes_bytes(int N, int K) { return (size_t)N * (K / 2); }
 hipError_t launch_pack_weight_mx(const uint8_t* qw, const uint8_t* sw, int N, int K, void* out, hipStream_t stream);

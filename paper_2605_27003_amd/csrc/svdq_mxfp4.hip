@@ -1044,7 +1044,7 @@ static int cu_count() {
 
 // the tile-walking kernel runs one block per CU (a multiple of 8 blocks, so that a block stays on one XCD's share of
 // the tile order)
-static inline int walking_blocks() { return cu_count() / 8 * 8; }
+int walking_blocks() { return cu_count() / 8 * 8; }
 
 int64_t mx_main_rows(int64_t M, int N, int K) { return mx_layer_split(M, N, K, walking_blocks()); }
 

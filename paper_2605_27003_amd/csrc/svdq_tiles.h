@@ -59,4 +59,20 @@ __device__ __forceinline__ bool tile_of(const TileGrid& g, int id, int& mt, int&
     return true;
 }
 
+// The order of a kernel whose blocks walk their tiles with one block per CU: XCD x takes a run of `chunk` consecutive
+// tiles, the same number on every XCD (token tiles owned by residue leave an XCD a token tile ahead of the others: 294 x
+// 20 tiles are 23.1 rounds of 32 CUs where the runs are 22.97).  Tiles are numbered in groups of eight token tiles across
+// the channel tiles, so the 32 tiles that an XCD's CUs hold at once are 8 x 4.
+struct WalkGrid {
+    int mtiles, ntiles, chunk;
+};
+inline WalkGrid make_walk_grid(int mtiles, int ntiles) { return WalkGrid{mtiles, ntiles, (mtiles * ntiles + 7) / 8}; }
+// tile of block id `id` (id % 8: its XCD), which exists
+__host__ __device__ inline void walk_tile(const WalkGrid& g, int id, int& mt, int& nt) {
+    const int n = (id & 7) * g.chunk + (id >> 3), sm = n / (8 * g.ntiles), rem = n - sm * (8 * g.ntiles);
+    const int width = g.mtiles - 8 * sm < 8 ? g.mtiles - 8 * sm : 8;
+    nt = rem / width;
+    mt = 8 * sm + rem - nt * width;
+}
+
 }  // namespace svdq

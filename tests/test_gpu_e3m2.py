@@ -250,3 +250,32 @@ def test_layers_with_resident_4bit_weights_share_one_staging_buffer(svdq, oracle
     assert len(binding._staging) == 1
     (buf,) = binding._staging.values()
     assert buf.numel() == max(svdq.packed_weight_e3m2_bytes(256, 512), svdq.packed_weight_e3m2_bytes(384, 256))
+
+
+# Many tokens on 256 x 256 tiles: ragged last tiles (1 and 255 rows of it, and rows split off for the 128 x 128 kernel), K
+# loops from as long as the ring (320) upwards with every position of the ring at a tile's end, both ranks and none, with
+# and without bias.  All kernels of the layer keep one order of operations, so bf16 out is the rounding of the binary32
+# that the 128 x 128 kernel writes, bit for bit (not-a-number where that is).
+@pytest.mark.parametrize("M,N,K,r,with_bias", [
+    (65537, 256, 320, 32, True), (65279, 256, 384, 16, False), (65281, 256, 448, 0, True), (16001, 1024, 512, 32, False),
+    (9215, 1792, 576, 0, False), (3072, 5120, 640, 32, True), (32700, 512, 1024, 16, True), (3300, 5120, 5120, 32, True)])
+def test_walked_tiles(svdq, M, N, K, r, with_bias):
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    x = torch.randn((M, K), generator=g, device="cuda", dtype=torch.bfloat16)
+    x[:, ::17] *= 20.0
+    x[M // 2, 5], x[M - 1, 64] = float("inf"), float("nan")
+    inv = torch.rand(K, generator=g, device="cuda") + 0.5
+    qw = torch.randint(0, 256, (N, K // 2), generator=g, device="cuda", dtype=torch.uint8)
+    sw = torch.rand((K // 64, N), generator=g, device="cuda") * 0.01 + 0.005
+    L1 = (torch.randn((K, 32), generator=g, device="cuda") * 0.02).to(torch.bfloat16)[:, :r].contiguous()
+    L2 = torch.randn((32, N), generator=g, device="cuda").to(torch.bfloat16)[:r].contiguous()
+    bias = torch.randn(N, generator=g, device="cuda") if with_bias else None
+    act, _, h = svdq.quantize_act_e3m2(x, inv, 0.8, svdq.pack_lowrank_down(L1, inv) if r else None, r)
+    wp = svdq.pack_weight_e3m2(qw, sw)
+    args = (act, wp, N, h, L2 if r else None, bias)
+    want = svdq.linear_w4a4_e3m2(*args, out_dtype=torch.float32)
+    room = torch.full((M + 1, N + 8), 3.0, device="cuda", dtype=torch.bfloat16)
+    got = svdq.linear_w4a4_e3m2(*args, out=room[:M, :N])
+    assert torch.equal(got.isnan(), want.isnan()) and want.isnan().any(1).sum() <= 2
+    assert torch.equal(got.nan_to_num(), want.to(torch.bfloat16).nan_to_num())
+    assert (room[M] == 3.0).all() and (room[:, N:] == 3.0).all()
