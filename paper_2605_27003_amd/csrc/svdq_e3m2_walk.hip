@@ -13,6 +13,7 @@
 // transfers 12 clocks, LDS reads 6 (timing only).  Fewer clocks are not always less time: transfers placed elsewhere in a
 // step, or waves 4..7 half a step behind, change the clocks by 5 to 14 and the frequency the other way.
 #include "svdq_dev.h"
+#include "svdq_epilogue.h"
 #include "svdq_kernels.h"
 #include "svdq_lds.h"
 #include "svdq_tiles.h"
@@ -37,13 +38,11 @@ constexpr uint32_t OFF_H = 0;          // h: [32-token block][4 columns][token] 
 constexpr uint32_t OFF_L2 = 16384;     // L2: [row] x 512 B, 16-byte piece c of row k at place c ^ 4 (k % 4)
 constexpr uint32_t OFF_B = 24576;      // bias: [channel] x 4 B
 
-constexpr uint32_t STORE_BYTES = 32 * 64;          // per wave: 32 tokens x 32 channels as bf16, 16-byte piece c of token t at place c ^ (t / 4) % 4
-constexpr uint32_t OFF_STORE = NSLOTS * STAGE, OFF_ZERO = OFF_STORE + 8 * STORE_BYTES;
+constexpr uint32_t OFF_STORE = NSLOTS * STAGE, OFF_ZERO = OFF_STORE + 8 * WALK_STORE_BYTES;
 constexpr uint32_t LDS_BYTES = OFF_ZERO + 1024;    // 1 KB of zeros: the scale-product operands of k half 1
 static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
 
 typedef int int8v __attribute__((ext_vector_type(8)));
-typedef short short4lds __attribute__((ext_vector_type(4)));
 
 // dma16 by the lower 32 lanes: 512 bytes
 __device__ __forceinline__ void dma16_half(const void* sbase, uint32_t voff, uint32_t lds_off) {
@@ -53,14 +52,6 @@ __device__ __forceinline__ void dma16_half(const void* sbase, uint32_t voff, uin
     lds_off = __builtin_amdgcn_readfirstlane(lds_off);
     asm volatile("s_mov_b32 m0, %2\n\ts_mov_b32 exec_hi, 0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b32 exec_hi, -1"
                  ::"v"(voff), "s"(sa), "s"(lds_off) : "memory");
-}
-
-// four rows of 16-bit values, transposed: lane i of 16 (its address: 4 values of row i / 4, columns 4 (i % 4) ..) gets
-// column i of the four rows
-__device__ __forceinline__ uint2 lds_read_tr16(uint32_t off) {
-    typedef __attribute__((address_space(3))) short4lds* p;
-    const short4lds v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((p)(lds_byte*)(uintptr_t)off);
-    return __builtin_bit_cast(uint2, v);
 }
 
 __global__ __launch_bounds__(512, 1)
@@ -75,7 +66,7 @@ void gemm_e3m2_walk_kernel(const uint8_t* __restrict__ act, const uint8_t* __res
     const int ng = K >> 6;                                        // >= NSLOTS (the launcher sees to it)
     const int64_t Mp = (M + 3) & ~(int64_t)3;
     const uint32_t ring0 = (uint32_t)(uintptr_t)(lds_byte*)lds;
-    const uint32_t store0 = ring0 + OFF_STORE + wave * STORE_BYTES;
+    const uint32_t store0 = ring0 + OFF_STORE + wave * WALK_STORE_BYTES;
     if (tid < 64) *reinterpret_cast<uint4*>(lds + OFF_ZERO + tid * 16) = uint4{0u, 0u, 0u, 0u};     // read behind two barriers
 
     struct Tile {
@@ -140,7 +131,7 @@ void gemm_e3m2_walk_kernel(const uint8_t* __restrict__ act, const uint8_t* __res
             dma16(h + t.m0 * r + c0, (uint32_t)(row * r * 4 + (2 * i + (ln >> 5)) * 16), s + OFF_H + wave * 2048 + i * 1024);
         }
         if (i == 2) {
-            const int k = 2 * wave + (ln >> 5), c = (ln & 31) ^ (4 * (k & 3));
+            const int k = 2 * wave + (ln >> 5), c = l2_piece(k, ln & 31);
             const int64_t on = r ? 1 : 0;                         // r = 0: the launcher passes something readable
             dma16(L2 + on * ((int64_t)c0 * N + t.n0), (uint32_t)(k * (int)on * N * 2 + c * 16), s + OFF_L2 + wave * 1024);
         }
@@ -199,7 +190,7 @@ void gemm_e3m2_walk_kernel(const uint8_t* __restrict__ act, const uint8_t* __res
     if (!exists(id)) return;
     Tile T = tile_at(id);
     uint32_t cur = 0;                                             // slot of the tile's first low-rank stage
-    bool stores_counted = false;                                  // the previous tile's 16 stores stand behind its transfers
+    int stores_counted = 0;                                       // the previous tile's 16 stores stand behind its transfers
     {
         uint32_t s = 0;
         for (int ks = 0; ks < 2; ++ks, s = next_slot(s))
@@ -218,71 +209,24 @@ void gemm_e3m2_walk_kernel(const uint8_t* __restrict__ act, const uint8_t* __res
 
         // ---- y starts as the low-rank term plus the bias
         const uint32_t slot_l1 = next_slot(cur);
-        if (stores_counted) asm volatile("s_waitcnt vmcnt(28)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        wait_left<12>(stores_counted);
         __syncthreads();
         {
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            const int q32 = ln & 31, qh = ln >> 5, i16 = ln & 15, g1 = (ln >> 4) & 1;
-            // row 8 qh + 4 q + i16 / 4 of L2, channels 16 g1 + 4 (i16 % 4) .. of the n-block: its byte within the row, with
-            // the row's rotation
-            const int krow = 8 * qh + (i16 >> 2);
-            const uint32_t col = (uint32_t)(wn * 128 + g1 * 32 + (i16 & 3) * 8);
-            const uint32_t rd_h = ring0 + OFF_H + wm * 8192 + qh * 1024 + q32 * 16;
+            const uint32_t rd_h = ring0 + OFF_H + wm * 8192 + (ln >> 5) * 1024 + (ln & 31) * 16;
+            const uint32_t rd_b = ring0 + OFF_B + cur + (wn * 64 + 4 * (ln >> 5)) * 4;
+            bf16x8 l2[2][2];
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                if (16 * ks >= r && (ks || r)) continue;
-                const uint32_t sl = ks ? slot_l1 : cur;
-                bf16x8 lf[2];
+            for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni) {
-                    const uint32_t at = ring0 + OFF_L2 + sl + krow * 512 + ((col + ni * 64) ^ (uint32_t)((krow & 3) * 64));
-                    const uint2 a = lds_read_tr16(at), b = lds_read_tr16(at + 2048);     // rows krow, krow + 4: the same rotation
-                    lf[ni] = __builtin_bit_cast(bf16x8, uint4{a.x, a.y, b.x, b.y});
-                }
-#pragma unroll
-                for (int mi = 0; mi < 4; ++mi) {
-                    if (ks == 0 && r == 0) {
-                        y[0][mi] = zero16;
-                        y[1][mi] = zero16;
-                        continue;
-                    }
-                    const uint4 h0 = lds_read16(rd_h + sl + mi * 2048), h1 = lds_read16(rd_h + sl + mi * 2048 + 512);
-                    const float v[8] = {bits_f(h0.x), bits_f(h0.y), bits_f(h0.z), bits_f(h0.w), bits_f(h1.x), bits_f(h1.y), bits_f(h1.z), bits_f(h1.w)};
-                    uint32_t hp[4], lp[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        hp[e] = f2_bf16_rne(v[2 * e], v[2 * e + 1]);
-                        lp[e] = f2_bf16_rne(v[2 * e] - bf16lo_f(hp[e]), v[2 * e + 1] - bf16hi_f(hp[e]));
-                    }
-                    const bf16x8 hi = __builtin_bit_cast(bf16x8, uint4{hp[0], hp[1], hp[2], hp[3]});
-                    const bf16x8 lo = __builtin_bit_cast(bf16x8, uint4{lp[0], lp[1], lp[2], lp[3]});
-#pragma unroll
-                    for (int ni = 0; ni < 2; ++ni) y[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf[ni], hi, ks ? y[ni][mi] : zero16, 0, 0, 0);
-#pragma unroll
-                    for (int ni = 0; ni < 2; ++ni) y[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf[ni], lo, y[ni][mi], 0, 0, 0);
-                }
-            }
-            if (has_bias) {
-#pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const uint4 b = lds_read16(ring0 + cur + OFF_B + (wn * 64 + ni * 32 + 8 * q + 4 * qh) * 4);
-#pragma unroll
-                        for (int mi = 0; mi < 4; ++mi) {
-                            y[ni][mi][4 * q + 0] += bits_f(b.x);
-                            y[ni][mi][4 * q + 1] += bits_f(b.y);
-                            y[ni][mi][4 * q + 2] += bits_f(b.z);
-                            y[ni][mi][4 * q + 3] += bits_f(b.w);
-                        }
-                    }
-            }
+                for (int ni = 0; ni < 2; ++ni) l2[ks][ni] = l2_fragment(ring0 + OFF_L2 + (ks ? slot_l1 : cur), wn * 64 + ni * 32, ln);
+            lowrank_bias_of<4>(y, l2,
+                               [&](const int mi, const int ks, const int half) { return lds_read16(rd_h + (ks ? slot_l1 : cur) + mi * 2048 + half * 512); },
+                               [&](const int ni, const int q) { return lds_read16(rd_b + ni * 128 + q * 32); }, r, has_bias);
         }
         // group 0 is here; the low-rank stages' slots take groups 3 and 4
-        if (stores_counted) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        wait_left<8>(stores_counted);
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 4; ++i) group_request(cur, i);
@@ -348,40 +292,11 @@ void gemm_e3m2_walk_kernel(const uint8_t* __restrict__ act, const uint8_t* __res
         group(cur, IC<2>{}, 0);
         cur = next_slot(cur);                                     // the next tile's first low-rank stage
 
-        // ---- store: one accumulator block at a time through this wave's LDS region, the next one converted and written
-        // behind the reads of the one before (LDS serves a wave's requests in order)
         {
             int ln = lane;
-            asm volatile("" : "+v"(ln));
-            const uint32_t wr0 = store0 + (ln & 31) * 64 + 8 * (ln >> 5), wrot = ((ln >> 2) & 3) * 16;
-            const int rsub = ln >> 2, c16 = ln & 3;
-            const uint32_t rd0 = store0 + rsub * 64 + ((c16 ^ ((rsub >> 2) & 3)) * 16);
+            asm volatile("" : "+v"(ln));                          // the store's address arithmetic stays behind the K loop
             const int64_t mw = T.m0 + wm * 128;
-            uint16_t* const yl = yout + (mw + rsub) * ldy + T.n0 + wn * 64 + c16 * 8;
-            const int64_t left = M - mw;
-            auto put = [&](auto BC) {
-                constexpr int b = decltype(BC)::value, mi = b >> 1, ni = b & 1;
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    lds_write8_pinned(wr0 + ((16 * q) ^ wrot), uint2{f2_bf16_rne(y[ni][mi][4 * q], y[ni][mi][4 * q + 1]),
-                                                          f2_bf16_rne(y[ni][mi][4 * q + 2], y[ni][mi][4 * q + 3])});
-            };
-            auto store = [&](auto FULLC) {
-                auto one = [&](auto BC) {
-                    constexpr int b = decltype(BC)::value, mi = b >> 1, ni = b & 1;
-                    const uint4 v0 = lds_read16_pinned(rd0), v1 = lds_read16_pinned(rd0 + 16 * 64);
-                    if constexpr (b < 7) put(IC<b + 1>{});
-                    uint16_t* const p = yl + (int64_t)(32 * mi) * ldy + ni * 32;
-                    if (decltype(FULLC)::value || 32 * mi + rsub < left) *reinterpret_cast<uint4*>(p) = v0;
-                    if (decltype(FULLC)::value || 32 * mi + 16 + rsub < left) *reinterpret_cast<uint4*>(p + 16 * ldy) = v1;
-                };
-                put(IC<0>{});
-                one(IC<0>{}); one(IC<1>{}); one(IC<2>{}); one(IC<3>{});
-                one(IC<4>{}); one(IC<5>{}); one(IC<6>{}); one(IC<7>{});
-            };
-            stores_counted = left >= 128;
-            if (stores_counted) store(IC<1>{});
-            else store(IC<0>{});
+            stores_counted = store_walked_bf16<4>(y, store0, ln, yout + mw * ldy + T.n0 + wn * 64, ldy, M - mw);
         }
         if (!more) break;
         id = nid;

@@ -1,6 +1,7 @@
 // Low-rank up-projection and bias of eq. 7 / eq. 11 on a wave's accumulator tile, shared by the GEMM kernels.
 #pragma once
 #include "svdq_dev.h"
+#include "svdq_lds.h"
 
 namespace svdq {
 
@@ -95,6 +96,69 @@ __device__ __forceinline__ void add_lowrank_bias_from(float16v (&y)[NI][MT], HPi
                 y[ni][mi][4 * q + 2] += bv[ni][q].z;
                 y[ni][mi][4 * q + 3] += bv[ni][q].w;
             }
+}
+
+// The same on operands that stand in LDS or registers already, for the kernels that walk their tiles: y is written, not
+// added to (same order of operations).  l2[ks][ni]: the L2^T fragments; h_piece(mi, ks, half): h[token][16 ks + 8 kh +
+// 4 half ..]; bias_piece(ni, q): bias[32 ni + 8 q + 4 kh ..] of the wave's channels.
+template <int MT, class HPiece, class BiasPiece>
+__device__ __forceinline__ void lowrank_bias_of(float16v (&y)[2][MT], const bf16x8 (&l2)[2][2], HPiece h_piece,
+                                                BiasPiece bias_piece, int r, bool has_bias) {
+    float16v zero16;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero16[i] = 0.0f;
+    if (r == 0) {
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi) y[0][mi] = y[1][mi] = zero16;
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        if (16 * ks >= r) continue;
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi) {
+            const uint4 h0 = h_piece(mi, ks, 0), h1 = h_piece(mi, ks, 1);
+            const float v[8] = {bits_f(h0.x), bits_f(h0.y), bits_f(h0.z), bits_f(h0.w), bits_f(h1.x), bits_f(h1.y), bits_f(h1.z), bits_f(h1.w)};
+            uint32_t hp[4], lp[4];                       // pairs of hi pieces, pairs of lo pieces
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                hp[e] = f2_bf16_rne(v[2 * e], v[2 * e + 1]);
+                lp[e] = f2_bf16_rne(v[2 * e] - bf16lo_f(hp[e]), v[2 * e + 1] - bf16hi_f(hp[e]));
+            }
+            const bf16x8 hi = __builtin_bit_cast(bf16x8, uint4{hp[0], hp[1], hp[2], hp[3]});
+            const bf16x8 lo = __builtin_bit_cast(bf16x8, uint4{lp[0], lp[1], lp[2], lp[3]});
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) y[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(l2[ks][ni], hi, ks ? y[ni][mi] : zero16, 0, 0, 0);
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) y[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(l2[ks][ni], lo, y[ni][mi], 0, 0, 0);
+        }
+    }
+    if (has_bias) {
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint4 b = bias_piece(ni, q);
+#pragma unroll
+                for (int mi = 0; mi < MT; ++mi) {
+                    y[ni][mi][4 * q + 0] += bits_f(b.x);
+                    y[ni][mi][4 * q + 1] += bits_f(b.y);
+                    y[ni][mi][4 * q + 2] += bits_f(b.z);
+                    y[ni][mi][4 * q + 3] += bits_f(b.w);
+                }
+            }
+    }
+}
+
+// L2 rows of a 256-channel tile in LDS for it: row k is 512 bytes, its 16-byte piece c at place c ^ 4 (k % 4), so that the
+// four rows of a transposing read stand in different banks.  l2_piece: the piece that belongs at 16-byte place `place` of row k.
+__device__ __forceinline__ int l2_piece(int k, int place) { return place ^ (4 * (k & 3)); }
+// fragment of the n-block whose first channel is n0 (of the tile's 256), 16 rows from byte offset `rows`
+__device__ __forceinline__ bf16x8 l2_fragment(uint32_t rows, int n0, int lane) {
+    const int i16 = lane & 15, k = 8 * (lane >> 5) + (i16 >> 2);                   // rows k, k + 4: the same rotation
+    const uint32_t col = (uint32_t)((n0 + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3)) * 2);
+    const uint32_t at = rows + k * 512 + (col ^ (uint32_t)((k & 3) * 64));
+    const uint2 a = lds_read_tr16(at), b = lds_read_tr16(at + 4 * 512);
+    return __builtin_bit_cast(bf16x8, uint4{a.x, a.y, b.x, b.y});
 }
 
 template <int NI, int MT>

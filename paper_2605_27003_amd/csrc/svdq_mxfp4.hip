@@ -670,28 +670,28 @@ void gemm_mx_kernel(const uint8_t* __restrict__ qx, const uint16_t* __restrict__
 // in the same XCD-aware order (tile ids b, b + gridDim, ...; gridDim a multiple of 8 keeps a block on one XCD's
 // share).  Same arithmetic, same order of operations per output as gemm_mx_kernel.
 //
-// The low-rank term's h rows (eq. 7: 256 tokens x r binary32 per tile) were what a tile start waited for longest:
-// sixteen 16-byte loads per lane, requested behind the previous tile's stores (measured: 6-7 % of the kernel at
-// K = 5120).  They now travel like the operands: the first two stages of a tile request the NEXT tile's rows into an
-// LDS area of their own, in the instruction slots of the second group that carry no operand request, and the tile
-// start reads them from there.  A token has eight 16-byte places there (128 bytes, r = 32; with r = 16 the upper four
-// hold nothing of use); piece c of token t sits at place c ^ ((t >> 1) & (r / 4 - 1)): a lane reads one piece of its
-// own token, and with the pieces rotated by token the 32 tokens of an instruction spread over the banks.  To make
-// room the store transposes one 32 x 32 accumulator block at a time (rows of 64 bytes, padded to 80).
+// The low-rank term's operands travel like the others: the first two stages of a tile request the NEXT tile's h rows
+// (256 tokens x r binary32), L2 rows and bias, in instruction slots that carry no operand request.
+// (As loads to registers at the tile's start they wait for the previous tile's stores: vmcnt counts both in one order.
+// h 6-7 % of the kernel at K = 5120; L2 and bias, in one process, M = 32760: N = 13824, K = 5120 1227 -> 1179 us, M = 16384,
+// N = 5120, K = 640 69 -> 64, N = 5120, K = 13824 even -- the power limit gives a tile's loop back what its start saves.)  h has an LDS area of its own; L2 stands where the
+// store transposes and is taken to registers between the K loop and the store.  A token has eight 16-byte places in the h
+// area (128 bytes, r = 32; with r = 16 the upper four hold nothing of use); piece c of token t sits at place c ^ ((t >> 1) &
+// (r / 4 - 1)): a lane reads one piece of its own token, and with the pieces rotated by token the 32 tokens of an
+// instruction spread over the banks.
 template <int MT>
 __global__ __launch_bounds__(512, 1)
 void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* __restrict__ sxe,
                                const uint4* __restrict__ wfrag, const uint16_t* __restrict__ wscale,
                                const float* __restrict__ h, const uint16_t* __restrict__ L2, const float* __restrict__ bias,
-                               int64_t M, int N, int K, int r, void* __restrict__ yout, int64_t ldy, int out_f32,
+                               int64_t M, int N, int K, int r, int has_bias, void* __restrict__ yout, int64_t ldy, int out_f32,
                                const TileGrid tg) {
     constexpr int WNC = 4;
     using G = MxGeom<MT, WNC>;
     constexpr int BM = G::BM, NDMA = G::NDMA, NS = 3;
-    constexpr uint32_t YROW32 = 80;                                   // 32 channels of a token as bf16 + 16 bytes of padding
-    constexpr uint32_t STORE_BYTES = 32 * YROW32;                     // per wave: one 32-token x 32-channel block at a time
-    constexpr uint32_t HBUF = (uint32_t)BM * 128;                     // the tile's h rows, r <= 32
-    __shared__ __attribute__((aligned(16))) uint8_t ring[NS * G::STAGE + 2 * WNC * STORE_BYTES + HBUF];
+    constexpr uint32_t OFF_STORE = NS * G::STAGE, OFF_H = OFF_STORE + 2 * WNC * WALK_STORE_BYTES, OFF_B = OFF_H + (uint32_t)BM * 128;
+    static_assert(2 * WNC * WALK_STORE_BYTES >= 32 * 512, "L2 rows of the next tile, r <= 32, where the store transposes");
+    __shared__ __attribute__((aligned(16))) uint8_t ring[OFF_B + 1024];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -700,10 +700,9 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
     const int ng = K >> 6;
     const int nstages = (ng + 1) >> 1;                                // >= NS + 2 (the launcher sees to it)
     const uint32_t ring0 = (uint32_t)(uintptr_t)(lds_byte*)ring;
-    const uint32_t store0 = ring0 + NS * G::STAGE + wave * STORE_BYTES;
-    const uint32_t hbuf0 = ring0 + NS * G::STAGE + 2 * WNC * STORE_BYTES;
+    const uint32_t hbuf0 = ring0 + OFF_H, l2buf0 = ring0 + OFF_STORE;
     const int ptm = (r >> 2) - 1;                                     // 16-byte pieces per token of h, less one; r is 0, 16 or 32
-    constexpr int H_TRANSFERS = 4;                                    // 1-KB transfers per wave and tile: BM x 128 bytes over 8 waves
+    constexpr int H_TRANSFERS = 4, LR_TRANSFERS = 7;                  // 1-KB transfers per wave and tile: h 4, L2 2, the bias (all waves the same)
 
     // tile ids: the one-tile kernel's order (svdq_tiles.h), of which this block takes ids b, b + gridDim, ...
     const int total = tile_ids(tg);
@@ -759,19 +758,28 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
 #pragma unroll
         for (int p = 0; p < NDMA; ++p) stage_piece(t, s, slot, p);
     };
-    // transfer i (0 .. H_TRANSFERS - 1) of this wave for the h rows of the tile whose first token is m0: eight tokens,
-    // lane l fills place l % 8 of token l / 8 (a place that holds nothing of use re-reads a piece that exists).  No
+    // transfer i (0 .. LR_TRANSFERS - 1) of this wave for the low-rank term and bias of tile t.  h: eight tokens, lane l
+    // fills place l % 8 of token l / 8 (a place that holds nothing of use re-reads a piece that exists); L2: two rows.  No
     // branch: a stage must stay one basic block, or the compiler moves its matrix instructions out of their places.
-    // With r = 0 the launcher passes some readable address as h, and the lanes read within its first 128 bytes.
-    auto h_request = [&](const int64_t m0, const int i) {
+    // With r = 0, or without a bias, the launcher passes some readable address, whose first bytes are read.
+    const int64_t l2_tile = r ? 1 : 0, b_tile = has_bias ? 1 : 0;
+    const int l2_rows = r ? r - 1 : 0;
+    auto lr_request = [&](const TileAddr& t, const int i) {
         int ln = lane;
         asm volatile("" : "+v"(ln));                                  // the address arithmetic stays where the request is
-        const int j = wave * H_TRANSFERS + i;
-        const int t = j * 8 + (ln >> 3);
-        const int c = ((ln & 7) ^ (t >> 1)) & ptm & 7;
-        const int64_t left = M - 1 - m0;                              // rows beyond M: the last row again
-        const int row = (t < left) ? t : (int)left;
-        dma16(h + m0 * r, (uint32_t)(row * r * 4 + c * 16), hbuf0 + j * 1024);
+        if (i < H_TRANSFERS) {
+            const int j = wave * H_TRANSFERS + i;
+            const int tok = j * 8 + (ln >> 3);
+            const int c = ((ln & 7) ^ (tok >> 1)) & ptm & 7;
+            const int64_t left = M - 1 - t.m0;                        // rows beyond M: the last row again
+            const int row = (tok < left) ? tok : (int)left;
+            dma16(h + t.m0 * r, (uint32_t)(row * r * 4 + c * 16), hbuf0 + j * 1024);
+        } else if (i < H_TRANSFERS + 2) {
+            const int j = wave * 2 + i - H_TRANSFERS, row = 2 * j + (ln >> 5);        // r = 16: rows 16 .. 31 repeat row 15
+            dma16(L2 + l2_tile * t.n0, (uint32_t)((row < l2_rows ? row : l2_rows) * N * 2 + l2_piece(row, ln & 31) * 16), l2buf0 + j * 1024);
+        } else {
+            dma16(bias + b_tile * t.n0, (uint32_t)ln * 16, ring0 + OFF_B);
+        }
     };
 
     const uint32_t rd_a = G::OFF_A + (kh * BM + wm * (32 * MT) + l32) * 16;
@@ -797,19 +805,19 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
         }
     };
     float16v y[2][MT];
-    auto mma_group = [&](const Operands& o, auto JC) {
-        constexpr int j = decltype(JC)::value;
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni) {
-            const int8v a = {(int)o.wf[ni].x, (int)o.wf[ni].y, (int)o.wf[ni].z, (int)o.wf[ni].w, 0, 0, 0, 0};
-#pragma unroll
-            for (int mi = 0; mi < MT; ++mi) {
-                const int8v b = {(int)o.xf[mi].x, (int)o.xf[mi].y, (int)o.xf[mi].z, (int)o.xf[mi].w, 0, 0, 0, 0};
-                y[ni][mi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, y[ni][mi], 4, 4, j, (int)o.sw[ni], j, (int)o.sx[mi]);
-            }
-        }
-    };
     auto next_slot = [&](const uint32_t c) { return (c == ring0 + (NS - 1) * G::STAGE) ? ring0 : c + G::STAGE; };
+
+    // the L2 fragments of the tile that starts next, from where lr_request has put its rows
+    bf16x8 l2[2][2];
+    auto take_l2 = [&] {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) l2[ks][ni] = l2_fragment(l2buf0 + ks * (16 * 512), wn * 64 + ni * 32, ln);
+        __syncthreads();                                              // the rows' place is free for the store
+    };
 
     int id = blockIdx.x;
     {
@@ -819,9 +827,10 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
     if (id < 0) return;
     TileAddr T = tile_addr(id);
     uint32_t cur = ring0;                                             // slot of the current tile's stage 0
+    int stores_counted = 0;                                           // the previous tile's 16 stores stand behind its transfers
     {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) h_request(T.m0, i);         // the first tile's h rows: requested first, awaited below
+        for (int i = 0; i < LR_TRANSFERS; ++i) lr_request(T, i);      // the first tile's: requested first, awaited below
         uint32_t sl = cur;
         for (int s = 0; s < NS; ++s) {
             stage_issue(T, s, sl);
@@ -829,8 +838,8 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
         }
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NS * NDMA) : "memory");
         __syncthreads();
+        take_l2();
     }
-
     // What a stage does once its first group is multiplied: the stage after it (of this tile or of the next) is awaited
     // and made visible, and the slot takes stage s + NS of this tile (SAME) or, when the tile has no such stage left,
     // stage s + NS - nstages of the block's next tile (NEXT).  END: the tile's last stage, whose successor's operands
@@ -844,23 +853,18 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
         // from the compiler here, it is redone per tile instead of being kept in (spilled) registers across the K loops
         int lane_t = lane;
         asm volatile("" : "+v"(lane_t));
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < MT; ++b)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) y[a][b][i] = 0.0f;
-        // y starts as the low-rank term plus the bias (eq. 7, 11).  The tile's h rows are in LDS: requested during the
-        // previous tile's first stages (by every wave, each of which has since waited for younger transfers and passed
-        // barriers), or before the loop for the block's first tile.
+        // y starts as the low-rank term plus the bias (eq. 7, 11), whose operands were requested during the previous tile's
+        // first stages (by every wave, each of which has since waited for younger transfers and passed barriers), or before
+        // the loop for the block's first tile.
         const int th = wm * (32 * MT) + (lane_t & 31);               // this lane's token of block 0; the rotation is the same for
         const int rot = (th >> 1) & ptm;                             // all its blocks (32 tokens apart)
-        const uint32_t hrow = hbuf0 + th * 128;
-        add_lowrank_bias_from<2, MT>(y, [&](const int mi, const int k) {
-            const uint4 v = lds_read16(hrow + (((k >> 2) ^ rot) << 4) + mi * (32 * 128));
-            return float4{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-        }, L2, bias, T.n0 + wn * 64, N, r, lane_t);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * NDMA) : "memory");    // stage 0 of this tile
+        const uint32_t hrow = hbuf0 + th * 128, brow = ring0 + OFF_B + (wn * 64 + 4 * (lane_t >> 5)) * 4;
+        lowrank_bias_of<MT>(y, l2,
+                            [&](const int mi, const int ks, const int half) {
+                                return lds_read16(hrow + (((4 * ks + 2 * (lane_t >> 5) + half) ^ rot) << 4) + mi * (32 * 128));
+                            },
+                            [&](const int ni, const int q) { return lds_read16(brow + ni * 128 + q * 32); }, r, has_bias);
+        wait_left<(NS - 1) * NDMA>(stores_counted);                             // stage 0 of this tile
         __syncthreads();
         fetch(op0, cur, 0);
 
@@ -895,24 +899,30 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
         // Between the two groups of a stage stand only the wait and the barrier: the stage after this one is awaited
         // and made visible, and this stage's slot is free (every read of it was requested during the first group).
         // The second group's instructions then also carry the slot's new transfer requests, one each.
-        // HC >= 0: the instructions left over also request transfers HC, HC + 1, ... of the NEXT tile's h rows.  These
-        // are younger than the operand transfers the waits count, so every wait holds for at least what it names.
+        // HC >= 0: the instructions left over also request transfers HC, HC + 1, ... of the NEXT tile's low-rank term.  These
+        // are younger than the operand transfers the waits count, so every wait holds for at least what it names.  In a
+        // tile's first stages the previous tile's stores are still under way, older than what those stages request: stage 0
+        // awaits stage 1 (behind it: stage 2, the stores), stage 1 stage 2 (the stores, stage 3 and four of these).
         auto stage_body = [&](const int s, const uint32_t c, const uint32_t nxt, auto SAMEC, auto ENDC, auto HCC) {
             constexpr bool SAME = decltype(SAMEC)::value, END = decltype(ENDC)::value;
             constexpr int HC = decltype(HCC)::value;
-            mma_with_fetch(op0, IC<0>{}, op1, c, 1, true, [](int) {});
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NDMA) : "memory");
+            mma_with_fetch(op0, IC<0>{}, op1, c, 1, true, [&](const int p) {
+                if (HC == 3 && p == 0) lr_request(T1, LR_TRANSFERS - 1);
+            });
+            if (HC == 0) wait_left<NDMA>(stores_counted);
+            else if (HC == 3) wait_left<NDMA + 4>(stores_counted);
+            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NDMA) : "memory");
             __syncthreads();
             mma_with_fetch(op1, IC<1>{}, op0, nxt, 0, !END, [&](const int p) {
                 if (p >= NDMA) {
-                    if (HC >= 0) h_request(T1.m0, HC + p - NDMA);
+                    if (HC >= 0) lr_request(T1, HC + p - NDMA);
                 } else if (SAME) stage_piece(T, s + NS, c, p);
                 else stage_piece(T1, s + NS - nstages, c, p);
             });
         };
         int s = 0;
         {
-            static_assert(NDMA == 5, "three free instructions per stage: the four h transfers take two stages");
+            static_assert(NDMA == 5 && NS == 3, "three free instructions per stage: h and L2 take two stages, the bias one of a first group");
             uint32_t nxt = next_slot(cur);
             stage_body(0, cur, nxt, IC<1>{}, IC<0>{}, IC<0>{});
             cur = nxt;
@@ -934,6 +944,7 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
         stage_body(s, cur, next_slot(cur), IC<0>{}, IC<1>{}, IC<-1>{});
         cur = next_slot(cur);                                         // where the next tile's stage 0 went
 
+        take_l2();
         // ---- store: the ring belongs to the next tile by now, so the transposition uses the area behind it.  (The
         // emitting epilogues stay with the four-wave kernel: alone on its CU a block would run their vector-ALU work,
         // about 10 k clocks per tile, beside nothing; measured 1.83 ms against 1.58 ms for the C3 up-projection.)
@@ -941,45 +952,10 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
         asm volatile("" : "+v"(lane_s));                              // the store's address arithmetic stays behind the K loop
         if (out_f32) {
             store_tile_f32<2, MT>(y, reinterpret_cast<float*>(yout), ldy, mw, T.n0 + wn * 64, M, lane_s);
+            stores_counted = 0;
         } else {
-            uint16_t* yw = reinterpret_cast<uint16_t*>(yout) + mw * ldy + T.n0 + wn * 64;
-            // One accumulator block (32 tokens x 32 channels) at a time through this wave's LDS region: a lane writes its
-            // token's 4-channel pieces, then four lanes store a token's 64 bytes.  Software-pipelined: a block's two
-            // reads are requested together, and the NEXT block is converted and written behind them, before the wait
-            // for their data -- LDS serves a wave's requests in order, so the reads see the old block and the writes
-            // land after them.  (One read, wait, store at a time, the 32 LDS round trips were the whole store phase.)
-            const int l32s = lane_s & 31, khs = lane_s >> 5;
-            const uint32_t wr0 = store0 + l32s * YROW32 + 8 * khs;
-            const int rsub = lane_s >> 2, c16 = lane_s & 3;
-            const uint32_t rd0 = store0 + rsub * YROW32 + c16 * 16;
-            uint16_t* const yl = yw + (int64_t)rsub * ldy + c16 * 8;
-            const int64_t rows_left = M - mw - rsub;                   // this lane stores rows rsub + 16 it + 32 c
-            auto cvt_write = [&](auto CC, auto NIC) {
-                constexpr int c = decltype(CC)::value, ni = decltype(NIC)::value;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint2 o = {f2_bf16_rne(y[ni][c][4 * q + 0], y[ni][c][4 * q + 1]),
-                                     f2_bf16_rne(y[ni][c][4 * q + 2], y[ni][c][4 * q + 3])};
-                    lds_write8_pinned(wr0 + 16 * q, o);
-                }
-            };
-            auto read_store = [&](auto CC, auto NIC, auto next) {
-                constexpr int c = decltype(CC)::value, ni = decltype(NIC)::value;
-                const uint4 v0 = lds_read16_pinned(rd0), v1 = lds_read16_pinned(rd0 + 16 * YROW32);
-                next();
-                if (32 * c < rows_left) *reinterpret_cast<uint4*>(yl + (int64_t)(32 * c) * ldy + ni * 32) = v0;
-                if (32 * c + 16 < rows_left) *reinterpret_cast<uint4*>(yl + (int64_t)(32 * c + 16) * ldy + ni * 32) = v1;
-            };
-            static_assert(MT == 4, "four 32-token chunks");
-            cvt_write(IC<0>{}, IC<0>{});
-            read_store(IC<0>{}, IC<0>{}, [&] { cvt_write(IC<0>{}, IC<1>{}); });
-            read_store(IC<0>{}, IC<1>{}, [&] { cvt_write(IC<1>{}, IC<0>{}); });
-            read_store(IC<1>{}, IC<0>{}, [&] { cvt_write(IC<1>{}, IC<1>{}); });
-            read_store(IC<1>{}, IC<1>{}, [&] { cvt_write(IC<2>{}, IC<0>{}); });
-            read_store(IC<2>{}, IC<0>{}, [&] { cvt_write(IC<2>{}, IC<1>{}); });
-            read_store(IC<2>{}, IC<1>{}, [&] { cvt_write(IC<3>{}, IC<0>{}); });
-            read_store(IC<3>{}, IC<0>{}, [&] { cvt_write(IC<3>{}, IC<1>{}); });
-            read_store(IC<3>{}, IC<1>{}, [] {});
+            stores_counted = store_walked_bf16<MT>(y, l2buf0 + wave * WALK_STORE_BYTES, lane_s,
+                                                   reinterpret_cast<uint16_t*>(yout) + mw * ldy + T.n0 + wn * 64, ldy, M - mw);
         }
         if (nid < 0) break;
         id = nid;
@@ -1066,12 +1042,13 @@ static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const v
     const int walkers = walking_blocks();
     const MxTile tile = mx_best(rows, N, K, walkers).tile;
     if (tile == MxTile::T256x256 && mx_walks((int)((rows + 255) / 256), N, K, walkers)) {
-        // one block per CU walking its tiles.  Without a low-rank branch the kernel's h transfers still run (they have no
-        // branch): give them the codes to read
+        // one block per CU walking its tiles.  Without a low-rank branch or a bias the kernel's transfers for them still run
+        // (they have no branch): give them the codes to read
         const float* hrows = (r > 0) ? h : (const float*)qx;
+        const uint16_t* l2rows = (r > 0) ? (const uint16_t*)L2 : (const uint16_t*)qx;
         hipLaunchKernelGGL((gemm_mx_persistent_kernel<4>), dim3((unsigned)walkers), dim3(512), 0, stream,
-                           qx, (const uint16_t*)sxe, (const uint4*)base, wsc, hrows, (const uint16_t*)L2, bias,
-                           M, N, K, r, y, ldy, out_f32, grid(256, 256));
+                           qx, (const uint16_t*)sxe, (const uint4*)base, wsc, hrows, l2rows, bias ? bias : (const float*)qx,
+                           M, N, K, r, bias != nullptr, y, ldy, out_f32, grid(256, 256));
     } else if (tile == MxTile::T256x256) {
         one_tile(gemm_mx_kernel<4, 4, MX_LAYER>, 256, 256, 512);
     } else if (tile == MxTile::T256x128) {
