@@ -14,8 +14,8 @@ struct MxPart {                  // tiles of a launch and its estimated cost, us
     double cost;
 };
 
-// The tile-walking kernel needs full 256-channel tiles, a K loop of at least five stages (two more than its ring), and
-// pays once every one of its `walkers` blocks has at least two tiles.
+// The tile-walking kernel needs full 256-channel tiles and a K loop of at least five stages (two more than its ring); with
+// two tiles and more for each of its `walkers` blocks its tiles cost less than blocks of their own.
 inline bool mx_walks(int mtiles, int N, int K, int walkers) {
     return N % 256 == 0 && K >= 576 && (int64_t)mtiles * (N / 256) >= 2 * (int64_t)walkers;
 }
@@ -61,27 +61,64 @@ inline double mx_few_cost(int64_t rows, int N, int K) {
 // smaller tiles pays where they would open another round of blocks for themselves (M = 2305, N = 13824: 70 tiles of
 // 256 x 256 on the busiest XCD's 32 CUs, 63 without the one row beyond 2304) and that round is longer than a launch, which
 // takes about 2 us at any K.  `tail_cost`: what a launch for the rest costs, in the unit of mx_best.
+struct MxSplit {
+    int64_t rows;
+    double cost;
+};
 template <class TailCost>
-int64_t mx_split(int64_t M, int N, int K, int walkers, TailCost tail_cost) {
+MxSplit mx_split(int64_t M, int N, int K, int walkers, TailCost tail_cost) {
     const int mtiles = (int)((M + 255) / 256);
-    double best = mx_best(M, N, K, walkers).cost;
-    int64_t rows = M;
+    MxSplit best{M, mx_best(M, N, K, walkers).cost};
     for (int mt = mtiles - 1; mt >= 1 && mt >= mtiles - 12; --mt) {
         const double c = mx_best((int64_t)mt * 256, N, K, walkers).cost + tail_cost(M - (int64_t)mt * 256) + 2.0;
-        if (c < 0.985 * best) {
-            best = c;
-            rows = (int64_t)mt * 256;
-        }
+        if (c < 0.985 * best.cost) best = MxSplit{(int64_t)mt * 256, c};
     }
-    return rows;
+    return best;
 }
 
-// Tokens of a layer that are best left to the tile kernels; the rest take the few-token kernel or smaller tiles.
+// The kernel whose blocks walk 256 x 256 tiles takes the tokens, or as many rows of tiles as fit full rounds of the CUs, where that is the cheapest.  Its tiles are
+// numbered evenly over the XCDs (svdq_tiles.h), so a round is 256 of them: 4.3 + 38 k us, k = K / 5120, and less for a
+// round that leaves CUs idle, whose clock rises (0.6 of it with a few tiles, 0.71 at five eighths of the CUs).  Measured, us:
+// 256 tiles 16.5, 19.2, 26.5, 50.7, 115 at K = 640, 1024, 2048, 5120, 13824, 260 tiles 23, 26, 38, 74, 178, 1280 tiles 53, 68,
+// 106, 220, 539.  With fewer than two fifths of the CUs in the last round the smaller tiles have to look a tenth slower: their
+// cost is a tenth too high there at K <= 2048 (M = 3300, N = 5120: 22 us at K = 1024, 33 at K = 2048).
+inline double mx_walk_cost(int64_t tiles, int K, int walkers) {
+    const double round = 4.3 + 37.8 * (K / 5120.0), full = (double)(tiles / walkers), f = (double)(tiles % walkers) / walkers;
+    return 7.5 + round * (full + (f == 0.0 ? 0.0 : f <= 0.65 ? 0.6 + 0.18 * f : 0.715 + 0.285 * (f - 0.65) / 0.35));
+}
+template <class TailCost>
+int64_t mx_walk_rows(int64_t M, int N, int K, int walkers, TailCost tail_cost) {
+    if (N % 256 || K < 576) return 0;
+    const int nt = N / 256;
+    const int64_t mt = (M + 255) / 256, rounds = (mt * nt + walkers - 1) / walkers;
+    int64_t best = 0;
+    double least = mx_split(M, N, K, walkers, tail_cost).cost;
+    for (int64_t r = rounds > 3 ? rounds - 2 : 1; r <= rounds; ++r) {
+        const int64_t m = r == rounds ? mt : r * walkers / nt;
+        if (m == 0) continue;
+        const int64_t rows = m >= mt ? M : m * 256;
+        const double c = mx_walk_cost(m * nt, K, walkers) + (rows < M ? 2.0 + tail_cost(M - rows) : 0.0);
+        const bool few = m * nt % walkers > 0 && 5 * (m * nt % walkers) < 2 * walkers;
+        if (c < (few ? 0.9 : 1.0) * least) {
+            least = c;
+            best = rows;
+        }
+    }
+    return best;
+}
+
+// The rest of a layer's tokens takes the few-token kernel or tiles.
+inline double mx_rest_cost(int64_t M, int64_t rest, int N, int K, int walkers) {
+    const double few = mx_few_cost(rest, N, K), tiles = mx_best(rest, N, K, walkers).cost;
+    return small_shape(rest, N, K) && small_reach(M, N, K) && few < tiles ? few : tiles;
+}
+// Tokens of a layer that are best left to the tile kernels other than the walking one; the rest as above.
 inline int64_t mx_layer_split(int64_t M, int N, int K, int walkers) {
-    return mx_split(M, N, K, walkers, [&](int64_t rest) {
-        const double few = mx_few_cost(rest, N, K), tiles = mx_best(rest, N, K, walkers).cost;
-        return small_shape(rest, N, K) && small_reach(M, N, K) && few < tiles ? few : tiles;
-    });
+    return mx_split(M, N, K, walkers, [&](int64_t rest) { return mx_rest_cost(M, rest, N, K, walkers); }).rows;
+}
+// ... and the walking one's
+inline int64_t mx_layer_walk_rows(int64_t M, int N, int K, int walkers) {
+    return mx_walk_rows(M, N, K, walkers, [&](int64_t rest) { return mx_rest_cost(M, rest, N, K, walkers); });
 }
 
 }  // namespace svdq

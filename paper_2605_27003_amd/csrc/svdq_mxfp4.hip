@@ -667,8 +667,8 @@ void gemm_mx_kernel(const uint8_t* __restrict__ qx, const uint16_t* __restrict__
 // store (6 k) stand beside a K loop of 62 k.  Here the ring never drains between tiles: the slots that the last
 // stages of a tile hand over take the first stages of the block's NEXT tile, so those arrive during the end of the
 // loop and the store, and the store transposes through its own LDS area behind a three-slot ring.  Tiles are taken
-// in the same XCD-aware order (tile ids b, b + gridDim, ...; gridDim a multiple of 8 keeps a block on one XCD's
-// share).  Same arithmetic, same order of operations per output as gemm_mx_kernel.
+// in an XCD-aware order of their own (svdq_tiles.h; ids b, b + gridDim, ...; gridDim a multiple of 8 keeps a block on
+// one XCD's share).  Same arithmetic, same order of operations per output as gemm_mx_kernel.
 //
 // The low-rank term's operands travel like the others: the first two stages of a tile request the NEXT tile's h rows
 // (256 tokens x r binary32), L2 rows and bias, in instruction slots that carry no operand request.
@@ -685,7 +685,7 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
                                const uint4* __restrict__ wfrag, const uint16_t* __restrict__ wscale,
                                const float* __restrict__ h, const uint16_t* __restrict__ L2, const float* __restrict__ bias,
                                int64_t M, int N, int K, int r, int has_bias, void* __restrict__ yout, int64_t ldy, int out_f32,
-                               const TileGrid tg) {
+                               const WalkGrid tg) {
     constexpr int WNC = 4;
     using G = MxGeom<MT, WNC>;
     constexpr int BM = G::BM, NDMA = G::NDMA, NS = 3;
@@ -704,16 +704,7 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
     const int ptm = (r >> 2) - 1;                                     // 16-byte pieces per token of h, less one; r is 0, 16 or 32
     constexpr int H_TRANSFERS = 4, LR_TRANSFERS = 7;                  // 1-KB transfers per wave and tile: h 4, L2 2, the bias (all waves the same)
 
-    // tile ids: the one-tile kernel's order (svdq_tiles.h), of which this block takes ids b, b + gridDim, ...
-    const int total = tile_ids(tg);
-    auto decode = [&](const int id, int& mt, int& nt) { return tile_of(tg, id, mt, nt); };
-    auto next_valid = [&](int id) {
-        for (id += gridDim.x; id < total; id += gridDim.x) {
-            int mt, nt;
-            if (decode(id, mt, nt)) return id;
-        }
-        return -1;
-    };
+    auto exists = [&](const int id) { return (id >> 3) < tg.chunk && (id & 7) * tg.chunk + (id >> 3) < tg.mtiles * tg.ntiles; };
 
     // ---- staging (the eight-wave assignment of gemm_mx_kernel); what depends on the tile sits in TileAddr
     const int cj = wave >> 2, sp = (wave >> 1) & 1, q0 = 2 * (wave & 1), nb0 = 2 * (wave & 3);
@@ -731,7 +722,7 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
     };
     auto tile_addr = [&](const int id) {
         int mt, nt;
-        decode(id, mt, nt);
+        walk_tile(tg, id, mt, nt);
         TileAddr t;
         t.m0 = (int64_t)mt * BM;
         t.n0 = nt * G::BN;
@@ -820,11 +811,7 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
     };
 
     int id = blockIdx.x;
-    {
-        int mt, nt;
-        if (!decode(id, mt, nt)) id = next_valid(id);
-    }
-    if (id < 0) return;
+    if (!exists(id)) return;
     TileAddr T = tile_addr(id);
     uint32_t cur = ring0;                                             // slot of the current tile's stage 0
     int stores_counted = 0;                                           // the previous tile's 16 stores stand behind its transfers
@@ -846,8 +833,9 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
     // the next tile requests itself.  The block's last tile "prefetches" its own first stages again: three stages
     // nobody reads, for a loop without a third variant.
     while (true) {
-        const int nid = next_valid(id);
-        const TileAddr T1 = tile_addr(nid >= 0 ? nid : id);
+        const int nid = id + (int)gridDim.x;
+        const bool more = exists(nid);
+        const TileAddr T1 = tile_addr(more ? nid : id);
         const int64_t mw = T.m0 + wm * (32 * MT);
         // the per-lane address arithmetic of the low-rank term and of the store is the same for every tile; hidden
         // from the compiler here, it is redone per tile instead of being kept in (spilled) registers across the K loops
@@ -957,7 +945,7 @@ void gemm_mx_persistent_kernel(const uint8_t* __restrict__ qx, const uint16_t* _
             stores_counted = store_walked_bf16<MT>(y, l2buf0 + wave * WALK_STORE_BYTES, lane_s,
                                                    reinterpret_cast<uint16_t*>(yout) + mw * ldy + T.n0 + wn * 64, ldy, M - mw);
         }
-        if (nid < 0) break;
+        if (!more) break;
         id = nid;
         T = T1;
     }
@@ -1022,7 +1010,30 @@ static int cu_count() {
 // the tile order)
 int walking_blocks() { return cu_count() / 8 * 8; }
 
-int64_t mx_main_rows(int64_t M, int N, int K) { return mx_layer_split(M, N, K, walking_blocks()); }
+// Where the walking kernel takes a part of the tokens, the rest is for the few-token kernel if that is cheaper than tiles.
+int64_t mx_main_rows(int64_t M, int N, int K) {
+    const int walkers = walking_blocks();
+    const int64_t walked = mx_layer_walk_rows(M, N, K, walkers);
+    if (walked == 0) return mx_layer_split(M, N, K, walkers);
+    return walked < M && mx_rest_cost(M, M - walked, N, K, walkers) < mx_best(M - walked, N, K, walkers).cost ? walked : M;
+}
+
+static bool mx_can_walk(int N, int K) { return N % 256 == 0 && K >= 576; }
+
+// Tokens [begin, end), begin a multiple of 256, on 256 x 256 tiles, one block per CU walking its tiles.  Without a low-rank
+// branch or a bias the kernel's transfers for them still run (they have no branch): give them the codes to read.
+static hipError_t launch_mx_walk(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
+                                 const float* h, const void* L2, const float* bias,
+                                 int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
+                                 hipStream_t stream) {
+    const uint8_t* base = (const uint8_t*)w_packed;
+    hipLaunchKernelGGL((gemm_mx_persistent_kernel<4>), dim3((unsigned)walking_blocks()), dim3(512), 0, stream,
+                       qx, (const uint16_t*)sxe, (const uint4*)base, (const uint16_t*)(base + mx_wfrag_bytes(N, K)),
+                       r > 0 ? h : (const float*)qx, r > 0 ? (const uint16_t*)L2 : (const uint16_t*)qx, bias ? bias : (const float*)qx,
+                       M, N, K, r, bias != nullptr, y, ldy, out_f32,
+                       make_walk_grid((int)((end - begin + 255) / 256), N / 256, (int)(begin / 256)));
+    return hipGetLastError();
+}
 
 // The tiles of tokens [begin, end), begin a multiple of 256.
 static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
@@ -1039,16 +1050,9 @@ static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const v
                            qx, (const uint16_t*)sxe, (const uint4*)base, wsc, h, (const uint16_t*)L2, bias,
                            M, N, K, r, y, ldy, out_f32, tg, MxNext{});
     };
-    const int walkers = walking_blocks();
-    const MxTile tile = mx_best(rows, N, K, walkers).tile;
-    if (tile == MxTile::T256x256 && mx_walks((int)((rows + 255) / 256), N, K, walkers)) {
-        // one block per CU walking its tiles.  Without a low-rank branch or a bias the kernel's transfers for them still run
-        // (they have no branch): give them the codes to read
-        const float* hrows = (r > 0) ? h : (const float*)qx;
-        const uint16_t* l2rows = (r > 0) ? (const uint16_t*)L2 : (const uint16_t*)qx;
-        hipLaunchKernelGGL((gemm_mx_persistent_kernel<4>), dim3((unsigned)walkers), dim3(512), 0, stream,
-                           qx, (const uint16_t*)sxe, (const uint4*)base, wsc, hrows, l2rows, bias ? bias : (const float*)qx,
-                           M, N, K, r, bias != nullptr, y, ldy, out_f32, grid(256, 256));
+    const MxTile tile = mx_best(rows, N, K, walking_blocks()).tile;
+    if (tile == MxTile::T256x256 && mx_can_walk(N, K)) {
+        return launch_mx_walk(qx, sxe, w_packed, h, L2, bias, M, begin, end, N, K, r, y, ldy, out_f32, stream);
     } else if (tile == MxTile::T256x256) {
         one_tile(gemm_mx_kernel<4, 4, MX_LAYER>, 256, 256, 512);
     } else if (tile == MxTile::T256x128) {
@@ -1064,8 +1068,16 @@ hipError_t launch_linear_mx(const uint8_t* qx, const uint8_t* sxe, const void* w
                             int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
                             hipStream_t stream) {
     const int walkers = walking_blocks();
-    const int64_t mid = begin + mx_split(end - begin, N, K, walkers, [&](int64_t rest) { return mx_best(rest, N, K, walkers).cost; });
-    hipError_t e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, begin, mid, N, K, r, y, ldy, out_f32, stream);
+    auto tail = [&](int64_t rest) { return mx_best(rest, N, K, walkers).cost; };
+    const int64_t walked = mx_walk_rows(end - begin, N, K, walkers, tail);
+    hipError_t e = hipSuccess;
+    if (walked) {
+        e = launch_mx_walk(qx, sxe, w_packed, h, L2, bias, M, begin, begin + walked, N, K, r, y, ldy, out_f32, stream);
+        begin += walked;
+        if (e != hipSuccess || begin == end) return e;
+    }
+    const int64_t mid = walked ? end : begin + mx_split(end - begin, N, K, walkers, tail).rows;
+    e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, begin, mid, N, K, r, y, ldy, out_f32, stream);
     if (e == hipSuccess && mid < end) e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, mid, end, N, K, r, y, ldy, out_f32, stream);
     return e;
 }
