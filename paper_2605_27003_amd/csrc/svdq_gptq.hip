@@ -10,8 +10,8 @@
 // condition numbers of 1e13 scales differ and at 1e15 codes), and there are no reductions other than max and one
 // sequential sum.  The published implementation factors H^-1 once (Cholesky) and reads the same numbers off the
 // factor; this form trades that for elementwise kernels: K^3 updates for the inverse, K^3 / 3 of H^-1 and K^2 N / 2
-// of the weights during the visit, taken in panels of 64 pivots (below), two at a time, so that the matrices cross HBM
-// once per 128 pivots.
+// of the weights during the visit, taken in panels of 64 pivots (below), four at a time, so that the matrices cross HBM
+// once per 256 pivots.
 #include <climits>
 #include <type_traits>
 
@@ -188,15 +188,25 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 //                  pivot (the tables below), and a column likewise, so the rows and columns are independent of each
 //                  other.  The pivots' columns and scaled rows, as they stood when taken, are saved.
 //   rank update    everything else receives its updates from the saved columns and rows, in pivot order, on the
-//                  binary64 matrix instruction.  Behind the first panel of a pair only the second panel's rows and
-//                  columns do; behind the second the rest takes both panels' 128 in one pass over memory.  One
-//                  block meanwhile does the same for the NEXT panel's diagonal block, takes that through its own 64
-//                  dependent steps and leaves the next panel's tables: a serial chain of about 40 us, which is what
-//                  the launch behind a pair's first panel takes.
+//                  binary64 matrix instruction.  Block 0 meanwhile brings the NEXT panel's diagonal block up to date, takes
+//                  it through its own 64 dependent steps and leaves the next panel's tables: a serial chain of about
+//                  44 us, which no launch is shorter than.
+// Only the strips (rows and columns) of the next panel have to be up to date when a launch ends.  The rest of the matrices
+// receives the updates of a whole batch of BATCH = 4 panels in one pass over memory, and its blocks are dealt over the four
+// launches of the next batch in whole rounds of one block per CU, beside the strips and the chain.  So at any time the
+// rest lacks up to two batches, which is what the rings of saved rows and columns hold, and a strip is brought up from
+// where the rest stands.  The diagonal block after the next one is brought up a panel early by a block of its own, so that
+// the chain begins with 64 updates instead of 512.
 // Same result as the pivot-by-pivot form bit for bit.  K = N = 5120: with a launch per pivot and step (25 600 of them)
-// 112 ms, of which the rank updates on the vector unit were 31.
-// Pairs: 19.56 -> 18.88 ms (the inverse's launches, us: 49 and 155 in turn).
+// 112 ms; updates of the rest behind every panel 19.56 ms, behind every second one (two passes of 155 us over the
+// inverse per 256 pivots, the others of 49 us waiting for the chain) 18.88, behind every fourth one, in rounds, 16.07:
+// 78 us each of the inverse's 80 launches, 44 to 162 the visit's.  (K = N = 512: 1.07 -> 1.05, 2048: 4.65 -> 4.20, 4096:
+// 11.85 -> 10.78.)  What bounds it: the matrix unit, 246e9 fused
+// multiply-subtracts (8.2 ms at the 60 TFLOP/s that a loop of these instructions reaches), and the serial path of a panel:
+// its kernel (20 to 25 us) and the chain.
 constexpr int PB = 64;
+constexpr int BATCH = 4;                         // panels whose updates of the rest are put off and done together
+constexpr int RING_PANELS = 2 * BATCH;           // whose saved rows and columns are kept; a power of two
 
 // ---- A vector of 64 elements (one row or column of the panel) lives in 16 lanes (a DPP row), four elements each.
 // Pivot 4 it + k is always element k of the row's lane 0: after every four pivots the vectors turn by one lane, so the
@@ -300,13 +310,16 @@ __device__ __forceinline__ bool diagonal_pass(double (&x)[4][4], double (*Rt)[PB
     return bad;
 }
 template <bool INV>
-__device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], PanelTables* __restrict__ out) {
+__device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], int* redo, PanelTables* __restrict__ out) {
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
         for (int j = 0; j < 4; ++j) out->D[4 * grp + v][4 * pos + j] = x[v][j];       // kept for a second pass
-    if (__syncthreads_or(diagonal_pass<INV, false>(x, Rt, ds, out))) {
+    if (threadIdx.x == 0) *redo = 0;                                  // ahead of the pass's barriers
+    if (diagonal_pass<INV, false>(x, Rt, ds, out)) *redo = 1;
+    __syncthreads();
+    if (*redo) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -333,13 +346,14 @@ template <bool INV>
 __global__ __launch_bounds__(256)
 void first_tables_kernel(const double* __restrict__ D, size_t ld, PanelTables* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
+    __shared__ int redo;
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
     double x[4][4];
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
         for (int j = 0; j < 4; ++j) x[v][j] = D[(size_t)(4 * grp + v) * ld + 4 * pos + j];
-    diagonal_block<INV>(x, Rt, ds, out);
+    diagonal_block<INV>(x, Rt, ds, &redo, out);
 }
 
 // Vectors per block of the panel kernels: 16 lane groups of two vectors.  Two vectors per group halve the LDS reads of
@@ -581,29 +595,46 @@ void visit_panel_kernel(const double* __restrict__ A, const double* __restrict__
     }
 }
 
-// ---- X[a][b] <- (..((X[a][b] - L[0][a] R[0][b]) - L[1][a] R[1][b]).. - L[depth - 1][a] R[depth - 1][b]) over rows
-// a0 + [0, rows) and columns b0 + [0, cols), leaving out the nskip indices from skip_a (rows) and skip_b (columns) on (rows
-// and cols count what is left) and the 64 x 64 block at (hole, hole).  L and R are [depth][ld].  rows % 64 == 0.
+// ---- X[a][b] <- (..(X[a][b] - L[q][a] R[q][b]) - L[q + 1][a] R[q + 1][b]).. over the pivots q of panels [base, to) that an
+// element has not had yet, in order, for rows a0 + [0, rows) and columns b0 + [0, cols), leaving out the nskip indices from
+// skip_a (rows) and skip_b (columns) on (rows and cols count what is left) and the 64 x 64 block at (hole, hole).  L and R are
+// rings of RING_PANELS panels' pivots, [64 RING_PANELS][ld].  own (the inverse): an element whose row or column belongs to
+// panel p of [base, to) stands as the panel kernel of p left it: it is to have the panels behind p.
 struct RankUpdate {
     double* X;
     const double *L, *R;
     size_t ldx, ldl, ldr;
-    int depth, a0, rows, b0, cols, skip_a, skip_b, nskip, hole;
-    int tiles_b, tiles;          // 128 x 128 tiles along b, and in all
-    bool backwards;              // every other update walks its tiles backwards, first through what is still in the caches
+    int a0, rows, b0, cols, skip_a, skip_b, nskip, hole;
+    int base, to;
+    int own;
+    int shape;                   // what a block of eight waves takes: 0: 128 x 256, 64 x 64 a wave; 1: 64 rows x 256, 32 x 64 a wave;
+                                 // 2: 256 rows x 64; 3: 64 x 64, 16 x 64 a wave on four waves; 4, 5: half of 1, 2, 16 x 64 a wave;
+                                 // 6: half of 0, 32 x 64 a wave
+    int tiles_a, tiles_b, tiles; // blocks along a and b, and of this launch (shapes 0 and 6: ids, a multiple of 8)
+    int first, count;            // this launch's blocks (shapes 0 and 6)
 };
-// The next panel's diagonal block (at index s0 of A), for the first block of a rank update: brought up to date with L
-// and R (none: it is already, as D), then through its own pivots (mode 1: inverse, 2: visit) into `next`.  Also puts the
+constexpr int MAX_UPDATES = 6;
+struct RankUpdates {
+    RankUpdate u[MAX_UPDATES];
+};
+__device__ __forceinline__ int first_pending(int base, int to, int own, int pa, int pb) {
+    int from = base;
+    if (own && pa >= base && pa < to) from = pa + 1;
+    if (own && pb >= from && pb < to) from = pb + 1;
+    return from;
+}
+// The next panel's diagonal block (panel s of A), for the first block of a rank update: brought up to panel `to` from L
+// and R (nothing to bring: it is `prev`'s), then through its own pivots (mode 1: inverse, 2: visit) into `next`.  Also puts the
 // finished diagonal block `prev` of the current panel (at p0) in place; null: nothing to put.
 struct Lookahead {
     double* A;
     const double *L, *R;
     const PanelTables* prev;
     PanelTables* next;
-    int depth, K, p0, s0, mode;
+    int from, to, K, p0, s0, mode;
 };
 
-// acc[i][k]: a wave's 16 NI x 64 elements through `depth` pivots (a multiple of 8); lane (j, kq) = (l % 16, l / 16) holds in acc[i][k][e]
+// acc[i][k]: a wave's 16 NI x 64 elements through the pivots of panels [from, to); lane (j, kq) = (l % 16, l / 16) holds in acc[i][k][e]
 // row 16 i + 4 e + kq, column wave_col(j, k): two neighbouring columns per lane, so that a row's accesses are 256
 // contiguous bytes of 16 bytes a lane.  Operands straight from global memory (L2): 64 x 64 elements per wave and 4
 // pivots are 16 matrix instructions (1024 clocks) on 6 loads, the next four pivots' requested while they run.
@@ -615,16 +646,18 @@ __device__ __forceinline__ double2 load2(const double* p, int d1) {
     return double2{p[0], p[d1]};
 }
 template <int NI, bool PAIR>
-__device__ __forceinline__ void update_chain(const int depth, double4v (&acc)[NI][4], const double* __restrict__ L, size_t ldl,
+__device__ __forceinline__ void update_chain(const int from, const int to, double4v (&acc)[NI][4], const double* __restrict__ L, size_t ldl,
                                              const double* __restrict__ R, size_t ldr, int lane, const int (&col)[2], const int (&d1)[2]) {
     const int j = lane & 15, kq = lane >> 4;
     double a[2][NI];
     double2 b[2][2];
+    const int steps = (to - from) * (PB / 4);
     auto request = [&](const int s, const int buf) {
+        const int q = ((from * PB + 4 * s) & (RING_PANELS * PB - 1)) + kq;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) a[buf][i] = -L[(size_t)(4 * s + kq) * ldl + 16 * i + j];
+        for (int i = 0; i < NI; ++i) a[buf][i] = -L[(size_t)q * ldl + 16 * i + j];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) b[buf][i] = load2<PAIR>(R + (size_t)(4 * s + kq) * ldr + col[i], d1[i]);
+        for (int i = 0; i < 2; ++i) b[buf][i] = load2<PAIR>(R + (size_t)q * ldr + col[i], d1[i]);
     };
     auto multiply = [&](const int buf) {
 #pragma unroll
@@ -633,22 +666,22 @@ __device__ __forceinline__ void update_chain(const int depth, double4v (&acc)[NI
             for (int k = 0; k < 4; ++k) acc[i][k] = mfma_f64(a[buf][i], (k & 1) ? b[buf][k >> 1].y : b[buf][k >> 1].x, acc[i][k]);
     };
     request(0, 0);
-    for (int s = 0; s < depth / 4; s += 2) {
+    for (int s = 0; s < steps; s += 2) {
         request(s + 1, 1);
         multiply(0);
-        if (s + 2 < depth / 4) request(s + 2, 0);
+        if (s + 2 < steps) request(s + 2, 0);
         multiply(1);
     }
 }
 
-__device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB], double (*ds)[2]) {
+__device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB], double (*ds)[2], int* redo) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, kq = lane >> 4;
     if (la.prev)
         for (int e = tid; e < PB * PB; e += 256) la.A[(size_t)(la.p0 + e / PB) * la.K + la.p0 + e % PB] = la.prev->D[e / PB][e % PB];
     if (la.mode == 0) return;
     const int grp = tid >> 4, pos = tid & 15;
     double x[4][4];
-    if (la.L) {
+    if (la.from < la.to) {
         double4v acc[1][4];
         const double* X = la.A + (size_t)(la.s0 + 16 * wave) * la.K + la.s0;
 #pragma unroll
@@ -656,7 +689,7 @@ __device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB]
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[0][k][e] = X[(size_t)(4 * e + kq) * la.K + wave_col(j, k)];
         const int col[2] = {2 * j, 32 + 2 * j}, d1[2] = {1, 1};
-        update_chain<1, true>(la.depth, acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, col, d1);
+        update_chain<1, true>(la.from, la.to, acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, col, d1);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -673,36 +706,23 @@ __device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB]
 #pragma unroll
             for (int i = 0; i < 4; ++i) x[v][i] = la.prev->D[4 * grp + v][4 * pos + i];
     }
-    if (la.mode == 1) diagonal_block<true>(x, Rt, ds, la.next);
-    else diagonal_block<false>(x, Rt, ds, la.next);
+    if (la.mode == 1) diagonal_block<true>(x, Rt, ds, redo, la.next);
+    else diagonal_block<false>(x, Rt, ds, redo, la.next);
 }
 
-// Block 0 looks ahead; the others take 128 x 128 elements of the matrix of u0, u1 or u2, 64 x 64 per wave.  Every element
-// is read and written once per `depth` updates, 16 bytes: with 64 HBM bounds the large matrices (K = 5120: 420 MB, 85 us
-// at the rate of a copy, and the matrix unit needs half of that), with 128 both take about as long.
-template <bool PAIR>
-__global__ __launch_bounds__(256, 2)
-void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const RankUpdate u2, const Lookahead la) {
-    __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
-    if (blockIdx.x == 0) {
-        look_ahead(la, Rt, ds);
-        return;
-    }
-    int t = (int)blockIdx.x - 1;
-    const bool first = t < u0.tiles, second = !first && t < u0.tiles + u1.tiles;
-    const RankUpdate u = first ? u0 : second ? u1 : u2;
-    t -= first ? 0 : second ? u0.tiles : u0.tiles + u1.tiles;
-    if (u.backwards) t = u.tiles - 1 - t;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+// a wave's 16 NI x 64 elements at row ia, column ib of what u leaves in
+template <int NI, bool PAIR>
+__device__ __forceinline__ void rank_update_wave(const RankUpdate& u, const int ia, const int ib, const int lane) {
     const int j = lane & 15, kq = lane >> 4;
-    const int ia = (t / u.tiles_b) * 128 + (wave >> 1) * 64, ib = (t % u.tiles_b) * 128 + (wave & 1) * 64;
     if (ia >= u.rows || ib >= u.cols) return;
-    int ga = u.a0 + ia, gb = u.b0 + ib;                     // 64-blocks do not straddle what is left out
+    int ga = u.a0 + ia, gb = u.b0 + ib;                     // a wave's rows and columns do not straddle what is left out
     if (ga >= u.skip_a) ga += u.nskip;
     if (gb >= u.skip_b) gb += u.nskip;
-    if (ga == u.hole && gb == u.hole) return;
+    if ((ga & ~(PB - 1)) == u.hole && gb == u.hole) return;
+    const int from = first_pending(u.base, u.to, u.own, ga / PB, gb / PB);
+    if (from >= u.to) return;
     double* X = u.X + (size_t)ga * u.ldx;
-    double4v acc[4][4];
+    double4v acc[NI][4];
     int col[2], d1[2];                                      // a column beyond the matrix re-reads one that exists
     bool in[2][2];
 #pragma unroll
@@ -714,7 +734,7 @@ void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const RankUpda
         d1[k] = in[k][1] ? 1 : 0;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -723,7 +743,7 @@ void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const RankUpda
                 acc[i][2 * k][e] = v.x;
                 acc[i][2 * k + 1][e] = v.y;
             }
-    update_chain<4, PAIR>(u.depth, acc, u.L + ga, u.ldl, u.R, u.ldr, lane, col, d1);
+    update_chain<NI, PAIR>(from, u.to, acc, u.L + ga, u.ldl, u.R, u.ldr, lane, col, d1);
     // the stores' addresses are formed again here; kept from the loads they would spill
 #pragma unroll
     for (int k = 0; k < 2; ++k) asm volatile("" : "+v"(col[k]));
@@ -731,7 +751,7 @@ void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const RankUpda
     for (int k = 0; k < 2; ++k)
         if (in[k][0]) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     double* to = X + (size_t)(16 * i + 4 * e + kq) * u.ldx + col[k];
@@ -745,16 +765,80 @@ void rank_update_kernel(const RankUpdate u0, const RankUpdate u1, const RankUpda
         }
 }
 
-void launch_rank_updates(RankUpdate u0, RankUpdate u1, RankUpdate u2, const Lookahead& la, bool backwards, hipStream_t stream) {
-    bool pair = true;
-    for (RankUpdate* u : {&u0, &u1, &u2}) {
-        u->tiles_b = (u->cols + 127) / 128;
-        u->tiles = (u->rows > 0 && u->cols > 0) ? u->tiles_b * ((u->rows + 127) / 128) : 0;
-        u->backwards = backwards;
-        pair = pair && u->ldx % 2 == 0 && u->ldr % 2 == 0;
+// Block 0 looks ahead; the others take blocks of the matrices of `us`, in turn.  Every element of the rest is read and
+// written once per batch of 256 updates, 16 bytes: the matrix unit bounds it (K = 5120: 220 us a batch at its rate, and
+// 420 MB, 70 us at the rate of a copy).  A round of 128 x 256 blocks takes 76 us for its 256 updates.
+template <bool PAIR>
+__global__ __launch_bounds__(512, 1)
+void rank_update_kernel(const RankUpdates us, const Lookahead la) {
+    __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
+    __shared__ int redo;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 256) look_ahead(la, Rt, ds, &redo);
+        return;
+    }
+    int t = (int)blockIdx.x - 1, which = 0;
+    while (which < MAX_UPDATES - 1 && t >= us.u[which].tiles) t -= us.u[which++].tiles;
+    const RankUpdate u = us.u[which];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (u.shape == 0 || u.shape == 6) {
+        // consecutive block ids go to the 8 XCDs in turn: an XCD takes a run of consecutive blocks, numbered in groups of
+        // eight along a, about 8 x 3 blocks whose L and R (256 and 512 KB a block) stay in its L2
+        const int chunk = u.tiles >> 3, n = (int)(blockIdx.x & 7) * chunk + (t >> 3);
+        if (n >= u.count) return;
+        const int m = u.first + n, sm = m / (8 * u.tiles_b), rem = m - sm * (8 * u.tiles_b);
+        const int width = u.tiles_a - 8 * sm < 8 ? u.tiles_a - 8 * sm : 8, tb = rem / width, ta = 8 * sm + rem - tb * width;
+        if (u.shape == 0) rank_update_wave<4, PAIR>(u, ta * 128 + (wave >> 2) * 64, tb * 256 + (wave & 3) * 64, lane);
+        else rank_update_wave<2, PAIR>(u, ta * 64 + (wave >> 2) * 32, tb * 256 + (wave & 3) * 64, lane);
+    } else if (u.shape >= 3) {
+        const bool flat = u.shape == 4;
+        rank_update_wave<1, PAIR>(u, flat ? (wave >> 1) * 16 : t * 128 + wave * 16, flat ? t * 128 + (wave & 1) * 64 : 0, lane);
+    } else {
+        const bool flat = u.shape == 1;
+        rank_update_wave<2, PAIR>(u, flat ? (wave >> 2) * 32 : t * 256 + wave * 32, flat ? t * 256 + (wave & 3) * 64 : 0, lane);
+    }
+}
+
+// an update's blocks, all of them
+RankUpdate whole(RankUpdate u) {
+    const int over_b[] = {256, 256, 64, 64, 128, 64, 256}, over_a[] = {128, 64, 256, 64, 64, 128, 64};
+    u.tiles_b = (u.cols + over_b[u.shape] - 1) / over_b[u.shape];
+    u.tiles_a = (u.rows + over_a[u.shape] - 1) / over_a[u.shape];
+    u.count = (u.rows > 0 && u.cols > 0 && u.base < u.to) ? u.tiles_b * u.tiles_a : 0;
+    u.tiles = u.shape == 0 || u.shape == 6 ? (u.count + 7) / 8 * 8 : u.count;
+    return u;
+}
+// `count` of them, behind the first `done` (or ahead of the last `done`)
+RankUpdate part_of(RankUpdate u, int done, int count, bool backwards) {
+    u = whole(u);
+    u.first = backwards ? u.count - done - count : done;
+    u.count = count;
+    u.tiles = (count + 7) / 8 * 8;
+    return u;
+}
+// How many of the `pending` blocks of a batch the next of `launches` launches takes, each of which has `fixed` blocks besides:
+// what fills whole rounds of `cus` blocks, as few of them as the batch needs (with room for the looking-ahead block and for
+// the ids that part_of adds: an XCD is given every eighth id, and one more than it has CUs is another round).
+int quota(int pending, int launches, int fixed, int cus) {
+    fixed += 16;
+    const int64_t all = pending + (int64_t)launches * fixed, slots = (int64_t)launches * cus;
+    const int take = (int)((all + slots - 1) / slots) * cus - fixed;
+    return launches <= 1 || take > pending ? pending : take < 0 ? 0 : take;
+}
+
+// One block per CU (with the kernel's own 33 KB more than half of its LDS), so that the block that looks ahead has its CU
+// for itself: beside another its dependent steps take 100 us instead of 50, as both want the binary64 unit.
+constexpr unsigned RANK_UPDATE_LDS = 52 * 1024;
+
+void launch_rank_updates(const RankUpdates& us, const Lookahead& la, hipStream_t stream) {
+    bool pair = true;                                  // rows aligned to 16 bytes: two columns per access
+    int blocks = 1;
+    for (const RankUpdate& u : us.u) {
+        blocks += u.tiles;
+        if (u.tiles) pair = pair && u.ldx % 2 == 0 && u.ldr % 2 == 0;
     }
     auto kern = pair ? rank_update_kernel<true> : rank_update_kernel<false>;
-    hipLaunchKernelGGL(kern, dim3(1 + u0.tiles + u1.tiles + u2.tiles), dim3(256), 0, stream, u0, u1, u2, la);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(512), RANK_UPDATE_LDS, stream, us, la);
 }
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -762,8 +846,8 @@ inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 }  // namespace
 
 size_t gptq_workspace_bytes(int N, int K) {
-    return up256((size_t)K * K * 8) + up256((size_t)K * N * 8) + 3 * up256((size_t)K * 2 * PB * 8) + up256((size_t)2 * PB * N * 8) +
-           2 * up256(sizeof(PanelTables)) + 256;
+    return up256((size_t)K * K * 8) + up256((size_t)K * N * 8) + 3 * up256((size_t)K * RING_PANELS * PB * 8) +
+           up256((size_t)RING_PANELS * PB * N * 8) + 2 * up256(sizeof(PanelTables)) + 256;
 }
 
 hipError_t launch_gptq_hessian(const void* x, int64_t ldx, const float* inv_lambda, int64_t M, int K, double* H,
@@ -787,11 +871,12 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     uint8_t* p = (uint8_t*)workspace;
     double* A = (double*)p;        p += up256((size_t)K * K * 8);
     double* W = (double*)p;        p += up256((size_t)K * N * 8);
-    // saved by the two panels of a pair, one behind the other
-    double* Lc = (double*)p;       p += up256((size_t)K * 2 * PB * 8);     // pivot columns         [2 PB][K]
-    double* Rr = (double*)p;       p += up256((size_t)K * 2 * PB * 8);     // scaled pivot rows     [2 PB][K]
-    double* Hr = (double*)p;       p += up256((size_t)K * 2 * PB * 8);     // rows of H^-1          [2 PB][K]
-    double* Err = (double*)p;      p += up256((size_t)2 * PB * N * 8);     // errors of the panel   [2 PB][N]
+    // saved by the panels, in a ring of two batches
+    constexpr size_t RING = (size_t)RING_PANELS * PB;
+    double* Lc = (double*)p;       p += up256((size_t)K * RING * 8);       // pivot columns         [RING][K]
+    double* Rr = (double*)p;       p += up256((size_t)K * RING * 8);       // scaled pivot rows     [RING][K]
+    double* Hr = (double*)p;       p += up256((size_t)K * RING * 8);       // rows of H^-1          [RING][K]
+    double* Err = (double*)p;      p += up256(RING * N * 8);               // errors of the panels  [RING][N]
     PanelTables* tabs[2];                                              // this panel's and the next one's
     for (auto& t : tabs) {
         t = (PanelTables*)p;
@@ -802,56 +887,88 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(256), 0, stream, R, H, add, N, K, A, W);
     const size_t ldk = (size_t)K, ldn = (size_t)N;
     constexpr int ALL = INT_MAX;                       // nothing left out
-    const RankUpdate none{A, nullptr, nullptr, ldk, ldk, ldk, PB, 0, 0, 0, 0, ALL, ALL, 0, -1, 1, 0, false};
-    // `depth` updates of A or W saved from row `from` of the pair's buffers on
-    auto of_inverse = [&](int from, int depth, int a0, int rows, int b0, int cols, int skip_a, int skip_b, int nskip, int hole) {
-        return RankUpdate{A, Lc + from * ldk, Rr + from * ldk, ldk, ldk, ldk, depth, a0, rows, b0, cols, skip_a, skip_b, nskip, hole, 1, 0, false};
-    };
-    auto of_weights = [&](int depth, int a0, int rows) {
-        return RankUpdate{W, Hr, Err, ldn, ldk, ldn, depth, a0, rows, 0, N, ALL, ALL, 0, -1, 1, 0, false};
-    };
     const int np = K / PB;
+    auto slot = [](int panel) { return (size_t)(panel % RING_PANELS) * PB; };
+    // rows [a0, a0 + rows) x columns [b0, b0 + cols) of what is left of the inverse (own), the visited inverse or the weights
+    auto update = [&](double* X, const double* L, const double* R, size_t ldx, bool own, int shape, int base, int to,
+                      int a0, int rows, int skip_a, int b0, int cols, int skip_b, int nskip, int hole) {
+        return RankUpdate{X, L, R, ldx, ldk, ldx, a0, rows, b0, cols, skip_a, skip_b, nskip, hole, base < 0 ? 0 : base, to, own, shape, 1, 1, 0, 0, 0};
+    };
+    const RankUpdate none = update(A, Lc, Rr, ldk, false, 0, 0, 0, 0, 0, ALL, 0, 0, ALL, 0, -1);
+    const int cus = walking_blocks();
+    // what panel t's strips have had when it is their turn; its diagonal block, a panel earlier (the one that a batch of
+    // updates of the rest would otherwise touch meanwhile is left out of that, as the batch's `hole`)
+    auto strip_base = [](int t) { return t % BATCH ? (t / BATCH - 1) * BATCH : t - 2 * BATCH; };
+    auto diag_base = [&](int t) { return t % BATCH == 1 ? t - 1 - 2 * BATCH : strip_base(t); };
+    // panel t's diagonal block up to panel t - 1, so that only that one's pivots stand ahead of its own
+    auto early = [&](int t) { return whole(update(A, Lc, Rr, ldk, false, 3, diag_base(t), t - 1, t * PB, PB, ALL, t * PB, PB, ALL, 0, -1)); };
+    // The strips have up to 512 updates ahead of them, 76 us where a wave has 32 rows of them, 38 where it has 16 (the looking
+    // ahead takes 44): in twice the blocks (shape + 3), where those open no round of their own
+    auto thin_strips = [&](int others, int length) { return others + length / 128 + 20 <= cus ? 3 : 0; };
+    // The same of the rest, for a batch that is less than a round of blocks per launch: 38 us instead of 76.  (Without the two
+    // rules K = N = 1536 takes 3.57 ms, with the first 3.37, with both 3.15; without batches 3.32.)
+    auto rest_shape = [&](int blocks, int launches, int length) { return 2 * blocks / launches + length / 128 + 20 <= cus ? 6 : 0; };
     int cur = 0;                                       // tabs[cur]: the current panel's
+    int done_a = 0, done_w = 0;                        // blocks of the batch's updates that its launches have had
     hipLaunchKernelGGL(first_tables_kernel<true>, dim3(1), dim3(256), 0, stream, A, ldk, tabs[cur]);
     for (int b = 0; b < np; ++b) {                     // the inverse, one panel of pivots at a time
-        const int p0 = b * PB, half = (b & 1) * PB;    // half: this panel's place in the pair's buffers
+        const int p0 = b * PB, t = b + 1, batch = b / BATCH * BATCH;
+        const bool back = batch / BATCH & 1;
         if (np > 1)
             hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (K - PB) / PVECS), dim3(256), 0, stream, A, K, p0, tabs[cur],
-                               Lc + half * ldk, Rr + half * ldk);
-        // next: the following panel, and after the last one the first panel of the visit
-        const int s0 = (b + 1 < np) ? p0 + PB : 0;
-        const bool same = s0 == p0;                    // a single panel: its own finished block is what is visited
-        // What the next diagonal block has not had yet: both panels of a pair, but the second's only where it lies in
-        // the first (two panels: the visit starts there).
-        const int from = (half && s0 == p0 - PB) ? PB : 0, depth = half + PB - from;
-        const Lookahead la{A, same ? nullptr : Lc + from * ldk, Rr + from * ldk, tabs[cur], tabs[cur ^ 1],
-                           depth, K, p0, s0, (b + 1 < np) ? 1 : 2};
-        if (half) {
-            // everything outside both panels; then the first panel's rows and columns, which only the second's pivots are left for
-            const int q0 = p0 - PB;
-            launch_rank_updates(of_inverse(0, 2 * PB, 0, K - 2 * PB, 0, K - 2 * PB, q0, q0, 2 * PB, s0),
-                                of_inverse(PB, PB, q0, PB, 0, K - PB, ALL, p0, PB, s0),
-                                of_inverse(PB, PB, 0, K - 2 * PB, q0, PB, q0, ALL, 2 * PB, s0), la, b & 2, stream);
-        } else if (b + 1 < np) {                       // the second panel's rows, and its columns in the rows of neither
-            launch_rank_updates(of_inverse(0, PB, s0, PB, 0, K - PB, ALL, p0, PB, s0),
-                                of_inverse(0, PB, 0, K - 2 * PB, s0, PB, p0, ALL, 2 * PB, s0), none, la, false, stream);
-        } else {                                       // a last panel without a second
-            launch_rank_updates(of_inverse(0, PB, 0, K - PB, 0, K - PB, p0, p0, PB, same ? -1 : s0), none, none, la, b & 2, stream);
+                               Lc + slot(b) * ldk, Rr + slot(b) * ldk);
+        RankUpdates us{{none, none, none, none, none, none}};
+        Lookahead la{A, Lc, Rr, tabs[cur], tabs[cur ^ 1], b, t, K, p0, t * PB, 1};
+        if (t < np) {
+            const int s0 = t * PB, base = strip_base(t);
+            const int left = batch * PB, nleft = K - left < (BATCH + 1) * PB ? K - left : (BATCH + 1) * PB;
+            const int launches = (batch + BATCH < np ? BATCH : np - 1 - batch) - (b - batch);   // the last launch of all is below
+            RankUpdate rest = update(A, Lc, Rr, ldk, true, 0, batch - BATCH, batch, 0, K - nleft, left, 0, K - nleft, left, nleft,
+                                     (batch + BATCH + 1) * PB);
+            rest.shape = rest_shape(whole(rest).count, launches + (b - batch), 2 * (K - PB));
+            if (b == batch) done_a = 0;
+            const int na = whole(rest).count - done_a, thin = thin_strips(na / launches, 2 * (K - PB));
+            us.u[0] = whole(update(A, Lc, Rr, ldk, true, 1 + thin, base, t, s0, PB, ALL, 0, K - PB, s0, PB, -1));
+            us.u[1] = whole(update(A, Lc, Rr, ldk, true, 2 + thin, base, t, 0, K - PB, s0, s0, PB, ALL, PB, -1));
+            if (t + 1 < np) us.u[2] = early(t + 1);
+            const int n = quota(na, launches, us.u[0].tiles + us.u[1].tiles + us.u[2].tiles, cus);
+            us.u[3] = part_of(rest, done_a, n, back);
+            done_a += n;
+        } else {
+            // everything that is pending; the first diagonal block of the visit is looked ahead for
+            const int base = batch + 1 < np ? batch : batch - BATCH;                 // a last batch of one panel had no launch before
+            us.u[0] = whole(update(A, Lc, Rr, ldk, true, 0, base, t, 0, K, ALL, 0, K, ALL, 0, 0));
+            la.from = base > 0 ? base : 1;                                           // panel 0 is behind its own pivots
+            la.s0 = 0;
+            la.mode = 2;
         }
+        launch_rank_updates(us, la, stream);
         cur ^= 1;
     }
     for (int b = 0; b < np; ++b) {                     // the weights, one panel (= one 64-group) at a time
-        const int i0 = b * PB, i1 = i0 + PB, rest = K - i1, half = (b & 1) * PB;
+        const int i0 = b * PB, t = b + 1, i1 = i0 + PB, rest = K - i1, batch = b / BATCH * BATCH;
         hipLaunchKernelGGL(visit_panel_kernel, dim3(2 * (rest / PVECS) + (N + PVECS - 1) / PVECS), dim3(256), 0, stream,
-                           A, W, N, K, i0, tabs[cur], Lc + half * ldk, Hr + half * ldk, Rr + half * ldk, Err + half * ldn, qw, sw);
+                           A, W, N, K, i0, tabs[cur], Lc + slot(b) * ldk, Hr + slot(b) * ldk, Rr + slot(b) * ldk, Err + slot(b) * ldn, qw, sw);
         if (rest > 0) {                                // the deferred updates of what is behind the panel
-            const Lookahead la{A, Lc, Rr, nullptr, tabs[cur ^ 1], half + PB, K, 0, i1, 2};
-            if (half)
-                launch_rank_updates(of_weights(2 * PB, i1, rest), of_inverse(0, 2 * PB, i1, rest, i1, rest, ALL, ALL, 0, i1), none,
-                                    la, b & 2, stream);
-            else                                       // of the second panel's rows and columns only
-                launch_rank_updates(of_weights(PB, i1, PB), of_inverse(0, PB, i1, PB, i1, rest, ALL, ALL, 0, i1),
-                                    of_inverse(0, PB, i1 + PB, rest - PB, i1, PB, ALL, ALL, 0, -1), la, false, stream);
+            const int base = strip_base(t), behind = (batch + BATCH + 1) * PB, far = K - behind;
+            const bool back = batch / BATCH & 1;
+            RankUpdate of_w = update(W, Hr, Err, ldn, false, 0, batch - BATCH, batch, behind, far, ALL, 0, N, ALL, 0, -1);
+            RankUpdate of_a = update(A, Lc, Rr, ldk, false, 0, batch - BATCH, batch, behind, far, ALL, behind, far, ALL, 0, behind);
+            of_w.shape = of_a.shape = rest_shape(whole(of_w).count + whole(of_a).count, BATCH, 2 * (K - batch * PB) + N);
+            if (b == batch) done_a = done_w = 0;
+            const int nw = whole(of_w).count - done_w, na = whole(of_a).count - done_a, launches = BATCH - (b - batch);
+            const int thin = thin_strips((nw + na) / launches, 2 * rest + N);
+            RankUpdates us{{
+                whole(update(W, Hr, Err, ldn, false, 1 + thin, base, t, i1, PB, ALL, 0, N, ALL, 0, -1)),
+                whole(update(A, Lc, Rr, ldk, false, 1 + thin, base, t, i1, PB, ALL, i1 + PB, rest - PB, ALL, 0, -1)),
+                whole(update(A, Lc, Rr, ldk, false, 2 + thin, base, t, i1 + PB, rest - PB, ALL, i1, PB, ALL, 0, -1)),
+                t + 1 < np ? early(t + 1) : none, none, none}};
+            const int n = quota(nw + na, launches, us.u[0].tiles + us.u[1].tiles + us.u[2].tiles + us.u[3].tiles, cus);
+            us.u[4] = part_of(of_w, done_w, n < nw ? n : nw, back);
+            us.u[5] = part_of(of_a, done_a, n < nw ? 0 : n - nw, back);
+            done_w += us.u[4].count;
+            done_a += us.u[5].count;
+            launch_rank_updates(us, Lookahead{A, Lc, Rr, nullptr, tabs[cur ^ 1], b, t, K, 0, i1, 2}, stream);
         }
         cur ^= 1;
     }

@@ -45,3 +45,39 @@ def test_hessian_edges(svdq, oracle, M, K, ld):
     H = oracle.gptq_hessian(np.ascontiguousarray(x[:, :K]), il)
     d = np.sqrt(np.diag(H))
     assert np.all(np.abs(Hg.cpu().numpy() - H) <= (M + 2) * 2.0 ** -52 * np.outer(d, d))
+
+
+def panels_hessian(seed, panels, classes):
+    """A Hessian that couples panel p (64 channels) with the panels p + i classes only: GPTQ then visits each class for
+    itself, and every other update subtracts zero."""
+    g = np.random.default_rng(seed)
+    K = 64 * panels
+    cls = (np.arange(K) // 64) % classes
+    H = np.zeros((K, K))
+    for c in range(classes):
+        i = np.flatnonzero(cls == c)
+        z = np.round(8 * (g.standard_normal((2 * len(i), len(i))) + np.repeat(g.standard_normal((2 * len(i), len(i) // 8)), 8, axis=1)))
+        H[np.ix_(i, i)] = z.T @ z
+    return H, cls
+
+
+@pytest.mark.parametrize("panels,N,classes,channels", [
+    (7, 65, 1, None), (8, 64, 1, None), (9, 258, 1, None), (12, 31, 1, None), (13, 130, 1, None),   # the last batch of four: 3, 4, 1, 4, 1
+    (49, 30011, 7, 40)])                                  # more blocks of the rest than fit one round, in every stage
+def test_gptq_batches_of_panels(svdq, oracle, panels, N, classes, channels):
+    """Bit for bit the oracle's, whatever share of a batch of four panels the last one is, and where the batch's updates
+    take several rounds of blocks.  Channels are independent, and classes of panels that H does not couple too (the damping
+    term, relative to the mean of the diagonal, is added here): the large case is checked on some channels, by class."""
+    H, cls = panels_hessian(panels, panels, classes)
+    H[np.diag_indices_from(H)] += 0.01 * H.diagonal().mean()
+    g = np.random.default_rng(N)
+    R = (g.standard_normal((64 * panels, N), dtype=np.float32) * np.float32(0.02))
+    qw, sw = svdq.gptq_quantize(dev(R), torch.from_numpy(H).cuda(), damp=0.0)
+    torch.cuda.synchronize()
+    n = np.arange(N) if channels is None else np.unique(np.concatenate([[0, N - 1], g.integers(0, N, channels)]))
+    qw, sw = qw.cpu().numpy()[n], sw.cpu().numpy()[:, n]
+    for c in range(classes):
+        k = np.flatnonzero(cls == c)
+        oq, os_ = oracle.gptq_quantize(np.ascontiguousarray(R[np.ix_(k, n)]), np.ascontiguousarray(H[np.ix_(k, k)]), damp=0.0)
+        assert np.array_equal(sw[k[::64] // 64].view(np.uint32), os_.view(np.uint32))
+        assert np.array_equal(qw[:, k[::2] // 2], oq)
