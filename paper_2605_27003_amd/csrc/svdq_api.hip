@@ -429,7 +429,12 @@ static svdq::ExpandJob layer_expand_job(const svdq_layer* L, void* staging) {
     return L->w_packed ? svdq::expand_packed_job(L->w_packed, L->N, L->K, staging) : svdq::expand_canonical_job(L->qw, L->sw, L->N, staging);
 }
 
-// The GEMM on checked arguments.  h: `slices` partial h's for the few-token kernel, whose sum goes to hsum; one otherwise.
+// Whether the layer's GEMM adds up the partial h's of the quantise pass itself.
+static bool gemm_takes_slices(const svdq_layer* L, int64_t M, bool fields) {
+    return small_path(L, M) || ((fields || L->format == SVDQ_FMT_INT4_E3M2) && svdq::layer_e3m2_takes_slices(M, L->N, L->K));
+}
+
+// The GEMM on checked arguments.  h: `slices` partial h's, whose sum goes to hsum, where gemm_takes_slices; one otherwise.
 // fields: codes are E3M2 fields whatever the format.  expanded: staging holds the layer's weights already.
 static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool fields, bool expanded, const float* h, int slices, float* hsum,
                       int64_t M, void* staging, void* y, int64_t ldy, hipStream_t stream) {
@@ -472,7 +477,7 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
         }
         wp = (const uint8_t*)staging;
     }
-    return hip_status(svdq::launch_layer_e3m2(codes, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, stream));
+    return hip_status(svdq::launch_layer_e3m2(codes, wp, h, L->L2_bf16, L->bias, M, N, K, r, y, ldy, stream, slices, hsum));
 }
 
 static int layer_out_check(const svdq_layer* L, const void* codes, const void* scales, const void* h, const void* y, int64_t ldy) {
@@ -520,7 +525,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
                                        expand ? layer_expand_job(L, staging) : svdq::ExpandJob{});
     if (e != hipSuccess) return hip_status(e);
     const float* hin = ho;
-    if (r != 0 && slices > 1 && !small_path(L, M)) {
+    if (r != 0 && slices > 1 && !gemm_takes_slices(L, M, fields)) {
         e = svdq::launch_sum_slices(ho, slices, M, r, h, stream);
         if (e != hipSuccess) return hip_status(e);
         hin = h;

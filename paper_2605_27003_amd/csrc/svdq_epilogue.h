@@ -1,9 +1,27 @@
 // Low-rank up-projection and bias of eq. 7 / eq. 11 on a wave's accumulator tile, shared by the GEMM kernels.
 #pragma once
 #include "svdq_dev.h"
+#include "svdq_kernels.h"
 #include "svdq_lds.h"
 
 namespace svdq {
+
+// Four elements of h, the sum of its slices of n elements in slice order.  All loads are requested before the first sum (a
+// slice that does not exist reads slice 0): one latency, not one per slice.
+__device__ __forceinline__ float4 sum_of_slices(const float* __restrict__ part, const int slices, const int64_t n, const int64_t i) {
+    float4 p[SMALL_SLICES];
+#pragma unroll
+    for (int s = 0; s < SMALL_SLICES; ++s) p[s] = *reinterpret_cast<const float4*>(part + (s < slices ? s * n : 0) + i);
+    float4 t = p[0];
+#pragma unroll
+    for (int s = 1; s < SMALL_SLICES; ++s) {
+        t.x = s < slices ? t.x + p[s].x : t.x;
+        t.y = s < slices ? t.y + p[s].y : t.y;
+        t.z = s < slices ? t.z + p[s].z : t.z;
+        t.w = s < slices ? t.w + p[s].w : t.w;
+    }
+    return t;
+}
 
 // y[ni][mi] += (h L2)^T + bias for a wave tile of NI 32-channel blocks (first channel n0) times MT 32-token
 // blocks (first token m0), in the accumulator layout of the 32x32 matrix instructions with the transposed

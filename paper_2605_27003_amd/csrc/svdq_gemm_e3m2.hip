@@ -97,17 +97,30 @@ struct NextLayer {
 // team would leave every SIMD a single wave that waits for its own operands: with the expansion of the weights,
 // M = 512 .. 640, N = 5120 (160, 200 tiles) 39.6 -> 34.7 us at K = 5120, 92 -> 76 and 96 -> 82 at K = 13824.  The halves
 // overlap by a group when the group count is odd; the second team multiplies that group by zero scales.
-template <int MODE, int KS>
+//
+// SLICED: h comes as the quantise pass of few tokens leaves it, in slices of K.  The block adds up its 128 rows into LDS
+// while the first groups travel, and the blocks of the first channel tile leave the sum in h, instead of a kernel between
+// the quantise pass and this one.  Whole layers, K = N = 5120: M = 512 40.6 -> 39.4 us, 640 40.1 -> 38.9, nibble
+// container, M = 700 44.0 -> 42.1.  With one team and more tiles than CUs every tile's start grows by more than the launch
+// took (M = 2048 92.0 -> 93.6, M = 4000 141.6 -> 142.8), so two teams only.
+struct SlicedH {
+    int slices;
+    float* sum;
+};
+template <int MODE, int KS, bool SLICED = false>
 __global__ __launch_bounds__(256 * KS, 2)
 void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict__ w0, const uint8_t* __restrict__ w1,
                       const uint8_t* __restrict__ sfr,
                       const float* __restrict__ h, const uint16_t* __restrict__ L2, const float* __restrict__ bias,
                       int64_t M, int N, int K, int r, void* __restrict__ yout, int64_t ldy, int out_f32,
                       int tile0, const TileGrid tg, int64_t dm0, int dmt, int32_t* __restrict__ dacc,
-                      const NextLayer nx) {
+                      const NextLayer nx, const SlicedH hs) {
     constexpr bool DUMP = MODE == MODE_DUMP, NEXT = MODE >= MODE_NEXT, GELU = MODE == MODE_NEXT_GELU;
     static_assert(KS == 1 || MODE == MODE_LAYER, "two teams: the layer only");
-    __shared__ __attribute__((aligned(16))) uint8_t rings[KS * NSLOTS * STAGE_BYTES];   // slot of group g: g % 5
+    static_assert(!SLICED || KS == 2, "slices: two teams only");
+    // slot of group g: g % 5.  SLICED: h of 32 tokens is 4 KB, [4 columns][token] x 16 B; three blocks of 32 stand in the
+    // last slot, which is filled behind the prologue, the fourth behind it.
+    __shared__ __attribute__((aligned(16))) uint8_t rings[KS * NSLOTS * STAGE_BYTES + (SLICED ? 4096 : 0)];
 
     int mt, nt;                                 // XCD-aware tile order (svdq_tiles.h)
     if (!tile_of(tg, blockIdx.x, mt, nt)) return;
@@ -216,7 +229,29 @@ void gemm_e3m2_kernel(const uint8_t* __restrict__ act, const uint8_t* __restrict
     // awaited and made visible.
     const int pre = ng < NSLOTS - 1 ? ng : NSLOTS - 1;
     for (int g = 0; g < pre; ++g) stage_issue(g);
-    if (!DUMP && team == 0) add_lowrank_bias<2, 2>(y, h, L2, bias, m0 + wm * 64, n0 + wn * 64, M, N, r, lane);
+    if constexpr (SLICED) {
+        static_assert(3 * 4096 <= OFF_ZERO, "the last slot's zeros stay");
+        auto h_block = [&](const int b) { return (uint32_t)(b < 3 ? (KS * NSLOTS - 1) * STAGE_BYTES + b * 4096 : KS * NSLOTS * STAGE_BYTES); };
+        const int sh = r > 16 ? 3 : 2;                          // a row of h is 1 << sh pieces of 16 bytes
+#pragma unroll
+        for (int j = 0; j < BM * 8 / (256 * KS); ++j) {
+            const int v = j * (256 * KS) + (int)threadIdx.x;
+            const int t = v >> sh, q = v & ((1 << sh) - 1);
+            if (t < BM) {
+                const int64_t m = m0 + t < M ? m0 + t : M - 1;
+                const float4 s = sum_of_slices(h, hs.slices, M * r, m * r + 4 * q);
+                *reinterpret_cast<float4*>(rings + h_block(t >> 5) + q * 512 + (t & 31) * 16) = s;
+                if (nt == 0 && m0 + t < M) *reinterpret_cast<float4*>(hs.sum + m * r + 4 * q) = s;
+            }
+        }
+        __syncthreads();
+        if (team == 0)
+            add_lowrank_bias_from<2, 2>(y, [&](const int mi, const int k) {
+                return *reinterpret_cast<const float4*>(rings + h_block(wm * 2 + mi) + (k >> 2) * 512 + l32 * 16);
+            }, L2, bias, n0 + wn * 64, N, r, lane);
+    } else if (!DUMP && team == 0) {
+        add_lowrank_bias<2, 2>(y, h, L2, bias, m0 + wm * 64, n0 + wn * 64, M, N, r, lane);
+    }
     wait_groups(pre - 1);
     __syncthreads();
 
@@ -614,9 +649,10 @@ hipError_t launch_unpack_act_e3m2(const uint8_t* act, int64_t M, int K, uint8_t*
 
 // teams: two teams of waves may split K where a launch has a tile per CU at most.  Below K = 2048 the second ring's
 // prologue and the sum of the tiles cost what the shorter loop saves (K = 1536, N = 2048, M = 640: 15.4 and 15.5 us).
+static bool two_team_shape(int mtiles, int N, int K) { return K >= 2048 && busiest_xcd(mtiles, N / BN) <= CUS_PER_XCD; }
 static hipError_t launch_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
                               int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32, bool teams,
-                              hipStream_t stream) {
+                              hipStream_t stream, const SlicedH& hs = SlicedH{}) {
     const int64_t walked = out_f32 ? 0 : e3m2_walk_rows(M, N, K, teams, walking_blocks());
     if (walked) {
         const hipError_t e = launch_e3m2_walk(act, w_packed, h, L2, bias, M, walked, N, K, r, y, ldy, stream);
@@ -624,13 +660,14 @@ static hipError_t launch_e3m2(const uint8_t* act, const void* w_packed, const fl
     }
     const uint8_t* base = (const uint8_t*)w_packed;
     const int mtiles = (int)((M - walked + BM - 1) / BM);
-    const bool two_teams = teams && K >= 2048 && busiest_xcd(mtiles, N / BN) <= CUS_PER_XCD;
+    const bool two_teams = teams && two_team_shape(mtiles, N, K);
     const TileGrid tg = make_tile_grid(mtiles, N / BN);
     auto kern = two_teams ? gemm_e3m2_kernel<MODE_LAYER, 2> : gemm_e3m2_kernel<MODE_LAYER, 1>;
+    if (hs.slices > 1) kern = gemm_e3m2_kernel<MODE_LAYER, 2, true>;      // layer_e3m2_takes_slices
     hipLaunchKernelGGL(kern, dim3((unsigned)tile_ids(tg)), dim3(two_teams ? 512 : 256), 0, stream,
                        act, base, base + w0_bytes(N, K), base + w0_bytes(N, K) + w1_bytes(N, K),
                        h, (const uint16_t*)L2, bias, M, N, K, r, y, ldy, out_f32,
-                       (int)(walked / BM), tg, (int64_t)0, 0, (int32_t*)nullptr, NextLayer{});
+                       (int)(walked / BM), tg, (int64_t)0, 0, (int32_t*)nullptr, NextLayer{}, hs);
     return hipGetLastError();
 }
 
@@ -642,8 +679,12 @@ hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
 }
 
 hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
-                             int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream) {
-    return launch_e3m2(act, w_packed, h, L2, bias, M, N, K, r, y, ldy, 0, true, stream);
+                             int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream, int slices, float* hsum) {
+    return launch_e3m2(act, w_packed, h, L2, bias, M, N, K, r, y, ldy, 0, true, stream, SlicedH{slices, hsum});
+}
+
+bool layer_e3m2_takes_slices(int64_t M, int N, int K) {
+    return two_team_shape((int)((M + BM - 1) / BM), N, K) && e3m2_walk_rows(M, N, K, true, walking_blocks()) == 0;
 }
 
 hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,
@@ -663,7 +704,7 @@ hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,
     hipLaunchKernelGGL(kern, dim3((unsigned)tile_ids(tg)), dim3(256), 0, stream,
                        act, base, base + w0_bytes(N, K), base + w0_bytes(N, K) + w1_bytes(N, K),
                        h, (const uint16_t*)L2, bias, M, N, K, r, (void*)nullptr, (int64_t)0, 0,
-                       0, tg, (int64_t)0, 0, (int32_t*)nullptr, nx);
+                       0, tg, (int64_t)0, 0, (int32_t*)nullptr, nx, SlicedH{});
     return hipGetLastError();
 }
 
@@ -678,7 +719,7 @@ hipError_t launch_group_acc_e3m2(const uint8_t* act, const void* w_packed, int64
                        act, base, base + w0_bytes(N, K), (const uint8_t*)nullptr,
                        (const float*)nullptr, (const uint16_t*)nullptr, (const float*)nullptr,
                        M, N, K, 0, (void*)nullptr, (int64_t)0, 0,
-                       t0, tg, m0, mt, acc, NextLayer{});
+                       t0, tg, m0, mt, acc, NextLayer{}, SlicedH{});
     return hipGetLastError();
 }
 

@@ -57,8 +57,10 @@ hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
 // svdq_e3m2_walk.hip: tokens [0, rows) of M, rows a multiple of 256 or M; N a multiple of 256, K >= 320, bf16 y
 hipError_t launch_e3m2_walk(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
                             int64_t M, int64_t rows, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
+// slices > 1: h is as many partial h's, whose sum goes to hsum; only where layer_e3m2_takes_slices says so
 hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
-                             int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
+                             int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream, int slices, float* hsum);
+bool layer_e3m2_takes_slices(int64_t M, int N, int K);
 hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,
                                    const float* h, const void* L2, const float* bias,
                                    int64_t M, int N, int K, int r, bool gelu,

@@ -217,15 +217,7 @@ __device__ __forceinline__ void multiply(const Tokens<SMALL_MXFP4, MT>& t, const
 __device__ __forceinline__ void sum_slices(const float* __restrict__ part, const int slices, const int64_t n, float* __restrict__ h, const int64_t v) {
     const int64_t i = v * 4;
     if (i >= n) return;
-    float4 t = *reinterpret_cast<const float4*>(part + i);
-    for (int s = 1; s < slices; ++s) {
-        const float4 p = *reinterpret_cast<const float4*>(part + s * n + i);
-        t.x += p.x;
-        t.y += p.y;
-        t.z += p.z;
-        t.w += p.w;
-    }
-    *reinterpret_cast<float4*>(h + i) = t;
+    *reinterpret_cast<float4*>(h + i) = sum_of_slices(part, slices, n, i);
 }
 
 template <int SRC, int NI, int MT>

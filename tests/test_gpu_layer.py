@@ -82,6 +82,32 @@ def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
     assert rel_fro(synth.bf16_bits_to_f32(host_bits(y2)).astype(np.float64), synth.bf16_bits_to_f32(host_bits(y1)).astype(np.float64)) <= 2e-3
 
 
+@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble"])
+@pytest.mark.parametrize("M,K,N,r", [
+    (500, 5120, 5120, 32), (513, 5120, 5120, 16),       # two teams, eight slices; a last tile of one token
+    (545, 2112, 2048, 32),                              # odd group count, four slices
+    (2048, 2048, 2048, 16), (2049, 2048, 2048, 16),     # a tile on every CU, the last of two teams; one team, slices summed ahead
+    (2100, 1024, 512, 32),                              # K < 2048: one team
+])
+def test_tiles_behind_a_sliced_quantise_pass(svdq, container, M, K, N, r):
+    """More tokens than the few-token path takes: two teams' blocks sum the slices of h.  The h left behind is whole (the bar
+    of the quantise pass alone), and the GEMM on it, the same kernel on one h, gives the same bits."""
+    x, _ = synth.make_x(M + K, M, K, outlier_count=3, outlier_scale=30.0)
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(x)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(M + K, K, N, r, cm)
+    lin = svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1), dev(L.L2), dev(L.qw), dev(L.sw), dev(L.bias),
+                          container=container.split()[0], resident="packed" if "packed" in container else "w4")
+    y = lin.forward(dev(x), 0.8).clone()
+    qx, sx, h, _ = lin.buffers(M, y.device)
+    want = (dev(x).view(torch.bfloat16).double() * dev(L.inv_lambda).double()) @ dev(L.L1).view(torch.bfloat16).double()
+    assert rel_fro(h.double().cpu().numpy(), want.cpu().numpy()) <= 3e-5
+    again = lin.gemm(qx, sx, h)
+    if container != "nibble":
+        assert torch.equal(again, y)
+    else:                                                # its gemm() multiplies on other matrix cores
+        assert rel_fro(again.double().cpu().numpy(), y.double().cpu().numpy()) <= 2e-3
+
+
 def test_layer_gemm_last_tokens_beyond_4_gb(svdq):
     """MXFP4, 4 GB of codes: the last tokens have a launch of their own on the few-token kernel where its 32-bit offsets
     reach them, and must not have one here.  Against the tile kernels alone (sums in another order: one bf16 step)."""
