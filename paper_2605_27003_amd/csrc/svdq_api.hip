@@ -8,6 +8,7 @@
 #include <cstring>
 
 #include "svdq_kernels.h"
+#include "svdq_mx_plan.h"
 
 namespace {
 
@@ -393,9 +394,14 @@ static bool small_path(const svdq_layer* L, int64_t M) {
 // block's eight waves, and no more slices than the few-token GEMM takes partial h's.
 static int layer_slices(const svdq_layer* L, int64_t M) {
     const int64_t row_blocks = (M + 31) / 32;
-    const int groups = L->K / 64, units = L->format == SVDQ_FMT_MXFP4 ? (groups + 1) / 2 : groups;   // MXFP4 splits by pairs
+    const bool mx = L->format == SVDQ_FMT_MXFP4;
+    const int groups = L->K / 64, units = mx ? (groups + 1) / 2 : groups;   // MXFP4 splits by pairs
     int s = svdq::SMALL_SLICES;
-    while (s > 1 && (s * row_blocks > 256 || groups / s < 8)) s >>= 1;
+    if (mx && !small_path(L, M) && row_blocks <= 128) {
+        s = svdq::mx_slices((int)row_blocks, groups);
+    } else {
+        while (s > 1 && (s * row_blocks > 256 || groups / s < 8)) s >>= 1;
+    }
     const int slice = (units + s - 1) / s;
     return (units + slice - 1) / slice;
 }

@@ -121,4 +121,26 @@ inline int64_t mx_layer_walk_rows(int64_t M, int N, int K, int walkers) {
     return mx_walk_rows(M, N, K, walkers, [&](int64_t rest) { return mx_rest_cost(M, rest, N, K, walkers); });
 }
 
+// Slices of K in the quantise pass of a layer whose GEMM is one of the tile kernels, `row_blocks` <= 128 blocks of 32 tokens.
+// A block's eight waves take a pair of groups each at a time; such a step takes 3.5 to 4 us, about 1.3 times that and half a
+// step more where CUs have two blocks, and the launch that adds up the slices about 0.8 of a step.  Against powers of two for
+// a block per CU at most, as the few-token path takes them (73 row blocks: 2 slices of 20 pairs, 3 steps), whole layers, us:
+// K = 5120: M = 1040, N = 5120 40.2 -> 38; 2800 60.9 -> 57.9; 2305, N = 13824 112.4 -> 108.5; K = 13824: M = 2305, N = 1024
+// 71.2 -> 58.1, M = 1500, N = 2048 58.0 -> 55.1; K = 1024 (no slices): M = 1300, N = 4096 20.4 -> 19.6.
+inline int mx_slices(int row_blocks, int groups) {
+    const int pairs = (groups + 1) / 2;
+    int best = 1;
+    double least = 1e30;
+    for (int s = 1; s <= SMALL_SLICES; ++s) {
+        if (s > 1 && (s * row_blocks > 512 || groups / s < 8)) break;
+        const int steps = ((pairs + s - 1) / s + 7) / 8;
+        const double c = (s * row_blocks > 256 ? 1.3 * steps + 0.5 : steps) + (s > 1 ? 0.8 : 0.0);
+        if (c <= least) {                                   // as many steps in more slices: more CUs load
+            least = c;
+            best = s;
+        }
+    }
+    return best;
+}
+
 }  // namespace svdq

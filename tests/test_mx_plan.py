@@ -66,3 +66,28 @@ def test_launch_split_off_where_it_pays(plan):
         for m in (1, 255, 256, 257, M):
             (tile, r), = plan([(K, m, N)])
             assert r == m or (0 < r < m and r % 256 == 0)
+
+
+SLICES_DRIVER = """
+#include <cstdio>
+#include "svdq_mx_plan.h"
+int main() {
+    for (int rb = 1; rb <= 128; ++rb)
+        for (int groups = 1; groups <= 256; ++groups) printf("%d ", svdq::mx_slices(rb, groups));
+}
+"""
+
+
+def test_slices_of_the_quantise_pass(tmp_path):
+    """Never more slices than partial sums are summed, a group per wave and slice, two blocks of 32 tokens per CU at most; and
+    the ones measured to be the fastest (K = 5120 and 13824)."""
+    (tmp_path / "driver.hip").write_text(SLICES_DRIVER)
+    subprocess.run([HIPCC, "--cuda-host-only", "-std=c++17", "-O1", "-I", CSRC, str(tmp_path / "driver.hip"), "-o", str(tmp_path / "driver")],
+                   check=True, capture_output=True, text=True)
+    flat = [int(v) for v in subprocess.run([str(tmp_path / "driver")], check=True, capture_output=True, text=True).stdout.split()]
+    got = {(1 + i // 256, 1 + i % 256): s for i, s in enumerate(flat)}
+    for (rb, groups), s in got.items():
+        assert s == 1 or (1 < s <= 8 and s * rb <= 512 and groups // s >= 8), (rb, groups, s)
+    # 1040, 1536, 2305, 2800 tokens; K = 13824; K = 1024
+    assert [got[rb, 80] for rb in (33, 48, 73, 88)] == [7, 5, 7, 5]
+    assert got[73, 216] == 7 and got[41, 16] == 1
