@@ -653,7 +653,7 @@ static bool two_team_shape(int mtiles, int N, int K) { return K >= 2048 && busie
 static hipError_t launch_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
                               int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32, bool teams,
                               hipStream_t stream, const SlicedH& hs = SlicedH{}) {
-    const int64_t walked = out_f32 ? 0 : e3m2_walk_rows(M, N, K, teams, walking_blocks());
+    const int64_t walked = out_f32 ? 0 : e3m2_walk_rows(M, N, K, teams, walking_blocks(), r != 0);
     if (walked) {
         const hipError_t e = launch_e3m2_walk(act, w_packed, h, L2, bias, M, walked, N, K, r, y, ldy, stream);
         if (e != hipSuccess || walked == M) return e;
@@ -683,8 +683,8 @@ hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const flo
     return launch_e3m2(act, w_packed, h, L2, bias, M, N, K, r, y, ldy, 0, true, stream, SlicedH{slices, hsum});
 }
 
-bool layer_e3m2_takes_slices(int64_t M, int N, int K) {
-    return two_team_shape((int)((M + BM - 1) / BM), N, K) && e3m2_walk_rows(M, N, K, true, walking_blocks()) == 0;
+bool layer_e3m2_takes_slices(int64_t M, int N, int K) {             // only a low-rank term has slices
+    return two_team_shape((int)((M + BM - 1) / BM), N, K) && e3m2_walk_rows(M, N, K, true, walking_blocks(), true) == 0;
 }
 
 hipError_t launch_linear_e3m2_next(const uint8_t* act, const void* w_packed,

@@ -109,6 +109,33 @@ def test_tiles_behind_a_sliced_quantise_pass(svdq, container, M, K, N, r):
         assert rel_fro(again.double().cpu().numpy(), y.double().cpu().numpy()) <= 2e-3
 
 
+@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble"])
+@pytest.mark.parametrize("M,K,N,r,walked", [
+    (3300, 5120, 5120, 32, 3072),                       # slices of h summed ahead; the last 228 tokens by two teams
+    (3300, 5120, 5120, 0, 3072),
+    (1216, 2112, 13824, 32, 1024),                      # odd group count in both kernels
+    (5376, 2112, 3072, 16, 5376),
+])
+def test_walked_layers(svdq, container, M, K, N, r, walked):
+    """Layers whose first tokens take 256 x 256 tiles and whose last are left to two teams of the 128 x 128 kernel, which begins
+    behind them (tests/test_e3m2_plan.py: they do).  Against that kernel with one team on the h that the layer has left:
+    the same bits where tokens are walked, another order of K elsewhere (the bar of the layer)."""
+    x, _ = synth.make_x(M + K, M, K, outlier_count=3, outlier_scale=30.0)
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(x)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(M + K, K, N, r, cm)
+    inv = dev(L.inv_lambda)
+    lin = svdq.W4A4Linear(inv, dev(L.L1) if r else None, dev(L.L2) if r else None, dev(L.qw), dev(L.sw), dev(L.bias),
+                          container=container.split()[0], resident="packed" if "packed" in container else "w4")
+    y = lin.forward(dev(x), 0.8)
+    h = lin.buffers(M, y.device)[2] if r else None
+    act = svdq.quantize_act_e3m2(dev(x), inv, 0.8, None, 0)[0]
+    want = svdq.linear_w4a4_e3m2(act, svdq.pack_weight_e3m2(dev(L.qw), dev(L.sw)), N, h, dev(L.L2) if r else None, dev(L.bias),
+                                 out_dtype=torch.float32).to(torch.bfloat16)
+    assert torch.equal(y[:walked], want[:walked])
+    if walked < M:
+        assert rel_fro(y[walked:].double().cpu().numpy(), want[walked:].double().cpu().numpy()) <= 2e-3
+
+
 def test_layer_gemm_last_tokens_beyond_4_gb(svdq):
     """MXFP4, 4 GB of codes: the last tokens have a launch of their own on the few-token kernel where its 32-bit offsets
     reach them, and must not have one here.  Against the tile kernels alone (sums in another order: one bf16 step)."""
