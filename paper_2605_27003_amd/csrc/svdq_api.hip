@@ -343,7 +343,7 @@ int svdq_linear_mxfp4(const uint8_t* qx, const uint8_t* sx_e8m0, const void* w_p
     if (M > SVDQ_MAX_M) return SVDQ_ERR_UNSUPPORTED_SHAPE;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
-    return hip_status(svdq::launch_linear_mx(qx, sx_e8m0, w_packed, h, L2_bf16, bias, M, 0, M, N, K, r, y, ldy,
+    return hip_status(svdq::launch_linear_mx(qx, sx_e8m0, w_packed, h, L2_bf16, bias, M, M, N, K, r, y, ldy,
                                              out_dtype == SVDQ_OUT_F32, (hipStream_t)stream));
 }
 
@@ -466,11 +466,9 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
         return hip_status(svdq::launch_small_gemm(source, codes, scales, w0, w1, w2, h, slices, slices > 1 ? hsum : nullptr, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
     }
     if (L->format == SVDQ_FMT_MXFP4) {
-        const int64_t main = svdq::mx_main_rows(M, N, K);
-        const hipError_t e = svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, 0, main, N, K, r, y, ldy, 0, stream);
+        const int64_t main = svdq::mx_main_rows(M, N, K, r);
+        const hipError_t e = svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, main, N, K, r, y, ldy, 0, stream);
         if (e != hipSuccess || main == M) return hip_status(e);
-        if (!svdq::small_shape(M - main, N, K) || !svdq::small_reach(M, N, K))
-            return hip_status(svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, main, M, N, K, r, y, ldy, 0, stream));
         return hip_status(svdq::launch_small_gemm(svdq::SMALL_MXFP4, codes, scales, wp, wp + svdq::packed_mx_codes_bytes(N, K), nullptr, h, 1, nullptr,
                                                   L->L2_bf16, L->bias, M, main, N, K, r, y, ldy, stream));
     }

@@ -104,12 +104,11 @@ hipError_t launch_pack_weight_mx(const uint8_t* qw, const uint8_t* sw, int N, in
 hipError_t launch_quantize_mx(const void* x, int64_t ldx, const float* inv_lambda, float rho,
                               const void* l1p, int64_t M, int K, int r,
                               uint8_t* qx, uint8_t* sxe, float* h, bool gelu, hipStream_t stream, int slices = 1);
-// tokens [begin, end) of M; begin a multiple of 256
+// tokens [0, rows) of M, rows a multiple of 256 or M
 hipError_t launch_linear_mx(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
                             const float* h, const void* L2, const float* bias,
-                            int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
-                            hipStream_t stream);
-int64_t mx_main_rows(int64_t M, int N, int K);       // tokens that are best left to the tile kernels (the rest: few tokens)
+                            int64_t M, int64_t rows, int N, int K, int r, void* y, int64_t ldy, int out_f32, hipStream_t stream);
+int64_t mx_main_rows(int64_t M, int N, int K, int r);   // tokens that are best left to the tile kernels; the few-token kernel takes the rest
 hipError_t launch_linear_mx_next(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
                                  const float* h, const void* L2, const float* bias,
                                  int64_t M, int N, int K, int r, bool gelu,

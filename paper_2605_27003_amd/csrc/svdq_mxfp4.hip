@@ -1010,32 +1010,10 @@ static int cu_count() {
 // the tile order)
 int walking_blocks() { return cu_count() / 8 * 8; }
 
-// Where the walking kernel takes a part of the tokens, the rest is for the few-token kernel if that is cheaper than tiles.
-int64_t mx_main_rows(int64_t M, int N, int K) {
-    const int walkers = walking_blocks();
-    const int64_t walked = mx_layer_walk_rows(M, N, K, walkers);
-    if (walked == 0) return mx_layer_split(M, N, K, walkers);
-    return walked < M && mx_rest_cost(M, M - walked, N, K, walkers) < mx_best(M - walked, N, K, walkers).cost ? walked : M;
-}
+int64_t mx_main_rows(int64_t M, int N, int K, int r) { return mx_tile_rows(M, N, K, walking_blocks(), r != 0); }
 
-static bool mx_can_walk(int N, int K) { return N % 256 == 0 && K >= 576; }
-
-// Tokens [begin, end), begin a multiple of 256, on 256 x 256 tiles, one block per CU walking its tiles.  Without a low-rank
-// branch or a bias the kernel's transfers for them still run (they have no branch): give them the codes to read.
-static hipError_t launch_mx_walk(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
-                                 const float* h, const void* L2, const float* bias,
-                                 int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
-                                 hipStream_t stream) {
-    const uint8_t* base = (const uint8_t*)w_packed;
-    hipLaunchKernelGGL((gemm_mx_persistent_kernel<4>), dim3((unsigned)walking_blocks()), dim3(512), 0, stream,
-                       qx, (const uint16_t*)sxe, (const uint4*)base, (const uint16_t*)(base + mx_wfrag_bytes(N, K)),
-                       r > 0 ? h : (const float*)qx, r > 0 ? (const uint16_t*)L2 : (const uint16_t*)qx, bias ? bias : (const float*)qx,
-                       M, N, K, r, bias != nullptr, y, ldy, out_f32,
-                       make_walk_grid((int)((end - begin + 255) / 256), N / 256, (int)(begin / 256)));
-    return hipGetLastError();
-}
-
-// The tiles of tokens [begin, end), begin a multiple of 256.
+// The tiles of tokens [begin, end), begin a multiple of 256.  Tokens that begin behind others take smaller tiles than
+// 256 x 256 (mx_split).
 static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
                                   const float* h, const void* L2, const float* bias,
                                   int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
@@ -1043,16 +1021,20 @@ static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const v
     const uint8_t* base = (const uint8_t*)w_packed;
     const uint16_t* wsc = (const uint16_t*)(base + mx_wfrag_bytes(N, K));
     const int64_t rows = end - begin;
-    auto grid = [&](int bm, int bn) { return make_tile_grid((int)((rows + bm - 1) / bm), N / bn, (int)(begin / bm)); };
     auto one_tile = [&](auto kern, int bm, int bn, int threads) {
-        const TileGrid tg = grid(bm, bn);
+        const TileGrid tg = make_tile_grid((int)((rows + bm - 1) / bm), N / bn, (int)(begin / bm));
         hipLaunchKernelGGL(kern, dim3((unsigned)tile_ids(tg)), dim3(threads), 0, stream,
                            qx, (const uint16_t*)sxe, (const uint4*)base, wsc, h, (const uint16_t*)L2, bias,
                            M, N, K, r, y, ldy, out_f32, tg, MxNext{});
     };
-    const MxTile tile = mx_best(rows, N, K, walking_blocks()).tile;
-    if (tile == MxTile::T256x256 && mx_can_walk(N, K)) {
-        return launch_mx_walk(qx, sxe, w_packed, h, L2, bias, M, begin, end, N, K, r, y, ldy, out_f32, stream);
+    const MxTile tile = mx_best(rows, N, K, walking_blocks(), r != 0).tile;
+    if (tile == MxTile::T256x256 && mx_can_walk(N, K) && begin == 0) {
+        // One block per CU walking its tiles.  Without a low-rank branch or a bias the kernel's transfers for them still run
+        // (they have no branch): give them the codes to read
+        hipLaunchKernelGGL((gemm_mx_persistent_kernel<4>), dim3((unsigned)walking_blocks()), dim3(512), 0, stream,
+                           qx, (const uint16_t*)sxe, (const uint4*)base, wsc,
+                           r > 0 ? h : (const float*)qx, r > 0 ? (const uint16_t*)L2 : (const uint16_t*)qx, bias ? bias : (const float*)qx,
+                           M, N, K, r, bias != nullptr, y, ldy, out_f32, make_walk_grid((int)((rows + 255) / 256), N / 256));
     } else if (tile == MxTile::T256x256) {
         one_tile(gemm_mx_kernel<4, 4, MX_LAYER>, 256, 256, 512);
     } else if (tile == MxTile::T256x128) {
@@ -1065,20 +1047,12 @@ static hipError_t launch_mx_tiles(const uint8_t* qx, const uint8_t* sxe, const v
 
 hipError_t launch_linear_mx(const uint8_t* qx, const uint8_t* sxe, const void* w_packed,
                             const float* h, const void* L2, const float* bias,
-                            int64_t M, int64_t begin, int64_t end, int N, int K, int r, void* y, int64_t ldy, int out_f32,
-                            hipStream_t stream) {
+                            int64_t M, int64_t rows, int N, int K, int r, void* y, int64_t ldy, int out_f32, hipStream_t stream) {
     const int walkers = walking_blocks();
-    auto tail = [&](int64_t rest) { return mx_best(rest, N, K, walkers).cost; };
-    const int64_t walked = mx_walk_rows(end - begin, N, K, walkers, tail);
-    hipError_t e = hipSuccess;
-    if (walked) {
-        e = launch_mx_walk(qx, sxe, w_packed, h, L2, bias, M, begin, begin + walked, N, K, r, y, ldy, out_f32, stream);
-        begin += walked;
-        if (e != hipSuccess || begin == end) return e;
-    }
-    const int64_t mid = walked ? end : begin + mx_split(end - begin, N, K, walkers, tail).rows;
-    e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, begin, mid, N, K, r, y, ldy, out_f32, stream);
-    if (e == hipSuccess && mid < end) e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, mid, end, N, K, r, y, ldy, out_f32, stream);
+    const bool lowrank = r != 0;
+    const int64_t mid = mx_split(rows, N, K, walkers, lowrank, [&](int64_t rest) { return mx_best(rest, N, K, walkers, lowrank).cost; }).rows;
+    hipError_t e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, 0, mid, N, K, r, y, ldy, out_f32, stream);
+    if (e == hipSuccess && mid < rows) e = launch_mx_tiles(qx, sxe, w_packed, h, L2, bias, M, mid, rows, N, K, r, y, ldy, out_f32, stream);
     return e;
 }
 

@@ -65,15 +65,14 @@ __device__ __forceinline__ bool tile_of(const TileGrid& g, int id, int& mt, int&
 // the channel tiles, so the 32 tiles that an XCD's CUs hold at once are 8 x 4.
 struct WalkGrid {
     int mtiles, ntiles, chunk;
-    int mt0;                     // first token tile
 };
-inline WalkGrid make_walk_grid(int mtiles, int ntiles, int mt0 = 0) { return WalkGrid{mtiles, ntiles, (mtiles * ntiles + 7) / 8, mt0}; }
+inline WalkGrid make_walk_grid(int mtiles, int ntiles) { return WalkGrid{mtiles, ntiles, (mtiles * ntiles + 7) / 8}; }
 // tile of block id `id` (id % 8: its XCD), which exists
 __host__ __device__ inline void walk_tile(const WalkGrid& g, int id, int& mt, int& nt) {
     const int n = (id & 7) * g.chunk + (id >> 3), sm = n / (8 * g.ntiles), rem = n - sm * (8 * g.ntiles);
     const int width = g.mtiles - 8 * sm < 8 ? g.mtiles - 8 * sm : 8;
     nt = rem / width;
-    mt = g.mt0 + 8 * sm + rem - nt * width;
+    mt = 8 * sm + rem - nt * width;
 }
 
 }  // namespace svdq

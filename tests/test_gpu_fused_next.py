@@ -207,9 +207,9 @@ def test_mx_exact_inputs_equal_oracle_chain(svdq, oracle):
         assert rel_fro(nh.cpu().numpy(), oh) <= 3e-5, gelu
 
 
-# the last two shapes have at least 512 tiles of 256 x 256 and K >= 576: there the un-fused MXFP4 GEMM runs as one block
+# the last shapes have many tokens and channels; in the first and the last of them the un-fused MXFP4 GEMM runs as one block
 # per CU walking its tiles, while the emitting one keeps one block per tile: the two must still agree byte for byte
-MX_CHAIN = CHAIN + [(1999, 640, 16384, 32, 32, True), (2050, 1088, 16384, 16, 16, False)]
+MX_CHAIN = CHAIN + [(1999, 640, 16384, 32, 32, True), (2050, 1088, 16384, 16, 16, False), (5000, 1088, 5120, 16, 16, False)]
 
 
 @pytest.mark.parametrize("M,K,N,r,r2,gelu", MX_CHAIN)

@@ -78,20 +78,23 @@ def test_ragged_shapes(svdq, oracle, M, K, N, r):
 
 
 @pytest.mark.parametrize("M,K,N,r", [(1999, 640, 16384, 32), (2050, 1088, 16384, 16), (4100, 576, 8192, 0),
-                                      (1999, 512, 16384, 32)])
+                                      (1999, 512, 16384, 32),
+                                      (2590, 576, 5120, 16), (6300, 576, 5120, 0), (2305, 1088, 5120, 32),
+                                      (5000, 1088, 5120, 16), (1803, 1600, 10240, 32)])
 def test_tile_walking_kernel_shapes(svdq, oracle, M, K, N, r):
-    """Shapes with at least 512 tiles of 256 x 256 and K >= 576: the GEMM then runs as one block per CU that walks
-    its tiles and stages each next tile's low-rank input in LDS.  Ragged last token tile, an odd group count, five
-    to nine stages per tile, r = 32, 16 and none; the last shape (four stages) stays with one block per tile."""
+    """Many tokens and channels.  Walked by one block per CU, which stages each next tile's low-rank input and bias in LDS
+    (tests/test_mx_walk_plan.py): the first shape, 512 tiles, and those of the second line, 220, 500 and 200 tiles (one a
+    block or none, two or one) and 400; K from the shortest that is walked (576: five stages, the last one half empty), odd
+    group counts, r = 32, 16 and none, ragged last token tiles.  The last shape has its last tokens on 128 x 128 tiles in a
+    launch of their own; the others have tiles of blocks of their own, which K = 512 (four stages) always has."""
     x, L = small_layer(11, M, K, N, r)
     run_layer(svdq, oracle, x, L, 0.8, f"tile-walking M={M} K={K} N={N} r={r}")
 
 
 def test_tile_walking_kernel_without_bias(svdq, oracle):
-    """The tile-walking GEMM with a low-rank branch and no bias, and with neither: its h transfers then read a
+    """The tile-walking GEMM with a low-rank branch and no bias, and with neither: its transfers for them then read a
     substitute address and must leave the result alone."""
-    M, K, N = 1100, 704, 32768
-    for r in (32, 0):
+    for M, K, N, r in ((1100, 704, 32768, 32), (1100, 704, 32768, 0), (6300, 576, 5120, 0)):
         x, L = small_layer(13, M, K, N, r)
         DL = MxLayer(svdq, L)
         qx, sx, h = svdq.quantize_act_mxfp4(dev(x), DL.inv_lambda, 0.8, DL.l1p, r)
