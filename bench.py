@@ -42,10 +42,11 @@ EXEC_WHAT = {
     "int4": "4-bit storage end to end: nibbles unpacked in registers, int8 matrix cores, one int32 accumulator per group",
     "mxfp4": "the layer in the MXFP4 format of the paper's Table I on the block-scaled FP4 matrix instruction",
 }
-KERNELS = {   # execution -> (GEMM kernel, quantise kernel as named in profiles/, matrix peak, unit)
-    "e3m2": ("gemm_e3m2_kernel", "quantize_kernel_e3m2", FP6_MFMA_PEAK_TFLOPS, "TFLOP/s"),
+# execution -> (GEMM kernel, which may leave its last tokens to another one's tiles, and quantise kernel as named in profiles/; matrix peak, unit)
+KERNELS = {
+    "e3m2": ("gemm_e3m2_walk_kernel", "quantize_kernel_e3m2", FP6_MFMA_PEAK_TFLOPS, "TFLOP/s"),
     "int4": ("gemm_kernel", "quantize_kernel", INT8_MFMA_PEAK_TOPS, "TOP/s"),
-    "mxfp4": ("gemm_mx_kernel", "quantize_mx_kernel", FP6_MFMA_PEAK_TFLOPS, "TFLOP/s"),
+    "mxfp4": ("gemm_mx_persistent_kernel", "quantize_mx_kernel", FP6_MFMA_PEAK_TFLOPS, "TFLOP/s"),
 }
 ENTRY = {"e3m2": ("svdq_linear_w4a4_e3m2", "svdq_quantize_act_e3m2"), "int4": ("svdq_linear_w4a4", "svdq_quantize_act"),
          "mxfp4": ("svdq_linear_mxfp4", "svdq_quantize_act_mxfp4")}
