@@ -35,7 +35,9 @@ SHAPES = [  # M, K, N, r, gelu
     (448, 2048, 4096, 32, False), (449, 2048, 4096, 16, False),   # and with many
     (10240, 64, 128, 32, False), (10241, 64, 128, 16, False),   # MXFP4: last of the 32 x 64 tiles and the next
     (1025, 2112, 2048, 32, False),                # E3M2: K in halves, odd group count; MXFP4: 128 x 128 tiles
-    (2049, 192, 4096, 16, True),                  # MXFP4: the last token in a launch of its own
+    (2049, 192, 4096, 16, True),
+    (2049, 1088, 1408, 32, False),                # MXFP4: the last token in a launch of its own on the few-token kernel,
+    (6401, 576, 2560, 16, True),                  # the others on 128 x 128 tiles or walked
     (2305, 3648, 640, 32, False),                 # MXFP4: six uneven slices of K, two blocks per CU in the quantise pass
 ]
 

@@ -66,12 +66,17 @@ def test_division_near_the_fastest(plan):
 
 
 def test_shapes_of_the_gpu_tests_are_walked(plan):
-    """The shapes of tests/test_gpu_mxfp4.py and tests/test_gpu_fused_next.py that are there for the walking kernel."""
+    """The shapes of tests/test_gpu_mxfp4.py and tests/test_gpu_fused_next.py that are there for the walking kernel, and of
+    tests/test_gpu_layer.py for the few-token kernel behind it."""
     whole = [(1999, 16384, 640, 32), (2590, 5120, 576, 16), (6300, 5120, 576, 0), (2305, 5120, 1088, 32), (5000, 5120, 1088, 16),
              (1100, 32768, 704, 32)]
     assert [(rows, walks) for rows, _, walks, _, _ in plan(whole)] == [(s[0], 1) for s in whole]
     (rows, _, walks, _, _), = plan([(1803, 10240, 1600, 32)])
     assert walks and rows == 1536
+    # tests/test_gpu_layer.py: the last token is for the few-token kernel, behind 128 x 128 tiles and behind walked ones
+    few = [(2049, 1408, 1088, 32), (6401, 2560, 576, 16)]
+    assert [tiles for _, tiles, *_ in plan(few)] == [2048, 6400]
+    assert [walks for _, _, walks, *_ in plan([(m // 256 * 256, n, k, r) for m, n, k, r in few])] == [0, 1]
 
 
 def test_divisions_are_what_the_kernels_take(plan):
