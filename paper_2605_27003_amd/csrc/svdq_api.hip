@@ -440,6 +440,21 @@ static bool gemm_takes_slices(const svdq_layer* L, int64_t M, bool fields) {
     return small_path(L, M) || ((fields || L->format == SVDQ_FMT_INT4_E3M2) && svdq::layer_e3m2_takes_slices(M, L->N, L->K));
 }
 
+// The layer's weights as the kernels for few tokens take them.
+struct SmallWeights {
+    int source;
+    const void *w0, *w1, *w2;
+};
+static SmallWeights small_weights(const svdq_layer* L) {
+    const int N = L->N, K = L->K;
+    const uint8_t* wp = (const uint8_t*)L->w_packed;
+    if (L->format == SVDQ_FMT_INT4) return {svdq::SMALL_NIBBLE, wp, wp + svdq::packed_weight_codes_bytes(N, K), nullptr};
+    if (L->format == SVDQ_FMT_MXFP4) return {svdq::SMALL_MXFP4, wp, wp + svdq::packed_mx_codes_bytes(N, K), nullptr};
+    if (!wp) return {svdq::SMALL_E3M2_CANONICAL, L->qw, L->sw, nullptr};
+    const uint8_t* w1 = wp + svdq::packed_e3m2_w0_bytes(N, K);
+    return {svdq::SMALL_E3M2_PACKED, wp, w1, w1 + svdq::packed_e3m2_w1_bytes(N, K)};
+}
+
 // The GEMM on checked arguments.  h: `slices` partial h's, whose sum goes to hsum, where gemm_takes_slices; one otherwise.
 // fields: codes are E3M2 fields whatever the format.  expanded: staging holds the layer's weights already.
 static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool fields, bool expanded, const float* h, int slices, float* hsum,
@@ -447,23 +462,8 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
     const int N = L->N, K = L->K, r = L->r;
     const uint8_t* wp = (const uint8_t*)L->w_packed;
     if (small_path(L, M)) {
-        const void *w0 = wp, *w1 = nullptr, *w2 = nullptr;
-        int source = svdq::SMALL_E3M2_PACKED;
-        if (L->format == SVDQ_FMT_INT4) {
-            source = svdq::SMALL_NIBBLE;
-            w1 = wp + svdq::packed_weight_codes_bytes(N, K);
-        } else if (L->format == SVDQ_FMT_MXFP4) {
-            source = svdq::SMALL_MXFP4;
-            w1 = wp + svdq::packed_mx_codes_bytes(N, K);
-        } else if (!wp) {
-            source = svdq::SMALL_E3M2_CANONICAL;
-            w0 = L->qw;
-            w1 = L->sw;
-        } else {
-            w1 = wp + svdq::packed_e3m2_w0_bytes(N, K);
-            w2 = (const uint8_t*)w1 + svdq::packed_e3m2_w1_bytes(N, K);
-        }
-        return hip_status(svdq::launch_small_gemm(source, codes, scales, w0, w1, w2, h, slices, slices > 1 ? hsum : nullptr, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
+        const SmallWeights w = small_weights(L);
+        return hip_status(svdq::launch_small_gemm(w.source, codes, scales, w.w0, w.w1, w.w2, h, slices, slices > 1 ? hsum : nullptr, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
     }
     if (L->format == SVDQ_FMT_MXFP4) {
         const int64_t main = svdq::mx_main_rows(M, N, K, r);
@@ -514,6 +514,11 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (int a = check_arch()) return a;
     hipStream_t stream = (hipStream_t)stream_;
     const int K = L->K, r = L->r;
+    if (small_path(L, M) && svdq::small_fused(M, L->N, K, r, L->format == SVDQ_FMT_MXFP4) != svdq::FUSED_NONE) {
+        const SmallWeights w = small_weights(L);
+        return hip_status(svdq::launch_fused_layer(w.source, x_bf16, ldx, L->inv_lambda, rho, gelu != 0, L->l1_packed, (uint8_t*)codes, scales, h,
+                                                   w.w0, w.w1, w.w2, L->L2_bf16, L->bias, M, L->N, K, r, y, ldy, stream));
+    }
     // without h there is nothing to add up over the slices
     int slices = (r == 0 || scratch) ? layer_slices(L, M) : 1;
     float* const ho = (r != 0 && slices > 1) ? (float*)scratch : h;

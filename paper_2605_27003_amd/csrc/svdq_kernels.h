@@ -94,6 +94,25 @@ inline bool small_reach(int64_t M, int64_t N, int64_t K) { return (M > N ? M : N
 hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1, const void* w2,
                              const float* h, int slices, float* hsum, const void* L2, const float* bias, int64_t M, int64_t begin, int N, int K, int r,
                              void* y, int64_t ldy, hipStream_t stream);
+// The whole layer in one launch (fused_layer_kernel), or FUSED_NONE: a quantise pass and a GEMM.  Every block quantises its own
+// tokens, so what it takes grows with K, and sooner with a low-rank term, whose L1 fragments every block reads too; the two launches
+// cost 9 to 10 us (6 of them on the host) as long as K is short.  Measured on whole layers, N = 512 .. 4096, us against the two launches:
+//   up to 8 tokens, K = 2048: E3M2 6.7 against 9.8 (with a term 10.1, 9.8), MXFP4 6.5 against 9.3 (8.6, 9.4);
+//   up to a 16-token tile per CU, K = 1536: M = 32 7.2 against 9.8 (10.4, 10.2), MXFP4 6.6 against 9.4 (9.1, 10.5);
+//   32-token tiles, M = 256, N = 2048: K = 1024 8.0 against 9.9 (10.8, 11.4), 2048 12.3 against 11.8; MXFP4 1024 6.6 against 9.4
+//   (8.8, 10.6), 2048 9.3 against 9.5 (12.7, 11.7).
+enum { FUSED_NONE = 0, FUSED_SPREAD = 1, FUSED_TILES = 2 };
+inline int small_fused(int64_t M, int N, int K, int r, bool mxfp4) {
+    const int64_t b16 = ((M + 15) / 16) * (N / 32), b32 = ((M + 31) / 32) * (N / 32);
+    const bool few = M <= 8;
+    if (b16 <= 256 && K <= (few ? (r ? (mxfp4 ? 2304 : 1792) : (mxfp4 ? 4352 : 3328)) : (r ? (mxfp4 ? 1792 : 1408) : (mxfp4 ? 3328 : 2560))) &&
+        (few || M <= 16 || K > 512))
+        return FUSED_SPREAD;
+    return b32 <= 512 && K <= (r ? (mxfp4 ? 1664 : 1216) : (mxfp4 ? 2048 : 1664)) ? FUSED_TILES : FUSED_NONE;
+}
+hipError_t launch_fused_layer(int source, const void* x, int64_t ldx, const float* inv_lambda, float rho, bool gelu, const void* l1p,
+                              uint8_t* codes, void* scales, float* h, const void* w0, const void* w1, const void* w2,
+                              const void* L2, const float* bias, int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
 hipError_t launch_sum_slices(const float* part, int slices, int64_t M, int r, float* h, hipStream_t stream);
 
 // svdq_mxfp4.hip

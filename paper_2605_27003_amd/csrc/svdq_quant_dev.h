@@ -165,4 +165,44 @@ __device__ __forceinline__ void quantize_rows(const uint4 (&xv)[4], const float*
     codes.lo = uint4{packed[0], packed[1], packed[2], packed[3]};
 }
 
+// The MXFP4 chain (svdq_mxfp4.hip).  One 32-row block of one group: this lane's 32 values -> 16 bytes of codes and the block's E8M0 byte.
+__device__ __forceinline__ void quantize_block_mx(const uint4 (&xv)[4], const float* __restrict__ il_lds, float rho,
+                                                  uint4& codes, uint32_t& e8) {
+    float xs[32];
+    float a = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const float4 i0 = *reinterpret_cast<const float4*>(il_lds + 8 * s);
+        const float4 i1 = *reinterpret_cast<const float4*>(il_lds + 8 * s + 4);
+        const float ilv[8] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
+        const uint32_t wds[4] = {xv[s].x, xv[s].y, xv[s].z, xv[s].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float lo = __fmul_rn(bf16lo_f(wds[j]), ilv[2 * j]);          // eq. 5 in binary32
+            float hi = __fmul_rn(bf16hi_f(wds[j]), ilv[2 * j + 1]);
+            xs[8 * s + 2 * j] = lo;
+            xs[8 * s + 2 * j + 1] = hi;
+            a = __builtin_fmaxf(a, __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)));
+        }
+    }
+    // eq. 8: alpha = rho * a is the block's reference magnitude; shared exponent floor(log2 alpha) - 2.
+    // For a normal alpha the binary32 exponent field is floor(log2 alpha) + 127, so the E8M0 byte is that
+    // field minus 2; below 2^-124 (field < 3) the block is empty.
+    const uint32_t field = (f_bits(__fmul_rn(rho, a)) >> 23) & 0xffu;
+    const bool live = field >= 3u;
+    e8 = live ? field - 2u : 0u;
+    const float X = bits_f((live ? field - 2u : 127u) << 23);           // 2^(byte - 127), a normal number
+    uint32_t packed[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        uint32_t wd = 0;
+        wd = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(wd, xs[8 * d + 0], xs[8 * d + 1], X, 0);
+        wd = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(wd, xs[8 * d + 2], xs[8 * d + 3], X, 1);
+        wd = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(wd, xs[8 * d + 4], xs[8 * d + 5], X, 2);
+        wd = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(wd, xs[8 * d + 6], xs[8 * d + 7], X, 3);
+        packed[d] = live ? wd : 0u;
+    }
+    codes = uint4{packed[0], packed[1], packed[2], packed[3]};
+}
+
 }  // namespace svdq

@@ -16,6 +16,7 @@
 // weights are what is read, and expanding them to 6 bits in memory first would move them three times), against the
 // expanded ones, nibble activations against the nibble kernel's packed weights (both turned into E3M2 fields in
 // registers; same integer group sums), and MXFP4.
+#include "svdq_act.h"
 #include "svdq_dev.h"
 #include "svdq_epilogue.h"
 #include "svdq_kernels.h"
@@ -119,11 +120,35 @@ struct Channels {
         }
     }
 };
-template <int SRC, int NI, int MT>
-__device__ __forceinline__ void multiply(const Tokens<SRC, MT>& t, const Channels<SRC, NI>& c, float16v (&y)[NI][MT], const int kh) {
+// y += one group of an n-block times one of a token block: the weights as loaded, the tokens as fields (b) and scale pieces (sp,
+// zeros in the lanes of k half 1: the scale product uses those of half 0 only).
+template <int SRC>
+__device__ __forceinline__ LaneCodes<true> weight_fields(const uint4& w, const uint2& wh) {
+    if constexpr (SRC == SMALL_E3M2_PACKED) return LaneCodes<true>{w, wh};
+    else return e3m2_of_nibbles(w);
+}
+template <int SRC>
+__device__ __forceinline__ uint2 weight_scales(const uint2& sf, const uint32_t sw, const int kh) {
+    uint2 s = sf;
+    if constexpr (SRC == SMALL_E3M2_CANONICAL) {
+        const uint32_t p = split_bf16(bits_f(sw)), w1 = p & 0xffffu, w2 = p >> 16;
+        s = uint2{w1 | (w1 << 16), w2 | (w2 << 16)};
+    }
+    return uint2{kh ? 0u : s.x, kh ? 0u : s.y};
+}
+__device__ __forceinline__ void fold(const LaneCodes<true>& w, const uint2& s, const LaneCodes<true>& x, const uint2& sp, float16v& y) {
+    const int8v av = {(int)w.lo.x, (int)w.lo.y, (int)w.lo.z, (int)w.lo.w, (int)w.hi.x, (int)w.hi.y, 0, 0};
+    const int8v bv = {(int)x.lo.x, (int)x.lo.y, (int)x.lo.z, (int)x.lo.w, (int)x.hi.x, (int)x.hi.y, 0, 0};
     float16v zero;
 #pragma unroll
     for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+    const float16v P = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, zero, 3, 3, 0, 0x7f, 0, 0x7f);
+    const float16v S = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(short4v, s), __builtin_bit_cast(short4v, sp), zero, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y[i] = __builtin_fmaf(P[i], S[i], y[i]);
+}
+template <int SRC, int NI, int MT>
+__device__ __forceinline__ void multiply(const Tokens<SRC, MT>& t, const Channels<SRC, NI>& c, float16v (&y)[NI][MT], const int kh) {
     LaneCodes<true> xf[MT];
     uint2 sp[MT];
 #pragma unroll
@@ -131,34 +156,15 @@ __device__ __forceinline__ void multiply(const Tokens<SRC, MT>& t, const Channel
         if constexpr (SRC == SMALL_NIBBLE) xf[mi] = e3m2_of_nibbles(t.x[mi]);
         else xf[mi] = LaneCodes<true>{t.x[mi], t.xh[mi]};
         uint32_t p = (SRC == SMALL_NIBBLE) ? split_bf16(bits_f(t.sx[mi])) : t.sx[mi];
-        p = kh ? 0u : p;                              // the scale product uses the lanes of k half 0 only
+        p = kh ? 0u : p;
         sp[mi] = uint2{p, p};
     }
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
-        LaneCodes<true> wf;
-        uint2 s;
-        if constexpr (SRC == SMALL_E3M2_PACKED) wf = LaneCodes<true>{c.w[ni], c.wh[ni]};
-        else wf = e3m2_of_nibbles(c.w[ni]);
-        if constexpr (SRC == SMALL_E3M2_CANONICAL) {
-            const uint32_t p = split_bf16(bits_f(c.sw[ni])), w1 = p & 0xffffu, w2 = p >> 16;
-            s = uint2{w1 | (w1 << 16), w2 | (w2 << 16)};
-        } else {
-            s = c.sf[ni];
-        }
-        s.x = kh ? 0u : s.x;
-        s.y = kh ? 0u : s.y;
-        const int8v av = {(int)wf.lo.x, (int)wf.lo.y, (int)wf.lo.z, (int)wf.lo.w, (int)wf.hi.x, (int)wf.hi.y, 0, 0};
+        const LaneCodes<true> wf = weight_fields<SRC>(c.w[ni], c.wh[ni]);
+        const uint2 s = weight_scales<SRC>(c.sf[ni], c.sw[ni], kh);
 #pragma unroll
-        for (int mi = 0; mi < MT; ++mi) {
-            const int8v bv = {(int)xf[mi].lo.x, (int)xf[mi].lo.y, (int)xf[mi].lo.z, (int)xf[mi].lo.w,
-                              (int)xf[mi].hi.x, (int)xf[mi].hi.y, 0, 0};
-            const float16v P = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, zero, 3, 3, 0, 0x7f, 0, 0x7f);
-            const float16v S = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(short4v, s),
-                                                                        __builtin_bit_cast(short4v, sp[mi]), zero, 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) y[ni][mi][i] = __builtin_fmaf(P[i], S[i], y[ni][mi][i]);
-        }
+        for (int mi = 0; mi < MT; ++mi) fold(wf, s, xf[mi], sp[mi], y[ni][mi]);
     }
 }
 
@@ -330,6 +336,305 @@ hipError_t launch_src(const SmallArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// ---- The whole layer in one launch, for few tokens and a short K.
+//
+// There a layer is what its two launches cost: M = 256, K = N = 512, 4.9 us of quantise pass and 4.2 of GEMM on the GPU, most of it
+// starts, ends and first loads, and 3.4 us of host time for each.  Here every block quantises the tokens of its tile itself,
+// through the quantise pass's own chain, and multiplies them by its channels' weights; only the partial tiles, and those of h,
+// meet in LDS.  The blocks of the first channel tile leave codes, scales and h in the layer's buffers.  Wave w has the 64-groups
+// w, w + 8, ..
+// The price is that the tokens are quantised and projected once per channel tile: 128 bytes of L1 fragments and some 6 vector
+// instructions per token for each of K, which is why K is short (small_fused).  M = 256, K = N = 512: 10.6 -> 6.6 us a call, of which
+// the kernel's 6.6 (one launch of 3.4 us and the caller's own host work take about as long); MXFP4 9.9 -> 6.9, the kernel 5.8.
+// SPREAD = false: 32 tokens.  A wave's lanes hold a group's codes just as the matrix instruction wants them.
+// SPREAD: 1 << rs tokens, at most 16.  The chain takes 32 blocks of 32 values per half wave, whatever tokens and groups they are of,
+// and the codes go through LDS.
+struct FusedArgs {
+    const uint16_t* x;
+    int64_t ldx;
+    const float* inv_lambda;
+    float rho;
+    int gelu, rs;
+    const uint4* l1p;
+    uint8_t* codes;              // out, as the format's quantise pass writes them
+    void* scales;
+    float* h;
+    const uint8_t *w0, *w1, *w2;
+    const uint16_t* L2;
+    const float* bias;
+    int64_t M;
+    int N, K, r;
+    uint16_t* y;
+    int64_t ldy;
+};
+// wait for this wave's LDS traffic, then for the other waves: loads from global memory stay in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+constexpr int IL_ROW = 36;                                 // floats between the smoothing factors of two halves of groups in LDS
+constexpr int H_ROW = 36;                                  // and between rows of h
+// LDS of a block, in bytes: partial tiles, partial h's and h, smoothing factors; SPREAD: 16 + 8 + 4 bytes per token and half
+// group, and its 32 values where they are projected
+constexpr uint32_t fused_h_bytes() { return WV * 32 * 32 * 4 + 32 * H_ROW * 4; }
+inline uint32_t fused_lds(int ni, int K, int r, bool spread, int rs) {
+    return (uint32_t)(WV * ni * 4096 + (r ? fused_h_bytes() : 0) + K / 32 * IL_ROW * 4 + (spread ? (K / 32 * (r ? 92 : 28)) << rs : 0));
+}
+
+template <int SRC, int NI, bool SPREAD>
+__global__ __launch_bounds__(64 * WV, 2)
+void fused_layer_kernel(const FusedArgs a) {
+    constexpr bool MX = SRC == SMALL_MXFP4;
+    constexpr int Q = NI * 4;                              // quads of the tile
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    float4 (*const part)[Q][64] = reinterpret_cast<float4 (*)[Q][64]>(smem);
+    float* const hpart = reinterpret_cast<float*>(smem + WV * Q * 1024);             // [WV][32][32]
+    float* const hsum = hpart + WV * 32 * 32;                                        // [32][H_ROW]
+    float* const il_s = a.r ? hsum + 32 * H_ROW : hpart;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, kh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = (int)blockIdx.x * 32 * NI, ng = a.K >> 6;
+    const int rs = SPREAD ? a.rs : 5, rmask = (1 << rs) - 1, trow = l32 & rmask;     // this lane's token of the tile
+    const int64_t m0 = (int64_t)blockIdx.y << rs, row = m0 + trow;
+    uint8_t* const clo = reinterpret_cast<uint8_t*>(il_s + (a.K >> 5) * IL_ROW);     // SPREAD: [2 g + kh][token] x 16, x 8, x 4 bytes
+    uint8_t* const chi = clo + (((a.K >> 5) * 16) << rs);
+    uint8_t* const csc = chi + (((a.K >> 5) * 8) << rs);
+    // its piece s at place s ^ (token / 4) % 4: the 16 tokens of a read stand in different banks
+    uint8_t* const cxv = csc + (((a.K >> 5) * 4) << rs);
+    auto x_place = [&](const int g, const int s) { return reinterpret_cast<uint4*>(cxv + (((2 * g + kh) << rs) + trow) * 64) + (s ^ ((trow >> 2) & 3)); };
+    const bool first = blockIdx.x == 0;
+    const Buffers B{buffer(nullptr), buffer(nullptr), buffer(a.w0), buffer(a.w1), buffer(a.w2)};
+    const uint16_t* const xrow = a.x + (row < a.M ? row : a.M - 1) * a.ldx + kh * 32;
+    auto load_x = [&](uint4 (&x)[4], const int g) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x[s] = reinterpret_cast<const uint4*>(xrow + g * 64)[s];
+    };
+
+    for (int i = tid * 4; i < a.K; i += 256 * WV) *reinterpret_cast<float4*>(il_s + (i >> 5) * IL_ROW + (i & 31)) = *reinterpret_cast<const float4*>(a.inv_lambda + i);
+    // quantise this lane's 32 values of group g into fields (MXFP4: nibbles) and scale, and into the layer's buffers
+    struct Coded {
+        LaneCodes<true> c;
+        uint32_t s;                                        // scale pieces; MXFP4: the E8M0 byte
+    };
+    auto quantise = [&](const uint4 (&x)[4], const int g, const bool writes) {
+        const float* il = il_s + (2 * g + kh) * IL_ROW;
+        Coded o;
+        if constexpr (MX) {
+            quantize_block_mx(x, il, a.rho, o.c.lo, o.s);
+            if (writes) {
+                *reinterpret_cast<uint4*>(a.codes + ((size_t)g * a.M + row) * 32 + kh * 16) = o.c.lo;
+                uint8_t* se = (uint8_t*)a.scales + (((size_t)(g >> 1) * a.M + row) * 2 + kh) * 2;
+                se[g & 1] = (uint8_t)o.s;
+                if (g == ng - 1 && (ng & 1)) se[1] = 0;                  // a group past K counts as empty
+            }
+        } else {
+            float s;
+            uint4 nib;
+            quantize_rows<true, SRC == SMALL_NIBBLE>(x, il, a.rho, o.c, s, &nib);
+            o.s = split_bf16(s);
+            if (writes) {
+                if constexpr (SRC == SMALL_NIBBLE) {
+                    *reinterpret_cast<uint4*>(a.codes + ((size_t)g * a.M + row) * 32 + kh * 16) = nib;
+                    if (kh == 0) ((float*)a.scales)[(size_t)g * a.M + row] = s;
+                } else {
+                    const size_t Mp = (size_t)((a.M + 3) & ~(int64_t)3);
+                    uint8_t* blk = a.codes + (size_t)g * Mp * E3M2_ROW_BYTES;
+                    *reinterpret_cast<uint4*>(blk + (size_t)row * 32 + kh * 16) = o.c.lo;
+                    *reinterpret_cast<uint2*>(blk + Mp * 32 + ((size_t)kh * Mp + row) * 8) = o.c.hi;
+                    if (kh == 0) *reinterpret_cast<uint2*>(blk + Mp * 48 + (size_t)row * 8) = uint2{o.s, o.s};
+                }
+            }
+        }
+        return o;
+    };
+    uint4 xt[4];                                           // SPREAD: the wave's first share of the chain
+    const int per_wave = 32 >> rs, tg = wave * per_wave + (l32 >> rs);
+    if (SPREAD && tg < ng) load_x(xt, tg);
+
+    struct Group {
+        uint4 x[4], l1[4][2], w[NI];
+        uint2 wh[NI], sf[NI];
+        uint32_t sw[NI];
+    };
+    auto load = [&](Group& o, const int g) {
+        if (!SPREAD) load_x(o.x, g);
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            const uint32_t fr = (uint32_t)((n0 >> 5) + ni) * ng + g;
+            if constexpr (SRC == SMALL_E3M2_CANONICAL) {
+                o.w[ni] = at<uint4>(B.w0, (uint32_t)g * 32 + (uint32_t)ni * 16 * a.K, (uint32_t)(n0 + l32) * (uint32_t)(a.K >> 1) + kh * 16);
+                o.sw[ni] = at<uint32_t>(B.w1, ((uint32_t)g * a.N + ni * 32) * 4, (uint32_t)(n0 + l32) * 4);
+            } else {
+                o.w[ni] = at<uint4>(B.w0, fr * 1024, lane * 16);
+                if constexpr (SRC == SMALL_E3M2_PACKED) {
+                    o.wh[ni] = at<uint2>(B.w1, fr * 512, lane * 8);
+                    o.sf[ni] = at<uint2>(B.w2, fr * 256, l32 * 8);
+                } else if constexpr (SRC == SMALL_NIBBLE) {
+                    o.sf[ni] = at<uint2>(B.w1, fr * 512, l32 * 8);
+                } else {
+                    o.sw[ni] = at<uint16_t>(B.w1, (((uint32_t)((n0 >> 5) + ni) * ((ng + 1) >> 1)) + (g >> 1)) * 128, lane * 2);
+                }
+            }
+        }
+        if (a.r > 0) {
+            const uint4* pb = a.l1p + (size_t)g * (4 * 2 * 64) + lane;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                o.l1[s][0] = pb[(s * 2 + 0) * 64];
+                o.l1[s][1] = pb[(s * 2 + 1) * 64];
+            }
+        }
+    };
+    Group cur, nxt;
+    if (wave < ng) load(cur, wave);
+    if (SPREAD && wave + WV < ng) load(nxt, wave + WV);
+    // what the end needs, requested now: this wave finishes quad fq of channel block fni
+    const int fni = (NI == 1) ? 0 : wave >> 2, fq = wave & 3;
+    const bool finishes = wave < Q;
+    uint32_t l2w[2][4] = {};
+    float4 bv{0.f, 0.f, 0.f, 0.f};
+    if (finishes) {
+        if (a.r > 0) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (16 * ks < a.r) {
+                        const uint16_t* p = a.L2 + (int64_t)(16 * ks + 8 * kh + 2 * e) * a.N + n0 + 32 * fni + l32;
+                        l2w[ks][e] = (uint32_t)p[0] | ((uint32_t)p[a.N] << 16);
+                    }
+        }
+        if (a.bias) bv = *reinterpret_cast<const float4*>(a.bias + n0 + 32 * fni + 8 * fq + 4 * kh);
+    }
+    float16v y[NI], hacc, zero;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+    hacc = zero;
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) y[ni] = zero;
+    lds_barrier();
+    if constexpr (SPREAD) {
+        for (int g = tg; g < ng; g += WV * per_wave) {
+            if (a.gelu) gelu_tanh_rows(xt);
+            const Coded o = quantise(xt, g, first && row < a.M);
+            const int at = ((2 * g + kh) << rs) + trow;
+            *reinterpret_cast<uint4*>(clo + at * 16) = o.c.lo;
+            if (!MX) *reinterpret_cast<uint2*>(chi + at * 8) = o.c.hi;
+            *reinterpret_cast<uint32_t*>(csc + at * 4) = o.s;
+            if (a.r > 0) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) *x_place(g, s) = xt[s];
+            }
+            if (g + WV * per_wave < ng) load_x(xt, g + WV * per_wave);
+        }
+        lds_barrier();
+    }
+
+    for (int g = wave; g < ng; g += WV) {
+        if (!SPREAD && g + WV < ng) load(nxt, g + WV);
+        if (!SPREAD && a.gelu) gelu_tanh_rows(cur.x);
+        if (a.r > 0) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const bf16x8 av = __builtin_bit_cast(bf16x8, SPREAD ? *x_place(g, s) : cur.x[s]);
+                hacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, cur.l1[s][0]), hacc, 0, 0, 0);
+                hacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, cur.l1[s][1]), hacc, 0, 0, 0);
+            }
+        }
+        Coded o;
+        if constexpr (SPREAD) {
+            const int at = ((2 * g + kh) << rs) + trow;
+            o.c.lo = *reinterpret_cast<const uint4*>(clo + at * 16);
+            if (!MX) o.c.hi = *reinterpret_cast<const uint2*>(chi + at * 8);
+            o.s = *reinterpret_cast<const uint32_t*>(csc + at * 4);
+        } else {
+            o = quantise(cur.x, g, first && row < a.M);
+        }
+        if constexpr (MX) {
+            const int8v bvx = {(int)o.c.lo.x, (int)o.c.lo.y, (int)o.c.lo.z, (int)o.c.lo.w, 0, 0, 0, 0};
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                const int8v av = {(int)cur.w[ni].x, (int)cur.w[ni].y, (int)cur.w[ni].z, (int)cur.w[ni].w, 0, 0, 0, 0};
+                y[ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bvx, y[ni], 4, 4, 0, (int)(cur.sw[ni] >> (8 * (g & 1))), 0, (int)o.s);
+            }
+        } else {
+            const uint32_t p = kh ? 0u : o.s;
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+                fold(weight_fields<SRC>(cur.w[ni], cur.wh[ni]), weight_scales<SRC>(cur.sf[ni], cur.sw[ni], kh), o.c, uint2{p, p}, y[ni]);
+        }
+        cur = nxt;
+        if (SPREAD && g + 2 * WV < ng) load(nxt, g + 2 * WV);
+    }
+
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const float16v& t = y[q >> 2];
+        part[wave][q][lane] = float4{t[4 * (q & 3)], t[4 * (q & 3) + 1], t[4 * (q & 3) + 2], t[4 * (q & 3) + 3]};
+    }
+    if (a.r > 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) hpart[wave * 1024 + (8 * (i >> 2) + 4 * kh + (i & 3)) * 32 + l32] = hacc[i];
+    }
+    lds_barrier();
+    if (a.r > 0) {
+        const int hr = tid >> 4, hj = (tid & 15) * 2;
+        auto piece = [&](const int w) { return *reinterpret_cast<const float2*>(hpart + w * 1024 + hr * 32 + hj); };
+        auto sum4 = [&](const int w) {
+            const float2 p0 = piece(w), p1 = piece(w + 1), p2 = piece(w + 2), p3 = piece(w + 3);
+            return float2{(p0.x + p1.x) + (p2.x + p3.x), (p0.y + p1.y) + (p2.y + p3.y)};
+        };
+        const float2 s0 = sum4(0), s1 = sum4(4), t{s0.x + s1.x, s0.y + s1.y};
+        *reinterpret_cast<float2*>(hsum + hr * H_ROW + hj) = t;
+        if (first && hr <= rmask && hj < a.r && m0 + hr < a.M) *reinterpret_cast<float2*>(a.h + (m0 + hr) * a.r + hj) = t;
+        lds_barrier();
+    }
+    if (!finishes) return;
+    float16v lr = zero;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+        if (16 * ks < a.r) {
+            const float* hp = hsum + l32 * H_ROW + 16 * ks + 8 * kh;
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float2 v = *reinterpret_cast<const float2*>(hp + 2 * e);
+                hi[e] = f2_bf16_rne(v.x, v.y);
+                lo[e] = f2_bf16_rne(v.x - bf16lo_f(hi[e]), v.y - bf16hi_f(hi[e]));
+            }
+            const bf16x8 lf = __builtin_bit_cast(bf16x8, uint4{l2w[ks][0], l2w[ks][1], l2w[ks][2], l2w[ks][3]});
+            lr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf, __builtin_bit_cast(bf16x8, uint4{hi[0], hi[1], hi[2], hi[3]}), lr, 0, 0, 0);
+            lr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf, __builtin_bit_cast(bf16x8, uint4{lo[0], lo[1], lo[2], lo[3]}), lr, 0, 0, 0);
+        }
+    float4 p[WV];
+#pragma unroll
+    for (int w = 0; w < WV; ++w) p[w] = part[w][wave][lane];
+    auto sum = [&](auto c, const float l, const float b) {
+        return (((c(p[0]) + c(p[4])) + (c(p[1]) + c(p[5]))) + ((c(p[2]) + c(p[6])) + (c(p[3]) + c(p[7])))) + (l + b);
+    };
+    auto low = [&](const int j) { return fq == 0 ? lr[j] : fq == 1 ? lr[4 + j] : fq == 2 ? lr[8 + j] : lr[12 + j]; };
+    const float v0 = sum([](const float4& f) { return f.x; }, low(0), bv.x), v1 = sum([](const float4& f) { return f.y; }, low(1), bv.y);
+    const float v2 = sum([](const float4& f) { return f.z; }, low(2), bv.z), v3 = sum([](const float4& f) { return f.w; }, low(3), bv.w);
+    if (l32 <= rmask && row < a.M)
+        *reinterpret_cast<uint2*>(a.y + row * a.ldy + n0 + 32 * fni + 8 * fq + 4 * kh) = uint2{f2_bf16_rne(v0, v1), f2_bf16_rne(v2, v3)};
+}
+
+template <int SRC>
+hipError_t launch_fused_src(FusedArgs a, hipStream_t stream) {
+    auto go = [&](auto kern, int ni, bool spread, int rs) {
+        a.rs = rs;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(a.N / (32 * ni)), (unsigned)((a.M + (1 << rs) - 1) >> rs)), dim3(64 * WV),
+                           fused_lds(ni, a.K, a.r, spread, rs), stream, a);
+    };
+    if (small_fused(a.M, a.N, a.K, a.r, SRC == SMALL_MXFP4) == FUSED_SPREAD) {
+        int rs = 0;
+        while (rs < 4 && (1 << rs) < a.M) ++rs;
+        go(fused_layer_kernel<SRC, 1, true>, 1, true, rs);
+    } else if ((a.M + 31) / 32 * (a.N / 32) <= 256) {
+        go(fused_layer_kernel<SRC, 1, false>, 1, false, 5);
+    } else {
+        go(fused_layer_kernel<SRC, 2, false>, 2, false, 5);
+    }
+    return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256)
 void sum_slices_kernel(const float* __restrict__ part, int slices, int64_t n, float* __restrict__ h) {
     sum_slices(part, slices, n, h, (int64_t)blockIdx.x * 256 + threadIdx.x);
@@ -353,6 +658,19 @@ hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scale
         case SMALL_E3M2_PACKED: return launch_src<SMALL_E3M2_PACKED>(a, stream);
         case SMALL_NIBBLE: return launch_src<SMALL_NIBBLE>(a, stream);
         default: return launch_src<SMALL_MXFP4>(a, stream);
+    }
+}
+
+hipError_t launch_fused_layer(int source, const void* x, int64_t ldx, const float* inv_lambda, float rho, bool gelu, const void* l1p,
+                              uint8_t* codes, void* scales, float* h, const void* w0, const void* w1, const void* w2,
+                              const void* L2, const float* bias, int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream) {
+    const FusedArgs a{(const uint16_t*)x, ldx, inv_lambda, rho, gelu, 0, (const uint4*)l1p, codes, scales, h,
+                      (const uint8_t*)w0, (const uint8_t*)w1, (const uint8_t*)w2, (const uint16_t*)L2, bias, M, N, K, r, (uint16_t*)y, ldy};
+    switch (source) {
+        case SMALL_E3M2_CANONICAL: return launch_fused_src<SMALL_E3M2_CANONICAL>(a, stream);
+        case SMALL_E3M2_PACKED: return launch_fused_src<SMALL_E3M2_PACKED>(a, stream);
+        case SMALL_NIBBLE: return launch_fused_src<SMALL_NIBBLE>(a, stream);
+        default: return launch_fused_src<SMALL_MXFP4>(a, stream);
     }
 }
 

@@ -85,6 +85,47 @@ def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
     assert rel_fro(synth.bf16_bits_to_f32(host_bits(y2)).astype(np.float64), synth.bf16_bits_to_f32(host_bits(y1)).astype(np.float64)) <= 2e-3
 
 
+@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble", "mxfp4"])
+@pytest.mark.parametrize("M,K,N,r,gelu,ldx", [
+    (1, 64, 128, 32, False, 64), (1, 1792, 256, 16, True, 1792), (1, 3328, 128, 0, False, 3400),    # one token; fewer groups than waves, the longest K
+    (2, 576, 128, 16, False, 584), (3, 1344, 384, 32, True, 1344), (5, 1600, 128, 0, False, 1600),  # odd group counts; a tile of 2, 4, 8
+    (16, 1408, 256, 32, False, 1408), (17, 832, 128, 16, False, 840), (500, 576, 128, 0, True, 576),   # 16-token tiles: full, one over, ragged
+    (33, 512, 128, 32, False, 512), (1000, 704, 256, 16, False, 704),             # 32-token tiles of 32 channels, ragged
+    (1025, 1216, 384, 32, True, 1224), (1023, 448, 512, 0, False, 448),           # and of 64
+])
+def test_layer_in_one_launch(svdq, container, M, K, N, r, gelu, ldx):
+    """Few tokens and a short K: forward() is one kernel.  Codes and scales left behind are those of the quantise pass, bit for bit,
+    h is its sum in another order at most (32-bit sums of K products: 1e-6), and y that of the GEMM on them (the bar of the layer)."""
+    mx = container == "mxfp4"
+    xs = torch.full((M, ldx), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    bits, _ = synth.make_x(M + K, M, K, outlier_count=3, outlier_scale=30.0)
+    xs[:, :K] = dev(bits).view(torch.bfloat16)
+    x = xs[:, :K]
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(bits)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(M + K, K, N, r, cm, fmt="mxfp4" if mx else "int4")
+    lin = svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1) if r else None, dev(L.L2) if r else None, dev(L.qw), dev(L.sw),
+                          dev(L.bias), container=container.split()[0], resident="packed" if "packed" in container else "w4")
+    codes, scales, h, _ = lin.buffers(M, "cuda:0")
+    buf = codes.buf if container.startswith("e3m2") else codes
+
+    def held():                                   # rows M .. M + 3 of the E3M2 planes are nobody's
+        if not container.startswith("e3m2"):
+            return [buf.clone(), scales.view(torch.uint8).clone()]
+        Mp = (M + 3) // 4 * 4
+        planes, at = buf.view(K // 64, Mp * 56), [(0, 32)] + [(Mp * 32 + i * Mp * 8, 8) for i in range(3)]
+        return [planes[:, o:o + M * w].clone() for o, w in at]
+
+    buf.fill_(0xA5)
+    y = lin.forward(x, 0.8, gelu=gelu).clone()
+    one, h_one = held(), None if h is None else h.clone()
+    two = lin.gemm(*lin.quantize(x, 0.8, gelu))
+    assert all(torch.equal(a, b) for a, b in zip(one, held()))
+    if r:
+        assert rel_fro(h_one.double().cpu().numpy(), h.double().cpu().numpy()) <= 1e-6
+    assert rel_fro(y.double().cpu().numpy(), two.double().cpu().numpy()) <= 2e-3
+    assert torch.isfinite(y.float()).all()
+
+
 @pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble"])
 @pytest.mark.parametrize("M,K,N,r", [
     (500, 5120, 5120, 32), (513, 5120, 5120, 16),       # two teams, eight slices; a last tile of one token
