@@ -1,5 +1,6 @@
 // How the E3M2 GEMM takes its tokens: the first of them on 256 x 256 tiles (svdq_e3m2_walk.hip), the rest on 128 x 128
-// tiles (svdq_gemm_e3m2.hip).  Host only.  Both give the same bits, unless the 128 x 128 kernel splits K between two teams.
+// tiles (svdq_gemm_e3m2.hip); or, where they are one tile for every CU at most, on the tiles of svdq_e3m2_mid.hip.  Host only.
+// All give the same bits, unless a kernel splits K between teams.
 #pragma once
 #include <cstdint>
 
@@ -46,6 +47,49 @@ inline int64_t e3m2_walk_rows(int64_t M, int N, int K, bool teams, int walkers, 
         if (c < least) {
             least = c;
             best = rows;
+        }
+    }
+    return best;
+}
+
+// The kernel for middling numbers of tokens (svdq_e3m2_mid.hip): tokens and channels of a block's tile, teams that split K,
+// slots of a team's ring.  Its K loop is as long as the ring at least.
+struct E3m2Mid {
+    int bm, bn, teams, slots;
+    double begin, group, loaded;                                 // us: a tile's start and end, a team's group on an idle chip, more on a full one
+};
+constexpr E3m2Mid E3M2_MID[] = {{256, 192, 1, 5, 9.1, 0.601, 0.242}, {128, 192, 2, 4, 8.2, 0.612, 0.314}, {128, 96, 4, 3, 8.5, 0.676, 0.390}, {64, 96, 8, 2, 8.0, 0.970, 0.385}};
+inline int e3m2_mid_groups(const E3m2Mid& m, int K) { return (K / 64 + m.teams - 1) / m.teams; }
+// Which of them a launch of all tokens takes, or -1: the others.  split: K may be split between teams (a whole layer).
+// Costs fitted to 95 shapes of M = 96 .. 4100, K = 1024 .. 13824 with a term (2 to 4 %); without one a tile's start is 2 us shorter.
+// Only where the tiles are one for every CU at most: further rounds take long.  The others are estimated as above, except that two teams of
+// 128 x 128 tiles on a chip that they fill take 9.3 + 3.1 k, and with a term their h is summed ahead of them (1.5 us) for up to 4096 tokens.  Layers, us:
+// M = 2048, K = N = 5120 94.2 -> 84.3, M = 1500, N = 3072 59.5 -> 50.8, M = 1024, K = 2048, N = 5120 36.3 -> 32.6, M = 512 38.8 -> 37.6.
+// With less than 1.5 % to gain the others are taken: M = 1500, K = 1024, N = 2048 20.8 against 22.5.
+inline int e3m2_mid_shape(int64_t M, int N, int K, bool split, int walkers, bool lowrank) {
+    if (walkers != 8 * CUS_PER_XCD) return -1;
+    const int64_t rows = e3m2_walk_rows(M, N, K, split, walkers, lowrank);
+    double least = 0.0;
+    if (rows) {
+        least = e3m2_walk_cost((rows + 255) / 256 * (N / 256), K, walkers, lowrank) + (rows < M ? 2.5 + e3m2_tiles_cost(M - rows, N, K, split, lowrank) : 0.0);
+    } else if (split && K >= 2048 && busiest_xcd((int)((M + 127) / 128), N / 128) <= CUS_PER_XCD) {
+        least = (lowrank ? 9.3 : 7.3) + 3.1 * (K / 1024.0);
+    } else {
+        least = e3m2_tiles_cost(M, N, K, split, lowrank);
+    }
+    if (!(split && rows == 0 && K >= 2048) && split && lowrank && M <= 4096 && K >= 1024) least += 1.5;
+    least *= 0.985;
+    int best = -1;
+    for (int i = 0; i < 4; ++i) {
+        const E3m2Mid& m = E3M2_MID[i];
+        const int64_t mtiles = (M + m.bm - 1) / m.bm;
+        const int ntiles = (N + m.bn - 1) / m.bn;
+        if ((m.teams > 1 && !split) || mtiles > 256 || busiest_xcd((int)mtiles, ntiles) > CUS_PER_XCD || e3m2_mid_groups(m, K) < m.slots) continue;
+        const double load = (double)mtiles * ntiles / walkers;
+        const double c = m.begin - (lowrank ? 0.0 : 2.0) + e3m2_mid_groups(m, K) * (m.group + (load > 0.4 ? m.loaded * (load - 0.4) : 0.0));
+        if (c < least) {
+            least = c;
+            best = i;
         }
     }
     return best;

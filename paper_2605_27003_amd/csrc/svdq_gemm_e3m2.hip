@@ -653,6 +653,10 @@ static bool two_team_shape(int mtiles, int N, int K) { return K >= 2048 && busie
 static hipError_t launch_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
                               int64_t M, int N, int K, int r, void* y, int64_t ldy, int out_f32, bool teams,
                               hipStream_t stream, const SlicedH& hs = SlicedH{}) {
+    if (!out_f32) {
+        const int mid = e3m2_mid_shape(M, N, K, teams, walking_blocks(), r != 0);
+        if (mid >= 0) return launch_e3m2_mid(mid, act, w_packed, h, hs.slices, hs.sum, L2, bias, M, N, K, r, y, ldy, stream);
+    }
     const int64_t walked = out_f32 ? 0 : e3m2_walk_rows(M, N, K, teams, walking_blocks(), r != 0);
     if (walked) {
         const hipError_t e = launch_e3m2_walk(act, w_packed, h, L2, bias, M, walked, N, K, r, y, ldy, stream);
@@ -684,6 +688,7 @@ hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const flo
 }
 
 bool layer_e3m2_takes_slices(int64_t M, int N, int K) {             // only a low-rank term has slices
+    if (e3m2_mid_shape(M, N, K, true, walking_blocks(), true) >= 0) return true;
     return two_team_shape((int)((M + BM - 1) / BM), N, K) && e3m2_walk_rows(M, N, K, true, walking_blocks(), true) == 0;
 }
 

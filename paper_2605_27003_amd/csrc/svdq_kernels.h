@@ -57,6 +57,9 @@ hipError_t launch_linear_e3m2(const uint8_t* act, const void* w_packed,
 // svdq_e3m2_walk.hip: tokens [0, rows) of M, rows a multiple of 256 or M; N a multiple of 256, K >= 320, bf16 y
 hipError_t launch_e3m2_walk(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
                             int64_t M, int64_t rows, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
+// svdq_e3m2_mid.hip: tiles of E3M2_MID[shape] (svdq_e3m2_plan.h), bf16 y.  slices > 1: h is as many partial h's, whose sum goes to hsum
+hipError_t launch_e3m2_mid(int shape, const uint8_t* act, const void* w_packed, const float* h, int slices, float* hsum, const void* L2, const float* bias,
+                           int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
 // slices > 1: h is as many partial h's, whose sum goes to hsum; only where layer_e3m2_takes_slices says so
 hipError_t launch_layer_e3m2(const uint8_t* act, const void* w_packed, const float* h, const void* L2, const float* bias,
                              int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream, int slices, float* hsum);
@@ -85,7 +88,7 @@ constexpr int SMALL_SLICES = 8;                  // waves of a block = most part
 inline int small_shape(int64_t M, int N, int K, bool mxfp4 = true) {
     const int64_t b32 = ((M + 31) / 32) * (N / 32), b64 = ((M + 63) / 64) * ((N + 63) / 64);
     if (b32 <= (mxfp4 ? 256 : 512)) return 1;
-    const int limit = mxfp4 ? (N <= 2048 && K >= 4096 ? 384 : 320) : (N >= 4096 && K >= 2048) ? 480 : 256;
+    const int limit = mxfp4 ? (N <= 2048 && K >= 4096 ? 384 : 320) : (N >= 4096 && K >= 2048 && (M <= 160 || N > 6144)) ? 480 : 256;
     return b64 <= limit ? 2 : 0;
 }
 // The few-token GEMM addresses codes and weights with 32-bit byte offsets (its tokens may be the last of many).

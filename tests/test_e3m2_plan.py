@@ -52,7 +52,14 @@ int main(int n, char** v) {
             most = own > most ? own : most;
         }
         for (int s : seen) bad += s != 1;
-        printf("%ld %d\\n", rows, bad + (rows && most > (mt * nt + 7) / 8));
+        const int N = atoi(v[i + 1]), K = atoi(v[i + 2]), mid = svdq::e3m2_mid_shape(M, N, K, true, 256, atoi(v[i + 3]) != 0);
+        const int alone = svdq::e3m2_mid_shape(M, N, K, false, 256, atoi(v[i + 3]) != 0);
+        int fits = 1;
+        if (mid >= 0) {
+            const svdq::E3m2Mid& m = svdq::E3M2_MID[mid];
+            fits = svdq::e3m2_mid_groups(m, K) >= m.slots && svdq::busiest_xcd((int)((M + m.bm - 1) / m.bm), (N + m.bn - 1) / m.bn) <= 32;
+        }
+        printf("%ld %d %d %d %d\\n", rows, bad + (rows && most > (mt * nt + 7) / 8), mid, alone, fits);
     }
 }
 """
@@ -65,10 +72,10 @@ def plan(tmp_path_factory):
     subprocess.run([HIPCC, "--cuda-host-only", "-std=c++17", "-O1", "-I", CSRC, str(d / "driver.hip"), "-o", str(d / "driver")],
                    check=True, capture_output=True, text=True)
 
-    def ask(shapes):
+    def ask(shapes, whole=False):
         args = [str(v) for s in shapes for v in (*s, 32)[:4]]          # M, N, K and the rank, 32 where a shape names none
         out = subprocess.run([str(d / "driver"), *args], check=True, capture_output=True, text=True).stdout
-        return [tuple(map(int, line.split())) for line in out.splitlines()]
+        return [tuple(map(int, line.split()))[:2 if not whole else None] for line in out.splitlines()]
     return ask
 
 
@@ -98,3 +105,31 @@ def test_shapes_of_the_gpu_tests_are_walked(plan):
     assert [rows for rows, _ in plan(shapes)] == [s[0] for s in shapes[:-1]] + [3072]
     layers = [(3300, 5120, 5120, 32), (3300, 5120, 5120, 0), (1216, 13824, 2112, 32), (5376, 3072, 2112, 16)]
     assert [rows for rows, _ in plan(layers)] == [3072, 3072, 1024, 5376]
+
+
+# M, N, K, layers with a low-rank term, us on the tiles of the entries of E3M2_MID and on the others
+MEASURED_MID = [
+    (384, 3072, 5120, (72.1, 46.6, 36.3, 31.8), 38.2), (700, 13824, 3072, (60.7, 68.3, 91.5, 115.5), 66.9), (1024, 5120, 2048, (42.4, 32.6, 42.8, 59.8), 36.3),
+    (1024, 5120, 5120, (76.9, 56.4, 68.8, 93.0), 61.3), (1024, 13824, 3072, (99.0, 99.4, 115.5, 151.0), 68.3), (1500, 2048, 1024, (29.1, 22.5, 30.4, 36.4), 20.8),
+    (1500, 3072, 5120, (75.9, 50.8, 66.0, 73.3), 59.5), (1500, 5120, 5120, (78.2, 87.3, 92.8, 128.4), 67.2), (2048, 5120, 2048, (44.3, 52.2, 74.1, 94.1), 48.0),
+    (2048, 1024, 5120, (74.4, 48.9, 38.5, 51.5), 40.5), (2048, 3072, 5120, (77.4, 56.9, 69.5, 91.4), 63.1), (2048, 5120, 5120, (84.3, 93.4, 120.2, 148.3), 94.2),
+    (2048, 13824, 3072, (148.1, 154.0, 190.9, 266.3), 116.2), (3000, 3072, 5120, (86.1, 95.6, 102.7, 135.6), 96.7), (3000, 5120, 5120, (149.1, 139.6, 174.6, 225.4), 107.4),
+    (4100, 1024, 5120, (82.0, 57.7, 70.5, 93.7), 64.7), (4100, 13824, 3072, (233.5, 280.4, 369.6, 564.3), 219.1),
+]
+
+
+def test_middling_tokens_near_the_fastest(plan):
+    """No choice more than 4 % from the fastest of the five."""
+    for (M, N, K, mids, others), out in zip(MEASURED_MID, plan([m[:3] for m in MEASURED_MID], whole=True)):
+        took = mids[out[2]] if out[2] >= 0 else others
+        assert took <= 1.04 * min(*mids, others), (M, N, K, out[2])
+
+
+def test_middling_tiles_are_what_the_kernel_takes(plan):
+    """A tile for every CU at most, K loops as long as the rings; without teams only the tile that does not split K.  And the
+    shapes of tests/test_gpu_layer.py take the tiles that they are there for."""
+    shapes = [(M, N, K, r) for M in (1, 64, 129, 700, 2047, 5000, 75600) for N in (128, 640, 2176, 5120, 13824) for K in (64, 320, 576, 1088, 13824) for r in (0, 32)]
+    for s, out in zip(shapes, plan(shapes, whole=True)):
+        assert out[4] == 1 and out[3] in (-1, 0), (s, out)
+    from tests.test_gpu_layer import MIDDLING
+    assert [out[2] for out in plan([(M, N, K, r) for M, K, N, r, _ in MIDDLING], whole=True)] == [m[4] for m in MIDDLING]

@@ -179,6 +179,39 @@ def test_walked_layers(svdq, container, M, K, N, r, walked):
         assert rel_fro(y[walked:].double().cpu().numpy(), want[walked:].double().cpu().numpy()) <= 2e-3
 
 
+# M, K, N, r and the entry of E3M2_MID that takes them (tests/test_e3m2_plan.py asks the plan)
+MIDDLING = [
+    (1916, 384, 4992, 32, 0), (2047, 448, 5120, 0, 0),       # 256 x 192: the shortest K but one, whole channel tiles; one that stands over N
+    (1300, 1088, 3072, 16, 1), (1916, 1088, 2176, 0, 1),     # 128 x 192, two teams of 9 and 8 groups
+    (1025, 1600, 1280, 32, 2), (2305, 3648, 640, 32, 2),     # 128 x 96, four teams of 7, 6, 6, 6 and of 15, 14, 14, 14; a last tile of one token
+    (1916, 1088, 768, 32, 3), (2100, 1216, 512, 0, 3),       # 64 x 96, eight teams, one and three of them with a group more
+    (206, 2112, 4992, 16, 3),
+]
+
+
+@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble"])
+@pytest.mark.parametrize("M,K,N,r,shape", MIDDLING)
+def test_layers_of_middling_tokens(svdq, container, M, K, N, r, shape):
+    """One tile for every CU at most, K split between teams of waves: against the 128 x 128 kernel's binary32 output on the same
+    codes (the bar of the layer); the h left behind is whole."""
+    x, _ = synth.make_x(M + K, M, K, outlier_count=3, outlier_scale=30.0)
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(x)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(M + K, K, N, r, cm)
+    make = lambda c: svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1) if r else None, dev(L.L2) if r else None, dev(L.qw), dev(L.sw), dev(L.bias),
+                                     container=c.split()[0], resident="packed" if "packed" in c else "w4")
+    lin, ref = make(container), make("e3m2 packed")
+    y = lin.forward(dev(x), 0.8).clone()
+    h = lin.buffers(M, y.device)[2]
+    act, _, h_ref = ref.quantize(dev(x), 0.8)
+    want = svdq.linear_w4a4_e3m2(act, ref.w_packed, N, h_ref, ref.L2, ref.bias, out_dtype=torch.float32).double()
+    if r:
+        assert rel_fro(h.double().cpu().numpy(), h_ref.double().cpu().numpy()) <= 1e-6
+    d = (y.double() - want).abs()
+    assert (d.norm() / want.norm()).item() <= 2e-3
+    ulp = torch.exp2(torch.floor(torch.log2(want.abs().clamp_min(1e-30))) - 7)
+    assert bool((d <= torch.maximum(1e-2 * want.pow(2).mean().sqrt(), ulp)).all())
+
+
 def test_layer_gemm_last_tokens_beyond_4_gb(svdq):
     """MXFP4, 4 GB of codes: the last tokens have a launch of their own on the few-token kernel where its 32-bit offsets
     reach them, and must not have one here.  Against the tile kernels alone (sums in another order: one bf16 step)."""
