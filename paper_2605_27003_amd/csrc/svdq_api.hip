@@ -401,6 +401,12 @@ static int layer_slices(const svdq_layer* L, int64_t M) {
         s = svdq::mx_slices((int)row_blocks, groups);
     } else {
         while (s > 1 && (s * row_blocks > 256 || groups / s < 8)) s >>= 1;
+        // With 32 x 32 tiles behind it no more than a round of a block's eight waves, where blocks are left for that (M = 100, K = 1600:
+        // the pass 6.1 us in two slices of thirteen groups, 4.9 in four).  64 x 64 tiles lose what it gains: each of their waves that
+        // has a slice to add adds 0.4 us.
+        const int one_round = (groups + 7) / 8;
+        if (!mx && one_round <= svdq::SMALL_SLICES && one_round > s && one_round * row_blocks <= 256 && small_path(L, M) && svdq::small_shape(M, L->N, L->K, mx) == 1)
+            s = one_round;
     }
     const int slice = (units + s - 1) / s;
     return (units + slice - 1) / slice;
@@ -443,16 +449,13 @@ static bool gemm_takes_slices(const svdq_layer* L, int64_t M, bool fields) {
 // The layer's weights as the kernels for few tokens take them.
 struct SmallWeights {
     int source;
-    const void *w0, *w1, *w2;
+    const void *w0, *w1;
 };
 static SmallWeights small_weights(const svdq_layer* L) {
-    const int N = L->N, K = L->K;
-    const uint8_t* wp = (const uint8_t*)L->w_packed;
-    if (L->format == SVDQ_FMT_INT4) return {svdq::SMALL_NIBBLE, wp, wp + svdq::packed_weight_codes_bytes(N, K), nullptr};
-    if (L->format == SVDQ_FMT_MXFP4) return {svdq::SMALL_MXFP4, wp, wp + svdq::packed_mx_codes_bytes(N, K), nullptr};
-    if (!wp) return {svdq::SMALL_E3M2_CANONICAL, L->qw, L->sw, nullptr};
-    const uint8_t* w1 = wp + svdq::packed_e3m2_w0_bytes(N, K);
-    return {svdq::SMALL_E3M2_PACKED, wp, w1, w1 + svdq::packed_e3m2_w1_bytes(N, K)};
+    if (L->format == SVDQ_FMT_INT4) return {svdq::SMALL_NIBBLE, L->w_packed, nullptr};
+    if (L->format == SVDQ_FMT_MXFP4) return {svdq::SMALL_MXFP4, L->w_packed, nullptr};
+    if (!L->w_packed) return {svdq::SMALL_E3M2_CANONICAL, L->qw, L->sw};
+    return {svdq::SMALL_E3M2_PACKED, L->w_packed, nullptr};
 }
 
 // The GEMM on checked arguments.  h: `slices` partial h's, whose sum goes to hsum, where gemm_takes_slices; one otherwise.
@@ -463,13 +466,13 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
     const uint8_t* wp = (const uint8_t*)L->w_packed;
     if (small_path(L, M)) {
         const SmallWeights w = small_weights(L);
-        return hip_status(svdq::launch_small_gemm(w.source, codes, scales, w.w0, w.w1, w.w2, h, slices, slices > 1 ? hsum : nullptr, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
+        return hip_status(svdq::launch_small_gemm(w.source, codes, scales, w.w0, w.w1, h, slices, slices > 1 ? hsum : nullptr, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
     }
     if (L->format == SVDQ_FMT_MXFP4) {
         const int64_t main = svdq::mx_main_rows(M, N, K, r);
         const hipError_t e = svdq::launch_linear_mx(codes, (const uint8_t*)scales, wp, h, L->L2_bf16, L->bias, M, main, N, K, r, y, ldy, 0, stream);
         if (e != hipSuccess || main == M) return hip_status(e);
-        return hip_status(svdq::launch_small_gemm(svdq::SMALL_MXFP4, codes, scales, wp, wp + svdq::packed_mx_codes_bytes(N, K), nullptr, h, 1, nullptr,
+        return hip_status(svdq::launch_small_gemm(svdq::SMALL_MXFP4, codes, scales, wp, nullptr, h, 1, nullptr,
                                                   L->L2_bf16, L->bias, M, main, N, K, r, y, ldy, stream));
     }
     if (L->format == SVDQ_FMT_INT4 && !fields)
@@ -517,7 +520,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (small_path(L, M) && svdq::small_fused(M, L->N, K, r, L->format == SVDQ_FMT_MXFP4) != svdq::FUSED_NONE) {
         const SmallWeights w = small_weights(L);
         return hip_status(svdq::launch_fused_layer(w.source, x_bf16, ldx, L->inv_lambda, rho, gelu != 0, L->l1_packed, (uint8_t*)codes, scales, h,
-                                                   w.w0, w.w1, w.w2, L->L2_bf16, L->bias, M, L->N, K, r, y, ldy, stream));
+                                                   w.w0, w.w1, L->L2_bf16, L->bias, M, L->N, K, r, y, ldy, stream));
     }
     // without h there is nothing to add up over the slices
     int slices = (r == 0 || scratch) ? layer_slices(L, M) : 1;

@@ -93,8 +93,8 @@ inline int small_shape(int64_t M, int N, int K, bool mxfp4 = true) {
 }
 // The few-token GEMM addresses codes and weights with 32-bit byte offsets (its tokens may be the last of many).
 inline bool small_reach(int64_t M, int64_t N, int64_t K) { return (M > N ? M : N) * K < (int64_t)1 << 32; }
-// tokens [begin, M).  hsum: receives the sum of the partial h's (null: not wanted)
-hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1, const void* w2,
+// tokens [begin, M), M up to SVDQ_MAX_M.  w1: the scales of canonical weights (packed ones hold theirs).  hsum: receives the sum of the partial h's (null: not wanted)
+hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1,
                              const float* h, int slices, float* hsum, const void* L2, const float* bias, int64_t M, int64_t begin, int N, int K, int r,
                              void* y, int64_t ldy, hipStream_t stream);
 // The whole layer in one launch (fused_layer_kernel), or FUSED_NONE: a quantise pass and a GEMM.  Every block quantises its own
@@ -114,7 +114,7 @@ inline int small_fused(int64_t M, int N, int K, int r, bool mxfp4) {
     return b32 <= 512 && K <= (r ? (mxfp4 ? 1664 : 1216) : (mxfp4 ? 2048 : 1664)) ? FUSED_TILES : FUSED_NONE;
 }
 hipError_t launch_fused_layer(int source, const void* x, int64_t ldx, const float* inv_lambda, float rho, bool gelu, const void* l1p,
-                              uint8_t* codes, void* scales, float* h, const void* w0, const void* w1, const void* w2,
+                              uint8_t* codes, void* scales, float* h, const void* w0, const void* w1,
                               const void* L2, const float* bias, int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream);
 hipError_t launch_sum_slices(const float* part, int slices, int64_t M, int r, float* h, hipStream_t stream);
 

@@ -43,18 +43,22 @@ namespace {
 // K / 64 groups in turn, about 1.7 us each (the latency of the x loads), so with few row blocks the walk is what is waited
 // for (M = 512, K = 5120: 8 blocks, 34 us): 1 x 8 then spreads rows and groups over more CUs and
 // waves (sixteen waves gain nothing: what a CU can deliver bounds it then).
+// The arguments are 112 bytes: with more a launch takes the host 0.4 us longer, and with the grid's size among them (256 bytes that
+// the compiler asks for) 0.6, and few tokens wait for the host.  w_codes .. w_out, w_N, canonical: the ExpandJob.
 template <bool LOWRANK, bool E3M2, bool GELU, int RB, int WV, bool BOTH>
 __global__ __launch_bounds__(64 * WV, WV == 4 ? 2 : 1)
-void quantize_kernel(const uint16_t* __restrict__ x, int64_t ldx,
-                     const float* __restrict__ inv_lambda, float rho,
-                     const uint4* __restrict__ l1p, int64_t M, int K, int r, int slice,
+void quantize_kernel(const uint16_t* __restrict__ x, const float* __restrict__ inv_lambda, const uint4* __restrict__ l1p,
                      uint8_t* __restrict__ qx, uint8_t* __restrict__ nib, float* __restrict__ sx, float* __restrict__ h,
-                     int row_blocks, const ExpandJob expand) {
+                     const void* w_codes, const void* w_scales, uint8_t* w_out, int64_t ldx, uint32_t M_, uint32_t row_blocks, float rho, int w_N,
+                     uint16_t K_, uint16_t slice_, uint16_t slices, uint8_t r_, uint8_t canonical) {
     static_assert(E3M2 || !BOTH, "nibbles are what the pass writes without E3M2");
+    const int64_t M = M_;
+    const int K = K_, r = r_, slice = slice_;
     if constexpr (E3M2) {
-        if ((int)blockIdx.x >= row_blocks) {
-            const int id = ((int)blockIdx.x - row_blocks) * (int)gridDim.y + (int)blockIdx.y;
-            expand_weights(expand, id * WV + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63, K);
+        if (blockIdx.x >= row_blocks) {
+            const int id = (int)(blockIdx.x - row_blocks) * slices + (int)blockIdx.y;
+            expand_weights(ExpandJob{w_codes, w_scales, w_out, w_N, canonical != 0}, id * WV + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+                           threadIdx.x & 63, K);
             return;
         }
     }
@@ -264,12 +268,10 @@ static hipError_t launch_quantize_geom(const void* x, int64_t ldx, const float* 
     const dim3 blocks(row_blocks + (expand_blocks + ny - 1) / ny, ny);
     const size_t hpart = l1p ? (size_t)WV * 32 * RB * 32 * sizeof(float) : 0;
     const size_t il = (size_t)slice * 64 * sizeof(float), lds = (il > hpart) ? il : hpart;
-    if (l1p)
-        hipLaunchKernelGGL((quantize_kernel<true, E3M2, GELU, RB, WV, BOTH>), blocks, dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)l1p, M, K, r, slice, qx, nib, sx, h, (int)row_blocks, expand);
-    else
-        hipLaunchKernelGGL((quantize_kernel<false, E3M2, GELU, RB, WV, BOTH>), blocks, dim3(64 * WV), lds, stream,
-                           (const uint16_t*)x, ldx, inv_lambda, rho, (const uint4*)nullptr, M, K, r, slice, qx, nib, sx, h, (int)row_blocks, expand);
+    auto kern = l1p ? quantize_kernel<true, E3M2, GELU, RB, WV, BOTH> : quantize_kernel<false, E3M2, GELU, RB, WV, BOTH>;
+    hipLaunchKernelGGL(kern, blocks, dim3(64 * WV), lds, stream, (const uint16_t*)x, inv_lambda, (const uint4*)l1p, qx, nib, sx, h,
+                       expand.codes, expand.scales, expand.out, ldx, (uint32_t)M, row_blocks, rho, expand.N,
+                       (uint16_t)K, (uint16_t)slice, (uint16_t)ny, (uint8_t)r, (uint8_t)expand.canonical);
     return hipGetLastError();
 }
 

@@ -31,20 +31,23 @@ typedef int int8v __attribute__((ext_vector_type(8)));
 
 constexpr int WV = SMALL_SLICES;
 
+// A launch with more than 112 bytes of arguments takes the host 0.4 us longer (3.2 against 2.8), with the grid's size among them
+// (256 bytes more that the compiler asks for) 0.6: few tokens wait for the host, so both kernels' arguments are packed below that.
 struct SmallArgs {
     const uint8_t* codes;
     const void* scales;
-    const uint8_t *w0, *w1, *w2;
+    const uint8_t *w0, *w1;      // w1: the scales of canonical weights; packed ones hold theirs behind the codes
     const float* h;              // hs partial h's, [M, r] each
-    int hs;
     float* hsum;                 // out: h, the sum of the partial ones in slice order (null: not wanted)
     const uint16_t* L2;
     const float* bias;
-    int64_t M, begin;            // tokens [begin, M)
-    int N, K, r;
     uint16_t* y;
     int64_t ldy;
+    uint32_t M, begin;           // tokens [begin, M)
+    int N, K;
+    uint8_t hs, r;
 };
+static_assert(sizeof(SmallArgs) <= 112, "arguments of a cheap launch");
 
 // Loads are buffer loads: a descriptor and a wave-uniform offset in scalar registers plus a per-lane 32-bit offset that is
 // fixed for the kernel.  (With 64-bit addresses per lane, two registers for every load in flight, the compiler spills.)
@@ -61,6 +64,13 @@ __device__ __forceinline__ T at(__amdgpu_buffer_rsrc_t b, const uint32_t uniform
     else if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b, lane_off, uniform, 0));
     else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, lane_off, uniform, 0));
     else return __builtin_amdgcn_raw_buffer_load_b16(b, lane_off, uniform, 0);
+}
+// the planes of packed weights behind the codes (svdq_kernels.h)
+template <int SRC>
+__device__ __forceinline__ Buffers buffers_of(const void* codes, const void* scales, const uint8_t* w0, const uint8_t* w1, const int N, const int K) {
+    const uint8_t* p1 = SRC == SMALL_E3M2_CANONICAL ? w1 : w0 + (SRC == SMALL_E3M2_PACKED ? packed_e3m2_w0_bytes(N, K) : (size_t)N * (K / 2));
+    const uint8_t* p2 = SRC == SMALL_E3M2_PACKED ? p1 + packed_e3m2_w1_bytes(N, K) : nullptr;
+    return Buffers{buffer(codes), buffer(scales), buffer(w0), buffer(p1), buffer(p2)};
 }
 template <int MT>
 struct LaneOffsets {
@@ -234,18 +244,18 @@ void small_gemm_kernel(const SmallArgs a) {
     const int lane = threadIdx.x & 63, l32 = lane & 31, kh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = (int)blockIdx.x * 32 * NI;
-    const int64_t m0 = a.begin + (int64_t)blockIdx.y * 32 * MT;
-    if (m0 >= a.M) {                                      // the blocks behind the token tiles
-        for (int b = (int)blockIdx.x; b < (a.M * a.r + 4 * 64 * WV - 1) / (4 * 64 * WV); b += (int)gridDim.x)
-            sum_slices(a.h, a.hs, a.M * a.r, a.hsum, (int64_t)b * (64 * WV) + threadIdx.x);
+    const int64_t M = a.M, m0 = a.begin + (int64_t)blockIdx.y * 32 * MT;
+    if (m0 >= M) {                                        // the blocks behind the token tiles
+        for (int b = (int)blockIdx.x; b < (M * a.r + 4 * 64 * WV - 1) / (4 * 64 * WV); b += a.N / (32 * NI))
+            sum_slices(a.h, a.hs, M * a.r, a.hsum, (int64_t)b * (64 * WV) + threadIdx.x);
         return;
     }
-    const Buffers B{buffer(a.codes), buffer(a.scales), buffer(a.w0), buffer(a.w1), buffer(a.w2)};
+    const Buffers B = buffers_of<SRC>(a.codes, a.scales, a.w0, a.w1, a.N, a.K);
     LaneOffsets<MT> off{{}, (uint32_t)kh, (uint32_t)l32, (uint32_t)lane, (uint32_t)(n0 + l32)};
 #pragma unroll
     for (int mi = 0; mi < MT; ++mi) {
         const int64_t m = m0 + 32 * mi + l32;
-        off.row[mi] = (uint32_t)(m < a.M ? m : a.M - 1);  // rows beyond M: results never stored
+        off.row[mi] = (uint32_t)(m < M ? m : M - 1);  // rows beyond M: results never stored
     }
     float16v y[NI][MT];
 #pragma unroll
@@ -294,7 +304,7 @@ void small_gemm_kernel(const SmallArgs a) {
         }
 
     if (wave == 0 || (a.r > 0 && wave < a.hs))
-        add_lowrank_bias<NI, MT>(y, a.h + (size_t)wave * a.M * a.r, a.L2, wave == 0 ? a.bias : nullptr, m0, n0, a.M, a.N, a.r, lane);
+        add_lowrank_bias<NI, MT>(y, a.h + (size_t)wave * M * a.r, a.L2, wave == 0 ? a.bias : nullptr, m0, n0, M, a.N, a.r, lane);
 
     // sum of the eight partial tiles: waves 4..7 hand theirs to waves 0..3, then every wave finishes Q / 8 quads of four
     auto quad = [&](const int q) {
@@ -321,14 +331,14 @@ void small_gemm_kernel(const SmallArgs a) {
         const int t = q >> 2;
         const int64_t m = m0 + 32 * (t % MT) + l32;
         const int n = n0 + 32 * (t / MT) + 8 * (q & 3) + 4 * kh;
-        if (m < a.M) *reinterpret_cast<uint2*>(a.y + m * a.ldy + n) = uint2{f2_bf16_rne(v[0], v[1]), f2_bf16_rne(v[2], v[3])};
+        if (m < M) *reinterpret_cast<uint2*>(a.y + m * a.ldy + n) = uint2{f2_bf16_rne(v[0], v[1]), f2_bf16_rne(v[2], v[3])};
     }
 }
 
 template <int SRC>
 hipError_t launch_src(const SmallArgs& a, hipStream_t stream) {
     auto go = [&](auto kern, int ni, int mt) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)(a.N / (32 * ni)), (unsigned)((a.M - a.begin + 32 * mt - 1) / (32 * mt)) + (a.hsum ? 1u : 0u)), dim3(64 * WV), 0, stream, a);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(a.N / (32 * ni)), (a.M - a.begin + 32 * mt - 1) / (32 * mt) + (a.hsum ? 1u : 0u)), dim3(64 * WV), 0, stream, a);
     };
     if (small_shape(a.M - a.begin, a.N, a.K, SRC == SMALL_MXFP4) == 1) go(small_gemm_kernel<SRC, 1, 1>, 1, 1);
     else if constexpr (SRC == SMALL_MXFP4) go(small_gemm_kernel<SRC, 1, 2>, 1, 2);
@@ -351,22 +361,22 @@ hipError_t launch_src(const SmallArgs& a, hipStream_t stream) {
 // and the codes go through LDS.
 struct FusedArgs {
     const uint16_t* x;
-    int64_t ldx;
     const float* inv_lambda;
-    float rho;
-    int gelu, rs;
     const uint4* l1p;
     uint8_t* codes;              // out, as the format's quantise pass writes them
-    void* scales;
+    void* scales;                // out; E3M2 fields have none: the scales of canonical weights
     float* h;
-    const uint8_t *w0, *w1, *w2;
+    const uint8_t* w0;
     const uint16_t* L2;
     const float* bias;
-    int64_t M;
-    int N, K, r;
     uint16_t* y;
-    int64_t ldy;
+    int64_t ldx, ldy;
+    uint32_t M;
+    float rho;
+    uint16_t K, nblocks;         // nblocks: N / 32
+    uint8_t r, rs, gelu;
 };
+static_assert(sizeof(FusedArgs) <= 112, "arguments of a cheap launch");
 // wait for this wave's LDS traffic, then for the other waves: loads from global memory stay in flight
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 constexpr int IL_ROW = 36;                                 // floats between the smoothing factors of two halves of groups in LDS
@@ -388,26 +398,28 @@ void fused_layer_kernel(const FusedArgs a) {
     float* const hpart = reinterpret_cast<float*>(smem + WV * Q * 1024);             // [WV][32][32]
     float* const hsum = hpart + WV * 32 * 32;                                        // [32][H_ROW]
     float* const il_s = a.r ? hsum + 32 * H_ROW : hpart;
+    const int N = a.nblocks * 32, K = a.K;
+    const int64_t M = a.M;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, kh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n0 = (int)blockIdx.x * 32 * NI, ng = a.K >> 6;
+    const int n0 = (int)blockIdx.x * 32 * NI, ng = K >> 6;
     const int rs = SPREAD ? a.rs : 5, rmask = (1 << rs) - 1, trow = l32 & rmask;     // this lane's token of the tile
     const int64_t m0 = (int64_t)blockIdx.y << rs, row = m0 + trow;
-    uint8_t* const clo = reinterpret_cast<uint8_t*>(il_s + (a.K >> 5) * IL_ROW);     // SPREAD: [2 g + kh][token] x 16, x 8, x 4 bytes
-    uint8_t* const chi = clo + (((a.K >> 5) * 16) << rs);
-    uint8_t* const csc = chi + (((a.K >> 5) * 8) << rs);
+    uint8_t* const clo = reinterpret_cast<uint8_t*>(il_s + (K >> 5) * IL_ROW);     // SPREAD: [2 g + kh][token] x 16, x 8, x 4 bytes
+    uint8_t* const chi = clo + (((K >> 5) * 16) << rs);
+    uint8_t* const csc = chi + (((K >> 5) * 8) << rs);
     // its piece s at place s ^ (token / 4) % 4: the 16 tokens of a read stand in different banks
-    uint8_t* const cxv = csc + (((a.K >> 5) * 4) << rs);
+    uint8_t* const cxv = csc + (((K >> 5) * 4) << rs);
     auto x_place = [&](const int g, const int s) { return reinterpret_cast<uint4*>(cxv + (((2 * g + kh) << rs) + trow) * 64) + (s ^ ((trow >> 2) & 3)); };
     const bool first = blockIdx.x == 0;
-    const Buffers B{buffer(nullptr), buffer(nullptr), buffer(a.w0), buffer(a.w1), buffer(a.w2)};
-    const uint16_t* const xrow = a.x + (row < a.M ? row : a.M - 1) * a.ldx + kh * 32;
+    const Buffers B = buffers_of<SRC>(nullptr, nullptr, a.w0, (const uint8_t*)a.scales, N, K);
+    const uint16_t* const xrow = a.x + (row < M ? row : M - 1) * a.ldx + kh * 32;
     auto load_x = [&](uint4 (&x)[4], const int g) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) x[s] = reinterpret_cast<const uint4*>(xrow + g * 64)[s];
     };
 
-    for (int i = tid * 4; i < a.K; i += 256 * WV) *reinterpret_cast<float4*>(il_s + (i >> 5) * IL_ROW + (i & 31)) = *reinterpret_cast<const float4*>(a.inv_lambda + i);
+    for (int i = tid * 4; i < K; i += 256 * WV) *reinterpret_cast<float4*>(il_s + (i >> 5) * IL_ROW + (i & 31)) = *reinterpret_cast<const float4*>(a.inv_lambda + i);
     // quantise this lane's 32 values of group g into fields (MXFP4: nibbles) and scale, and into the layer's buffers
     struct Coded {
         LaneCodes<true> c;
@@ -419,8 +431,8 @@ void fused_layer_kernel(const FusedArgs a) {
         if constexpr (MX) {
             quantize_block_mx(x, il, a.rho, o.c.lo, o.s);
             if (writes) {
-                *reinterpret_cast<uint4*>(a.codes + ((size_t)g * a.M + row) * 32 + kh * 16) = o.c.lo;
-                uint8_t* se = (uint8_t*)a.scales + (((size_t)(g >> 1) * a.M + row) * 2 + kh) * 2;
+                *reinterpret_cast<uint4*>(a.codes + ((size_t)g * M + row) * 32 + kh * 16) = o.c.lo;
+                uint8_t* se = (uint8_t*)a.scales + (((size_t)(g >> 1) * M + row) * 2 + kh) * 2;
                 se[g & 1] = (uint8_t)o.s;
                 if (g == ng - 1 && (ng & 1)) se[1] = 0;                  // a group past K counts as empty
             }
@@ -431,10 +443,10 @@ void fused_layer_kernel(const FusedArgs a) {
             o.s = split_bf16(s);
             if (writes) {
                 if constexpr (SRC == SMALL_NIBBLE) {
-                    *reinterpret_cast<uint4*>(a.codes + ((size_t)g * a.M + row) * 32 + kh * 16) = nib;
-                    if (kh == 0) ((float*)a.scales)[(size_t)g * a.M + row] = s;
+                    *reinterpret_cast<uint4*>(a.codes + ((size_t)g * M + row) * 32 + kh * 16) = nib;
+                    if (kh == 0) ((float*)a.scales)[(size_t)g * M + row] = s;
                 } else {
-                    const size_t Mp = (size_t)((a.M + 3) & ~(int64_t)3);
+                    const size_t Mp = (size_t)((M + 3) & ~(int64_t)3);
                     uint8_t* blk = a.codes + (size_t)g * Mp * E3M2_ROW_BYTES;
                     *reinterpret_cast<uint4*>(blk + (size_t)row * 32 + kh * 16) = o.c.lo;
                     *reinterpret_cast<uint2*>(blk + Mp * 32 + ((size_t)kh * Mp + row) * 8) = o.c.hi;
@@ -459,8 +471,8 @@ void fused_layer_kernel(const FusedArgs a) {
         for (int ni = 0; ni < NI; ++ni) {
             const uint32_t fr = (uint32_t)((n0 >> 5) + ni) * ng + g;
             if constexpr (SRC == SMALL_E3M2_CANONICAL) {
-                o.w[ni] = at<uint4>(B.w0, (uint32_t)g * 32 + (uint32_t)ni * 16 * a.K, (uint32_t)(n0 + l32) * (uint32_t)(a.K >> 1) + kh * 16);
-                o.sw[ni] = at<uint32_t>(B.w1, ((uint32_t)g * a.N + ni * 32) * 4, (uint32_t)(n0 + l32) * 4);
+                o.w[ni] = at<uint4>(B.w0, (uint32_t)g * 32 + (uint32_t)ni * 16 * K, (uint32_t)(n0 + l32) * (uint32_t)(K >> 1) + kh * 16);
+                o.sw[ni] = at<uint32_t>(B.w1, ((uint32_t)g * N + ni * 32) * 4, (uint32_t)(n0 + l32) * 4);
             } else {
                 o.w[ni] = at<uint4>(B.w0, fr * 1024, lane * 16);
                 if constexpr (SRC == SMALL_E3M2_PACKED) {
@@ -497,8 +509,8 @@ void fused_layer_kernel(const FusedArgs a) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (16 * ks < a.r) {
-                        const uint16_t* p = a.L2 + (int64_t)(16 * ks + 8 * kh + 2 * e) * a.N + n0 + 32 * fni + l32;
-                        l2w[ks][e] = (uint32_t)p[0] | ((uint32_t)p[a.N] << 16);
+                        const uint16_t* p = a.L2 + (int64_t)(16 * ks + 8 * kh + 2 * e) * N + n0 + 32 * fni + l32;
+                        l2w[ks][e] = (uint32_t)p[0] | ((uint32_t)p[N] << 16);
                     }
         }
         if (a.bias) bv = *reinterpret_cast<const float4*>(a.bias + n0 + 32 * fni + 8 * fq + 4 * kh);
@@ -513,7 +525,7 @@ void fused_layer_kernel(const FusedArgs a) {
     if constexpr (SPREAD) {
         for (int g = tg; g < ng; g += WV * per_wave) {
             if (a.gelu) gelu_tanh_rows(xt);
-            const Coded o = quantise(xt, g, first && row < a.M);
+            const Coded o = quantise(xt, g, first && row < M);
             const int at = ((2 * g + kh) << rs) + trow;
             *reinterpret_cast<uint4*>(clo + at * 16) = o.c.lo;
             if (!MX) *reinterpret_cast<uint2*>(chi + at * 8) = o.c.hi;
@@ -545,7 +557,7 @@ void fused_layer_kernel(const FusedArgs a) {
             if (!MX) o.c.hi = *reinterpret_cast<const uint2*>(chi + at * 8);
             o.s = *reinterpret_cast<const uint32_t*>(csc + at * 4);
         } else {
-            o = quantise(cur.x, g, first && row < a.M);
+            o = quantise(cur.x, g, first && row < M);
         }
         if constexpr (MX) {
             const int8v bvx = {(int)o.c.lo.x, (int)o.c.lo.y, (int)o.c.lo.z, (int)o.c.lo.w, 0, 0, 0, 0};
@@ -583,7 +595,7 @@ void fused_layer_kernel(const FusedArgs a) {
         };
         const float2 s0 = sum4(0), s1 = sum4(4), t{s0.x + s1.x, s0.y + s1.y};
         *reinterpret_cast<float2*>(hsum + hr * H_ROW + hj) = t;
-        if (first && hr <= rmask && hj < a.r && m0 + hr < a.M) *reinterpret_cast<float2*>(a.h + (m0 + hr) * a.r + hj) = t;
+        if (first && hr <= rmask && hj < a.r && m0 + hr < M) *reinterpret_cast<float2*>(a.h + (m0 + hr) * a.r + hj) = t;
         lds_barrier();
     }
     if (!finishes) return;
@@ -612,22 +624,22 @@ void fused_layer_kernel(const FusedArgs a) {
     auto low = [&](const int j) { return fq == 0 ? lr[j] : fq == 1 ? lr[4 + j] : fq == 2 ? lr[8 + j] : lr[12 + j]; };
     const float v0 = sum([](const float4& f) { return f.x; }, low(0), bv.x), v1 = sum([](const float4& f) { return f.y; }, low(1), bv.y);
     const float v2 = sum([](const float4& f) { return f.z; }, low(2), bv.z), v3 = sum([](const float4& f) { return f.w; }, low(3), bv.w);
-    if (l32 <= rmask && row < a.M)
+    if (l32 <= rmask && row < M)
         *reinterpret_cast<uint2*>(a.y + row * a.ldy + n0 + 32 * fni + 8 * fq + 4 * kh) = uint2{f2_bf16_rne(v0, v1), f2_bf16_rne(v2, v3)};
 }
 
 template <int SRC>
 hipError_t launch_fused_src(FusedArgs a, hipStream_t stream) {
-    auto go = [&](auto kern, int ni, bool spread, int rs) {
-        a.rs = rs;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(a.N / (32 * ni)), (unsigned)((a.M + (1 << rs) - 1) >> rs)), dim3(64 * WV),
-                           fused_lds(ni, a.K, a.r, spread, rs), stream, a);
+    const unsigned M = a.M;
+    auto go = [&](auto kern, unsigned ni, bool spread, int rs) {
+        a.rs = (uint8_t)rs;
+        hipLaunchKernelGGL(kern, dim3(a.nblocks / ni, (M + (1u << rs) - 1) >> rs), dim3(64 * WV), fused_lds(ni, a.K, a.r, spread, rs), stream, a);
     };
-    if (small_fused(a.M, a.N, a.K, a.r, SRC == SMALL_MXFP4) == FUSED_SPREAD) {
+    if (small_fused(M, a.nblocks * 32, a.K, a.r, SRC == SMALL_MXFP4) == FUSED_SPREAD) {
         int rs = 0;
-        while (rs < 4 && (1 << rs) < a.M) ++rs;
+        while (rs < 4 && (1u << rs) < M) ++rs;
         go(fused_layer_kernel<SRC, 1, true>, 1, true, rs);
-    } else if ((a.M + 31) / 32 * (a.N / 32) <= 256) {
+    } else if ((M + 31) / 32 * a.nblocks <= 256) {
         go(fused_layer_kernel<SRC, 1, false>, 1, false, 5);
     } else {
         go(fused_layer_kernel<SRC, 2, false>, 2, false, 5);
@@ -648,11 +660,11 @@ hipError_t launch_sum_slices(const float* part, int slices, int64_t M, int r, fl
     return hipGetLastError();
 }
 
-hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1, const void* w2,
+hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scales, const void* w0, const void* w1,
                              const float* h, int slices, float* hsum, const void* L2, const float* bias, int64_t M, int64_t begin, int N, int K, int r,
                              void* y, int64_t ldy, hipStream_t stream) {
-    const SmallArgs a{codes, scales, (const uint8_t*)w0, (const uint8_t*)w1, (const uint8_t*)w2, h, slices, hsum,
-                      (const uint16_t*)L2, bias, M, begin, N, K, r, (uint16_t*)y, ldy};
+    const SmallArgs a{codes, scales, (const uint8_t*)w0, (const uint8_t*)w1, h, hsum, (const uint16_t*)L2, bias, (uint16_t*)y, ldy,
+                      (uint32_t)M, (uint32_t)begin, N, K, (uint8_t)slices, (uint8_t)r};
     switch (source) {
         case SMALL_E3M2_CANONICAL: return launch_src<SMALL_E3M2_CANONICAL>(a, stream);
         case SMALL_E3M2_PACKED: return launch_src<SMALL_E3M2_PACKED>(a, stream);
@@ -662,10 +674,11 @@ hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scale
 }
 
 hipError_t launch_fused_layer(int source, const void* x, int64_t ldx, const float* inv_lambda, float rho, bool gelu, const void* l1p,
-                              uint8_t* codes, void* scales, float* h, const void* w0, const void* w1, const void* w2,
+                              uint8_t* codes, void* scales, float* h, const void* w0, const void* w1,
                               const void* L2, const float* bias, int64_t M, int N, int K, int r, void* y, int64_t ldy, hipStream_t stream) {
-    const FusedArgs a{(const uint16_t*)x, ldx, inv_lambda, rho, gelu, 0, (const uint4*)l1p, codes, scales, h,
-                      (const uint8_t*)w0, (const uint8_t*)w1, (const uint8_t*)w2, (const uint16_t*)L2, bias, M, N, K, r, (uint16_t*)y, ldy};
+    const FusedArgs a{(const uint16_t*)x, inv_lambda, (const uint4*)l1p, codes, source == SMALL_E3M2_CANONICAL ? const_cast<void*>(w1) : scales, h,
+                      (const uint8_t*)w0, (const uint16_t*)L2, bias, (uint16_t*)y, ldx, ldy, (uint32_t)M, rho, (uint16_t)K, (uint16_t)(N / 32),
+                      (uint8_t)r, 0, (uint8_t)gelu};
     switch (source) {
         case SMALL_E3M2_CANONICAL: return launch_fused_src<SMALL_E3M2_CANONICAL>(a, stream);
         case SMALL_E3M2_PACKED: return launch_fused_src<SMALL_E3M2_PACKED>(a, stream);
