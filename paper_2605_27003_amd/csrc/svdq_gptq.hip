@@ -17,6 +17,7 @@
 
 #include "svdq_dev.h"
 #include "svdq_kernels.h"
+#include "svdq_lds.h"
 
 namespace svdq {
 
@@ -190,7 +191,7 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 //   rank update    everything else receives its updates from the saved columns and rows, in pivot order, on the
 //                  binary64 matrix instruction.  Block 0 meanwhile brings the NEXT panel's diagonal block up to date, takes
 //                  it through its own 64 dependent steps and leaves the next panel's tables: a serial chain of about
-//                  44 us, which no launch is shorter than.
+//                  35 us, which no launch is shorter than.
 // Only the strips (rows and columns) of the next panel have to be up to date when a launch ends.  The rest of the matrices
 // receives the updates of a whole batch of BATCH = 4 panels in one pass over memory, and its blocks are dealt over the four
 // launches of the next batch in whole rounds of one block per CU, beside the strips and the chain.  So at any time the
@@ -203,7 +204,7 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 // 78 us each of the inverse's 80 launches, 44 to 162 the visit's.  (K = N = 512: 1.07 -> 1.05, 2048: 4.65 -> 4.20, 4096:
 // 11.85 -> 10.78.)  What bounds it: the matrix unit, 246e9 fused
 // multiply-subtracts (8.2 ms at the 60 TFLOP/s that a loop of these instructions reaches), and the serial path of a panel:
-// its kernel (20 to 25 us) and the chain.
+// its kernel (9 us with a block per CU at most, 18 at K = 5120) and the chain (33 us).
 constexpr int PB = 64;
 constexpr int BATCH = 4;                         // panels whose updates of the rest are put off and done together
 constexpr int RING_PANELS = 2 * BATCH;           // whose saved rows and columns are kept; a power of two
@@ -223,20 +224,22 @@ __device__ __forceinline__ double row_turn(double v) { return dpp64<0x120 + 15>(
 
 // a / d, correctly rounded, from y = RN(1 / d): two corrections of a y.  The first makes the quotient faithful, and
 // from a faithful quotient and a correctly rounded reciprocal the second gives the rounded quotient (Markstein's
-// theorem), as long as nothing leaves the exponent range; `bad` collects whether anything may have, and the callers
+// theorem), as long as nothing leaves the exponent range; `far` collects whether anything may have (far_out), and the callers
 // then repeat the whole panel with SLOW, the division itself.  (A branch at every division would cost more than the
 // division: it ends the overlap of one vector's chain with the next one's.)  d and y: reciprocal_of below.
 template <bool SLOW>
-__device__ __forceinline__ double divide_by(double a, double d, double y, bool& bad) {
+__device__ __forceinline__ double divide_by(double a, double d, double y, uint32_t& far) {
     if (SLOW) return __ddiv_rn(a, d);
     double q = a * y;
     q = __builtin_fma(__builtin_fma(-d, q, a), y, q);
     q = __builtin_fma(__builtin_fma(-d, q, a), y, q);
-    const uint32_t ex = (uint32_t)(__builtin_bit_cast(uint64_t, q) >> 52) & 0x7ffu;     // 2^-600 .. 2^600, or 0 / d
-    bad |= (ex - 423u > 1200u) && !(q == 0.0 && a == 0.0);
+    // twice the quotient's upper word from that of 2^-600 on: up to that of 2^600 further, or 0 / d (the callers look at y)
+    const uint32_t above = ((uint32_t)(__builtin_bit_cast(uint64_t, q) >> 32) << 1) - (423u << 21), t = a == 0.0 ? 0u : above;
+    far = t > far ? t : far;
     return q;
 }
-// RN(1 / d), or NaN (which every quotient then is: bad) where d is too large or small for divide_by
+__device__ __forceinline__ bool far_out(uint32_t far) { return far >= (1201u << 21); }
+// RN(1 / d), or NaN where d is too large or small for divide_by
 __device__ __forceinline__ double reciprocal_of(double d) {
     const double y = __ddiv_rn(1.0, d);
     return (fabs(d) >= 0x1p-200 && fabs(d) <= 0x1p200) ? y : __builtin_nan("");
@@ -255,51 +258,77 @@ struct PanelTables {
 // The diagonal block through its 64 pivots, 256 threads: lane group g = tid / 16 holds rows 4 g .. 4 g + 3, so pivot
 // 4 it + k is row k of group it.  INV: in-place Gauss-Jordan inverse (see below); otherwise only the rows and columns
 // behind the pivot are updated (row q of D is then the row as it stood at pivot q).  Rt: PB x PB in LDS, ds: 2 in LDS.
+// A group takes its own rows through its own four pivots, which need nothing of the others; these take all four behind one barrier.
 template <bool INV, bool SLOW>
 __device__ __forceinline__ bool diagonal_pass(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], PanelTables* __restrict__ out) {
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
-    bool bad = false;
+    uint32_t far = 0;
     for (int it = 0; it < 16; ++it) {
         const int sl = (pos + it) & 15;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        // pivot q = 4 it + k, its scaled row r, on this group's rows; OWN: it is one of them
+        auto eliminate = [&](auto OWNC, const int k, const double (&c)[4], const double d, const double y, const double (&r)[4]) {
+            constexpr bool OWN = decltype(OWNC)::value;
             const int q = 4 * it + k;
-            double c[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) c[v] = row_first(x[v][k]);
-            if (grp == it) {                              // this group's row k is the pivot's
-                const double d = c[k], y = reciprocal_of(d);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) Rt[q][4 * sl + j] = divide_by<SLOW>(x[k][j], d, y, bad);
-                if (pos == 0) {
-                    ds[q][0] = d;
-                    ds[q][1] = y;
-                }
-            }
             if (pos == 0) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) out->C[q][4 * grp + v] = c[v];
             }
-            lds_barrier();
-            const double d = ds[q][0], y = ds[q][1];
-            double r[4];
+            if (INV) {
+                // the four rows' new elements of column q, one each in lanes 0 .. 3 (and again behind them)
+                double a = pos & 1 ? c[1] : c[0];
+                const double a23 = pos & 1 ? c[3] : c[2];
+                a = pos & 2 ? a23 : a;
+                const double e = divide_by<SLOW>(OWN && (pos & 3) == k ? 1.0 : -a, d, y, far);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) r[j] = Rt[q][4 * sl + j];
+                for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if (INV) {
-                    const bool isq = v == k && grp == it;
-                    const double e = divide_by<SLOW>(isq ? 1.0 : -c[v], d, y, bad);
+                    for (int j = 0; j < 4; ++j) x[v][j] = OWN && v == k ? r[j] : __builtin_fma(-c[v], r[j], x[v][j]);
+                const double e1 = dpp64<0x151>(e), e2 = dpp64<0x152>(e), e3 = dpp64<0x153>(e);       // row_newbcast
+                x[0][k] = pos == 0 ? e : x[0][k];
+                x[1][k] = pos == 0 ? e1 : x[1][k];
+                x[2][k] = pos == 0 ? e2 : x[2][k];
+                x[3][k] = pos == 0 ? e3 : x[3][k];
+            } else if (OWN || grp > it) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) x[v][j] = isq ? r[j] : __builtin_fma(-c[v], r[j], x[v][j]);
-                    x[v][k] = (pos == 0) ? e : x[v][k];
-                } else {
+                for (int v = OWN ? k + 1 : 0; v < 4; ++v)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const double u = __builtin_fma(-c[v], r[j], x[v][j]);
-                        x[v][j] = (4 * grp + v > q && 4 * sl + j > q) ? u : x[v][j];
+                        x[v][j] = (4 * sl + j > q) ? u : x[v][j];
                     }
+            }
+        };
+        if (grp == it) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                double c[4], r[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) c[v] = row_first(x[v][k]);
+                const double d = c[k], y = reciprocal_of(d);
+                far = y == y ? far : ~0u;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    r[j] = divide_by<SLOW>(x[k][j], d, y, far);
+                    Rt[4 * it + k][4 * sl + j] = r[j];
                 }
+                if (pos == 0) {
+                    ds[4 * it + k][0] = d;
+                    ds[4 * it + k][1] = y;
+                }
+                eliminate(std::true_type{}, k, c, d, y, r);
+            }
+        }
+        lds_barrier();
+        if (grp != it) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                double c[4], r[4];
+                const double d = ds[4 * it + k][0], y = ds[4 * it + k][1];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) r[j] = Rt[4 * it + k][4 * sl + j];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) c[v] = row_first(x[v][k]);
+                eliminate(std::false_type{}, k, c, d, y, r);
             }
         }
 #pragma unroll
@@ -307,7 +336,7 @@ __device__ __forceinline__ bool diagonal_pass(double (&x)[4][4], double (*Rt)[PB
 #pragma unroll
             for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
     }
-    return bad;
+    return far_out(far);
 }
 template <bool INV>
 __device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], int* redo, PanelTables* __restrict__ out) {
@@ -356,17 +385,68 @@ void first_tables_kernel(const double* __restrict__ D, size_t ld, PanelTables* _
     diagonal_block<INV>(x, Rt, ds, &redo, out);
 }
 
-// Vectors per block of the panel kernels: 16 lane groups of two vectors.  Two vectors per group halve the LDS reads of
-// the table (four values per lane and pivot), and 32 per block spread K = 5120 over every CU.
-constexpr int PV = 2, PVECS = 16 * PV;
+// Panel kernels: a vector for each of a block's 16 lane groups.  What bounds them is the chain of a vector's 64 pivots (a broadcast,
+// five operations of a division, an update) and the instructions beside it on a wave that has its SIMD for itself: the
+// table is read an iteration of four pivots ahead of its use and holds the NEGATED values, what is to be saved stays in
+// registers (lane `it` keeps iteration it's) and nothing branches.  Two vectors to a group halve the reads of the table, but take
+// longer than two blocks on a CU; K = N = 512, 2048, 5120 0.92, 3.74, 15.34 ms with two, 0.84, 3.46, 15.09 with one (three: 0.99, 4.04,
+// 15.8; two, read where they are used, masked and saved pivot by pivot: 1.04, 4.18, 16.05, a panel of 15 to 25 us).
+constexpr int PVECS = 16;
 __device__ __forceinline__ void load_table(double (*to)[PB], const double (*from)[PB]) {
-    for (int e = threadIdx.x * 2; e < PB * PB; e += 512)
-        *reinterpret_cast<double2*>(&to[0][0] + e) = *reinterpret_cast<const double2*>(&from[0][0] + e);
+    for (int e = threadIdx.x * 2; e < PB * PB; e += 512) {
+        const double2 v = *reinterpret_cast<const double2*>(&from[0][0] + e);
+        *reinterpret_cast<double2*>(&to[0][0] + e) = double2{-v.x, -v.y};
+    }
+}
+// (d, y) of the panel's pivots; whether any of them has no reciprocal that divide_by can use.  A barrier.
+__device__ __forceinline__ bool load_pivots(double (*ds)[2], const PanelTables* __restrict__ tb) {
+    int odd = 0;
+    if (threadIdx.x < PB) {
+        const double y = tb->y[threadIdx.x];
+        ds[threadIdx.x][0] = tb->d[threadIdx.x];
+        ds[threadIdx.x][1] = y;
+        odd = y != y;
+    }
+    return __syncthreads_or(odd) != 0;
+}
+struct TableRows {                               // four pivots' rows at a lane's four places, and (d, y)
+    double t[4][4], d[4], y[4];
+    __device__ __forceinline__ void load(const double (*tab)[PB], const double (*ds)[2], const int it, const int sl) {
+        auto pair = [](const double* p, double& a, double& b) {
+            const u32x4 v = *reinterpret_cast<const volatile __attribute__((address_space(3))) u32x4*>((const lds_byte*)p);
+            a = __builtin_bit_cast(double, (uint64_t)v.x | ((uint64_t)v.y << 32));
+            b = __builtin_bit_cast(double, (uint64_t)v.z | ((uint64_t)v.w << 32));
+        };
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            pair(ds[4 * it + k], d[k], y[k]);
+            pair(&tab[4 * it + k][4 * sl], t[k][0], t[k][1]);
+            pair(&tab[4 * it + k][4 * sl + 2], t[k][2], t[k][3]);
+        }
+    }
+};
+// body(it, rows) for the 16 iterations, the vector x turned behind each
+template <class Body>
+__device__ __forceinline__ void panel_iterations(const double (*tab)[PB], const double (*ds)[2], double (&x)[4], Body body) {
+    const int pos = threadIdx.x & 15;
+    TableRows rows[2];
+    rows[0].load(tab, ds, 0, pos);
+    auto one = [&](const int it, const TableRows& now, TableRows& next) {
+        next.load(tab, ds, (it + 1) & 15, (pos + it + 1) & 15);
+        body(it, now);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = row_turn(x[j]);
+    };
+#pragma unroll 1
+    for (int it = 0; it < 16; it += 2) {
+        one(it, rows[0], rows[1]);
+        one(it + 1, rows[1], rows[0]);
+    }
 }
 
 // ---- in-place Gauss-Jordan inverse without pivoting.  Step p: d = A[p][p], col = A[:, p], row = A[p, :] / d;
 // A[a][j] -= col[a] row[j] elsewhere, A[p][j] = row[j], A[a][p] = -col[a] / d, A[p][p] = 1 / d.
-// Blocks 0 .. nb - 1: PVECS rows outside the panel; nb .. 2 nb - 1: PVECS columns outside it.
+// Blocks 0 .. nb - 1: PVECS rows outside the panel; nb .. 2 nb - 1: columns outside it.
 // Saves LT[q][a] = column of pivot p0 + q, Rr[q][j] = its scaled row.
 __global__ __launch_bounds__(256)
 void gj_panel_kernel(double* __restrict__ A, int K, int p0, const PanelTables* __restrict__ tb,
@@ -375,86 +455,56 @@ void gj_panel_kernel(double* __restrict__ A, int K, int p0, const PanelTables* _
     const int nb = (K - PB) / PVECS;
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
     const bool rows = (int)blockIdx.x < nb;
-    double x[PV][4];
-    int idx[PV];
-#pragma unroll
-    for (int v = 0; v < PV; ++v) {
-        idx[v] = ((int)blockIdx.x - (rows ? 0 : nb)) * PVECS + (grp >> 2) * 4 * PV + v * 4 + (grp & 3);
-        if (idx[v] >= p0) idx[v] += PB;
-    }
+    double x[4];
+    int idx = ((int)blockIdx.x - (rows ? 0 : nb)) * PVECS + grp;
+    if (idx >= p0) idx += PB;
     auto load = [&]() {
 #pragma unroll
-        for (int v = 0; v < PV; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                x[v][j] = rows ? A[(size_t)idx[v] * K + p0 + 4 * pos + j] : A[(size_t)(p0 + 4 * pos + j) * K + idx[v]];
+        for (int j = 0; j < 4; ++j) x[j] = rows ? A[(size_t)idx * K + p0 + 4 * pos + j] : A[(size_t)(p0 + 4 * pos + j) * K + idx];
     };
     load();
     load_table(tab, rows ? tb->R : tb->C);
-    if (threadIdx.x < PB) {
-        ds[threadIdx.x][0] = tb->d[threadIdx.x];
-        ds[threadIdx.x][1] = tb->y[threadIdx.x];
-    }
-    __syncthreads();
-    double* const save = rows ? LT : Rr;
+    const bool slow = load_pivots(ds, tb);
+    double keep[4] = {};
     auto pass = [&](auto ROWS, auto SLOWC) {
         constexpr bool R = decltype(ROWS)::value;
-        bool bad = false;
-        for (int it = 0; it < 16; ++it) {
-            const int sl = (pos + it) & 15;
-            double f[4][PV];
+        uint32_t far = 0;
+        panel_iterations(tab, ds, x, [&](const int it, const TableRows& tr) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int q = 4 * it + k;
-                const double d = ds[q][0], y = ds[q][1];
-                double t[4];
+                const double c = row_first(x[k]);
+                const double e = divide_by<decltype(SLOWC)::value>(R ? -c : c, tr.d[k], tr.y[k], far), f = R ? c : e;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
-#pragma unroll
-                for (int v = 0; v < PV; ++v) {
-                    const double c = row_first(x[v][k]);
-                    const double e = divide_by<decltype(SLOWC)::value>(R ? -c : c, d, y, bad);
-                    f[k][v] = R ? c : e;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[v][j] = __builtin_fma(-f[k][v], t[j], x[v][j]);
-                    x[v][k] = (pos == 0) ? e : x[v][k];
-                }
+                for (int j = 0; j < 4; ++j) x[j] = __builtin_fma(f, tr.t[k][j], x[j]);
+                x[k] = (pos == 0) ? e : x[k];
+                keep[k] = (pos == it) ? f : keep[k];
             }
-            if (pos == 0) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int v = 0; v < PV; ++v) save[(size_t)(4 * it + k) * K + idx[v]] = f[k][v];
-            }
-#pragma unroll
-            for (int v = 0; v < PV; ++v)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
-        }
-        return bad;
+        });
+        return far_out(far);
     };
     auto run = [&](auto ROWS) {
-        if (__any(pass(ROWS, std::false_type{}))) {
+        if (__any(pass(ROWS, std::false_type{}) || slow)) {
             load();
             pass(ROWS, std::true_type{});
         }
     };
     if (rows) run(std::true_type{});
     else run(std::false_type{});
+    double* const save = rows ? LT : Rr;
 #pragma unroll
-    for (int v = 0; v < PV; ++v)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (rows) A[(size_t)idx[v] * K + p0 + 4 * pos + j] = x[v][j];
-            else A[(size_t)(p0 + 4 * pos + j) * K + idx[v]] = x[v][j];
-        }
+    for (int j = 0; j < 4; ++j) {
+        save[(size_t)(4 * pos + j) * K + idx] = keep[j];
+        if (rows) A[(size_t)idx * K + p0 + 4 * pos + j] = x[j];
+        else A[(size_t)(p0 + 4 * pos + j) * K + idx] = x[j];
+    }
 }
 
 // ---- one panel of the visit: indices i0 .. i0 + 63 = one 64-group.  For each index i: code and error of every
 // channel, the error spread over the panel's later weights, index i eliminated from H^-1 (A[a][b] -= A[a][i] (A[i][b] / d)
 // for a, b > i).  Blocks 0 .. nr - 1: PVECS rows of A behind the panel; nr .. 2 nr - 1: columns; the rest: channels
 // of W.  Saves, per pivot q, what the rank updates need: HcT[q][a] = A[a][i], HrT[q][b] = A[i][b],
-// T[q][b] = A[i][b] / d, Err[q][n].  The panel's own rows and columns of A and W are not read again.
+// T[q][b] = A[i][b] / d, Err[q][n].  The panel's own rows and columns of A and W are not read again, and what a pivot leaves in
+// places up to its own is of no use: a vector is updated as a whole.
 __global__ __launch_bounds__(256)
 void visit_panel_kernel(const double* __restrict__ A, const double* __restrict__ W, int N, int K, int i0,
                         const PanelTables* __restrict__ tb,
@@ -464,134 +514,100 @@ void visit_panel_kernel(const double* __restrict__ A, const double* __restrict__
     const int i1 = i0 + PB, nr = (K - i1) / PVECS;
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
     const int role = ((int)blockIdx.x < nr) ? 0 : ((int)blockIdx.x < 2 * nr) ? 1 : 2;      // rows, columns, channels
-    double x[PV][4];
-    int idx[PV];
-    bool live[PV];
-#pragma unroll
-    for (int v = 0; v < PV; ++v) {
-        idx[v] = (role < 2 ? i1 : 0) + ((int)blockIdx.x - role * nr) * PVECS + (grp >> 2) * 4 * PV + v * 4 + (grp & 3);
-        live[v] = role < 2 || idx[v] < N;
-    }
+    double x[4];
+    int idx = (role < 2 ? i1 : 0) + ((int)blockIdx.x - role * nr) * PVECS + grp;
+    const bool live = role < 2 || idx < N;
+    if (!live) idx = N - 1;                               // taken along, not stored
     auto load = [&]() {
 #pragma unroll
-        for (int v = 0; v < PV; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                x[v][j] = 0.0;
-                if (role == 0) x[v][j] = A[(size_t)idx[v] * K + i0 + 4 * pos + j];
-                if (role == 1) x[v][j] = A[(size_t)(i0 + 4 * pos + j) * K + idx[v]];
-                if (role == 2 && live[v]) x[v][j] = W[(size_t)(i0 + 4 * pos + j) * N + idx[v]];
-            }
+        for (int j = 0; j < 4; ++j)
+            x[j] = role == 0 ? A[(size_t)idx * K + i0 + 4 * pos + j] : role == 1 ? A[(size_t)(i0 + 4 * pos + j) * K + idx]
+                                                                                 : W[(size_t)(i0 + 4 * pos + j) * N + idx];
     };
     load();
     load_table(tab, role == 0 ? tb->R : role == 1 ? tb->C : tb->D);
-    if (threadIdx.x < PB) {
-        ds[threadIdx.x][0] = tb->d[threadIdx.x];
-        ds[threadIdx.x][1] = tb->y[threadIdx.x];
-    }
-    __syncthreads();
+    const bool slow = load_pivots(ds, tb);
     if (role == 2) {
-        float s[PV];
+        double a = fmax(fmax(fabs(x[0]), fabs(x[1])), fmax(fabs(x[2]), fabs(x[3])));
 #pragma unroll
-        for (int v = 0; v < PV; ++v) {
-            double a = fmax(fmax(fabs(x[v][0]), fabs(x[v][1])), fmax(fabs(x[v][2]), fabs(x[v][3])));
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) a = fmax(a, __shfl_xor(a, o));
-            s[v] = __fdiv_rn((float)a, 7.0f);
-            if (pos == 0 && live[v]) sw[(size_t)(i0 >> 6) * N + idx[v]] = s[v];
-        }
+        for (int o = 1; o < 16; o <<= 1) a = fmax(a, __shfl_xor(a, o));
+        const float s = __fdiv_rn((float)a, 7.0f), ys = s > 0.0f ? __fdiv_rn(1.0f, s) : 0.0f;
+        const bool odd = s != 0.0f && !(s >= 0x1p-60f && s <= 0x1p60f);      // not for the quotients below
+        if (pos == 0 && live) sw[(size_t)(i0 >> 6) * N + idx] = s;
+        double keep[4] = {};
+        uint32_t codes = 0;
         auto pass = [&](auto SLOWC) {
-            bool bad = false;
-            for (int it = 0; it < 16; ++it) {
-                const int sl = (pos + it) & 15;
-                uint32_t codes[PV] = {};
-                double e[4][PV];
+            constexpr bool SLOW = decltype(SLOWC)::value;
+            uint32_t far = 0;
+            bool large = false;
+            panel_iterations(tab, ds, x, [&](const int it, const TableRows& tr) {
+                uint32_t cd = 0;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const int q = 4 * it + k;
-                    const double d = ds[q][0], y = ds[q][1];
-                    double t[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
-#pragma unroll
-                    for (int v = 0; v < PV; ++v) {
-                        const double w = row_first(x[v][k]);
-                        float c = fminf(fmaxf(rintf(__fdiv_rn((float)w, s[v])), -8.0f), 7.0f);
-                        c = (s[v] > 0.0f) ? c : 0.0f;
-                        codes[v] |= ((uint32_t)(int)c & 15u) << (4 * k);
-                        e[k][v] = divide_by<decltype(SLOWC)::value>(__builtin_fma(-(double)c, (double)s[v], w), d, y, bad);   // code x scale is exact
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const double u = __builtin_fma(-t[j], e[k][v], x[v][j]);
-                            x[v][j] = (4 * sl + j > q) ? u : x[v][j];
-                        }
+                    const double w = row_first(x[k]);
+                    const float wf = (float)w;
+                    float c;
+                    if (SLOW) {
+                        c = fminf(fmaxf(rintf(__fdiv_rn(wf, s)), -8.0f), 7.0f);
+                        c = (s > 0.0f) ? c : 0.0f;
+                    } else {
+                        // wf / s as in divide_by, in binary32 (a scale of 0 has ys = 0: code 0).  One below 2^-40, where the corrections may not
+                        // be exact, is rounded to 0 all the same; a large or not finite wf is left to SLOW.
+                        float q = wf * ys;
+                        q = __builtin_fmaf(__builtin_fmaf(-s, q, wf), ys, q);
+                        q = __builtin_fmaf(__builtin_fmaf(-s, q, wf), ys, q);
+                        large |= !(fabsf(wf) < 0x1p60f);
+                        c = fminf(fmaxf(rintf(q), -8.0f), 7.0f);
                     }
+                    cd |= ((uint32_t)(int)c & 15u) << (4 * k);
+                    const double e = divide_by<SLOW>(__builtin_fma(-(double)c, (double)s, w), tr.d[k], tr.y[k], far);   // code x scale is exact
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[j] = __builtin_fma(tr.t[k][j], e, x[j]);
+                    keep[k] = (pos == it) ? e : keep[k];
                 }
-#pragma unroll
-                for (int v = 0; v < PV; ++v) {
-                    if (pos == 0 && live[v]) {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) Err[(size_t)(4 * it + k) * N + idx[v]] = e[k][v];
-                        // four codes: two bytes, low nibble = even index
-                        *reinterpret_cast<uint16_t*>(qw + (size_t)idx[v] * (K >> 1) + (i0 >> 1) + 2 * it) = (uint16_t)codes[v];
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
-                }
-            }
-            return bad;
+                codes = (pos == it) ? cd : codes;
+            });
+            return far_out(far) || large;
         };
-        if (__any(pass(std::false_type{}))) {
+        if (__any(pass(std::false_type{}) || odd || slow)) {
             load();
             pass(std::true_type{});
         }
+        if (!live) return;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) Err[(size_t)(4 * pos + k) * N + idx] = keep[k];
+        // four codes: two bytes, low nibble = even index
+        *reinterpret_cast<uint16_t*>(qw + (size_t)idx * (K >> 1) + (i0 >> 1) + 2 * pos) = (uint16_t)codes;
         return;
     }
-    double* const save = role == 0 ? HcT : HrT;
+    double keep_c[4] = {}, keep_f[4] = {};
     auto pass = [&](auto COLS, auto SLOWC) {
         constexpr bool C = decltype(COLS)::value;
-        bool bad = false;
-        for (int it = 0; it < 16; ++it) {
-            const int sl = (pos + it) & 15;
-            double c[4][PV], f[4][PV];
+        uint32_t far = 0;
+        panel_iterations(tab, ds, x, [&](const int it, const TableRows& tr) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int q = 4 * it + k;
-                double t[4];
+                const double c = row_first(x[k]);
+                const double f = C ? divide_by<decltype(SLOWC)::value>(c, tr.d[k], tr.y[k], far) : c;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) t[j] = tab[q][4 * sl + j];
-#pragma unroll
-                for (int v = 0; v < PV; ++v) {
-                    c[k][v] = row_first(x[v][k]);
-                    f[k][v] = C ? divide_by<decltype(SLOWC)::value>(c[k][v], ds[q][0], ds[q][1], bad) : c[k][v];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const double u = __builtin_fma(-f[k][v], t[j], x[v][j]);
-                        x[v][j] = (4 * sl + j > q) ? u : x[v][j];
-                    }
-                }
+                for (int j = 0; j < 4; ++j) x[j] = __builtin_fma(f, tr.t[k][j], x[j]);
+                keep_c[k] = (pos == it) ? c : keep_c[k];
+                if (C) keep_f[k] = (pos == it) ? f : keep_f[k];
             }
-            if (pos == 0) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int v = 0; v < PV; ++v) {
-                        save[(size_t)(4 * it + k) * K + idx[v]] = c[k][v];
-                        if (C) T[(size_t)(4 * it + k) * K + idx[v]] = f[k][v];
-                    }
-            }
-#pragma unroll
-            for (int v = 0; v < PV; ++v)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
-        }
-        return bad;
+        });
+        return far_out(far);
     };
     if (role == 0) {
         pass(std::false_type{}, std::false_type{});
-    } else if (__any(pass(std::true_type{}, std::false_type{}))) {
+    } else if (__any(pass(std::true_type{}, std::false_type{}) || slow)) {
         load();
         pass(std::true_type{}, std::true_type{});
+    }
+    double* const save = role == 0 ? HcT : HrT;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        save[(size_t)(4 * pos + k) * K + idx] = keep_c[k];
+        if (role == 1) T[(size_t)(4 * pos + k) * K + idx] = keep_f[k];
     }
 }
 

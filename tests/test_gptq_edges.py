@@ -35,6 +35,24 @@ def test_gptq_bit_exact_at_the_edges(svdq, oracle, K, N, scale):
     assert np.array_equal(qw.cpu().numpy(), oq)
 
 
+@pytest.mark.parametrize("K,N", [(128, 37), (192, 80)])
+def test_gptq_scales_of_every_size(svdq, oracle, K, N):
+    """Channels beside each other whose weights are ordinary, all zero, on the halfway points of the grid, so small or so
+    large that the fast quotient by the scale does not take them, and zero in one group only: bit for bit the oracle's."""
+    g = np.random.default_rng(K)
+    z = np.round(8 * (g.standard_normal((2 * K, K)) + np.repeat(g.standard_normal((2 * K, K // 8)), 8, axis=1)))
+    R = (g.standard_normal((K, N)) * 0.02).astype(np.float32)
+    R *= np.array([1, 2.0 ** -40, 2.0 ** -58, 2.0 ** -66, 2.0 ** -120, 2.0 ** -141, 2.0 ** 54, 2.0 ** 70, 2.0 ** 120, 0, 1], np.float32)[np.arange(N) % 11]
+    R[:, 10::11] = np.float32(0.25) * g.integers(-14, 15, R[:, 10::11].shape)
+    R[0::64, 10::11] = 3.5
+    R[64:128, 1::3] = 0
+    qw, sw = svdq.gptq_quantize(dev(R), torch.from_numpy(z.T @ z).cuda())
+    torch.cuda.synchronize()
+    oq, os_ = oracle.gptq_quantize(R, z.T @ z)
+    assert np.array_equal(sw.cpu().numpy().view(np.uint32), os_.view(np.uint32))
+    assert np.array_equal(qw.cpu().numpy(), oq)
+
+
 @pytest.mark.parametrize("M,K,ld", [(1, 64, 64), (37, 192, 192), (130, 256, 257), (41, 2048, 2048), (19, 2048, 2051)])
 def test_hessian_edges(svdq, oracle, M, K, ld):
     """Against the oracle's binary64 product; sums of M terms in another order: M 2^-53 relative to the diagonal's size."""
