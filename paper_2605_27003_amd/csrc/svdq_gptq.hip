@@ -191,7 +191,7 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 //   rank update    everything else receives its updates from the saved columns and rows, in pivot order, on the
 //                  binary64 matrix instruction.  Block 0 meanwhile brings the NEXT panel's diagonal block up to date, takes
 //                  it through its own 64 dependent steps and leaves the next panel's tables: a serial chain of about
-//                  35 us, which no launch is shorter than.
+//                  30 us, which no launch is shorter than.
 // Only the strips (rows and columns) of the next panel have to be up to date when a launch ends.  The rest of the matrices
 // receives the updates of a whole batch of BATCH = 4 panels in one pass over memory, and its blocks are dealt over the four
 // launches of the next batch in whole rounds of one block per CU, beside the strips and the chain.  So at any time the
@@ -204,7 +204,7 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 // 78 us each of the inverse's 80 launches, 44 to 162 the visit's.  (K = N = 512: 1.07 -> 1.05, 2048: 4.65 -> 4.20, 4096:
 // 11.85 -> 10.78.)  What bounds it: the matrix unit, 246e9 fused
 // multiply-subtracts (8.2 ms at the 60 TFLOP/s that a loop of these instructions reaches), and the serial path of a panel:
-// its kernel (9 us with a block per CU at most, 18 at K = 5120) and the chain (33 us).
+// its kernel (9 us with a block per CU at most, 18 at K = 5120) and the chain (30 us).
 constexpr int PB = 64;
 constexpr int BATCH = 4;                         // panels whose updates of the rest are put off and done together
 constexpr int RING_PANELS = 2 * BATCH;           // whose saved rows and columns are kept; a power of two
@@ -255,114 +255,110 @@ struct PanelTables {
     double d[PB], y[PB];   // pivots and their reciprocals
 };
 
-// The diagonal block through its 64 pivots, 256 threads: lane group g = tid / 16 holds rows 4 g .. 4 g + 3, so pivot
-// 4 it + k is row k of group it.  INV: in-place Gauss-Jordan inverse (see below); otherwise only the rows and columns
-// behind the pivot are updated (row q of D is then the row as it stood at pivot q).  Rt: PB x PB in LDS, ds: 2 in LDS.
-// A group takes its own rows through its own four pivots, which need nothing of the others; these take all four behind one barrier.
+// The diagonal block through its 64 pivots, 512 threads: lane group g = tid / 16 holds rows 2 g and 2 g + 1, so pivots
+// 4 it + 2 p and 4 it + 2 p + 1 are the rows of group 2 it + p.  INV: in-place Gauss-Jordan inverse (see below); otherwise only the
+// rows and columns behind the pivot are updated (row q of D is then the row as it stood at pivot q).  Rt: PB x PB in LDS, ds: 2 in LDS.
+// A group takes its own rows through its own two pivots, which need nothing of the others; these take both behind one barrier.
+// What bounds it is the number of instructions of the wave that has the pivots: with four rows a group (256 threads) and
+// a barrier per pivot the block takes 37 us alone, with one per four pivots 34, and so 28.
 template <bool INV, bool SLOW>
-__device__ __forceinline__ bool diagonal_pass(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], PanelTables* __restrict__ out) {
+__device__ __forceinline__ bool diagonal_pass(double (&x)[2][4], double (*Rt)[PB], double (*ds)[2], PanelTables* __restrict__ out) {
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
     uint32_t far = 0;
+#pragma unroll 1
     for (int it = 0; it < 16; ++it) {
         const int sl = (pos + it) & 15;
-        // pivot q = 4 it + k, its scaled row r, on this group's rows; OWN: it is one of them
-        auto eliminate = [&](auto OWNC, const int k, const double (&c)[4], const double d, const double y, const double (&r)[4]) {
+        // pivot q = 4 it + k, its scaled row r, on this group's rows; OWN: it is the group's row k % 2
+        auto eliminate = [&](auto OWNC, const int k, const double c0, const double c1, const double d, const double y, const double (&r)[4]) {
             constexpr bool OWN = decltype(OWNC)::value;
             const int q = 4 * it + k;
-            if (pos == 0) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) out->C[q][4 * grp + v] = c[v];
-            }
+            if (pos == 0) *reinterpret_cast<double2*>(&out->C[q][2 * grp]) = double2{c0, c1};
             if (INV) {
-                // the four rows' new elements of column q, one each in lanes 0 .. 3 (and again behind them)
-                double a = pos & 1 ? c[1] : c[0];
-                const double a23 = pos & 1 ? c[3] : c[2];
-                a = pos & 2 ? a23 : a;
-                const double e = divide_by<SLOW>(OWN && (pos & 3) == k ? 1.0 : -a, d, y, far);
+                // the two rows' new elements of column q, in the even lanes and in the odd ones; the pivot's own is 1 / d
+                const double e = divide_by<SLOW>(OWN && (pos & 1) == (k & 1) ? 1.0 : -(pos & 1 ? c1 : c0), d, y, far);
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
+                for (int v = 0; v < 2; ++v)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) x[v][j] = OWN && v == k ? r[j] : __builtin_fma(-c[v], r[j], x[v][j]);
-                const double e1 = dpp64<0x151>(e), e2 = dpp64<0x152>(e), e3 = dpp64<0x153>(e);       // row_newbcast
+                    for (int j = 0; j < 4; ++j) x[v][j] = OWN && v == (k & 1) ? r[j] : __builtin_fma(v ? -c1 : -c0, r[j], x[v][j]);
+                const double e1 = dpp64<0x151>(e);                           // row_newbcast:1
                 x[0][k] = pos == 0 ? e : x[0][k];
                 x[1][k] = pos == 0 ? e1 : x[1][k];
-                x[2][k] = pos == 0 ? e2 : x[2][k];
-                x[3][k] = pos == 0 ? e3 : x[3][k];
-            } else if (OWN || grp > it) {
+            } else if (OWN || 2 * grp > q) {
 #pragma unroll
-                for (int v = OWN ? k + 1 : 0; v < 4; ++v)
+                for (int v = OWN ? (k & 1) + 1 : 0; v < 2; ++v)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const double u = __builtin_fma(-c[v], r[j], x[v][j]);
+                        const double u = __builtin_fma(v ? -c1 : -c0, r[j], x[v][j]);
                         x[v][j] = (4 * sl + j > q) ? u : x[v][j];
                     }
             }
         };
-        if (grp == it) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                double c[4], r[4];
+        for (int p = 0; p < 2; ++p) {
+            if (grp == 2 * it + p) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) c[v] = row_first(x[v][k]);
-                const double d = c[k], y = reciprocal_of(d);
-                far = y == y ? far : ~0u;
+                for (int k = 2 * p; k < 2 * p + 2; ++k) {
+                    double r[4];
+                    const double c0 = row_first(x[0][k]), c1 = row_first(x[1][k]);
+                    const double d = k & 1 ? c1 : c0, y = reciprocal_of(d);
+                    far = y == y ? far : ~0u;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    r[j] = divide_by<SLOW>(x[k][j], d, y, far);
-                    Rt[4 * it + k][4 * sl + j] = r[j];
+                    for (int j = 0; j < 4; ++j) {
+                        r[j] = divide_by<SLOW>(x[k & 1][j], d, y, far);
+                        Rt[4 * it + k][4 * sl + j] = r[j];
+                    }
+                    if (pos == 0) {
+                        ds[4 * it + k][0] = d;
+                        ds[4 * it + k][1] = y;
+                    }
+                    eliminate(std::true_type{}, k, c0, c1, d, y, r);
                 }
-                if (pos == 0) {
-                    ds[4 * it + k][0] = d;
-                    ds[4 * it + k][1] = y;
+            }
+            lds_barrier();
+            if (grp != 2 * it + p) {
+#pragma unroll
+                for (int k = 2 * p; k < 2 * p + 2; ++k) {
+                    double r[4];
+                    const double d = ds[4 * it + k][0], y = ds[4 * it + k][1];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) r[j] = Rt[4 * it + k][4 * sl + j];
+                    const double c0 = row_first(x[0][k]), c1 = row_first(x[1][k]);
+                    eliminate(std::false_type{}, k, c0, c1, d, y, r);
                 }
-                eliminate(std::true_type{}, k, c, d, y, r);
             }
         }
-        lds_barrier();
-        if (grp != it) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                double c[4], r[4];
-                const double d = ds[4 * it + k][0], y = ds[4 * it + k][1];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) r[j] = Rt[4 * it + k][4 * sl + j];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) c[v] = row_first(x[v][k]);
-                eliminate(std::false_type{}, k, c, d, y, r);
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < 2; ++v)
 #pragma unroll
             for (int j = 0; j < 4; ++j) x[v][j] = row_turn(x[v][j]);
     }
     return far_out(far);
 }
 template <bool INV>
-__device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[PB], double (*ds)[2], int* redo, PanelTables* __restrict__ out) {
+__device__ __forceinline__ void diagonal_block(double (&x)[2][4], double (*Rt)[PB], double (*ds)[2], int* redo, PanelTables* __restrict__ out) {
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int v = 0; v < 2; ++v)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) out->D[4 * grp + v][4 * pos + j] = x[v][j];       // kept for a second pass
+        for (int j = 0; j < 4; ++j) out->D[2 * grp + v][4 * pos + j] = x[v][j];       // kept for a second pass
     if (threadIdx.x == 0) *redo = 0;                                  // ahead of the pass's barriers
     if (diagonal_pass<INV, false>(x, Rt, ds, out)) *redo = 1;
     __syncthreads();
     if (*redo) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < 2; ++v)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[v][j] = out->D[4 * grp + v][4 * pos + j];
+            for (int j = 0; j < 4; ++j) x[v][j] = out->D[2 * grp + v][4 * pos + j];
         __syncthreads();
         diagonal_pass<INV, true>(x, Rt, ds, out);
         __syncthreads();
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int v = 0; v < 2; ++v)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            out->D[4 * grp + v][4 * pos + j] = x[v][j];
-            out->R[4 * grp + v][4 * pos + j] = Rt[4 * grp + v][4 * pos + j];
+            out->D[2 * grp + v][4 * pos + j] = x[v][j];
+            out->R[2 * grp + v][4 * pos + j] = Rt[2 * grp + v][4 * pos + j];
         }
     if (threadIdx.x < PB) {
         out->d[threadIdx.x] = ds[threadIdx.x][0];
@@ -372,16 +368,16 @@ __device__ __forceinline__ void diagonal_block(double (&x)[4][4], double (*Rt)[P
 
 // The panel's first tables: nothing precedes them that could carry them along.
 template <bool INV>
-__global__ __launch_bounds__(256)
+__global__ __launch_bounds__(512)
 void first_tables_kernel(const double* __restrict__ D, size_t ld, PanelTables* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
     __shared__ int redo;
     const int grp = threadIdx.x >> 4, pos = threadIdx.x & 15;
-    double x[4][4];
+    double x[2][4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int v = 0; v < 2; ++v)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[v][j] = D[(size_t)(4 * grp + v) * ld + 4 * pos + j];
+        for (int j = 0; j < 4; ++j) x[v][j] = D[(size_t)(2 * grp + v) * ld + 4 * pos + j];
     diagonal_block<INV>(x, Rt, ds, &redo, out);
 }
 
@@ -693,34 +689,36 @@ __device__ __forceinline__ void update_chain(const int from, const int to, doubl
 __device__ __forceinline__ void look_ahead(const Lookahead& la, double (*Rt)[PB], double (*ds)[2], int* redo) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, kq = lane >> 4;
     if (la.prev)
-        for (int e = tid; e < PB * PB; e += 256) la.A[(size_t)(la.p0 + e / PB) * la.K + la.p0 + e % PB] = la.prev->D[e / PB][e % PB];
+        for (int e = tid; e < PB * PB; e += 512) la.A[(size_t)(la.p0 + e / PB) * la.K + la.p0 + e % PB] = la.prev->D[e / PB][e % PB];
     if (la.mode == 0) return;
     const int grp = tid >> 4, pos = tid & 15;
-    double x[4][4];
+    double x[2][4];
     if (la.from < la.to) {
-        double4v acc[1][4];
-        const double* X = la.A + (size_t)(la.s0 + 16 * wave) * la.K + la.s0;
+        if (wave < 4) {                                     // 16 rows each
+            double4v acc[1][4];
+            const double* X = la.A + (size_t)(la.s0 + 16 * wave) * la.K + la.s0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[0][k][e] = X[(size_t)(4 * e + kq) * la.K + wave_col(j, k)];
-        const int col[2] = {2 * j, 32 + 2 * j}, d1[2] = {1, 1};
-        update_chain<1, true>(la.from, la.to, acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, col, d1);
+                for (int e = 0; e < 4; ++e) acc[0][k][e] = X[(size_t)(4 * e + kq) * la.K + wave_col(j, k)];
+            const int col[2] = {2 * j, 32 + 2 * j}, d1[2] = {1, 1};
+            update_chain<1, true>(la.from, la.to, acc, la.L + la.s0 + 16 * wave, (size_t)la.K, la.R + la.s0, (size_t)la.K, lane, col, d1);
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) Rt[16 * wave + 4 * e + kq][wave_col(j, k)] = acc[0][k][e];
+                for (int e = 0; e < 4; ++e) Rt[16 * wave + 4 * e + kq][wave_col(j, k)] = acc[0][k][e];
+        }
         __syncthreads();
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < 2; ++v)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[v][i] = Rt[4 * grp + v][4 * pos + i];
+            for (int i = 0; i < 4; ++i) x[v][i] = Rt[2 * grp + v][4 * pos + i];
         __syncthreads();
     } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < 2; ++v)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[v][i] = la.prev->D[4 * grp + v][4 * pos + i];
+            for (int i = 0; i < 4; ++i) x[v][i] = la.prev->D[2 * grp + v][4 * pos + i];
     }
     if (la.mode == 1) diagonal_block<true>(x, Rt, ds, redo, la.next);
     else diagonal_block<false>(x, Rt, ds, redo, la.next);
@@ -790,7 +788,7 @@ void rank_update_kernel(const RankUpdates us, const Lookahead la) {
     __shared__ __attribute__((aligned(16))) double Rt[PB][PB], ds[PB][2];
     __shared__ int redo;
     if (blockIdx.x == 0) {
-        if (threadIdx.x < 256) look_ahead(la, Rt, ds, &redo);
+        look_ahead(la, Rt, ds, &redo);
         return;
     }
     int t = (int)blockIdx.x - 1, which = 0;
@@ -926,7 +924,7 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     auto rest_shape = [&](int blocks, int launches, int length) { return 2 * blocks / launches + length / 128 + 20 <= cus ? 6 : 0; };
     int cur = 0;                                       // tabs[cur]: the current panel's
     int done_a = 0, done_w = 0;                        // blocks of the batch's updates that its launches have had
-    hipLaunchKernelGGL(first_tables_kernel<true>, dim3(1), dim3(256), 0, stream, A, ldk, tabs[cur]);
+    hipLaunchKernelGGL(first_tables_kernel<true>, dim3(1), dim3(512), 0, stream, A, ldk, tabs[cur]);
     for (int b = 0; b < np; ++b) {                     // the inverse, one panel of pivots at a time
         const int p0 = b * PB, t = b + 1, batch = b / BATCH * BATCH;
         const bool back = batch / BATCH & 1;
