@@ -193,7 +193,7 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 //                  it through its own 64 dependent steps and leaves the next panel's tables: a serial chain of about
 //                  30 us, which no launch is shorter than.
 // Only the strips (rows and columns) of the next panel have to be up to date when a launch ends.  The rest of the matrices
-// receives the updates of a whole batch of BATCH = 4 panels in one pass over memory, and its blocks are dealt over the four
+// receives the updates of a whole batch of two to four panels in one pass over memory, and its blocks are dealt over the
 // launches of the next batch in whole rounds of one block per CU, beside the strips and the chain.  So at any time the
 // rest lacks up to two batches, which is what the rings of saved rows and columns hold, and a strip is brought up from
 // where the rest stands.  The diagonal block after the next one is brought up a panel early by a block of its own, so that
@@ -202,12 +202,12 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 // 112 ms; updates of the rest behind every panel 19.56 ms, behind every second one (two passes of 155 us over the
 // inverse per 256 pivots, the others of 49 us waiting for the chain) 18.88, behind every fourth one, in rounds, 16.07:
 // 78 us each of the inverse's 80 launches, 44 to 162 the visit's.  (K = N = 512: 1.07 -> 1.05, 2048: 4.65 -> 4.20, 4096:
-// 11.85 -> 10.78.)  What bounds it: the matrix unit, 246e9 fused
+// 11.85 -> 10.78; with panels, chains and batches as they are now 0.72, 2.96, 9.08, and 14.94 for 5120.)  What bounds it: the matrix unit, 246e9 fused
 // multiply-subtracts (8.2 ms at the 60 TFLOP/s that a loop of these instructions reaches), and the serial path of a panel:
 // its kernel (9 us with a block per CU at most, 18 at K = 5120) and the chain (30 us).
 constexpr int PB = 64;
-constexpr int BATCH = 4;                         // panels whose updates of the rest are put off and done together
-constexpr int RING_PANELS = 2 * BATCH;           // whose saved rows and columns are kept; a power of two
+constexpr int MAX_BATCH = 4;                     // panels whose updates of the rest are put off and done together, at most
+constexpr int RING_PANELS = 2 * MAX_BATCH;       // whose saved rows and columns are kept; a power of two
 
 // ---- A vector of 64 elements (one row or column of the panel) lives in 16 lanes (a DPP row), four elements each.
 // Pivot 4 it + k is always element k of the row's lane 0: after every four pivots the vectors turn by one lane, so the
@@ -855,6 +855,29 @@ void launch_rank_updates(const RankUpdates& us, const Lookahead& la, hipStream_t
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(512), RANK_UPDATE_LDS, stream, us, la);
 }
 
+// Panels in a batch.  A long one passes over memory less often and fills its rounds better, but a launch waits for the
+// strips, which lack up to two batches: with four panels 38 us where the chain takes 33.  A launch of the inverse takes, us, the chain,
+// or its share of the batch's rounds of 128 x 256 blocks (19 per 64 pivots), or half of that where blocks of half the size fit it;
+// where the lengths are even the longest is taken.  K = N, batches of 2, 3 and 4 of the inverse, ms: 2048 3.18, 3.15, 3.32, 3072 5.55,
+// 5.46, 5.71, 3584 6.97, 7.38, 7.14, 4096 9.77, 9.31, 9.82, 4480 11.6, 11.2, 12.1, 5120 15.9, 15.3, 15.0.
+// What is left of the visit shrinks from panel to panel: 2, 3, 4: K = N = 2048 3.11, 3.12, 3.32, 4096 9.79, 9.59, 9.82, 5120 15.34, 14.92, 15.02.
+constexpr int VISIT_BATCH = 3;
+int inverse_batch(int K, int cus) {
+    int best = 2;
+    double least = 1e30;
+    for (int n = 2; n <= MAX_BATCH; ++n) {
+        const int rows = K - (n + 1) * PB > 0 ? K - (n + 1) * PB : 0, blocks = (rows + 127) / 128 * ((rows + 255) / 256);
+        const int rounds = (blocks + n * (K / 128 + 17) + cus - 1) / cus;
+        double c = 2 * blocks / n + K / 64 + 20 <= cus ? 9.5 * n + 2.0 : 19.0 * (rounds > n ? rounds : n);
+        if (c < 33.0) c = 33.0;
+        if (c <= least) {
+            least = c;
+            best = n;
+        }
+    }
+    return best;
+}
+
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -900,6 +923,7 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     hipLaunchKernelGGL(diag_sum_kernel, dim3(1), dim3(256), 0, stream, H, damp, K, add);
     hipLaunchKernelGGL(prepare_kernel, dim3(K), dim3(256), 0, stream, R, H, add, N, K, A, W);
     const size_t ldk = (size_t)K, ldn = (size_t)N;
+    int span = inverse_batch(K, walking_blocks());
     constexpr int ALL = INT_MAX;                       // nothing left out
     const int np = K / PB;
     auto slot = [](int panel) { return (size_t)(panel % RING_PANELS) * PB; };
@@ -912,8 +936,8 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     const int cus = walking_blocks();
     // what panel t's strips have had when it is their turn; its diagonal block, a panel earlier (the one that a batch of
     // updates of the rest would otherwise touch meanwhile is left out of that, as the batch's `hole`)
-    auto strip_base = [](int t) { return t % BATCH ? (t / BATCH - 1) * BATCH : t - 2 * BATCH; };
-    auto diag_base = [&](int t) { return t % BATCH == 1 ? t - 1 - 2 * BATCH : strip_base(t); };
+    auto strip_base = [&](int t) { return t % span ? (t / span - 1) * span : t - 2 * span; };
+    auto diag_base = [&](int t) { return (t - 1) % span == 0 ? t - 1 - 2 * span : strip_base(t); };
     // panel t's diagonal block up to panel t - 1, so that only that one's pivots stand ahead of its own
     auto early = [&](int t) { return whole(update(A, Lc, Rr, ldk, false, 3, diag_base(t), t - 1, t * PB, PB, ALL, t * PB, PB, ALL, 0, -1)); };
     // The strips have up to 512 updates ahead of them, 76 us where a wave has 32 rows of them, 38 where it has 16 (the looking
@@ -926,8 +950,8 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     int done_a = 0, done_w = 0;                        // blocks of the batch's updates that its launches have had
     hipLaunchKernelGGL(first_tables_kernel<true>, dim3(1), dim3(512), 0, stream, A, ldk, tabs[cur]);
     for (int b = 0; b < np; ++b) {                     // the inverse, one panel of pivots at a time
-        const int p0 = b * PB, t = b + 1, batch = b / BATCH * BATCH;
-        const bool back = batch / BATCH & 1;
+        const int p0 = b * PB, t = b + 1, batch = b / span * span;
+        const bool back = batch / span & 1;
         if (np > 1)
             hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (K - PB) / PVECS), dim3(256), 0, stream, A, K, p0, tabs[cur],
                                Lc + slot(b) * ldk, Rr + slot(b) * ldk);
@@ -935,10 +959,10 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
         Lookahead la{A, Lc, Rr, tabs[cur], tabs[cur ^ 1], b, t, K, p0, t * PB, 1};
         if (t < np) {
             const int s0 = t * PB, base = strip_base(t);
-            const int left = batch * PB, nleft = K - left < (BATCH + 1) * PB ? K - left : (BATCH + 1) * PB;
-            const int launches = (batch + BATCH < np ? BATCH : np - 1 - batch) - (b - batch);   // the last launch of all is below
-            RankUpdate rest = update(A, Lc, Rr, ldk, true, 0, batch - BATCH, batch, 0, K - nleft, left, 0, K - nleft, left, nleft,
-                                     (batch + BATCH + 1) * PB);
+            const int left = batch * PB, nleft = K - left < (span + 1) * PB ? K - left : (span + 1) * PB;
+            const int launches = (batch + span < np ? span : np - 1 - batch) - (b - batch);   // the last launch of all is below
+            RankUpdate rest = update(A, Lc, Rr, ldk, true, 0, batch - span, batch, 0, K - nleft, left, 0, K - nleft, left, nleft,
+                                     (batch + span + 1) * PB);
             rest.shape = rest_shape(whole(rest).count, launches + (b - batch), 2 * (K - PB));
             if (b == batch) done_a = 0;
             const int na = whole(rest).count - done_a, thin = thin_strips(na / launches, 2 * (K - PB));
@@ -950,7 +974,7 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
             done_a += n;
         } else {
             // everything that is pending; the first diagonal block of the visit is looked ahead for
-            const int base = batch + 1 < np ? batch : batch - BATCH;                 // a last batch of one panel had no launch before
+            const int base = batch + 1 < np ? batch : batch - span;                 // a last batch of one panel had no launch before
             us.u[0] = whole(update(A, Lc, Rr, ldk, true, 0, base, t, 0, K, ALL, 0, K, ALL, 0, 0));
             la.from = base > 0 ? base : 1;                                           // panel 0 is behind its own pivots
             la.s0 = 0;
@@ -959,18 +983,19 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
         launch_rank_updates(us, la, stream);
         cur ^= 1;
     }
+    span = VISIT_BATCH;
     for (int b = 0; b < np; ++b) {                     // the weights, one panel (= one 64-group) at a time
-        const int i0 = b * PB, t = b + 1, i1 = i0 + PB, rest = K - i1, batch = b / BATCH * BATCH;
+        const int i0 = b * PB, t = b + 1, i1 = i0 + PB, rest = K - i1, batch = b / span * span;
         hipLaunchKernelGGL(visit_panel_kernel, dim3(2 * (rest / PVECS) + (N + PVECS - 1) / PVECS), dim3(256), 0, stream,
                            A, W, N, K, i0, tabs[cur], Lc + slot(b) * ldk, Hr + slot(b) * ldk, Rr + slot(b) * ldk, Err + slot(b) * ldn, qw, sw);
         if (rest > 0) {                                // the deferred updates of what is behind the panel
-            const int base = strip_base(t), behind = (batch + BATCH + 1) * PB, far = K - behind;
-            const bool back = batch / BATCH & 1;
-            RankUpdate of_w = update(W, Hr, Err, ldn, false, 0, batch - BATCH, batch, behind, far, ALL, 0, N, ALL, 0, -1);
-            RankUpdate of_a = update(A, Lc, Rr, ldk, false, 0, batch - BATCH, batch, behind, far, ALL, behind, far, ALL, 0, behind);
-            of_w.shape = of_a.shape = rest_shape(whole(of_w).count + whole(of_a).count, BATCH, 2 * (K - batch * PB) + N);
+            const int base = strip_base(t), behind = (batch + span + 1) * PB, far = K - behind;
+            const bool back = batch / span & 1;
+            RankUpdate of_w = update(W, Hr, Err, ldn, false, 0, batch - span, batch, behind, far, ALL, 0, N, ALL, 0, -1);
+            RankUpdate of_a = update(A, Lc, Rr, ldk, false, 0, batch - span, batch, behind, far, ALL, behind, far, ALL, 0, behind);
+            of_w.shape = of_a.shape = rest_shape(whole(of_w).count + whole(of_a).count, span, 2 * (K - batch * PB) + N);
             if (b == batch) done_a = done_w = 0;
-            const int nw = whole(of_w).count - done_w, na = whole(of_a).count - done_a, launches = BATCH - (b - batch);
+            const int nw = whole(of_w).count - done_w, na = whole(of_a).count - done_a, launches = span - (b - batch);
             const int thin = thin_strips((nw + na) / launches, 2 * rest + N);
             RankUpdates us{{
                 whole(update(W, Hr, Err, ldn, false, 1 + thin, base, t, i1, PB, ALL, 0, N, ALL, 0, -1)),

@@ -99,3 +99,9 @@ def test_gptq_batches_of_panels(svdq, oracle, panels, N, classes, channels):
         oq, os_ = oracle.gptq_quantize(np.ascontiguousarray(R[np.ix_(k, n)]), np.ascontiguousarray(H[np.ix_(k, k)]), damp=0.0)
         assert np.array_equal(sw[k[::64] // 64].view(np.uint32), os_.view(np.uint32))
         assert np.array_equal(qw[:, k[::2] // 2], oq)
+
+
+@pytest.mark.parametrize("panels,N,classes", [(56, 70, 7), (76, 33, 19)])
+def test_gptq_batches_of_two_and_four(svdq, oracle, panels, N, classes):
+    """The sizes at which a batch of the inverse is two panels and four (three in the cases above)."""
+    test_gptq_batches_of_panels(svdq, oracle, panels, N, classes, None)
