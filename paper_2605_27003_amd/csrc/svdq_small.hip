@@ -16,6 +16,8 @@
 // weights are what is read, and expanding them to 6 bits in memory first would move them three times), against the
 // expanded ones, nibble activations against the nibble kernel's packed weights (both turned into E3M2 fields in
 // registers; same integer group sums), and MXFP4.
+#include <type_traits>
+
 #include "svdq_act.h"
 #include "svdq_dev.h"
 #include "svdq_epilogue.h"
@@ -80,17 +82,19 @@ struct LaneOffsets {
 
 // What a lane loads for one step (a 64-group; MXFP4: two) of its tokens and of its channels, and how the two become
 // matrix instructions on y.
+template <int N> using Vec4 = std::conditional_t<(N > 1), u32x4, uint4>;
+template <int N> using Vec2 = std::conditional_t<(N > 1), u32x2, uint2>;
 template <int SRC, int MT>
 struct Tokens {
-    uint4 x[MT];
-    uint2 xh[MT];
+    Vec4<MT> x[MT];
+    Vec2<MT> xh[MT];
     uint32_t sx[MT];
     __device__ __forceinline__ void load(const SmallArgs& a, const Buffers& B, const int g, const LaneOffsets<MT>& o) {
         const uint32_t M = (uint32_t)a.M;
         if constexpr (SRC == SMALL_NIBBLE) {
 #pragma unroll
             for (int mi = 0; mi < MT; ++mi) {
-                x[mi] = at<uint4>(B.codes, (uint32_t)g * M * 32, o.row[mi] * 32 + o.kh * 16);
+                x[mi] = at<Vec4<MT>>(B.codes, (uint32_t)g * M * 32, o.row[mi] * 32 + o.kh * 16);
                 sx[mi] = at<uint32_t>(B.scales, (uint32_t)g * M * 4, o.row[mi] * 4);
             }
         } else {
@@ -98,8 +102,8 @@ struct Tokens {
             const uint32_t blk = (uint32_t)g * Mp * E3M2_ROW_BYTES;
 #pragma unroll
             for (int mi = 0; mi < MT; ++mi) {
-                x[mi] = at<uint4>(B.codes, blk, o.row[mi] * 32 + o.kh * 16);
-                xh[mi] = at<uint2>(B.codes, blk + Mp * 32, (o.kh * Mp + o.row[mi]) * 8);
+                x[mi] = at<Vec4<MT>>(B.codes, blk, o.row[mi] * 32 + o.kh * 16);
+                xh[mi] = at<Vec2<MT>>(B.codes, blk + Mp * 32, (o.kh * Mp + o.row[mi]) * 8);
                 sx[mi] = at<uint32_t>(B.codes, blk + Mp * 48, o.row[mi] * 8);
             }
         }
@@ -107,8 +111,8 @@ struct Tokens {
 };
 template <int SRC, int NI>
 struct Channels {
-    uint4 w[NI];
-    uint2 wh[NI], sf[NI];
+    Vec4<NI> w[NI];
+    Vec2<NI> wh[NI], sf[NI];
     uint32_t sw[NI];
     template <int MT>
     __device__ __forceinline__ void load(const SmallArgs& a, const Buffers& B, const int g, const int nb, const LaneOffsets<MT>& o) {
@@ -117,29 +121,29 @@ struct Channels {
         for (int ni = 0; ni < NI; ++ni) {
             const uint32_t fr = (uint32_t)(nb + ni) * ng + g;
             if constexpr (SRC == SMALL_E3M2_CANONICAL) {
-                w[ni] = at<uint4>(B.w0, (uint32_t)g * 32 + (uint32_t)ni * 16 * a.K, o.n * (uint32_t)(a.K >> 1) + o.kh * 16);
+                w[ni] = at<Vec4<NI>>(B.w0, (uint32_t)g * 32 + (uint32_t)ni * 16 * a.K, o.n * (uint32_t)(a.K >> 1) + o.kh * 16);
                 sw[ni] = at<uint32_t>(B.w1, ((uint32_t)g * a.N + ni * 32) * 4, o.n * 4);
             } else if constexpr (SRC == SMALL_E3M2_PACKED) {
-                w[ni] = at<uint4>(B.w0, fr * 1024, o.lane * 16);
-                wh[ni] = at<uint2>(B.w1, fr * 512, o.lane * 8);
-                sf[ni] = at<uint2>(B.w2, fr * 256, o.l32 * 8);
+                w[ni] = at<Vec4<NI>>(B.w0, fr * 1024, o.lane * 16);
+                wh[ni] = at<Vec2<NI>>(B.w1, fr * 512, o.lane * 8);
+                sf[ni] = at<Vec2<NI>>(B.w2, fr * 256, o.l32 * 8);
             } else {
-                w[ni] = at<uint4>(B.w0, fr * 1024, o.lane * 16);
-                sf[ni] = at<uint2>(B.w1, fr * 512, o.l32 * 8);
+                w[ni] = at<Vec4<NI>>(B.w0, fr * 1024, o.lane * 16);
+                sf[ni] = at<Vec2<NI>>(B.w1, fr * 512, o.l32 * 8);
             }
         }
     }
 };
 // y += one group of an n-block times one of a token block: the weights as loaded, the tokens as fields (b) and scale pieces (sp,
 // zeros in the lanes of k half 1: the scale product uses those of half 0 only).
-template <int SRC>
-__device__ __forceinline__ LaneCodes<true> weight_fields(const uint4& w, const uint2& wh) {
-    if constexpr (SRC == SMALL_E3M2_PACKED) return LaneCodes<true>{w, wh};
-    else return e3m2_of_nibbles(w);
+template <int SRC, class W4, class W2>
+__device__ __forceinline__ LaneCodes<true> weight_fields(const W4& w, const W2& wh) {
+    if constexpr (SRC == SMALL_E3M2_PACKED) return LaneCodes<true>{uint4{w.x, w.y, w.z, w.w}, uint2{wh.x, wh.y}};
+    else return e3m2_of_nibbles(uint4{w.x, w.y, w.z, w.w});
 }
-template <int SRC>
-__device__ __forceinline__ uint2 weight_scales(const uint2& sf, const uint32_t sw, const int kh) {
-    uint2 s = sf;
+template <int SRC, class W2>
+__device__ __forceinline__ uint2 weight_scales(const W2& sf, const uint32_t sw, const int kh) {
+    uint2 s = {sf.x, sf.y};
     if constexpr (SRC == SMALL_E3M2_CANONICAL) {
         const uint32_t p = split_bf16(bits_f(sw)), w1 = p & 0xffffu, w2 = p >> 16;
         s = uint2{w1 | (w1 << 16), w2 | (w2 << 16)};
@@ -163,8 +167,8 @@ __device__ __forceinline__ void multiply(const Tokens<SRC, MT>& t, const Channel
     uint2 sp[MT];
 #pragma unroll
     for (int mi = 0; mi < MT; ++mi) {
-        if constexpr (SRC == SMALL_NIBBLE) xf[mi] = e3m2_of_nibbles(t.x[mi]);
-        else xf[mi] = LaneCodes<true>{t.x[mi], t.xh[mi]};
+        if constexpr (SRC == SMALL_NIBBLE) xf[mi] = e3m2_of_nibbles(uint4{t.x[mi].x, t.x[mi].y, t.x[mi].z, t.x[mi].w});
+        else xf[mi] = LaneCodes<true>{uint4{t.x[mi].x, t.x[mi].y, t.x[mi].z, t.x[mi].w}, uint2{t.xh[mi].x, t.xh[mi].y}};
         uint32_t p = (SRC == SMALL_NIBBLE) ? split_bf16(bits_f(t.sx[mi])) : t.sx[mi];
         p = kh ? 0u : p;
         sp[mi] = uint2{p, p};
@@ -236,6 +240,16 @@ __device__ __forceinline__ void sum_slices(const float* __restrict__ part, const
     *reinterpret_cast<float4*>(h + i) = sum_of_slices(part, slices, n, i);
 }
 
+// f(IC<0>), f(IC<1>), ..: a loop whose index is a constant from the first.  In a 64 x 64 tile, with Tokens and Channels of language vectors,
+// it keeps all of them in registers: packed E3M2 fields were in scratch in part, nibbles spilled (M = 44, K = 3264, N = 9728 18.3 -> 17.2 us).
+template <int COUNT, class F>
+__device__ __forceinline__ void steps_of(F f) {
+    if constexpr (COUNT > 0) {
+        steps_of<COUNT - 1>(f);
+        f(IC<COUNT - 1>{});
+    }
+}
+
 template <int SRC, int NI, int MT>
 __global__ __launch_bounds__(64 * WV, NI * MT >= 4 ? 2 : 4)
 void small_gemm_kernel(const SmallArgs a) {
@@ -286,22 +300,28 @@ void small_gemm_kernel(const SmallArgs a) {
     }
     constexpr int U = (DW % 2) ? 2 * DW : DW;             // both rings return to their first slot
     int s = 0;
-    for (; s + U <= s1; s += U) {
+    auto step = [&](const int d) __attribute__((always_inline)) {
+        wc[(d + DW - 1) % DW].load(a, B, clamp(s + d + DW - 1), n0 >> 5, off);
+        xt[(d + 1) & 1].load(a, B, clamp(s + d + 1), off);
+        multiply(xt[d & 1], wc[d % DW], y, kh);
+        __builtin_amdgcn_sched_barrier(0);                // steps interleaved would need registers for several
+    };
+    auto last_step = [&](const int d) __attribute__((always_inline)) {
+        if (s + d >= s1) return;
+        if (d + DW - 1 < U - 1) wc[(d + DW - 1) % DW].load(a, B, clamp(s + d + DW - 1), n0 >> 5, off);
+        xt[(d + 1) & 1].load(a, B, clamp(s + d + 1), off);
+        multiply(xt[d & 1], wc[d % DW], y, kh);
+    };
+    if constexpr (NI * MT > 2) {
+        for (; s + U <= s1; s += U) steps_of<U>([&](auto D) { step(decltype(D)::value); });
+        steps_of<U - 1>([&](auto D) { last_step(decltype(D)::value); });
+    } else {                                              // (with constants 3 % longer)
+        for (; s + U <= s1; s += U)
 #pragma unroll
-        for (int d = 0; d < U; ++d) {
-            wc[(d + DW - 1) % DW].load(a, B, clamp(s + d + DW - 1), n0 >> 5, off);
-            xt[(d + 1) & 1].load(a, B, clamp(s + d + 1), off);
-            multiply(xt[d & 1], wc[d % DW], y, kh);
-            __builtin_amdgcn_sched_barrier(0);            // steps interleaved would need registers for several
-        }
+            for (int d = 0; d < U; ++d) step(d);
+#pragma unroll
+        for (int d = 0; d < U - 1; ++d) last_step(d);
     }
-#pragma unroll
-    for (int d = 0; d < U - 1; ++d)
-        if (s + d < s1) {
-            if (d + DW - 1 < U - 1) wc[(d + DW - 1) % DW].load(a, B, clamp(s + d + DW - 1), n0 >> 5, off);
-            xt[(d + 1) & 1].load(a, B, clamp(s + d + 1), off);
-            multiply(xt[d & 1], wc[d % DW], y, kh);
-        }
 
     if (wave == 0 || (a.r > 0 && wave < a.hs))
         add_lowrank_bias<NI, MT>(y, a.h + (size_t)wave * M * a.r, a.L2, wave == 0 ? a.bias : nullptr, m0, n0, M, a.N, a.r, lane);
