@@ -940,10 +940,10 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
     auto diag_base = [&](int t) { return (t - 1) % span == 0 ? t - 1 - 2 * span : strip_base(t); };
     // panel t's diagonal block up to panel t - 1, so that only that one's pivots stand ahead of its own
     auto early = [&](int t) { return whole(update(A, Lc, Rr, ldk, false, 3, diag_base(t), t - 1, t * PB, PB, ALL, t * PB, PB, ALL, 0, -1)); };
-    // The strips have up to 512 updates ahead of them, 76 us where a wave has 32 rows of them, 38 where it has 16 (the looking
-    // ahead takes 44): in twice the blocks (shape + 3), where those open no round of their own
+    // The strips have up to two batches ahead of them, 512 updates, 76 us, at most where a wave has 32 rows of them, 38 where it has 16 (the
+    // looking ahead takes 30): in twice the blocks (shape + 3), where those open no round of their own
     auto thin_strips = [&](int others, int length) { return others + length / 128 + 20 <= cus ? 3 : 0; };
-    // The same of the rest, for a batch that is less than a round of blocks per launch: 38 us instead of 76.  (Without the two
+    // The same of the rest, for a batch that is less than a round of blocks per launch: 38 us instead of 76.  (With batches of four, without the two
     // rules K = N = 1536 takes 3.57 ms, with the first 3.37, with both 3.15; without batches 3.32.)
     auto rest_shape = [&](int blocks, int launches, int length) { return 2 * blocks / launches + length / 128 + 20 <= cus ? 6 : 0; };
     int cur = 0;                                       // tabs[cur]: the current panel's
