@@ -184,7 +184,7 @@ void gemm_e3m2_mid_kernel(const uint8_t* __restrict__ act, const uint8_t* __rest
     __syncthreads();
     if (team == 0) {
         const int nw = n0 + wn * 96;
-        add_lowrank_bias_from<NI, MT>(y, [&](const int mi, const int k) {
+        add_lowrank_bias_from<NI, MT, true>(y, [&](const int mi, const int k) {
             return *reinterpret_cast<const float4*>(hbuf + (wm * 2 + mi) * 4096 + (k >> 2) * 512 + l32 * 16);
         }, L2, bias, nw, N, r, lane, N - 32);
     }

@@ -1,7 +1,5 @@
 // Low-rank up-projection and bias of eq. 7 / eq. 11 on a wave's accumulator tile, shared by the GEMM kernels.
 #pragma once
-#include <climits>
-
 #include "svdq_dev.h"
 #include "svdq_kernels.h"
 #include "svdq_lds.h"
@@ -38,11 +36,13 @@ __device__ __forceinline__ float4 sum_of_slices(const float* __restrict__ part, 
 //
 // h_piece(mi, k) returns the four values h[token of block mi][k .. k + 3] of this lane's token (k a multiple of 4):
 // from global memory in add_lowrank_bias, from wherever the caller staged the tile's h rows in add_lowrank_bias_from.
-// last_n: 32-channel blocks beyond it read that one (their results are never stored).
-template <int NI, int MT, class HPiece>
+// OVER: the tile may stand over the end of N; 32-channel blocks beyond last_n read that one (their results are never stored).
+// (Without it the addresses are formed as bias + n0 + .., from the left: with the sum of the offsets taken first the 128 x 128 E3M2
+// kernel has 247 registers instead of 231, and its layers take 3 % longer: M = 3140, K = 4672, N = 3968 108.4 -> 112.5 us.)
+template <int NI, int MT, bool OVER = false, class HPiece>
 __device__ __forceinline__ void add_lowrank_bias_from(float16v (&y)[NI][MT], HPiece h_piece,
                                                       const uint16_t* __restrict__ L2, const float* __restrict__ bias,
-                                                      int n0, int N, int r, int lane, int last_n = INT_MAX) {
+                                                      int n0, int N, int r, int lane, int last_n = 0) {
     const int l32 = lane & 31, kh = lane >> 5;
     float4 bv[NI][4];
 #pragma unroll
@@ -50,7 +50,7 @@ __device__ __forceinline__ void add_lowrank_bias_from(float16v (&y)[NI][MT], HPi
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             bv[ni][q] = float4{0.f, 0.f, 0.f, 0.f};
-            if (bias) bv[ni][q] = *reinterpret_cast<const float4*>(bias + min(n0 + ni * 32, last_n) + 8 * q + 4 * kh);
+            if (bias) bv[ni][q] = *reinterpret_cast<const float4*>((OVER ? bias + min(n0 + ni * 32, last_n) : bias + n0 + ni * 32) + 8 * q + 4 * kh);
         }
     if (r > 0) {
         uint32_t wds[2][NI][4];
@@ -60,7 +60,7 @@ __device__ __forceinline__ void add_lowrank_bias_from(float16v (&y)[NI][MT], HPi
             const int k0 = (16 * ks < r) ? 16 * ks : 0;
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
-                const int n = min(n0 + ni * 32, last_n) + l32;
+                const int n = (OVER ? min(n0 + ni * 32, last_n) : n0 + ni * 32) + l32;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const uint32_t lo = L2[(int64_t)(k0 + 8 * kh + 2 * e) * N + n];
