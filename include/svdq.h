@@ -268,7 +268,7 @@ int svdq_debug_gelu(const void* x_bf16, int64_t n, void* out_bf16, void* stream)
  *                   GEMM (0 bytes if they are resident or M is small: NULL then), and for SVDQ_FMT_INT4, which runs as
  *                   E3M2 fields with many tokens (same codes and scales), for the activations' fields.  Holds nothing
  *                   between calls
- *   y               out [M, ldy] bf16
+ *   y               out [M, ldy] bf16; may share memory with x, and with nothing else
  * svdq_layer_gemm: the second half, from activations quantised by the format's own call.
  */
 typedef struct {

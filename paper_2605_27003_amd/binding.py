@@ -656,6 +656,7 @@ class W4A4Linear:
         return work.y
 
     def forward(self, x_bf16, rho, gelu=False):
+        """The layer's output, in the layer's own buffer, which the next call writes again.  x may be that buffer."""
         M, K = x_bf16.shape
         # the MXFP4 pass also takes the bits in another two-byte type, as quantize_act_mxfp4 does
         assert x_bf16.dtype == torch.bfloat16 or (self.container == "mxfp4" and not gelu and x_bf16.element_size() == 2)

@@ -503,6 +503,12 @@ int svdq_layer_gemm(const svdq_layer* L, const void* codes, const void* scales, 
     return layer_gemm(L, (const uint8_t*)codes, scales, false, false, h, 1, nullptr, M, staging, y, ldy, (hipStream_t)stream);
 }
 
+// Whether two bf16 matrices may share memory: the spans from their first elements to their last meet.
+static bool spans_meet(const void* a, int64_t lda, int cols_a, const void* b, int64_t ldb, int cols_b, int64_t rows) {
+    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
+    return a0 < b0 + 2 * ((uintptr_t)(rows - 1) * ldb + cols_b) && b0 < a0 + 2 * ((uintptr_t)(rows - 1) * lda + cols_a);
+}
+
 int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, float rho, int gelu, int64_t M,
                        void* codes, void* scales, float* h, void* scratch, void* staging,
                        void* y, int64_t ldy, void* stream_) {
@@ -517,7 +523,9 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (int a = check_arch()) return a;
     hipStream_t stream = (hipStream_t)stream_;
     const int K = L->K, r = L->r;
-    if (small_path(L, M) && svdq::small_fused(M, L->N, K, r, L->format == SVDQ_FMT_MXFP4) != svdq::FUSED_NONE) {
+    // A layer may be given its own output (K = N).  With two launches all of x has been read before y is written; in one, blocks of other
+    // channel tiles still read x.
+    if (!spans_meet(x_bf16, ldx, K, y, ldy, L->N, M) && small_path(L, M) && svdq::small_fused(M, L->N, K, r, L->format == SVDQ_FMT_MXFP4) != svdq::FUSED_NONE) {
         const SmallWeights w = small_weights(L);
         return hip_status(svdq::launch_fused_layer(w.source, x_bf16, ldx, L->inv_lambda, rho, gelu != 0, L->l1_packed, (uint8_t*)codes, scales, h,
                                                    w.w0, w.w1, L->L2_bf16, L->bias, M, L->N, K, r, y, ldy, stream));

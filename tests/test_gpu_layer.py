@@ -126,6 +126,29 @@ def test_layer_in_one_launch(svdq, container, M, K, N, r, gelu, ldx):
     assert torch.isfinite(y.float()).all()
 
 
+@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble", "mxfp4"])
+@pytest.mark.parametrize("M,K,r", [(1, 1536, 32), (12, 1024, 16), (256, 512, 32), (256, 512, 0), (700, 512, 16), (300, 2048, 32)])
+def test_layer_on_its_own_output(svdq, container, M, K, r):
+    """forward(forward(x)) of a square layer: the buffer that the first call returns is the second one's x and y.  Codes and
+    scales are bit for bit those of a copy of it, and y their product (the bar of the layer)."""
+    mx = container == "mxfp4"
+    bits, _ = synth.make_x(M + K, M, K, outlier_count=3, outlier_scale=30.0)
+    cm = np.maximum(np.abs(synth.bf16_bits_to_f32(bits)).max(axis=0), 1e-3).astype(np.float32)
+    L = synth.make_layer(M + K, K, K, r, cm, fmt="mxfp4" if mx else "int4")
+    lin = svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1) if r else None, dev(L.L2) if r else None, dev(L.qw), dev(L.sw),
+                          dev(L.bias), container=container.split()[0], resident="packed" if "packed" in container else "w4")
+    x = dev(bits).view(torch.bfloat16)
+    codes, scales, _, buf = lin.buffers(M, "cuda:0")
+    fields = svdq.unpack_act_e3m2 if container.startswith("e3m2") else torch.clone
+    once = lin.forward(x, 0.8).clone()
+    want = lin.gemm(*lin.quantize(once, 0.8)).clone()
+    want_codes, want_scales = fields(codes).clone(), None if scales is None else scales.clone()
+    y = lin.forward(lin.forward(x, 0.8), 0.8)
+    assert y.data_ptr() == buf.data_ptr()
+    assert torch.equal(fields(codes), want_codes) and (scales is None or torch.equal(scales, want_scales))
+    assert rel_fro(y.double().cpu().numpy(), want.double().cpu().numpy()) <= 2e-3
+
+
 @pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble"])
 @pytest.mark.parametrize("M,K,N,r", [
     (500, 5120, 5120, 32), (513, 5120, 5120, 16),       # two teams, eight slices; a last tile of one token
