@@ -386,8 +386,10 @@ static int layer_check(const svdq_layer* L, int64_t M) {
     return M > SVDQ_MAX_M ? SVDQ_ERR_UNSUPPORTED_SHAPE : SVDQ_OK;
 }
 
+// Whether the GEMM takes the layer's own codes and weights, as they are held, on the kernel for few tokens: no staging then.
 static bool small_path(const svdq_layer* L, int64_t M) {
-    return svdq::small_shape(M, L->N, L->K, L->format == SVDQ_FMT_MXFP4) != 0 && svdq::small_reach(M, L->N, L->K);
+    return svdq::small_shape(M, L->N, L->K, L->format == SVDQ_FMT_MXFP4, L->format == SVDQ_FMT_INT4_E3M2 && L->w_packed) != 0 &&
+           svdq::small_reach(M, L->N, L->K);
 }
 
 // K slices of the quantise pass: blocks for every CU where the row blocks (32 rows) are few, at least a group for each of a
@@ -422,8 +424,11 @@ size_t svdq_layer_scratch_bytes(const svdq_layer* L, int64_t M) {
 // whole group at twice the int8 rate, and writing the activations as fields (56 instead of 36 bytes per token and group)
 // and expanding the weights cost less than that saves (M = 32760, K = N = 5120: 1.05 against 1.39 ms; M = 512: 39
 // against 44 us).  Same codes, same integer group sums, same scale pieces.  Fields and expanded weights live in the
-// caller's staging for the call only; codes and scales receive the layer's own 4-bit form beside them.
-static bool as_fields(const svdq_layer* L, int64_t M) { return L->format == SVDQ_FMT_INT4 && !small_path(L, M); }
+// caller's staging for the call only; codes and scales receive the layer's own 4-bit form beside them.  Without staging (staged =
+// false) it is what the few-token GEMM does not take.
+static bool as_fields(const svdq_layer* L, int64_t M, bool staged = true) {
+    return L->format == SVDQ_FMT_INT4 && (!small_path(L, M) || (staged && svdq::small_shape(M, L->N, L->K, false, true) == 0));
+}
 static size_t staged_weight_bytes(const svdq_layer* L) { return (svdq::packed_weight_e3m2_bytes(L->N, L->K) + 255) & ~(size_t)255; }
 
 size_t svdq_layer_codes_bytes(const svdq_layer* L, int64_t M) {
@@ -432,9 +437,9 @@ size_t svdq_layer_codes_bytes(const svdq_layer* L, int64_t M) {
 }
 
 size_t svdq_layer_staging_bytes(const svdq_layer* L, int64_t M) {
-    if (layer_check(L, M) != SVDQ_OK || small_path(L, M)) return 0;
+    if (layer_check(L, M) != SVDQ_OK) return 0;
     if (as_fields(L, M)) return staged_weight_bytes(L) + svdq::act_e3m2_bytes(M, L->K);
-    return L->w_packed ? 0 : svdq::packed_weight_e3m2_bytes(L->N, L->K);
+    return L->w_packed || small_path(L, M) ? 0 : svdq::packed_weight_e3m2_bytes(L->N, L->K);
 }
 
 static svdq::ExpandJob layer_expand_job(const svdq_layer* L, void* staging) {
@@ -443,7 +448,7 @@ static svdq::ExpandJob layer_expand_job(const svdq_layer* L, void* staging) {
 
 // Whether the layer's GEMM adds up the partial h's of the quantise pass itself.
 static bool gemm_takes_slices(const svdq_layer* L, int64_t M, bool fields) {
-    return small_path(L, M) || ((fields || L->format == SVDQ_FMT_INT4_E3M2) && svdq::layer_e3m2_takes_slices(M, L->N, L->K));
+    return (!fields && small_path(L, M)) || ((fields || L->format == SVDQ_FMT_INT4_E3M2) && svdq::layer_e3m2_takes_slices(M, L->N, L->K));
 }
 
 // The layer's weights as the kernels for few tokens take them.
@@ -464,7 +469,7 @@ static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* sca
                       int64_t M, void* staging, void* y, int64_t ldy, hipStream_t stream) {
     const int N = L->N, K = L->K, r = L->r;
     const uint8_t* wp = (const uint8_t*)L->w_packed;
-    if (small_path(L, M)) {
+    if (!fields && small_path(L, M)) {
         const SmallWeights w = small_weights(L);
         return hip_status(svdq::launch_small_gemm(w.source, codes, scales, w.w0, w.w1, h, slices, slices > 1 ? hsum : nullptr, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
     }
@@ -516,7 +521,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
     if (!x_bf16 || !(rho > 0.0f) || !(rho <= 1.0f)) return SVDQ_ERR_INVALID_ARG;
     if (L->K > SVDQ_MAX_K || ldx < L->K || ldx % 8 || !aligned16(x_bf16) || !aligned16(scratch)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
-    const bool fields = as_fields(L, M);                                     // they follow the weights in staging
+    const bool fields = as_fields(L, M, staging && aligned16(staging));      // they follow the weights in staging
     const bool expand = fields || (!L->w_packed && !small_path(L, M));       // the GEMM needs the weights in staging
     if (expand && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
@@ -525,7 +530,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     const int K = L->K, r = L->r;
     // A layer may be given its own output (K = N).  With two launches all of x has been read before y is written; in one, blocks of other
     // channel tiles still read x.
-    if (!spans_meet(x_bf16, ldx, K, y, ldy, L->N, M) && small_path(L, M) && svdq::small_fused(M, L->N, K, r, L->format == SVDQ_FMT_MXFP4) != svdq::FUSED_NONE) {
+    if (!spans_meet(x_bf16, ldx, K, y, ldy, L->N, M) && !fields && small_path(L, M) && svdq::small_fused(M, L->N, K, r, L->format == SVDQ_FMT_MXFP4) != svdq::FUSED_NONE) {
         const SmallWeights w = small_weights(L);
         return hip_status(svdq::launch_fused_layer(w.source, x_bf16, ldx, L->inv_lambda, rho, gelu != 0, L->l1_packed, (uint8_t*)codes, scales, h,
                                                    w.w0, w.w1, L->L2_bf16, L->bias, M, L->N, K, r, y, ldy, stream));

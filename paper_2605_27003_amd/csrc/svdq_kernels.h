@@ -85,10 +85,16 @@ constexpr int SMALL_SLICES = 8;                  // waves of a block = most part
 // M = 307, even; but K = 512 16 against 15, and N = 2048, M = 960, 42 against 38).  MXFP4 expands nothing and wins up to 320
 // blocks (K = 5120: N = 512, M = 2304, 30 against 35; N = 5120, M = 230, 24 against 26; M = 307, 400 blocks, 29 against 27),
 // with few channels and a long K up to 384 (K = 5120, N = 1024, M = 1536, 27 against 31; K = 512 even).
-inline int small_shape(int64_t M, int N, int K, bool mxfp4 = true) {
+// fields: the tiles find E3M2 fields with nothing to expand ahead of them, or with the layer's staging for it (packed E3M2 weights;
+// forward() of nibbles).  Where a row of tiles is 48 at most they then win from 161 tokens on with more than one block per CU
+// (packed, K = 11840, N = 6144, M = 178, 50 against 42; K = 7040, N = 4736, M = 205, 35 against 27; K = 3968, N = 4096, M = 384, even;
+// nibbles, K = 6336, N = 5248, M = 200, 46 against 36).  With more channels or fewer tokens the limit is as without them:
+// nibbles lose there as often as they gain (N = 13824, M = 66, K = 2944, 28 against 32; N = 9088, M = 77, K = 5120, 36
+// against 30), packed weights would gain (N = 10112, M = 123, K = 11648, 58 against 44).
+inline int small_shape(int64_t M, int N, int K, bool mxfp4 = true, bool fields = false) {
     const int64_t b32 = ((M + 31) / 32) * (N / 32), b64 = ((M + 63) / 64) * ((N + 63) / 64);
     if (b32 <= (mxfp4 ? 256 : 512)) return 1;
-    const int limit = mxfp4 ? (N <= 2048 && K >= 4096 ? 384 : 320) : (N >= 4096 && K >= 2048 && (M <= 160 || N > 6144)) ? 480 : 256;
+    const int limit = mxfp4 ? (N <= 2048 && K >= 4096 ? 384 : 320) : (N >= 4096 && K >= 2048 && !(fields && M > 160 && N <= 6144)) ? 480 : 256;
     return b64 <= limit ? 2 : 0;
 }
 // The few-token GEMM addresses codes and weights with 32-bit byte offsets (its tokens may be the last of many).

@@ -2,6 +2,7 @@
 import copy
 import pickle
 
+import pytest
 import torch
 
 import paper_2605_27003_amd as svdq
@@ -111,3 +112,15 @@ def test_stream_without_torchs_private_functions(monkeypatch):
     monkeypatch.setattr(torch, "_C", object())
     monkeypatch.setattr(torch.cuda, "current_stream", Stream)
     assert binding._raw_stream() == 1234
+
+
+@pytest.mark.parametrize("M,K,N", [(161, 2112, 5504), (175, 4672, 5632), (320, 5120, 5120), (384, 2048, 4096), (500, 2048, 4096)])
+def test_few_tokens_on_canonical_weights_need_no_staging(M, K, N):
+    """Up to 480 tiles of 64 x 64 the weights are expanded in registers: such layers have no memory in common, whatever streams
+    they run on, and a caller of the C functions passes none."""
+    f, lib = binding._FORMATS["e3m2"], binding.load_library()
+    at = lambda format, packed: lib.svdq_layer_staging_bytes(binding.ctypes.byref(binding._Layer(
+        format, N, K, 0, 256, None, None, None, 256 if packed else None, None if packed else 256, None if packed else 256)), M)
+    few = -(-M // 64) * (N // 64) <= 480
+    assert (at(f, False) == 0) == few and at(f, True) == 0
+    assert at(binding._FORMATS["nibble"], True) > 0          # forward() of nibbles runs as fields there
