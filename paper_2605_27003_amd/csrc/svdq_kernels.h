@@ -110,12 +110,37 @@ hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scale
 //   up to a 16-token tile per CU, K = 1536: M = 32 7.2 against 9.8 (10.4, 10.2), MXFP4 6.6 against 9.4 (9.1, 10.5);
 //   32-token tiles, M = 256, N = 2048: K = 1024 8.0 against 9.9 (10.8, 11.4), 2048 12.3 against 11.8; MXFP4 1024 6.6 against 9.4
 //   (8.8, 10.6), 2048 9.3 against 9.5 (12.7, 11.7).
+// N up to 16384 with few tokens: 0.68 to 0.98 of the two launches.  More than 16 tokens with K <= 512 take as long either way (6.4 to
+// 6.9 us, what the launch takes the host): 32-token tiles, whose codes need not go through LDS.
 enum { FUSED_NONE = 0, FUSED_SPREAD = 1, FUSED_TILES = 2 };
+// LDS of a block, byte offsets: partial tiles; with a low-rank term partial h's and h, rows FUSED_H_ROW floats apart; smoothing factors,
+// halves of groups FUSED_IL_ROW floats apart; SPREAD (1 << rs tokens) the values where they are projected, and 16 + 8 + 4 bytes of codes
+// and scale, per token and half group: planes of falling alignment, since with one token they are 64, 16, 8 and 4 K / 32 bytes.
+constexpr int FUSED_IL_ROW = 36, FUSED_H_ROW = 36;
+constexpr uint32_t LDS_OF_A_CU = 160 * 1024;
+struct FusedLds {
+    uint32_t hpart, h, il, x, lo, hi, scale, end;
+};
+__host__ __device__ constexpr FusedLds fused_lds(int ni, int K, bool lowrank, bool spread, int rs) {
+    FusedLds a{};
+    const uint32_t halves = (uint32_t)K / 32;
+    a.hpart = SMALL_SLICES * ni * 4096;
+    a.h = a.hpart + (lowrank ? SMALL_SLICES * 32 * 32 * 4 : 0);
+    a.il = a.h + (lowrank ? 32 * FUSED_H_ROW * 4 : 0);
+    a.x = a.il + halves * FUSED_IL_ROW * 4;
+    a.lo = a.x + (spread && lowrank ? (halves * 64) << rs : 0);
+    a.hi = a.lo + (spread ? (halves * 16) << rs : 0);
+    a.scale = a.hi + (spread ? (halves * 8) << rs : 0);
+    a.end = a.scale + (spread ? (halves * 4) << rs : 0);
+    return a;
+}
+inline int fused_spread(int64_t M) { return M <= 1 ? 0 : M <= 2 ? 1 : M <= 4 ? 2 : M <= 8 ? 3 : 4; }     // rs
 inline int small_fused(int64_t M, int N, int K, int r, bool mxfp4) {
     const int64_t b16 = ((M + 15) / 16) * (N / 32), b32 = ((M + 31) / 32) * (N / 32);
     const bool few = M <= 8;
+    // (MXFP4 with a term, 16 tokens and K = 1792: 160 640 bytes of LDS)
     if (b16 <= 256 && K <= (few ? (r ? (mxfp4 ? 2304 : 1792) : (mxfp4 ? 4352 : 3328)) : (r ? (mxfp4 ? 1792 : 1408) : (mxfp4 ? 3328 : 2560))) &&
-        (few || M <= 16 || K > 512))
+        (few || M <= 16 || K > 512) && fused_lds(1, K, r != 0, true, fused_spread(M)).end <= LDS_OF_A_CU)
         return FUSED_SPREAD;
     return b32 <= 512 && K <= (r ? (mxfp4 ? 1664 : 1216) : (mxfp4 ? 2048 : 1664)) ? FUSED_TILES : FUSED_NONE;
 }

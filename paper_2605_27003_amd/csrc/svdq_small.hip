@@ -399,14 +399,6 @@ struct FusedArgs {
 static_assert(sizeof(FusedArgs) <= 112, "arguments of a cheap launch");
 // wait for this wave's LDS traffic, then for the other waves: loads from global memory stay in flight
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-constexpr int IL_ROW = 36;                                 // floats between the smoothing factors of two halves of groups in LDS
-constexpr int H_ROW = 36;                                  // and between rows of h
-// LDS of a block, in bytes: partial tiles, partial h's and h, smoothing factors; SPREAD: 16 + 8 + 4 bytes per token and half
-// group, and its 32 values where they are projected
-constexpr uint32_t fused_h_bytes() { return WV * 32 * 32 * 4 + 32 * H_ROW * 4; }
-inline uint32_t fused_lds(int ni, int K, int r, bool spread, int rs) {
-    return (uint32_t)(WV * ni * 4096 + (r ? fused_h_bytes() : 0) + K / 32 * IL_ROW * 4 + (spread ? (K / 32 * (r ? 92 : 28)) << rs : 0));
-}
 
 template <int SRC, int NI, bool SPREAD>
 __global__ __launch_bounds__(64 * WV, 2)
@@ -415,21 +407,23 @@ void fused_layer_kernel(const FusedArgs a) {
     constexpr int Q = NI * 4;                              // quads of the tile
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     float4 (*const part)[Q][64] = reinterpret_cast<float4 (*)[Q][64]>(smem);
-    float* const hpart = reinterpret_cast<float*>(smem + WV * Q * 1024);             // [WV][32][32]
-    float* const hsum = hpart + WV * 32 * 32;                                        // [32][H_ROW]
-    float* const il_s = a.r ? hsum + 32 * H_ROW : hpart;
+    const int rs = SPREAD ? a.rs : 5, rmask = (1 << rs) - 1;
+    const FusedLds lds = fused_lds(NI, a.K, a.r > 0, SPREAD, rs);
+    float* const hpart = reinterpret_cast<float*>(smem + lds.hpart);                 // [WV][32][32]
+    float* const hsum = reinterpret_cast<float*>(smem + lds.h);                      // [32][FUSED_H_ROW]
+    float* const il_s = reinterpret_cast<float*>(smem + lds.il);
     const int N = a.nblocks * 32, K = a.K;
     const int64_t M = a.M;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, kh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = (int)blockIdx.x * 32 * NI, ng = K >> 6;
-    const int rs = SPREAD ? a.rs : 5, rmask = (1 << rs) - 1, trow = l32 & rmask;     // this lane's token of the tile
+    const int trow = l32 & rmask;                          // this lane's token of the tile
     const int64_t m0 = (int64_t)blockIdx.y << rs, row = m0 + trow;
-    uint8_t* const clo = reinterpret_cast<uint8_t*>(il_s + (K >> 5) * IL_ROW);     // SPREAD: [2 g + kh][token] x 16, x 8, x 4 bytes
-    uint8_t* const chi = clo + (((K >> 5) * 16) << rs);
-    uint8_t* const csc = chi + (((K >> 5) * 8) << rs);
+    uint8_t* const clo = smem + lds.lo;                    // SPREAD: [2 g + kh][token] x 16, x 8, x 4 bytes
+    uint8_t* const chi = smem + lds.hi;
+    uint8_t* const csc = smem + lds.scale;
     // its piece s at place s ^ (token / 4) % 4: the 16 tokens of a read stand in different banks
-    uint8_t* const cxv = csc + (((K >> 5) * 4) << rs);
+    uint8_t* const cxv = smem + lds.x;
     auto x_place = [&](const int g, const int s) { return reinterpret_cast<uint4*>(cxv + (((2 * g + kh) << rs) + trow) * 64) + (s ^ ((trow >> 2) & 3)); };
     const bool first = blockIdx.x == 0;
     const Buffers B = buffers_of<SRC>(nullptr, nullptr, a.w0, (const uint8_t*)a.scales, N, K);
@@ -439,14 +433,14 @@ void fused_layer_kernel(const FusedArgs a) {
         for (int s = 0; s < 4; ++s) x[s] = reinterpret_cast<const uint4*>(xrow + g * 64)[s];
     };
 
-    for (int i = tid * 4; i < K; i += 256 * WV) *reinterpret_cast<float4*>(il_s + (i >> 5) * IL_ROW + (i & 31)) = *reinterpret_cast<const float4*>(a.inv_lambda + i);
+    for (int i = tid * 4; i < K; i += 256 * WV) *reinterpret_cast<float4*>(il_s + (i >> 5) * FUSED_IL_ROW + (i & 31)) = *reinterpret_cast<const float4*>(a.inv_lambda + i);
     // quantise this lane's 32 values of group g into fields (MXFP4: nibbles) and scale, and into the layer's buffers
     struct Coded {
         LaneCodes<true> c;
         uint32_t s;                                        // scale pieces; MXFP4: the E8M0 byte
     };
     auto quantise = [&](const uint4 (&x)[4], const int g, const bool writes) {
-        const float* il = il_s + (2 * g + kh) * IL_ROW;
+        const float* il = il_s + (2 * g + kh) * FUSED_IL_ROW;
         Coded o;
         if constexpr (MX) {
             quantize_block_mx(x, il, a.rho, o.c.lo, o.s);
@@ -614,7 +608,7 @@ void fused_layer_kernel(const FusedArgs a) {
             return float2{(p0.x + p1.x) + (p2.x + p3.x), (p0.y + p1.y) + (p2.y + p3.y)};
         };
         const float2 s0 = sum4(0), s1 = sum4(4), t{s0.x + s1.x, s0.y + s1.y};
-        *reinterpret_cast<float2*>(hsum + hr * H_ROW + hj) = t;
+        *reinterpret_cast<float2*>(hsum + hr * FUSED_H_ROW + hj) = t;
         if (first && hr <= rmask && hj < a.r && m0 + hr < M) *reinterpret_cast<float2*>(a.h + (m0 + hr) * a.r + hj) = t;
         lds_barrier();
     }
@@ -623,7 +617,7 @@ void fused_layer_kernel(const FusedArgs a) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
         if (16 * ks < a.r) {
-            const float* hp = hsum + l32 * H_ROW + 16 * ks + 8 * kh;
+            const float* hp = hsum + l32 * FUSED_H_ROW + 16 * ks + 8 * kh;
             uint32_t hi[4], lo[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -653,12 +647,10 @@ hipError_t launch_fused_src(FusedArgs a, hipStream_t stream) {
     const unsigned M = a.M;
     auto go = [&](auto kern, unsigned ni, bool spread, int rs) {
         a.rs = (uint8_t)rs;
-        hipLaunchKernelGGL(kern, dim3(a.nblocks / ni, (M + (1u << rs) - 1) >> rs), dim3(64 * WV), fused_lds(ni, a.K, a.r, spread, rs), stream, a);
+        hipLaunchKernelGGL(kern, dim3(a.nblocks / ni, (M + (1u << rs) - 1) >> rs), dim3(64 * WV), fused_lds((int)ni, a.K, a.r != 0, spread, rs).end, stream, a);
     };
     if (small_fused(M, a.nblocks * 32, a.K, a.r, SRC == SMALL_MXFP4) == FUSED_SPREAD) {
-        int rs = 0;
-        while (rs < 4 && (1u << rs) < M) ++rs;
-        go(fused_layer_kernel<SRC, 1, true>, 1, true, rs);
+        go(fused_layer_kernel<SRC, 1, true>, 1, true, fused_spread(M));
     } else if ((M + 31) / 32 * a.nblocks <= 256) {
         go(fused_layer_kernel<SRC, 1, false>, 1, false, 5);
     } else {

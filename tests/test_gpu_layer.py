@@ -85,14 +85,21 @@ def test_layer_forward(svdq, oracle, container, M, K, N, r, gelu):
     assert rel_fro(synth.bf16_bits_to_f32(host_bits(y2)).astype(np.float64), synth.bf16_bits_to_f32(host_bits(y1)).astype(np.float64)) <= 2e-3
 
 
-@pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble", "mxfp4"])
-@pytest.mark.parametrize("M,K,N,r,gelu,ldx", [
+# M, K, N, r, gelu, ldx; tests/test_small_plan.py asks the plan whether they are one launch
+ONE_LAUNCH = [
     (1, 64, 128, 32, False, 64), (1, 1792, 256, 16, True, 1792), (1, 3328, 128, 0, False, 3400),    # one token; fewer groups than waves, the longest K
     (2, 576, 128, 16, False, 584), (3, 1344, 384, 32, True, 1344), (5, 1600, 128, 0, False, 1600),  # odd group counts; a tile of 2, 4, 8
     (16, 1408, 256, 32, False, 1408), (17, 832, 128, 16, False, 840), (500, 576, 128, 0, True, 576),   # 16-token tiles: full, one over, ragged
     (33, 512, 128, 32, False, 512), (1000, 704, 256, 16, False, 704),             # 32-token tiles of 32 channels, ragged
     (1025, 1216, 384, 32, True, 1224), (1023, 448, 512, 0, False, 448),           # and of 64
-])
+]
+# where MXFP4 goes further: the longest K of every kind, and 160 640 bytes of LDS (16 tokens)
+ONE_LAUNCH_MX = [(9, 1792, 256, 32, False, 1792), (16, 1792, 256, 16, True, 1800), (8, 2304, 128, 32, False, 2304), (1, 4352, 128, 0, False, 4352),
+                 (16, 3328, 128, 0, True, 3328), (40, 1664, 1024, 32, False, 1664)]
+
+
+@pytest.mark.parametrize("container,M,K,N,r,gelu,ldx", [(c, *s) for s in ONE_LAUNCH for c in ("e3m2", "e3m2 packed", "nibble", "mxfp4")] +
+                         [("mxfp4", *s) for s in ONE_LAUNCH_MX])
 def test_layer_in_one_launch(svdq, container, M, K, N, r, gelu, ldx):
     """Few tokens and a short K: forward() is one kernel.  Codes and scales left behind are those of the quantise pass, bit for bit,
     h is its sum in another order at most (32-bit sums of K products: 1e-6), and y that of the GEMM on them (the bar of the layer)."""
