@@ -142,7 +142,9 @@ inline int small_fused(int64_t M, int N, int K, int r, bool mxfp4) {
     if (b16 <= 256 && K <= (few ? (r ? (mxfp4 ? 2304 : 1792) : (mxfp4 ? 4352 : 3328)) : (r ? (mxfp4 ? 1792 : 1408) : (mxfp4 ? 3328 : 2560))) &&
         (few || M <= 16 || K > 512) && fused_lds(1, K, r != 0, true, fused_spread(M)).end <= LDS_OF_A_CU)
         return FUSED_SPREAD;
-    return b32 <= 512 && K <= (r ? (mxfp4 ? 1664 : 1216) : (mxfp4 ? 2048 : 1664)) ? FUSED_TILES : FUSED_NONE;
+    // MXFP4 without a term: from K = 2048 on the quantise pass has four slices and catches up with more tokens (M = 200, N = 2048 10.4
+    // against 9.5 here, M = 500, N = 1024 9.8 against 9.9, M = 1000, N = 512 9.7 against 11.4)
+    return b32 <= 512 && K <= (r ? (mxfp4 ? 1664 : 1216) : mxfp4 ? (M <= 448 ? 2048 : 1984) : 1664) ? FUSED_TILES : FUSED_NONE;
 }
 hipError_t launch_fused_layer(int source, const void* x, int64_t ldx, const float* inv_lambda, float rho, bool gelu, const void* l1p,
                               uint8_t* codes, void* scales, float* h, const void* w0, const void* w1,

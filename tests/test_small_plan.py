@@ -67,3 +67,8 @@ def test_layers_of_the_gpu_tests_are_one_launch(plan):
         assert all(kinds), list(zip(shapes, kinds))
         if not mx:
             assert kinds == [1] * 9 + [2] * 4
+
+
+def test_mxfp4_without_a_term_at_k_2048(plan):
+    """Two launches there for many tokens (M = 1000, N = 512: 9.7 against 11.4 us)."""
+    assert [row[1] for row in plan([(1000, K, 512, 0, True) for K in (1984, 2048)] + [(M, 2048, 1024, 0, True) for M in (400, 500)])[0]] == [2, 0, 2, 0]
