@@ -861,8 +861,12 @@ void launch_rank_updates(const RankUpdates& us, const Lookahead& la, hipStream_t
 // where the lengths are even the longest is taken.  K = N, batches of 2, 3 and 4 of the inverse, ms: 2048 3.18, 3.15, 3.32, 3072 5.55,
 // 5.46, 5.71, 3584 6.97, 7.38, 7.14, 4096 9.77, 9.31, 9.82, 4480 11.6, 11.2, 12.1, 5120 15.9, 15.3, 15.0.
 // What is left of the visit shrinks from panel to panel: 2, 3, 4: K = N = 2048 3.11, 3.12, 3.32, 4096 9.79, 9.59, 9.82, 5120 15.34, 14.92, 15.02.
-constexpr int VISIT_BATCH = 3;
+// From some 6000 indices on the passes over memory weigh most, and both take four.  N = 5120, inverse and visit 3 and 3, 4 and 3, 4 and 4:
+// 6144 22.4, 23.1, 23.0, 6656 27.7, 27.1, 26.9, 8192 46.2, 44.7, 44.0, 9344 65.8, 63.3, 62.6, 13824 177, 170, 167.
+constexpr int LONG_K = 6144;
+inline int visit_batch(int K) { return K > LONG_K ? MAX_BATCH : 3; }
 int inverse_batch(int K, int cus) {
+    if (K > LONG_K) return MAX_BATCH;
     int best = 2;
     double least = 1e30;
     for (int n = 2; n <= MAX_BATCH; ++n) {
@@ -983,7 +987,7 @@ hipError_t launch_gptq_quantize(const float* R, const double* H, double damp, in
         launch_rank_updates(us, la, stream);
         cur ^= 1;
     }
-    span = VISIT_BATCH;
+    span = visit_batch(K);
     for (int b = 0; b < np; ++b) {                     // the weights, one panel (= one 64-group) at a time
         const int i0 = b * PB, t = b + 1, i1 = i0 + PB, rest = K - i1, batch = b / span * span;
         hipLaunchKernelGGL(visit_panel_kernel, dim3(2 * (rest / PVECS) + (N + PVECS - 1) / PVECS), dim3(256), 0, stream,

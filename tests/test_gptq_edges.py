@@ -101,7 +101,7 @@ def test_gptq_batches_of_panels(svdq, oracle, panels, N, classes, channels):
         assert np.array_equal(qw[:, k[::2] // 2], oq)
 
 
-@pytest.mark.parametrize("panels,N,classes", [(56, 70, 7), (76, 33, 19)])
+@pytest.mark.parametrize("panels,N,classes", [(56, 70, 7), (76, 33, 19), (97, 40, 13)])
 def test_gptq_batches_of_two_and_four(svdq, oracle, panels, N, classes):
-    """The sizes at which a batch of the inverse is two panels and four (three in the cases above)."""
+    """The sizes at which a batch of the inverse is two panels and four (three in the cases above), and the visit's four too."""
     test_gptq_batches_of_panels(svdq, oracle, panels, N, classes, None)
