@@ -63,21 +63,23 @@ inline int e3m2_mid_groups(const E3m2Mid& m, int K) { return (K / 64 + m.teams -
 // Which of them a launch of all tokens takes, or -1: the others.  split: K may be split between teams (a whole layer).
 // Costs fitted to 95 shapes of M = 96 .. 4100, K = 1024 .. 13824 with a term (2 to 4 %); without one a tile's start is 2 us shorter.
 // Only where the tiles are one for every CU at most: further rounds take long.  The others are estimated as above, except that two teams of
-// 128 x 128 tiles on a chip that they fill take 9.3 + 3.1 k, and with a term their h is summed ahead of them (1.5 us) for up to 4096 tokens.  Layers, us:
+// 128 x 128 tiles on a chip that they fill take 9.3 + 3.1 k, and ahead of the others, which do not add up h's slices themselves, that
+// takes a launch (1.5 us) for up to 4096 tokens.  Layers, us:
 // M = 2048, K = N = 5120 94.2 -> 84.3, M = 1500, N = 3072 59.5 -> 50.8, M = 1024, K = 2048, N = 5120 36.3 -> 32.6, M = 512 38.8 -> 37.6.
 // With less than 1.5 % to gain the others are taken: M = 1500, K = 1024, N = 2048 20.8 against 22.5.
 inline int e3m2_mid_shape(int64_t M, int N, int K, bool split, int walkers, bool lowrank) {
     if (walkers != 8 * CUS_PER_XCD) return -1;
     const int64_t rows = e3m2_walk_rows(M, N, K, split, walkers, lowrank);
+    const bool two_teams = split && rows == 0 && K >= 2048 && busiest_xcd((int)((M + 127) / 128), N / 128) <= CUS_PER_XCD;
     double least = 0.0;
     if (rows) {
         least = e3m2_walk_cost((rows + 255) / 256 * (N / 256), K, walkers, lowrank) + (rows < M ? 2.5 + e3m2_tiles_cost(M - rows, N, K, split, lowrank) : 0.0);
-    } else if (split && K >= 2048 && busiest_xcd((int)((M + 127) / 128), N / 128) <= CUS_PER_XCD) {
+    } else if (two_teams) {
         least = (lowrank ? 9.3 : 7.3) + 3.1 * (K / 1024.0);
     } else {
         least = e3m2_tiles_cost(M, N, K, split, lowrank);
     }
-    if (!(split && rows == 0 && K >= 2048) && split && lowrank && M <= 4096 && K >= 1024) least += 1.5;
+    if (!two_teams && split && lowrank && M <= 4096 && K >= 1024) least += 1.5;
     least *= 0.985;
     int best = -1;
     for (int i = 0; i < 4; ++i) {

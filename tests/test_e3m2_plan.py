@@ -125,6 +125,11 @@ def test_middling_tokens_near_the_fastest(plan):
         assert took <= 1.04 * min(*mids, others), (M, N, K, out[2])
 
 
+def test_tiles_of_one_team_have_h_summed_ahead(plan):
+    """K >= 2048, but more than a tile for every CU: their launch for h's slices counts (packed, M = 833, K = 11328: 154 -> 147 us)."""
+    assert [out[2] for out in plan([(785, 12032, 9984, 16), (833, 12288, 11328, 32), (833, 12032, 13568, 16)], whole=True)] == [0, 0, 0]
+
+
 def test_middling_tiles_are_what_the_kernel_takes(plan):
     """A tile for every CU at most, K loops as long as the rings; without teams only the tile that does not split K.  And the
     shapes of tests/test_gpu_layer.py take the tiles that they are there for."""
