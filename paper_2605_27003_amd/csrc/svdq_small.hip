@@ -303,6 +303,7 @@ void small_gemm_kernel(const SmallArgs a) {
     auto step = [&](const int d) __attribute__((always_inline)) {
         wc[(d + DW - 1) % DW].load(a, B, clamp(s + d + DW - 1), n0 >> 5, off);
         xt[(d + 1) & 1].load(a, B, clamp(s + d + 1), off);
+        if constexpr (SRC == SMALL_E3M2_PACKED && NI * MT == 1) __builtin_amdgcn_sched_barrier(0);   // left to itself the compiler requests them behind the products
         multiply(xt[d & 1], wc[d % DW], y, kh);
         __builtin_amdgcn_sched_barrier(0);                // steps interleaved would need registers for several
     };
