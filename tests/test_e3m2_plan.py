@@ -59,7 +59,8 @@ int main(int n, char** v) {
             const svdq::E3m2Mid& m = svdq::E3M2_MID[mid];
             fits = svdq::e3m2_mid_groups(m, K) >= m.slots && svdq::busiest_xcd((int)((M + m.bm - 1) / m.bm), (N + m.bn - 1) / m.bn) <= 32;
         }
-        printf("%ld %d %d %d %d\\n", rows, bad + (rows && most > (mt * nt + 7) / 8), mid, alone, fits);
+        const int teams = K >= 2048 && svdq::busiest_xcd((int)((M + 127) / 128), N / 128) <= 32;          // of the 128 x 128 kernel
+        printf("%ld %d %d %d %d %d\\n", rows, bad + (rows && most > (mt * nt + 7) / 8), mid, alone, fits, teams);
     }
 }
 """
@@ -97,14 +98,18 @@ def test_split_is_what_the_kernels_take(plan):
             assert rows == 0
 
 
-def test_shapes_of_the_gpu_tests_are_walked(plan):
-    """The shapes of test_walked_tiles (tests/test_gpu_e3m2.py): all tokens on 256 x 256 tiles, one with the last split off; and
-    of test_walked_layers (tests/test_gpu_layer.py)."""
-    shapes = [(65537, 256, 320, 32), (65279, 256, 384, 16), (65281, 256, 448, 0), (16001, 1024, 512, 32), (9215, 1792, 576, 0),
-              (3072, 5120, 640, 32), (32700, 512, 1024, 16), (3300, 5120, 5120, 32)]
-    assert [rows for rows, _ in plan(shapes)] == [s[0] for s in shapes[:-1]] + [3072]
-    layers = [(3300, 5120, 5120, 32), (3300, 5120, 5120, 0), (1216, 13824, 2112, 32), (5376, 3072, 2112, 16)]
-    assert [rows for rows, _ in plan(layers)] == [3072, 3072, 1024, 5376]
+def test_shapes_of_the_gpu_tests(plan):
+    """Those of test_walked_tiles (tests/test_gpu_e3m2.py): all tokens on 256 x 256 tiles, one with the last split off, or one tile for
+    every CU; of test_walked_layers (tests/test_gpu_layer.py); and of the layers behind a sliced quantise pass, on 128 x 128 tiles."""
+    from tests.test_gpu_e3m2 import ONE_EACH, WALKED
+    from tests.test_gpu_layer import SLICED
+    walked = plan([w[:4] for w in WALKED], whole=True)
+    assert [out[0] for out in walked] == [w[0] for w in WALKED[:-1]] + [3072] and all(out[3] == -1 for out in walked)
+    assert [out[3] for out in plan([w[:4] for w in ONE_EACH], whole=True)] == [0] * len(ONE_EACH)
+    layers = plan([(3300, 5120, 5120, 32), (3300, 5120, 5120, 0), (1216, 13824, 2112, 32), (5376, 3072, 2112, 16)], whole=True)
+    assert [out[0] for out in layers] == [3072, 3072, 1024, 5376] and all(out[2] == -1 for out in layers)
+    sliced = plan([(M, N, K, r) for M, K, N, r, _, _ in SLICED], whole=True)
+    assert all(out[0] == 0 and out[2] == -1 for out in sliced) and [out[5] for out in sliced] == [int(s[5]) for s in SLICED]
 
 
 # M, N, K, layers with a low-rank term, us on the tiles of the entries of E3M2_MID and on the others

@@ -256,9 +256,14 @@ def test_layers_with_resident_4bit_weights_share_one_staging_buffer(svdq, oracle
 # loops from as long as the ring (320) upwards with every position of the ring at a tile's end, both ranks and none, with
 # and without bias.  All kernels of the layer keep one order of operations, so bf16 out is the rounding of the binary32
 # that the 128 x 128 kernel writes, bit for bit (not-a-number where that is).
-@pytest.mark.parametrize("M,N,K,r,with_bias", [
-    (65537, 256, 320, 32, True), (65279, 256, 384, 16, False), (65281, 256, 448, 0, True), (16001, 1024, 512, 32, False),
-    (9215, 1792, 576, 0, False), (3072, 5120, 640, 32, True), (32700, 512, 1024, 16, True), (3300, 5120, 5120, 32, True)])
+# The same of one 256 x 192 tile for every CU (ONE_EACH), whole in N and standing over it, K from the ring's length on.
+WALKED = [(65537, 256, 320, 32, True), (65279, 256, 384, 16, False), (65281, 256, 448, 0, True), (16001, 1024, 512, 32, False),
+          (9215, 1792, 576, 0, False), (3072, 5120, 640, 32, True), (32700, 512, 1024, 16, True), (3300, 5120, 5120, 32, True)]
+ONE_EACH = [(1500, 6784, 320, 16, False), (1025, 7296, 320, 0, True), (1793, 4480, 384, 0, False), (2047, 4480, 320, 32, True),
+            (1500, 5504, 1088, 32, True), (1793, 4480, 2112, 16, False)]
+
+
+@pytest.mark.parametrize("M,N,K,r,with_bias", WALKED + ONE_EACH)
 def test_walked_tiles(svdq, M, N, K, r, with_bias):
     g = torch.Generator(device="cuda").manual_seed(M + K)
     x = torch.randn((M, K), generator=g, device="cuda", dtype=torch.bfloat16)

@@ -32,13 +32,17 @@ SHAPES = [  # M, K, N, r, gelu
     (4096, 64, 128, 16, False), (4097, 64, 128, 16, False),     # last of the 32 x 32 tiles and the next
     (15360, 64, 128, 0, False), (15361, 64, 128, 32, False),
     (8192, 64, 128, 16, False), (8193, 64, 128, 16, False),     # int4: last of the 64 x 64 tiles with few weights and the next
-    (448, 2048, 4096, 32, False), (449, 2048, 4096, 16, False),   # and with many
+    (448, 2048, 4096, 32, False), (449, 2048, 4096, 16, False),   # and with many: canonical weights
+    (160, 2112, 6144, 0, False), (161, 2112, 6144, 32, False), (170, 2112, 6272, 16, True),     # E3M2 fields: the last, the next, and more channels
+    (150, 5120, 5120, 32, False), (130, 2112, 9728, 16, False),   # 64 x 64 tiles in all forms, ten and five steps a wave (MXFP4: the first)
+    (16, 1408, 256, 32, False), (1000, 704, 256, 16, True),     # one launch: 16-token tiles, 32-token tiles
+    (1916, 384, 4992, 32, False), (1300, 1088, 3072, 16, False), (206, 2112, 4992, 16, False),   # E3M2: one tile for every CU, K whole, in 2 and in 8
     (10240, 64, 128, 32, False), (10241, 64, 128, 16, False),   # MXFP4: last of the 32 x 64 tiles and the next
     (1025, 2112, 2048, 32, False),                # E3M2: K in halves, odd group count; MXFP4: 128 x 128 tiles
     (2049, 192, 4096, 16, True),
     (2049, 1088, 1408, 32, False),                # MXFP4: the last token in a launch of its own on the few-token kernel,
     (6401, 576, 2560, 16, True),                  # the others on 128 x 128 tiles or walked
-    (2305, 3648, 640, 32, False),                 # MXFP4: six uneven slices of K, two blocks per CU in the quantise pass
+    (2305, 3648, 640, 32, False),                 # MXFP4: six uneven slices of K, two blocks per CU in the quantise pass; E3M2: in 4
 ]
 
 
@@ -156,14 +160,18 @@ def test_layer_on_its_own_output(svdq, container, M, K, r):
     assert rel_fro(y.double().cpu().numpy(), want.double().cpu().numpy()) <= 2e-3
 
 
+# M, K, N, r, slices of K in the quantise pass, two teams of waves (tests/test_e3m2_plan.py asks the plan)
+SLICED = [
+    (500, 5120, 5120, 32, 8, True), (513, 5120, 5120, 16, 8, True),   # two teams, eight slices; a last tile of one token
+    (513, 2624, 3200, 32, 4, True),                                   # odd group count, four slices
+    (2048, 2048, 2048, 16, 4, True), (2049, 2048, 2048, 16, 2, False),   # a tile on every CU, the last of two teams; one team, slices summed ahead
+    (801, 1088, 2944, 32, 2, False),                                  # K < 2048: one team
+]
+
+
 @pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble"])
-@pytest.mark.parametrize("M,K,N,r", [
-    (500, 5120, 5120, 32), (513, 5120, 5120, 16),       # two teams, eight slices; a last tile of one token
-    (545, 2112, 2048, 32),                              # odd group count, four slices
-    (2048, 2048, 2048, 16), (2049, 2048, 2048, 16),     # a tile on every CU, the last of two teams; one team, slices summed ahead
-    (2100, 1024, 512, 32),                              # K < 2048: one team
-])
-def test_tiles_behind_a_sliced_quantise_pass(svdq, container, M, K, N, r):
+@pytest.mark.parametrize("M,K,N,r,slices,teams", SLICED)
+def test_tiles_behind_a_sliced_quantise_pass(svdq, container, M, K, N, r, slices, teams):
     """More tokens than the few-token path takes: two teams' blocks sum the slices of h.  The h left behind is whole (the bar
     of the quantise pass alone), and the GEMM on it, the same kernel on one h, gives the same bits."""
     x, _ = synth.make_x(M + K, M, K, outlier_count=3, outlier_scale=30.0)
@@ -172,7 +180,9 @@ def test_tiles_behind_a_sliced_quantise_pass(svdq, container, M, K, N, r):
     lin = svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1), dev(L.L2), dev(L.qw), dev(L.sw), dev(L.bias),
                           container=container.split()[0], resident="packed" if "packed" in container else "w4")
     y = lin.forward(dev(x), 0.8).clone()
-    qx, sx, h, _ = lin.buffers(M, y.device)
+    work = lin._workspace(M, y.device, lin._descriptor(r))
+    assert work.scratch.numel() == slices * M * r * 4
+    qx, sx, h, _ = work.public
     want = (dev(x).view(torch.bfloat16).double() * dev(L.inv_lambda).double()) @ dev(L.L1).view(torch.bfloat16).double()
     assert rel_fro(h.double().cpu().numpy(), want.cpu().numpy()) <= 3e-5
     again = lin.gemm(qx, sx, h)
@@ -211,7 +221,7 @@ def test_walked_layers(svdq, container, M, K, N, r, walked):
 
 # M, K, N, r and the entry of E3M2_MID that takes them (tests/test_e3m2_plan.py asks the plan)
 MIDDLING = [
-    (1916, 384, 4992, 32, 0), (2047, 448, 5120, 0, 0),       # 256 x 192: the shortest K but one, whole channel tiles; one that stands over N
+    (1500, 320, 6784, 16, 0), (1916, 384, 4992, 32, 0), (2047, 448, 5120, 0, 0),   # 256 x 192: K as long as the ring, whole channel tiles; one that stands over N
     (1300, 1088, 3072, 16, 1), (1916, 1088, 2176, 0, 1),     # 128 x 192, two teams of 9 and 8 groups
     (1025, 1600, 1280, 32, 2), (2305, 3648, 640, 32, 2),     # 128 x 96, four teams of 7, 6, 6, 6 and of 15, 14, 14, 14; a last tile of one token
     (1916, 1088, 768, 32, 3), (2100, 1216, 512, 0, 3),       # 64 x 96, eight teams, one and three of them with a group more
@@ -227,7 +237,8 @@ def test_layers_of_middling_tokens(svdq, container, M, K, N, r, shape):
     x, _ = synth.make_x(M + K, M, K, outlier_count=3, outlier_scale=30.0)
     cm = np.maximum(np.abs(synth.bf16_bits_to_f32(x)).max(axis=0), 1e-3).astype(np.float32)
     L = synth.make_layer(M + K, K, N, r, cm)
-    make = lambda c: svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1) if r else None, dev(L.L2) if r else None, dev(L.qw), dev(L.sw), dev(L.bias),
+    bias = dev(L.bias) if r else None
+    make = lambda c: svdq.W4A4Linear(dev(L.inv_lambda), dev(L.L1) if r else None, dev(L.L2) if r else None, dev(L.qw), dev(L.sw), bias,
                                      container=c.split()[0], resident="packed" if "packed" in c else "w4")
     lin, ref = make(container), make("e3m2 packed")
     y = lin.forward(dev(x), 0.8).clone()
@@ -240,6 +251,16 @@ def test_layers_of_middling_tokens(svdq, container, M, K, N, r, shape):
     assert (d.norm() / want.norm()).item() <= 2e-3
     ulp = torch.exp2(torch.floor(torch.log2(want.abs().clamp_min(1e-30))) - 7)
     assert bool((d <= torch.maximum(1e-2 * want.pow(2).mean().sqrt(), ulp)).all())
+    # rows of a wider tensor: the same bits, and nothing beside them
+    from paper_2605_27003_amd import binding
+    layer = lin._descriptor(r)
+    work = lin._workspace(M, y.device, layer)
+    staging = lin._staging(work, y.device)
+    room = torch.full((M + 1, N + 8), 3.0, device="cuda", dtype=torch.bfloat16)
+    xd = dev(x)
+    assert binding.load_library().svdq_layer_forward(layer.address, xd.data_ptr(), K, 0.8, 0, M, *work.ptrs, binding._addr(staging),
+                                                     room.data_ptr(), N + 8, binding._raw_stream()) == 0
+    assert torch.equal(room[:M, :N], y) and (room[M] == 3.0).all() and (room[:, N:] == 3.0).all()
 
 
 def test_layer_gemm_last_tokens_beyond_4_gb(svdq):
@@ -328,8 +349,10 @@ def _random_layer(svdq, container, K, N, r, seed=1):
                            resident="packed" if "packed" in container else "w4")
 
 
-# few tokens (32 x 32, 64 x 64); two teams; tile kernels; MXFP4 with a launch for the last token
-FORMS = [(40, 1088, 128, 16), (420, 2112, 4096, 0), (1025, 2112, 2048, 32), (2305, 2048, 6912, 32)]
+# few tokens (one launch, 32 x 32, 64 x 64: in all forms, canonical weights only); two teams; one tile for every CU;
+# tile kernels; MXFP4 with a launch for the last token
+FORMS = [(40, 1088, 128, 16), (40, 2112, 640, 16), (150, 5120, 5120, 0), (420, 2112, 4096, 0), (1025, 2112, 2048, 32), (1300, 1088, 3072, 16),
+         (2305, 2048, 6912, 32)]
 
 
 @pytest.mark.parametrize("container", ["e3m2", "e3m2 packed", "nibble", "mxfp4"])

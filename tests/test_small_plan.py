@@ -72,3 +72,17 @@ def test_layers_of_the_gpu_tests_are_one_launch(plan):
 def test_mxfp4_without_a_term_at_k_2048(plan):
     """Two launches there for many tokens (M = 1000, N = 512: 9.7 against 11.4 us)."""
     assert [row[1] for row in plan([(1000, K, 512, 0, True) for K in (1984, 2048)] + [(M, 2048, 1024, 0, True) for M in (400, 500)])[0]] == [2, 0, 2, 0]
+
+
+def test_shapes_of_the_gpu_tests_on_the_few_token_kernel(plan):
+    """tests/test_gpu_layer.py: the tile (1: 32 x 32, 2: 64 x 64 or MXFP4's 32 x 64, 0: none) with canonical weights or nibble codes, with
+    E3M2 fields, and of MXFP4; two launches each, so that the kernel runs."""
+    from tests.test_gpu_layer import FORMS, SHAPES
+    want = {(1030, 1024, 640, 32): (2, 2, 2), (448, 2048, 4096, 32): (2, 0, 0), (449, 2048, 4096, 16): (0, 0, 0), (160, 2112, 6144, 0): (2, 2, 2),
+            (161, 2112, 6144, 32): (2, 0, 2), (170, 2112, 6272, 16): (2, 2, 2), (150, 5120, 5120, 32): (2, 2, 2), (130, 2112, 9728, 16): (2, 2, 0),
+            (8192, 64, 128, 16): (2, 2, 2), (8193, 64, 128, 16): (0, 0, 2), (10240, 64, 128, 32): (0, 0, 2), (10241, 64, 128, 16): (0, 0, 0),
+            (65, 2112, 384, 16): (1, 1, 1), (40, 2112, 640, 16): (1, 1, 1), (150, 5120, 5120, 0): (2, 2, 2), (420, 2112, 4096, 0): (2, 0, 0)}
+    assert set(want) <= {s[:4] for s in SHAPES} | set(FORMS)
+    int4, mx = (plan([(*s, m) for s in want])[0] for m in (False, True))
+    assert [(a[0], a[2], b[0]) for a, b in zip(int4, mx)] == list(want.values())
+    assert not any(row[1] for row in int4 + mx)
