@@ -125,8 +125,8 @@ __host__ __device__ constexpr FusedLds fused_lds(int ni, int K, bool lowrank, bo
     FusedLds a{};
     const uint32_t halves = (uint32_t)K / 32;
     a.hpart = SMALL_SLICES * ni * 4096;
-    a.h = a.hpart + (lowrank ? SMALL_SLICES * 32 * 32 * 4 : 0);
-    a.il = a.h + (lowrank ? 32 * FUSED_H_ROW * 4 : 0);
+    a.h = a.hpart + SMALL_SLICES * 32 * 32 * 4;
+    a.il = lowrank ? a.h + 32 * FUSED_H_ROW * 4 : a.hpart;
     a.x = a.il + halves * FUSED_IL_ROW * 4;
     a.lo = a.x + (spread && lowrank ? (halves * 64) << rs : 0);
     a.hi = a.lo + (spread ? (halves * 16) << rs : 0);

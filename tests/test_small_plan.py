@@ -31,7 +31,7 @@ int main(int n, char** v) {
                         const FusedLds a = fused_lds(ni, K, r != 0, spread, spread ? fused_spread(M) : 5);
                         most = a.end > most ? a.end : most;
                         askew += a.hpart % 16 || a.h % 16 || a.il % 16 || a.x % 16 || a.lo % 16 || a.hi % 8 || a.scale % 4;
-                        askew += !(a.hpart <= a.h && a.h <= a.il && a.il < a.x && a.x <= a.lo && a.lo <= a.hi && a.hi <= a.scale && a.scale <= a.end);
+                        askew += !((r == 0 ? a.hpart == a.il : a.hpart < a.h && a.h < a.il) && a.il < a.x && a.x <= a.lo && a.lo <= a.hi && a.hi <= a.scale && a.scale <= a.end);
                     }
                 }
     printf("%u %u\\n", most, askew);
