@@ -414,6 +414,7 @@ static int layer_slices(const svdq_layer* L, int64_t M) {
     return (units + slice - 1) / slice;
 }
 
+// Also for layers that are one launch: on their own output they are two.
 size_t svdq_layer_scratch_bytes(const svdq_layer* L, int64_t M) {
     if (layer_check(L, M) != SVDQ_OK || L->r == 0) return 0;
     const int s = layer_slices(L, M);

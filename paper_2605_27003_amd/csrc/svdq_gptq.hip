@@ -10,8 +10,8 @@
 // condition numbers of 1e13 scales differ and at 1e15 codes), and there are no reductions other than max and one
 // sequential sum.  The published implementation factors H^-1 once (Cholesky) and reads the same numbers off the
 // factor; this form trades that for elementwise kernels: K^3 updates for the inverse, K^3 / 3 of H^-1 and K^2 N / 2
-// of the weights during the visit, taken in panels of 64 pivots (below), four at a time, so that the matrices cross HBM
-// once per 256 pivots.
+// of the weights during the visit, taken in panels of 64 pivots (below), two to four at a time, so that the matrices cross
+// HBM once per 128 to 256 pivots.
 #include <climits>
 #include <type_traits>
 
@@ -191,7 +191,7 @@ void prepare_kernel(const float* __restrict__ R, const double* __restrict__ H, c
 //   rank update    everything else receives its updates from the saved columns and rows, in pivot order, on the
 //                  binary64 matrix instruction.  Block 0 meanwhile brings the NEXT panel's diagonal block up to date, takes
 //                  it through its own 64 dependent steps and leaves the next panel's tables: a serial chain of about
-//                  30 us, which no launch is shorter than.
+//                  30 us (32 with the launch's start and end), which no launch is shorter than.
 // Only the strips (rows and columns) of the next panel have to be up to date when a launch ends.  The rest of the matrices
 // receives the updates of a whole batch of two to four panels in one pass over memory, and its blocks are dealt over the
 // launches of the next batch in whole rounds of one block per CU, beside the strips and the chain.  So at any time the
@@ -780,8 +780,8 @@ __device__ __forceinline__ void rank_update_wave(const RankUpdate& u, const int 
 }
 
 // Block 0 looks ahead; the others take blocks of the matrices of `us`, in turn.  Every element of the rest is read and
-// written once per batch of 256 updates, 16 bytes: the matrix unit bounds it (K = 5120: 220 us a batch at its rate, and
-// 420 MB, 70 us at the rate of a copy).  A round of 128 x 256 blocks takes 76 us for its 256 updates.
+// written once per batch of panels, 16 bytes: the matrix unit bounds it (K = 5120, four panels, 256 updates: 220 us a batch at its
+// rate, and 420 MB, 70 us at the rate of a copy).  A round of 128 x 256 blocks takes 19 us for 64 updates, 76 for 256.
 template <bool PAIR>
 __global__ __launch_bounds__(512, 1)
 void rank_update_kernel(const RankUpdates us, const Lookahead la) {
@@ -841,7 +841,8 @@ int quota(int pending, int launches, int fixed, int cus) {
 }
 
 // One block per CU (with the kernel's own 33 KB more than half of its LDS), so that the block that looks ahead has its CU
-// for itself: beside another its dependent steps take 100 us instead of 50, as both want the binary64 unit.
+// for itself: beside another its dependent steps take twice as long, as both want the binary64 unit (100 us instead of 50 when they
+// stood on fewer waves; 30 alone by now).
 constexpr unsigned RANK_UPDATE_LDS = 52 * 1024;
 
 void launch_rank_updates(const RankUpdates& us, const Lookahead& la, hipStream_t stream) {
@@ -856,8 +857,8 @@ void launch_rank_updates(const RankUpdates& us, const Lookahead& la, hipStream_t
 }
 
 // Panels in a batch.  A long one passes over memory less often and fills its rounds better, but a launch waits for the
-// strips, which lack up to two batches: with four panels 38 us where the chain takes 33.  A launch of the inverse takes, us, the chain,
-// or its share of the batch's rounds of 128 x 256 blocks (19 per 64 pivots), or half of that where blocks of half the size fit it;
+// strips, which lack up to two batches: with four panels 38 us where one that waits for the chain takes 32 to 33.  A launch of the inverse
+// takes, us, those 33, or its share of the batch's rounds of 128 x 256 blocks (19 per 64 pivots), or half of that where blocks of half the size fit it;
 // where the lengths are even the longest is taken.  K = N, batches of 2, 3 and 4 of the inverse, ms: 2048 3.18, 3.15, 3.32, 3072 5.55,
 // 5.46, 5.71, 3584 6.97, 7.38, 7.14, 4096 9.77, 9.31, 9.82, 4480 11.6, 11.2, 12.1, 5120 15.9, 15.3, 15.0.
 // What is left of the visit shrinks from panel to panel: 2, 3, 4: K = N = 2048 3.11, 3.12, 3.32, 4096 9.79, 9.59, 9.82, 5120 15.34, 14.92, 15.02.
