@@ -113,25 +113,26 @@ hipError_t launch_small_gemm(int source, const uint8_t* codes, const void* scale
 // N up to 16384 with few tokens: 0.68 to 0.98 of the two launches.  More than 16 tokens with K <= 512 take as long either way (6.4 to
 // 6.9 us, what the launch takes the host): 32-token tiles, whose codes need not go through LDS.
 enum { FUSED_NONE = 0, FUSED_SPREAD = 1, FUSED_TILES = 2 };
-// LDS of a block, byte offsets: partial tiles; with a low-rank term partial h's and h, rows FUSED_H_ROW floats apart; smoothing factors,
-// halves of groups FUSED_IL_ROW floats apart; SPREAD (1 << rs tokens) the values where they are projected, and 16 + 8 + 4 bytes of codes
-// and scale, per token and half group: planes of falling alignment, since with one token they are 64, 16, 8 and 4 K / 32 bytes.
-constexpr int FUSED_IL_ROW = 36, FUSED_H_ROW = 36;
+// LDS of a block, bytes of its planes, one behind the other: partial tiles; with a low-rank term partial h's and h, rows FUSED_H_ROW floats
+// apart; smoothing factors, halves of groups FUSED_IL_ROW floats apart; SPREAD (1 << rs tokens), per token and half group, 16 + 8 + 4 bytes
+// of codes and scale and with a term the values as they are projected, 64 bytes.  The scales' plane is rounded up to 16 bytes: with one token and an
+// odd number of 64-groups it is 8 K / 64, and the values behind it are read 16 bytes at a time.
+constexpr int FUSED_IL_ROW = 36, FUSED_H_ROW = 36, FUSED_HPART = SMALL_SLICES * 32 * 32, FUSED_H = 32 * FUSED_H_ROW;
 constexpr uint32_t LDS_OF_A_CU = 160 * 1024;
 struct FusedLds {
-    uint32_t hpart, h, il, x, lo, hi, scale, end;
+    uint32_t tiles, hpart, h, il, lo, hi, scale, x;
+    __host__ __device__ constexpr uint32_t end() const { return tiles + hpart + h + il + lo + hi + scale + x; }
 };
 __host__ __device__ constexpr FusedLds fused_lds(int ni, int K, bool lowrank, bool spread, int rs) {
-    FusedLds a{};
     const uint32_t halves = (uint32_t)K / 32;
-    a.hpart = SMALL_SLICES * ni * 4096;
-    a.h = a.hpart + SMALL_SLICES * 32 * 32 * 4;
-    a.il = lowrank ? a.h + 32 * FUSED_H_ROW * 4 : a.hpart;
-    a.x = a.il + halves * FUSED_IL_ROW * 4;
-    a.lo = a.x + (spread && lowrank ? (halves * 64) << rs : 0);
-    a.hi = a.lo + (spread ? (halves * 16) << rs : 0);
-    a.scale = a.hi + (spread ? (halves * 8) << rs : 0);
-    a.end = a.scale + (spread ? (halves * 4) << rs : 0);
+    FusedLds a{};
+    a.tiles = SMALL_SLICES * ni * 4096;
+    if (lowrank) a.hpart = FUSED_HPART * 4, a.h = FUSED_H * 4;
+    a.il = halves * FUSED_IL_ROW * 4;
+    if (spread) {
+        a.lo = (halves * 16) << rs, a.hi = (halves * 8) << rs, a.scale = (((halves * 4) << rs) + 15) & ~15u;
+        if (lowrank) a.x = (halves * 64) << rs;
+    }
     return a;
 }
 inline int fused_spread(int64_t M) { return M <= 1 ? 0 : M <= 2 ? 1 : M <= 4 ? 2 : M <= 8 ? 3 : 4; }     // rs
@@ -140,7 +141,7 @@ inline int small_fused(int64_t M, int N, int K, int r, bool mxfp4) {
     const bool few = M <= 8;
     // (MXFP4 with a term, 16 tokens and K = 1792: 160 640 bytes of LDS)
     if (b16 <= 256 && K <= (few ? (r ? (mxfp4 ? 2304 : 1792) : (mxfp4 ? 4352 : 3328)) : (r ? (mxfp4 ? 1792 : 1408) : (mxfp4 ? 3328 : 2560))) &&
-        (few || M <= 16 || K > 512) && fused_lds(1, K, r != 0, true, fused_spread(M)).end <= LDS_OF_A_CU)
+        (few || M <= 16 || K > 512) && fused_lds(1, K, r != 0, true, fused_spread(M)).end() <= LDS_OF_A_CU)
         return FUSED_SPREAD;
     // MXFP4 without a term: from K = 2048 on the quantise pass has four slices and catches up with more tokens (M = 200, N = 2048 10.4
     // against 9.5 here, M = 500, N = 1024 9.8 against 9.9, M = 1000, N = 512 9.7 against 11.4)

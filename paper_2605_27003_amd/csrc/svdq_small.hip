@@ -410,9 +410,11 @@ void fused_layer_kernel(const FusedArgs a) {
     float4 (*const part)[Q][64] = reinterpret_cast<float4 (*)[Q][64]>(smem);
     const int rs = SPREAD ? a.rs : 5, rmask = (1 << rs) - 1;
     const FusedLds lds = fused_lds(NI, a.K, a.r > 0, SPREAD, rs);
-    float* const hpart = reinterpret_cast<float*>(smem + lds.hpart);                 // [WV][32][32]
-    float* const hsum = reinterpret_cast<float*>(smem + lds.h);                      // [32][FUSED_H_ROW]
-    float* const il_s = reinterpret_cast<float*>(smem + lds.il);
+    // the planes, each formed from the one ahead of it and what is constant written as such (M = 16, K = N = 512 5.92 us, otherwise 5.97)
+    constexpr uint32_t TILES = fused_lds(NI, 64, true, SPREAD, 0).tiles;
+    float* const hpart = reinterpret_cast<float*>(smem + TILES);                     // [WV][32][32]
+    float* const hsum = hpart + FUSED_HPART;                                         // [32][FUSED_H_ROW]
+    float* const il_s = a.r ? hsum + FUSED_H : hpart;
     const int N = a.nblocks * 32, K = a.K;
     const int64_t M = a.M;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, kh = lane >> 5;
@@ -420,11 +422,11 @@ void fused_layer_kernel(const FusedArgs a) {
     const int n0 = (int)blockIdx.x * 32 * NI, ng = K >> 6;
     const int trow = l32 & rmask;                          // this lane's token of the tile
     const int64_t m0 = (int64_t)blockIdx.y << rs, row = m0 + trow;
-    uint8_t* const clo = smem + lds.lo;                    // SPREAD: [2 g + kh][token] x 16, x 8, x 4 bytes
-    uint8_t* const chi = smem + lds.hi;
-    uint8_t* const csc = smem + lds.scale;
+    uint8_t* const clo = reinterpret_cast<uint8_t*>(il_s) + lds.il;                // SPREAD: [2 g + kh][token] x 16, x 8, x 4 bytes
+    uint8_t* const chi = clo + lds.lo;
+    uint8_t* const csc = chi + lds.hi;
     // its piece s at place s ^ (token / 4) % 4: the 16 tokens of a read stand in different banks
-    uint8_t* const cxv = smem + lds.x;
+    uint8_t* const cxv = csc + lds.scale;
     auto x_place = [&](const int g, const int s) { return reinterpret_cast<uint4*>(cxv + (((2 * g + kh) << rs) + trow) * 64) + (s ^ ((trow >> 2) & 3)); };
     const bool first = blockIdx.x == 0;
     const Buffers B = buffers_of<SRC>(nullptr, nullptr, a.w0, (const uint8_t*)a.scales, N, K);
@@ -648,7 +650,7 @@ hipError_t launch_fused_src(FusedArgs a, hipStream_t stream) {
     const unsigned M = a.M;
     auto go = [&](auto kern, unsigned ni, bool spread, int rs) {
         a.rs = (uint8_t)rs;
-        hipLaunchKernelGGL(kern, dim3(a.nblocks / ni, (M + (1u << rs) - 1) >> rs), dim3(64 * WV), fused_lds((int)ni, a.K, a.r != 0, spread, rs).end, stream, a);
+        hipLaunchKernelGGL(kern, dim3(a.nblocks / ni, (M + (1u << rs) - 1) >> rs), dim3(64 * WV), fused_lds((int)ni, a.K, a.r != 0, spread, rs).end(), stream, a);
     };
     if (small_fused(M, a.nblocks * 32, a.K, a.r, SRC == SMALL_MXFP4) == FUSED_SPREAD) {
         go(fused_layer_kernel<SRC, 1, true>, 1, true, fused_spread(M));

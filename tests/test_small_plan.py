@@ -29,9 +29,10 @@ int main(int n, char** v) {
                     const bool spread = kind == FUSED_SPREAD;
                     for (int ni = 1; ni <= (spread ? 1 : 2); ++ni) {
                         const FusedLds a = fused_lds(ni, K, r != 0, spread, spread ? fused_spread(M) : 5);
-                        most = a.end > most ? a.end : most;
-                        askew += a.hpart % 16 || a.h % 16 || a.il % 16 || a.x % 16 || a.lo % 16 || a.hi % 8 || a.scale % 4;
-                        askew += !((r == 0 ? a.hpart == a.il : a.hpart < a.h && a.h < a.il) && a.il < a.x && a.x <= a.lo && a.lo <= a.hi && a.hi <= a.scale && a.scale <= a.end);
+                        most = a.end() > most ? a.end() : most;
+                        const unsigned h = a.tiles + a.hpart, il = h + a.h, lo = il + a.il, hi = lo + a.lo, scale = hi + a.hi, x = scale + a.scale;
+                        askew += a.tiles % 16 || h % 16 || il % 16 || lo % 16 || hi % 8 || scale % 4 || x % 16;
+                        if (r) askew += a.hpart != FUSED_HPART * 4 || a.h != FUSED_H * 4;
                     }
                 }
     printf("%u %u\\n", most, askew);
