@@ -266,8 +266,9 @@ int svdq_debug_gelu(const void* x_bf16, int64_t n, void* out_bf16, void* stream)
  *   scratch         svdq_layer_scratch_bytes(layer, M) bytes, 16-byte aligned, or NULL (slower with few tokens)
  *   staging         svdq_layer_staging_bytes(layer, M) bytes, 16-byte aligned: room for the expanded weights of one
  *                   GEMM (0 bytes if they are resident or M is small: NULL then), and for SVDQ_FMT_INT4, which runs as
- *                   E3M2 fields with many tokens (same codes and scales), for the activations' fields.  (That format also takes
- *                   NULL with up to two 64 x 64 tiles of y per CU, and is slower then.)  Holds nothing between calls
+ *                   E3M2 fields with many tokens (same codes and scales), for the activations' fields.  Holds nothing between
+ *                   calls.  With up to 480 tiles of y of 64 x 64, N >= 4096 and K >= 2048 it may be NULL all the same (on average 5 % slower),
+ *                   and svdq_layer_gemm uses none
  *   y               out [M, ldy] bf16; may share memory with x, and with nothing else
  * svdq_layer_gemm: the second half, from activations quantised by the format's own call.
  */

@@ -540,7 +540,8 @@ class W4A4Linear:
     weights (quantize() and gemm() on 4-bit activations and the int8 matrix cores; forward() on the FP6 ones, with the
     same codes and scales), "mxfp4" the MXFP4 format (qw then holds E2M1 codes and sw [K/32, N] E8M0 bytes).
     resident "w4" (default, container "e3m2" only) keeps the canonical 4-bit weights (qw, sw) and expands them into a
-    staging buffer shared by all such layers of the device right before a GEMM of many tokens (calls on one stream only);
+    staging buffer shared by all such layers of the device right before a GEMM of many tokens (calls on one stream only;
+    where weights could also be expanded in registers the memory is taken for the call alone, so that any streams do);
     "packed" keeps the container's own packed form (7 - 8 bits per weight for the int4 containers), and forward() of the
     nibble container takes the memory that it expands weights and codes into for the call alone, from torch's allocator.
     buffers() holds, after quantize() as after forward(), what the container's quantise pass wrote."""
@@ -615,9 +616,12 @@ class W4A4Linear:
             scratch = torch.empty(n, dtype=torch.uint8, device=device) if n else None
             # Room for expanded weights: the canonical form's is shared between layers (and reserved here, though few tokens
             # expand nothing).  The nibble container's is taken for each call: its layers may run on several streams at
-            # once, and kept it would be as much again as the packed weights, in every layer.
-            staging, shared = lib.svdq_layer_staging_bytes(ref, M), self.container == "e3m2" and self.w_packed is None
-            if shared:
+            # once, and kept it would be as much again as the packed weights, in every layer.  So is the canonical form's where
+            # svdq_layer_forward would do without.
+            canonical = self.container == "e3m2" and self.w_packed is None
+            staging, few = lib.svdq_layer_staging_bytes(ref, M), self.N >= 4096 and 2048 <= K <= 16384 and -(-M // 64) * -(-self.N // 64) <= 480
+            shared = canonical and not few
+            if canonical:
                 _staging_buffer(packed_weight_e3m2_bytes(self.N, K), device)
             work = self._work = _Work(codes, sx, h, scratch, staging, shared, y, (qx, sx, h, y),
                                       tuple(map(_addr, (codes, sx, h, scratch))), y.data_ptr(), key, layer)

@@ -421,15 +421,17 @@ size_t svdq_layer_scratch_bytes(const svdq_layer* L, int64_t M) {
     return s > 1 ? (size_t)s * (size_t)M * L->r * sizeof(float) : 0;
 }
 
+// Whether svdq_layer_forward takes the few-token GEMM.  With staging the int4 formats leave it where tiles on E3M2 fields win (the weights
+// expanded beside the quantise pass); without, they stay as long as it takes them.
+static bool small_forward(const svdq_layer* L, int64_t M, bool staged) {
+    return small_path(L, M) && !(staged && L->format != SVDQ_FMT_MXFP4 && svdq::small_shape(M, L->N, L->K, false, true) == 0);
+}
+
 // Nibble storage with more tokens than the few-token path takes runs as E3M2 fields as well: the FP6 instruction takes a
 // whole group at twice the int8 rate, and writing the activations as fields (56 instead of 36 bytes per token and group)
 // and expanding the weights cost less than that saves (M = 32760, K = N = 5120: 1.05 against 1.39 ms; M = 512: 39
 // against 44 us).  Same codes, same integer group sums, same scale pieces.  Fields and expanded weights live in the
-// caller's staging for the call only; codes and scales receive the layer's own 4-bit form beside them.  Without staging (staged =
-// false) it is what the few-token GEMM does not take.
-static bool as_fields(const svdq_layer* L, int64_t M, bool staged = true) {
-    return L->format == SVDQ_FMT_INT4 && (!small_path(L, M) || (staged && svdq::small_shape(M, L->N, L->K, false, true) == 0));
-}
+// caller's staging for the call only; codes and scales receive the layer's own 4-bit form beside them.
 static size_t staged_weight_bytes(const svdq_layer* L) { return (svdq::packed_weight_e3m2_bytes(L->N, L->K) + 255) & ~(size_t)255; }
 
 size_t svdq_layer_codes_bytes(const svdq_layer* L, int64_t M) {
@@ -439,17 +441,18 @@ size_t svdq_layer_codes_bytes(const svdq_layer* L, int64_t M) {
 
 size_t svdq_layer_staging_bytes(const svdq_layer* L, int64_t M) {
     if (layer_check(L, M) != SVDQ_OK) return 0;
-    if (as_fields(L, M)) return staged_weight_bytes(L) + svdq::act_e3m2_bytes(M, L->K);
-    return L->w_packed || small_path(L, M) ? 0 : svdq::packed_weight_e3m2_bytes(L->N, L->K);
+    if (small_forward(L, M, true)) return 0;
+    if (L->format == SVDQ_FMT_INT4) return staged_weight_bytes(L) + svdq::act_e3m2_bytes(M, L->K);
+    return L->w_packed ? 0 : svdq::packed_weight_e3m2_bytes(L->N, L->K);
 }
 
 static svdq::ExpandJob layer_expand_job(const svdq_layer* L, void* staging) {
     return L->w_packed ? svdq::expand_packed_job(L->w_packed, L->N, L->K, staging) : svdq::expand_canonical_job(L->qw, L->sw, L->N, staging);
 }
 
-// Whether the layer's GEMM adds up the partial h's of the quantise pass itself.
-static bool gemm_takes_slices(const svdq_layer* L, int64_t M, bool fields) {
-    return (!fields && small_path(L, M)) || ((fields || L->format == SVDQ_FMT_INT4_E3M2) && svdq::layer_e3m2_takes_slices(M, L->N, L->K));
+// Whether the layer's GEMM (small: the one for few tokens) adds up the partial h's of the quantise pass itself.
+static bool gemm_takes_slices(const svdq_layer* L, int64_t M, bool small, bool fields) {
+    return small || ((fields || L->format == SVDQ_FMT_INT4_E3M2) && svdq::layer_e3m2_takes_slices(M, L->N, L->K));
 }
 
 // The layer's weights as the kernels for few tokens take them.
@@ -465,12 +468,12 @@ static SmallWeights small_weights(const svdq_layer* L) {
 }
 
 // The GEMM on checked arguments.  h: `slices` partial h's, whose sum goes to hsum, where gemm_takes_slices; one otherwise.
-// fields: codes are E3M2 fields whatever the format.  expanded: staging holds the layer's weights already.
-static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool fields, bool expanded, const float* h, int slices, float* hsum,
+// small: the one for few tokens.  fields: codes are E3M2 fields whatever the format.  expanded: staging holds the layer's weights already.
+static int layer_gemm(const svdq_layer* L, const uint8_t* codes, const void* scales, bool small, bool fields, bool expanded, const float* h, int slices, float* hsum,
                       int64_t M, void* staging, void* y, int64_t ldy, hipStream_t stream) {
     const int N = L->N, K = L->K, r = L->r;
     const uint8_t* wp = (const uint8_t*)L->w_packed;
-    if (!fields && small_path(L, M)) {
+    if (small) {
         const SmallWeights w = small_weights(L);
         return hip_status(svdq::launch_small_gemm(w.source, codes, scales, w.w0, w.w1, h, slices, slices > 1 ? hsum : nullptr, L->L2_bf16, L->bias, M, 0, N, K, r, y, ldy, stream));
     }
@@ -503,10 +506,11 @@ int svdq_layer_gemm(const svdq_layer* L, const void* codes, const void* scales, 
                     void* staging, void* y, int64_t ldy, void* stream) {
     if (int e = layer_check(L, M)) return e;
     if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
-    if (!L->w_packed && !small_path(L, M) && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
+    const bool small = small_path(L, M);                   // with staging too: the expansion has no quantise pass to stand beside
+    if (!L->w_packed && !small && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
-    return layer_gemm(L, (const uint8_t*)codes, scales, false, false, h, 1, nullptr, M, staging, y, ldy, (hipStream_t)stream);
+    return layer_gemm(L, (const uint8_t*)codes, scales, small, false, false, h, 1, nullptr, M, staging, y, ldy, (hipStream_t)stream);
 }
 
 // Whether two bf16 matrices may share memory: the spans from their first elements to their last meet.
@@ -522,8 +526,9 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     if (int e = layer_out_check(L, codes, scales, h, y, ldy)) return e;
     if (!x_bf16 || !(rho > 0.0f) || !(rho <= 1.0f)) return SVDQ_ERR_INVALID_ARG;
     if (L->K > SVDQ_MAX_K || ldx < L->K || ldx % 8 || !aligned16(x_bf16) || !aligned16(scratch)) return SVDQ_ERR_UNSUPPORTED_SHAPE;
-    const bool fields = as_fields(L, M, staging && aligned16(staging));      // they follow the weights in staging
-    const bool expand = fields || (!L->w_packed && !small_path(L, M));       // the GEMM needs the weights in staging
+    const bool small = small_forward(L, M, staging && aligned16(staging));
+    const bool fields = L->format == SVDQ_FMT_INT4 && !small;                // they follow the weights in staging
+    const bool expand = fields || (!L->w_packed && !small);                  // the GEMM needs the weights in staging
     if (expand && (!staging || !aligned16(staging))) return SVDQ_ERR_INVALID_ARG;
     if (M == 0) return SVDQ_OK;
     if (int a = check_arch()) return a;
@@ -531,7 +536,7 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
     const int K = L->K, r = L->r;
     // A layer may be given its own output (K = N).  With two launches all of x has been read before y is written; in one, blocks of other
     // channel tiles still read x.
-    if (!spans_meet(x_bf16, ldx, K, y, ldy, L->N, M) && !fields && small_path(L, M) && svdq::small_fused(M, L->N, K, r, L->format == SVDQ_FMT_MXFP4) != svdq::FUSED_NONE) {
+    if (!spans_meet(x_bf16, ldx, K, y, ldy, L->N, M) && small && svdq::small_fused(M, L->N, K, r, L->format == SVDQ_FMT_MXFP4) != svdq::FUSED_NONE) {
         const SmallWeights w = small_weights(L);
         return hip_status(svdq::launch_fused_layer(w.source, x_bf16, ldx, L->inv_lambda, rho, gelu != 0, L->l1_packed, (uint8_t*)codes, scales, h,
                                                    w.w0, w.w1, L->L2_bf16, L->bias, M, L->N, K, r, y, ldy, stream));
@@ -551,13 +556,13 @@ int svdq_layer_forward(const svdq_layer* L, const void* x_bf16, int64_t ldx, flo
                                        expand ? layer_expand_job(L, staging) : svdq::ExpandJob{});
     if (e != hipSuccess) return hip_status(e);
     const float* hin = ho;
-    if (r != 0 && slices > 1 && !gemm_takes_slices(L, M, fields)) {
+    if (r != 0 && slices > 1 && !gemm_takes_slices(L, M, small, fields)) {
         e = svdq::launch_sum_slices(ho, slices, M, r, h, stream);
         if (e != hipSuccess) return hip_status(e);
         hin = h;
         slices = 1;
     }
-    return layer_gemm(L, act, scales, fields, expand, r ? hin : nullptr, r ? slices : 1, h, M, staging, y, ldy, stream);
+    return layer_gemm(L, act, scales, small, fields, expand, r ? hin : nullptr, r ? slices : 1, h, M, staging, y, ldy, stream);
 }
 
 size_t svdq_gptq_workspace_bytes(int N, int K) {

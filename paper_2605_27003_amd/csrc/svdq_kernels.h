@@ -86,9 +86,9 @@ constexpr int SMALL_SLICES = 8;                  // waves of a block = most part
 // blocks (K = 5120: N = 512, M = 2304, 30 against 35; N = 5120, M = 230, 24 against 26; M = 307, 400 blocks, 29 against 27),
 // with few channels and a long K up to 384 (K = 5120, N = 1024, M = 1536, 27 against 31; K = 512 even).
 // fields: the tiles find E3M2 fields with nothing to expand ahead of them, or with the layer's staging for it (packed E3M2 weights;
-// forward() of nibbles).  Where a row of tiles is 48 at most they then win from 161 tokens on with more than one block per CU
+// svdq_layer_forward of the others).  Where a row of tiles is 48 at most they then win from 161 tokens on with more than one block per CU
 // (packed, K = 11840, N = 6144, M = 178, 50 against 42; K = 7040, N = 4736, M = 205, 35 against 27; K = 3968, N = 4096, M = 384, even;
-// nibbles, K = 6336, N = 5248, M = 200, 46 against 36).  With more channels or fewer tokens the limit is as without them:
+// nibbles, K = 6336, N = 5248, M = 200, 46 against 36; canonical, K = 4736, N = 6016, M = 185, 36 against 31; K = 2240, N = 4224, M = 354, even).  With more channels or fewer tokens the limit is as without them:
 // nibbles lose there as often as they gain (N = 13824, M = 66, K = 2944, 28 against 32; N = 9088, M = 77, K = 5120, 36
 // against 30), packed weights would gain (N = 10112, M = 123, K = 11648, 58 against 44).
 inline int small_shape(int64_t M, int N, int K, bool mxfp4 = true, bool fields = false) {

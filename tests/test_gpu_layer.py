@@ -408,7 +408,7 @@ def test_nibble_layers_on_two_streams(svdq, M):
 
 
 def test_few_tokens_on_canonical_weights_on_two_streams(svdq):
-    """Layers whose weights are expanded in registers share no buffer either (300 tokens, 400 tiles of 64 x 64)."""
+    """Layers whose weights could be expanded in registers share no buffer either (300 tokens, 400 tiles of 64 x 64)."""
     M, K, N = 300, 5120, 5120
     lins = [_random_layer(svdq, "e3m2", K, N, 16, seed) for seed in (1, 2)]
     xs = [torch.randn(M, K, generator=torch.Generator(device="cuda").manual_seed(s), device="cuda").bfloat16() for s in (3, 4)]
@@ -424,25 +424,31 @@ def test_few_tokens_on_canonical_weights_on_two_streams(svdq):
         assert torch.equal(lin.buffers(M, w.device)[3], w)
 
 
+@pytest.mark.parametrize("container", ["e3m2", "nibble"])
 @pytest.mark.parametrize("M,K,N,r", [(161, 2112, 5504, 32), (300, 5120, 5120, 16), (448, 2048, 4096, 0)])
-def test_nibble_layer_without_staging(svdq, M, K, N, r):
-    """The C call takes NULL for the staging of a nibble layer of few tokens: codes and scales of forward(), bit for bit, and the
+def test_layer_without_staging(svdq, container, M, K, N, r):
+    """The C call takes NULL for the staging of a layer of few tokens: codes and scales of forward(), bit for bit, and the
     product on the few-token kernel (the bar of the layer)."""
     from paper_2605_27003_amd import binding
-    lin = _random_layer(svdq, "nibble", K, N, r)
+    lin = _random_layer(svdq, container, K, N, r)
     x = torch.randn(M, K, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda").bfloat16()
     want = lin.forward(x, 0.8).clone()
     codes, scales, h, y = lin.buffers(M, "cuda:0")
-    held = codes.clone(), scales.clone()
-    for t in (codes, scales, y):
+    if container == "e3m2":
+        codes, scales = codes.buf, None
+        read = lambda: unpack_act_e3m2_np(codes.cpu().numpy(), M, K)      # rows up to M, of a buffer with whole tiles
+    else:
+        read = lambda: (codes.cpu().numpy(), scales.cpu().numpy())
+    held = read()
+    for t in (codes, y) + (() if scales is None else (scales,)):
         t.zero_()
     scratch = torch.empty(8 * M * max(r, 1) * 4, dtype=torch.uint8, device="cuda")
     layer = lin._descriptor(r)
     for part in (scratch, None):
-        status = binding.load_library().svdq_layer_forward(layer.address, x.data_ptr(), K, 0.8, 0, M, codes.data_ptr(), scales.data_ptr(), binding._addr(h),
+        status = binding.load_library().svdq_layer_forward(layer.address, x.data_ptr(), K, 0.8, 0, M, codes.data_ptr(), binding._addr(scales), binding._addr(h),
                                                            binding._addr(part), None, y.data_ptr(), N, binding._raw_stream())
         assert status == 0
-        assert torch.equal(codes, held[0]) and torch.equal(scales, held[1])
+        assert all(np.array_equal(a, b) for a, b in zip(read(), held))
         assert rel_fro(y.double().cpu().numpy(), want.double().cpu().numpy()) <= 2e-3
 
 

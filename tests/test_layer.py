@@ -114,13 +114,24 @@ def test_stream_without_torchs_private_functions(monkeypatch):
     assert binding._raw_stream() == 1234
 
 
-@pytest.mark.parametrize("M,K,N", [(161, 2112, 5504), (175, 4672, 5632), (320, 5120, 5120), (384, 2048, 4096), (500, 2048, 4096)])
-def test_few_tokens_on_canonical_weights_need_no_staging(M, K, N):
-    """Up to 480 tiles of 64 x 64 the weights are expanded in registers: such layers have no memory in common, whatever streams
-    they run on, and a caller of the C functions passes none."""
-    f, lib = binding._FORMATS["e3m2"], binding.load_library()
-    at = lambda format, packed: lib.svdq_layer_staging_bytes(binding.ctypes.byref(binding._Layer(
-        format, N, K, 0, 256, None, None, None, 256 if packed else None, None if packed else 256, None if packed else 256)), M)
-    few = -(-M // 64) * (N // 64) <= 480
-    assert (at(f, False) == 0) == few and at(f, True) == 0
-    assert at(binding._FORMATS["nibble"], True) > 0          # forward() of nibbles runs as fields there
+@pytest.mark.parametrize("M,K,N", [(161, 2112, 5504), (175, 4672, 5632), (320, 5120, 5120), (384, 2048, 4096), (480, 2048, 4096), (481, 2048, 4096),
+                                   (384, 1984, 4096), (384, 2048, 3968)])
+def test_few_tokens_on_weights_to_expand(M, K, N):
+    """Up to 480 tiles of 64 x 64, N >= 4096 and K >= 2048 the weights can also be expanded in registers: the C functions take NULL for the
+    staging, and W4A4Linear, whose layers may run on several streams there, takes it for each call."""
+    lib, can = binding.load_library(), -(-M // 64) * (-(-N // 64)) <= 480 and N >= 4096 and K >= 2048
+    for container, packed in (("e3m2", False), ("nibble", True), ("e3m2", True)):
+        held = (256, None, None) if packed else (None, 256, 256)
+        layer = binding._Layer(binding._FORMATS[container], N, K, 0, 256, None, None, None, *held)
+        ref = binding.ctypes.byref(layer)
+        assert (lib.svdq_layer_staging_bytes(ref, M) > 0) == (container == "nibble" or not packed)
+        call = lambda staging: lib.svdq_layer_forward(ref, 256, K, 0.8, 0, M, 256, 256, None, None, staging, 256 << 30, N, None)
+        if not torch.cuda.is_available():            # refused for their arguments, or for want of a GPU
+            none = lib.svdq_layer_forward(ref, None, K, 0.8, 0, M, 256, 256, None, None, None, 256, N, None)
+            assert (call(None) == none) == (not can and (container, packed) != ("e3m2", True)) and call(256) != none
+            product = lib.svdq_layer_gemm(ref, 256, 256, None, M, None, 256, N, None)
+            assert (product == none) == (not can and not packed)
+    lin = _layer(K=K, N=N)
+    lin.buffers(M, "cpu")
+    assert lin._work.staging and lin._work.shared == (not can)
+    binding._staging.clear()
