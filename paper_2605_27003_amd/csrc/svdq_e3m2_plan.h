@@ -66,7 +66,8 @@ inline int e3m2_mid_groups(const E3m2Mid& m, int K) { return (K / 64 + m.teams -
 // 128 x 128 tiles on a chip that they fill take 9.3 + 3.1 k, and ahead of the others, which do not add up h's slices themselves, that
 // takes a launch (1.5 us) for up to 4096 tokens.  Layers, us:
 // M = 2048, K = N = 5120 94.2 -> 84.3, M = 1500, N = 3072 59.5 -> 50.8, M = 1024, K = 2048, N = 5120 36.3 -> 32.6;
-// 150 random layers 0.97 on average, single ones up to 1.04.  With less than 1.5 % to gain the others are taken: M = 1500, K = 1024, N = 2048 20.8
+// 270 random layers that take one 0.94 on average, 0.97 for K < 1024, where nothing was fitted; 12 of them lost more than 2 %, 1.07 at most and
+// 1.11 (M = 396, K = 896, N = 2816, 18.3 -> 20.3) below K = 1024.  With less than 1.5 % to gain the others are taken: M = 1500, K = 1024, N = 2048 20.8
 // against 22.5, and M = 512, K = N = 5120, whose GEMM alone takes 24.6 us here and 28.8 there but whose layer 37.9 and 38.9.
 inline int e3m2_mid_shape(int64_t M, int N, int K, bool split, int walkers, bool lowrank) {
     if (walkers != 8 * CUS_PER_XCD) return -1;
