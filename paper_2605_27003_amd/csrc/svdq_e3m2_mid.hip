@@ -11,7 +11,7 @@
 // instructions alone take): five operands of 2 KB are read for six tiles.  With four teams the transfers weigh more than the reads
 // (12.5 KB for twelve tiles of a CU), and a tile's start and end, 8 us, are a third of M = 512.  Counters, one, two, four and eight teams
 // (K = 5120; M = 2048 and 1024, N = 5120; M = 2048, N = 1024; M = 384, N = 3072): matrix pipe 37, 31, 19, 13 % busy, vector issue 31, 27,
-// 23, 16 % of wave-time, waits 55, 59, 61, 70 %, HBM 2.9, 4.5, 1.9, 1.5 TB/s.
+// 23, 16 % of wave-time, waits 55, 59, 60, 70 %, HBM 2.8, 4.3, 1.8, 1.5 TB/s.
 // A last tile may stand over the end of N: it re-reads the last 32 channels and stores nothing of them.
 // The group counts of the teams differ by one at most: a team with fewer multiplies the group before its own by zero scales.
 #include "svdq_dev.h"
